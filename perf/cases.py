@@ -255,7 +255,8 @@ def _prepare_gcn(c, rand):
              ws=_workspace(pk.gnn_gcn_workspace_bytes(g, fin, fout)))
     if c["edge_weights"]:       # averages with random weights: uniform in (0, 2 / in-degree)
         row = torch.repeat_interleave(2 / deg, g.indptr.diff())
-        s["ew"] = pk.EdgeWeights(g, rand.uniform(g.nnz) * row)
+        s["ew_values"] = rand.uniform(g.nnz) * row
+        s["ew"] = pk.EdgeWeights(g, s["ew_values"])
     else:                       # symmetric normalisation
         out_deg = torch.bincount(g.indices, minlength=n).clamp_(min=1).float()
         s.update(c_src=out_deg.rsqrt(), c_dst=deg.rsqrt())
@@ -451,3 +452,203 @@ def tolerance(case):
     if op in ("edgeconv", "ec2"):
         return {"rel": 1.3e-3, "max": 0.25, "differ": 1e-4}
     return {"rel": 3e-6, "max": 5e-5}
+
+
+# ------------------------------------------------------------------------------------------------
+# the same outputs in 64 bits, with plain torch
+# ------------------------------------------------------------------------------------------------
+def exact(case, seed):
+    s = prepare(case, seed)
+    return {"gat": _exact_gat, "gat2": _exact_gat2, "gcn": _exact_gcn, "gmm": _exact_gmm, "monet": _exact_monet,
+            "edgeconv": _exact_edgeconv, "ec2": _exact_ec2}[case["op"]](s)
+
+
+class _Edges:
+    """The edges in both orders: by destination, and by source (`by_src` = their positions in the first order)."""
+
+    def __init__(self, indptr, indices):
+        self.n = indptr.numel() - 1
+        self.src = indices.long()
+        self.ptr = indptr.long()
+        self.dst = torch.repeat_interleave(torch.arange(self.n, device="cuda"), self.ptr.diff())
+        self.by_src = self.src.sort(stable=True).indices
+        self.ptr_t = torch.zeros(self.n + 1, dtype=torch.long, device="cuda")
+        self.ptr_t[1:] = torch.bincount(self.src, minlength=self.n).cumsum(0)
+
+    def chunks(self, ptr, width):
+        """(first row, end row, first edge, end edge) of runs of whole rows, about 2 GB of 64-bit rows each."""
+        most, host, r = max(1, (1 << 28) // width), ptr.cpu(), 0
+        while r < self.n:
+            end = max(r + 1, int(torch.searchsorted(host, host[r] + most, right=True)) - 1)
+            end = min(end, self.n)
+            yield r, end, int(host[r]), int(host[end])
+            r = end
+
+
+class _WeightedSum(torch.autograd.Function):
+    """out[v, h, :] = sum over the in-edges e of v of w[e, h] z[src e, h, :], a run of rows at a time."""
+
+    @staticmethod
+    def forward(ctx, edges, w, z):
+        ctx.edges = edges
+        ctx.save_for_backward(w, z)
+        return _WeightedSum.rows(edges, edges.ptr, edges.src, w, z)
+
+    @staticmethod
+    def rows(edges, ptr, col, w, z, perm=None):
+        out = torch.empty_like(z)
+        for r, end, a, b in edges.chunks(ptr, z[0].numel()):
+            at = slice(a, b) if perm is None else perm[a:b]
+            terms = z[col[at]].mul_(w[at].unsqueeze(-1)).view(b - a, -1)
+            out[r:end] = torch.segment_reduce(terms, "sum", lengths=ptr[r:end + 1].diff(), axis=0,
+                                              initial=0).view(end - r, *z.shape[1:])
+        return out
+
+    @staticmethod
+    def backward(ctx, gout):
+        edges, (w, z) = ctx.edges, ctx.saved_tensors
+        gw = gz = None
+        if ctx.needs_input_grad[1]:
+            gw = torch.empty_like(w)
+            for _, _, a, b in edges.chunks(edges.ptr, z[0].numel()):
+                gw[a:b] = gout[edges.dst[a:b]].mul_(z[edges.src[a:b]]).sum(-1)
+        if ctx.needs_input_grad[2]:
+            gz = _WeightedSum.rows(edges, edges.ptr_t, edges.dst, w, gout.contiguous(), edges.by_src)
+        return None, gw, gz
+
+
+def _wide(*tensors):
+    return [t.double().requires_grad_() for t in tensors]
+
+
+def _gat_layer(edges, x, w, a_l, a_r):
+    """z, el, er, m, d, out, t, sg."""
+    h, f = a_l.shape
+    z = (x @ w).view(-1, h, f)
+    el, er = (z * a_l).sum(-1), (z * a_r).sum(-1)
+    raw = el.index_select(0, edges.src) + er.index_select(0, edges.dst)
+    score = torch.nn.functional.leaky_relu(raw, SLOPE)
+    with torch.no_grad():
+        m = torch.segment_reduce(score, "max", lengths=edges.ptr.diff(), axis=0)
+    p = (score - m.index_select(0, edges.dst)).exp()
+    one = torch.ones_like(z[..., :1])
+    d = _WeightedSum.apply(edges, p, one)
+    out = _WeightedSum.apply(edges, p, z) / d
+    with torch.no_grad():
+        p2 = torch.where(raw > 0, p, SLOPE * p)
+        t, sg = (_WeightedSum.apply(edges, p2, v) / d for v in (z, one))
+    return [v.flatten(1) for v in (z, el, er, m, d, out, t, sg)]
+
+
+def _outputs(names, values):
+    return {k: v.detach() for k, v in zip(names, values)}
+
+
+def _exact_gat(s):
+    c, edges = s["c"], _Edges(s["g"].indptr, s["g"].indices)
+    names = ("z", "el", "er", "m", "d", "out", "t", "sg")
+    ins = _wide(s["x"], s["w"], s["a_l"], s["a_r"])
+    if not c["train"]:
+        with torch.no_grad():
+            return _outputs(names[:6], _gat_layer(edges, *ins))
+    res = _gat_layer(edges, *ins)
+    grads = torch.autograd.grad(res[5], ins, s["gout"].double())
+    return _outputs(names + ("gx", "gw", "ga_l", "ga_r"), res + list(grads))
+
+
+def _step_exact(model, layers, x, act):
+    """Loss, logits, updated parameters and gradients of one step of a TwoLayerStep."""
+    params = _wide(*(p for p, _ in model.parameters()))
+    b1, b2, per = params[0], params[1], (len(params) - 2) // 2
+    a1 = act(layers[0](x.double(), *params[2:2 + per]) + b1)
+    logits = layers[1](a1, *params[2 + per:]) + b2
+    on = (model.labels >= 0) & (model.labels < model.c)
+    loss = torch.nn.functional.cross_entropy(logits[on], model.labels[on].long(), reduction="sum") / model.n_labelled
+    grads = torch.autograd.grad(loss, params)
+    return {"loss": loss.detach().view(1), "logits": logits.detach(),
+            "params": [(p - LR * q).detach() for p, q in zip(params, grads)], "grads": list(grads)}
+
+
+def _exact_gat2(s):
+    model = s["model"]
+    edges = _Edges(model.l1.g.indptr, model.l1.g.indices)
+
+    def layer(x, w, a_l, a_r):
+        return _gat_layer(edges, x, w, a_l, a_r)[5]
+    return _step_exact(model, (layer, layer), s["x"], torch.nn.functional.elu)
+
+
+def _exact_gcn(s):
+    edges = _Edges(s["g"].indptr, s["g"].indices)
+    x, w = _wide(s["x"], s["w"])
+    if s["c"]["edge_weights"]:
+        zs = x @ w
+        out = _WeightedSum.apply(edges, s["ew_values"].double().unsqueeze(-1), zs.unsqueeze(1)).flatten(1)
+    else:
+        zs = s["c_src"].double().unsqueeze(-1) * (x @ w)
+        one = torch.ones(edges.src.numel(), 1, dtype=torch.float64, device="cuda")
+        out = s["c_dst"].double().unsqueeze(-1) * _WeightedSum.apply(edges, one, zs.unsqueeze(1)).flatten(1)
+    return _outputs(("zs", "out", "gx", "gw"), (zs, out, *torch.autograd.grad(out, (x, w), s["gout"].double())))
+
+
+def _mixture(edges, x, w_fc, pseudo, mu, inv_sigma):
+    """hk, out of a Gaussian mixture layer; pseudo is [edges, r]."""
+    k = mu.shape[0]
+    hk = x @ w_fc
+    q = (pseudo.unsqueeze(1) - mu) * inv_sigma
+    weights = (-0.5 * q.square().sum(-1)).exp()
+    return hk, _WeightedSum.apply(edges, weights, hk.view(hk.shape[0], k, -1)).mean(1)
+
+
+def _exact_gmm(s):
+    edges = _Edges(s["g"].indptr, s["g"].indices)
+    ins, cc = _wide(s["x"], s["w_fc"], s["mu"], s["inv_sigma"]), s["cc"].double()
+    _, out = _mixture(edges, *ins[:2], torch.stack((cc[edges.src], cc[edges.dst]), 1), *ins[2:])
+    grads = torch.autograd.grad(out, ins, s["gout"].double())
+    return _outputs(("out", "gx", "gw_fc", "gmu", "gis"), (out, *grads))
+
+
+def _exact_monet(s):
+    edges = _Edges(s["g"].indptr, s["g"].indices)
+    ins = _wide(s["x"], s["w_fc"], s["mu"], s["inv_sigma"], s["proj_w"], s["proj_b"])
+    cc = s["cc"].double()
+    pair = torch.stack((cc[edges.src], cc[edges.dst]), 1)
+    hk, out = _mixture(edges, *ins[:2], (pair @ ins[4].T + ins[5]).tanh(), *ins[2:4])
+    grads = torch.autograd.grad(out, ins, s["gout"].double())
+    return _outputs(("hk", "out", "gx", "gw_fc", "gmu", "gis", "gproj_w", "gproj_b"), (hk, out, *grads))
+
+
+def _neighbours(coords, c):
+    """[n, k] nearest points of the same cloud.  The choice is defined on 32-bit distances, each step rounded."""
+    pts = coords.view(c["clouds"], c["points"], -1)
+    d2 = None
+    for i in range(pts.shape[2]):
+        sq = (pts[:, :, None, i] - pts[:, None, :, i]).square()
+        d2 = sq if d2 is None else d2 + sq
+    near = d2.sort(dim=-1, stable=True).indices[..., :c["k"]].sort(dim=-1).values
+    first = torch.arange(c["clouds"], device="cuda").mul_(c["points"]).view(-1, 1, 1)
+    return (near + first).view(-1, c["k"])
+
+
+def _edgeconv_layer(near, x, theta, phi):
+    """pq, out, position of the winner."""
+    pq = torch.cat((x @ theta, x @ (phi - theta)), 1)
+    p, q = pq.chunk(2, 1)
+    best, at = p[near].max(1)
+    return pq, best + q, at
+
+
+def _exact_edgeconv(s):
+    near = s["g"].indices.long().view(s["g"].n, -1)
+    ins = _wide(s["x"], s["theta"], s["phi"])
+    pq, out, _ = _edgeconv_layer(near, *ins)
+    grads = torch.autograd.grad(out, ins, s["gout"].double())
+    return dict(_outputs(("pq", "out"), (pq, out)), argmax=None, **_outputs(("gx", "gtheta", "gphi"), grads))
+
+
+def _exact_ec2(s):
+    near = _neighbours(s["coords"], s["c"])
+
+    def layer(x, theta, phi):
+        return _edgeconv_layer(near, x, theta, phi)[1]
+    return _step_exact(s["model"], (layer, layer), s["coords"], lambda v: torch.nn.functional.leaky_relu(v, 0.2))
