@@ -1,31 +1,45 @@
-// fp32 dense products on the MFMA matrix cores (v_mfma_f32_32x32x2_f32): the
-// ExpensiveApply projections that the reorganization moves onto vertices
-// (Sec. 4) and their two backward products (App. B, "Apply").
+// fp32 dense products on the MFMA matrix cores: the ExpensiveApply projections that the
+// reorganization moves onto vertices (Sec. 4) and their two backward products (App. B, "Apply").
 //
-// Tiling: a 256-thread workgroup (4 wavefronts, 2 x 2) owns a 128 x BN tile of
-// C; each wavefront owns 64 x BN/2 of it as 2 x (BN/64) MFMA 32x32 tiles held in
-// accumulators.  K advances 16 at a time through LDS; both operands sit in LDS
-// k-major ([k][m] and [k][n]) so every MFMA operand read is one conflict-free
-// ds_read_b32 with consecutive lanes on consecutive addresses, whatever the
-// operands' layout in HBM.  Global loads of the next K-slab are issued before the
-// MFMAs of the current one (register prefetch).
+// The fp32 MFMA runs at 1/16 of the bf16 rate, so every fp32 operand element is split into three
+// bf16 parts, x = h + m + l (8 + 8 + 8 significand bits: the whole fp32 significand), and a
+// product is the sum of the six partial products h h, h m, m h, m m, h l, l h with fp32
+// accumulators (v_mfma_f32_32x32x16_bf16).  What is left out (m l, l m, l l) is below 2^-26 of the
+// product, less than one fp32 rounding.  A tile whose result is not finite (an infinity or a NaN
+// among the operands, an operand so close to the largest float that h rounds to infinity, or an
+// overflowing sum) is computed again with the fp32 MFMA, so such values come out as fp32
+// arithmetic gives them.
+//
+// Tiling: a workgroup of WR x WC wavefronts owns a BM x BN tile of C.  K advances 16 at a time
+// through two LDS buffers: while the matrix cores work on one slab, the wavefronts split the next
+// one in registers and park it in the other buffer, and the loads of the slab after that travel.
+// The vector instructions of the split have to stand between the MFMAs of the same wavefront: a
+// wavefront that issues MFMAs back to back keeps the vector instructions of the others on its SIMD
+// waiting (measured: MFMA and FMA loops of two wavefronts take the sum of their times, interleaved
+// in one wavefront the larger of the two).  LDS is laid out [part][k / 8][row], so a wavefront's
+// operand read is two contiguous runs of 512 bytes whatever the operands' layout in HBM (an operand
+// stored k-major is transposed on the way, in registers).
+#include <type_traits>
+
 #include "common.h"
 
 namespace gnn {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int BM = 128;
-constexpr int BK = 16;
-constexpr int GEMM_THREADS = 256;
-constexpr int LDS_PAD = 4;  // row stride = 4 (mod 32) banks: transposing stores spread over banks
+constexpr int BK = 16;     // k per slab
+constexpr int kParts = 3;
 
 // Attention halves in the epilogue of the projection (Sec. 4, text after Eq. 1: the score splits
 // into a source half <a_l, z[u]> and a destination half <a_r, z[v]>, both per-vertex): el[m, h] =
 // sum_f a_l[h, f] C[m, h*F + f], er likewise, taken from the accumulators before they are stored,
 // so z is not read again.  A lane holds one column of a 32-column MFMA tile, so the sum over a
-// head is a butterfly over the lanes of the tile that belong to that head (F = 4, 8, 16, 32), or,
-// for F = 64 with two tiles per wavefront, over both tiles and all 32 lanes.
+// head is a butterfly over the lanes of the tile that belong to that head (F = 4, 8, 16, 32),
+// over all tiles and lanes of a wavefront (F = its columns), or, for a single head that one
+// workgroup covers, over its wavefronts as well (through LDS).
 // v + (v of the lane the DPP control pairs this lane with), one VALU operation
 template <int CTRL>
 __device__ __forceinline__ float dpp_add(float v) {
@@ -53,189 +67,255 @@ struct AttnEpilogue {
   int H, F;
 };
 
-// VEC: operands are fetched and parked in vectors, 2 floats of A and 4 floats of B per load along
-// whichever dimension is contiguous in memory (needs even lda, ldb % 4 == 0, matching alignment
-// and extents; the host checks).  A slab then costs a thread 6 global loads and 6 to 10 LDS
-// stores instead of 16 and 16 (measured on the Reddit-scale projection: +9 % throughput).
-template <int BN, bool A_KMAJOR, bool B_KCONTIG, bool EPI = false, bool VEC = false>
-__global__ __launch_bounds__(GEMM_THREADS, 3) void k_gemm_f32(
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {  // round to nearest even, both at once
+  const floatx2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+// One operand of a workgroup's tile: ROWS rows (of A) or columns (of B), fetched 16 k at a time.
+// A thread fetches kUnit consecutive k of one row.  Rows past the matrix are clamped to its last one
+// (their products land where nothing is stored); only the last, partial slab needs predicated loads.
+template <int ROWS, int THREADS, bool KCONTIG>
+struct Operand {
+  static constexpr int kUnit = ROWS * BK / THREADS;   // 2, 4 or 8
+  static constexpr int kPerRow = BK / kUnit;          // threads that fetch one row
+  static constexpr int kOctStride = ROWS + 4;         // padded: 8 lanes that store two octets of 4 rows meet different banks
+  static constexpr int kPartStride = BK / 8 * kOctStride;   // in 16-byte vectors, like kLds
+  static constexpr int kLds = kParts * kPartStride;
+  static_assert(kUnit == 2 || kUnit == 4 || kUnit == 8, "a thread stores 4, 8 or 16 bytes of each part");
+
+  float raw[2][kUnit];
+  uint32_t off;  // floats from the slab's base to the thread's first one
+  const float* base;
+  int64_t ld, step;
+
+  static __device__ __forceinline__ int row() { return KCONTIG ? threadIdx.x / kPerRow : threadIdx.x % ROWS; }
+  static __device__ __forceinline__ int k() { return kUnit * (KCONTIG ? threadIdx.x % kPerRow : threadIdx.x / ROWS); }
+
+  __device__ __forceinline__ void init(const float* p, int64_t ld_, int64_t row0, int64_t rows, int64_t k_begin) {
+    ld = ld_;
+    base = KCONTIG ? p + row0 * ld + k_begin : p + k_begin * ld + row0;
+    step = KCONTIG ? BK : BK * ld;
+    const int64_t r = row0 + row() < rows ? row() : rows - 1 - row0;
+    off = (uint32_t)(KCONTIG ? r * ld + k() : k() * ld + r);
+  }
+
+  // slab `s`, all of its k in the matrix
+  __device__ __forceinline__ void load(int set, int64_t s) {
+    const float* b = base + s * step;
+    if constexpr (KCONTIG) {
+      typedef float vec __attribute__((ext_vector_type(kUnit < 4 ? kUnit : 4), aligned(4)));
+      constexpr int V = kUnit < 4 ? kUnit : 4;
+#pragma unroll
+      for (int j = 0; j < kUnit; j += V) {
+        const vec v = *reinterpret_cast<const vec*>(b + off + j);
+#pragma unroll
+        for (int c = 0; c < V; ++c) raw[set][j + c] = v[c];
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < kUnit; ++j)  // uniform row address + 32-bit byte offset
+        raw[set][j] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b + j * ld) + 4u * off);
+    }
+  }
+
+  // the last slab, of which only `rem` < BK values of k exist
+  __device__ __forceinline__ void load_partial(int64_t s, int rem) {
+    const float* b = base + s * step;
+#pragma unroll
+    for (int j = 0; j < kUnit; ++j) raw[0][j] = k() + j < rem ? b[(int64_t)off + (KCONTIG ? j : j * ld)] : 0.f;
+  }
+
+  // sign * raw = h + m + l in bf16, to LDS
+  template <bool SIGNED>
+  __device__ __forceinline__ void store(int set, float sign, uint4* lds) const {
+    uint32_t w[kParts][kUnit / 2];
+#pragma unroll
+    for (int q = 0; q < kUnit / 2; ++q) {
+      float a = raw[set][2 * q], b = raw[set][2 * q + 1];
+      if (SIGNED) {
+        a *= sign;
+        b *= sign;
+      }
+#pragma unroll
+      for (int p = 0; p < kParts; ++p) {
+        w[p][q] = pack_bf16(a, b);
+        if (p + 1 < kParts) {  // exact: what the bf16 part left over
+          a -= __uint_as_float(w[p][q] << 16);
+          b -= __uint_as_float(w[p][q] & 0xffff0000u);
+        }
+      }
+    }
+    uint32_t* dst = reinterpret_cast<uint32_t*>(lds + k() / 8 * kOctStride + row()) + k() % 8 / 2;
+#pragma unroll
+    for (int p = 0; p < kParts; ++p, dst += 4 * kPartStride) {
+      if constexpr (kUnit == 8) *reinterpret_cast<uint4*>(dst) = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
+      else if constexpr (kUnit == 4) *reinterpret_cast<uint2*>(dst) = make_uint2(w[p][0], w[p][1]);
+      else *dst = w[p][0];
+    }
+  }
+
+  // part p of the MFMA operand of a 32-row tile: 8 k of row `r`
+  static __device__ __forceinline__ bf16x8 frag(const uint4* lds, int p, int oct, int r) {
+    return __builtin_bit_cast(bf16x8, lds[p * kPartStride + oct * kOctStride + r]);
+  }
+};
+
+template <int BM, int BN, int WR, int WC, bool A_KMAJOR, bool B_KCONTIG, bool EPI>
+__global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
     int64_t M, int N, int64_t K, const float* __restrict__ A, int64_t lda,
     const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc,
-    int64_t k_per_split, int64_t split_stride, AttnEpilogue epi) {
-  constexpr int TN = BN / 64;          // MFMA tiles per wavefront along n
-  constexpr int VA = VEC ? 2 : 1, VB = VEC ? 4 : 1;  // floats per load
-  constexpr int A_PER_T = BM * BK / GEMM_THREADS / VA;  // loads per thread and slab
-  constexpr int B_PER_T = BN * BK / GEMM_THREADS / VB;
-  __shared__ __align__(16) float As[BK][BM + LDS_PAD];
-  __shared__ __align__(16) float Bs[BK][BN + LDS_PAD];
+    int64_t k_per_split, int64_t split_stride, int tiles_m, int tiles_n, int splits, AttnEpilogue epi) {
+  constexpr int THREADS = 64 * WR * WC;  // WR x WC wavefronts
+  constexpr int WM = BM / WR, WN = BN / WC;
+  constexpr int TM = WM / 32, TN = WN / 32;  // MFMA tiles per wavefront
+  static_assert(TM >= 1 && TN >= 1, "a wavefront owns at least one MFMA tile");
+  using OpA = Operand<BM, THREADS, !A_KMAJOR>;
+  using OpB = Operand<BN, THREADS, B_KCONTIG>;
+  __shared__ uint4 lds[2][OpA::kLds + OpB::kLds];
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm0 = (wave >> 1) * 64;
-  const int wn0 = (wave & 1) * (BN / 2);
-  const int64_t m0 = (int64_t)blockIdx.x * BM;
-  const int n0 = blockIdx.y * BN;
-  const int64_t k_begin = (int64_t)blockIdx.z * k_per_split;
-  int64_t k_end = k_begin + k_per_split;
-  if (k_end > K) k_end = K;
+  // Workgroups go to the XCDs round-robin.  All tiles along n of a row of tiles (and all tiles of a
+  // k range of a split product) run on one XCD, one after the other: they read the same rows.
+  const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+  const int per = splits > 1 ? tiles_m * tiles_n : tiles_n;  // tiles that share operand rows
+  const int set = slot / per * kXcds + xcd, in_set = slot % per;
+  const int tm = splits > 1 ? in_set / tiles_n : set, tn = in_set % tiles_n, split = splits > 1 ? set : 0;
+  if (tm >= tiles_m || split >= splits) return;  // the grid is rounded up to whole XCD rounds
 
-  floatx16 acc[2][TN];
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int wm0 = wave / WC * WM, wn0 = wave % WC * WN;
+  const int64_t m0 = (int64_t)tm * BM;
+  const int n0 = tn * BN;
+  const int64_t k_begin = (int64_t)split * k_per_split;
+  const int64_t k_end = k_begin + k_per_split < K ? k_begin + k_per_split : K;
+  const int lrow = lane & 31, lk = lane >> 5;
+
+  floatx16 part[2][TM][TN];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[h][i][j][r] = 0.f;
+
+  OpA opa;
+  OpB opb;
+  opa.init(A, lda, m0, M, k_begin);
+  opb.init(B, ldb, n0, N, k_begin);
+
+  // The matrix core cuts its sums off (towards minus infinity) where fp32 arithmetic rounds, which
+  // would pull a long sum down.  So A's elements are stored with the sign (-1)^(row + slab): even slabs
+  // sum up in acc[0], odd ones, negated, in acc[1], and what both lose cancels in their difference; a
+  // product too short for that is at least pulled the other way in every other row.
+  const float row_sign = OpA::row() & 1 ? -1.f : 1.f;
+  auto store = [&](int raw_set, int parity, uint4* dst) {
+    opa.template store<true>(raw_set, parity ? -row_sign : row_sign, dst);
+    opb.template store<false>(raw_set, 1.f, dst + OpA::kLds);
+  };
+  auto multiply = [&](int parity, const uint4* src) {
+    constexpr int pa[6] = {1, 2, 0, 0, 1, 0}, pb[6] = {1, 0, 2, 1, 0, 0};  // smallest products first
+    bf16x8 a[kParts][TM], b[kParts][TN];
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[p][i] = OpA::frag(src, p, lk, wm0 + i * 32 + lrow);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[p][j] = OpB::frag(src + OpA::kLds, p, lk, wn0 + j * 32 + lrow);
+    }
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          part[parity][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pa[q]][i], b[pb[q]][j], part[parity][i][j], 0, 0, 0);
+  };
+
+  const int64_t slabs = (k_end - k_begin) / BK;  // whole ones
+  if (slabs > 0) {
+    opa.load(0, 0);
+    opb.load(0, 0);
+    const int64_t s1 = slabs > 1 ? 1 : 0;
+    opa.load(1, s1);
+    opb.load(1, s1);
+    store(0, 0, lds[0]);
+    // slab s, of parity P: its parts are in lds[P], slab s + 1 is in raw[P ^ 1] or on its way, and
+    // raw[P] is free for slab s + 2 (past the end: the last slab again, for nothing)
+    auto step = [&](auto parity, int64_t s) {
+      constexpr int P = decltype(parity)::value;
+      __syncthreads();  // lds[P] is complete, lds[P ^ 1] has been read
+      const int64_t s2 = s + 2 < slabs ? s + 2 : slabs - 1;
+      opa.load(P, s2);
+      opb.load(P, s2);
+      multiply(P, lds[P]);
+      store(P ^ 1, P ^ 1, lds[P ^ 1]);
+      // one MFMA, then the vector instructions that fit its time
+#pragma unroll
+      for (int q = 0; q < 6 * TM * TN; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
+      }
+    };
+    int64_t s = 0;
+    for (; s + 2 <= slabs; s += 2) {
+      step(std::integral_constant<int, 0>{}, s);
+      step(std::integral_constant<int, 1>{}, s + 1);
+    }
+    if (s < slabs) step(std::integral_constant<int, 0>{}, s);
+  }
+  if (const int rem = (int)(k_end - k_begin - slabs * BK); rem > 0) {
+    opa.load_partial(slabs, rem);
+    opb.load_partial(slabs, rem);
+    __syncthreads();  // the buffers have been read
+    store(0, 0, lds[0]);
+    __syncthreads();
+    multiply(0, lds[0]);
+  }
+  floatx16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int r = 0; r < 16; ++r)  // r has the row's parity
+        acc[i][j][r] = r & 1 ? part[1][i][j][r] - part[0][i][j][r] : part[0][i][j][r] - part[1][i][j][r];
 
-  float ra[A_PER_T][VA], rb[B_PER_T][VB];
-
-  // Load i of this thread covers V consecutive elements along the operand's contiguous dimension,
-  // at a fixed (row, k) of the slab.  Its address is a uniform base pointer, advanced once per
-  // slab, plus a 32-bit offset computed once; rows past M and columns past N are clamped to the
-  // last valid one (their products land in rows / columns of C that are never stored), so only
-  // the last, partial K-slab needs predicated loads.
-  // position of load i inside the slab: (k, x) of its first element; k-contiguous operands are
-  // vectorised along k, the others along x
-  auto pos_a = [&](int i, int& kk, int& mm) {
-    const int idx = tid + GEMM_THREADS * i;
-    if (A_KMAJOR) { mm = VA * (idx % (BM / VA)); kk = idx / (BM / VA); }
-    else { kk = VA * (idx % (BK / VA)); mm = idx / (BK / VA); }
-  };
-  auto pos_b = [&](int i, int& kk, int& nn) {
-    const int idx = tid + GEMM_THREADS * i;
-    if (B_KCONTIG) { kk = VB * (idx % (BK / VB)); nn = idx / (BK / VB); }
-    else { nn = VB * (idx % (BN / VB)); kk = idx / (BN / VB); }
-  };
-  uint32_t offa[A_PER_T], offb[B_PER_T];
-  int ka[A_PER_T], kb[B_PER_T];
+  // Not finite: the whole wavefront's tile again on the fp32 MFMA, operands straight from memory
+  bool bad = false;
 #pragma unroll
-  for (int i = 0; i < A_PER_T; ++i) {
-    int kk, mm;
-    pos_a(i, kk, mm);
-    // a vector along m starts at a multiple of VA and M is one too (host check): it is either
-    // whole inside the matrix or whole outside (then clamped as a whole)
-    const int64_t last = A_KMAJOR ? M - VA : M - 1;
-    const int64_t mrow = (m0 + mm <= last ? m0 + mm : last) - m0;
-    offa[i] = (uint32_t)(A_KMAJOR ? kk * lda + mrow : mrow * lda + kk);
-    ka[i] = kk;
-  }
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-  for (int i = 0; i < B_PER_T; ++i) {
-    int kk, nn;
-    pos_b(i, kk, nn);
-    const int last = B_KCONTIG ? N - 1 : N - VB;
-    const int64_t ncol = (n0 + nn <= last ? n0 + nn : last) - n0;
-    offb[i] = (uint32_t)(B_KCONTIG ? ncol * ldb + kk : kk * ldb + ncol);
-    kb[i] = kk;
-  }
-  const float* abase = A + (A_KMAJOR ? k_begin * lda + m0 : m0 * lda + k_begin);
-  const float* bbase = B + (B_KCONTIG ? (int64_t)n0 * ldb + k_begin : k_begin * ldb + n0);
-  const int64_t astep = A_KMAJOR ? BK * lda : BK, bstep = B_KCONTIG ? BK : BK * ldb;
-
-  typedef float vec_a __attribute__((ext_vector_type(VA)));
-  typedef float vec_b __attribute__((ext_vector_type(VB)));
-  auto load_slab = [&](int64_t k0) {
-    const int64_t rem = k_end - k0;
-    if (rem >= BK) {
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int i = 0; i < A_PER_T; ++i) {
-        if constexpr (VA == 1) ra[i][0] = abase[offa[i]];
-        else {
-          const vec_a v = *reinterpret_cast<const vec_a*>(abase + offa[i]);
+      for (int r = 0; r < 16; ++r) bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
+  if (__ballot(bad) != 0) {
 #pragma unroll
-          for (int c = 0; c < VA; ++c) ra[i][c] = v[c];
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        int64_t m = m0 + wm0 + i * 32 + lrow;
+        int64_t n = n0 + wn0 + j * 32 + lrow;
+        if (m >= M) m = M - 1;
+        if (n >= N) n = N - 1;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int64_t k0 = k_begin; k0 < k_end; k0 += 2) {
+          const int64_t k = k0 + lk;
+          const float av = k < k_end ? A[A_KMAJOR ? k * lda + m : m * lda + k] : 0.f;
+          const float bv = k < k_end ? B[B_KCONTIG ? n * ldb + k : k * ldb + n] : 0.f;
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
         }
       }
-#pragma unroll
-      for (int i = 0; i < B_PER_T; ++i) {
-        if constexpr (VB == 1) rb[i][0] = bbase[offb[i]];
-        else {
-          const vec_b v = *reinterpret_cast<const vec_b*>(bbase + offb[i]);
-#pragma unroll
-          for (int c = 0; c < VB; ++c) rb[i][c] = v[c];
-        }
-      }
-    } else {  // the last, partial slab: element by element
-#pragma unroll
-      for (int i = 0; i < A_PER_T; ++i)
-#pragma unroll
-        for (int c = 0; c < VA; ++c) {
-          const int kc = A_KMAJOR ? ka[i] : ka[i] + c;  // k of component c
-          ra[i][c] = kc < rem ? abase[offa[i] + c] : 0.f;
-        }
-#pragma unroll
-      for (int i = 0; i < B_PER_T; ++i)
-#pragma unroll
-        for (int c = 0; c < VB; ++c) {
-          const int kc = B_KCONTIG ? kb[i] + c : kb[i];
-          rb[i][c] = kc < rem ? bbase[offb[i] + c] : 0.f;
-        }
-    }
-    abase += astep;
-    bbase += bstep;
-  };
-  auto store_slab = [&]() {
-#pragma unroll
-    for (int i = 0; i < A_PER_T; ++i) {
-      int kk, mm;
-      pos_a(i, kk, mm);
-      if constexpr (A_KMAJOR && VA > 1) {
-        vec_a v;
-#pragma unroll
-        for (int c = 0; c < VA; ++c) v[c] = ra[i][c];
-        *reinterpret_cast<vec_a*>(&As[kk][mm]) = v;
-      } else {
-#pragma unroll
-        for (int c = 0; c < VA; ++c) As[A_KMAJOR ? kk : kk + c][A_KMAJOR ? mm + c : mm] = ra[i][c];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < B_PER_T; ++i) {
-      int kk, nn;
-      pos_b(i, kk, nn);
-      if constexpr (!B_KCONTIG && VB > 1) {
-        vec_b v;
-#pragma unroll
-        for (int c = 0; c < VB; ++c) v[c] = rb[i][c];
-        *reinterpret_cast<vec_b*>(&Bs[kk][nn]) = v;
-      } else {
-#pragma unroll
-        for (int c = 0; c < VB; ++c) Bs[B_KCONTIG ? kk + c : kk][B_KCONTIG ? nn : nn + c] = rb[i][c];
-      }
-    }
-  };
-
-  const int lrow = lane & 31;   // row (A) / column (B) inside an MFMA tile
-  const int lk = lane >> 5;     // which of the 2 k values of one MFMA step
-
-  if (k_begin < k_end) load_slab(k_begin);
-  for (int64_t k0 = k_begin; k0 < k_end; k0 += BK) {
-    store_slab();
-    __syncthreads();
-    if (k0 + BK < k_end) load_slab(k0 + BK);
-#pragma unroll
-    for (int ks = 0; ks < BK / 2; ++ks) {
-      const int kk = ks * 2 + lk;
-      float a[2], b[TN];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = As[kk][wm0 + i * 32 + lrow];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) b[j] = Bs[kk][wn0 + j * 32 + lrow];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
   }
 
   // accumulator layout of the 32x32 tile: register r of lane l holds
   // row 8*(r/4) + 4*(l/32) + r%4, column l%32
-  float* Cout = C + (int64_t)blockIdx.z * split_stride;
+  float* Cout = C + (int64_t)split * split_stride;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int n = n0 + wn0 + j * 32 + lrow;
@@ -250,25 +330,31 @@ __global__ __launch_bounds__(GEMM_THREADS, 3) void k_gemm_f32(
     const int F = epi.F, H = epi.H;
     float wl[TN], wr[TN];
     int hd[TN];           // head of the lane's column in tile j; -1: this lane stores nothing
-    const bool whole = F > 32;            // F == 32 * TN: the wavefront's columns are one head
-    const int seg = whole ? 32 : F;       // lanes of a tile that share a head
+    const bool whole = F > 32 || H == 1;       // all columns of the wavefront belong to one head
+    const bool across = H == 1 && WC > 1;      // and so do those of the wavefronts beside it
+    const int seg = whole ? 32 : F;            // lanes of a tile that share a head
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int n = n0 + wn0 + j * 32 + lrow;
       wl[j] = n < N ? epi.a_l[n] : 0.f;  // a_l, a_r are [H, F] = one value per column of C
       wr[j] = n < N ? epi.a_r[n] : 0.f;
-      hd[j] = ((lrow & (seg - 1)) == 0 && n < N) ? n / F : -1;
+      hd[j] = (lrow & (seg - 1)) == 0 && (n < N || across) ? (H == 1 ? 0 : n / F) : -1;
     }
+    float* sub = reinterpret_cast<float*>(lds);  // [WC][BM][2]
+    if (across) __syncthreads();               // the last slab has been read
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int64_t m = m0 + wm0 + i * 32 + (r >> 2) * 8 + lk * 4 + (r & 3);
+        const int ml = wm0 + i * 32 + (r >> 2) * 8 + lk * 4 + (r & 3);
+        const int64_t m = m0 + ml;
         float vl[TN], vr[TN];
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-          vl[j] = wl[j] * acc[i][j][r];
-          vr[j] = wr[j] * acc[i][j][r];
+          // columns past N hold products of a clamped column, possibly not finite: left out, not times 0
+          const bool in = n0 + wn0 + j * 32 + lrow < N;
+          vl[j] = in ? wl[j] * acc[i][j][r] : 0.f;
+          vr[j] = in ? wr[j] * acc[i][j][r] : 0.f;
         }
         if (whole) {
 #pragma unroll
@@ -280,12 +366,28 @@ __global__ __launch_bounds__(GEMM_THREADS, 3) void k_gemm_f32(
 #pragma unroll
         for (int j = 0; j < (whole ? 1 : TN); ++j) {
           const float sl = segment_sum(vl[j], seg), sr = segment_sum(vr[j], seg);
-          if (hd[j] >= 0 && m < M) {
+          if (across) {
+            if (lrow == 0) *reinterpret_cast<float2*>(sub + 2 * (wave % WC * BM + ml)) = make_float2(sl, sr);
+          } else if (hd[j] >= 0 && m < M) {
             epi.el[m * H + hd[j]] = sl;
             epi.er[m * H + hd[j]] = sr;
           }
         }
       }
+    if (across) {
+      __syncthreads();
+      for (int ml = threadIdx.x; ml < BM; ml += THREADS) {
+        if (m0 + ml >= M) break;
+        float sl = 0.f, sr = 0.f;
+#pragma unroll
+        for (int c = 0; c < WC; ++c) {
+          sl += sub[2 * (c * BM + ml)];
+          sr += sub[2 * (c * BM + ml) + 1];
+        }
+        epi.el[m0 + ml] = sl;
+        epi.er[m0 + ml] = sr;
+      }
+    }
   }
 }
 
@@ -393,60 +495,74 @@ gnn_status_t sum_partials_two_level(int64_t count, int parts, const float* parti
   return sum_partials(count, rows, scratch, out, s);
 }
 
-// 128 output columns per tile unless the last such tile would be at least half empty
+// ---- choice of the tile -----------------------------------------------------------------
+// Measured (x w, us; the fp32 MFMA on 128-row tiles before -> now): 232965 x 602 x 256 638 -> 470,
+// x 128 346 -> 262, x 64 202 -> 200, x 32 209 -> 180; 232965 x 1024 x 1024 3965 -> 2600; 20000 x 500 x 64
+// 30 -> 22; 65536 x 128 x 512 84 -> 65.  The wide products keep the matrix cores busy half of the time
+//, in 3/8 of the cycles that the fp32 MFMA would need; the narrow ones are bound
+// by the fetch of A, whose rows of 602 floats straddle cache lines (608 floats: 160 us at x 64).
+//
+// 128 output columns per tile unless the last such tile would be at least half empty; 32 for the
+// narrowest products
 static int gemm_tile_cols(int N) {
+  if (N <= 32) return 32;
   if (N <= 64) return 64;
   const int waste = (N + 127) / 128 * 128 - N;
   return waste >= 64 ? 64 : 128;
 }
 
+// 128 rows per tile; 64 where there are no more, or where 128 would leave a CU fewer than two tiles to
+// overlap (20000 x 500 x 64: 22 us against 28 us; 32768 x 64 x 128: 10.5 against 13.8; with 8 tiles per CU,
+// 65536 x 128 x 512, 128 rows win: 67 us against 79 us)
+static int gemm_tile_rows(int64_t M, int N, int bn, int split_k) {
+  if (bn < 64) return 128;
+  return M <= 64 || (split_k == 1 && cdiv(M, 128) * cdiv(N, bn) < 512) ? 64 : 128;
+}
+
+// Parts of K that different workgroups sum: what fills the chip once with the three workgroups a CU
+// holds, at least 128 of K each
 int gemm_pick_split_k(int64_t M, int N, int64_t K) {
-  const int bn = gemm_tile_cols(N);
-  int64_t tiles = cdiv(M, BM) * cdiv(N, bn);
-  if (tiles >= 512 || K < 256) return 1;
-  int64_t want = cdiv(1536, tiles);
-  int64_t max_by_k = K / 128;  // keep at least 128 of K (8 slabs) per split
+  const int64_t tiles = cdiv(M, 128) * cdiv(N, gemm_tile_cols(N));
+  if (tiles >= 128 || K < 256) return 1;
+  int64_t want = 768 / tiles;
+  const int64_t max_by_k = K / 128;
   if (want > max_by_k) want = max_by_k;
   if (want > 512) want = 512;
   return want < 1 ? 1 : (int)want;
 }
 
-// true when both operands can be fetched in vectors (see VEC of k_gemm_f32)
-static bool gemm_vec_ok(int64_t M, int N, const float* a, int64_t lda, bool a_kmajor, const float* b,
-                        int64_t ldb, bool b_kcontig) {
-  return lda % 2 == 0 && ldb % 4 == 0 && (reinterpret_cast<uintptr_t>(a) & 7u) == 0 &&
-         (reinterpret_cast<uintptr_t>(b) & 15u) == 0 && (!a_kmajor || M % 2 == 0) &&
-         (b_kcontig || N % 4 == 0);
+template <int BM, int BN, int WR, int WC, bool AK, bool BKC, bool EPI>
+static gnn_status_t launch(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
+                           float* c, int64_t ldc, int split_k, float* partials, const AttnEpilogue& epi,
+                           hipStream_t s) {
+  const int64_t tm = cdiv(M, BM), tn = cdiv(N, BN);
+  // workgroups: whole rounds over the XCDs of the sets of tiles that share rows
+  const int64_t sets = split_k > 1 ? split_k : tm, per = split_k > 1 ? tm * tn : tn;
+  const int64_t grid = cdiv(sets, kXcds) * kXcds * per;
+  GNN_REQUIRE(grid < (int64_t)INT32_MAX, GNN_ERR_UNSUPPORTED, "gemm_f32: grid too large");
+  const int64_t kps = split_k > 1 ? cdiv(cdiv(K, split_k), BK) * BK : K;
+  ProfScope p(EPI ? "gemm_f32_mfma_attn" : split_k > 1 ? "gemm_f32_mfma_splitk" : "gemm_f32_mfma", s);
+  float* out = split_k > 1 ? partials : c;
+  const int64_t ldo = split_k > 1 ? N : ldc;
+  k_gemm_f32<BM, BN, WR, WC, AK, BKC, EPI><<<(unsigned)grid, 64 * WR * WC, 0, s>>>(
+      M, N, K, a, lda, b, ldb, out, ldo, kps, M * (int64_t)N, (int)tm, (int)tn, split_k, epi);
+  GNN_LAUNCH_CHECK();
+  return GNN_OK;
 }
 
-template <int BN, bool AK, bool BKC, bool VEC>
-static gnn_status_t launch(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b,
-                           int64_t ldb, float* c, int64_t ldc, int split_k, float* partials,
-                           hipStream_t s) {
-  dim3 grid((unsigned)cdiv(M, BM), (unsigned)cdiv(N, BN), (unsigned)split_k);
-  const AttnEpilogue none{nullptr, nullptr, nullptr, nullptr, 0, 0};
-  if (split_k == 1) {
-    ProfScope p("gemm_f32_mfma", s);
-    k_gemm_f32<BN, AK, BKC, false, VEC><<<grid, GEMM_THREADS, 0, s>>>(M, N, K, a, lda, b, ldb, c, ldc, K, 0, none);
-    GNN_LAUNCH_CHECK();
-  } else {
-    int64_t kps = cdiv(cdiv(K, split_k), BK) * BK;
-    {
-      ProfScope p("gemm_f32_mfma_splitk", s);
-      k_gemm_f32<BN, AK, BKC, false, VEC><<<grid, GEMM_THREADS, 0, s>>>(M, N, K, a, lda, b, ldb, partials, N, kps,
-                                                            M * (int64_t)N, none);
-      GNN_LAUNCH_CHECK();
-    }
-    ProfScope p("gemm_sum_partials", s);
-    int64_t count = M * (int64_t)N;
-    if (ldc == N) {
-      GNN_TRY(sum_partials(count, split_k, partials, c, s));
-    } else {
-      set_error("gemm_f32: split-K needs a dense output (ldc == N)");
-      return GNN_ERR_INVALID_ARG;
-    }
-  }
-  return GNN_OK;
+template <bool AK, bool BKC, bool EPI>
+static gnn_status_t launch_tile(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
+                                float* c, int64_t ldc, int split_k, float* partials, const AttnEpilogue& epi,
+                                hipStream_t s) {
+  const int bn = gemm_tile_cols(N), bm = gemm_tile_rows(M, N, bn, split_k);
+#define GNN_GEMM_TILE(...) \
+  return launch<__VA_ARGS__, AK, BKC, EPI>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, epi, s)
+  if (bn == 32) GNN_GEMM_TILE(128, 32, 4, 1);
+  if (bn == 64 && bm == 64) GNN_GEMM_TILE(64, 64, 2, 2);
+  if (bn == 64) GNN_GEMM_TILE(128, 64, 2, 2);
+  if (bm == 64) GNN_GEMM_TILE(64, 128, 2, 2);
+  GNN_GEMM_TILE(128, 128, 2, 2);
+#undef GNN_GEMM_TILE
 }
 
 gnn_status_t gemm_f32(int64_t M, int N, int64_t K, const float* a, int64_t lda, bool a_kmajor,
@@ -456,28 +572,31 @@ gnn_status_t gemm_f32(int64_t M, int N, int64_t K, const float* a, int64_t lda, 
   GNN_REQUIRE(K > 0, GNN_ERR_INVALID_ARG, "gemm_f32: K must be positive");
   GNN_REQUIRE(lda > 0 && ldb > 0 && lda < (1 << 24) && ldb < (1 << 24), GNN_ERR_UNSUPPORTED,
               "gemm_f32: leading dimensions must be below 2^24 (32-bit tile offsets)");
-  GNN_REQUIRE(cdiv(M, BM) < (int64_t)INT32_MAX && split_k >= 1 && split_k <= 65535,
+  GNN_REQUIRE(cdiv(M, 32) < (int64_t)INT32_MAX && split_k >= 1 && split_k <= 65535,
               GNN_ERR_UNSUPPORTED, "gemm_f32: grid too large");
   GNN_REQUIRE(split_k == 1 || partials != nullptr, GNN_ERR_INVALID_ARG,
               "gemm_f32: split-K without a partials buffer");
-  const bool vec = gemm_vec_ok(M, N, a, lda, a_kmajor, b, ldb, b_kcontig);
-#define GNN_GEMM_CASE(BN_, AK_, BK_)                                                                      \
-  return vec ? launch<BN_, AK_, BK_, true>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, s)         \
-             : launch<BN_, AK_, BK_, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, s)
-  if (gemm_tile_cols(N) == 128) {
-    if (a_kmajor) { if (b_kcontig) GNN_GEMM_CASE(128, true, true); else GNN_GEMM_CASE(128, true, false); }
-    else          { if (b_kcontig) GNN_GEMM_CASE(128, false, true); else GNN_GEMM_CASE(128, false, false); }
+  GNN_REQUIRE(split_k == 1 || ldc == N, GNN_ERR_INVALID_ARG,
+              "gemm_f32: split-K needs a dense output (ldc == N)");
+  const AttnEpilogue none{nullptr, nullptr, nullptr, nullptr, 0, 0};
+  if (a_kmajor) {
+    if (b_kcontig) GNN_TRY((launch_tile<true, true, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
+    else GNN_TRY((launch_tile<true, false, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
   } else {
-    if (a_kmajor) { if (b_kcontig) GNN_GEMM_CASE(64, true, true); else GNN_GEMM_CASE(64, true, false); }
-    else          { if (b_kcontig) GNN_GEMM_CASE(64, false, true); else GNN_GEMM_CASE(64, false, false); }
+    if (b_kcontig) GNN_TRY((launch_tile<false, true, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
+    else GNN_TRY((launch_tile<false, false, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
   }
-#undef GNN_GEMM_CASE
+  if (split_k == 1) return GNN_OK;
+  ProfScope p("gemm_sum_partials", s);
+  return sum_partials(M * (int64_t)N, split_k, partials, c, s);
 }
 
-// z = x w with el, er from the epilogue; only for shapes gemm_attn_epilogue_ok() accepts
+// z = x w with el, er from the epilogue; only for shapes gemm_attn_epilogue_ok() accepts: heads inside
+// one 32-column MFMA tile, heads that are the 64 columns of a wavefront, or one head inside a tile of C
 bool gemm_attn_epilogue_ok(int heads, int f) {
   const int N = heads * f;
   if (f == 4 || f == 8 || f == 16 || f == 32) return true;
+  if (heads == 1) return N <= gemm_tile_cols(N);
   return f == 64 && gemm_tile_cols(N) == 128;
 }
 
@@ -487,22 +606,10 @@ gnn_status_t gemm_f32_attn(int64_t M, int heads, int f, int64_t K, const float* 
   const int N = heads * f;
   if (M <= 0) return GNN_OK;
   GNN_REQUIRE(gemm_attn_epilogue_ok(heads, f), GNN_ERR_UNSUPPORTED, "gemm_f32_attn: unsupported head width");
-  GNN_REQUIRE(K > 0 && K < (1 << 24) && N < (1 << 24) && cdiv(M, BM) < (int64_t)INT32_MAX, GNN_ERR_UNSUPPORTED,
+  GNN_REQUIRE(K > 0 && K < (1 << 24) && N < (1 << 24) && cdiv(M, 32) < (int64_t)INT32_MAX, GNN_ERR_UNSUPPORTED,
               "gemm_f32_attn: sizes out of range");
   const AttnEpilogue epi{a_l, a_r, el, er, heads, f};
-  ProfScope p("gemm_f32_mfma_attn", s);
-  const bool vec = gemm_vec_ok(M, N, x, K, false, w, N, false);
-  if (gemm_tile_cols(N) == 128) {
-    dim3 grid((unsigned)cdiv(M, BM), (unsigned)cdiv(N, 128), 1);
-    if (vec) k_gemm_f32<128, false, false, true, true><<<grid, GEMM_THREADS, 0, s>>>(M, N, K, x, K, w, N, z, N, K, 0, epi);
-    else k_gemm_f32<128, false, false, true, false><<<grid, GEMM_THREADS, 0, s>>>(M, N, K, x, K, w, N, z, N, K, 0, epi);
-  } else {
-    dim3 grid((unsigned)cdiv(M, BM), (unsigned)cdiv(N, 64), 1);
-    if (vec) k_gemm_f32<64, false, false, true, true><<<grid, GEMM_THREADS, 0, s>>>(M, N, K, x, K, w, N, z, N, K, 0, epi);
-    else k_gemm_f32<64, false, false, true, false><<<grid, GEMM_THREADS, 0, s>>>(M, N, K, x, K, w, N, z, N, K, 0, epi);
-  }
-  GNN_LAUNCH_CHECK();
-  return GNN_OK;
+  return launch_tile<false, false, true>(M, N, K, x, K, w, N, z, N, 1, nullptr, epi, s);
 }
 
 }  // namespace gnn

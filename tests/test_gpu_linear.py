@@ -19,3 +19,66 @@ def test_linear(n, fin, fout):
     pk.gnn_linear_fwd(dev(x), dev(w), y)
     torch.cuda.synchronize()
     assert_close("y", y.cpu().numpy(), x.astype(np.float64) @ w.astype(np.float64))
+
+
+def _assert_within_rounding(name, got, a, b):
+    """|got - a b| <= (6 ceil(K / 16) + 3) 2^-23 |a| |b| elementwise: each of the six partial products of 16 k is
+    added with a loss of at most one unit in the last place of a sum that |a| |b| bounds, and what the bf16 parts
+    leave out is below 2^-25 of it."""
+    a, b = a.astype(np.float64), b.astype(np.float64)
+    bound = (6 * -(-a.shape[1] // 16) + 3) * 2.0 ** -23 * (np.abs(a) @ np.abs(b))
+    worst = (np.abs(got - a @ b) / np.maximum(bound, 1e-300)).max()
+    print(f"{name}: worst error {worst:.3f} of the bound", flush=True)
+    assert worst <= 1.0
+
+
+@pytest.mark.parametrize("n,fin,fout", [(31, 15, 4), (64, 16, 32), (65, 17, 36), (129, 31, 64), (33000, 33, 68),
+                                        (66000, 48, 132), (66000, 600, 96), (33001, 130, 20)])
+def test_products_of_every_layout_and_tile(n, fin, fout):
+    """A GCN layer on a graph of loops alone is its three products: x w, x^T g and g w^T."""
+    import paper_2110_09524_amd as pk
+    import torch
+    from gpu_harness import dev, empty
+    print(f"products: {n} x {fin} x {fout}", flush=True)
+    rng = np.random.default_rng(n + fin + fout)
+    x, w, gout = (rng.standard_normal(s).astype(np.float32) for s in ((n, fin), (fin, fout), (n, fout)))
+    g = pk.Graph(dev(np.arange(n + 1, dtype=np.int32)), dev(np.arange(n, dtype=np.int32)))
+    one, zs, out, gx, gw = dev(np.ones(n, np.float32)), empty((n, fout)), empty((n, fout)), empty((n, fin)), empty((fin, fout))
+    ws = torch.empty(max(pk.gnn_gcn_workspace_bytes(g, fin, fout), 16), dtype=torch.uint8, device="cuda")
+    pk.gnn_gcn_fwd(g, fin, fout, dev(x), dev(w), one, one, zs, out)
+    pk.gnn_gcn_bwd(g, fin, fout, dev(x), dev(w), one, one, dev(gout), gx, gw, ws)
+    torch.cuda.synchronize()
+    _assert_within_rounding("x w", zs.cpu().numpy(), x, w)
+    _assert_within_rounding("g w^T", gx.cpu().numpy(), gout, w.T)
+    # the split product adds up to 512 parts: their sum loses at most one unit per part as well
+    got, xt = gw.cpu().numpy(), np.ascontiguousarray(x.T).astype(np.float64)
+    bound = (6 * -(-n // 16) + 515) * 2.0 ** -23 * (np.abs(xt) @ np.abs(gout.astype(np.float64)))
+    assert (np.abs(got - xt @ gout.astype(np.float64)) <= bound).all()
+
+
+@pytest.mark.parametrize("n,fin,fout", [(100, 40, 20), (200, 33, 60), (300, 70, 130)])
+def test_values_at_the_end_of_the_range(n, fin, fout):
+    """Infinities, NaN, the largest floats and tiny ones come out as fp32 arithmetic gives them."""
+    import paper_2110_09524_amd as pk
+    import torch
+    from gpu_harness import dev, empty
+    rng = np.random.default_rng(fin)
+    x = rng.standard_normal((n, fin)).astype(np.float32)
+    w = rng.standard_normal((fin, fout)).astype(np.float32)
+    w[1] = np.abs(w[1]) + 0.5
+    x[3, 1], x[40, 1], x[41, 2], x[42, 1] = np.inf, -np.inf, np.nan, np.finfo(np.float32).max
+    x[43] = 0
+    x[43, 1] = np.finfo(np.float32).max      # its bf16 rounding is an infinity, the product may be finite
+    w[1, 0] = 0.5
+    x[44] *= np.float32(2.0 ** -100)
+    y = empty((n, fout))
+    pk.gnn_linear_fwd(dev(x), dev(w), y)
+    torch.cuda.synchronize()
+    got = y.cpu().numpy()
+    with np.errstate(all="ignore"):
+        ref = (x.astype(np.float64) @ w.astype(np.float64)).astype(np.float32)
+    assert (got[3] == np.inf).all() and (got[40] == -np.inf).all() and np.isnan(got[41]).all()
+    assert got[43, 0] == np.float32(np.finfo(np.float32).max / 2)
+    assert np.array_equal(np.isfinite(got[42:44]), np.isfinite(ref[42:44]))
+    rest = np.setdiff1d(np.arange(n), (3, 40, 41, 42, 43))
+    _assert_within_rounding("the other rows", got[rest], x[rest], w)
