@@ -207,12 +207,122 @@ __global__ __launch_bounds__(kEcBlock) void k_edgeconv_bwd_src(
     }
 }
 
+// ---- a8 with byte codes ------------------------------------------------------------------
+// The kernel above reads 8 bytes per edge and column to find the one edge in deg(v) that won.  Where no
+// vertex has more than kEcCodeEmpty in-edges, a first pass writes the winner's position among the
+// in-edges of v as one byte, and the walk over the out-edges reads one byte per edge and column and
+// those 16 bytes of gout that hold a match.  The sums and their order are the same.
+constexpr int kEcCodeEmpty = 255;  // no in-edge
+
+template <int L, int NV>
+__global__ __launch_bounds__(kEcBlock) void k_edgeconv_codes(int32_t n_rows, const int32_t* __restrict__ indptr,
+                                                             const int32_t* __restrict__ argmax, int F,
+                                                             uint32_t* __restrict__ codes) {
+  const int li = threadIdx.x & (L - 1);
+  const int64_t v = (int64_t)blockIdx.x * (kEcBlock / L) + threadIdx.x / L;
+  if (v >= n_rows) return;
+  const int32_t beg = indptr[v];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int q = li + j * L;
+    if (4 * q >= F) continue;
+    const int4 a = *reinterpret_cast<const int4*>(argmax + v * F + 4 * q);
+    auto code = [&](int32_t e) { return (uint32_t)(e < 0 ? kEcCodeEmpty : e - beg) & 0xffu; };
+    codes[v * (F / 4) + q] = code(a.x) | code(a.y) << 8 | code(a.z) << 16 | code(a.w) << 24;
+  }
+}
+
+template <int L, int NV>
+__global__ __launch_bounds__(kEcBlock) void k_edgeconv_bwd_src_codes(
+    int32_t n_rows, const int32_t* __restrict__ order_t, const int32_t* __restrict__ indptr,
+    const int32_t* __restrict__ indptr_t, const int32_t* __restrict__ indices_t,
+    const int32_t* __restrict__ eid_t, const uint32_t* __restrict__ codes, const float* __restrict__ gout, int F,
+    float* __restrict__ dpq) {
+  constexpr int GPB = kEcBlock / L;
+  __shared__ int lds[GPB * 2 * L];
+  const int li = threadIdx.x & (L - 1);
+  const int grp = threadIdx.x / L;
+  const int64_t r = order_t ? (int64_t)blockIdx.x * GPB + grp : xcd_contiguous_row(blockIdx.x, gridDim.x, GPB, grp);
+  if (r >= n_rows) return;
+  int* l_v = lds + grp * 2 * L;
+  int* l_p = l_v + L;
+  const int32_t u = order_t ? order_t[r] : (int32_t)r;
+  const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
+
+  bool slot_ok[NV];
+  float4 acc[NV];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    slot_ok[j] = 4 * (li + j * L) < F;
+    acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  for (int32_t c0 = beg; c0 < end; c0 += L) {
+    const int32_t i = c0 + li;
+    const int32_t v = i < end ? indices_t[i] : 0;
+    l_v[li] = v;
+    l_p[li] = i < end ? eid_t[i] - indptr[v] : kEcCodeEmpty + 1;  // past the row's end: no code equals it
+    wave_lds_fence();
+    constexpr int U = L < 8 ? 4 : 8;
+    const int cnt = min(L, end - c0);
+    for (int t0 = 0; t0 < cnt; t0 += U) {
+      int vv[U];
+      uint32_t pp[U];
+#pragma unroll
+      for (int t = 0; t < U; ++t) {
+        vv[t] = l_v[t0 + t];
+        pp[t] = l_p[t0 + t];
+        if (L == 64) { vv[t] = __builtin_amdgcn_readfirstlane(vv[t]); pp[t] = __builtin_amdgcn_readfirstlane(pp[t]); }
+      }
+#pragma unroll
+      for (int j = 0; j < NV; ++j) {
+        if (!slot_ok[j]) continue;
+        uint32_t c[U];
+        float4 gg[U];
+#pragma unroll
+        for (int t = 0; t < U; ++t) c[t] = codes[(int64_t)vv[t] * (F / 4) + li + j * L];
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+          gg[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+          const uint32_t x = c[t] ^ pp[t] * 0x01010101u;  // a byte that matches becomes zero (256 * 0x01010101
+                                                          // has a bit above every byte but the lowest: kept apart)
+          if (pp[t] <= kEcCodeEmpty && ((x - 0x01010101u) & ~x & 0x80808080u) != 0)
+            gg[t] = ld4(gout + (int64_t)vv[t] * F + 4 * (li + j * L));
+        }
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+          acc[j].x += (c[t] & 0xffu) == pp[t] ? gg[t].x : 0.f;
+          acc[j].y += (c[t] >> 8 & 0xffu) == pp[t] ? gg[t].y : 0.f;
+          acc[j].z += (c[t] >> 16 & 0xffu) == pp[t] ? gg[t].z : 0.f;
+          acc[j].w += c[t] >> 24 == pp[t] ? gg[t].w : 0.f;
+        }
+      }
+    }
+    wave_lds_fence();
+  }
+  const bool constant = indptr[u] == indptr[u + 1];  // without in-edges out[u] does not depend on Q[u]
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+    if (slot_ok[j]) {
+      const int col = 4 * (li + j * L);
+      st4(dpq + (int64_t)u * 2 * F + col, acc[j]);
+      const float4 gq = ld4(gout + (int64_t)u * F + col);
+      st4(dpq + (int64_t)u * 2 * F + F + col, constant ? make_float4(0.f, 0.f, 0.f, 0.f) : gq);
+    }
+}
+
 // Degree order (heaviest rows first) balances skewed graphs; when the largest degree is within
 // a small factor of the mean it buys nothing and vertex order keeps neighbourhoods together.
 static bool near_uniform_degrees(const gnn_graph_t* g, int side) {
   if (config_get(kCfgForceSimple)) return false;
   const int64_t mean = g->n > 0 ? (g->nnz + g->n - 1) / g->n : 0;
   return (int64_t)g->max_degree[side] <= 4 * (mean > 1 ? mean : 1);
+}
+
+// The pass that writes the codes is one more launch: it pays from about 64 million (edge, column) pairs
+// (us, plain -> codes and their pass: 65 536 vertices x 40 neighbours x 256 columns 246 -> 188, x 128 140 ->
+// 109, x 64 68 -> 56; 32 768 x 20 x 64, 42 million: 20 -> 24)
+static bool ec_codes_pay(const gnn_graph_t* g, int F) {
+  return g->max_degree[0] <= kEcCodeEmpty && g->nnz * F >= (int64_t)1 << 26 && !config_get(kCfgForceSimple);
 }
 
 template <int L, int NV>
@@ -233,13 +343,26 @@ struct EcFwdLauncher {
 template <int L, int NV>
 struct EcBwdLauncher {
   static gnn_status_t run(const gnn_graph_t* g, const int32_t* argmax, const float* gout, int F,
-                          float* dpq, hipStream_t st) {
+                          uint32_t* codes, float* dpq, hipStream_t st) {
     constexpr int GPB = (kWave / L) * (kEcBlock / kWave);
-    ProfScope p("edgeconv_bwd_src", st);
     const bool by_id = near_uniform_degrees(g, 1);
     const unsigned grid = by_id ? xcd_contiguous_grid(g->n, GPB) : (unsigned)cdiv(g->n, GPB);
-    k_edgeconv_bwd_src<L, NV><<<grid, kEcBlock, 0, st>>>(g->n, by_id ? nullptr : g->order[1], g->indptr_t,
-                                                         g->indices_t, g->eid_t, argmax, gout, F, dpq);
+    const int32_t* order = by_id ? nullptr : g->order[1];
+    if (ec_codes_pay(g, F)) {
+      {
+        ProfScope p("edgeconv_codes", st);
+        k_edgeconv_codes<L, NV><<<(unsigned)cdiv(g->n, GPB), kEcBlock, 0, st>>>(g->n, g->indptr, argmax, F, codes);
+        GNN_LAUNCH_CHECK();
+      }
+      ProfScope p("edgeconv_bwd_src", st);
+      k_edgeconv_bwd_src_codes<L, NV><<<grid, kEcBlock, 0, st>>>(g->n, order, g->indptr, g->indptr_t, g->indices_t,
+                                                                 g->eid_t, codes, gout, F, dpq);
+      GNN_LAUNCH_CHECK();
+      return GNN_OK;
+    }
+    ProfScope p("edgeconv_bwd_src", st);
+    k_edgeconv_bwd_src<L, NV><<<grid, kEcBlock, 0, st>>>(g->n, order, g->indptr_t, g->indices_t, g->eid_t, argmax,
+                                                         gout, F, dpq);
     GNN_LAUNCH_CHECK();
     return GNN_OK;
   }
@@ -265,7 +388,7 @@ static gnn_status_t ec_dispatch(GroupShape gs, Args... args) {
 }
 
 struct EcWs {
-  size_t total, wcat, dpq, gcat, gemm;
+  size_t total, wcat, dpq, gcat, gemm, codes;
   int split_k;
 };
 
@@ -278,6 +401,7 @@ static EcWs ec_ws_layout(int64_t n, int fin, int fout) {
   w.gcat = take(sizeof(float) * 2 * (size_t)fin * fout);
   w.split_k = gemm_pick_split_k(fin, 2 * fout, n);
   w.gemm = take(w.split_k > 1 ? sizeof(float) * (size_t)w.split_k * fin * 2 * fout : 0);
+  w.codes = take((size_t)n * fout);
   w.total = off;
   return w;
 }
@@ -347,7 +471,8 @@ extern "C" gnn_status_t gnn_edgeconv_bwd(const gnn_graph_t* g, int fin, int fout
   float* part = reinterpret_cast<float*>(base + L.gemm);
   const int64_t n = g->n;
 
-  GNN_TRY(ec_dispatch<EcBwdLauncher>(pick_group(fout), g, argmax, gout, fout, dpq, st));
+  GNN_TRY(ec_dispatch<EcBwdLauncher>(pick_group(fout), g, argmax, gout, fout, reinterpret_cast<uint32_t*>(base + L.codes),
+                                     dpq, st));
   GNN_TRY(gemm_f32(fin, 2 * fout, n, x, fin, true, dpq, 2 * fout, false, gcat, 2 * fout, L.split_k, part, st));
   {
     ProfScope p("edgeconv_split_weight_grads", st);

@@ -103,3 +103,53 @@ def test_duplicate_edges_empty_rows_and_hub():
     assert set(res["argmax"][5].tolist()) <= {int(indptr[5]), int(indptr[5]) + 2}
     assert (res["argmax"][1] == -1).all() and (res["out"][1] == 0).all()
     check(c)
+
+
+@pytest.mark.parametrize("n,longest,fout", [(4200, 255, 64), (4200, 256, 64), (2100, 255, 132), (1100, 254, 260),
+                                            (700, 255, 516)])
+def test_backward_by_winner_codes(n, longest, fout):
+    """67 to 92 million (edge, column) pairs, so rows of up to 255 in-edges take the one-byte codes and one row of
+    256 the plain kernel; the reference scatters the upstream gradient to the winners of the forward call in fp64.
+    Bound: sums of at most n terms in a fixed order, then products of K = 2 fout terms, one unit each."""
+    import paper_2110_09524_amd as pk
+    import torch
+    from gpu_harness import dev, empty
+    print(f"edgeconv codes: {n} {longest} {fout}", flush=True)
+    rng = np.random.default_rng(n + longest + fout)
+    deg = np.full(n, 254)
+    deg[3], deg[n - 1] = longest, 0                 # an empty row as well
+    deg[10:20] = 1
+    indptr = np.concatenate(([0], np.cumsum(deg))).astype(np.int32)
+    indices = np.sort(rng.integers(0, n, size=indptr[-1])).astype(np.int32)
+    for v in range(n):                              # sources ascending inside a row, spread over all vertices
+        indices[indptr[v]:indptr[v + 1]] = np.sort(rng.choice(n, size=deg[v], replace=deg[v] > n))
+    fin = 8
+    c = synth(rng, indptr, indices, fin, fout)
+    g = pk.Graph(dev(indptr), dev(indices))
+    assert g.nnz * fout >= 1 << 26
+    x, theta, phi, gout = (dev(c[k]) for k in ("x", "theta", "phi", "gout"))
+    pq, out, argmax = empty((n, 2 * fout)), empty((n, fout)), torch.empty((n, fout), dtype=torch.int32, device="cuda")
+    ws = torch.empty(pk.gnn_edgeconv_workspace_bytes(g, fin, fout), dtype=torch.uint8, device="cuda")
+    pk.gnn_edgeconv_fwd(g, fin, fout, x, theta, phi, pq, out, argmax, ws)
+    gx, gtheta, gphi = empty((n, fin)), empty((fin, fout)), empty((fin, fout))
+    pk.gnn_edgeconv_bwd(g, fin, fout, x, theta, phi, argmax, gout, gx, gtheta, gphi, ws)
+    torch.cuda.synchronize()
+    arg, go = argmax.cpu().numpy(), c["gout"].astype(np.float64)
+    won = arg >= 0
+    assert (~won[n - 1]).all() and won[:n - 1].all()
+    dP = np.zeros((n, fout))
+    np.add.at(dP, (indices[arg[won]], np.nonzero(won)[1]), go[won])
+    dQ = np.where(won, go, 0.0)
+    mag = np.zeros((n, fout))
+    np.add.at(mag, (indices[arg[won]], np.nonzero(won)[1]), np.abs(go[won]))
+    th, ph, x64 = (c[k].astype(np.float64) for k in ("theta", "phi", "x"))
+    eps = 2.0 ** -23
+    ref = dP @ th.T + dQ @ (ph - th).T
+    bound = (2 * fout + n) * eps * (mag @ np.abs(th).T + np.abs(dQ) @ np.abs(ph - th).T)
+    assert (np.abs(gx.cpu().numpy() - ref) <= bound + 1e-30).all()
+    bound = (2 * n + 600) * eps * (np.abs(x64).T @ (mag + np.abs(dQ)))
+    assert (np.abs(gtheta.cpu().numpy() - x64.T @ (dP - dQ)) <= bound).all()
+    assert (np.abs(gphi.cpu().numpy() - x64.T @ dQ) <= bound).all()
+    # far inside these bounds: every single contribution went to its winner
+    assert np.abs(gx.cpu().numpy() - ref).max() <= 1e-4 * np.abs(ref).max()
+    g.close()
