@@ -52,6 +52,20 @@ def test_workload_graphs(name):
     _check(c["indptr"], c["indices"])
 
 
+@pytest.mark.parametrize("longest", [1, 63, 64, 65, 129, 2046, 2047, 2048, 2049])
+def test_out_rows_and_degrees_around_the_limits_of_the_sorts(longest):
+    """Out-rows of one wavefront and more; 2048 is the longest row that is placed and sorted by itself, degrees
+    up to 2047 are ordered by counting."""
+    rng = np.random.default_rng(longest)
+    n = max(2 * longest, 700)
+    pairs = [(u, v) for u, cnt in ((5, longest), (6, longest // 2), (7, 1)) for v in rng.permutation(n)[:cnt]]
+    pairs += [(int(u), int(v)) for u, v in rng.integers(8, n, size=(3 * n, 2))]
+    pairs += [(9, 9)] * min(longest, 3)
+    _check(*tiny_graph(n, pairs))
+    # the same graph the other way round: the long row is an in-row
+    _check(*tiny_graph(n, [(v, u) for u, v in pairs]))
+
+
 def test_malformed_graphs_are_rejected():
     import paper_2110_09524_amd as pk
     from gpu_harness import dev
