@@ -33,6 +33,21 @@ def test_matches_the_oracle_exactly(clouds, points, dim, k):
     assert (ix == rx).all()
 
 
+@pytest.mark.parametrize("points,dim,k", [(129, 3, 64), (129, 3, 65), (256, 2, 1), (257, 3, 64), (1000, 3, 63),
+                                          (1024, 2, 40), (1024, 5, 64), (2047, 3, 64)])
+def test_packed_search_against_the_oracle(points, dim, k):
+    """Up to 64 neighbours among more than 128 points, spread out and with most distances tied (the candidates
+    then overflow the packed list and the search goes over all of them)."""
+    rng = np.random.default_rng(points + dim + k)
+    spread = rng.random((2 * points, dim), dtype=np.float32)
+    tied = rng.integers(0, 3, size=(2 * points, dim)).astype(np.float32)
+    one_far = np.zeros((2 * points, dim), dtype=np.float32)
+    one_far[points // 2] = 7
+    for coords in (spread, tied, one_far):
+        _, ix = build(coords, 2, points, k)
+        assert (ix == ok.knn_graph(coords, 2, points, k)[1]).all()
+
+
 def test_ties_go_to_the_lower_index():
     # points on an integer grid: many exactly equal distances
     rng = np.random.default_rng(5)
