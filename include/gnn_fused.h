@@ -576,8 +576,8 @@ gnn_status_t gnn_sgd_update(int64_t count, float lr, const float* grad, float* p
  * [clouds*points, dim] fp32; vertex id = cloud * points + i.  For every point: the k
  * points of its own cloud with the smallest squared Euclidean distance, itself included,
  * ties towards the lower index.  The squared distance is accumulated in float32,
- * coordinate by coordinate in index order, each operation rounded on its own, so the
- * choice is reproducible bit for bit.  Output: CSR by destination, indptr [n+1]
+ * coordinate by coordinate in index order (the first square rounded, each further one
+ * added by a fused multiply-add), so the choice is reproducible bit for bit.  Output: CSR by destination, indptr [n+1]
  * (= i*k), indices [n*k] (sources ascending in a row), ready for gnn_graph_create.
  * Limits: k <= points <= 2048, n*k < 2^31.  Coordinates must not be NaN.
  * Errors: INVALID_ARG, UNSUPPORTED, HIP.

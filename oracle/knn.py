@@ -7,8 +7,11 @@ point itself included, ties broken towards the lower index; an edge runs from ea
 neighbour to the point.  The result is the CSR by destination with sources ascending.
 
 Floating point decides integers here, so the precision is part of the definition: the
-squared distance is accumulated in float32, coordinate by coordinate in index order,
-each step rounded ( ((d0*d0 + d1*d1) + d2*d2) + ... with d_i = a_i - b_i rounded first ).
+squared distance is accumulated in float32, coordinate by coordinate in index order, with
+d_i = a_i - b_i rounded first, d0*d0 rounded, and each further square added by one fused
+multiply-add, fma(d2, d2, fma(d1, d1, d0*d0)).  In float64 a square of floats is exact and the
+sum is rounded once more before it becomes a float32, which differs from the fused operation
+in about one of 2^29 sums.
 """
 import numpy as np
 
@@ -20,8 +23,8 @@ def squared_distances_f32(cloud):
     acc = np.zeros((P, P), dtype=np.float32)
     for i in range(D):
         diff = (c[:, None, i] - c[None, :, i]).astype(np.float32)
-        sq = (diff * diff).astype(np.float32)
-        acc = sq if i == 0 else (acc + sq).astype(np.float32)
+        wide = diff.astype(np.float64)
+        acc = (acc + wide * wide).astype(np.float32)      # the first sum starts at zero
     return acc
 
 

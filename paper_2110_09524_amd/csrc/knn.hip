@@ -6,8 +6,10 @@
 // Euclidean distance, itself included, ties towards the lower index; edges run from the
 // neighbours to the point, so the result is the CSR by destination with k sources per row,
 // ascending.  Floating point decides integers here, so the arithmetic is pinned down: the
-// squared distance is accumulated in float32, coordinate by coordinate in index order, every
-// subtraction, product and sum rounded on its own (no fused multiply-add).
+// squared distance is accumulated in float32, coordinate by coordinate in index order: every
+// subtraction is rounded, the first square is rounded, and each further square is added by one fused
+// multiply-add.  (Written out as an intrinsic: from a product and a sum the compiler makes a fused form
+// of its own choice, also out of __fmul_rn and __fadd_rn, and not the same one in every loop.)
 //
 // One wavefront per query point: lane l keeps the distance bits of candidates l, l+64, ... in
 // registers (non-negative floats order like unsigned integers).  The k-th smallest distance is found
@@ -87,9 +89,8 @@ __global__ __launch_bounds__(kKnnThreads) void k_knn(int64_t n, int points, int 
   auto squared_distance = [&](const float* p) {
     float acc = 0.f;
     auto add = [&](float x, float y, bool first) {
-      const float diff = __fsub_rn(x, y);
-      const float sq = __fmul_rn(diff, diff);
-      acc = first ? sq : __fadd_rn(acc, sq);
+      const float diff = x - y;
+      acc = first ? diff * diff : __builtin_fmaf(diff, diff, acc);
     };
     if constexpr (DIM > 0) {
 #pragma unroll

@@ -48,6 +48,15 @@ def test_packed_search_against_the_oracle(points, dim, k):
         assert (ix == ok.knn_graph(coords, 2, points, k)[1]).all()
 
 
+@pytest.mark.parametrize("points,dim", [(60, 3), (333, 3), (1024, 3), (400, 2), (300, 5)])
+def test_rounding_of_the_distance(points, dim):
+    """Multiples of 0.1: distances that are equal in the reals and differ by rounding alone, so the choice shows in
+    which order the squares are added and where they are fused."""
+    coords = np.random.default_rng(points).integers(0, 9, size=(3 * points, dim)).astype(np.float32) * np.float32(0.1)
+    _, ix = build(coords, 3, points, 20)
+    assert (ix == ok.knn_graph(coords, 3, points, 20)[1]).all()
+
+
 def test_ties_go_to_the_lower_index():
     # points on an integer grid: many exactly equal distances
     rng = np.random.default_rng(5)
