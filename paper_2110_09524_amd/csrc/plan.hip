@@ -1,6 +1,6 @@
 // Graph plan: device-side validation of the CSR arrays, the CSC transpose
-// (stable radix sort by source), and the degree order / degree buckets of both
-// sides.  Integer work only; every table is a pure function of the input.
+// (rows filled and sorted in place, or a stable radix sort by source), and the degree order / degree
+// buckets of both sides.  Integer work only; every table is a pure function of the input.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -84,9 +84,12 @@ __global__ void k_dst_of_position(int32_t n, int64_t nnz, const int32_t* __restr
 // (a k-nearest-neighbour graph of 655 000 edges, rebuilt every training step: 24 launches, 150 us on the
 // device; 2 launches and 43 us here).  Every edge goes to the next free slot of its source's row, in whatever order the
 // atomics fall, and one wavefront per row then sorts the row's CSR positions.  They are distinct, so
-// the table is the same whatever the order was.  Sorting by counting smaller entries costs
-// len^2 / 64 steps: rows up to kPlaceMaxRow stay below what the radix sort's launches cost.
-constexpr int kPlaceMaxRow = 2048;
+// the table is the same whatever the order was.  Sorting by counting smaller entries costs len^2 / 64
+// steps and a slot counter serves one edge at a time, so long rows are left to the radix sort.  Whole
+// plan, us, radix sort -> this: 5 10^3 vertices and 10^5 edges with out-degrees up to 38 189 -> 91,
+// 2 10^5 edges up to 113 185 -> 133, 233 10^3 vertices and 10^7 edges up to 79 1969 -> 1511; beyond the
+// limit it would lose: 10^5 edges up to 324 157 -> 240, 2 10^6 up to 1403 630 -> 2260.
+constexpr int kPlaceMaxRow = 128;
 
 // left[u]: out-degree of u, counted down to 0 here
 __global__ __launch_bounds__(256) void k_place_edges(int32_t n, const int32_t* __restrict__ indptr,
@@ -130,8 +133,9 @@ __global__ __launch_bounds__(256) void k_sort_rows(int32_t n, const int32_t* __r
 // ---- degree order by counting: stable, descending ------------------------------------------
 // One pass over blocks of 256 vertices for both sides (blockIdx.y): histograms of the degrees, laid out
 // so that their running sum in memory order is the position of each (degree, block) in the order.
-// Takes over from the radix sorts where the largest degree is below kCountMaxBins and the table of all
-// blocks' histograms stays small.
+// Takes over from the radix sorts (two of ten launches, 55 us each) where the largest degree is below
+// kCountMaxBins, so that a workgroup's counters fit its LDS, and the table of all blocks' histograms is no
+// larger than a scan of a few microseconds (whole plan of 2 10^4 vertices, degrees up to 330: 240 -> 172 us).
 constexpr int kCountMaxBins = 2048;
 constexpr int64_t kCountMaxTable = 1 << 19;
 struct DegreeSides {

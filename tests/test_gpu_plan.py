@@ -52,9 +52,9 @@ def test_workload_graphs(name):
     _check(c["indptr"], c["indices"])
 
 
-@pytest.mark.parametrize("longest", [1, 63, 64, 65, 129, 2046, 2047, 2048, 2049])
+@pytest.mark.parametrize("longest", [1, 63, 64, 65, 127, 128, 129, 2046, 2047, 2048])
 def test_out_rows_and_degrees_around_the_limits_of_the_sorts(longest):
-    """Out-rows of one wavefront and more; 2048 is the longest row that is placed and sorted by itself, degrees
+    """Out-rows of one wavefront and more; 128 is the longest row that is placed and sorted by itself, degrees
     up to 2047 are ordered by counting."""
     rng = np.random.default_rng(longest)
     n = max(2 * longest, 700)
