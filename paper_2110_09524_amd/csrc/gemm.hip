@@ -5,10 +5,11 @@
 // bf16 parts, x = h + m + l (8 + 8 + 8 significand bits: the whole fp32 significand), and a
 // product is the sum of the six partial products h h, h m, m h, m m, h l, l h with fp32
 // accumulators (v_mfma_f32_32x32x16_bf16).  What is left out (m l, l m, l l) is below 2^-26 of the
-// product, less than one fp32 rounding.  A tile whose result is not finite (an infinity or a NaN
-// among the operands, an operand so close to the largest float that h rounds to infinity, or an
-// overflowing sum) is computed again with the fp32 MFMA, so such values come out as fp32
-// arithmetic gives them.
+// product, less than one fp32 rounding.  bf16 ends 16 binary digits above fp32 (2^-133 against
+// 2^-149), so below 2^-109 the last part would lose digits: both operands are multiplied by 2^16
+// before they are split, and the result by 2^-32.  A tile whose scaled result is not finite (an
+// infinity or a NaN among the operands, an operand above 2^111, or a sum above 2^96) is computed
+// again with the fp32 MFMA, so such values come out as fp32 arithmetic gives them.
 //
 // Tiling: a workgroup of WR x WC wavefronts owns a BM x BN tile of C.  K advances 16 at a time
 // through two LDS buffers: while the matrix cores work on one slab, the wavefronts split the next
@@ -32,6 +33,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int BK = 16;     // k per slab
 constexpr int kParts = 3;
+constexpr float kScale = 65536.f;  // of either operand
 
 // Attention halves in the epilogue of the projection (Sec. 4, text after Eq. 1: the score splits
 // into a source half <a_l, z[u]> and a destination half <a_r, z[v]>, both per-vertex): el[m, h] =
@@ -126,17 +128,12 @@ struct Operand {
     for (int j = 0; j < kUnit; ++j) raw[0][j] = k() + j < rem ? b[(int64_t)off + (KCONTIG ? j : j * ld)] : 0.f;
   }
 
-  // sign * raw = h + m + l in bf16, to LDS
-  template <bool SIGNED>
-  __device__ __forceinline__ void store(int set, float sign, uint4* lds) const {
+  // scale * raw = h + m + l in bf16, to LDS
+  __device__ __forceinline__ void store(int set, float scale, uint4* lds) const {
     uint32_t w[kParts][kUnit / 2];
 #pragma unroll
     for (int q = 0; q < kUnit / 2; ++q) {
-      float a = raw[set][2 * q], b = raw[set][2 * q + 1];
-      if (SIGNED) {
-        a *= sign;
-        b *= sign;
-      }
+      float a = scale * raw[set][2 * q], b = scale * raw[set][2 * q + 1];
 #pragma unroll
       for (int p = 0; p < kParts; ++p) {
         w[p][q] = pack_bf16(a, b);
@@ -210,10 +207,10 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
   // would pull a long sum down.  So A's elements are stored with the sign (-1)^(row + slab): even slabs
   // sum up in acc[0], odd ones, negated, in acc[1], and what both lose cancels in their difference; a
   // product too short for that is at least pulled the other way in every other row.
-  const float row_sign = OpA::row() & 1 ? -1.f : 1.f;
+  const float row_scale = OpA::row() & 1 ? -kScale : kScale;
   auto store = [&](int raw_set, int parity, uint4* dst) {
-    opa.template store<true>(raw_set, parity ? -row_sign : row_sign, dst);
-    opb.template store<false>(raw_set, 1.f, dst + OpA::kLds);
+    opa.store(raw_set, parity ? -row_scale : row_scale, dst);
+    opb.store(raw_set, kScale, dst + OpA::kLds);
   };
   auto multiply = [&](int parity, const uint4* src) {
     constexpr int pa[6] = {1, 2, 0, 0, 1, 0}, pb[6] = {1, 0, 2, 1, 0, 0};  // smallest products first
@@ -309,6 +306,13 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
         }
       }
+  } else {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] *= 1.f / (kScale * kScale);
   }
 
   // accumulator layout of the 32x32 tile: register r of lane l holds
@@ -498,9 +502,9 @@ gnn_status_t sum_partials_two_level(int64_t count, int parts, const float* parti
 // ---- choice of the tile -----------------------------------------------------------------
 // Measured (x w, us; the fp32 MFMA on 128-row tiles before -> now): 232965 x 602 x 256 638 -> 470,
 // x 128 346 -> 262, x 64 202 -> 200, x 32 209 -> 180; 232965 x 1024 x 1024 3965 -> 2600; 20000 x 500 x 64
-// 30 -> 22; 65536 x 128 x 512 84 -> 65.  The wide products keep the matrix cores busy half of the time
-//, in 3/8 of the cycles that the fp32 MFMA would need; the narrow ones are bound
-// by the fetch of A, whose rows of 602 floats straddle cache lines (608 floats: 160 us at x 64).
+// 30 -> 22; 65536 x 128 x 512 84 -> 65.  The wide products keep the matrix cores busy half of the
+// time, with 3/8 of the cycles that the fp32 MFMA would need; the narrow ones are bound by the fetch
+// of A, whose rows of 602 floats straddle cache lines (608 floats: 160 us at x 64).
 //
 // 128 output columns per tile unless the last such tile would be at least half empty; 32 for the
 // narrowest products

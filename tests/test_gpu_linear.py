@@ -82,3 +82,21 @@ def test_values_at_the_end_of_the_range(n, fin, fout):
     assert np.array_equal(np.isfinite(got[42:44]), np.isfinite(ref[42:44]))
     rest = np.setdiff1d(np.arange(n), (3, 40, 41, 42, 43))
     _assert_within_rounding("the other rows", got[rest], x[rest], w)
+
+
+@pytest.mark.parametrize("sx,sw", [(-115, 0), (0, -122), (60, -126), (-126, 70), (60, -140), (85, 20), (100, -60)])
+@pytest.mark.parametrize("n,fin,fout", [(100, 40, 20), (300, 70, 130)])
+def test_products_of_very_small_and_large_operands(n, fin, fout, sx, sw):
+    """Operands near and below the smallest normal float keep their whole significand; sums above 2^96 take the
+    fp32 matrix instruction.  The results are normal floats, so the bound is the one of ordinary values."""
+    import paper_2110_09524_amd as pk
+    import torch
+    from gpu_harness import dev, empty
+    print(f"scaled products: {n} x {fin} x {fout}, 2^{sx} and 2^{sw}", flush=True)
+    rng = np.random.default_rng(fin)
+    x = (rng.uniform(0.5, 2, (n, fin)) * 2.0 ** sx).astype(np.float32)
+    w = (rng.uniform(0.5, 2, (fin, fout)) * 2.0 ** sw).astype(np.float32)
+    y = empty((n, fout))
+    pk.gnn_linear_fwd(dev(x), dev(w), y)
+    torch.cuda.synchronize()
+    _assert_within_rounding("y", y.cpu().numpy(), x, w)
