@@ -20,7 +20,7 @@
 // before me that are chosen), which leaves the row in ascending index order because index = lane +
 // 64 * slot.
 //
-// The votes of 16 slots in 32 probes were most of the work.  So for k <= 64 the k-th smallest of the
+// The votes of 16 slots in 32 probes are most of that work.  So for k <= 64 the k-th smallest of the
 // 64 lanes' minima comes first: at least k candidates lie at or below it, seldom more than a few
 // dozen beyond, and these are packed into two slots (in index order) for the search proper.
 // 32 x 1024 points, k = 20: 114 -> 45 us (84 us with the coordinates loaded one after the other).
