@@ -95,10 +95,11 @@ int64_t config_get(ConfigKey k);
 int device_cu_count();  // compute units of the current device (256 when the query fails)
 
 // ---- dense products (gemm.hip) ------------------------------------------------
-// c[M,N] = op(a) op(b), fp32 MFMA.  a_kmajor: a is stored [K,M] (m contiguous)
+// c[M,N] = op(a) op(b), fp32.  a_kmajor: a is stored [K,M] (m contiguous)
 // instead of [M,K]; b_kcontig: b is stored [N,K] (k contiguous) instead of [K,N].
 // split_k > 1 writes split_k partial products into `partials` and sums them in a
-// fixed order (deterministic).  partials needs split_k*M*N floats.
+// fixed order (deterministic), or leaves them to the caller (c == nullptr).  partials needs
+// split_k*M*N floats.
 gnn_status_t gemm_f32(int64_t M, int N, int64_t K, const float* a, int64_t lda, bool a_kmajor,
                       const float* b, int64_t ldb, bool b_kcontig, float* c, int64_t ldc,
                       int split_k, float* partials, hipStream_t s);

@@ -27,16 +27,53 @@ __global__ void k_ec_concat_weights(int fin, int fout, const float* __restrict__
   wcat[(int64_t)r * 2 * fout + fout + c] = phi[i] - t;
 }
 
-// gtheta = gcat[:, :fout] - gcat[:, fout:], gphi = gcat[:, fout:]
-__global__ void k_ec_split_weight_grads(int fin, int fout, const float* __restrict__ gcat,
-                                        float* __restrict__ gtheta, float* __restrict__ gphi) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= fin * fout) return;
-  int r = i / fout, c = i % fout;
-  float gp = gcat[(int64_t)r * 2 * fout + c];
-  float gq = gcat[(int64_t)r * 2 * fout + fout + c];
+// Closes x^T [dP | dQ] = [gTheta' | gQ'], given as `parts` matrices to add up ([parts][fin][2 fout]):
+// gtheta = gTheta' - gQ', gphi = gQ', and, for the product that follows (wcat != null), wcat as above.
+// Eight threads share an element: each adds every 8th part in four interleaved running sums, the eight
+// subtotals are added in order, so the result is reproducible.  On small layers these are launches of a
+// few microseconds that wait for each other, so the sum, the difference and the weights share one
+// (32 768 points, 64 -> 64, whole layer: 77.7 -> 75.6 us).
+__global__ __launch_bounds__(256) void k_ec_weight_grads(int fin, int fout, int parts, const float* __restrict__ partials,
+                                                         const float* __restrict__ theta, const float* __restrict__ phi,
+                                                         float* __restrict__ gtheta, float* __restrict__ gphi,
+                                                         float* __restrict__ wcat) {
+  __shared__ float sub[2][8][32];
+  const int col = threadIdx.x & 31, lane8 = threadIdx.x >> 5;
+  const int64_t i = (int64_t)blockIdx.x * 32 + col, count = (int64_t)fin * fout, stride = 2 * count;
+  const int64_t at = i < count ? i / fout * 2 * fout + i % fout : 0;
+  float p[4] = {0.f, 0.f, 0.f, 0.f}, q[4] = {0.f, 0.f, 0.f, 0.f};
+  if (i < count) {
+    const float* src = partials + at;
+    int z = lane8;
+    for (; z + 24 < parts; z += 32) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        p[t] += src[(z + 8 * t) * stride];
+        q[t] += src[(z + 8 * t) * stride + fout];
+      }
+    }
+    for (; z < parts; z += 8) {
+      p[0] += src[z * stride];
+      q[0] += src[z * stride + fout];
+    }
+  }
+  sub[0][lane8][col] = (p[0] + p[1]) + (p[2] + p[3]);
+  sub[1][lane8][col] = (q[0] + q[1]) + (q[2] + q[3]);
+  __syncthreads();
+  if (lane8 != 0 || i >= count) return;
+  float gp = 0.f, gq = 0.f;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    gp += sub[0][t][col];
+    gq += sub[1][t][col];
+  }
   gtheta[i] = gp - gq;
   gphi[i] = gq;
+  if (wcat != nullptr) {
+    const float t = theta[i];
+    wcat[at] = t;
+    wcat[at + fout] = phi[i] - t;
+  }
 }
 
 // ---- a7: fused gather-max ------------------------------------------------------------
@@ -473,18 +510,16 @@ extern "C" gnn_status_t gnn_edgeconv_bwd(const gnn_graph_t* g, int fin, int fout
 
   GNN_TRY(ec_dispatch<EcBwdLauncher>(pick_group(fout), g, argmax, gout, fout, reinterpret_cast<uint32_t*>(base + L.codes),
                                      dpq, st));
-  GNN_TRY(gemm_f32(fin, 2 * fout, n, x, fin, true, dpq, 2 * fout, false, gcat, 2 * fout, L.split_k, part, st));
+  const bool split = L.split_k > 1;
+  GNN_TRY(gemm_f32(fin, 2 * fout, n, x, fin, true, dpq, 2 * fout, false, split ? nullptr : gcat, 2 * fout, L.split_k, part,
+                   st));
   {
-    ProfScope p("edgeconv_split_weight_grads", st);
-    k_ec_split_weight_grads<<<(unsigned)cdiv((int64_t)fin * fout, 256), 256, 0, st>>>(fin, fout, gcat, gtheta, gphi);
+    ProfScope p("edgeconv_weight_grads", st);
+    k_ec_weight_grads<<<(unsigned)cdiv((int64_t)fin * fout, 32), 256, 0, st>>>(
+        fin, fout, L.split_k, split ? part : gcat, theta, phi, gtheta, gphi, gx ? wcat : nullptr);
     GNN_LAUNCH_CHECK();
   }
   if (gx) {
-    {
-      ProfScope p("edgeconv_concat_weights", st);
-      k_ec_concat_weights<<<(unsigned)cdiv((int64_t)fin * fout, 256), 256, 0, st>>>(fin, fout, theta, phi, wcat);
-      GNN_LAUNCH_CHECK();
-    }
     GNN_TRY(gemm_f32(n, fin, 2 * fout, dpq, 2 * fout, false, wcat, 2 * fout, true, gx, fin, 1, nullptr, st));
   }
   return GNN_OK;
