@@ -34,6 +34,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int BK = 16;     // k per slab
 constexpr int kParts = 3;
 constexpr float kScale = 65536.f;  // of either operand
+// Up to this many terms the fp32 MFMA alone: it rounds once per two terms, six partial products up to six times,
+// and the time is that of the launch either way (32768 x 3 x 128: 7.8 us).  EdgeConv step from 3 coordinates, gradient
+// of the first layer against 64 bits, median of 9 inputs: 1.4e-5 split, 4.9e-6 direct (5 terms: 4.3e-8 direct, 3.2e-8 split).
+constexpr int kDirectK = 4;
 
 // Attention halves in the epilogue of the projection (Sec. 4, text after Eq. 1: the score splits
 // into a source half <a_l, z[u]> and a destination half <a_r, z[v]>, both per-vertex): el[m, h] =
@@ -263,7 +267,8 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
     }
     if (s < slabs) step(std::integral_constant<int, 0>{}, s);
   }
-  if (const int rem = (int)(k_end - k_begin - slabs * BK); rem > 0) {
+  const bool direct = K <= kDirectK;
+  if (const int rem = (int)(k_end - k_begin - slabs * BK); rem > 0 && !direct) {
     opa.load_partial(slabs, rem);
     opb.load_partial(slabs, rem);
     __syncthreads();  // the buffers have been read
@@ -280,7 +285,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
       for (int r = 0; r < 16; ++r)  // r has the row's parity
         acc[i][j][r] = r & 1 ? part[1][i][j][r] - part[0][i][j][r] : part[0][i][j][r] - part[1][i][j][r];
 
-  // Not finite: the whole wavefront's tile again on the fp32 MFMA, operands straight from memory
+  // Not finite, or a very short sum: the whole wavefront's tile on the fp32 MFMA, operands straight from memory
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -288,7 +293,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
-  if (__ballot(bad) != 0) {
+  if (__ballot(bad) != 0 || direct) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
