@@ -313,7 +313,8 @@ gnn_status_t gnn_gat_bwd_stashed(const gnn_graph_t* graph, int fin, int heads, i
  * EdgeConv layer (App. A.2 "EdgeConv"), in the reorganized form of Sec. 4:
  * Theta(h_u - h_v) + Phi h_v = (x Theta)[u] + (x (Phi - Theta))[v].
  *
- *   pq  = x [Theta | Phi - Theta]                [n, 2*fout]  (P | Q), saved
+ *   pq  = x [Theta | Phi - Theta]                [n, 2*fout]  (P | Q), saved; every element
+ *                  the chain of fp32 fused multiply-adds over ascending input columns
  *   out = max over in-edges of P[u] + Q[v]       [n, fout]    (0 for an empty row)
  *   argmax[v, j] = CSR position of the winning in-edge, the earliest one on an
  *                  exact tie, -1 for an empty row             [n, fout] int32

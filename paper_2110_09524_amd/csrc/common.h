@@ -103,6 +103,10 @@ int device_cu_count();  // compute units of the current device (256 when the que
 gnn_status_t gemm_f32(int64_t M, int N, int64_t K, const float* a, int64_t lda, bool a_kmajor,
                       const float* b, int64_t ldb, bool b_kcontig, float* c, int64_t ldc,
                       int split_k, float* partials, hipStream_t s);
+// c = a b for a [M,K], b [K,N], every element the chain fma(a[k], b[k], ...) over ascending k from 0, in fp32: for
+// products that decide a comparison, so that the choice does not move with the way a product is summed up
+gnn_status_t gemm_f32_chain(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
+                            float* c, int64_t ldc, hipStream_t s);
 int gemm_pick_split_k(int64_t M, int N, int64_t K);
 // z[M, heads*f] = x[M, K] w[K, heads*f] with the attention halves el = <a_l, z>, er = <a_r, z> ([M, heads])
 // taken from the accumulators; gemm_attn_epilogue_ok says for which head widths this exists

@@ -88,6 +88,8 @@ struct Operand {
   static constexpr int kOctStride = ROWS + 4;         // padded: 8 lanes that store two octets of 4 rows meet different banks
   static constexpr int kPartStride = BK / 8 * kOctStride;   // in 16-byte vectors, like kLds
   static constexpr int kLds = kParts * kPartStride;
+  static constexpr int kChainStride = ROWS + 4;             // floats from one k to the next, padded likewise
+  static constexpr int kChainLds = BK * kChainStride / 4;   // in 16-byte vectors
   static_assert(kUnit == 2 || kUnit == 4 || kUnit == 8, "a thread stores 4, 8 or 16 bytes of each part");
 
   float raw[2][kUnit];
@@ -156,13 +158,82 @@ struct Operand {
     }
   }
 
+  // raw itself, k-major, to LDS
+  __device__ __forceinline__ void store_chain(int set, float* lds) const {
+#pragma unroll
+    for (int j = 0; j < kUnit; ++j) lds[(k() + j) * kChainStride + row()] = raw[set][j];
+  }
+
   // part p of the MFMA operand of a 32-row tile: 8 k of row `r`
   static __device__ __forceinline__ bf16x8 frag(const uint4* lds, int p, int oct, int r) {
     return __builtin_bit_cast(bf16x8, lds[p * kPartStride + oct * kOctStride + r]);
   }
 };
 
-template <int BM, int BN, int WR, int WC, bool A_KMAJOR, bool B_KCONTIG, bool EPI>
+// acc += A B on the fp32 MFMA, which adds its two products one after the other, each with one rounding: every
+// element is fma(a[k], b[k], ...) over ascending k, whatever the tile.  Buffers and prefetch as in the kernel below.
+template <int TM, int TN, class OpA, class OpB>
+__device__ __forceinline__ void chain_product(OpA& opa, OpB& opb, int64_t k_len, int wm0, int wn0, uint4* lds,
+                                              floatx16 (&acc)[TM][TN]) {
+  const int lrow = threadIdx.x & 31, lk = threadIdx.x >> 5 & 1;
+  auto buffer = [&](int b) { return reinterpret_cast<float*>(lds + b * (OpA::kChainLds + OpB::kChainLds)); };
+  auto store = [&](int raw_set, float* dst) {
+    opa.store_chain(raw_set, dst);
+    opb.store_chain(raw_set, dst + 4 * OpA::kChainLds);
+  };
+  auto multiply = [&](const float* src) {
+#pragma unroll
+    for (int k0 = 0; k0 < BK; k0 += 2) {
+      const float* pa = src + (k0 + lk) * OpA::kChainStride + wm0 + lrow;
+      const float* pb = src + 4 * OpA::kChainLds + (k0 + lk) * OpB::kChainStride + wn0 + lrow;
+      float a[TM], b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[i] = pa[32 * i];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[j] = pb[32 * j];
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+  };
+  const int64_t slabs = k_len / BK;  // whole ones
+  if (slabs > 0) {
+    opa.load(0, 0);
+    opb.load(0, 0);
+    const int64_t s1 = slabs > 1 ? 1 : 0;
+    opa.load(1, s1);
+    opb.load(1, s1);
+    store(0, buffer(0));
+    auto step = [&](auto parity, int64_t s) {
+      constexpr int P = decltype(parity)::value;
+      __syncthreads();  // buffer P is complete, the other one has been read
+      const int64_t s2 = s + 2 < slabs ? s + 2 : slabs - 1;
+      opa.load(P, s2);
+      opb.load(P, s2);
+      multiply(buffer(P));
+      store(P ^ 1, buffer(P ^ 1));
+    };
+    int64_t s = 0;
+    for (; s + 2 <= slabs; s += 2) {
+      step(std::integral_constant<int, 0>{}, s);
+      step(std::integral_constant<int, 1>{}, s + 1);
+    }
+    if (s < slabs) step(std::integral_constant<int, 0>{}, s);
+  }
+  if (const int rem = (int)(k_len - slabs * BK); rem > 0) {
+    opa.load_partial(slabs, rem);
+    opb.load_partial(slabs, rem);
+    __syncthreads();  // the buffers have been read
+    store(0, buffer(0));
+    __syncthreads();
+    multiply(buffer(0));
+  }
+}
+
+// CHAIN: the whole product as chain_product gives it
+template <int BM, int BN, int WR, int WC, bool A_KMAJOR, bool B_KCONTIG, bool EPI, bool CHAIN>
 __global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
     int64_t M, int N, int64_t K, const float* __restrict__ A, int64_t lda,
     const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc,
@@ -173,7 +244,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
   static_assert(TM >= 1 && TN >= 1, "a wavefront owns at least one MFMA tile");
   using OpA = Operand<BM, THREADS, !A_KMAJOR>;
   using OpB = Operand<BN, THREADS, B_KCONTIG>;
-  __shared__ uint4 lds[2][OpA::kLds + OpB::kLds];
+  __shared__ uint4 lds[2][CHAIN ? OpA::kChainLds + OpB::kChainLds : OpA::kLds + OpB::kLds];
 
   // Workgroups go to the XCDs round-robin.  All tiles along n of a row of tiles (and all tiles of a
   // k range of a split product) run on one XCD, one after the other: they read the same rows.
@@ -192,132 +263,142 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
   const int64_t k_end = k_begin + k_per_split < K ? k_begin + k_per_split : K;
   const int lrow = lane & 31, lk = lane >> 5;
 
-  floatx16 part[2][TM][TN];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) part[h][i][j][r] = 0.f;
-
   OpA opa;
   OpB opb;
   opa.init(A, lda, m0, M, k_begin);
   opb.init(B, ldb, n0, N, k_begin);
 
-  // The matrix core cuts its sums off (towards minus infinity) where fp32 arithmetic rounds, which
-  // would pull a long sum down.  So A's elements are stored with the sign (-1)^(row + slab): even slabs
-  // sum up in acc[0], odd ones, negated, in acc[1], and what both lose cancels in their difference; a
-  // product too short for that is at least pulled the other way in every other row.
-  const float row_scale = OpA::row() & 1 ? -kScale : kScale;
-  auto store = [&](int raw_set, int parity, uint4* dst) {
-    opa.store(raw_set, parity ? -row_scale : row_scale, dst);
-    opb.store(raw_set, kScale, dst + OpA::kLds);
-  };
-  auto multiply = [&](int parity, const uint4* src) {
-    constexpr int pa[6] = {1, 2, 0, 0, 1, 0}, pb[6] = {1, 0, 2, 1, 0, 0};  // smallest products first
-    bf16x8 a[kParts][TM], b[kParts][TN];
-#pragma unroll
-    for (int p = 0; p < kParts; ++p) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i) a[p][i] = OpA::frag(src, p, lk, wm0 + i * 32 + lrow);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) b[p][j] = OpB::frag(src + OpA::kLds, p, lk, wn0 + j * 32 + lrow);
-    }
-#pragma unroll
-    for (int q = 0; q < 6; ++q)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          part[parity][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pa[q]][i], b[pb[q]][j], part[parity][i][j], 0, 0, 0);
-  };
-
-  const int64_t slabs = (k_end - k_begin) / BK;  // whole ones
-  if (slabs > 0) {
-    opa.load(0, 0);
-    opb.load(0, 0);
-    const int64_t s1 = slabs > 1 ? 1 : 0;
-    opa.load(1, s1);
-    opb.load(1, s1);
-    store(0, 0, lds[0]);
-    // slab s, of parity P: its parts are in lds[P], slab s + 1 is in raw[P ^ 1] or on its way, and
-    // raw[P] is free for slab s + 2 (past the end: the last slab again, for nothing)
-    auto step = [&](auto parity, int64_t s) {
-      constexpr int P = decltype(parity)::value;
-      __syncthreads();  // lds[P] is complete, lds[P ^ 1] has been read
-      const int64_t s2 = s + 2 < slabs ? s + 2 : slabs - 1;
-      opa.load(P, s2);
-      opb.load(P, s2);
-      multiply(P, lds[P]);
-      store(P ^ 1, P ^ 1, lds[P ^ 1]);
-      // one MFMA, then the vector instructions that fit its time
-#pragma unroll
-      for (int q = 0; q < 6 * TM * TN; ++q) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
-      }
-    };
-    int64_t s = 0;
-    for (; s + 2 <= slabs; s += 2) {
-      step(std::integral_constant<int, 0>{}, s);
-      step(std::integral_constant<int, 1>{}, s + 1);
-    }
-    if (s < slabs) step(std::integral_constant<int, 0>{}, s);
-  }
-  const bool direct = K <= kDirectK;
-  if (const int rem = (int)(k_end - k_begin - slabs * BK); rem > 0 && !direct) {
-    opa.load_partial(slabs, rem);
-    opb.load_partial(slabs, rem);
-    __syncthreads();  // the buffers have been read
-    store(0, 0, lds[0]);
-    __syncthreads();
-    multiply(0, lds[0]);
-  }
   floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)  // r has the row's parity
-        acc[i][j][r] = r & 1 ? part[1][i][j][r] - part[0][i][j][r] : part[0][i][j][r] - part[1][i][j][r];
-
-  // Not finite, or a very short sum: the whole wavefront's tile on the fp32 MFMA, operands straight from memory
-  bool bad = false;
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
-  if (__ballot(bad) != 0 || direct) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        int64_t m = m0 + wm0 + i * 32 + lrow;
-        int64_t n = n0 + wn0 + j * 32 + lrow;
-        if (m >= M) m = M - 1;
-        if (n >= N) n = N - 1;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-        for (int64_t k0 = k_begin; k0 < k_end; k0 += 2) {
-          const int64_t k = k0 + lk;
-          const float av = k < k_end ? A[A_KMAJOR ? k * lda + m : m * lda + k] : 0.f;
-          const float bv = k < k_end ? B[B_KCONTIG ? n * ldb + k : k * ldb + n] : 0.f;
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
-        }
-      }
-  } else {
+  if constexpr (CHAIN) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] *= 1.f / (kScale * kScale);
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    chain_product(opa, opb, k_end - k_begin, wm0, wn0, lds[0], acc);
+  } else {
+    floatx16 part[2][TM][TN];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) part[h][i][j][r] = 0.f;
+
+    // The matrix core cuts its sums off (towards minus infinity) where fp32 arithmetic rounds, which
+    // would pull a long sum down.  So A's elements are stored with the sign (-1)^(row + slab): even slabs
+    // sum up in acc[0], odd ones, negated, in acc[1], and what both lose cancels in their difference; a
+    // product too short for that is at least pulled the other way in every other row.
+    const float row_scale = OpA::row() & 1 ? -kScale : kScale;
+    auto store = [&](int raw_set, int parity, uint4* dst) {
+      opa.store(raw_set, parity ? -row_scale : row_scale, dst);
+      opb.store(raw_set, kScale, dst + OpA::kLds);
+    };
+    auto multiply = [&](int parity, const uint4* src) {
+      constexpr int pa[6] = {1, 2, 0, 0, 1, 0}, pb[6] = {1, 0, 2, 1, 0, 0};  // smallest products first
+      bf16x8 a[kParts][TM], b[kParts][TN];
+#pragma unroll
+      for (int p = 0; p < kParts; ++p) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) a[p][i] = OpA::frag(src, p, lk, wm0 + i * 32 + lrow);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) b[p][j] = OpB::frag(src + OpA::kLds, p, lk, wn0 + j * 32 + lrow);
+      }
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            part[parity][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pa[q]][i], b[pb[q]][j], part[parity][i][j], 0, 0, 0);
+    };
+
+    const int64_t slabs = (k_end - k_begin) / BK;  // whole ones
+    if (slabs > 0) {
+      opa.load(0, 0);
+      opb.load(0, 0);
+      const int64_t s1 = slabs > 1 ? 1 : 0;
+      opa.load(1, s1);
+      opb.load(1, s1);
+      store(0, 0, lds[0]);
+      // slab s, of parity P: its parts are in lds[P], slab s + 1 is in raw[P ^ 1] or on its way, and
+      // raw[P] is free for slab s + 2 (past the end: the last slab again, for nothing)
+      auto step = [&](auto parity, int64_t s) {
+        constexpr int P = decltype(parity)::value;
+        __syncthreads();  // lds[P] is complete, lds[P ^ 1] has been read
+        const int64_t s2 = s + 2 < slabs ? s + 2 : slabs - 1;
+        opa.load(P, s2);
+        opb.load(P, s2);
+        multiply(P, lds[P]);
+        store(P ^ 1, P ^ 1, lds[P ^ 1]);
+        // one MFMA, then the vector instructions that fit its time
+#pragma unroll
+        for (int q = 0; q < 6 * TM * TN; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
+        }
+      };
+      int64_t s = 0;
+      for (; s + 2 <= slabs; s += 2) {
+        step(std::integral_constant<int, 0>{}, s);
+        step(std::integral_constant<int, 1>{}, s + 1);
+      }
+      if (s < slabs) step(std::integral_constant<int, 0>{}, s);
+    }
+    const bool direct = K <= kDirectK;
+    if (const int rem = (int)(k_end - k_begin - slabs * BK); rem > 0 && !direct) {
+      opa.load_partial(slabs, rem);
+      opb.load_partial(slabs, rem);
+      __syncthreads();  // the buffers have been read
+      store(0, 0, lds[0]);
+      __syncthreads();
+      multiply(0, lds[0]);
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)  // r has the row's parity
+          acc[i][j][r] = r & 1 ? part[1][i][j][r] - part[0][i][j][r] : part[0][i][j][r] - part[1][i][j][r];
+
+    // Not finite, or a very short sum: the whole wavefront's tile on the fp32 MFMA, operands straight from memory
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
+    if (__ballot(bad) != 0 || direct) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          int64_t m = m0 + wm0 + i * 32 + lrow;
+          int64_t n = n0 + wn0 + j * 32 + lrow;
+          if (m >= M) m = M - 1;
+          if (n >= N) n = N - 1;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+          for (int64_t k0 = k_begin; k0 < k_end; k0 += 2) {
+            const int64_t k = k0 + lk;
+            const float av = k < k_end ? A[A_KMAJOR ? k * lda + m : m * lda + k] : 0.f;
+            const float bv = k < k_end ? B[B_KCONTIG ? n * ldb + k : k * ldb + n] : 0.f;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
+          }
+        }
+    } else {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] *= 1.f / (kScale * kScale);
+    }
   }
 
   // accumulator layout of the 32x32 tile: register r of lane l holds
@@ -540,7 +621,7 @@ int gemm_pick_split_k(int64_t M, int N, int64_t K) {
   return want < 1 ? 1 : (int)want;
 }
 
-template <int BM, int BN, int WR, int WC, bool AK, bool BKC, bool EPI>
+template <int BM, int BN, int WR, int WC, bool AK, bool BKC, bool EPI, bool CHAIN>
 static gnn_status_t launch(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
                            float* c, int64_t ldc, int split_k, float* partials, const AttnEpilogue& epi,
                            hipStream_t s) {
@@ -553,19 +634,19 @@ static gnn_status_t launch(int64_t M, int N, int64_t K, const float* a, int64_t 
   ProfScope p(EPI ? "gemm_f32_mfma_attn" : split_k > 1 ? "gemm_f32_mfma_splitk" : "gemm_f32_mfma", s);
   float* out = split_k > 1 ? partials : c;
   const int64_t ldo = split_k > 1 ? N : ldc;
-  k_gemm_f32<BM, BN, WR, WC, AK, BKC, EPI><<<(unsigned)grid, 64 * WR * WC, 0, s>>>(
+  k_gemm_f32<BM, BN, WR, WC, AK, BKC, EPI, CHAIN><<<(unsigned)grid, 64 * WR * WC, 0, s>>>(
       M, N, K, a, lda, b, ldb, out, ldo, kps, M * (int64_t)N, (int)tm, (int)tn, split_k, epi);
   GNN_LAUNCH_CHECK();
   return GNN_OK;
 }
 
-template <bool AK, bool BKC, bool EPI>
+template <bool AK, bool BKC, bool EPI, bool CHAIN>
 static gnn_status_t launch_tile(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
                                 float* c, int64_t ldc, int split_k, float* partials, const AttnEpilogue& epi,
                                 hipStream_t s) {
   const int bn = gemm_tile_cols(N), bm = gemm_tile_rows(M, N, bn, split_k);
 #define GNN_GEMM_TILE(...) \
-  return launch<__VA_ARGS__, AK, BKC, EPI>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, epi, s)
+  return launch<__VA_ARGS__, AK, BKC, EPI, CHAIN>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, epi, s)
   if (bn == 32) GNN_GEMM_TILE(128, 32, 4, 1);
   if (bn == 64 && bm == 64) GNN_GEMM_TILE(64, 64, 2, 2);
   if (bn == 64) GNN_GEMM_TILE(128, 64, 2, 2);
@@ -589,15 +670,25 @@ gnn_status_t gemm_f32(int64_t M, int N, int64_t K, const float* a, int64_t lda, 
               "gemm_f32: split-K needs a dense output (ldc == N)");
   const AttnEpilogue none{nullptr, nullptr, nullptr, nullptr, 0, 0};
   if (a_kmajor) {
-    if (b_kcontig) GNN_TRY((launch_tile<true, true, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
-    else GNN_TRY((launch_tile<true, false, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
+    if (b_kcontig) GNN_TRY((launch_tile<true, true, false, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
+    else GNN_TRY((launch_tile<true, false, false, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
   } else {
-    if (b_kcontig) GNN_TRY((launch_tile<false, true, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
-    else GNN_TRY((launch_tile<false, false, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
+    if (b_kcontig) GNN_TRY((launch_tile<false, true, false, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
+    else GNN_TRY((launch_tile<false, false, false, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
   }
   if (split_k == 1 || c == nullptr) return GNN_OK;
   ProfScope p("gemm_sum_partials", s);
   return sum_partials(M * (int64_t)N, split_k, partials, c, s);
+}
+
+gnn_status_t gemm_f32_chain(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
+                            float* c, int64_t ldc, hipStream_t s) {
+  if (M <= 0 || N <= 0) return GNN_OK;
+  GNN_REQUIRE(K > 0, GNN_ERR_INVALID_ARG, "gemm_f32_chain: K must be positive");
+  GNN_REQUIRE(lda > 0 && ldb > 0 && lda < (1 << 24) && ldb < (1 << 24) && cdiv(M, 32) < (int64_t)INT32_MAX,
+              GNN_ERR_UNSUPPORTED, "gemm_f32_chain: sizes out of range");
+  const AttnEpilogue none{nullptr, nullptr, nullptr, nullptr, 0, 0};
+  return launch_tile<false, false, false, true>(M, N, K, a, lda, b, ldb, c, ldc, 1, nullptr, none, s);
 }
 
 // z = x w with el, er from the epilogue; only for shapes gemm_attn_epilogue_ok() accepts: heads inside
@@ -618,7 +709,7 @@ gnn_status_t gemm_f32_attn(int64_t M, int heads, int f, int64_t K, const float* 
   GNN_REQUIRE(K > 0 && K < (1 << 24) && N < (1 << 24) && cdiv(M, 32) < (int64_t)INT32_MAX, GNN_ERR_UNSUPPORTED,
               "gemm_f32_attn: sizes out of range");
   const AttnEpilogue epi{a_l, a_r, el, er, heads, f};
-  return launch_tile<false, false, true>(M, N, K, x, K, w, N, z, N, 1, nullptr, epi, s);
+  return launch_tile<false, false, true, false>(M, N, K, x, K, w, N, z, N, 1, nullptr, epi, s);
 }
 
 }  // namespace gnn

@@ -105,6 +105,50 @@ def test_duplicate_edges_empty_rows_and_hub():
     check(c)
 
 
+def fma_chain(x, w):
+    """fma(x[:, k], w[k], ...) over ascending k in fp32.  A product of two floats is exact in fp64 and the sum is
+    rounded once more on its way to fp32, which differs from the fused operation in about one of 2^29 steps."""
+    acc = np.zeros((x.shape[0], w.shape[1]), dtype=np.float32)
+    for k in range(x.shape[1]):
+        acc = (x[:, k:k + 1].astype(np.float64) * w[k].astype(np.float64) + acc).astype(np.float32)
+    return acc
+
+
+@pytest.mark.parametrize("n,fin,fout", [(301, 3, 4), (65, 16, 12), (200, 37, 16), (130, 64, 64), (70, 129, 132),
+                                        (33000, 20, 68)])
+def test_projection_is_the_chain_of_fused_multiply_adds(n, fin, fout):
+    """Every tile of the product that the maximum compares (32, 64 and 128 columns, 64 and 128 rows, whole and partial
+    last slabs), bit for bit, and a winner that is the earliest edge with the largest of these values."""
+    from gpu_harness import run_edgeconv
+    print(f"edgeconv projection: {n} x {fin} -> {fout}", flush=True)
+    rng = np.random.default_rng(n + fin + fout)
+    indptr = (4 * np.arange(n + 1)).astype(np.int32)
+    indices = np.sort(rng.integers(0, n, size=(n, 4)), axis=1).astype(np.int32)
+    c = synth(rng, indptr, indices.reshape(-1), fin, fout)
+    res = run_edgeconv(c, backward=False)
+    ref = fma_chain(c["x"], np.concatenate([c["theta"], c["phi"] - c["theta"]], axis=1))
+    assert np.array_equal(res["pq"], ref)
+    first = ref[indices][:, :, :fout].argmax(axis=1)
+    assert np.array_equal(res["argmax"], first + indptr[:-1, None])
+
+
+@pytest.mark.parametrize("fin,fout", [(3, 64), (16, 16), (64, 64), (128, 260)])
+def test_repeated_points_tie_exactly(fin, fout):
+    """A cloud padded by repeating its points: copies have the same bits wherever they stand, so the earliest wins."""
+    from gpu_harness import run_edgeconv
+    print(f"edgeconv: repeated points {fin} -> {fout}", flush=True)
+    rng = np.random.default_rng(fin + fout)
+    points = 171
+    copies = np.concatenate([np.arange(points), rng.integers(0, points, size=2 * points)])
+    n = copies.size
+    indptr = (n * np.arange(n + 1)).astype(np.int32)
+    c = synth(rng, indptr, np.tile(np.arange(n, dtype=np.int32), n), fin, fout)
+    c["x"] = np.ascontiguousarray(c["x"][copies])
+    res = run_edgeconv(c, backward=False)
+    assert np.array_equal(res["pq"], res["pq"][copies])
+    assert (res["argmax"] - indptr[:-1, None] < points).all()
+
+
 @pytest.mark.parametrize("n,longest,fout", [(4200, 255, 64), (4200, 256, 64), (2100, 255, 132), (1100, 254, 260),
                                             (700, 255, 516)])
 def test_backward_by_winner_codes(n, longest, fout):
