@@ -289,12 +289,11 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
           for (int r = 0; r < 16; ++r) part[h][i][j][r] = 0.f;
 
     // The matrix core cuts its sums off (towards minus infinity) where fp32 arithmetic rounds, which
-    // would pull a long sum down.  So A's elements are stored with the sign (-1)^(row + slab): even slabs
-    // sum up in acc[0], odd ones, negated, in acc[1], and what both lose cancels in their difference; a
-    // product too short for that is at least pulled the other way in every other row.
-    const float row_scale = OpA::row() & 1 ? -kScale : kScale;
+    // would pull a long sum down.  So A's elements of odd slabs are stored negated and sum up in part[1], those of
+    // even slabs in part[0], and what both lose cancels in their difference.  The sign depends on the slab alone: equal
+    // rows have equal results wherever they stand.
     auto store = [&](int raw_set, int parity, uint4* dst) {
-      opa.store(raw_set, parity ? -row_scale : row_scale, dst);
+      opa.store(raw_set, parity ? -kScale : kScale, dst);
       opb.store(raw_set, kScale, dst + OpA::kLds);
     };
     auto multiply = [&](int parity, const uint4* src) {
@@ -352,18 +351,19 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
     if (const int rem = (int)(k_end - k_begin - slabs * BK); rem > 0 && !direct) {
       opa.load_partial(slabs, rem);
       opb.load_partial(slabs, rem);
+      const bool odd = slabs & 1;
       __syncthreads();  // the buffers have been read
-      store(0, 0, lds[0]);
+      store(0, odd, lds[0]);
       __syncthreads();
-      multiply(0, lds[0]);
+      if (odd) multiply(1, lds[0]);
+      else multiply(0, lds[0]);
     }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)  // r has the row's parity
-          acc[i][j][r] = r & 1 ? part[1][i][j][r] - part[0][i][j][r] : part[0][i][j][r] - part[1][i][j][r];
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = part[0][i][j][r] - part[1][i][j][r];
 
     // Not finite, or a very short sum: the whole wavefront's tile on the fp32 MFMA, operands straight from memory
     bool bad = false;

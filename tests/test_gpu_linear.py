@@ -56,6 +56,29 @@ def test_products_of_every_layout_and_tile(n, fin, fout):
     assert (np.abs(got - xt @ gout.astype(np.float64)) <= bound).all()
 
 
+@pytest.mark.parametrize("n,fin,fout", [(90, 8, 16), (100, 40, 20), (200, 33, 60), (300, 70, 132), (33000, 48, 68),
+                                        (66000, 96, 132)])
+def test_equal_rows_have_equal_products(n, fin, fout):
+    """Rows repeated at even and odd places, in x w and in g w^T."""
+    import paper_2110_09524_amd as pk
+    import torch
+    from gpu_harness import dev, empty
+    print(f"equal rows: {n} x {fin} x {fout}", flush=True)
+    rng = np.random.default_rng(n + fin)
+    again = rng.integers(0, 37, size=n)
+    x, gout = (np.ascontiguousarray(rng.standard_normal((37, s)).astype(np.float32)[again]) for s in (fin, fout))
+    w = rng.standard_normal((fin, fout)).astype(np.float32)
+    g = pk.Graph(dev(np.arange(n + 1, dtype=np.int32)), dev(np.arange(n, dtype=np.int32)))
+    one, zs, out, gx, gw = dev(np.ones(n, np.float32)), empty((n, fout)), empty((n, fout)), empty((n, fin)), empty((fin, fout))
+    ws = torch.empty(max(pk.gnn_gcn_workspace_bytes(g, fin, fout), 16), dtype=torch.uint8, device="cuda")
+    pk.gnn_gcn_fwd(g, fin, fout, dev(x), dev(w), one, one, zs, out)
+    pk.gnn_gcn_bwd(g, fin, fout, dev(x), dev(w), one, one, dev(gout), gx, gw, ws)
+    torch.cuda.synchronize()
+    first = np.unique(again, return_index=True)[1]
+    for got in (zs.cpu().numpy(), gx.cpu().numpy()):
+        assert np.array_equal(got, got[first][np.unique(again, return_inverse=True)[1]])
+
+
 @pytest.mark.parametrize("n,fin,fout", [(100, 40, 20), (200, 33, 60), (300, 70, 130)])
 def test_values_at_the_end_of_the_range(n, fin, fout):
     """Infinities, NaN, the largest floats and tiny ones come out as fp32 arithmetic gives them."""
