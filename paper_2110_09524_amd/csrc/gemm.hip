@@ -7,9 +7,10 @@
 // accumulators (v_mfma_f32_32x32x16_bf16).  What is left out (m l, l m, l l) is below 2^-26 of the
 // product, less than one fp32 rounding.  bf16 ends 16 binary digits above fp32 (2^-133 against
 // 2^-149), so below 2^-109 the last part would lose digits: both operands are multiplied by 2^16
-// before they are split, and the result by 2^-32.  A tile whose scaled result is not finite (an
-// infinity or a NaN among the operands, an operand above 2^111, or a sum above 2^96) is computed
-// again with the fp32 MFMA, so such values come out as fp32 arithmetic gives them.
+// before they are split, and the result by 2^-32.  A result that is not finite in these units (an
+// infinity or a NaN among the operands, an operand above 2^111, or a sum above 2^96) is taken from
+// the fp32 MFMA, on which its whole tile is computed again, so such values come out as fp32
+// arithmetic gives them (232965 x 602 x 256: 469 us, 476 us with one infinity, 1013 us with one in every tile).
 //
 // Tiling: a workgroup of WR x WC wavefronts owns a BM x BN tile of C.  K advances 16 at a time
 // through two LDS buffers: while the matrix cores work on one slab, the wavefronts split the next
@@ -365,39 +366,34 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = part[0][i][j][r] - part[1][i][j][r];
 
-    // Not finite, or a very short sum: the whole wavefront's tile on the fp32 MFMA, operands straight from memory
-    bool bad = false;
+    // What is not finite, and very short sums, as the fp32 chain gives them.  Element by element: a result depends on
+    // its own row and column, not on what else the tile holds.
+    float zero = 0.f;  // stays so as long as everything is finite
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
-    if (__ballot(bad) != 0 || direct) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          int64_t m = m0 + wm0 + i * 32 + lrow;
-          int64_t n = n0 + wn0 + j * 32 + lrow;
-          if (m >= M) m = M - 1;
-          if (n >= N) n = N - 1;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-          for (int64_t k0 = k_begin; k0 < k_end; k0 += 2) {
-            const int64_t k = k0 + lk;
-            const float av = k < k_end ? A[A_KMAJOR ? k * lda + m : m * lda + k] : 0.f;
-            const float bv = k < k_end ? B[B_KCONTIG ? n * ldb + k : k * ldb + n] : 0.f;
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
-          }
+        for (int r = 0; r < 16; ++r) {
+          acc[i][j][r] *= 1.f / (kScale * kScale);
+          zero = __builtin_fmaf(acc[i][j][r], 0.f, zero);
         }
-    } else {
+    if (__syncthreads_or(direct || zero != 0.f)) {  // uniform over the workgroup; the buffers have been read
+      floatx16 chain[TM][TN];
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] *= 1.f / (kScale * kScale);
+          for (int r = 0; r < 16; ++r) chain[i][j][r] = 0.f;
+      chain_product(opa, opb, k_end - k_begin, wm0, wn0, lds[0], chain);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (direct || !(fabsf(acc[i][j][r]) <= 3.402823466e38f)) acc[i][j][r] = chain[i][j][r];
     }
   }
 

@@ -107,6 +107,39 @@ def test_values_at_the_end_of_the_range(n, fin, fout):
     _assert_within_rounding("the other rows", got[rest], x[rest], w)
 
 
+@pytest.mark.parametrize("n,fin,fout", [(100, 40, 20), (200, 33, 60), (300, 70, 132), (33000, 48, 68), (66000, 96, 132)])
+def test_results_beside_infinities_and_nan(n, fin, fout):
+    """What is not finite takes the fp32 matrix instruction; every other element keeps the bits it has without that."""
+    import paper_2110_09524_amd as pk
+    import torch
+    from gpu_harness import dev, empty
+    print(f"beside infinities: {n} x {fin} x {fout}", flush=True)
+    rng = np.random.default_rng(n + fin)
+    x, w, gout = (rng.standard_normal(s).astype(np.float32) for s in ((n, fin), (fin, fout), (n, fout)))
+    g = pk.Graph(dev(np.arange(n + 1, dtype=np.int32)), dev(np.arange(n, dtype=np.int32)))
+    one = dev(np.ones(n, np.float32))
+    ws = torch.empty(max(pk.gnn_gcn_workspace_bytes(g, fin, fout), 16), dtype=torch.uint8, device="cuda")
+
+    def products(x, w, gout):
+        zs, out, gx, gw = empty((n, fout)), empty((n, fout)), empty((n, fin)), empty((fin, fout))
+        pk.gnn_gcn_fwd(g, fin, fout, dev(x), dev(w), one, one, zs, out)
+        pk.gnn_gcn_bwd(g, fin, fout, dev(x), dev(w), one, one, dev(gout), gx, gw, ws)
+        torch.cuda.synchronize()
+        return [t.cpu().numpy() for t in (zs, gx, gw)]
+
+    zs, gx, gw = products(x, w, gout)
+    x2, w2, g2 = x.copy(), w.copy(), gout.copy()
+    x2[[3, 50], [1, 9]] = np.inf, np.nan     # rows 3, 50 of x w; columns 1, 9 of x, rows of x^T g
+    w2[5, 7] = -np.inf                       # column 7 of x w, column 5 of g w^T
+    g2[[11, 40], [2, 4]] = np.nan, np.inf    # rows 11, 40 of g w^T, columns 2, 4 of x^T g
+    zs2, gx2, gw2 = products(x2, w2, g2)
+    for got, ref, rows, cols in ((zs2, zs, (3, 50), (7,)), (gx2, gx, (11, 40), (5,)), (gw2, gw, (1, 9), (2, 4))):
+        same = np.ones(ref.shape, dtype=bool)
+        same[list(rows)], same[:, list(cols)] = False, False
+        assert np.array_equal(got[same], ref[same])
+        assert not np.isfinite(got[~same]).any()
+
+
 @pytest.mark.parametrize("sx,sw", [(-115, 0), (0, -122), (60, -126), (-126, 70), (60, -140), (85, 20), (100, -60)])
 @pytest.mark.parametrize("n,fin,fout", [(100, 40, 20), (300, 70, 130)])
 def test_products_of_very_small_and_large_operands(n, fin, fout, sx, sw):
