@@ -52,10 +52,10 @@ def test_workload_graphs(name):
     _check(c["indptr"], c["indices"])
 
 
-@pytest.mark.parametrize("longest", [1, 63, 64, 65, 127, 128, 129, 2046, 2047, 2048])
+@pytest.mark.parametrize("longest", [1, 63, 64, 65, 127, 128, 129, 255, 256, 257, 1400, 2046, 2047, 2048])
 def test_out_rows_and_degrees_around_the_limits_of_the_sorts(longest):
-    """Out-rows of one wavefront and more; 128 is the longest row that is placed and sorted by itself, degrees
-    up to 2047 are ordered by counting."""
+    """Out-rows of one wavefront and more; 128 is the longest row that is placed and sorted by itself, 256 the
+    longest in-row that is placed by row, and degrees up to 2047 are ordered by counting."""
     rng = np.random.default_rng(longest)
     n = max(2 * longest, 700)
     pairs = [(u, v) for u, cnt in ((5, longest), (6, longest // 2), (7, 1)) for v in rng.permutation(n)[:cnt]]
@@ -64,6 +64,39 @@ def test_out_rows_and_degrees_around_the_limits_of_the_sorts(longest):
     _check(*tiny_graph(n, pairs))
     # the same graph the other way round: the long row is an in-row
     _check(*tiny_graph(n, [(v, u) for u, v in pairs]))
+
+
+def _plan_ms(indptr, indices):
+    """Fastest of five builds, in ms, without the column-blocked lists that the other tests ask for."""
+    import time
+    import paper_2110_09524_amd as pk
+    best = float("inf")
+    pk.gnn_config_set("blocked_min_edges", 16)
+    for _ in range(5):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        g = pk.Graph(indptr, indices)
+        torch.cuda.synchronize()
+        best = min(best, 1e3 * (time.perf_counter() - t0))
+        g.close()
+    pk.gnn_config_set("blocked_min_edges", 0)
+    return best
+
+
+@pytest.mark.parametrize("n,hub", [(300_000, 200_000), (1_000_000, 1_000_000)])
+def test_hub_in_rows_of_short_out_rows(n, hub):
+    """Every vertex has one out-edge, the first `hub` of them into vertex 7: the plan takes about as long as without a
+    hub (five times is far above the noise; a row walked by 16 lanes took 27 and 48 times)."""
+    from gpu_harness import dev
+    dst = np.concatenate([np.full(hub, 7), np.arange(n - hub) % n])
+    indptr = np.concatenate([[0], np.cumsum(np.bincount(dst, minlength=n))]).astype(np.int32)
+    indices = np.argsort(dst, kind="stable").astype(np.int32)
+    print(f"plan: in-row of {hub} edges", flush=True)
+    _check(indptr, indices)
+    hub_ms = _plan_ms(dev(indptr), dev(indices))
+    even_ms = _plan_ms(dev(np.arange(n + 1, dtype=np.int32)), dev(np.random.default_rng(1).permutation(n).astype(np.int32)))
+    print(f"  {hub_ms:.3f} ms, without a hub {even_ms:.3f} ms", flush=True)
+    assert hub_ms < 5 * even_ms
 
 
 def test_malformed_graphs_are_rejected():
