@@ -93,6 +93,12 @@ __global__ void k_dst_of_position(int32_t n, int64_t nnz, const int32_t* __restr
 // limit it would lose: 10^5 edges up to 324 157 -> 240, 2 10^6 up to 1403 630 -> 2260.
 constexpr int kPlaceMaxRow = 128;
 
+// Workgroups for kernels that give several threads to a row: a launch may not have 2^32 threads along a dimension,
+// so such a kernel goes on with the row gridDim.x workgroups further (2^23 workgroups of 256 threads are 2^31).
+static unsigned row_grid(int32_t n, int rows_per_block) {
+  return (unsigned)std::min(cdiv((int64_t)n, rows_per_block), (int64_t)1 << 23);
+}
+
 // left[u]: out-degree of u, counted down to 0 here
 __device__ __forceinline__ void place_edge(int32_t e, int32_t v, const int32_t* __restrict__ indices,
                                            const int32_t* __restrict__ indptr_t, int32_t* __restrict__ left,
@@ -112,10 +118,10 @@ __global__ __launch_bounds__(256) void k_place_rows(int32_t n, const int32_t* __
                                                     const int32_t* __restrict__ indptr_t, int32_t* __restrict__ left,
                                                     int2* __restrict__ placed) {
   const int li = threadIdx.x & 15;
-  const int64_t v = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 4;
-  if (v >= n) return;
-  const int32_t beg = indptr[v], end = indptr[v + 1];
-  for (int32_t e = beg + li; e < end; e += 16) place_edge(e, (int32_t)v, indices, indptr_t, left, placed);
+  for (int64_t v = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); v < n; v += (int64_t)gridDim.x * 16) {
+    const int32_t beg = indptr[v], end = indptr[v + 1];
+    for (int32_t e = beg + li; e < end; e += 16) place_edge(e, (int32_t)v, indices, indptr_t, left, placed);
+  }
 }
 
 // One thread per edge: a workgroup takes kPlaceEdges consecutive edges, finds the rows of the first and the last of
@@ -141,21 +147,21 @@ __global__ __launch_bounds__(256) void k_sort_rows(int32_t n, const int32_t* __r
                                                    const int2* __restrict__ placed, int32_t* __restrict__ eid_t,
                                                    int32_t* __restrict__ indices_t) {
   const int lane = threadIdx.x & 63;
-  const int64_t u = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  if (u >= n) return;  // whole wavefront
-  const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
-  for (int32_t i0 = beg; i0 < end; i0 += kWave) {
-    const bool ok = i0 + lane < end;
-    const int2 mine = ok ? placed[i0 + lane] : make_int2(0, 0);
-    int rank = 0;
-    for (int32_t j0 = beg; j0 < end; j0 += kWave) {
-      const int other = j0 == i0 ? mine.x : j0 + lane < end ? placed[j0 + lane].x : 0;
-      const int cnt = min(kWave, end - j0);
-      for (int j = 0; j < cnt; ++j) rank += __builtin_amdgcn_readlane(other, j) < mine.x ? 1 : 0;
-    }
-    if (ok) {
-      eid_t[beg + rank] = mine.x;
-      indices_t[beg + rank] = mine.y;
+  for (int64_t u = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); u < n; u += (int64_t)gridDim.x * 4) {
+    const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
+    for (int32_t i0 = beg; i0 < end; i0 += kWave) {
+      const bool ok = i0 + lane < end;
+      const int2 mine = ok ? placed[i0 + lane] : make_int2(0, 0);
+      int rank = 0;
+      for (int32_t j0 = beg; j0 < end; j0 += kWave) {
+        const int other = j0 == i0 ? mine.x : j0 + lane < end ? placed[j0 + lane].x : 0;
+        const int cnt = min(kWave, end - j0);
+        for (int j = 0; j < cnt; ++j) rank += __builtin_amdgcn_readlane(other, j) < mine.x ? 1 : 0;
+      }
+      if (ok) {
+        eid_t[beg + rank] = mine.x;
+        indices_t[beg + rank] = mine.y;
+      }
     }
   }
 }
@@ -693,14 +699,12 @@ static gnn_status_t build(gnn_graph* g, hipStream_t st) {
     int2* placed = nullptr;
     GNN_HIP(tmp.alloc(&placed, (size_t)nnz));
     if (g->max_degree[0] <= kPlaceMaxInRow)
-      k_place_rows<<<(unsigned)cdiv((int64_t)n * 16, thr), thr, 0, st>>>(n, g->indptr, g->indices, g->indptr_t, outdeg,
-                                                                         placed);
+      k_place_rows<<<row_grid(n, 16), thr, 0, st>>>(n, g->indptr, g->indices, g->indptr_t, outdeg, placed);
     else
       k_place_edges<<<(unsigned)cdiv(nnz, kPlaceEdges), thr, 0, st>>>(n, nnz, g->indptr, g->indices, g->indptr_t,
                                                                       outdeg, placed);
     GNN_LAUNCH_CHECK();
-    k_sort_rows<<<(unsigned)cdiv((int64_t)n * kWave, thr), thr, 0, st>>>(n, g->indptr_t, placed, g->eid_t,
-                                                                         g->indices_t);
+    k_sort_rows<<<row_grid(n, 4), thr, 0, st>>>(n, g->indptr_t, placed, g->eid_t, g->indices_t);
     GNN_LAUNCH_CHECK();
   } else if (nnz > 0) {
     // stable sort of (source, CSR position): positions stay ascending inside a source

@@ -99,6 +99,28 @@ def test_hub_in_rows_of_short_out_rows(n, hub):
     assert hub_ms < 5 * even_ms
 
 
+@pytest.mark.parametrize("n", [2 ** 26 + 77, 2 ** 28 + 5])
+def test_more_rows_than_one_launch_has_threads_for(n):
+    """64 threads to a row pass 2^32 from 2^26 rows on, 16 threads from 2^28 on."""
+    import paper_2110_09524_amd as pk
+    print(f"plan: {n} vertices", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    key = torch.randint(n, (2, 3000), generator=gen, device="cuda")
+    key[:, :40] = n - 1 - torch.arange(40, device="cuda") // 8       # the last rows too
+    key = (key[0] * n + key[1]).unique()                             # by destination, sources ascending
+    dst, src = key // n, key % n
+    indptr = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    indptr[1:] = torch.bincount(dst, minlength=n).cumsum(0)
+    g = pk.Graph(indptr, src.to(torch.int32))
+    ptr_t, dst_t, eid_t = g.csc()
+    want = torch.sort(src, stable=True)
+    assert torch.equal(eid_t.long(), want.indices)
+    assert torch.equal(dst_t.long(), dst[want.indices])
+    assert int(ptr_t[0]) == 0 and torch.equal(ptr_t[1:].long(), torch.bincount(src, minlength=n).cumsum(0))
+    g.close()
+    pk.gnn_release_cached_memory()
+
+
 def test_malformed_graphs_are_rejected():
     import paper_2110_09524_amd as pk
     from gpu_harness import dev
