@@ -119,8 +119,9 @@ __global__ __launch_bounds__(256) void k_place_rows(int32_t n, const int32_t* __
                                                     int2* __restrict__ placed) {
   const int li = threadIdx.x & 15;
   for (int64_t v = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); v < n; v += (int64_t)gridDim.x * 16) {
-    const int32_t beg = indptr[v], end = indptr[v + 1];
-    for (int32_t e = beg + li; e < end; e += 16) place_edge(e, (int32_t)v, indices, indptr_t, left, placed);
+    const int32_t beg = indptr[v], len = indptr[v + 1] - beg;  // counted from the row's start: beg + len + 16 may
+    for (int i = li; i < len; i += 16)                         // not fit 32 bits
+      place_edge(beg + i, (int32_t)v, indices, indptr_t, left, placed);
   }
 }
 
@@ -148,14 +149,15 @@ __global__ __launch_bounds__(256) void k_sort_rows(int32_t n, const int32_t* __r
                                                    int32_t* __restrict__ indices_t) {
   const int lane = threadIdx.x & 63;
   for (int64_t u = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); u < n; u += (int64_t)gridDim.x * 4) {
-    const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
-    for (int32_t i0 = beg; i0 < end; i0 += kWave) {
-      const bool ok = i0 + lane < end;
-      const int2 mine = ok ? placed[i0 + lane] : make_int2(0, 0);
+    const int32_t beg = indptr_t[u], len = indptr_t[u + 1] - beg;
+    const int2* row = placed + beg;
+    for (int i0 = 0; i0 < len; i0 += kWave) {
+      const bool ok = i0 + lane < len;
+      const int2 mine = ok ? row[i0 + lane] : make_int2(0, 0);
       int rank = 0;
-      for (int32_t j0 = beg; j0 < end; j0 += kWave) {
-        const int other = j0 == i0 ? mine.x : j0 + lane < end ? placed[j0 + lane].x : 0;
-        const int cnt = min(kWave, end - j0);
+      for (int j0 = 0; j0 < len; j0 += kWave) {
+        const int other = j0 == i0 ? mine.x : j0 + lane < len ? row[j0 + lane].x : 0;
+        const int cnt = min(kWave, len - j0);
         for (int j = 0; j < cnt; ++j) rank += __builtin_amdgcn_readlane(other, j) < mine.x ? 1 : 0;
       }
       if (ok) {

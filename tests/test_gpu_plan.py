@@ -121,6 +121,33 @@ def test_more_rows_than_one_launch_has_threads_for(n):
     pk.gnn_release_cached_memory()
 
 
+def test_edge_positions_up_to_the_end_of_32_bits():
+    """2^31 - 3 edges in rows of 128: the last in-row and the last out-row have 125 and end 16 and 64 positions before
+    anything larger fits 32 bits."""
+    import paper_2110_09524_amd as pk
+    print("plan: 2^31 - 3 edges", flush=True)
+    n, d, step = 2 ** 24, 128, 1_000_003
+    i = torch.arange(d, device="cuda")
+    hop = torch.where(i < 125, i * step, 0)              # edge i of row v comes from v + hop[i]; the last three are loops
+    indices = torch.empty(n * d, dtype=torch.int32, device="cuda")
+    runs = [slice(r, r + 2 ** 20) for r in range(0, n, 2 ** 20)]
+    rows = torch.arange(n, device="cuda").unsqueeze(1)
+    for r in runs:
+        indices.view(n, d)[r] = (rows[r] + hop).remainder_(n).to(torch.int32)
+    indptr = torch.arange(n + 1, device="cuda") * d
+    indptr[n] -= 3
+    g = pk.Graph(indptr.to(torch.int32), indices[:-3])
+    ptr_t, dst_t, eid_t = g.csc()
+    assert torch.equal(ptr_t.long(), indptr)
+    print("  built", flush=True)
+    for r in runs:
+        want = ((rows[r] - hop).remainder_(n) * d + i).sort(dim=1).values.view(-1)[:int(indptr[r.stop]) - r.start * d]
+        at = slice(r.start * d, int(indptr[r.stop]))
+        assert torch.equal(eid_t[at].long(), want)
+        assert torch.equal(dst_t[at].long(), want // d)
+    g.close()
+
+
 def test_malformed_graphs_are_rejected():
     import paper_2110_09524_amd as pk
     from gpu_harness import dev
