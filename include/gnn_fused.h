@@ -318,6 +318,8 @@ gnn_status_t gnn_gat_bwd_stashed(const gnn_graph_t* graph, int fin, int heads, i
  *   out = max over in-edges of P[u] + Q[v]       [n, fout]    (0 for an empty row)
  *   argmax[v, j] = CSR position of the winning in-edge, the earliest one on an
  *                  exact tie, -1 for an empty row             [n, fout] int32
+ *                  (and for a column in which every gathered P is -infinity or NaN: no edge takes its
+ *                  gradient, Q[v] does)
  *
  * Requirements: fout % 4 == 0, fout <= 1024.  theta, phi are [fin, fout].
  * Only argmax (O(|V|)) is needed by the backward pass (Sec. 7.2 "EdgeConv").

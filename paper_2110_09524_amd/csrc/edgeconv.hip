@@ -168,9 +168,9 @@ __global__ __launch_bounds__(kEcBlock) void k_edgeconv_fwd(
 // (zero when u has no in-edge: then out[u] = 0 does not depend on Q[u])
 template <int L, int NV>
 __global__ __launch_bounds__(kEcBlock) void k_edgeconv_bwd_src(
-    int32_t n_rows, const int32_t* __restrict__ order_t, const int32_t* __restrict__ indptr_t,
-    const int32_t* __restrict__ indices_t, const int32_t* __restrict__ eid_t,
-    const int32_t* __restrict__ argmax, const float* __restrict__ gout, int F,
+    int32_t n_rows, const int32_t* __restrict__ order_t, const int32_t* __restrict__ indptr,
+    const int32_t* __restrict__ indptr_t, const int32_t* __restrict__ indices_t,
+    const int32_t* __restrict__ eid_t, const int32_t* __restrict__ argmax, const float* __restrict__ gout, int F,
     float* __restrict__ dpq) {
   constexpr int G = kWave / L;
   constexpr int GPB = G * (kEcBlock / kWave);
@@ -231,16 +231,15 @@ __global__ __launch_bounds__(kEcBlock) void k_edgeconv_bwd_src(
     }
     wave_lds_fence();
   }
+  // by the degree: a column without a winner (nothing gathered above -infinity) still adds Q[u] to its output
+  const bool constant = indptr[u] == indptr[u + 1];
 #pragma unroll
   for (int j = 0; j < NV; ++j)
     if (slot_ok[j]) {
       const int col = 4 * (li + j * L);
       st4(dpq + (int64_t)u * 2 * F + col, acc[j]);
-      // dQ[u] = gout[u], except that a vertex without in-edges has a constant output
-      const int4 own = *reinterpret_cast<const int4*>(argmax + (int64_t)u * F + col);
-      float4 gq = ld4(gout + (int64_t)u * F + col);
-      if (own.x < 0) gq = make_float4(0.f, 0.f, 0.f, 0.f);
-      st4(dpq + (int64_t)u * 2 * F + F + col, gq);
+      const float4 gq = ld4(gout + (int64_t)u * F + col);
+      st4(dpq + (int64_t)u * 2 * F + F + col, constant ? make_float4(0.f, 0.f, 0.f, 0.f) : gq);
     }
 }
 
@@ -336,7 +335,7 @@ __global__ __launch_bounds__(kEcBlock) void k_edgeconv_bwd_src_codes(
     }
     wave_lds_fence();
   }
-  const bool constant = indptr[u] == indptr[u + 1];  // without in-edges out[u] does not depend on Q[u]
+  const bool constant = indptr[u] == indptr[u + 1];
 #pragma unroll
   for (int j = 0; j < NV; ++j)
     if (slot_ok[j]) {
@@ -398,8 +397,8 @@ struct EcBwdLauncher {
       return GNN_OK;
     }
     ProfScope p("edgeconv_bwd_src", st);
-    k_edgeconv_bwd_src<L, NV><<<grid, kEcBlock, 0, st>>>(g->n, order, g->indptr_t, g->indices_t, g->eid_t, argmax,
-                                                         gout, F, dpq);
+    k_edgeconv_bwd_src<L, NV><<<grid, kEcBlock, 0, st>>>(g->n, order, g->indptr, g->indptr_t, g->indices_t, g->eid_t,
+                                                         argmax, gout, F, dpq);
     GNN_LAUNCH_CHECK();
     return GNN_OK;
   }

@@ -197,3 +197,34 @@ def test_backward_by_winner_codes(n, longest, fout):
     # far inside these bounds: every single contribution went to its winner
     assert np.abs(gx.cpu().numpy() - ref).max() <= 1e-4 * np.abs(ref).max()
     g.close()
+
+
+@pytest.mark.parametrize("n,deg,fout", [(300, 3, 4), (90, 70, 20), (130, 5, 64), (100, 9, 260), (4200, 254, 64)])
+def test_columns_without_a_winner(n, deg, fout):
+    """Vertex 5 hears only from vertex 2, whose P is -infinity in every third column, and vertex 6 only from vertex 3, whose P
+    is NaN: no in-edge wins there (arg-max -1).  The output still adds Q, so dQ is the upstream gradient as long as
+    there are in-edges; the last shape takes the one-byte codes (67 million (edge, column) pairs)."""
+    from gpu_harness import run_edgeconv
+    print(f"edgeconv, no winner: {n} {deg} {fout}", flush=True)
+    rng = np.random.default_rng(n + fout)
+    degs = np.full(n, deg)
+    degs[[5, 6, 7]] = 2, 1, 0
+    indptr = np.concatenate(([0], np.cumsum(degs))).astype(np.int32)
+    indices = rng.integers(8, n, size=indptr[-1]).astype(np.int32)
+    indices[indptr[5]:indptr[6]], indices[indptr[6]:indptr[7]] = 2, 3
+    fin = 6
+    c = synth(rng, indptr, indices, fin, fout)
+    c["x"][2, 1], c["x"][3, 4] = np.inf, np.nan
+    c["theta"][1] = np.where(np.arange(fout) % 3 == 0, -1, 1) * (0.5 + rng.random(fout))
+    res = run_edgeconv(c)
+    arg = res["argmax"]
+    assert (arg[5] == np.where(np.arange(fout) % 3 == 0, -1, indptr[5])).all() and (arg[6:8] == -1).all()
+    go, won = c["gout"].astype(np.float64), arg >= 0
+    dP = np.zeros((n, fout))
+    np.add.at(dP, (indices[arg[won]], np.nonzero(won)[1]), go[won])
+    dQ = np.where((degs > 0)[:, None], go, 0.0)
+    th, ph = c["theta"].astype(np.float64), c["phi"].astype(np.float64)
+    ref = dP @ th.T + dQ @ (ph - th).T
+    # sums of up to n terms of order 1 into dP, then 2 fout products; far below a missing gradient row
+    assert np.abs(res["gx"] - ref).max() <= 1e-5 * np.abs(ref).max()
+    np.testing.assert_allclose(res["gx"][5:8], ref[5:8], rtol=1e-4, atol=1e-4 * np.abs(ref[5:8]).max())
