@@ -356,7 +356,8 @@ static bool near_uniform_degrees(const gnn_graph_t* g, int side) {
 
 // The pass that writes the codes is one more launch: it pays from about 64 million (edge, column) pairs
 // (us, plain -> codes and their pass: 65 536 vertices x 40 neighbours x 256 columns 246 -> 188, x 128 140 ->
-// 109, x 64 68 -> 56; 32 768 x 20 x 64, 42 million: 20 -> 24)
+// 109, x 64 68 -> 56; 32 768 x 20 x 64, 42 million: 20 -> 24).  Both ways give the same bits, so a workspace without
+// room for the codes, sized for another graph of as many vertices, takes the plain kernel.
 static bool ec_codes_pay(const gnn_graph_t* g, int F) {
   return g->max_degree[0] <= kEcCodeEmpty && g->nnz * F >= (int64_t)1 << 26 && !config_get(kCfgForceSimple);
 }
@@ -384,7 +385,7 @@ struct EcBwdLauncher {
     const bool by_id = near_uniform_degrees(g, 1);
     const unsigned grid = by_id ? xcd_contiguous_grid(g->n, GPB) : (unsigned)cdiv(g->n, GPB);
     const int32_t* order = by_id ? nullptr : g->order[1];
-    if (ec_codes_pay(g, F)) {
+    if (codes != nullptr) {
       {
         ProfScope p("edgeconv_codes", st);
         k_edgeconv_codes<L, NV><<<(unsigned)cdiv(g->n, GPB), kEcBlock, 0, st>>>(g->n, g->indptr, argmax, F, codes);
@@ -424,7 +425,7 @@ static gnn_status_t ec_dispatch(GroupShape gs, Args... args) {
 }
 
 struct EcWs {
-  size_t total, wcat, dpq, gcat, gemm, codes;
+  size_t total, wcat, dpq, gcat, gemm;  // codes come last, at `total`, for graphs that use them
   int split_k;
 };
 
@@ -437,9 +438,12 @@ static EcWs ec_ws_layout(int64_t n, int fin, int fout) {
   w.gcat = take(sizeof(float) * 2 * (size_t)fin * fout);
   w.split_k = gemm_pick_split_k(fin, 2 * fout, n);
   w.gemm = take(w.split_k > 1 ? sizeof(float) * (size_t)w.split_k * fin * 2 * fout : 0);
-  w.codes = take((size_t)n * fout);
   w.total = off;
   return w;
+}
+
+static size_t ec_codes_bytes(const gnn_graph_t* g, int fout) {
+  return ec_codes_pay(g, fout) ? ws_granule((size_t)g->n * fout) : 0;
 }
 
 static gnn_status_t ec_check(const gnn_graph_t* g, int fin, int fout, const char* who) {
@@ -456,7 +460,7 @@ using namespace gnn;
 
 extern "C" size_t gnn_edgeconv_workspace_bytes(const gnn_graph_t* g, int fin, int fout) {
   if (!g || fin <= 0 || fout <= 0) return 0;
-  return ec_ws_layout(g->n, fin, fout).total;
+  return ec_ws_layout(g->n, fin, fout).total + ec_codes_bytes(g, fout);
 }
 
 extern "C" gnn_status_t gnn_edgeconv_fwd(const gnn_graph_t* g, int fin, int fout, const float* x,
@@ -509,8 +513,10 @@ extern "C" gnn_status_t gnn_edgeconv_bwd(const gnn_graph_t* g, int fin, int fout
   float* part = reinterpret_cast<float*>(base + L.gemm);
   const int64_t n = g->n;
 
-  GNN_TRY(ec_dispatch<EcBwdLauncher>(pick_group(fout), g, argmax, gout, fout, reinterpret_cast<uint32_t*>(base + L.codes),
-                                     dpq, st));
+  const size_t codes_bytes = ec_codes_bytes(g, fout);
+  uint32_t* codes =
+      codes_bytes != 0 && ws_bytes >= L.total + codes_bytes ? reinterpret_cast<uint32_t*>(base + L.total) : nullptr;
+  GNN_TRY(ec_dispatch<EcBwdLauncher>(pick_group(fout), g, argmax, gout, fout, codes, dpq, st));
   const bool split = L.split_k > 1;
   GNN_TRY(gemm_f32(fin, 2 * fout, n, x, fin, true, dpq, 2 * fout, false, split ? nullptr : gcat, 2 * fout, L.split_k, part,
                    st));

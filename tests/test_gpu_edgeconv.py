@@ -228,3 +228,38 @@ def test_columns_without_a_winner(n, deg, fout):
     # sums of up to n terms of order 1 into dP, then 2 fout products; far below a missing gradient row
     assert np.abs(res["gx"] - ref).max() <= 1e-5 * np.abs(ref).max()
     np.testing.assert_allclose(res["gx"][5:8], ref[5:8], rtol=1e-4, atol=1e-4 * np.abs(ref[5:8]).max())
+
+
+def test_workspace_of_a_graph_without_codes_serves_one_with():
+    """The room for the byte codes (n fout bytes) is asked for where they are used; without it the plain kernel gives the
+    same bits, and the forward call needs none."""
+    import paper_2110_09524_amd as pk
+    import torch
+    from gpu_harness import dev, empty
+    print("edgeconv: workspace of another graph", flush=True)
+    n, fin, fout = 4200, 12, 64
+    rng = np.random.default_rng(11)
+    graphs = []
+    for deg in (2, 254):
+        indptr = (deg * np.arange(n + 1)).astype(np.int32)
+        graphs.append((indptr, rng.integers(0, n, size=n * deg).astype(np.int32)))
+    few, many = (pk.Graph(dev(p), dev(i)) for p, i in graphs)
+    small, large = (pk.gnn_edgeconv_workspace_bytes(g, fin, fout) for g in (few, many))
+    assert n * fout <= large - small < n * fout + 256
+    c = synth(rng, *graphs[1], fin, fout)
+    x, theta, phi, gout = (dev(c[k]) for k in ("x", "theta", "phi", "gout"))
+    runs = []
+    for size in (small, large):
+        ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+        pq, out, arg = empty((n, 2 * fout)), empty((n, fout)), torch.empty((n, fout), dtype=torch.int32, device="cuda")
+        pk.gnn_edgeconv_fwd(many, fin, fout, x, theta, phi, pq, out, arg, ws)
+        grads = empty((n, fin)), empty((fin, fout)), empty((fin, fout))
+        pk.gnn_edgeconv_bwd(many, fin, fout, x, theta, phi, arg, gout, *grads, ws)
+        torch.cuda.synchronize()
+        runs.append([t.cpu().numpy() for t in (pq, out, arg, *grads)])
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b)
+    with pytest.raises(pk.GnnError) as e:
+        pk.gnn_edgeconv_bwd(many, fin, fout, x, theta, phi, arg, gout, *grads, ws[:small - 256])
+    assert e.value.status == 3
+    few.close(), many.close()
