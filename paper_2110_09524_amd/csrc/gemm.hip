@@ -233,9 +233,15 @@ __device__ __forceinline__ void chain_product(OpA& opa, OpB& opb, int64_t k_len,
   }
 }
 
+// Wavefronts per SIMD that the registers have to leave room for: the accumulators of a 128 x 128 tile allow two.  The
+// smaller tiles of x^T g would end a few registers above the limit of three (232965 x 602 x 64: 225 us, 254 with two);
+// x w fits three by itself and is slower when held to it (198 -> 215 us).
+template <int BM, int BN, bool A_KMAJOR>
+constexpr int kMinWaves = A_KMAJOR && BM * BN <= 128 * 64 ? 3 : 2;
+
 // CHAIN: the whole product as chain_product gives it
 template <int BM, int BN, int WR, int WC, bool A_KMAJOR, bool B_KCONTIG, bool EPI, bool CHAIN>
-__global__ __launch_bounds__(64 * WR * WC, 2) void k_gemm_f32(
+__global__ __launch_bounds__(64 * WR * WC, (kMinWaves<BM, BN, A_KMAJOR>)) void k_gemm_f32(
     int64_t M, int N, int64_t K, const float* __restrict__ A, int64_t lda,
     const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc,
     int64_t k_per_split, int64_t split_stride, int tiles_m, int tiles_n, int splits, AttnEpilogue epi) {
