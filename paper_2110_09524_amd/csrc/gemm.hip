@@ -129,10 +129,10 @@ struct Operand {
   }
 
   // the last slab, of which only `rem` < BK values of k exist
-  __device__ __forceinline__ void load_partial(int64_t s, int rem) {
+  __device__ __forceinline__ void load_partial(int set, int64_t s, int rem) {
     const float* b = base + s * step;
 #pragma unroll
-    for (int j = 0; j < kUnit; ++j) raw[0][j] = k() + j < rem ? b[(int64_t)off + (KCONTIG ? j : j * ld)] : 0.f;
+    for (int j = 0; j < kUnit; ++j) raw[set][j] = k() + j < rem ? b[(int64_t)off + (KCONTIG ? j : j * ld)] : 0.f;
   }
 
   // scale * raw = h + m + l in bf16, to LDS
@@ -224,8 +224,8 @@ __device__ __forceinline__ void chain_product(OpA& opa, OpB& opb, int64_t k_len,
     if (s < slabs) step(std::integral_constant<int, 0>{}, s);
   }
   if (const int rem = (int)(k_len - slabs * BK); rem > 0) {
-    opa.load_partial(slabs, rem);
-    opb.load_partial(slabs, rem);
+    opa.load_partial(0, slabs, rem);
+    opb.load_partial(0, slabs, rem);
     __syncthreads();  // the buffers have been read
     store(0, buffer(0));
     __syncthreads();
@@ -233,14 +233,18 @@ __device__ __forceinline__ void chain_product(OpA& opa, OpB& opb, int64_t k_len,
   }
 }
 
+// How a kernel sums up: kLoop over the slabs of bf16 parts; kShallow the same for products of up to kShallowK terms;
+// kChain the whole product as chain_product gives it
+enum Mode { kLoop, kShallow, kChain };
+constexpr int kShallowK = 2 * BK;
+
 // Wavefronts per SIMD that the registers have to leave room for: the accumulators of a 128 x 128 tile allow two.  The
 // smaller tiles of x^T g would end a few registers above the limit of three (232965 x 602 x 64: 225 us, 254 with two);
 // x w fits three by itself and is slower when held to it (198 -> 215 us).
 template <int BM, int BN, bool A_KMAJOR>
 constexpr int kMinWaves = A_KMAJOR && BM * BN <= 128 * 64 ? 3 : 2;
 
-// CHAIN: the whole product as chain_product gives it
-template <int BM, int BN, int WR, int WC, bool A_KMAJOR, bool B_KCONTIG, bool EPI, bool CHAIN>
+template <int BM, int BN, int WR, int WC, bool A_KMAJOR, bool B_KCONTIG, bool EPI, Mode MODE>
 __global__ __launch_bounds__(64 * WR * WC, (kMinWaves<BM, BN, A_KMAJOR>)) void k_gemm_f32(
     int64_t M, int N, int64_t K, const float* __restrict__ A, int64_t lda,
     const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc,
@@ -251,7 +255,7 @@ __global__ __launch_bounds__(64 * WR * WC, (kMinWaves<BM, BN, A_KMAJOR>)) void k
   static_assert(TM >= 1 && TN >= 1, "a wavefront owns at least one MFMA tile");
   using OpA = Operand<BM, THREADS, !A_KMAJOR>;
   using OpB = Operand<BN, THREADS, B_KCONTIG>;
-  __shared__ uint4 lds[2][CHAIN ? OpA::kChainLds + OpB::kChainLds : OpA::kLds + OpB::kLds];
+  __shared__ uint4 lds[2][MODE == kChain ? OpA::kChainLds + OpB::kChainLds : OpA::kLds + OpB::kLds];
 
   // Workgroups go to the XCDs round-robin.  All tiles along n of a row of tiles (and all tiles of a
   // k range of a split product) run on one XCD, one after the other: they read the same rows.
@@ -276,7 +280,7 @@ __global__ __launch_bounds__(64 * WR * WC, (kMinWaves<BM, BN, A_KMAJOR>)) void k
   opb.init(B, ldb, n0, N, k_begin);
 
   floatx16 acc[TM][TN];
-  if constexpr (CHAIN) {
+  if constexpr (MODE == kChain) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -284,6 +288,95 @@ __global__ __launch_bounds__(64 * WR * WC, (kMinWaves<BM, BN, A_KMAJOR>)) void k
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     chain_product(opa, opb, k_end - k_begin, wm0, wn0, lds[0], acc);
+  } else if constexpr (MODE == kShallow) {
+    // Little more than a fetch and a store, so it takes many wavefronts per CU, that is few registers: both slabs at
+    // once, one accumulator pair at a time, and the fp32 chain likewise (106 registers for 128 x 64 instead of 164).
+    // x w, us, loop -> here (on the fp32 MFMA alone): 232965 x 16 x 64 17.2 -> 15.6 (15.9), x 256 51 -> 41 (45);
+    // 100000 x 8 x 64 11.8 -> 9.0 (9.4), x 24 x 128 22.4 -> 16.6 (21.2); 50000 x 12 x 512 32 -> 21 (25).  At two whole
+    // slabs they meet: 232965 x 32 x 64 20.1 -> 20.3, x 256 63 -> 60.  GAT forward with 4 heads of 64 from 16 columns,
+    // 232965 vertices: 304 -> 247 (251).
+    const int k0 = (int)(K < BK ? K : BK), k1 = (int)K - k0;
+    if (k0 == BK) {
+      opa.load(0, 0);
+      opb.load(0, 0);
+    } else {
+      opa.load_partial(0, 0, k0);
+      opb.load_partial(0, 0, k0);
+    }
+    if (k1 == BK) {
+      opa.load(1, 1);
+      opb.load(1, 1);
+    } else if (k1 > 0) {
+      opa.load_partial(1, 1, k1);
+      opb.load_partial(1, 1, k1);
+    }
+    const bool direct = K <= kDirectK;
+    float zero = 0.f;
+    if (!direct) {
+      opa.store(0, kScale, lds[0]);
+      opb.store(0, kScale, lds[0] + OpA::kLds);
+      if (k1 > 0) {  // the odd slab: negated, as below
+        opa.store(1, -kScale, lds[1]);
+        opb.store(1, kScale, lds[1] + OpA::kLds);
+      }
+      __syncthreads();
+      auto multiply = [&](int i, int j, const uint4* src) {
+        constexpr int pa[6] = {1, 2, 0, 0, 1, 0}, pb[6] = {1, 0, 2, 1, 0, 0};
+        bf16x8 a[kParts], b[kParts];
+#pragma unroll
+        for (int p = 0; p < kParts; ++p) {
+          a[p] = OpA::frag(src, p, lk, wm0 + i * 32 + lrow);
+          b[p] = OpB::frag(src + OpA::kLds, p, lk, wn0 + j * 32 + lrow);
+        }
+        floatx16 sum;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pa[q]], b[pb[q]], sum, 0, 0, 0);
+        return sum;
+      };
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          acc[i][j] = multiply(i, j, lds[0]);
+          if (k1 > 0) acc[i][j] -= multiply(i, j, lds[1]);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            acc[i][j][r] *= 1.f / (kScale * kScale);
+            zero = __builtin_fmaf(acc[i][j][r], 0.f, zero);
+          }
+        }
+    }
+    if (__syncthreads_or(direct || zero != 0.f)) {
+      float* dst[2] = {reinterpret_cast<float*>(lds[0]), reinterpret_cast<float*>(lds[1])};
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (h == 0 || k1 > 0) {
+          opa.store_chain(h, dst[h]);
+          opb.store_chain(h, dst[h] + 4 * OpA::kChainLds);
+        }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          floatx16 chain;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) chain[r] = 0.f;
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            if (h == 0 || k1 > 0)
+#pragma unroll
+              for (int k = lk; k < BK; k += 2)
+                chain = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                    dst[h][k * OpA::kChainStride + wm0 + i * 32 + lrow],
+                    dst[h][4 * OpA::kChainLds + k * OpB::kChainStride + wn0 + j * 32 + lrow], chain, 0, 0, 0);
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (direct || !(fabsf(acc[i][j][r]) <= 3.402823466e38f)) acc[i][j][r] = chain[r];
+        }
+    }
   } else {
     floatx16 part[2][TM][TN];
 #pragma unroll
@@ -356,8 +449,8 @@ __global__ __launch_bounds__(64 * WR * WC, (kMinWaves<BM, BN, A_KMAJOR>)) void k
     }
     const bool direct = K <= kDirectK;
     if (const int rem = (int)(k_end - k_begin - slabs * BK); rem > 0 && !direct) {
-      opa.load_partial(slabs, rem);
-      opb.load_partial(slabs, rem);
+      opa.load_partial(0, slabs, rem);
+      opb.load_partial(0, slabs, rem);
       const bool odd = slabs & 1;
       __syncthreads();  // the buffers have been read
       store(0, odd, lds[0]);
@@ -623,7 +716,7 @@ int gemm_pick_split_k(int64_t M, int N, int64_t K) {
   return want < 1 ? 1 : (int)want;
 }
 
-template <int BM, int BN, int WR, int WC, bool AK, bool BKC, bool EPI, bool CHAIN>
+template <int BM, int BN, int WR, int WC, bool AK, bool BKC, bool EPI, Mode MODE>
 static gnn_status_t launch(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
                            float* c, int64_t ldc, int split_k, float* partials, const AttnEpilogue& epi,
                            hipStream_t s) {
@@ -636,20 +729,26 @@ static gnn_status_t launch(int64_t M, int N, int64_t K, const float* a, int64_t 
   ProfScope p(EPI ? "gemm_f32_mfma_attn" : split_k > 1 ? "gemm_f32_mfma_splitk" : "gemm_f32_mfma", s);
   float* out = split_k > 1 ? partials : c;
   const int64_t ldo = split_k > 1 ? N : ldc;
-  k_gemm_f32<BM, BN, WR, WC, AK, BKC, EPI, CHAIN><<<(unsigned)grid, 64 * WR * WC, 0, s>>>(
+  k_gemm_f32<BM, BN, WR, WC, AK, BKC, EPI, MODE><<<(unsigned)grid, 64 * WR * WC, 0, s>>>(
       M, N, K, a, lda, b, ldb, out, ldo, kps, M * (int64_t)N, (int)tm, (int)tn, split_k, epi);
   GNN_LAUNCH_CHECK();
   return GNN_OK;
 }
 
-template <bool AK, bool BKC, bool EPI, bool CHAIN>
+template <bool AK, bool BKC, bool EPI, Mode MODE>
 static gnn_status_t launch_tile(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
                                 float* c, int64_t ldc, int split_k, float* partials, const AttnEpilogue& epi,
                                 hipStream_t s) {
-  const int bn = gemm_tile_cols(N), bm = gemm_tile_rows(M, N, bn, split_k);
+  // The shallow product in 128-column tiles leaves two wavefronts per SIMD, so it takes 64 columns (232965 x 16 x 256:
+  // 41 us against 50), with an epilogue over heads of 64 columns all of them in one wavefront; only one head of more than
+  // 64 columns needs the wide tile.
+  const int bn = MODE == kShallow && N > 32 && (epi.F <= 32 || epi.H > 1) ? 64 : gemm_tile_cols(N), bm = gemm_tile_rows(M, N, bn, split_k);
 #define GNN_GEMM_TILE(...) \
-  return launch<__VA_ARGS__, AK, BKC, EPI, CHAIN>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, epi, s)
+  return launch<__VA_ARGS__, AK, BKC, EPI, MODE>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, epi, s)
   if (bn == 32) GNN_GEMM_TILE(128, 32, 4, 1);
+  if constexpr (MODE == kShallow && EPI) {
+    if (bn == 64 && epi.H > 1 && epi.F == 64) GNN_GEMM_TILE(128, 64, 4, 1);
+  }
   if (bn == 64 && bm == 64) GNN_GEMM_TILE(64, 64, 2, 2);
   if (bn == 64) GNN_GEMM_TILE(128, 64, 2, 2);
   if (bm == 64) GNN_GEMM_TILE(64, 128, 2, 2);
@@ -671,13 +770,21 @@ gnn_status_t gemm_f32(int64_t M, int N, int64_t K, const float* a, int64_t lda, 
   GNN_REQUIRE(split_k == 1 || ldc == N, GNN_ERR_INVALID_ARG,
               "gemm_f32: split-K needs a dense output (ldc == N)");
   const AttnEpilogue none{nullptr, nullptr, nullptr, nullptr, 0, 0};
+  const bool shallow = K <= kShallowK && split_k == 1;
+#define GNN_GEMM_RUN(...) \
+  GNN_TRY((launch_tile<__VA_ARGS__>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)))
   if (a_kmajor) {
-    if (b_kcontig) GNN_TRY((launch_tile<true, true, false, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
-    else GNN_TRY((launch_tile<true, false, false, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
+    if (b_kcontig) GNN_GEMM_RUN(true, true, false, kLoop);
+    else GNN_GEMM_RUN(true, false, false, kLoop);
+  } else if (b_kcontig) {
+    if (shallow) GNN_GEMM_RUN(false, true, false, kShallow);
+    else GNN_GEMM_RUN(false, true, false, kLoop);
   } else {
-    if (b_kcontig) GNN_TRY((launch_tile<false, true, false, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
-    else GNN_TRY((launch_tile<false, false, false, false>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)));
+    if (shallow && K <= kDirectK) GNN_GEMM_RUN(false, false, false, kChain);
+    else if (shallow) GNN_GEMM_RUN(false, false, false, kShallow);
+    else GNN_GEMM_RUN(false, false, false, kLoop);
   }
+#undef GNN_GEMM_RUN
   if (split_k == 1 || c == nullptr) return GNN_OK;
   ProfScope p("gemm_sum_partials", s);
   return sum_partials(M * (int64_t)N, split_k, partials, c, s);
@@ -690,7 +797,7 @@ gnn_status_t gemm_f32_chain(int64_t M, int N, int64_t K, const float* a, int64_t
   GNN_REQUIRE(lda > 0 && ldb > 0 && lda < (1 << 24) && ldb < (1 << 24) && cdiv(M, 32) < (int64_t)INT32_MAX,
               GNN_ERR_UNSUPPORTED, "gemm_f32_chain: sizes out of range");
   const AttnEpilogue none{nullptr, nullptr, nullptr, nullptr, 0, 0};
-  return launch_tile<false, false, false, true>(M, N, K, a, lda, b, ldb, c, ldc, 1, nullptr, none, s);
+  return launch_tile<false, false, false, kChain>(M, N, K, a, lda, b, ldb, c, ldc, 1, nullptr, none, s);
 }
 
 // z = x w with el, er from the epilogue; only for shapes gemm_attn_epilogue_ok() accepts: heads inside
@@ -711,7 +818,8 @@ gnn_status_t gemm_f32_attn(int64_t M, int heads, int f, int64_t K, const float* 
   GNN_REQUIRE(K > 0 && K < (1 << 24) && N < (1 << 24) && cdiv(M, 32) < (int64_t)INT32_MAX, GNN_ERR_UNSUPPORTED,
               "gemm_f32_attn: sizes out of range");
   const AttnEpilogue epi{a_l, a_r, el, er, heads, f};
-  return launch_tile<false, false, true, false>(M, N, K, x, K, w, N, z, N, 1, nullptr, epi, s);
+  if (K <= kShallowK) return launch_tile<false, false, true, kShallow>(M, N, K, x, K, w, N, z, N, 1, nullptr, epi, s);
+  return launch_tile<false, false, true, kLoop>(M, N, K, x, K, w, N, z, N, 1, nullptr, epi, s);
 }
 
 }  // namespace gnn

@@ -33,7 +33,8 @@ def _assert_within_rounding(name, got, a, b):
 
 
 @pytest.mark.parametrize("n,fin,fout", [(31, 15, 4), (64, 16, 32), (65, 17, 36), (129, 31, 64), (33000, 33, 68),
-                                        (66000, 48, 132), (66000, 600, 96), (33001, 130, 20)])
+                                        (66000, 48, 132), (66000, 600, 96), (33001, 130, 20), (33000, 5, 68),
+                                        (66000, 8, 132), (40000, 16, 16), (33000, 17, 28), (300, 30, 260), (900, 32, 32)])
 def test_products_of_every_layout_and_tile(n, fin, fout):
     """A GCN layer on a graph of loops alone is its three products: x w, x^T g and g w^T."""
     import paper_2110_09524_amd as pk
@@ -107,7 +108,8 @@ def test_values_at_the_end_of_the_range(n, fin, fout):
     _assert_within_rounding("the other rows", got[rest], x[rest], w)
 
 
-@pytest.mark.parametrize("n,fin,fout", [(100, 40, 20), (200, 33, 60), (300, 70, 132), (33000, 48, 68), (66000, 96, 132)])
+@pytest.mark.parametrize("n,fin,fout", [(100, 40, 20), (200, 33, 60), (300, 70, 132), (33000, 48, 68), (66000, 96, 132),
+                                        (100, 10, 8), (200, 16, 60), (33000, 29, 68), (900, 32, 132)])
 def test_results_beside_infinities_and_nan(n, fin, fout):
     """What is not finite takes the fp32 matrix instruction; every other element keeps the bits it has without that."""
     import paper_2110_09524_amd as pk
