@@ -4,8 +4,8 @@
 // The fp32 MFMA runs at 1/16 of the bf16 rate, so every fp32 operand element is split into three
 // bf16 parts, x = h + m + l (8 + 8 + 8 significand bits: the whole fp32 significand), and a
 // product is the sum of the six partial products h h, h m, m h, m m, h l, l h with fp32
-// accumulators (v_mfma_f32_32x32x16_bf16).  What is left out (m l, l m, l l) is below 2^-26 of the
-// product, less than one fp32 rounding.  bf16 ends 16 binary digits above fp32 (2^-133 against
+// accumulators (v_mfma_f32_32x32x16_bf16).  What is left out (m l, l m, l l) is at most 2^-24 of the
+// product, the largest error of one fp32 rounding (above 2^-26 for one product in eight).  bf16 ends 16 binary digits above fp32 (2^-133 against
 // 2^-149), so below 2^-109 the last part would lose digits: both operands are multiplied by 2^16
 // before they are split, and the result by 2^-32.  A result that is not finite in these units (an
 // infinity or a NaN among the operands, an operand above 2^111, or a sum above 2^96) is taken from
@@ -35,10 +35,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int BK = 16;     // k per slab
 constexpr int kParts = 3;
 constexpr float kScale = 65536.f;  // of either operand
-// Up to this many terms the fp32 MFMA alone: it rounds once per two terms, six partial products up to six times,
-// and the time is that of the launch either way (32768 x 3 x 128: 7.8 us).  EdgeConv step from 3 coordinates, gradient
-// of the first layer against 64 bits, median of 9 inputs: 1.4e-5 split, 4.9e-6 direct (5 terms: 4.3e-8 direct, 3.2e-8 split).
-constexpr int kDirectK = 4;
+// Up to this many terms the fp32 chain alone: it rounds once per term, six partial products up to six times.  Relative
+// error of x w against 64 bits (40000 x K x 64, 2-norm, four inputs), parts and chain: K = 1 3.4e-8 and 2.5e-8, 2 3.4e-8 and
+// 3.1e-8, 3 3.3e-8 and 3.6e-8, 4 3.3e-8 and 4.0e-8, 8 3.1e-8 and 5.4e-8.
+constexpr int kDirectK = 2;
 
 // Attention halves in the epilogue of the projection (Sec. 4, text after Eq. 1: the score splits
 // into a source half <a_l, z[u]> and a destination half <a_r, z[v]>, both per-vertex): el[m, h] =

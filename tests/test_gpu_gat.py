@@ -78,8 +78,8 @@ def test_workload_forward_backward(name):
     compare(c, run_gat(c, stash=False), fwd, bwd)
 
 
-@pytest.mark.parametrize("fin,H,F", [(7, 1, 4), (33, 3, 8), (5, 2, 12), (19, 5, 4), (64, 2, 64), (12, 2, 64), (20, 3, 64), (31, 1, 128), (32, 4, 32),
-                                     (40, 8, 64), (24, 3, 256), (130, 1, 16)])
+@pytest.mark.parametrize("fin,H,F", [(7, 1, 4), (33, 3, 8), (5, 2, 12), (19, 5, 4), (64, 2, 64),
+                                     (12, 2, 64), (20, 3, 64), (31, 1, 128), (32, 4, 32), (40, 8, 64), (24, 3, 256), (130, 1, 16)])
 def test_shapes_heads_and_widths(fin, H, F):
     from gpu_harness import run_gat
     print(f"gat: shape fin={fin} H={H} F={F}", flush=True)

@@ -57,6 +57,34 @@ def test_products_of_every_layout_and_tile(n, fin, fout):
     assert (np.abs(got - xt @ gout.astype(np.float64)) <= bound).all()
 
 
+@pytest.mark.parametrize("fin", [1, 2])
+@pytest.mark.parametrize("n,fout", [(70, 24), (300, 64), (40000, 132)])
+def test_one_and_two_terms_are_rounded_like_fp32(n, fin, fout):
+    """Products of so few terms are the chain of fused multiply-adds, bit for bit: x w alone, with the attention halves in
+    its epilogue, and x^T g of two rows."""
+    import paper_2110_09524_amd as pk
+    import torch
+    from gpu_harness import dev, empty, run_gat
+    from test_gpu_edgeconv import fma_chain
+    from test_gpu_gat import synth
+    print(f"terms: {n} x {fin} x {fout}", flush=True)
+    rng = np.random.default_rng(n + fin)
+    x, w = (rng.standard_normal(s).astype(np.float32) for s in ((n, fin), (fin, fout)))
+    y = empty((n, fout))
+    pk.gnn_linear_fwd(dev(x), dev(w), y)
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy(), fma_chain(x, w))
+    c = synth(rng, np.arange(n + 1, dtype=np.int32), np.arange(n, dtype=np.int32), fin, fout // 4, 4)
+    assert np.array_equal(run_gat(c)["z"].reshape(n, -1), fma_chain(c["x"], c["w"]))
+    g = pk.Graph(dev(np.arange(fin + 1, dtype=np.int32)), dev(np.arange(fin, dtype=np.int32)))
+    one, gw = dev(np.ones(fin, np.float32)), empty((n, fout))
+    ws = torch.empty(max(pk.gnn_gcn_workspace_bytes(g, n, fout), 16), dtype=torch.uint8, device="cuda")
+    pk.gnn_gcn_bwd(g, n, fout, dev(np.ascontiguousarray(x.T)), dev(np.zeros((n, fout), np.float32)), one, one, dev(w), None,
+                   gw, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(gw.cpu().numpy(), fma_chain(x, w))
+
+
 @pytest.mark.parametrize("n,fin,fout", [(90, 8, 16), (100, 40, 20), (200, 33, 60), (300, 70, 132), (33000, 48, 68),
                                         (66000, 96, 132)])
 def test_equal_rows_have_equal_products(n, fin, fout):
