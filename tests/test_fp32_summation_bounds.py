@@ -11,10 +11,12 @@ row_scale for the unnormalised sums of hub rows).  Everything else in the GPU te
 the literal bound.
 """
 import numpy as np
+import pytest
+import torch
 
 from oracle import gat as og
 from oracle import gmm as ogmm
-from helpers import tiny_graph
+from helpers import PRODUCT_RTOL, relative_error, tiny_graph
 from workloads import make
 
 RTOL, ATOL = 1e-4, 1e-5
@@ -83,3 +85,25 @@ def test_unnormalised_hub_row_sum_in_fp32_misses_the_literal_bound():
     assert misses > 0 and worst > 2.0
     row_tol = ATOL * np.maximum(1.0, np.abs(ref).max(axis=1, keepdims=True)) + RTOL * np.abs(ref)
     assert (err <= row_tol).all()                # the row-scaled bound holds for the plain fp32 sum
+
+
+@pytest.mark.parametrize("n,k,f", [(129, 17, 20), (200, 96, 132), (300, 600, 96), (40, 5000, 64)])
+def test_a_lost_partial_product_shows(n, k, f):
+    """The operands of the product tests in three bf16 parts: all six partial products are far inside the 2-norm that the
+    tests allow, any five of them outside."""
+    rng = np.random.default_rng(n + k)
+
+    def parts(x):
+        rest, out = torch.from_numpy(x), []
+        for _ in range(3):
+            out.append(rest.bfloat16().float())
+            rest = rest - out[-1]
+        return [p.double().numpy() for p in out]
+
+    a, b = (rng.standard_normal(s).astype(np.float32) for s in ((n, k), (k, f)))
+    pa, pb = parts(a), parts(b)
+    terms = [pa[i] @ pb[j] for i, j in ((0, 0), (0, 1), (1, 0), (1, 1), (0, 2), (2, 0))]
+    ref = a.astype(np.float64) @ b.astype(np.float64)
+    assert relative_error(sum(terms), ref) < PRODUCT_RTOL / 50
+    for t in terms:
+        assert relative_error(sum(terms) - t, ref) > 2 * PRODUCT_RTOL
