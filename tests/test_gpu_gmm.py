@@ -9,7 +9,8 @@ from workloads import make
 pytestmark = pytest.mark.gpu
 
 
-def check(c, gx_row_scale=False, **kw):
+def check(c, gx_row_scale_from=None, **kw):
+    """gx_row_scale_from: rows of gx with at least so many out-edges get a bound that scales with the row."""
     from gpu_harness import assert_close, run_gmm
     args = (c["indptr"], c["indices"], c["x"], c["w_fc"], c["c"], c["mu"], c["inv_sigma"])
     fwd = om.gmm_forward(*args)
@@ -21,7 +22,13 @@ def check(c, gx_row_scale=False, **kw):
     if not aggregate_first:      # hk is only written when the layer projects before it aggregates
         assert_close("hk", res["hk"], fwd["Hk"].reshape(n, -1))
     assert_close("out", res["out"], fwd["out"])
-    assert_close("gx", res["gx"], bwd["gx"], row_scale=gx_row_scale)
+    if gx_row_scale_from is None:
+        assert_close("gx", res["gx"], bwd["gx"])
+    else:
+        long = np.bincount(c["indices"], minlength=n) >= gx_row_scale_from
+        assert long.any() and not long.all()
+        assert_close("gx, short rows", res["gx"][~long], bwd["gx"][~long])
+        assert_close("gx, long rows", res["gx"][long], bwd["gx"][long], row_scale=True)
     assert_close("gw_fc", res["gw_fc"], bwd["gw_fc"], reduce_scale=True)
     assert_close("gmu", res["gmu"], bwd["gmu"])
     assert_close("ginv_sigma", res["ginv_sigma"], bwd["ginv_sigma"])
@@ -97,12 +104,12 @@ def edge_balanced():
 
 @pytest.mark.parametrize("name", ["gmm_c5_mid", "gmm_c5"])
 def test_edge_balanced_workloads(edge_balanced, name):
-    # The runs of a hub row are added by atomics, in an order that differs from call to call.  A row of d = 1300
-    # out-edges in runs of 64 takes 64 + d / 64 = 84 roundings, each up to 2^-24 of the partial sum: as a random
+    # The runs of a hub row are added by atomics, in an order that differs from call to call; it takes three runs of 64 for
+    # the order to show, so shorter rows keep the literal bound.  A row of d = 1300 out-edges in runs of 64 takes 64 + d / 64 = 84 roundings, each up to 2^-24 of the partial sum: as a random
     # walk 9 * 6e-8 = 5e-7 of the row's scale, and 5 times that for the worst of 6.4 million entries, 3e-6.  Its
     # entries reach 30, so the literal 1e-5 for a cancelled entry is below one such walk (1 call in 5 missed it).
     print("gmm: edge-balanced", name, flush=True)
-    check(make(name), gx_row_scale=True)
+    check(make(name), gx_row_scale_from=66)
 
 
 @pytest.mark.parametrize("fin,fout,K", [(5, 16, 1), (9, 16, 4), (64, 64, 3), (6, 4, 2), (7, 256, 3), (20, 24, 2),
