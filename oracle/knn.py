@@ -9,11 +9,22 @@ neighbour to the point.  The result is the CSR by destination with sources ascen
 Floating point decides integers here, so the precision is part of the definition: the
 squared distance is accumulated in float32, coordinate by coordinate in index order, with
 d_i = a_i - b_i rounded first, d0*d0 rounded, and each further square added by one fused
-multiply-add, fma(d2, d2, fma(d1, d1, d0*d0)).  In float64 a square of floats is exact and the
-sum is rounded once more before it becomes a float32, which differs from the fused operation
-in about one of 2^29 sums.
+multiply-add, fma(d2, d2, fma(d1, d1, d0*d0)).
 """
 import numpy as np
+
+
+def square_plus(diff, acc):
+    """fma(diff, diff, acc) of float32 arrays, rounded once.  The square is exact in float64; the sum is rounded to
+    odd there (the last bit set where it was inexact), after which rounding to float32 is what rounding the
+    exact sum would give, since float64 has more than two bits to spare."""
+    a, b = diff.astype(np.float64) ** 2, acc.astype(np.float64)
+    s = a + b
+    t = s - a
+    rest = (a - (s - t)) + (b - t)                  # exact: a + b = s + rest
+    even = (s.view(np.int64) & 1) == 0
+    s = np.where((rest != 0) & even, np.nextafter(s, np.where(rest > 0, np.inf, -np.inf)), s)
+    return s.astype(np.float32)
 
 
 def squared_distances_f32(cloud):
@@ -22,9 +33,7 @@ def squared_distances_f32(cloud):
     P, D = c.shape
     acc = np.zeros((P, P), dtype=np.float32)
     for i in range(D):
-        diff = (c[:, None, i] - c[None, :, i]).astype(np.float32)
-        wide = diff.astype(np.float64)
-        acc = (acc + wide * wide).astype(np.float32)      # the first sum starts at zero
+        acc = square_plus((c[:, None, i] - c[None, :, i]).astype(np.float32), acc)      # the first sum starts at zero
     return acc
 
 

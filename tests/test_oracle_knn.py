@@ -1,4 +1,6 @@
 """Pins of the k-nearest-neighbour oracle: cases with a known answer, brute force, the fp64 generator."""
+from fractions import Fraction
+
 import numpy as np
 
 from oracle import knn as ok
@@ -27,6 +29,28 @@ def test_duplicate_points_tie_to_the_lower_index():
     assert (nb == np.array([0, 1])).all()
 
 
+def nearest_float32(q):
+    """The float32 nearest to a non-negative fraction in the normal range, ties to even, with whole numbers alone."""
+    if q == 0:
+        return Fraction(0)
+    e = q.numerator.bit_length() - q.denominator.bit_length()
+    e -= q < Fraction(2) ** e                       # 2^e <= q < 2^(e+1)
+    ulp = Fraction(2) ** (e - 23)
+    return round(q / ulp) * ulp                     # round() of a fraction goes to even
+
+
+def test_the_fused_step_is_rounded_once():
+    """Random operands, and 4097^2, half way between two floats, plus something too small for a double to hold."""
+    rng = np.random.default_rng(3)
+    diff = np.append(rng.random(3000, dtype=np.float32), np.float32([4097, 4097, 4099, 0]))
+    acc = np.append((rng.random(3000) * 2.0 ** rng.integers(-40, 3, 3000)).astype(np.float32),
+                    np.float32([2.0 ** -40, 0, 2.0 ** -40, 0]))
+    got = ok.square_plus(diff, acc)
+    for d, a, g in zip(diff, acc, got):
+        assert Fraction(float(g)) == nearest_float32(Fraction(float(d)) ** 2 + Fraction(float(a)))
+    assert got[3000] == 4097 ** 2 + 1 and got[3001] == 4097 ** 2 - 1
+
+
 def test_against_brute_force_in_python_loops():
     rng = np.random.default_rng(7)
     clouds, P, D, k = 2, 23, 3, 5
@@ -36,11 +60,11 @@ def test_against_brute_force_in_python_loops():
         for i in range(P):
             cand = []
             for j in range(P):
-                acc = np.float32(0)
+                acc = Fraction(0)
                 for d in range(D):
                     diff = np.float32(coords[b * P + i, d] - coords[b * P + j, d])
-                    acc = np.float32(acc + np.float32(diff * diff))
-                cand.append((float(acc), j))
+                    acc = nearest_float32(acc + Fraction(float(diff)) ** 2)
+                cand.append((acc, j))
             want = sorted(j + b * P for _, j in sorted(cand)[:k])
             assert indices[(b * P + i) * k:(b * P + i + 1) * k].tolist() == want
 
