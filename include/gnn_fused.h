@@ -202,7 +202,7 @@ gnn_status_t gnn_config_set(const char* key, int64_t value);
  * Projection: the ExpensiveApply on vertices, y = x w  (Sec. 3, Sec. 4; App. A.2
  * "H~ = H W").  x [n, fin], w [fin, fout], y [n, fout]; any positive sizes.
  * On the matrix cores: each operand as three bf16 parts, which hold its fp32 significand, fp32 accumulate;
- * tiles with results that are not finite on the fp32 MFMA.  No workspace.
+ * products of one or two terms, and results that are not finite, on the fp32 MFMA.  No workspace.
  * ------------------------------------------------------------------------- */
 gnn_status_t gnn_linear_fwd(int64_t n, int fin, int fout, const float* x, const float* w, float* y,
                             void* stream);

@@ -720,18 +720,31 @@ template <int BM, int BN, int WR, int WC, bool AK, bool BKC, bool EPI, Mode MODE
 static gnn_status_t launch(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
                            float* c, int64_t ldc, int split_k, float* partials, const AttnEpilogue& epi,
                            hipStream_t s) {
-  const int64_t tm = cdiv(M, BM), tn = cdiv(N, BN);
-  // workgroups: whole rounds over the XCDs of the sets of tiles that share rows
-  const int64_t sets = split_k > 1 ? split_k : tm, per = split_k > 1 ? tm * tn : tn;
-  const int64_t grid = cdiv(sets, kXcds) * kXcds * per;
-  GNN_REQUIRE(grid < (int64_t)INT32_MAX, GNN_ERR_UNSUPPORTED, "gemm_f32: grid too large");
+  // A launch may not have 2^32 threads, so products of very many rows go out in pieces of whole tiles (one up to 2^30 rows
+  // of 128-row tiles).  A split product has at most 512 x 128 tiles.
+  constexpr int64_t kMaxGrid = (int64_t)1 << 23;
+  const int64_t tn = cdiv(N, BN);
+  GNN_REQUIRE(tn <= kMaxGrid / kXcds, GNN_ERR_UNSUPPORTED, "gemm_f32: grid too large");
+  const int64_t max_rows = split_k > 1 ? M : kMaxGrid / (kXcds * tn) * kXcds * BM;
   const int64_t kps = split_k > 1 ? cdiv(cdiv(K, split_k), BK) * BK : K;
   ProfScope p(EPI ? "gemm_f32_mfma_attn" : split_k > 1 ? "gemm_f32_mfma_splitk" : "gemm_f32_mfma", s);
-  float* out = split_k > 1 ? partials : c;
-  const int64_t ldo = split_k > 1 ? N : ldc;
-  k_gemm_f32<BM, BN, WR, WC, AK, BKC, EPI, MODE><<<(unsigned)grid, 64 * WR * WC, 0, s>>>(
-      M, N, K, a, lda, b, ldb, out, ldo, kps, M * (int64_t)N, (int)tm, (int)tn, split_k, epi);
-  GNN_LAUNCH_CHECK();
+  for (int64_t m0 = 0; m0 < M; m0 += max_rows) {
+    const int64_t rows = M - m0 < max_rows ? M - m0 : max_rows, tm = cdiv(rows, BM);
+    // workgroups: whole rounds over the XCDs of the sets of tiles that share rows
+    const int64_t sets = split_k > 1 ? split_k : tm, per = split_k > 1 ? tm * tn : tn;
+    const int64_t grid = cdiv(sets, kXcds) * kXcds * per;
+    GNN_REQUIRE(grid <= kMaxGrid, GNN_ERR_UNSUPPORTED, "gemm_f32: grid too large");
+    AttnEpilogue piece = epi;
+    if (EPI) {
+      piece.el += m0 * epi.H;
+      piece.er += m0 * epi.H;
+    }
+    float* out = split_k > 1 ? partials : c + m0 * ldc;
+    const int64_t ldo = split_k > 1 ? N : ldc;
+    k_gemm_f32<BM, BN, WR, WC, AK, BKC, EPI, MODE><<<(unsigned)grid, 64 * WR * WC, 0, s>>>(
+        rows, N, K, a + (AK ? m0 : m0 * lda), lda, b, ldb, out, ldo, kps, M * (int64_t)N, (int)tm, (int)tn, split_k, piece);
+    GNN_LAUNCH_CHECK();
+  }
   return GNN_OK;
 }
 

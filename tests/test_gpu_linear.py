@@ -61,6 +61,22 @@ def test_products_of_every_layout_and_tile(n, fin, fout):
     _assert_within_rounding("x^T g", gw.cpu().numpy(), np.ascontiguousarray(x.T), gout, max(1, min(n // 128, 512)))
 
 
+def test_as_many_rows_as_vertices_can_have():
+    """2^31 - 100 rows: their 128-row tiles have 2^32 threads, more than one launch may."""
+    import paper_2110_09524_amd as pk
+    import torch
+    n = 2 ** 31 - 100
+    print(f"linear: {n} rows", flush=True)
+    x = torch.empty((n, 1), device="cuda")
+    for r in range(0, n, 2 ** 27):
+        x[r:r + 2 ** 27, 0] = torch.randn(min(2 ** 27, n - r), device="cuda")
+    w = torch.tensor([[1.0, -0.3, 1e-3, 7.7]], device="cuda")
+    y = torch.full((n, 4), float("nan"), device="cuda")
+    pk.gnn_linear_fwd(x, w, y)
+    for r in range(0, n, 2 ** 27):
+        assert torch.equal(y[r:r + 2 ** 27], x[r:r + 2 ** 27] * w)
+
+
 @pytest.mark.parametrize("fin", [1, 2])
 @pytest.mark.parametrize("n,fout", [(70, 24), (300, 64), (40000, 132)])
 def test_one_and_two_terms_are_rounded_like_fp32(n, fin, fout):
