@@ -21,6 +21,7 @@
 // in one wavefront the larger of the two).  LDS is laid out [part][k / 8][row], so a wavefront's
 // operand read is two contiguous runs of 512 bytes whatever the operands' layout in HBM (an operand
 // stored k-major is transposed on the way, in registers).
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -233,9 +234,8 @@ __device__ __forceinline__ void chain_product(OpA& opa, OpB& opb, int64_t k_len,
   }
 }
 
-// How a kernel sums up: kLoop over the slabs of bf16 parts; kShallow the same for products of up to kShallowK terms;
-// kChain the whole product as chain_product gives it
-enum Mode { kLoop, kShallow, kChain };
+// How a kernel sums up: kLoop over the slabs of bf16 parts; kShallow the same for products of up to kShallowK terms
+enum Mode { kLoop, kShallow };
 constexpr int kShallowK = 2 * BK;
 
 // Wavefronts per SIMD that the registers have to leave room for: the accumulators of a 128 x 128 tile allow two.  The
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(64 * WR * WC, (kMinWaves<BM, BN, A_KMAJOR>)) void k
   static_assert(TM >= 1 && TN >= 1, "a wavefront owns at least one MFMA tile");
   using OpA = Operand<BM, THREADS, !A_KMAJOR>;
   using OpB = Operand<BN, THREADS, B_KCONTIG>;
-  __shared__ uint4 lds[2][MODE == kChain ? OpA::kChainLds + OpB::kChainLds : OpA::kLds + OpB::kLds];
+  __shared__ uint4 lds[2][OpA::kLds + OpB::kLds];
 
   // Workgroups go to the XCDs round-robin.  All tiles along n of a row of tiles (and all tiles of a
   // k range of a split product) run on one XCD, one after the other: they read the same rows.
@@ -280,15 +280,7 @@ __global__ __launch_bounds__(64 * WR * WC, (kMinWaves<BM, BN, A_KMAJOR>)) void k
   opb.init(B, ldb, n0, N, k_begin);
 
   floatx16 acc[TM][TN];
-  if constexpr (MODE == kChain) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    chain_product(opa, opb, k_end - k_begin, wm0, wn0, lds[0], acc);
-  } else if constexpr (MODE == kShallow) {
+  if constexpr (MODE == kShallow) {
     // Little more than a fetch and a store, so it takes many wavefronts per CU, that is few registers: both slabs at
     // once, one accumulator pair at a time, and the fp32 chain likewise (106 registers for 128 x 64 instead of 164).
     // x w, us, loop -> here (on the fp32 MFMA alone): 232965 x 16 x 64 17.2 -> 15.6 (15.9), x 256 51 -> 41 (45);
@@ -576,6 +568,129 @@ __global__ __launch_bounds__(64 * WR * WC, (kMinWaves<BM, BN, A_KMAJOR>)) void k
   }
 }
 
+// c = a b, a [M,K], b [K,N], every element fma(a[k], b[k], ...) over ascending k: the fp32 MFMA adds its two products one
+// after the other, each with one rounding.  The MFMAs bound it (64 cycles each); while one wavefront issues a slab's
+// worth of them, the vector instructions of the others on its SIMD wait, so the loop keeps those few: uniform addresses,
+// one LDS buffer, the fetch one slab ahead, vectors of 2 floats of A and VB of B (VB = 4 where N and ldb are multiples of
+// 4), three wavefronts per SIMD.  chain_product above, made for the recomputation (two buffers, tile indices in vector
+// registers), takes 12 % longer: 65536 x 128 x 512 93 us here and 104 there, 131072 x 320 x 128 121 and 137.
+template <int BM, int BN, int VB>
+__global__ __launch_bounds__(256, 3) void k_chain_f32(int64_t M, int N, int64_t K, const float* __restrict__ A,
+                                                      int64_t lda, const float* __restrict__ B, int64_t ldb,
+                                                      float* __restrict__ C, int64_t ldc) {
+  constexpr int TM = BM / 64, TN = BN / 64, VA = 2, PAD = 4;
+  constexpr int NA = BM * BK / 256 / VA, NB = BN * BK / 256 / VB;  // loads per thread and slab
+  __shared__ __align__(16) float as[BK][BM + PAD], bs[BK][BN + PAD];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lrow = lane & 31, lk = lane >> 5;
+  const int wm0 = (wave >> 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
+  const int64_t m0 = (int64_t)blockIdx.x * BM;
+  const int n0 = blockIdx.y * BN;
+
+  floatx16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  // load i of a thread: VA consecutive k of a row of A, VB consecutive columns of a row of B; rows and columns past the
+  // matrix are clamped to the last ones (their products are not stored)
+  auto a_row = [](int i) { return (int)(threadIdx.x + 256 * i) / (BK / VA); };
+  auto a_k = [](int i) { return VA * (int)((threadIdx.x + 256 * i) % (BK / VA)); };
+  auto b_k = [](int i) { return (int)(threadIdx.x + 256 * i) / (BN / VB); };
+  auto b_col = [](int i) { return VB * (int)((threadIdx.x + 256 * i) % (BN / VB)); };
+  typedef float vec_a __attribute__((ext_vector_type(VA), aligned(4)));
+  typedef float vec_b __attribute__((ext_vector_type(VB), aligned(4)));
+  uint32_t offa[NA], offb[NB];
+  float ra[NA][VA], rb[NB][VB];
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    const int64_t r = (m0 + a_row(i) < M ? m0 + a_row(i) : M - 1) - m0;
+    offa[i] = (uint32_t)(r * lda + a_k(i));
+  }
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int64_t c = (n0 + b_col(i) <= N - VB ? n0 + b_col(i) : N - VB) - n0;
+    offb[i] = (uint32_t)(b_k(i) * ldb + c);
+  }
+  const float* pa = A + m0 * lda;
+  const float* pb = B + n0;
+  const int64_t step_b = BK * ldb;
+  auto load = [&](int64_t k0) {
+    const int64_t rem = K - k0;
+    if (rem >= BK) {
+#pragma unroll
+      for (int i = 0; i < NA; ++i) {
+        const vec_a v = *reinterpret_cast<const vec_a*>(pa + offa[i]);
+#pragma unroll
+        for (int c = 0; c < VA; ++c) ra[i][c] = v[c];
+      }
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if constexpr (VB == 1) rb[i][0] = pb[offb[i]];
+        else {
+          const vec_b v = *reinterpret_cast<const vec_b*>(pb + offb[i]);
+#pragma unroll
+          for (int c = 0; c < VB; ++c) rb[i][c] = v[c];
+        }
+      }
+    } else {  // the last, partial slab: element by element
+#pragma unroll
+      for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int c = 0; c < VA; ++c) ra[i][c] = a_k(i) + c < rem ? pa[offa[i] + c] : 0.f;
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int c = 0; c < VB; ++c) rb[i][c] = b_k(i) < rem ? pb[offb[i] + c] : 0.f;
+    }
+    pa += BK;
+    pb += step_b;
+  };
+  load(0);
+  for (int64_t k0 = 0; k0 < K; k0 += BK) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int c = 0; c < VA; ++c) as[a_k(i) + c][a_row(i)] = ra[i][c];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      float* dst = &bs[b_k(i)][b_col(i)];
+      if constexpr (VB == 4) *reinterpret_cast<float4*>(dst) = make_float4(rb[i][0], rb[i][1], rb[i][2], rb[i][3]);
+      else *dst = rb[i][0];
+    }
+    __syncthreads();
+    if (k0 + BK < K) load(k0 + BK);
+#pragma unroll
+    for (int ks = 0; ks < BK / 2; ++ks) {
+      const int k = ks * 2 + lk;
+      float a[TM], b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[i] = as[k][wm0 + i * 32 + lrow];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[j] = bs[k][wn0 + j * 32 + lrow];
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int n = n0 + wn0 + j * 32 + lrow;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int64_t m = m0 + wm0 + i * 32 + (r >> 2) * 8 + lk * 4 + (r & 3);
+        if (m < M && n < N) C[m * ldc + n] = acc[i][j][r];
+      }
+    }
+}
+
 // c[i] = sum over z of partials[z][i], z ascending (fixed order => reproducible)
 // c2 != null: elements from index `cut` on go to c2[i - cut] (two results from one launch)
 __device__ __forceinline__ void store_split(float* c, float* c2, int64_t cut, int64_t i, float v) {
@@ -769,6 +884,37 @@ static gnn_status_t launch_tile(int64_t M, int N, int64_t K, const float* a, int
 #undef GNN_GEMM_TILE
 }
 
+template <int BM, int BN, int VB>
+static gnn_status_t launch_chain_tile(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
+                                      float* c, int64_t ldc, hipStream_t s) {
+  // rows and columns of tiles in pieces, so that a launch stays below 2^32 threads along x and 2^16 workgroups along y
+  constexpr int64_t kMaxRows = (int64_t)BM << 23, kMaxCols = (int64_t)BN << 15;
+  ProfScope p("gemm_f32_chain", s);
+  for (int64_t m0 = 0; m0 < M; m0 += kMaxRows)
+    for (int64_t n0 = 0; n0 < N; n0 += kMaxCols) {
+      const int64_t rows = std::min(M - m0, kMaxRows);
+      const int cols = (int)std::min(N - n0, kMaxCols);
+      k_chain_f32<BM, BN, VB><<<dim3((unsigned)cdiv(rows, BM), (unsigned)cdiv(cols, BN)), 256, 0, s>>>(
+          rows, cols, K, a + m0 * lda, lda, b + n0, ldb, c + m0 * ldc + n0, ldc);
+      GNN_LAUNCH_CHECK();
+    }
+  return GNN_OK;
+}
+
+static gnn_status_t launch_chain(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
+                                 float* c, int64_t ldc, hipStream_t s) {
+  const int bn = gemm_tile_cols(N) == 128 ? 128 : 64, bm = gemm_tile_rows(M, N, bn, 1);
+  const bool vec = N % 4 == 0 && ldb % 4 == 0;
+#define GNN_CHAIN_TILE(BM_, BN_)                                                                 \
+  return vec ? launch_chain_tile<BM_, BN_, 4>(M, N, K, a, lda, b, ldb, c, ldc, s)               \
+             : launch_chain_tile<BM_, BN_, 1>(M, N, K, a, lda, b, ldb, c, ldc, s)
+  if (bn == 64 && bm == 64) GNN_CHAIN_TILE(64, 64);
+  if (bn == 64) GNN_CHAIN_TILE(128, 64);
+  if (bm == 64) GNN_CHAIN_TILE(64, 128);
+  GNN_CHAIN_TILE(128, 128);
+#undef GNN_CHAIN_TILE
+}
+
 gnn_status_t gemm_f32(int64_t M, int N, int64_t K, const float* a, int64_t lda, bool a_kmajor,
                       const float* b, int64_t ldb, bool b_kcontig, float* c, int64_t ldc,
                       int split_k, float* partials, hipStream_t s) {
@@ -793,8 +939,8 @@ gnn_status_t gemm_f32(int64_t M, int N, int64_t K, const float* a, int64_t lda, 
     if (shallow) GNN_GEMM_RUN(false, true, false, kShallow);
     else GNN_GEMM_RUN(false, true, false, kLoop);
   } else {
-    if (shallow && K <= kDirectK) GNN_GEMM_RUN(false, false, false, kChain);
-    else if (shallow) GNN_GEMM_RUN(false, false, false, kShallow);
+    if (shallow && K <= kDirectK) return launch_chain(M, N, K, a, lda, b, ldb, c, ldc, s);
+    if (shallow) GNN_GEMM_RUN(false, false, false, kShallow);
     else GNN_GEMM_RUN(false, false, false, kLoop);
   }
 #undef GNN_GEMM_RUN
@@ -809,8 +955,7 @@ gnn_status_t gemm_f32_chain(int64_t M, int N, int64_t K, const float* a, int64_t
   GNN_REQUIRE(K > 0, GNN_ERR_INVALID_ARG, "gemm_f32_chain: K must be positive");
   GNN_REQUIRE(lda > 0 && ldb > 0 && lda < (1 << 24) && ldb < (1 << 24) && cdiv(M, 32) < (int64_t)INT32_MAX,
               GNN_ERR_UNSUPPORTED, "gemm_f32_chain: sizes out of range");
-  const AttnEpilogue none{nullptr, nullptr, nullptr, nullptr, 0, 0};
-  return launch_tile<false, false, false, kChain>(M, N, K, a, lda, b, ldb, c, ldc, 1, nullptr, none, s);
+  return launch_chain(M, N, K, a, lda, b, ldb, c, ldc, s);
 }
 
 // z = x w with el, er from the epilogue; only for shapes gemm_attn_epilogue_ok() accepts: heads inside

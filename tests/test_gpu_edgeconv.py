@@ -115,7 +115,8 @@ def fma_chain(x, w):
 
 
 @pytest.mark.parametrize("n,fin,fout", [(301, 3, 4), (65, 16, 12), (200, 37, 16), (130, 64, 64), (70, 129, 132),
-                                        (33000, 20, 68)])
+                                        (33000, 20, 68),
+                                        (33000, 33, 128), (17000, 16, 516)])
 def test_projection_is_the_chain_of_fused_multiply_adds(n, fin, fout):
     """Every tile of the product that the maximum compares (32, 64 and 128 columns, 64 and 128 rows, whole and partial
     last slabs), bit for bit, and a winner that is the earliest edge with the largest of these values."""

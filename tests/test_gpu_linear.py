@@ -105,6 +105,22 @@ def test_one_and_two_terms_are_rounded_like_fp32(n, fin, fout):
     assert np.array_equal(gw.cpu().numpy(), fma_chain(x, w))
 
 
+@pytest.mark.parametrize("n,fin,fout", [(1, 1, 1), (70, 2, 3), (300, 1, 33), (40000, 2, 131), (66000, 2, 127), (66001, 1, 130)])
+def test_one_and_two_terms_of_any_width(n, fin, fout):
+    """Widths that no vector of four columns divides, on every tile of the chain."""
+    import paper_2110_09524_amd as pk
+    import torch
+    from gpu_harness import dev, empty
+    from test_gpu_edgeconv import fma_chain
+    print(f"terms: {n} x {fin} x {fout}", flush=True)
+    rng = np.random.default_rng(n + fout)
+    x, w = (rng.standard_normal(s).astype(np.float32) for s in ((n, fin), (fin, fout)))
+    y = empty((n, fout))
+    pk.gnn_linear_fwd(dev(x), dev(w), y)
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy(), fma_chain(x, w))
+
+
 @pytest.mark.parametrize("n,fin,fout", [(90, 8, 16), (100, 40, 20), (200, 33, 60), (300, 70, 132), (33000, 48, 68),
                                         (66000, 96, 132)])
 def test_equal_rows_have_equal_products(n, fin, fout):
