@@ -569,7 +569,7 @@ __global__ __launch_bounds__(64 * WR * WC, (kMinWaves<BM, BN, A_KMAJOR>)) void k
 }
 
 // c = a b, a [M,K], b [K,N], every element fma(a[k], b[k], ...) over ascending k: the fp32 MFMA adds its two products one
-// after the other, each with one rounding.  The MFMAs bound it (64 cycles each); while one wavefront issues a slab's
+// after the other, each with one rounding.  The MFMAs (64 cycles each) are busy 60 % of the time; while one wavefront issues a slab's
 // worth of them, the vector instructions of the others on its SIMD wait, so the loop keeps those few: uniform addresses,
 // one LDS buffer, the fetch one slab ahead, vectors of 2 floats of A and VB of B (VB = 4 where N and ldb are multiples of
 // 4), three wavefronts per SIMD.  chain_product above, made for the recomputation (two buffers, tile indices in vector
