@@ -336,3 +336,43 @@ def test_plans_reuse_cached_memory_and_release_it():
     for a, b in zip(csc, again):
         assert torch.equal(a, b)
     g.close()
+
+
+# (sizes of the closed runs, in-degrees): runs that end before, at and after the blocks of 256 vertices and the parts of 128
+# sources, runs of one vertex and of 2048, rows of up to 256 edges, and more than 12 288 edges of 128 sources
+RUNS = [([300] * 30, (3, 4, 5)), ([257] * 40, (0, 1, 2, 7, 8, 9)), ([1] * 700 + [90] * 20, (1, 4, 12, 255)),
+        ([1024] * 9, (20,)), ([1024, 1025, 1023, 1] * 4, (16, 17)), ([2048] * 5, (11, 23)),
+        ([2048, 256, 2047, 1, 512] * 3, (6,)), ([2048, 30, 2047], (3,)), ([256] * 7, (2,)), ([2000], (5,)),
+        ([1] * 257, (0, 1)), ([2048, 2048, 100], (256,)), ([700] * 3, (256, 0)), ([40] * 5 + [300], (257, 4))]
+
+
+@pytest.mark.parametrize("sizes,degrees", RUNS)
+def test_closed_runs_of_vertices(sizes, degrees):
+    """Graphs of runs that no edge leaves are transposed run by run; then one of whose edges join runs, and one whose runs
+    hear from their first vertex only."""
+    print(f"plan: runs {sizes[:4]} degrees {degrees}", flush=True)
+    rng = np.random.default_rng(len(sizes) + degrees[0])
+    first = np.cumsum([0] + list(sizes))
+    n = int(first[-1])
+    deg = rng.choice(degrees, size=n)
+    indptr = np.concatenate(([0], np.cumsum(deg))).astype(np.int32)
+    run = np.repeat(np.repeat(np.arange(len(sizes)), sizes), deg)
+    indices = (first[run] + rng.integers(0, np.array(sizes)[run])).astype(np.int32)
+    _check(indptr, indices)
+    crossing = indices.copy()
+    crossing[rng.integers(0, indices.size, 3)] = rng.integers(0, n, 3)
+    _check(indptr, crossing)
+    _check(indptr, first[run].astype(np.int32))
+
+
+def test_source_outside_a_graph_of_short_rows():
+    import paper_2110_09524_amd as pk
+    from gpu_harness import dev
+    print("plan: source ids out of range", flush=True)
+    indptr = (4 * np.arange(1025)).astype(np.int32)
+    for at, bad in ((0, -1), (4095, 1024), (2000, 2 ** 31 - 1), (77, -2 ** 31)):
+        indices = (np.arange(4096) // 4).astype(np.int32)
+        indices[at] = bad
+        with pytest.raises(pk.GnnError) as e:
+            pk.Graph(dev(indptr), dev(indices))
+        assert e.value.status == 2 and "source id outside" in str(e.value)
