@@ -9,6 +9,9 @@
 // walks the CSC transpose (no atomics); dQ = gout.  Then
 //   [gTheta' | gQ'] = x^T [dP | dQ],  gTheta = gTheta' - gQ',  gPhi = gQ',
 //   gx = [dP | dQ] [Theta | Phi - Theta]^T.
+#include <algorithm>
+#include <atomic>
+
 #include "common.h"
 #include "rowgroup.h"
 
@@ -346,6 +349,269 @@ __global__ __launch_bounds__(kEcBlock) void k_edgeconv_bwd_src_codes(
     }
 }
 
+// ---- tiles in LDS ------------------------------------------------------------------------
+// Where the plan found tiles (runs of vertices that no edge leaves: the clouds of a batch), a workgroup takes one tile
+// and a slice of S columns, which fit the 160 KB of a CU: gathers and scatters then run at the LDS's rate and the
+// memory sees every row once.  Workgroups go to the 8 XCDs round-robin: the slices of a tile follow each other on one XCD, whose L2 then
+// serves the tile's index list and the 128-byte lines that slices of fewer columns share.
+__device__ __forceinline__ bool ec_pick_tile(int n_tiles, int slices, int parts, int& tile, int& slice, int& part) {
+  int k = blockIdx.x / kXcds;
+  part = k % parts;
+  k /= parts;
+  tile = k / slices * kXcds + blockIdx.x % kXcds;
+  slice = k % slices;
+  return tile < n_tiles;
+}
+
+typedef int int4_u __attribute__((ext_vector_type(4), aligned(4)));  // four ints at any int's address
+typedef int int2_u __attribute__((ext_vector_type(2), aligned(4)));
+
+// Forward: the slice of P is staged once and the rows of every vertex's sources are gathered from LDS.  64 clouds of 1024
+// points, 40 neighbours, 256 columns: 166 -> 102 us (268 MB in and out take 56 at the rate of a large copy; the
+// LDS is busy for 45 of them, half of it with bank conflicts between the rows that share a cycle, the vector units for 50).
+template <int S, int T>
+__global__ __launch_bounds__(T) void k_edgeconv_fwd_tile(int n_tiles, int slices, int parts,
+                                                         const int32_t* __restrict__ tile_start,
+                                                         const int32_t* __restrict__ indptr,
+                                                         const int32_t* __restrict__ indices,
+                                                         const float* __restrict__ pq, int F, float* __restrict__ out,
+                                                         int32_t* __restrict__ argmax) {
+  constexpr int L = S / 4, ROWS = T / L;
+  extern __shared__ float4 l_p[];  // [rows of the tile][L]
+  int tile, slice, part;
+  if (!ec_pick_tile(n_tiles, slices, parts, tile, slice, part)) return;
+  const int32_t base = tile_start[tile];
+  int32_t rows = tile_start[tile + 1] - base;
+  const int li = threadIdx.x % L, col = slice * S + 4 * li;
+  const int64_t ld = 2 * (int64_t)F;
+  if (col < F) {
+    const float* src = pq + base * ld + col;
+    int r = threadIdx.x / L;
+    for (; r + 3 * ROWS < rows; r += 4 * ROWS) {
+      float4 p[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) p[k] = ld4(src + (r + k * ROWS) * ld);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) l_p[(r + k * ROWS) * L + li] = p[k];
+    }
+    for (; r < rows; r += ROWS) l_p[r * L + li] = ld4(src + r * ld);
+  }
+  __syncthreads();
+  if (col >= F) return;
+  const float4* mine = l_p + li - (int64_t)base * L;
+  const int2_u none = {0, 0};
+  auto bounds = [&](int r) { return r < rows ? *reinterpret_cast<const int2_u*>(indptr + base + r) : none; };
+  // four sources at position e of a row of at least four, the row's last four when e is beyond them
+  auto four = [&](const int2_u& row, int32_t e) {
+    const int4_u nothing = {0, 0, 0, 0};
+    return row[1] - row[0] >= 4 ? *reinterpret_cast<const int4_u*>(indices + min(e, row[1] - 4)) : nothing;
+  };
+  // a row's bounds are fetched two rows ahead and its first eight sources one row ahead
+  const int per = (rows + parts - 1) / parts;
+  int r = part * per + threadIdx.x / L;
+  rows = min(rows, (part + 1) * per);
+  int2_u row = bounds(r), row1 = bounds(r + ROWS);
+  int4_u ua = four(row, row[0]), ub = four(row, row[0] + 4);
+  for (; r < rows; r += ROWS) {
+    const int64_t v = base + r;
+    const int32_t beg = row[0], end = row[1];
+    const int2_u row2 = bounds(r + 2 * ROWS);
+    const int4_u next_a = four(row1, row1[0]), next_b = four(row1, row1[0] + 4);
+    const float4 q = ld4(pq + v * ld + F + col);
+    float best[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    int32_t arg[4] = {-1, -1, -1, -1};
+    if (end - beg >= 4) {
+      // the largest value, and the four edges that first reached it: 4 operations a column where edge by edge takes 12
+      auto take4 = [&](const int4_u& u, int32_t e) {
+        float4 p[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) p[k] = mine[u[k] * L];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float before = best[c];
+          best[c] = fmaxf(fmaxf(best[c], (&p[0].x)[c]), (&p[1].x)[c]);
+          best[c] = fmaxf(fmaxf(best[c], (&p[2].x)[c]), (&p[3].x)[c]);
+          if (best[c] > before) arg[c] = e;
+        }
+      };
+      // the last four again where the degree is no multiple of four: none of them is above the maximum a second time
+      for (int32_t e = beg; e < end; e += 8) {
+        const int4_u un = four(row, e + 8);
+        take4(ua, min(e, end - 4));
+        ua = un;
+        if (e + 4 < end) {
+          const int4_u um = four(row, e + 12);
+          take4(ub, min(e + 4, end - 4));
+          ub = um;
+        }
+      }
+      // the earliest of the four with that value, and its bits (zeros of either sign are equal)
+      int4_u won[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) won[c] = *reinterpret_cast<const int4_u*>(indices + max(arg[c], beg));
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        float at[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) at[k] = reinterpret_cast<const float*>(mine + won[c][k] * L)[c];
+        const float most = best[c];
+        const int32_t first = arg[c];
+#pragma unroll
+        for (int k = 3; k >= 0; --k)
+          if (first >= 0 && at[k] == most) {
+            best[c] = at[k];
+            arg[c] = first + k;
+          }
+      }
+    } else {
+      for (int32_t e = beg; e < end; ++e) {
+        const float4 p = mine[indices[e] * L];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if ((&p.x)[c] > best[c]) best[c] = (&p.x)[c], arg[c] = e;  // strict '>' keeps the earliest edge on a tie
+      }
+    }
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (beg != end) o = make_float4(best[0] + q.x, best[1] + q.y, best[2] + q.z, best[3] + q.w);
+    st4(out + v * F + col, o);
+    *reinterpret_cast<int4*>(argmax + v * F + col) = make_int4(arg[0], arg[1], arg[2], arg[3]);
+    row = row1;
+    row1 = row2;
+    ua = next_a;
+    ub = next_b;
+  }
+}
+
+// Backward: the winners are scattered.  A thread holds four columns of up to four vertices: it finds the winning
+// sources and adds gout to their sums in LDS.  LDS float atomics take 3 cycles a lane and their order would show in
+// the result, integer ones 8 to 12 a wavefront; so the sums are 64-bit fixed point.  The unit is 2^-28 of the largest
+// power of two among the slice's gradients (but never below fp32's smallest): every term at or above that has all its 24
+// digits on multiples of the unit and up to 2^11 of them stay below 2^63, so the sum is exact, whatever the order,
+// and is rounded once.  Gradients that are smaller still, which few slices have, get a pass of their own
+// with the next unit, and infinities and NaN one before the others.  64 clouds of 1024 points, 40 neighbours, 256 columns:
+// byte codes and walk over the out-edges 189 -> 92 us (268 MB), error against 64 bits 9.8e-8 -> 2.5e-8; 32 clouds, 20
+// neighbours, 64 columns 23 -> 11 us.
+constexpr int kEcFixedRange = 28;
+constexpr int kEcNonFinite = 255;  // exponent field
+
+template <int S, int T>
+__global__ __launch_bounds__(T) void k_edgeconv_bwd_tile(int n_tiles, int slices, const int32_t* __restrict__ tile_start,
+                                                         const int32_t* __restrict__ indptr,
+                                                         const int32_t* __restrict__ indices,
+                                                         const int32_t* __restrict__ argmax,
+                                                         const float* __restrict__ gout, int F, float* __restrict__ dpq) {
+  constexpr int L = S / 4, ROWS = T / L, STEPS = 4, W = T / kWave;  // at most STEPS * ROWS vertices in a tile
+  extern __shared__ unsigned long long l_sum[];                     // [rows of the tile][S]
+  __shared__ int l_top[W], l_low[W];
+  int tile, slice, part;
+  if (!ec_pick_tile(n_tiles, slices, 1, tile, slice, part)) return;
+  const int32_t base = tile_start[tile], rows = tile_start[tile + 1] - base;
+  const int w = threadIdx.x / kWave, li = threadIdx.x % L, col = slice * S + 4 * li;
+  const int64_t ld = 2 * (int64_t)F;
+  auto exponent = [](float v) { return max((__float_as_int(v) >> 23) & 255, 1); };
+  float g[STEPS][4];
+  int at[STEPS][4];
+  int top = 1, low = kEcNonFinite;  // largest exponent, and the smallest of those that are not zero
+#pragma unroll
+  for (int k = 0; k < STEPS; ++k) {
+    const int r = threadIdx.x / L + k * ROWS;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) g[k][c] = 0.f, at[k][c] = -1;
+    if (r < rows && col < F) {
+      const int64_t v = base + r;
+      const int2_u row = *reinterpret_cast<const int2_u*>(indptr + v);
+      const int4 e = *reinterpret_cast<const int4*>(argmax + v * F + col);
+      const float4 go = ld4(gout + v * F + col);
+      const int ee[4] = {e.x, e.y, e.z, e.w};
+      const float gg[4] = {go.x, go.y, go.z, go.w};
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (ee[c] >= row[0] && ee[c] < row[1] && gg[c] != 0.f) {
+          at[k][c] = indices[ee[c]] - base;
+          g[k][c] = gg[c];
+          top = max(top, exponent(gg[c]));
+          low = min(low, exponent(gg[c]));
+        }
+      st4(dpq + v * ld + F + col, row[0] == row[1] ? make_float4(0.f, 0.f, 0.f, 0.f) : go);
+    }
+  }
+  for (int i = threadIdx.x; i < rows * (S / 2); i += T) reinterpret_cast<uint4*>(l_sum)[i] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) low = min(low, __shfl_xor(low, o, kWave));
+  if (threadIdx.x % kWave == 0) l_low[w] = low;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) top = max(top, __shfl_xor(top, o, kWave));
+  if (threadIdx.x % kWave == 0) l_top[w] = top;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < W; ++i) top = max(top, l_top[i]), low = min(low, l_low[i]);
+  auto unit_of = [](int t) { return t == kEcNonFinite ? kEcNonFinite : max(t - kEcFixedRange, 1); };
+  int unit = unit_of(top);
+  // adds the gradients with exponents from `unit` to below `above`; returns this thread's largest exponent below `unit`
+  auto scatter = [&](int above) {
+    int left = 1;
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int bits = __float_as_int(g[k][c]), field = bits >> 23 & 255, x = max(field, 1);
+        if ((unsigned)at[k][c] >= (unsigned)rows || x >= above) continue;
+        unsigned long long* sum = l_sum + at[k][c] * S + 4 * li + c;
+        if (x < unit) {
+          left = max(left, x);
+        } else if (unit == kEcNonFinite) {
+          atomicOr(sum, (bits & 0x7fffff) != 0 ? 4ull : bits < 0 ? 2ull : 1ull);
+        } else {
+          const int digits = (bits & 0x7fffff) | (field != 0 ? 0x800000 : 0);
+          atomicAdd(sum, (unsigned long long)((long long)(bits < 0 ? -digits : digits) << (x - unit)));
+        }
+      }
+    return left;
+  };
+  // the sums in fp32; the unit's value, 2^(unit - 150), is two factors, since it may lie below the normal range
+  auto collect = [&](bool first, bool last) {
+    const float scale = __int_as_float(min(unit, 127) << 23), rest = __int_as_float((unit <= 127 ? 104 : unit - 23) << 23);
+    for (int r = threadIdx.x / L; r < rows && col < F; r += ROWS) {
+      unsigned long long* sum = l_sum + r * S + 4 * li;
+      float* dst = dpq + (base + r) * ld + col;
+      float o[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const long long s = (long long)sum[c];
+        if (unit == kEcNonFinite) o[c] = s == 0 ? 0.f : s == 1 ? INFINITY : s == 2 ? -INFINITY : NAN;
+        else o[c] = (float)s * scale * rest;
+        if (!last) sum[c] = 0;
+      }
+      float4 v = make_float4(o[0], o[1], o[2], o[3]);
+      if (!first) {
+        const float4 so_far = ld4(dst);
+        v = make_float4(so_far.x + v.x, so_far.y + v.y, so_far.z + v.z, so_far.w + v.w);
+      }
+      st4(dst, v);
+    }
+  };
+  if (low >= unit && top != kEcNonFinite) {
+    scatter(kEcNonFinite);
+    __syncthreads();
+    collect(true, true);
+    return;
+  }
+  for (int above = kEcNonFinite + 1;;) {
+    int left = scatter(above);
+    __syncthreads();
+    collect(above > kEcNonFinite, low >= unit);
+    if (low >= unit) return;
+    above = unit;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) left = max(left, __shfl_xor(left, o, kWave));
+    if (threadIdx.x % kWave == 0) l_top[w] = left;
+    __syncthreads();
+    for (int i = 0; i < W; ++i) left = max(left, l_top[i]);
+    unit = unit_of(left);
+    __syncthreads();
+  }
+}
+
 // Degree order (heaviest rows first) balances skewed graphs; when the largest degree is within
 // a small factor of the mean it buys nothing and vertex order keeps neighbourhoods together.
 static bool near_uniform_degrees(const gnn_graph_t* g, int side) {
@@ -405,6 +671,69 @@ struct EcBwdLauncher {
   }
 };
 
+constexpr int kEcTileLds = 144 * 1024;
+constexpr int kEcMinTiles = 4;  // a graph that is a tile or two as a whole gains nothing
+
+// Columns per slice of the forward kernel, 0 where there are no tiles; the widest that fits: rows of 128 bytes have the
+// fewest bank conflicts.  Where tiles and slices do not give every CU a workgroup, several share one, each with
+// its part of the vertices and the whole slice (us, slices of 8 | 16 | 32 columns | 32 and four parts; without tiles first:
+// 64 clouds of 1024 points x 40 neighbours x 256 columns 166: 146 | 112 | 103 | 110; 32 x 1024 x 20 x 64 13: 13 | 16 | 25 | 9;
+// 7 x 1024 x 40 x 128 16: 14 | 20 | 34 | 11).
+static int ec_fwd_tile_cols(const gnn_graph_t* g) {
+  if (g->n_tiles < kEcMinTiles || config_get(kCfgForceSimple)) return 0;
+  return (int64_t)g->max_tile * 32 * sizeof(float) <= kEcTileLds ? 32 : 16;
+}
+
+// The same for the backward kernel.  Its sums are whole columns of a tile, so a CU without a workgroup is avoided with
+// narrower slices (us, without tiles | slices of 8, 16 columns: 64 x 1024 x 40 x 256 189 | 131, 92; 32 x 1024 x 20 x 64
+// 23 | 11, 14), and with fewer than kEcMinWorkgroups even so the kernels without tiles are ahead (2 x 2048 x 20 x 64, 16
+// workgroups, 6 -> 16; 7 x 1024 x 40 x 128, 112 of them, 19 -> 12).
+constexpr int64_t kEcMinWorkgroups = 64;
+static int ec_bwd_tile_cols(const gnn_graph_t* g, int F) {
+  if (g->n_tiles < kEcMinTiles || g->n_tiles * cdiv(F, 8) < kEcMinWorkgroups || config_get(kCfgForceSimple)) return 0;
+  return (int64_t)g->max_tile * 16 * sizeof(int64_t) <= kEcTileLds && g->n_tiles * cdiv(F, 16) >= device_cu_count() ? 16 : 8;
+}
+
+template <int S, int T>
+struct EcTile {
+  static unsigned grid(const gnn_graph_t* g, int F, int parts) {
+    return (unsigned)(cdiv(g->n_tiles, kXcds) * kXcds * cdiv(F, S) * parts);
+  }
+  template <typename K>
+  static gnn_status_t allow_lds(K kernel, std::atomic<bool>& done) {  // more than 64 KB has to be asked for once
+    if (!done.load(std::memory_order_acquire)) {
+      GNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  kEcTileLds));
+      done.store(true, std::memory_order_release);
+    }
+    return GNN_OK;
+  }
+  static gnn_status_t fwd(const gnn_graph_t* g, const float* pq, int F, float* out, int32_t* argmax, hipStream_t st) {
+    static std::atomic<bool> allowed{false};
+    GNN_TRY(allow_lds(k_edgeconv_fwd_tile<S, T>, allowed));
+    const size_t bytes = (size_t)g->max_tile * S * sizeof(float);
+    const int slices = (int)cdiv(F, S);
+    const int64_t most = cdiv(g->max_tile, T / (S / 4));  // a part has a vertex for every group of lanes
+    const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(device_cu_count() / ((int64_t)g->n_tiles * slices), most));
+    ProfScope p("edgeconv_fwd_fused", st);
+    k_edgeconv_fwd_tile<S, T><<<grid(g, F, parts), T, bytes, st>>>(g->n_tiles, slices, parts, g->tile_start, g->indptr,
+                                                                   g->indices, pq, F, out, argmax);
+    GNN_LAUNCH_CHECK();
+    return GNN_OK;
+  }
+  static gnn_status_t bwd(const gnn_graph_t* g, const int32_t* argmax, const float* gout, int F, float* dpq,
+                          hipStream_t st) {
+    static std::atomic<bool> allowed{false};
+    GNN_TRY(allow_lds(k_edgeconv_bwd_tile<S, T>, allowed));
+    const size_t bytes = (size_t)g->max_tile * S * sizeof(int64_t);
+    ProfScope p("edgeconv_bwd_src", st);
+    k_edgeconv_bwd_tile<S, T><<<grid(g, F, 1), T, bytes, st>>>(g->n_tiles, (int)cdiv(F, S), g->tile_start, g->indptr,
+                                                               g->indices, argmax, gout, F, dpq);
+    GNN_LAUNCH_CHECK();
+    return GNN_OK;
+  }
+};
+
 template <template <int, int> class Launcher, typename... Args>
 static gnn_status_t ec_dispatch(GroupShape gs, Args... args) {
   switch (gs.L) {
@@ -443,7 +772,7 @@ static EcWs ec_ws_layout(int64_t n, int fin, int fout) {
 }
 
 static size_t ec_codes_bytes(const gnn_graph_t* g, int fout) {
-  return ec_codes_pay(g, fout) ? ws_granule((size_t)g->n * fout) : 0;
+  return ec_codes_pay(g, fout) && ec_bwd_tile_cols(g, fout) == 0 ? ws_granule((size_t)g->n * fout) : 0;
 }
 
 static gnn_status_t ec_check(const gnn_graph_t* g, int fin, int fout, const char* who) {
@@ -487,6 +816,10 @@ extern "C" gnn_status_t gnn_edgeconv_fwd(const gnn_graph_t* g, int fin, int fout
   // pair within rounding, shared by all rows that see both, sends its gradient rows elsewhere in bulk.  So it is
   // the fp32 chain, which does not depend on tiles or on a row's place: 20 of 16.8 million winners moved with the bf16 parts.
   GNN_TRY(gemm_f32_chain(g->n, 2 * fout, fin, x, fin, wcat, 2 * fout, pq, 2 * fout, st));
+  switch (ec_fwd_tile_cols(g)) {
+    case 32: return EcTile<32, 1024>::fwd(g, pq, fout, out, argmax, st);
+    case 16: return EcTile<16, 1024>::fwd(g, pq, fout, out, argmax, st);
+  }
   return ec_dispatch<EcFwdLauncher>(pick_group(fout), g, (const float*)pq, fout, out, argmax, st);
 }
 
@@ -513,10 +846,18 @@ extern "C" gnn_status_t gnn_edgeconv_bwd(const gnn_graph_t* g, int fin, int fout
   float* part = reinterpret_cast<float*>(base + L.gemm);
   const int64_t n = g->n;
 
-  const size_t codes_bytes = ec_codes_bytes(g, fout);
-  uint32_t* codes =
-      codes_bytes != 0 && ws_bytes >= L.total + codes_bytes ? reinterpret_cast<uint32_t*>(base + L.total) : nullptr;
-  GNN_TRY(ec_dispatch<EcBwdLauncher>(pick_group(fout), g, argmax, gout, fout, codes, dpq, st));
+  const int tile_cols = ec_bwd_tile_cols(g, fout);
+  switch (tile_cols == 8 && g->max_tile > 1024 ? 9 : tile_cols) {
+    case 16: GNN_TRY((EcTile<16, 1024>::bwd(g, argmax, gout, fout, dpq, st))); break;
+    case 9: GNN_TRY((EcTile<8, 1024>::bwd(g, argmax, gout, fout, dpq, st))); break;
+    case 8: GNN_TRY((EcTile<8, 512>::bwd(g, argmax, gout, fout, dpq, st))); break;
+    default: {
+      const size_t codes_bytes = ec_codes_bytes(g, fout);
+      uint32_t* codes =
+          codes_bytes != 0 && ws_bytes >= L.total + codes_bytes ? reinterpret_cast<uint32_t*>(base + L.total) : nullptr;
+      GNN_TRY(ec_dispatch<EcBwdLauncher>(pick_group(fout), g, argmax, gout, fout, codes, dpq, st));
+    }
+  }
   const bool split = L.split_k > 1;
   GNN_TRY(gemm_f32(fin, 2 * fout, n, x, fin, true, dpq, 2 * fout, false, split ? nullptr : gcat, 2 * fout, L.split_k, part,
                    st));

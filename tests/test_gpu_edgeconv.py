@@ -264,3 +264,79 @@ def test_workspace_of_a_graph_without_codes_serves_one_with():
         pk.gnn_edgeconv_bwd(many, fin, fout, x, theta, phi, arg, gout, *grads, ws[:small - 256])
     assert e.value.status == 3
     few.close(), many.close()
+
+
+def _blocks(rng, sizes, degrees):
+    """A graph of closed runs of vertices: run i has sizes[i] of them, and each vertex hears from a random number out of
+    `degrees` of sources of its own run, in any order and with repetitions."""
+    counts, cols, first = [], [], 0
+    for m in sizes:
+        deg = rng.choice(degrees, size=m)
+        counts.append(deg)
+        cols.append(first + rng.integers(0, m, size=int(deg.sum())))
+        first += m
+    indptr = np.concatenate(([0], np.cumsum(np.concatenate(counts)))).astype(np.int32)
+    return indptr, np.concatenate(cols).astype(np.int32)
+
+
+# (sizes of the closed runs, degrees, columns): slices of 32, 16 and 8 columns forward and of 16 and 8 backward with whole and
+# partial last slices, degrees around the four and eight edges of a step, runs of 1 vertex, of 1024 and 1025 (two
+# vertices more than a workgroup takes at once) and of 2048; the last two are no tiles: one edge joins two runs to
+# more than 2048 vertices, and too few workgroups for a GPU
+TILES = [([300] * 30, (3, 4, 5), 64), ([257] * 40, (0, 1, 2, 7, 8, 9), 132), ([1] * 700 + [90] * 20, (1, 4, 12, 255), 260),
+         ([1024] * 9, (20,), 516), ([1024, 1025, 1023, 1] * 4, (16, 17), 68), ([2048] * 5, (11, 23), 256),
+         ([2048, 256, 2047, 1, 512] * 3, (6,), 1024), ([1500, 1500, 200, 200], (9,), 512), ([40] * 5, (4,), 8)]
+
+
+@pytest.mark.parametrize("case", range(len(TILES)))
+@pytest.mark.parametrize("scale", ["plain", "wide", "not finite"])
+def test_tiles_of_closed_runs(case, scale):
+    """Runs of vertices that no edge leaves are worked on in LDS.  Forward: the bits of the kernels that gather from
+    memory.  Backward: dP (read off gx, with theta the identity and phi equal to it) is the exact sum rounded to fp32
+    when all gradients of a run are within 2^28 of each other, at most one more rounding per 28 powers of two otherwise: the
+    bound is 2^-24 of the sum of magnitudes, times the ranges that the gradients span (4 of them at most here), and
+    half an ulp more for a product with one."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import run_edgeconv
+    sizes, degrees, fout = TILES[case]
+    print(f"edgeconv tiles: case {case} {scale}", flush=True)
+    rng = np.random.default_rng(1000 * case + len(scale))
+    indptr, indices = _blocks(rng, sizes, degrees)
+    if case == 7:
+        indices[indptr[5]] = 2000
+    n = indptr.size - 1
+    c = synth(rng, indptr, indices, fout, fout)
+    c["theta"] = np.eye(fout, dtype=np.float32)
+    c["phi"] = c["theta"].copy()
+    c["x"][rng.integers(0, n, 50)] = c["x"][0]                  # ties
+    if scale == "wide":
+        c["gout"] *= np.float32(2.0) ** rng.integers(-100, 0, size=(n, 1)).astype(np.float32)
+    if scale == "not finite":
+        c["gout"][rng.integers(0, n, 9), rng.integers(0, fout, 9)] = (np.inf, -np.inf, np.nan) * 3
+    res = run_edgeconv(c)
+    pk.gnn_config_set("force_simple_kernels", 1)
+    try:
+        ref = run_edgeconv(c)
+    finally:
+        pk.gnn_config_set("force_simple_kernels", 0)
+    for k in ("pq", "out", "argmax"):
+        assert np.array_equal(res[k].view(np.int32), ref[k].view(np.int32)), k
+    arg = res["argmax"]
+    won = arg >= 0
+    dP, mag = np.zeros((n, fout)), np.zeros((n, fout))
+    to = (indices[arg[won]], np.nonzero(won)[1])
+    with np.errstate(invalid="ignore"):
+        np.add.at(dP, to, c["gout"].astype(np.float64)[won])
+        np.add.at(mag, to, np.abs(c["gout"].astype(np.float64))[won])
+    if scale == "not finite":
+        # a row of gx with an infinity in dP or dQ is not finite elsewhere either (0 times infinity): both ways the same
+        assert np.array_equal(np.isfinite(res["gx"]), np.isfinite(ref["gx"]))
+        ok = np.isfinite(dP).all(axis=1) & np.isfinite(c["gout"]).all(axis=1)
+        assert 0 < (~ok).sum() <= 18 and np.isfinite(res["gx"][ok]).all()
+        dP, mag, got = dP[ok], mag[ok], res["gx"][ok]
+    else:
+        got = res["gx"]
+    err = np.abs(got - dP)
+    # without tiles a sum is rounded at every term
+    rounded = np.bincount(indices).max() if case >= 7 else 4 if scale == "wide" else 1
+    assert (err <= 2.0 ** -24 * (rounded * mag + np.abs(dP)) + 2.0 ** -60).all()
