@@ -8,16 +8,18 @@
 //
 // Backward.  dw_j(e) = (1/K) <gout[v], hk[u,j,:]> would need one dot product per
 // edge and kernel; by the distributive law the dot product is taken after the
-// neighbourhood sum instead.  Per destination v and kernel j the kernel aggregates
-//   A_j = sum_e w_j hk[u,j,:],  R_j = sum_e w_j (c[u]-mu_j0) hk[u,j,:],
-//   S_j = sum_e w_j (c[u]-mu_j0)^2 hk[u,j,:]
-// and then, with tA = <gout[v], A_j> etc. (the second coordinate c[v] is constant
-// along a destination row):
-//   gmu[j,0]  += tR is_j0^2 / K             gmu[j,1]  += tA (c[v]-mu_j1) is_j1^2 / K
-//   gis[j,0]  += -tS is_j0 / K              gis[j,1]  += -tA (c[v]-mu_j1)^2 is_j1 / K
-// summed over destinations in a fixed two-stage order.  The source side
-//   dhk[u,j,:] = (1/K) sum over out-edges w_j(e) gout[v,:]
-// walks the CSC transpose (no atomics).
+// neighbourhood sum instead.  Per source u and kernel j one walk over the out-edges (CSC
+// transpose, no atomics) aggregates
+//   A_j = (1/K) sum_e w_j gout[v,:] = dhk[u,j,:],  R_j = (1/K) sum_e w_j (c[v]-mu_j1) gout[v,:],
+//   S_j = (1/K) sum_e w_j (c[v]-mu_j1)^2 gout[v,:]
+// and then, with tA = <hk[u,j,:], A_j> etc. (the first coordinate c[u] is constant along a source's row):
+//   gmu[j,0]  += tA (c[u]-mu_j0) is_j0^2     gmu[j,1]  += tR is_j1^2
+//   gis[j,0]  += -tA (c[u]-mu_j0)^2 is_j0    gis[j,1]  += -tS is_j1
+// summed over the sources in a fixed two-stage order.  Where the tuner finds an edge-balanced mapping faster for one
+// half, the halves are walked apart: dhk as above, and gmu, gis per destination v from the same three
+// sums over its in-edges of hk[u,j,:] with the roles of the two coordinates exchanged.
+#include <algorithm>
+
 #include "common.h"
 #include "rowgroup.h"
 
@@ -290,8 +292,7 @@ __global__ __launch_bounds__(kGmmBlock) void k_gmm_fwd_eb(
 //   out[v] = (1/K) sum_j ( sum_e w_j(e) x[u] ) W_j = (1/K) sum_j agg_j[v] W_j .
 // When the input row is narrower than the K projected rows, an edge then gathers fin floats once
 // instead of K * fout, and the projection becomes one dense product on vertices,
-// out = agg [n, K*fin] . W' [K*fin, fout].  The destination side of backward changes the same way:
-// <gout[v], hk[u,j,:]> = <G_j[v], x[u]> with G = gout W'^T, so it gathers x as well.
+// out = agg [n, K*fin] . W' [K*fin, fout].
 template <int L>
 __global__ __launch_bounds__(kGmmBlock) void k_gmm_fwd_x(
     RowLaunch rl, const int32_t* __restrict__ order, const int32_t* __restrict__ indptr,
@@ -387,130 +388,6 @@ __global__ __launch_bounds__(kGmmBlock) void k_gmm_fwd_x(
       for (int q = 0; q < KB; ++q)
         if (k0 + q < K) st4(agg + ((int64_t)v * K + k0 + q) * fin + 4 * li, acc[q]);
     }
-  }
-}
-
-// destination side of backward on gathered x rows; G [n, K*fin] = gout W'^T.  Partials as k_gmm_bwd_dst.
-template <int L>
-__global__ __launch_bounds__(kGmmBlock) void k_gmm_bwd_dst_x(
-    RowLaunch rl, const int32_t* __restrict__ order, const int32_t* __restrict__ indptr,
-    const int32_t* __restrict__ indices, const float* __restrict__ x, const float* __restrict__ c,
-    const float* __restrict__ mu, const float* __restrict__ inv_sigma, const float* __restrict__ G, int K,
-    int fin, float* __restrict__ partial) {
-  constexpr int GPB = kGmmBlock / L;
-  constexpr int KB = kGmmKB, U = 4;
-  constexpr int GS = (1 + 3 * KB) * L;
-  __shared__ __align__(16) float lds[GPB * GS];
-  __shared__ float blk[GPB][kMaxK][4];
-  __shared__ float coop_buf[GPB * L * 3];
-  const int lane = threadIdx.x & 63;
-  const int li = lane & (L - 1);
-  const int grp = threadIdx.x / L;
-  int64_t r;
-  int gi, ngrp;
-  RowRange rr;
-  const bool active = pick_row<GPB>(rl, grp, rr, r, gi, ngrp);
-  int* l_idx = reinterpret_cast<int*>(lds + grp * GS);
-  float* l_w = lds + grp * GS + L;
-  float* l_wr = l_w + KB * L;
-  float* l_ws = l_wr + KB * L;
-  const float inv_k = 1.f / (float)K;
-  for (int i = li; i < kMaxK * 4; i += L) blk[grp][i >> 2][i & 3] = 0.f;
-  if (active) {
-    const int32_t v = order[r];
-    const int32_t beg = indptr[v], end = indptr[v + 1];
-    const float cv = c[v];
-    const bool col_ok = 4 * li < fin;
-    for (int k0 = 0; k0 < K; k0 += KB) {
-      float mu0[KB], mu1[KB], is0[KB], is1[KB];
-#pragma unroll
-      for (int q = 0; q < KB; ++q) {
-        const bool ok = k0 + q < K;
-        mu0[q] = ok ? mu[2 * (k0 + q)] : 0.f;
-        mu1[q] = ok ? mu[2 * (k0 + q) + 1] : 0.f;
-        is0[q] = ok ? inv_sigma[2 * (k0 + q)] : 0.f;
-        is1[q] = ok ? inv_sigma[2 * (k0 + q) + 1] : 0.f;
-      }
-      float4 aA[KB], aR[KB], aS[KB];
-#pragma unroll
-      for (int q = 0; q < KB; ++q) {
-        aA[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-        aR[q] = aA[q];
-        aS[q] = aA[q];
-      }
-      for (int32_t c0 = beg + gi * L; c0 < end; c0 += ngrp * L) {
-        const bool e_ok = c0 + li < end;
-        const int32_t u = e_ok ? indices[c0 + li] : 0;
-        const float cu = c[u];
-        l_idx[li] = u;
-#pragma unroll
-        for (int q = 0; q < KB; ++q) {
-          const float w = (e_ok && k0 + q < K) ? gauss_w(cu, cv, mu0[q], mu1[q], is0[q], is1[q]) : 0.f;
-          const float d0 = cu - mu0[q];
-          l_w[q * L + li] = w;
-          l_wr[q * L + li] = w * d0;
-          l_ws[q * L + li] = w * d0 * d0;
-        }
-        wave_lds_fence();
-        const int cnt = min(L, end - c0);
-        if (col_ok) {
-          for (int t0 = 0; t0 < cnt; t0 += U) {
-            float4 rowv[U];
-#pragma unroll
-            for (int t = 0; t < U; ++t) {
-              int uu = l_idx[min(t0 + t, L - 1)];
-              if (L == 64) uu = __builtin_amdgcn_readfirstlane(uu);
-              rowv[t] = ld4(x + (int64_t)uu * fin + 4 * li);
-            }
-#pragma unroll
-            for (int t = 0; t < U; ++t) {
-              if (t0 + t < L) {
-#pragma unroll
-                for (int q = 0; q < KB; ++q) {
-                  fma4(aA[q], l_w[q * L + t0 + t], rowv[t]);
-                  fma4(aR[q], l_wr[q * L + t0 + t], rowv[t]);
-                  fma4(aS[q], l_ws[q * L + t0 + t], rowv[t]);
-                }
-              }
-            }
-          }
-        }
-        wave_lds_fence();
-      }
-#pragma unroll
-      for (int q = 0; q < KB; ++q) {
-        if (k0 + q >= K) continue;
-        float tA = 0.f, tR = 0.f, tS = 0.f;
-        if (col_ok) {
-          const float4 g4 = ld4(G + ((int64_t)v * K + k0 + q) * fin + 4 * li);
-          tA = dot4(g4, aA[q]);
-          tR = dot4(g4, aR[q]);
-          tS = dot4(g4, aS[q]);
-        }
-        tA = group_sum_from<L>(tA, 1);
-        tR = group_sum_from<L>(tR, 1);
-        tS = group_sum_from<L>(tS, 1);
-        if (rr.coop) {
-          float vv[3] = {tA, tR, tS};
-          coop_sum<L, 3, GPB>(coop_buf, vv, grp, li);
-          tA = vv[0]; tR = vv[1]; tS = vv[2];
-        }
-        if (li == 0 && (!rr.coop || grp == 0)) {
-          const float d1 = cv - mu1[q];
-          blk[grp][k0 + q][0] = tR * is0[q] * is0[q] * inv_k;
-          blk[grp][k0 + q][1] = tA * d1 * is1[q] * is1[q] * inv_k;
-          blk[grp][k0 + q][2] = -tS * is0[q] * inv_k;
-          blk[grp][k0 + q][3] = -tA * d1 * d1 * is1[q] * inv_k;
-        }
-      }
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < kMaxK * 4) {
-    const int k = threadIdx.x >> 2, q = threadIdx.x & 3;
-    float s = 0.f;
-    for (int g2 = 0; g2 < GPB; ++g2) s += blk[g2][k][q];  // fixed order
-    partial[((int64_t)blockIdx.x * kMaxK + k) * 4 + q] = s;
   }
 }
 
@@ -684,114 +561,148 @@ __global__ void k_gmm_param_split(int K, const float* __restrict__ totals, float
 }
 
 // ---- a10, source side: dhk[u,j,:] = (1/K) sum over out-edges w_j(e) gout[v,:] ----------
-template <int L, int NV>
+// MOMENTS: with R_j and S_j, from which the gradients of mu and inv_sigma come: the destination side need not be walked at
+// all, one gather per edge instead of two.  100 000 vertices, 2 10^6 edges, 64 columns, K = 3, us: destination side 131
+// and this kernel without MOMENTS 70 -> 98.  KB kernels per pass (2, 3 or 4, as many as K where that is one
+// pass); the vector units take 12 KB multiply-adds an edge and lane, the gathers past the L2s bound it.
+template <int L, int KB, bool MOMENTS>
 __global__ __launch_bounds__(kGmmBlock) void k_gmm_bwd_src(
     RowLaunch rl, const int32_t* __restrict__ order_t, const int32_t* __restrict__ indptr_t,
     const int32_t* __restrict__ indices_t, const float* __restrict__ c, const float* __restrict__ mu,
-    const float* __restrict__ inv_sigma, const float* __restrict__ gout, GmmParams pm,
-    float* __restrict__ dhk) {
-  constexpr int G = kWave / L;
-  constexpr int GPB = G * (kGmmBlock / kWave);
-  constexpr int KB = kGmmKB;  // kernels accumulated per pass over the out-edges
-  constexpr int U = 4;        // gathered rows in flight per lane
-  constexpr int NC = 4 * KB * NV;
-  constexpr int GS = (1 + KB) * L;  // LDS floats per group: idx | w[KB][L]
+    const float* __restrict__ inv_sigma, const float* __restrict__ gout, GmmParams pm, float* __restrict__ dhk,
+    const float* __restrict__ hk, float* __restrict__ partial) {
+  constexpr int GPB = kGmmBlock / L;
+  constexpr int U = 4;                 // gathered rows in flight per lane
+  constexpr int WS = KB == 2 ? 2 : 4;  // weights of an edge, read at once
+  constexpr int GS = (2 + WS) * L;     // LDS floats per group: idx | c[v] | weights
+  constexpr int NC = 4 * KB;
   __shared__ __align__(16) float lds[GPB * GS];
   __shared__ float coop_buf[GPB * L * NC];
+  __shared__ float blk[MOMENTS ? GPB : 1][kMaxK][4];
   const int lane = threadIdx.x & 63;
   const int li = lane & (L - 1);
   const int grp = threadIdx.x / L;
   int64_t r;
   int gi, ngrp;
   RowRange rr;
-  if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp)) return;
-  int* l_idx = reinterpret_cast<int*>(lds + grp * GS);
-  float* l_w = lds + grp * GS + L;
-
-  const int K = pm.K, F = pm.F, KF = K * F;
-  const float inv_k = 1.f / (float)K;
-  const int32_t u = order_t[r];
-  const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
-  const float cu = c[u];
-  bool slot_ok[NV];
+  const bool active = pick_row<GPB>(rl, grp, rr, r, gi, ngrp);
+  if (MOMENTS) {
+    for (int i = li; i < kMaxK * 4; i += L) blk[grp][i >> 2][i & 3] = 0.f;
+  } else if (!active) {
+    return;
+  }
+  if (active) {
+    int* l_idx = reinterpret_cast<int*>(lds + grp * GS);
+    float* l_cv = lds + grp * GS + L;
+    float* l_w = l_cv + L;
+    const int K = pm.K, F = pm.F, KF = K * F;
+    const float inv_k = 1.f / (float)K;
+    const int32_t u = order_t[r];
+    const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
+    const float cu = c[u];
+    const bool col_ok = 4 * li < F;
+    for (int k0 = 0; k0 < K; k0 += KB) {
+      float mu0[KB], mu1[KB], is0[KB], is1[KB];
 #pragma unroll
-  for (int j = 0; j < NV; ++j) slot_ok[j] = 4 * (li + j * L) < F;
-
-  for (int k0 = 0; k0 < K; k0 += KB) {
-    float mu0[KB], mu1[KB], is0[KB], is1[KB];
+      for (int q = 0; q < KB; ++q) {
+        const bool ok = k0 + q < K;
+        mu0[q] = ok ? mu[2 * (k0 + q)] : 0.f;
+        mu1[q] = ok ? mu[2 * (k0 + q) + 1] : 0.f;
+        is0[q] = ok ? inv_sigma[2 * (k0 + q)] : 0.f;
+        is1[q] = ok ? inv_sigma[2 * (k0 + q) + 1] : 0.f;
+      }
+      const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+      float4 acc[KB], aR[MOMENTS ? KB : 1], aS[MOMENTS ? KB : 1];
 #pragma unroll
-    for (int q = 0; q < KB; ++q) {
-      const bool ok = k0 + q < K;
-      mu0[q] = ok ? mu[2 * (k0 + q)] : 0.f;
-      mu1[q] = ok ? mu[2 * (k0 + q) + 1] : 0.f;
-      is0[q] = ok ? inv_sigma[2 * (k0 + q)] : 0.f;
-      is1[q] = ok ? inv_sigma[2 * (k0 + q) + 1] : 0.f;
-    }
-    float4 acc[KB][NV];
+      for (int q = 0; q < KB; ++q) {
+        acc[q] = zero;
+        if (MOMENTS) aR[q] = aS[q] = zero;
+      }
+      for (int32_t c0 = beg + gi * L; c0 < end; c0 += ngrp * L) {
+        // chunk phase: lane li owns out-edge c0 + li; edges past the end become vertex 0, weight 0
+        const bool e_ok = c0 + li < end;
+        const int32_t v = e_ok ? indices_t[c0 + li] : 0;
+        const float cv = c[v];
+        l_idx[li] = v;
+        if (MOMENTS) l_cv[li] = cv;
 #pragma unroll
-    for (int q = 0; q < KB; ++q)
+        for (int q = 0; q < KB; ++q)
+          l_w[WS * li + q] = (e_ok && k0 + q < K) ? gauss_w(cu, cv, mu0[q], mu1[q], is0[q], is1[q]) * inv_k : 0.f;
+        wave_lds_fence();
+        float4 part[KB];  // this chunk's share of A (two-level summation)
 #pragma unroll
-      for (int j = 0; j < NV; ++j) acc[q][j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int32_t c0 = beg + gi * L; c0 < end; c0 += ngrp * L) {
-      // chunk phase: lane li owns out-edge c0 + li; edges past the end become vertex 0, weight 0
-      const bool e_ok = c0 + li < end;
-      const int32_t v = e_ok ? indices_t[c0 + li] : 0;
-      const float cv = c[v];
-      l_idx[li] = v;
-#pragma unroll
-      for (int q = 0; q < KB; ++q)
-        l_w[q * L + li] = (e_ok && k0 + q < K) ? gauss_w(cu, cv, mu0[q], mu1[q], is0[q], is1[q]) * inv_k : 0.f;
-      wave_lds_fence();
-      float4 part[KB][NV];  // this chunk's share (two-level summation)
-#pragma unroll
-      for (int q = 0; q < KB; ++q)
-#pragma unroll
-        for (int j = 0; j < NV; ++j) part[q][j] = make_float4(0.f, 0.f, 0.f, 0.f);
-      const int cnt = min(L, end - c0);
-      for (int t0 = 0; t0 < cnt; t0 += U) {
-        int vv[U];
-#pragma unroll
-        for (int t = 0; t < U; ++t) {
-          vv[t] = l_idx[t0 + t];
-          if (L == 64) vv[t] = __builtin_amdgcn_readfirstlane(vv[t]);
-        }
-#pragma unroll
-        for (int j = 0; j < NV; ++j) {
-          if (!slot_ok[j]) continue;
+        for (int q = 0; q < KB; ++q) part[q] = zero;
+        const int cnt = min(L, end - c0);
+        for (int t0 = 0; t0 < cnt; t0 += U) {
+          const int4 idx4 = *reinterpret_cast<const int4*>(l_idx + t0);
+          int vv[U] = {idx4.x, idx4.y, idx4.z, idx4.w};
+          float cvv[U];
+          if (MOMENTS) pack4(cvv, *reinterpret_cast<const float4*>(l_cv + t0));
           float4 rowv[U];
 #pragma unroll
-          for (int t = 0; t < U; ++t) rowv[t] = ld4(gout + (int64_t)vv[t] * F + 4 * (li + j * L));
+          for (int t = 0; t < U; ++t) {
+            if (L == 64) vv[t] = __builtin_amdgcn_readfirstlane(vv[t]);
+            rowv[t] = col_ok ? ld4(gout + (int64_t)vv[t] * F + 4 * li) : zero;
+          }
 #pragma unroll
-          for (int t = 0; t < U; ++t)
+          for (int t = 0; t < U; ++t) {
+            float w[4];
+            if constexpr (WS == 4) pack4(w, *reinterpret_cast<const float4*>(l_w + 4 * (t0 + t)));
+            else *reinterpret_cast<float2*>(w) = *reinterpret_cast<const float2*>(l_w + 2 * (t0 + t));
 #pragma unroll
-            for (int q = 0; q < KB; ++q) fma4(part[q][j], l_w[q * L + t0 + t], rowv[t]);
+            for (int q = 0; q < KB; ++q) {
+              fma4(part[q], w[q], rowv[t]);
+              if (MOMENTS) {
+                const float d = cvv[t] - mu1[q], wd = w[q] * d;
+                fma4(aR[q], wd, rowv[t]);
+                fma4(aS[q], wd * d, rowv[t]);
+              }
+            }
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < KB; ++q) add4(acc[q], part[q]);
+        wave_lds_fence();
+      }
+      if (MOMENTS) {  // linear in the sums: the groups of a shared row each add what they have
+#pragma unroll
+        for (int q = 0; q < KB; ++q) {
+          if (k0 + q >= K) continue;
+          const float4 h = col_ok ? ld4(hk + (int64_t)u * KF + (k0 + q) * F + 4 * li) : zero;
+          const float tA = group_sum_from<L>(dot4(h, acc[q]), 1);
+          const float tR = group_sum_from<L>(dot4(h, aR[q]), 1);
+          const float tS = group_sum_from<L>(dot4(h, aS[q]), 1);
+          if (li == 0) {
+            const float d0 = cu - mu0[q];
+            blk[grp][k0 + q][0] = tA * d0 * is0[q] * is0[q];
+            blk[grp][k0 + q][1] = tR * is1[q] * is1[q];
+            blk[grp][k0 + q][2] = -tA * d0 * d0 * is0[q];
+            blk[grp][k0 + q][3] = -tS * is1[q];
+          }
         }
       }
+      if (rr.coop) {
+        float vv[NC];
 #pragma unroll
-      for (int q = 0; q < KB; ++q)
+        for (int q = 0; q < KB; ++q) pack4(vv + 4 * q, acc[q]);
+        coop_sum<L, NC, GPB>(coop_buf, vv, grp, li);
 #pragma unroll
-        for (int j = 0; j < NV; ++j) add4(acc[q][j], part[q][j]);
-      wave_lds_fence();
+        for (int q = 0; q < KB; ++q) acc[q] = unpack4(vv + 4 * q);
+      }
+      if (col_ok && (!rr.coop || grp == 0)) {
+#pragma unroll
+        for (int q = 0; q < KB; ++q)
+          if (k0 + q < K) st4(dhk + (int64_t)u * KF + (k0 + q) * F + 4 * li, acc[q]);
+      }
     }
-    if (rr.coop) {
-      float vv[NC];
-#pragma unroll
-      for (int q = 0; q < KB; ++q)
-#pragma unroll
-        for (int j = 0; j < NV; ++j) pack4(vv + 4 * (q * NV + j), acc[q][j]);
-      coop_sum<L, NC, GPB>(coop_buf, vv, grp, li);
-#pragma unroll
-      for (int q = 0; q < KB; ++q)
-#pragma unroll
-        for (int j = 0; j < NV; ++j) acc[q][j] = unpack4(vv + 4 * (q * NV + j));
+  }
+  if (MOMENTS) {
+    __syncthreads();
+    if (threadIdx.x < kMaxK * 4) {
+      float sum = 0.f;
+      for (int g2 = 0; g2 < GPB; ++g2) sum += blk[g2][threadIdx.x >> 2][threadIdx.x & 3];  // fixed order
+      partial[(int64_t)blockIdx.x * kMaxK * 4 + threadIdx.x] = sum;
     }
-    if (!rr.coop || grp == 0)
-#pragma unroll
-    for (int q = 0; q < KB; ++q)
-      if (k0 + q < K)
-#pragma unroll
-        for (int j = 0; j < NV; ++j)
-          if (slot_ok[j]) st4(dhk + (int64_t)u * KF + (k0 + q) * F + 4 * (li + j * L), acc[q][j]);
   }
 }
 
@@ -1137,34 +1048,21 @@ struct GmmFwdXLauncher {
   }
 };
 
-template <int L, int NV>
-struct GmmBwdDstXLauncher {
-  static gnn_status_t run(const gnn_graph_t* g, const float* x, const float* c, const float* mu,
-                          const float* is, const float* G, int K, int fin, float* partial, float* gmu,
-                          float* gis, hipStream_t st) {
-    constexpr int GPB = kGmmBlock / L;
-    ProfScope p("gmm_bwd_dst", st);
-    const RowSplit sp = split_rows(g, 0, L, GPB);
-    const unsigned grid = sp.hub_grid + sp.rest_grid;
-    const RowLaunch rl{sp.hub.end, g->n};
-    if (grid != 0) {
-      k_gmm_bwd_dst_x<L><<<grid, kGmmBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, x, c, mu, is, G, K,
-                                                    fin, partial);
-      GNN_LAUNCH_CHECK();
-    }
-    float* totals = partial + (int64_t)grid * kMaxK * 4;
-    GNN_TRY(sum_partials_two_level(kMaxK * 4, (int)grid, partial, totals + kMaxK * 4, totals, st));
-    k_gmm_param_split<<<1, 64, 0, st>>>(K, totals, gmu, gis);
-    GNN_LAUNCH_CHECK();
-    return GNN_OK;
-  }
-};
+// gradients of mu and inv_sigma from the workgroups' partial sums; behind their slots lie one for the totals and the
+// second-level scratch
+static gnn_status_t gmm_param_sums(int K, unsigned grid, float* partial, float* gmu, float* gis, hipStream_t st) {
+  float* totals = partial + (int64_t)grid * kMaxK * 4;
+  GNN_TRY(sum_partials_two_level(kMaxK * 4, (int)grid, partial, totals + kMaxK * 4, totals, st));
+  k_gmm_param_split<<<1, 64, 0, st>>>(K, totals, gmu, gis);
+  GNN_LAUNCH_CHECK();
+  return GNN_OK;
+}
 
-// number of workgroups (= partial slots) the destination-side kernel uses
+// number of workgroups (= partial slots) of the kernels that sum the gradients of mu and inv_sigma
 template <int L>
-static int64_t gmm_dst_blocks(const gnn_graph_t* g) {
+static int64_t gmm_blocks(const gnn_graph_t* g, int side) {
   constexpr int GPB = (kWave / L) * (kGmmBlock / kWave);
-  const RowSplit sp = split_rows(g, 0, L, GPB);
+  const RowSplit sp = split_rows(g, side, L, GPB);
   return (int64_t)sp.hub_grid + sp.rest_grid;
 }
 
@@ -1184,31 +1082,41 @@ struct GmmBwdDstLauncher {
                                                        gout, pm, partial);
       GNN_LAUNCH_CHECK();
     }
-    // after the block slots: one slot for the totals, then the second-level scratch
-    float* totals = partial + (int64_t)grid * kMaxK * 4;
-    GNN_TRY(sum_partials_two_level(kMaxK * 4, (int)grid, partial, totals + kMaxK * 4, totals, st));
-    k_gmm_param_split<<<1, 64, 0, st>>>(pm.K, totals, gmu, gis);
-    GNN_LAUNCH_CHECK();
-    return GNN_OK;
+    return gmm_param_sums(pm.K, grid, partial, gmu, gis, st);
   }
 };
 
+// hk == nullptr: dhk alone
 template <int L, int NV>
 struct GmmBwdSrcLauncher {
+  template <int KB, bool MOMENTS>
+  static gnn_status_t launch(const gnn_graph_t* g, const RowLaunch& rl, unsigned grid, const float* c, const float* mu,
+                             const float* is, const float* gout, GmmParams pm, float* dhk, const float* hk,
+                             float* partial, hipStream_t st) {
+    k_gmm_bwd_src<L, KB, MOMENTS><<<grid, kGmmBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, c, mu, is, gout,
+                                                              pm, dhk, hk, partial);
+    GNN_LAUNCH_CHECK();
+    return GNN_OK;
+  }
   static gnn_status_t run(const gnn_graph_t* g, const float* c, const float* mu, const float* is,
-                          const float* gout, GmmParams pm, float* dhk, hipStream_t st) {
+                          const float* gout, GmmParams pm, float* dhk, const float* hk, float* partial, float* gmu,
+                          float* gis, hipStream_t st) {
     constexpr int GPB = (kWave / L) * (kGmmBlock / kWave);
-    ProfScope p("gmm_bwd_src", st);
+    ProfScope p(hk != nullptr ? "gmm_bwd" : "gmm_bwd_src", st);
     const RowSplit sp = split_rows(g, 1, L, GPB);
     // hub rows (one workgroup each) and the rest in one launch
     const unsigned grid = sp.hub_grid + sp.rest_grid;
     const RowLaunch rl{sp.hub.end, g->n};
+#define GNN_GMM_SRC(KB_)                                                                                     \
+  GNN_TRY(hk != nullptr ? (launch<KB_, true>(g, rl, grid, c, mu, is, gout, pm, dhk, hk, partial, st))        \
+                        : (launch<KB_, false>(g, rl, grid, c, mu, is, gout, pm, dhk, hk, partial, st)))
     if (grid != 0) {
-      k_gmm_bwd_src<L, NV><<<grid, kGmmBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, c, mu, is,
-                                                       gout, pm, dhk);
-      GNN_LAUNCH_CHECK();
+      if (pm.K <= 2) GNN_GMM_SRC(2);
+      else if (pm.K == 3) GNN_GMM_SRC(3);
+      else GNN_GMM_SRC(4);
     }
-    return GNN_OK;
+#undef GNN_GMM_SRC
+    return hk != nullptr ? gmm_param_sums(pm.K, grid, partial, gmu, gis, st) : GNN_OK;
   }
 };
 
@@ -1225,11 +1133,7 @@ struct GmmBwdDstEbLauncher {
                                                           is, gout, pm, partial);
       GNN_LAUNCH_CHECK();
     }
-    float* totals = partial + (int64_t)grid * kMaxK * 4;
-    GNN_TRY(sum_partials_two_level(kMaxK * 4, (int)grid, partial, totals + kMaxK * 4, totals, st));
-    k_gmm_param_split<<<1, 64, 0, st>>>(pm.K, totals, gmu, gis);
-    GNN_LAUNCH_CHECK();
-    return GNN_OK;
+    return gmm_param_sums(pm.K, grid, partial, gmu, gis, st);
   }
 };
 
@@ -1301,13 +1205,13 @@ struct GmmWs {
   int64_t nblk;
 };
 
-static int64_t gmm_dst_blocks_for(const gnn_graph_t* g, int width) {
+static int64_t gmm_blocks_for(const gnn_graph_t* g, int side, int width) {
   switch (pick_group(width).L) {
-    case 4: return gmm_dst_blocks<4>(g);
-    case 8: return gmm_dst_blocks<8>(g);
-    case 16: return gmm_dst_blocks<16>(g);
-    case 32: return gmm_dst_blocks<32>(g);
-    default: return gmm_dst_blocks<64>(g);
+    case 4: return gmm_blocks<4>(g, side);
+    case 8: return gmm_blocks<8>(g, side);
+    case 16: return gmm_blocks<16>(g, side);
+    case 32: return gmm_blocks<32>(g, side);
+    default: return gmm_blocks<64>(g, side);
   }
 }
 
@@ -1317,11 +1221,7 @@ static GmmWs gmm_ws_layout(const gnn_graph_t* g, int fin, int fout, int K) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += ws_granule(bytes); return o; };
   const bool xg = gmm_aggregate_first(fin, fout, K);
-  w.nblk = gmm_dst_blocks_for(g, fout);
-  if (xg) {
-    const int64_t nb = gmm_dst_blocks_for(g, fin);
-    if (nb > w.nblk) w.nblk = nb;
-  }
+  w.nblk = std::max(gmm_blocks_for(g, 0, fout), gmm_blocks_for(g, 1, fout));
   if (K <= kGmmKB) {  // the edge-balanced destination side: one slot per workgroup of runs
     const int64_t nb = cdiv(cdiv(g->nnz, kGmmEbEdges), kGmmBlock / pick_group(fout).L);
     if (nb > w.nblk) w.nblk = nb;
@@ -1331,7 +1231,7 @@ static GmmWs gmm_ws_layout(const gnn_graph_t* g, int fin, int fout, int K) {
   w.partial = take(sizeof(float) * (size_t)(w.nblk + 1 + sum_partials_scratch_rows((int)w.nblk)) * kMaxK * 4);
   w.split_k = gemm_pick_split_k(fin, K * fout, n);
   w.gemm = take(w.split_k > 1 ? sizeof(float) * (size_t)w.split_k * fin * K * fout : 0);
-  w.agg = take(xg ? sizeof(float) * (size_t)n * K * fin : 0);  // forward: aggregated inputs; backward: gout W'^T
+  w.agg = take(xg ? sizeof(float) * (size_t)n * K * std::max(fin, fout) : 0);  // forward: aggregated inputs; backward: hk
   w.wt = take(xg ? sizeof(float) * (size_t)K * fin * fout : 0);
   w.total = off;
   return w;
@@ -1489,7 +1389,7 @@ extern "C" gnn_status_t gnn_gmm_tune_bwd(gnn_graph_t* g, int fin, int fout, int 
     constexpr int kReps = 3;
     GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdDstLauncher>(gs, g, hk, c, mu, inv_sigma, gout, pm, partial, gmu, gis, st); }, &ms[0]));
     GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdDstEbLauncher>(gs, g, hk, c, mu, inv_sigma, gout, pm, partial, gmu, gis, st); }, &ms[1]));
-    GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdSrcLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, st); }, &ms[2]));
+    GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdSrcLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, (const float*)nullptr, partial, gmu, gis, st); }, &ms[2]));
     GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdSrcEbLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, st); }, &ms[3]));
     g->gmm_bwd_edge_balanced[0] = ms[1] < ms[0] ? 1 : 0;
     g->gmm_bwd_edge_balanced[1] = ms[3] < ms[2] ? 1 : 0;
@@ -1529,33 +1429,23 @@ extern "C" gnn_status_t gnn_gmm_bwd(const gnn_graph_t* g, int fin, int fout, int
   const bool eb_dst = gmm_bwd_use_edge_balanced(g, k, 0) &&
                       (config_get(kCfgGmmMapping) == 1 || !gmm_aggregate_first(fin, fout, k));
   const bool eb_src = gmm_bwd_use_edge_balanced(g, k, 1);
-  if (eb_dst) {
-    const float* hk_use = hk;
-    if (gmm_aggregate_first(fin, fout, k)) {
-      // the forward call may have aggregated first and left hk unwritten: project again, into the
-      // dhk area, which the source side fills only afterwards
-      GNN_TRY(gemm_f32(n, KF, fin, x, fin, false, w_fc, KF, false, dhk, KF, 1, nullptr, st));
-      hk_use = dhk;
-    }
-    GNN_TRY(gmm_dispatch<GmmBwdDstEbLauncher>(gs, g, hk_use, c, mu, inv_sigma, gout, pm, partial, gmu, ginv_sigma, st));
-  } else if (gmm_aggregate_first(fin, fout, k)) {
-    // <gout[v], hk[u,j,:]> = <G_j[v], x[u]>, G = gout W'^T: the destination side gathers x rows
-    float* G = reinterpret_cast<float*>(base + L.agg);
-    float* wt = reinterpret_cast<float*>(base + L.wt);
-    {
-      ProfScope p("gmm_weight_layout", st);
-      const int64_t cnt = (int64_t)fin * k * fout;
-      k_gmm_wt<<<(unsigned)cdiv(cnt, 256), 256, 0, st>>>(fin, k, fout, w_fc, wt);
-      GNN_LAUNCH_CHECK();
-    }
-    GNN_TRY(gemm_f32(n, k * fin, fout, gout, fout, false, wt, fout, true, G, (int64_t)k * fin, 1, nullptr, st));
-    GNN_TRY((gmm_dispatch<GmmBwdDstXLauncher>(pick_group(fin), g, x, c, mu, inv_sigma, (const float*)G, k, fin,
-                                              partial, gmu, ginv_sigma, st)));
-  } else {
-    GNN_TRY(gmm_dispatch<GmmBwdDstLauncher>(gs, g, hk, c, mu, inv_sigma, gout, pm, partial, gmu, ginv_sigma, st));
+  const float* hk_use = hk;
+  if (gmm_aggregate_first(fin, fout, k)) {
+    // the forward call may have aggregated first and left hk unwritten: project again
+    float* again = reinterpret_cast<float*>(base + L.agg);
+    GNN_TRY(gemm_f32(n, KF, fin, x, fin, false, w_fc, KF, false, again, KF, 1, nullptr, st));
+    hk_use = again;
   }
-  if (eb_src) GNN_TRY(gmm_dispatch<GmmBwdSrcEbLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, st));
-  else GNN_TRY(gmm_dispatch<GmmBwdSrcLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, st));
+  const float* no_hk = nullptr;
+  if (eb_dst)
+    GNN_TRY(gmm_dispatch<GmmBwdDstEbLauncher>(gs, g, hk_use, c, mu, inv_sigma, gout, pm, partial, gmu, ginv_sigma, st));
+  else if (eb_src)
+    GNN_TRY(gmm_dispatch<GmmBwdDstLauncher>(gs, g, hk_use, c, mu, inv_sigma, gout, pm, partial, gmu, ginv_sigma, st));
+  if (eb_src)
+    GNN_TRY(gmm_dispatch<GmmBwdSrcEbLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, st));
+  else
+    GNN_TRY(gmm_dispatch<GmmBwdSrcLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, eb_dst ? no_hk : hk_use, partial, gmu,
+                                            ginv_sigma, st));
   GNN_TRY(gemm_f32(fin, KF, n, x, fin, true, dhk, KF, false, gw_fc, KF, L.split_k, part, st));
   if (gx) GNN_TRY(gemm_f32(n, fin, KF, dhk, KF, false, w_fc, KF, true, gx, fin, 1, nullptr, st));
   return GNN_OK;

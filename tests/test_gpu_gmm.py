@@ -76,6 +76,20 @@ def test_aggregate_first_and_project_first_agree_with_the_oracle(fin, fout, K):
     check(c, fwd_workspace=False)
 
 
+@pytest.mark.parametrize("fin,fout,K", [(9, 4, 1), (30, 20, 2), (12, 60, 3), (300, 64, 3), (8, 132, 4), (20, 256, 5), (64, 16, 8)])
+def test_gradients_of_one_walk_over_the_out_edges(fin, fout, K):
+    """Every lane width, one and two passes over the kernels, projected rows given and made again, sources without
+    out-edges, of one, four and five (a step and one more), and hub sources whose row a workgroup shares."""
+    print(f"gmm: out-edge walk {fin}->{fout} K={K}", flush=True)
+    rng = np.random.default_rng(fin + 3 * fout + K)
+    n = 600
+    edges = [(2, v) for v in range(n)] + [(5, int(v)) for v in rng.integers(0, n, 300)]
+    edges += [(u, int(v)) for u in range(20, n) for v in rng.integers(0, n, (0, 1, 4, 5)[u % 4])]
+    c = synth(rng, *tiny_graph(n, edges), fin, fout, K)
+    check(c)
+    check(c, fwd_workspace=False)
+
+
 def test_graph_without_edges():
     print("gmm: no edges", flush=True)
     rng = np.random.default_rng(62)
