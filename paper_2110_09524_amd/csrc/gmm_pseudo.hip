@@ -14,6 +14,7 @@
 //     gmu, ginv_sigma (summed over all edges in a fixed two-stage order) and gm[e,:];
 //   source side (CSC walk, no atomics): dhk[u,k,:] = (1/K) sum_out-edges w_k(e) gout[v,:],
 //     with m read through the plan's CSC position -> CSR edge id table.
+// Where the coordinates are projected on the spot, or few enough, one walk over the out-edges does both.
 // At most 4 kernels and 4 pseudo-coordinate dimensions; fout <= 256.
 #include <algorithm>
 #include <type_traits>
@@ -32,31 +33,35 @@ struct PsParams {
   int K, R, F;
 };
 
-// the K x R means and inverse widths, zero-padded, in registers (uniform)
+// the K x R means and inverse widths, zero-padded to KT x RT, in registers (uniform)
+template <int KT = kPsK, int RT = kPsR>
 struct PsKernels {
-  float mu[kPsK][kPsR], is[kPsK][kPsR];
+  float mu[KT][RT], is[KT][RT];
 };
-__device__ __forceinline__ PsKernels load_kernels(const float* __restrict__ mu, const float* __restrict__ is,
-                                                  int K, int R) {
-  PsKernels p;
+template <int KT = kPsK, int RT = kPsR>
+__device__ __forceinline__ PsKernels<KT, RT> load_kernels(const float* __restrict__ mu, const float* __restrict__ is,
+                                                          int K, int R) {
+  PsKernels<KT, RT> p;
 #pragma unroll
-  for (int k = 0; k < kPsK; ++k)
+  for (int k = 0; k < KT; ++k)
 #pragma unroll
-    for (int d = 0; d < kPsR; ++d) {
+    for (int d = 0; d < RT; ++d) {
       const bool ok = k < K && d < R;
       p.mu[k][d] = ok ? mu[k * R + d] : 0.f;
       p.is[k][d] = ok ? is[k * R + d] : 0.f;
     }
   return p;
 }
-__device__ __forceinline__ void load_pseudo(const float* __restrict__ m, int64_t e, int R, float (&out)[kPsR]) {
+template <int RT>
+__device__ __forceinline__ void load_pseudo(const float* __restrict__ m, int64_t e, int R, float (&out)[RT]) {
 #pragma unroll
-  for (int d = 0; d < kPsR; ++d) out[d] = d < R ? m[e * R + d] : 0.f;
+  for (int d = 0; d < RT; ++d) out[d] = d < R ? m[e * R + d] : 0.f;
 }
-__device__ __forceinline__ float gauss_k(const PsKernels& p, int k, const float (&m)[kPsR]) {
+template <int KT, int RT>
+__device__ __forceinline__ float gauss_k(const PsKernels<KT, RT>& p, int k, const float (&m)[RT]) {
   float q = 0.f;
 #pragma unroll
-  for (int d = 0; d < kPsR; ++d) {  // padded dimensions have inv_sigma 0
+  for (int d = 0; d < RT; ++d) {  // padded dimensions have inv_sigma 0
     const float t = (m[d] - p.mu[k][d]) * p.is[k][d];
     q = fmaf(t, t, q);
   }
@@ -79,7 +84,7 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_fwd(
   if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp)) return;
   const int K = pm.K, R = pm.R, F = pm.F, KF = K * F;
   const float inv_k = 1.f / (float)K;
-  const PsKernels pk = load_kernels(mu, inv_sigma, K, R);
+  const PsKernels<> pk = load_kernels(mu, inv_sigma, K, R);
   const int32_t v = order[r];
   const int32_t beg = indptr[v], end = indptr[v + 1];
   const bool col_ok = 4 * li < F;
@@ -143,7 +148,7 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_dst(
       gs_acc[k][d] = 0.f;
     }
   if (active) {
-    const PsKernels pk = load_kernels(mu, inv_sigma, K, R);
+    const PsKernels<> pk = load_kernels(mu, inv_sigma, K, R);
     const int32_t v = order[r];
     const int32_t beg = indptr[v], end = indptr[v + 1];
     const bool col_ok = 4 * li < F;
@@ -229,7 +234,7 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_src(
   if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp)) return;
   const int K = pm.K, R = pm.R, F = pm.F, KF = K * F;
   const float inv_k = 1.f / (float)K;
-  const PsKernels pk = load_kernels(mu, inv_sigma, K, R);
+  const PsKernels<> pk = load_kernels(mu, inv_sigma, K, R);
   const int32_t u = order_t[r];
   const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
   const bool col_ok = 4 * li < F;
@@ -286,13 +291,15 @@ struct ProjArgs {
   const float* P;   // [r, 2]
   const float* pb;  // [r]
 };
+template <int RT>
 struct ProjRegs {
-  float p0[kPsR], p1[kPsR], b[kPsR];
+  float p0[RT], p1[RT], b[RT];
 };
-__device__ __forceinline__ ProjRegs load_proj(const ProjArgs& a, int R) {
-  ProjRegs q;
+template <int RT>
+__device__ __forceinline__ ProjRegs<RT> load_proj(const ProjArgs& a, int R) {
+  ProjRegs<RT> q;
 #pragma unroll
-  for (int d = 0; d < kPsR; ++d) {
+  for (int d = 0; d < RT; ++d) {
     const bool ok = d < R;
     q.p0[d] = ok ? a.P[2 * d] : 0.f;
     q.p1[d] = ok ? a.P[2 * d + 1] : 0.f;
@@ -300,9 +307,10 @@ __device__ __forceinline__ ProjRegs load_proj(const ProjArgs& a, int R) {
   }
   return q;
 }
-__device__ __forceinline__ void project(const ProjRegs& q, int R, float cu, float cv, float (&m)[kPsR]) {
+template <int RT>
+__device__ __forceinline__ void project(const ProjRegs<RT>& q, int R, float cu, float cv, float (&m)[RT]) {
 #pragma unroll
-  for (int d = 0; d < kPsR; ++d) m[d] = d < R ? tanhf(fmaf(q.p0[d], cu, fmaf(q.p1[d], cv, q.b[d]))) : 0.f;
+  for (int d = 0; d < RT; ++d) m[d] = d < R ? tanhf(fmaf(q.p0[d], cu, fmaf(q.p1[d], cv, q.b[d]))) : 0.f;
 }
 constexpr int kPsValsProj = kPsVals + 3 * kPsR;  // + (gP[d,0], gP[d,1], gpb[d]) per dimension
 
@@ -340,13 +348,13 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_fwd_nr(
   if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp)) return;
   const int K = pm.K, R = pm.R, F = pm.F, KF = K * F, F4 = F / 4;
   const float inv_k = 1.f / (float)K;
-  const PsKernels pk = load_kernels(mu, inv_sigma, K, R);
+  const PsKernels<> pk = load_kernels(mu, inv_sigma, K, R);
   const int32_t v = order[r];
   const int32_t beg = indptr[v], end = indptr[v + 1];
-  ProjRegs pq;
+  ProjRegs<kPsR> pq;
   float cv = 0.f;
   if (PROJ) {
-    pq = load_proj(pa, R);
+    pq = load_proj<kPsR>(pa, R);
     cv = pa.c[v];
   }
   const bool col_ok = li < K * F4;
@@ -420,20 +428,17 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_fwd_nr(
 
 // destination side of backward: the row phase leaves every lane's part of <gout[v], hk[u, k, :]> in
 // LDS, and the lane that owns the edge adds the F/4 parts of each kernel in lane order
-// PROJ: the gradient of the projection's parameters is summed here as well (slots kPsVals ... of a
-// partial row), so gpseudo is never written
-template <int G, bool PROJ>
+template <int G>
 __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_dst_nr(
     RowLaunch rl, const int32_t* __restrict__ order, const int32_t* __restrict__ indptr,
     const int32_t* __restrict__ indices, const float* __restrict__ hk, const float* __restrict__ pseudo,
-    ProjArgs pa, const float* __restrict__ mu, const float* __restrict__ inv_sigma,
+    const float* __restrict__ mu, const float* __restrict__ inv_sigma,
     const float* __restrict__ gout, PsParams pm, float* __restrict__ partial,
     float* __restrict__ gpseudo /* nullable */) {
   constexpr int GPB = kPsBlock / G;
   constexpr int GS = kNrGroupFloats<G>;
-  constexpr int NVALS = PROJ ? kPsValsProj : kPsVals;
   __shared__ __align__(16) float lds[GPB * GS];
-  __shared__ float blk[GPB][NVALS];
+  __shared__ float blk[GPB][kPsVals];
   const int li = threadIdx.x & (G - 1);
   const int grp = threadIdx.x / G;
   int64_t r;
@@ -450,19 +455,10 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_dst_nr(
       gm_acc[k][d] = 0.f;
       gs_acc[k][d] = 0.f;
     }
-  float gp_acc[3 * kPsR];  // PROJ: (gP[d,0], gP[d,1], gpb[d])
-#pragma unroll
-  for (int i = 0; i < 3 * kPsR; ++i) gp_acc[i] = 0.f;
   if (active) {
-    const PsKernels pk = load_kernels(mu, inv_sigma, K, R);
+    const PsKernels<> pk = load_kernels(mu, inv_sigma, K, R);
     const int32_t v = order[r];
     const int32_t beg = indptr[v], end = indptr[v + 1];
-    ProjRegs pq;
-    float cv = 0.f;
-    if (PROJ) {
-      pq = load_proj(pa, R);
-      cv = pa.c[v];
-    }
     const bool col_ok = li < K * F4;
     const int f4 = col_ok ? li % F4 : 0;
     const float4 g4 = col_ok ? ld4(gout + (int64_t)v * F + 4 * f4) : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -474,17 +470,11 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_dst_nr(
       const int cnt = min(G, end - e0);
       int32_t u = 0;
       float m[kPsR];
-      float cu = 0.f;
 #pragma unroll
       for (int d = 0; d < kPsR; ++d) m[d] = 0.f;
       if (e_ok) {
         u = indices[e0 + li];
-        if (PROJ) {
-          cu = pa.c[u];
-          project(pq, R, cu, cv, m);
-        } else {
-          load_pseudo(pseudo, e0 + li, R, m);
-        }
+        load_pseudo(pseudo, e0 + li, R, m);
       }
       wave_lds_fence();
       l_idx[li] = u;
@@ -526,15 +516,7 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_dst_nr(
             gm[d] = fmaf(-t, is, gm[d]);
           }
         }
-        if (PROJ) {
-#pragma unroll
-          for (int d = 0; d < kPsR; ++d) {
-            const float dpre = gm[d] * (1.f - m[d] * m[d]);  // through the tanh; padded dimensions: gm = 0
-            gp_acc[3 * d] = fmaf(dpre, cu, gp_acc[3 * d]);
-            gp_acc[3 * d + 1] = fmaf(dpre, cv, gp_acc[3 * d + 1]);
-            gp_acc[3 * d + 2] += dpre;
-          }
-        } else if (gpseudo != nullptr) {
+        if (gpseudo != nullptr) {
 #pragma unroll
           for (int d = 0; d < kPsR; ++d)
             if (d < R) gpseudo[(int64_t)(e0 + li) * R + d] = gm[d];
@@ -558,30 +540,22 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_dst_nr(
         blk[grp][kPsK * kPsR + k * kPsR + d] = 0.f;
       }
     }
-  if (PROJ) {
-#pragma unroll
-    for (int i = 0; i < 3 * kPsR; ++i) {
-      float a = 0.f;
-      if (i / 3 < R) a = group_sum_from<G>(gp_acc[i], 1);
-      if (li == 0) blk[grp][kPsVals + i] = a;
-    }
-  }
   __syncthreads();
-  if (threadIdx.x < NVALS) {
+  if (threadIdx.x < kPsVals) {
     float s = 0.f;
     for (int g2 = 0; g2 < GPB; ++g2) s += blk[g2][threadIdx.x];
-    partial[(int64_t)blockIdx.x * NVALS + threadIdx.x] = s;
+    partial[(int64_t)blockIdx.x * kPsVals + threadIdx.x] = s;
   }
 }
 
 // source side of backward: dhk[u, k, f] = (1/K) sum over out-edges w_k(e) gout[v, f]; the lanes of the K
 // kernels read the same columns of gout[v]
-template <int G, bool PROJ>
+template <int G>
 __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_src_nr(
     RowLaunch rl, const int32_t* __restrict__ order_t, const int32_t* __restrict__ indptr_t,
     const int32_t* __restrict__ indices_t, const int32_t* __restrict__ eid_t,
     const float* __restrict__ pseudo, const float* __restrict__ pseudo_t /* nullable: pseudo in this walk's order */,
-    ProjArgs pa, const float* __restrict__ mu, const float* __restrict__ inv_sigma,
+    const float* __restrict__ mu, const float* __restrict__ inv_sigma,
     const float* __restrict__ gout, PsParams pm, float* __restrict__ dhk) {
   constexpr int GPB = kPsBlock / G;
   constexpr int GS = kNrGroupFloats<G>;
@@ -595,15 +569,9 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_src_nr(
   if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp)) return;
   const int K = pm.K, R = pm.R, F = pm.F, KF = K * F, F4 = F / 4;
   const float inv_k = 1.f / (float)K;
-  const PsKernels pk = load_kernels(mu, inv_sigma, K, R);
+  const PsKernels<> pk = load_kernels(mu, inv_sigma, K, R);
   const int32_t u = order_t[r];
   const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
-  ProjRegs pq;
-  float cu = 0.f;
-  if (PROJ) {
-    pq = load_proj(pa, R);
-    cu = pa.c[u];
-  }
   const bool col_ok = li < K * F4;
   const int myk = col_ok ? li / F4 : 0;
   const int f4 = col_ok ? li % F4 : 0;
@@ -621,8 +589,7 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_src_nr(
     for (int d = 0; d < kPsR; ++d) m[d] = 0.f;
     if (e_ok) {
       v = indices_t[p0 + li];
-      if (PROJ) project(pq, R, cu, pa.c[v], m);
-      else if (pseudo_t != nullptr) load_pseudo(pseudo_t, p0 + li, R, m);
+      if (pseudo_t != nullptr) load_pseudo(pseudo_t, p0 + li, R, m);
       else load_pseudo(pseudo, eid_t[p0 + li], R, m);
     }
     wave_lds_fence();
@@ -663,6 +630,184 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_src_nr(
     acc = unpack4(vv);
   }
   if (col_ok) st4(dhk + (int64_t)u * KF + 4 * li, acc);
+}
+
+// Backward, both sides in one walk over the out-edges.  A row owns hk[u] and dhk[u] and gathers gout[v], with which
+// a lane adds w_k(e) gout[v] to dhk and, through LDS, hands its part of <gout[v], hk[u, k, :]> to the lane that
+// owns the edge; that lane has the pseudo-coordinates and weights already and sums the parameters' gradients.
+// Apart, the destination side gathered the K times wider hk[u] and both sides evaluated every tanh and exp.
+// 232 965 vertices, 1.12 10^8 edges, K = 2, R = 1, 16 columns, us: 1470 + 1240 -> 1320 (1860 compiled for the most kernels and
+// dimensions, as the forward kernel is, which the gathers of hk[u] bound: 1425, and 1478 compiled for K = 2, R = 1).
+template <int G, bool PROJ, int KT, int RT>
+__global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
+    RowLaunch rl, const int32_t* __restrict__ order_t, const int32_t* __restrict__ indptr_t,
+    const int32_t* __restrict__ indices_t, const int32_t* __restrict__ eid_t, const float* __restrict__ hk,
+    const float* __restrict__ pseudo, const float* __restrict__ pseudo_t /* nullable: pseudo in this walk's order */,
+    ProjArgs pa, const float* __restrict__ mu, const float* __restrict__ inv_sigma, const float* __restrict__ gout,
+    PsParams pm, float* __restrict__ dhk, float* __restrict__ partial, float* __restrict__ gpseudo /* nullable */) {
+  constexpr int NVALS = PROJ ? kPsValsProj : kPsVals;
+  constexpr int GPB = kPsBlock / G;
+  constexpr int GS = G + KT * G + G * G;  // indices | weights [KT][G] | partial dot products [column lane][edge]
+  __shared__ __align__(16) float lds[GPB * GS];
+  __shared__ float coop_buf[GPB * G * 4];
+  __shared__ float blk[GPB][NVALS];
+  const int li = threadIdx.x & (G - 1);
+  const int grp = threadIdx.x / G;
+  int64_t r;
+  int gi, ngrp;
+  RowRange rr;
+  const bool active = pick_row<GPB>(rl, grp, rr, r, gi, ngrp);
+  const int K = pm.K, R = pm.R, F = pm.F, KF = K * F, F4 = F / 4;
+  const float inv_k = 1.f / (float)K;
+  float gm_acc[KT][RT], gs_acc[KT][RT], gp_acc[3 * RT];  // sums over the edges this lane owned
+#pragma unroll
+  for (int k = 0; k < KT; ++k)
+#pragma unroll
+    for (int d = 0; d < RT; ++d) gm_acc[k][d] = gs_acc[k][d] = 0.f;
+#pragma unroll
+  for (int i = 0; i < 3 * RT; ++i) gp_acc[i] = 0.f;
+  if (active) {
+    const PsKernels<KT, RT> pk = load_kernels<KT, RT>(mu, inv_sigma, K, R);
+    const int32_t u = order_t[r];
+    const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
+    ProjRegs<RT> pq;
+    float cu = 0.f;
+    if (PROJ) {
+      pq = load_proj<RT>(pa, R);
+      cu = pa.c[u];
+    }
+    const bool col_ok = li < K * F4;
+    const int myk = col_ok ? li / F4 : 0, f4 = col_ok ? li % F4 : 0;
+    const float4 h4 = col_ok ? ld4(hk + (int64_t)u * KF + 4 * li) : make_float4(0.f, 0.f, 0.f, 0.f);
+    int* l_idx = reinterpret_cast<int*>(lds + grp * GS);
+    float* l_w = lds + grp * GS + G;
+    float* l_d = l_w + KT * G;
+    const float* my_row = gout + 4 * f4;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), part = acc;
+    int folded = 0;
+    for (int32_t p0 = beg + gi * G; p0 < end; p0 += ngrp * G) {
+      const bool e_ok = p0 + li < end;
+      const int cnt = min(G, end - p0);
+      int32_t v = 0, e = 0;
+      float cv = 0.f, m[RT], w[KT];
+#pragma unroll
+      for (int d = 0; d < RT; ++d) m[d] = 0.f;
+      if (e_ok) {
+        v = indices_t[p0 + li];
+        if (PROJ) {
+          cv = pa.c[v];
+          project(pq, R, cu, cv, m);
+        } else {
+          e = eid_t[p0 + li];
+          if (pseudo_t != nullptr) load_pseudo(pseudo_t, p0 + li, R, m);
+          else load_pseudo(pseudo, e, R, m);
+        }
+      }
+      wave_lds_fence();  // the previous chunk's reads are done
+      l_idx[li] = v;
+#pragma unroll
+      for (int k = 0; k < KT; ++k)
+        if (k < K) l_w[k * G + li] = w[k] = e_ok ? gauss_k(pk, k, m) * inv_k : 0.f;
+      wave_lds_fence();
+#pragma unroll
+      for (int t0 = 0; t0 < G; t0 += kNrU) {
+        if (t0 < cnt) {
+          int idv[kNrU];
+          float wv[kNrU], dv[kNrU];
+          read8i(l_idx + t0, idv);
+          float4 rowv[kNrU];
+#pragma unroll
+          for (int t = 0; t < kNrU; ++t)
+            if (col_ok && t0 + t < cnt) rowv[t] = ld4(my_row + (int64_t)idv[t] * F);
+          read8f(l_w + myk * G + t0, wv);
+#pragma unroll
+          for (int t = 0; t < kNrU; ++t) {
+            const bool ok = col_ok && t0 + t < cnt;
+            if (ok) fma4(part, wv[t], rowv[t]);
+            dv[t] = ok ? dot4(h4, rowv[t]) : 0.f;
+          }
+          *reinterpret_cast<float4*>(l_d + li * G + t0) = make_float4(dv[0], dv[1], dv[2], dv[3]);
+          *reinterpret_cast<float4*>(l_d + li * G + t0 + 4) = make_float4(dv[4], dv[5], dv[6], dv[7]);
+        }
+      }
+      wave_lds_fence();
+      if (e_ok) {
+        float gm[RT];
+#pragma unroll
+        for (int d = 0; d < RT; ++d) gm[d] = 0.f;
+#pragma unroll
+        for (int k = 0; k < KT; ++k) {
+          if (k >= K) continue;
+          float dot = 0.f;
+          for (int j = 0; j < F4; ++j) dot += l_d[(k * F4 + j) * G + li];
+          const float dlog = dot * w[k];  // dw_k(e) w_k(e), 1 / K in the weight
+#pragma unroll
+          for (int d = 0; d < RT; ++d) {
+            const float diff = m[d] - pk.mu[k][d];
+            const float is = pk.is[k][d];
+            const float t = dlog * diff * is;  // padded dimensions: is = 0
+            gm_acc[k][d] = fmaf(t, is, gm_acc[k][d]);
+            gs_acc[k][d] = fmaf(-t, diff, gs_acc[k][d]);
+            gm[d] = fmaf(-t, is, gm[d]);
+          }
+        }
+        if (PROJ) {
+#pragma unroll
+          for (int d = 0; d < RT; ++d) {
+            const float dpre = gm[d] * (1.f - m[d] * m[d]);  // through the tanh; padded dimensions: gm = 0
+            gp_acc[3 * d] = fmaf(dpre, cu, gp_acc[3 * d]);
+            gp_acc[3 * d + 1] = fmaf(dpre, cv, gp_acc[3 * d + 1]);
+            gp_acc[3 * d + 2] += dpre;
+          }
+        } else if (gpseudo != nullptr) {
+#pragma unroll
+          for (int d = 0; d < RT; ++d)
+            if (d < R) gpseudo[(int64_t)e * R + d] = gm[d];
+        }
+      }
+      folded += G;
+      if (folded >= 32) {  // two-level summation keeps long rows accurate
+        add4(acc, part);
+        part = make_float4(0.f, 0.f, 0.f, 0.f);
+        folded = 0;
+      }
+    }
+    add4(acc, part);
+    if (rr.coop) {
+      float vv[4];
+      pack4(vv, acc);
+      coop_sum<G, 4, GPB>(coop_buf, vv, grp, li);
+      acc = unpack4(vv);
+    }
+    if (col_ok && (!rr.coop || grp == 0)) st4(dhk + (int64_t)u * KF + 4 * li, acc);
+  }
+  // the group's lanes are added in a fixed (butterfly) order, then the groups in order; what K and R leave out stays 0
+  for (int i = li; i < NVALS; i += G) blk[grp][i] = 0.f;
+  wave_lds_fence();
+#pragma unroll
+  for (int k = 0; k < KT; ++k)
+#pragma unroll
+    for (int d = 0; d < RT; ++d) {
+      const bool used = k < K && d < R;
+      const float a = used ? group_sum_from<G>(gm_acc[k][d], 1) : 0.f, b = used ? group_sum_from<G>(gs_acc[k][d], 1) : 0.f;
+      if (li == 0) {
+        blk[grp][k * kPsR + d] = a;
+        blk[grp][kPsK * kPsR + k * kPsR + d] = b;
+      }
+    }
+  if (PROJ) {
+#pragma unroll
+    for (int i = 0; i < 3 * RT; ++i) {
+      const float a = i / 3 < R ? group_sum_from<G>(gp_acc[i], 1) : 0.f;
+      if (li == 0) blk[grp][kPsVals + i] = a;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < NVALS) {
+    float s = 0.f;
+    for (int g2 = 0; g2 < GPB; ++g2) s += blk[g2][threadIdx.x];
+    partial[(int64_t)blockIdx.x * NVALS + threadIdx.x] = s;
+  }
 }
 
 // ---- the projection that makes pseudo-coordinates from the degree pair ------------------------
@@ -777,7 +922,7 @@ static unsigned nr_grid(const gnn_graph_t* g, int side, RowLaunch& rl) {
   return sp.hub_grid + sp.rest_grid;
 }
 
-// partial slots of the destination-side kernel: enough for either kernel family
+// partial slots of the kernels that sum the parameters' gradients: enough for any of them
 static int64_t ps_dst_blocks(const gnn_graph_t* g, int fout) {
   RowLaunch rl;
   int64_t b;
@@ -788,8 +933,8 @@ static int64_t ps_dst_blocks(const gnn_graph_t* g, int fout) {
     case 32: b = ps_grid<32>(g, 0, rl); break;
     default: b = ps_grid<64>(g, 0, rl); break;
   }
-  const int64_t b8 = nr_grid<8>(g, 0, rl), b16 = nr_grid<16>(g, 0, rl);
-  return std::max(b, std::max(b8, b16));
+  for (int side = 0; side < 2; ++side) b = std::max<int64_t>({b, nr_grid<8>(g, side, rl), nr_grid<16>(g, side, rl)});
+  return b;
 }
 
 struct GmmpWs {
@@ -831,6 +976,33 @@ static gnn_status_t for_lanes(int lanes, Fn fn) {
     default: return fn(std::integral_constant<int, 64>{});
   }
 }
+
+// Calls fn with the numbers of kernels and of dimensions that a kernel is compiled for, as constants: the vector units
+// bound the backward kernel, and its work per edge grows with both.
+template <typename Fn>
+static gnn_status_t for_kernels(int K, int R, Fn fn) {
+  auto dims = [&](auto kernels) -> gnn_status_t {
+    switch (R) {
+      case 1: return fn(kernels, std::integral_constant<int, 1>{});
+      case 2: return fn(kernels, std::integral_constant<int, 2>{});
+      case 3: return fn(kernels, std::integral_constant<int, 3>{});
+      default: return fn(kernels, std::integral_constant<int, 4>{});
+    }
+  };
+  switch (K) {
+    case 1:
+    case 2: return dims(std::integral_constant<int, 2>{});
+    case 3: return dims(std::integral_constant<int, 3>{});
+    default: return dims(std::integral_constant<int, 4>{});
+  }
+}
+
+// With coordinates given per edge the one walk stores gpseudo through the CSC position -> CSR edge id table, 4 R bytes at a time,
+// which pays while the array stays in the caches (us, both kernels -> one walk, coordinates in both orders: 2 10^6
+// edges, R = 3, K = 3, 25 MB 144 -> 107; 3 10^6, R = 2, 24 MB 237 -> 178; 10^7, R = 1, 40 MB 360 -> 369; R = 3, 120 MB
+// 422 -> 500; 1.12 10^8, R = 1 2657 -> 3743).
+constexpr int64_t kOneWalkBytes = (int64_t)32 << 20;
+static bool one_walk_pays(const gnn_graph_t* g, int R) { return g->nnz * R * (int64_t)sizeof(float) <= kOneWalkBytes; }
 
 }  // namespace gnn
 
@@ -903,50 +1075,68 @@ extern "C" gnn_status_t gnn_gmmp_bwd(const gnn_graph_t* g, int fin, int fout, in
   float* part = reinterpret_cast<float*>(base + W.gemm);
   const PsParams pm{k, r, fout};
   const int KF = k * fout;
-  {
-    ProfScope p("gmmp_bwd_dst", st);
-    unsigned grid = 0;
-    const int G = nr_lanes(k, fout);
-    GNN_TRY(for_lanes(G ? G : ps_lanes(fout), [&](auto lanes) -> gnn_status_t {
-      constexpr int L = decltype(lanes)::value;
-      constexpr int GL = L == 8 ? 8 : 16;
-      RowLaunch rl;
-      grid = G ? nr_grid<GL>(g, 0, rl) : ps_grid<L>(g, 0, rl);
-      if (grid == 0) return GNN_OK;
-      if (G)
-        k_gmmp_bwd_dst_nr<GL, false><<<grid, kPsBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, hk, pseudo,
-                                                               ProjArgs{}, mu, inv_sigma, gout, pm, partial,
-                                                               gpseudo);
-      else
-        k_gmmp_bwd_dst<L><<<grid, kPsBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, hk, pseudo, mu,
-                                                    inv_sigma, gout, pm, partial, gpseudo);
-      GNN_LAUNCH_CHECK();
-      return GNN_OK;
-    }));
+  const int G = nr_lanes(k, fout);
+  auto param_sums = [&](unsigned grid) -> gnn_status_t {
     float* totals = partial + (int64_t)grid * kPsVals;
     GNN_TRY(sum_partials_two_level(kPsVals, (int)grid, partial, totals + kPsVals, totals, st));
     k_gmmp_param_split<<<1, 64, 0, st>>>(k, r, totals, gmu, ginv_sigma);
     GNN_LAUNCH_CHECK();
-  }
-  {
-    ProfScope p("gmmp_bwd_src", st);
-    const int G = nr_lanes(k, fout);
-    GNN_TRY(for_lanes(G ? G : ps_lanes(fout), [&](auto lanes) -> gnn_status_t {
-      constexpr int L = decltype(lanes)::value;
-      constexpr int GL = L == 8 ? 8 : 16;
+    return GNN_OK;
+  };
+  if (G && one_walk_pays(g, r)) {
+    ProfScope p("gmmp_bwd", st);
+    unsigned grid = 0;
+    GNN_TRY(for_lanes(G, [&](auto lanes) -> gnn_status_t {
+      constexpr int GL = decltype(lanes)::value == 8 ? 8 : 16;
       RowLaunch rl;
-      const unsigned grid = G ? nr_grid<GL>(g, 1, rl) : ps_grid<L>(g, 1, rl);
+      grid = nr_grid<GL>(g, 1, rl);
       if (grid == 0) return GNN_OK;
-      if (G)
-        k_gmmp_bwd_src_nr<GL, false><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t,
-                                                               g->eid_t, pseudo, pseudo_t, ProjArgs{}, mu,
-                                                               inv_sigma, gout, pm, dhk);
-      else
-        k_gmmp_bwd_src<L><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, g->eid_t, pseudo,
-                                                    pseudo_t, mu, inv_sigma, gout, pm, dhk);
+      k_gmmp_bwd_nr<GL, false, kPsK, kPsR><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, g->eid_t, hk,
+                                                                     pseudo, pseudo_t, ProjArgs{}, mu, inv_sigma, gout, pm,
+                                                                     dhk, partial, gpseudo);
       GNN_LAUNCH_CHECK();
       return GNN_OK;
     }));
+    GNN_TRY(param_sums(grid));
+  } else {
+    {
+      ProfScope p("gmmp_bwd_dst", st);
+      unsigned grid = 0;
+      GNN_TRY(for_lanes(G ? G : ps_lanes(fout), [&](auto lanes) -> gnn_status_t {
+        constexpr int L = decltype(lanes)::value;
+        constexpr int GL = L == 8 ? 8 : 16;
+        RowLaunch rl;
+        grid = G ? nr_grid<GL>(g, 0, rl) : ps_grid<L>(g, 0, rl);
+        if (grid == 0) return GNN_OK;
+        if (G)
+          k_gmmp_bwd_dst_nr<GL><<<grid, kPsBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, hk, pseudo, mu,
+                                                          inv_sigma, gout, pm, partial, gpseudo);
+        else
+          k_gmmp_bwd_dst<L><<<grid, kPsBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, hk, pseudo, mu,
+                                                      inv_sigma, gout, pm, partial, gpseudo);
+        GNN_LAUNCH_CHECK();
+        return GNN_OK;
+      }));
+      GNN_TRY(param_sums(grid));
+    }
+    {
+      ProfScope p("gmmp_bwd_src", st);
+      GNN_TRY(for_lanes(G ? G : ps_lanes(fout), [&](auto lanes) -> gnn_status_t {
+        constexpr int L = decltype(lanes)::value;
+        constexpr int GL = L == 8 ? 8 : 16;
+        RowLaunch rl;
+        const unsigned grid = G ? nr_grid<GL>(g, 1, rl) : ps_grid<L>(g, 1, rl);
+        if (grid == 0) return GNN_OK;
+        if (G)
+          k_gmmp_bwd_src_nr<GL><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, g->eid_t, pseudo,
+                                                          pseudo_t, mu, inv_sigma, gout, pm, dhk);
+        else
+          k_gmmp_bwd_src<L><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, g->eid_t, pseudo,
+                                                      pseudo_t, mu, inv_sigma, gout, pm, dhk);
+        GNN_LAUNCH_CHECK();
+        return GNN_OK;
+      }));
+    }
   }
   GNN_TRY(gemm_f32(fin, KF, g->n, x, fin, true, dhk, KF, false, gw_fc, KF, W.split_k, part, st));
   if (gx) GNN_TRY(gemm_f32(g->n, fin, KF, dhk, KF, false, w_fc, KF, true, gx, fin, 1, nullptr, st));
@@ -1076,17 +1266,21 @@ extern "C" gnn_status_t gnn_monet_bwd(const gnn_graph_t* g, int fin, int fout, i
   const int KF = k * fout;
   const int G = KF <= 32 ? 8 : 16;
   {
-    ProfScope p("monet_bwd_dst", st);
+    ProfScope p("monet_bwd", st);
     unsigned grid = 0;
     GNN_TRY(for_lanes(G, [&](auto lanes) -> gnn_status_t {
       constexpr int GL = decltype(lanes)::value == 8 ? 8 : 16;
       RowLaunch rl;
-      grid = nr_grid<GL>(g, 0, rl);
+      grid = nr_grid<GL>(g, 1, rl);
       if (grid == 0) return GNN_OK;
-      k_gmmp_bwd_dst_nr<GL, true><<<grid, kPsBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, hk, nullptr, pa,
-                                                            mu, inv_sigma, gout, pm, partial, nullptr);
-      GNN_LAUNCH_CHECK();
-      return GNN_OK;
+      return for_kernels(k, r, [&](auto kernels, auto dims) -> gnn_status_t {
+        constexpr int KT = decltype(kernels)::value, RT = decltype(dims)::value;
+        k_gmmp_bwd_nr<GL, true, KT, RT><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, g->eid_t, hk,
+                                                                  nullptr, nullptr, pa, mu, inv_sigma, gout, pm, dhk,
+                                                                  partial, nullptr);
+        GNN_LAUNCH_CHECK();
+        return GNN_OK;
+      });
     }));
     float* totals = partial + (int64_t)grid * kPsValsProj;
     GNN_TRY(sum_partials_two_level(kPsValsProj, (int)grid, partial, totals + kPsValsProj, totals, st));
@@ -1094,19 +1288,6 @@ extern "C" gnn_status_t gnn_monet_bwd(const gnn_graph_t* g, int fin, int fout, i
     GNN_LAUNCH_CHECK();
     k_pseudo_proj_split<<<1, 64, 0, st>>>(r, totals + kPsVals, gproj_w, gproj_b);
     GNN_LAUNCH_CHECK();
-  }
-  {
-    ProfScope p("monet_bwd_src", st);
-    GNN_TRY(for_lanes(G, [&](auto lanes) -> gnn_status_t {
-      constexpr int GL = decltype(lanes)::value == 8 ? 8 : 16;
-      RowLaunch rl;
-      const unsigned grid = nr_grid<GL>(g, 1, rl);
-      if (grid == 0) return GNN_OK;
-      k_gmmp_bwd_src_nr<GL, true><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, g->eid_t,
-                                                            nullptr, nullptr, pa, mu, inv_sigma, gout, pm, dhk);
-      GNN_LAUNCH_CHECK();
-      return GNN_OK;
-    }));
   }
   GNN_TRY(gemm_f32(fin, KF, g->n, x, fin, true, dhk, KF, false, gw_fc, KF, W.split_k, part, st));
   if (gx) GNN_TRY(gemm_f32(g->n, fin, KF, dhk, KF, false, w_fc, KF, true, gx, fin, 1, nullptr, st));

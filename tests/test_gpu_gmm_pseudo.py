@@ -92,6 +92,19 @@ def test_coordinates_in_the_transposed_order_give_the_same_bits(fout, K, r):
         assert np.array_equal(a[k], b[k]), k
 
 
+@pytest.mark.parametrize("fout,K", [(4, 2), (12, 4)])
+def test_more_coordinates_than_one_walk_stores(fout, K):
+    """2.2 10^6 edges with 4 coordinates, 35 MB: both sides walked apart, with the coordinates in one and in both orders."""
+    print(f"gmmp: walked apart {fout} {K}", flush=True)
+    rng = np.random.default_rng(fout)
+    n, deg = 100_000, 22
+    indptr = (deg * np.arange(n + 1)).astype(np.int32)
+    c = synth(rng, indptr, rng.integers(0, n, n * deg).astype(np.int32), 3, fout, K, 4)
+    a, b = check(c), run(c, transposed=True)
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
+
+
 def test_single_edge_kernels_agree_with_the_chunked_ones():
     """Rows of up to 64 projected floats take the chunked kernels; force_simple_kernels selects the
     one-edge-at-a-time kernels that wider rows use.  Both against the oracle."""

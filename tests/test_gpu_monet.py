@@ -88,6 +88,20 @@ def test_shapes(fin, fout, K, r):
     check(synth(rng, indptr, indices, fin, fout, K, r))
 
 
+@pytest.mark.parametrize("K", [1, 2, 3, 4])
+@pytest.mark.parametrize("r", [1, 2, 3, 4])
+def test_every_number_of_kernels_and_dimensions(K, r):
+    """The backward walk is compiled for each; groups of 8 and of 16 lanes, whole and partial, sources without out-edges,
+    of as many as a chunk and one more, and hub sources whose row a workgroup shares."""
+    print(f"monet: K={K} r={r}", flush=True)
+    rng = np.random.default_rng(16 * K + r)
+    n = 700
+    edges = [(3, v) for v in range(n)] * 2 + [(u, int(v)) for u in range(10, n) for v in rng.integers(0, n, (0, 1, 8, 9, 16, 17)[u % 6])]
+    indptr, indices = tiny_graph(n, edges)
+    for fout in (4, 8 if K > 2 else 16, 64 // K // 4 * 4):
+        check(synth(rng, indptr, indices, 5, fout, K, r))
+
+
 def test_the_papers_settings_on_a_power_law_graph_and_the_two_call_form():
     """k = 3, r = 3 and k = 2, r = 1 with 16 hidden features (Sec. 7.2, 7.3) on a graph with hub rows.  The
     fused kernels evaluate the same expressions in the same order as projection + general layer, so
