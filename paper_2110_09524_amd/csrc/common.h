@@ -149,6 +149,9 @@ struct gnn_graph {
   int32_t* eid_t;
   int32_t* bucket_of[2];
   int32_t* order[2];
+  // (vertex, first edge, edge behind the last, 0) in degree order: what a row group needs first, in one load where the
+  // order and then the two bounds would be two that wait for each other
+  int4* rows[2];
   int32_t* bucket_offsets[2];            // device copies
   int32_t h_bucket_offsets[2][GNN_NUM_BUCKETS + 1];  // host copies
   int32_t max_degree[2];

@@ -20,6 +20,7 @@
 #include <hip/hip_fp16.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "gat_common.h"
 #include "rowgroup.h"
@@ -66,9 +67,8 @@ struct GroupLds {
 // recompute only when computation / memory is O(1); here it is |E|/|V|).
 template <int L, int NV, bool WT, int ES>
 __global__ __launch_bounds__(kBlock) void k_gat_fwd(
-    RowLaunch rl, const int32_t* __restrict__ order, const int32_t* __restrict__ indptr,
-    const int32_t* __restrict__ indices, const float* __restrict__ z, const float* __restrict__ el,
-    const float* __restrict__ er, GatDims dm, float* __restrict__ out, float* __restrict__ m_out,
+    RowLaunch rl, const int4* __restrict__ rows, const int32_t* __restrict__ indices, const float* __restrict__ z,
+    const float* __restrict__ el, const float* __restrict__ er, GatDims dm, float* __restrict__ out, float* __restrict__ m_out,
     float* __restrict__ d_out, float* __restrict__ t_out, float* __restrict__ sg_out) {
   // A row group has GL = L * ES lanes: L column lanes (float4 slots), replicated ES times.  The
   // chunk phase spreads all GL lanes over (edge, head) pairs; in the row phase replica s takes
@@ -106,8 +106,8 @@ __global__ __launch_bounds__(kBlock) void k_gat_fwd(
   const int h = li & (Hp - 1);
   const bool head_ok = h < H;
 
-  const int32_t v = order[r];
-  const int32_t beg = indptr[v], end = indptr[v + 1];
+  const int4 ri = rows[r];
+  const int32_t v = ri.x, beg = ri.y, end = ri.z;
   const float er_vh = head_ok ? er[(int64_t)v * H + h] : 0.f;
 
   int hs[NV];
@@ -123,14 +123,45 @@ __global__ __launch_bounds__(kBlock) void k_gat_fwd(
   }
 
   float m_run = -INFINITY, d_run = 0.f, d2_run = 0.f;
+  const int32_t e_first = beg + gi * epc + e_loc;
+  int32_t u_next = e_first < end ? indices[e_first] : 0;
   for (int32_t c0 = beg + gi * epc; c0 < end; c0 += ngrp * epc) {
-    // chunk phase: lane = (edge e_loc of the chunk, head h)
+    // On short rows a row is one chunk and a chain of loads that wait for each other: bounds, sources, then scalars,
+    // then rows.  The rows need nothing but the sources, so the first batch of them travels together with the scalars, which
+    // are asked for first because loads come back in order; and so do the next chunk's sources.  A batch that is not
+    // whole asks for what it has, all at once, instead of one by one.  us, rows after the scores -> here: forward with
+    // stash, 2 10^4 vertices, 10^5 edges, 8 x 8 18.2 -> 15.7; 10^5, 2 10^6, 1 x 64 118 -> 72; source side 18.5 -> 13.1,
+    // 85 -> 77; 10^4, 6 10^5, 8 x 8 34 -> 24.
     const int32_t e = c0 + e_loc;
     const bool e_ok = e < end;
-    const int32_t u = e_ok ? indices[e] : 0;
+    const int32_t u = u_next;
+    const float el_u = e_ok && head_ok ? el[(int64_t)u * H + h] : 0.f;
+    if (h == 0) l_idx[e_loc] = u;
+    const int step = ngrp * epc;
+    u_next = e < end - step ? indices[e + step] : 0;
+    wave_lds_fence();
+    const int cnt = min(epc, end - c0);
+    float4 row[kU][NV];
+    auto fetch_some = [&](int t, auto whole) {  // whole: the batch has all its edges
+#pragma unroll
+      for (int q = 0; q < kU; ++q) {
+        if (!whole.value && t + q * ES >= cnt) continue;
+        int uu = l_idx[t + q * ES];
+        if (L == 64) uu = __builtin_amdgcn_readfirstlane(uu);
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+          if (slot_ok[j]) row[q][j] = ld4(z + (int64_t)uu * HF + 4 * (cl + j * L));
+      }
+    };
+    auto fetch = [&](int t) {
+      if (ES == 1 && t + kU <= cnt) fetch_some(t, std::true_type{});
+      else fetch_some(t, std::false_type{});
+    };
+    fetch(rep);
+    // chunk phase: lane = (edge e_loc of the chunk, head h)
     float s = -INFINITY, raw = 0.f;
     if (e_ok && head_ok) {
-      raw = el[(int64_t)u * H + h] + er_vh;
+      raw = el_u + er_vh;
       s = leaky(raw, dm.slope);
     }
     const float cmax = group_max_from<GL>(s, Hp);
@@ -139,7 +170,6 @@ __global__ __launch_bounds__(kBlock) void k_gat_fwd(
     const float sc = (m_run == -INFINITY) ? 0.f : __expf(m_run - m_new);
     d_run = d_run * sc + p;
     m_run = m_new;
-    if (h == 0) l_idx[e_loc] = u;
     l_p[li] = p;
     if (WT) {
       const float p2 = raw > 0.f ? p : dm.slope * p;  // weight times LeakyReLU'
@@ -155,23 +185,10 @@ __global__ __launch_bounds__(kBlock) void k_gat_fwd(
       part[j] = make_float4(0.f, 0.f, 0.f, 0.f);
       part2[j] = part[j];
     }
-    const int cnt = min(epc, end - c0);
-    int t = rep;
-    for (; t + (kU - 1) * ES < cnt; t += kU * ES) {
-      int uu[kU];
-      float4 row[kU][NV];
+    auto add_some = [&](int t, auto whole) {
 #pragma unroll
       for (int q = 0; q < kU; ++q) {
-        uu[q] = l_idx[t + q * ES];
-        if (L == 64) uu[q] = __builtin_amdgcn_readfirstlane(uu[q]);
-      }
-#pragma unroll
-      for (int q = 0; q < kU; ++q)
-#pragma unroll
-        for (int j = 0; j < NV; ++j)
-          if (slot_ok[j]) row[q][j] = ld4(z + (int64_t)uu[q] * HF + 4 * (cl + j * L));
-#pragma unroll
-      for (int q = 0; q < kU; ++q)
+        if (!whole.value && t + q * ES >= cnt) continue;
 #pragma unroll
         for (int j = 0; j < NV; ++j)
           if (slot_ok[j]) {
@@ -179,18 +196,13 @@ __global__ __launch_bounds__(kBlock) void k_gat_fwd(
             fma4(part[j], l_p[pi], row[q][j]);
             if (WT) fma4(part2[j], l_p2[pi], row[q][j]);
           }
-    }
-    for (; t < cnt; t += ES) {
-      int uu = l_idx[t];
-      if (L == 64) uu = __builtin_amdgcn_readfirstlane(uu);
-#pragma unroll
-      for (int j = 0; j < NV; ++j)
-        if (slot_ok[j]) {
-          const float4 row1 = ld4(z + (int64_t)uu * HF + 4 * (cl + j * L));
-          const int pi = (t << dm.log2Hp) + hs[j];
-          fma4(part[j], l_p[pi], row1);
-          if (WT) fma4(part2[j], l_p2[pi], row1);
-        }
+      }
+    };
+    for (int t = rep; t < cnt;) {
+      if (ES == 1 && t + kU <= cnt) add_some(t, std::true_type{});
+      else add_some(t, std::false_type{});
+      t += kU * ES;
+      if (t < cnt) fetch(t);
     }
 #pragma unroll
     for (int j = 0; j < NV; ++j) {  // rescale to the new max, add the chunk
@@ -433,9 +445,8 @@ __global__ __launch_bounds__(kBlock) void k_gat_bwd_dst(
 // dz[u] = sum_out alpha_e gout[v] + a_l del[u] + a_r der[u];  writes del[u,h] too
 template <int L, int NV, int ES>
 __global__ __launch_bounds__(kBlock) void k_gat_bwd_src(
-    RowLaunch rl, const int32_t* __restrict__ order_t, const int32_t* __restrict__ indptr_t,
-    const int32_t* __restrict__ indices_t, const float* __restrict__ z, const float* __restrict__ el,
-    const float4* __restrict__ vstate, const float* __restrict__ der, const float* __restrict__ gout,
+    RowLaunch rl, const int4* __restrict__ rows_t, const int32_t* __restrict__ indices_t, const float* __restrict__ z,
+    const float* __restrict__ el, const float4* __restrict__ vstate, const float* __restrict__ der, const float* __restrict__ gout,
     const float* __restrict__ a_l, const float* __restrict__ a_r, GatDims dm,
     float* __restrict__ dz, float* __restrict__ del,
     const float* __restrict__ alpha_t /* nullable: stashed softmax values, CSC order, signed */) {
@@ -471,8 +482,8 @@ __global__ __launch_bounds__(kBlock) void k_gat_bwd_src(
   const int h = li & (Hp - 1);
   const bool head_ok = h < H;
 
-  const int32_t u = order_t[r];
-  const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
+  const int4 ri = rows_t[r];
+  const int32_t u = ri.x, beg = ri.y, end = ri.z;
   const float el_uh = head_ok ? el[(int64_t)u * H + h] : 0.f;
 
   int hs[NV];
@@ -487,14 +498,44 @@ __global__ __launch_bounds__(kBlock) void k_gat_bwd_src(
     acc2[j] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
 
+  // Needed at the end of the row.  Where a wavefront has one row it travels from here on (50 000 vertices, 10^6 edges, 4 x 64:
+  // 146 -> 135 us); with several rows the registers cost more than the wait (2 10^4, 10^5, 8 x 8: 13 -> 15 us).
+  constexpr bool kOwnEarly = L == 64 && NV == 1;
+  float4 z_own = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (kOwnEarly && slot_ok[0]) z_own = ld4(z + (int64_t)u * HF + 4 * cl);
+
   float sd_run = 0.f;  // partial of sum alpha_e g_e D[v,h]
+  const int32_t e_first = beg + gi * epc + e_loc;
+  int32_t v_next = e_first < end ? indices_t[e_first] : 0;
   for (int32_t c0 = beg + gi * epc; c0 < end; c0 += ngrp * epc) {
-    const int32_t e = c0 + e_loc;
+    // as in k_gat_fwd: the first rows and the next chunk's destinations travel while the weights are made
+    const int32_t e = c0 + e_loc, v = v_next;
     const bool e_ok = e < end;
-    const int32_t v = e_ok ? indices_t[e] : 0;
+    const float4 vs = e_ok && head_ok ? vstate[(int64_t)v * H + h] : make_float4(0.f, 0.f, 0.f, 0.f);  // (er, m, 1/d, D)
+    if (h == 0) l_idx[e_loc] = v;
+    const int step = ngrp * epc;
+    v_next = e < end - step ? indices_t[e + step] : 0;
+    wave_lds_fence();
+    const int cnt = min(epc, end - c0);
+    float4 row[kU][NV];
+    auto fetch_some = [&](int t, auto whole) {  // whole: the batch has all its edges
+#pragma unroll
+      for (int k = 0; k < kU; ++k) {
+        if (!whole.value && t + k * ES >= cnt) continue;
+        int vv = l_idx[t + k * ES];
+        if (L == 64) vv = __builtin_amdgcn_readfirstlane(vv);
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+          if (slot_ok[j]) row[k][j] = ld4(gout + (int64_t)vv * HF + 4 * (cl + j * L));
+      }
+    };
+    auto fetch = [&](int t) {
+      if (ES == 1 && t + kU <= cnt) fetch_some(t, std::true_type{});
+      else fetch_some(t, std::false_type{});
+    };
+    fetch(rep);
     float alpha = 0.f, ag = 0.f;
     if (e_ok && head_ok) {
-      const float4 vs = vstate[(int64_t)v * H + h];  // (er, m, 1/d, D)
       if (alpha_t) {  // the "fusion with stashing" arm: nothing per-edge is recomputed
         const float a = alpha_t[(int64_t)e * H + h];
         alpha = fabsf(a);
@@ -506,7 +547,6 @@ __global__ __launch_bounds__(kBlock) void k_gat_bwd_src(
       }
       sd_run = fmaf(ag, vs.w, sd_run);
     }
-    if (h == 0) l_idx[e_loc] = v;
     l_p[li] = alpha;
     l_p2[li] = ag;
     wave_lds_fence();
@@ -516,23 +556,10 @@ __global__ __launch_bounds__(kBlock) void k_gat_bwd_src(
       part1[j] = make_float4(0.f, 0.f, 0.f, 0.f);
       part2[j] = part1[j];
     }
-    const int cnt = min(epc, end - c0);
-    int t = rep;
-    for (; t + (kU - 1) * ES < cnt; t += kU * ES) {
-      int vv[kU];
-      float4 row[kU][NV];
+    auto add_some = [&](int t, auto whole) {
 #pragma unroll
       for (int k = 0; k < kU; ++k) {
-        vv[k] = l_idx[t + k * ES];
-        if (L == 64) vv[k] = __builtin_amdgcn_readfirstlane(vv[k]);
-      }
-#pragma unroll
-      for (int k = 0; k < kU; ++k)
-#pragma unroll
-        for (int j = 0; j < NV; ++j)
-          if (slot_ok[j]) row[k][j] = ld4(gout + (int64_t)vv[k] * HF + 4 * (cl + j * L));
-#pragma unroll
-      for (int k = 0; k < kU; ++k)
+        if (!whole.value && t + k * ES >= cnt) continue;
 #pragma unroll
         for (int j = 0; j < NV; ++j)
           if (slot_ok[j]) {
@@ -540,18 +567,13 @@ __global__ __launch_bounds__(kBlock) void k_gat_bwd_src(
             fma4(part1[j], l_p[pi], row[k][j]);
             fma4(part2[j], l_p2[pi], row[k][j]);
           }
-    }
-    for (; t < cnt; t += ES) {
-      int vv = l_idx[t];
-      if (L == 64) vv = __builtin_amdgcn_readfirstlane(vv);
-#pragma unroll
-      for (int j = 0; j < NV; ++j)
-        if (slot_ok[j]) {
-          const float4 row = ld4(gout + (int64_t)vv * HF + 4 * (cl + j * L));
-          const int pi = (t << dm.log2Hp) + hs[j];
-          fma4(part1[j], l_p[pi], row);
-          fma4(part2[j], l_p2[pi], row);
-        }
+      }
+    };
+    for (int t = rep; t < cnt;) {
+      if (ES == 1 && t + kU <= cnt) add_some(t, std::true_type{});
+      else add_some(t, std::false_type{});
+      t += kU * ES;
+      if (t < cnt) fetch(t);
     }
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
@@ -597,7 +619,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_bwd_src(
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     float p = 0.f;
-    if (slot_ok[j]) p = dot4(ld4(z + (int64_t)u * HF + 4 * (cl + j * L)), acc2[j]);
+    if (slot_ok[j]) p = dot4(kOwnEarly ? z_own : ld4(z + (int64_t)u * HF + 4 * (cl + j * L)), acc2[j]);
     if (rep == 0) l_red[j * L + cl] = p;   // per-slot partials of <z[u], A2[u]>, read by head_sum
   }
   wave_lds_fence();
@@ -759,11 +781,9 @@ struct FwdLauncher {
       const RowLaunch rl{sp.hub.end, g->n};
       if (grid != 0) {
         if (t)
-          k_gat_fwd<L, NV, true, ES><<<grid, kBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, z, el,
-                                                              er, dm, out, m, d, t, sg);
+          k_gat_fwd<L, NV, true, ES><<<grid, kBlock, 0, st>>>(rl, g->rows[0], g->indices, z, el, er, dm, out, m, d, t, sg);
         else
-          k_gat_fwd<L, NV, false, ES><<<grid, kBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, z, el,
-                                                               er, dm, out, m, d, nullptr, nullptr);
+          k_gat_fwd<L, NV, false, ES><<<grid, kBlock, 0, st>>>(rl, g->rows[0], g->indices, z, el, er, dm, out, m, d, nullptr, nullptr);
         GNN_LAUNCH_CHECK();
       }
     }
@@ -941,8 +961,7 @@ struct BwdSrcLauncher {
       const unsigned grid = sp.hub_grid + sp.rest_grid;
       const RowLaunch rl{sp.hub.end, g->n};
       if (grid != 0) {
-        k_gat_bwd_src<L, NV, ES><<<grid, kBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, z, el,
-                                                          vstate, der, gout, a_l, a_r, dm, dz, del, alpha_t);
+        k_gat_bwd_src<L, NV, ES><<<grid, kBlock, 0, st>>>(rl, g->rows[1], g->indices_t, z, el, vstate, der, gout, a_l, a_r, dm, dz, del, alpha_t);
         GNN_LAUNCH_CHECK();
       }
     }

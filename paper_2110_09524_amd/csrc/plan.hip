@@ -510,6 +510,7 @@ struct DegreeSides {
   const int32_t* ptr[2];
   int32_t* bucket[2];
   int32_t* order[2];
+  int4* rows[2];
 };
 
 __global__ __launch_bounds__(256) void k_degree_histograms(int32_t n, int bins, DegreeSides sides,
@@ -546,7 +547,8 @@ __global__ __launch_bounds__(256) void k_degree_scatter(int32_t n, int bins, Deg
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const bool ok = v < n;
-  const int d = ok ? sides.ptr[side][v + 1] - sides.ptr[side][v] : -1;
+  const int32_t beg = ok ? sides.ptr[side][v] : 0, end = ok ? sides.ptr[side][v + 1] : -1;
+  const int d = end - beg;
   int rank = 0;
   unsigned long long todo = __ballot(ok);
   while (todo) {  // uniform over the wavefront: one turn per distinct degree
@@ -563,6 +565,15 @@ __global__ __launch_bounds__(256) void k_degree_scatter(int32_t n, int bins, Deg
   for (int q = 0; q < w; ++q) rank += l_bins[q * bins + d];
   const int64_t at = first[((int64_t)side * bins + (bins - 1 - d)) * gridDim.x + blockIdx.x] - (int64_t)side * n;
   sides.order[side][at + rank] = (int32_t)v;
+  sides.rows[side][at + rank] = make_int4((int32_t)v, beg, end, 0);
+}
+
+__global__ void k_row_table(int32_t n, const int32_t* __restrict__ order, const int32_t* __restrict__ ptr,
+                            int4* __restrict__ rows) {
+  const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (r >= n) return;
+  const int32_t v = order[r];
+  rows[r] = make_int4(v, ptr[v], ptr[v + 1], 0);
 }
 
 // The histogram is counted per workgroup in LDS first, one vote per distinct bucket of a
@@ -738,6 +749,7 @@ static void free_all(gnn_graph* g) {
   for (int s = 0; s < 2; ++s) {
     pool_free(g->bucket_of[s]);
     pool_free(g->order[s]);
+    pool_free(g->rows[s]);
     pool_free(g->bucket_offsets[s]);
     pool_free(g->bptr[s]);
     pool_free(g->bcol[s]);
@@ -830,6 +842,8 @@ static gnn_status_t sort_side(gnn_graph* g, int side, const int32_t* ptr, int32_
   GNN_HIP(tmp.alloc((char**)&scratch, bytes));
   GNN_HIP(rocprim::radix_sort_pairs_desc(scratch, bytes, deg, deg_sorted, ids, g->order[side],
                                          (size_t)n, 0, key_bits, st));
+  k_row_table<<<cdiv(n, thr), thr, 0, st>>>(n, g->order[side], ptr, g->rows[side]);
+  GNN_LAUNCH_CHECK();
   return GNN_OK;
 }
 
@@ -841,12 +855,14 @@ static gnn_status_t build_sides(gnn_graph* g, int32_t* hist, TempBuffers& tmp, P
   for (int side = 0; side < 2; ++side) {
     GNN_HIP(pool_alloc((void**)&g->bucket_of[side], sizeof(int32_t) * (n ? n : 1)));
     GNN_HIP(pool_alloc((void**)&g->order[side], sizeof(int32_t) * (n ? n : 1)));
+    GNN_HIP(pool_alloc((void**)&g->rows[side], sizeof(int4) * (n ? n : 1)));
     GNN_HIP(pool_alloc((void**)&g->bucket_offsets[side], sizeof(int32_t) * (GNN_NUM_BUCKETS + 1)));
   }
   const int bins = std::max(g->max_degree[0], g->max_degree[1]) + 1;
   const int64_t blocks = cdiv(n, 256), table_len = 2 * (int64_t)bins * blocks;
   if (n > 0 && bins <= kCountMaxBins && table_len <= kCountMaxTable) {
-    const DegreeSides sides{{ptr[0], ptr[1]}, {g->bucket_of[0], g->bucket_of[1]}, {g->order[0], g->order[1]}};
+    const DegreeSides sides{{ptr[0], ptr[1]}, {g->bucket_of[0], g->bucket_of[1]}, {g->order[0], g->order[1]},
+                            {g->rows[0], g->rows[1]}};
     int32_t *table = nullptr, *first = nullptr;
     GNN_HIP(tmp.alloc(&table, (size_t)table_len));
     GNN_HIP(tmp.alloc(&first, (size_t)table_len));
