@@ -644,13 +644,13 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
     const int32_t* __restrict__ indices_t, const int32_t* __restrict__ eid_t, const float* __restrict__ hk,
     const float* __restrict__ pseudo, const float* __restrict__ pseudo_t /* nullable: pseudo in this walk's order */,
     ProjArgs pa, const float* __restrict__ mu, const float* __restrict__ inv_sigma, const float* __restrict__ gout,
-    PsParams pm, float* __restrict__ dhk, float* __restrict__ partial, float* __restrict__ gpseudo /* nullable */) {
-  constexpr int NVALS = PROJ ? kPsValsProj : kPsVals;
+    PsParams pm, float* __restrict__ dhk, double* __restrict__ partial, float* __restrict__ gpseudo /* nullable */) {
+  constexpr int NVALS = 2 * KT * RT + (PROJ ? 3 * RT : 0);
   constexpr int GPB = kPsBlock / G;
   constexpr int GS = G + KT * G + G * G;  // indices | weights [KT][G] | partial dot products [column lane][edge]
   __shared__ __align__(16) float lds[GPB * GS];
   __shared__ float coop_buf[GPB * G * 4];
-  __shared__ float blk[GPB][NVALS];
+  __shared__ double blk[GPB][NVALS];
   const int li = threadIdx.x & (G - 1);
   const int grp = threadIdx.x / G;
   int64_t r;
@@ -659,13 +659,9 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
   const bool active = pick_row<GPB>(rl, grp, rr, r, gi, ngrp);
   const int K = pm.K, R = pm.R, F = pm.F, KF = K * F, F4 = F / 4;
   const float inv_k = 1.f / (float)K;
-  float gm_acc[KT][RT], gs_acc[KT][RT], gp_acc[3 * RT];  // sums over the edges this lane owned
+  float sums[NVALS];  // over the edges this lane owned
 #pragma unroll
-  for (int k = 0; k < KT; ++k)
-#pragma unroll
-    for (int d = 0; d < RT; ++d) gm_acc[k][d] = gs_acc[k][d] = 0.f;
-#pragma unroll
-  for (int i = 0; i < 3 * RT; ++i) gp_acc[i] = 0.f;
+  for (int i = 0; i < NVALS; ++i) sums[i] = 0.f;
   if (active) {
     const PsKernels<KT, RT> pk = load_kernels<KT, RT>(mu, inv_sigma, K, R);
     const int32_t u = order_t[r];
@@ -746,8 +742,8 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
             const float diff = m[d] - pk.mu[k][d];
             const float is = pk.is[k][d];
             const float t = dlog * diff * is;  // padded dimensions: is = 0
-            gm_acc[k][d] = fmaf(t, is, gm_acc[k][d]);
-            gs_acc[k][d] = fmaf(-t, diff, gs_acc[k][d]);
+            sums[k * RT + d] = fmaf(t, is, sums[k * RT + d]);
+            sums[KT * RT + k * RT + d] = fmaf(-t, diff, sums[KT * RT + k * RT + d]);
             gm[d] = fmaf(-t, is, gm[d]);
           }
         }
@@ -755,9 +751,10 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
 #pragma unroll
           for (int d = 0; d < RT; ++d) {
             const float dpre = gm[d] * (1.f - m[d] * m[d]);  // through the tanh; padded dimensions: gm = 0
-            gp_acc[3 * d] = fmaf(dpre, cu, gp_acc[3 * d]);
-            gp_acc[3 * d + 1] = fmaf(dpre, cv, gp_acc[3 * d + 1]);
-            gp_acc[3 * d + 2] += dpre;
+            float* gp = sums + 2 * KT * RT + 3 * d;
+            gp[0] = fmaf(dpre, cu, gp[0]);
+            gp[1] = fmaf(dpre, cv, gp[1]);
+            gp[2] += dpre;
           }
         } else if (gpseudo != nullptr) {
 #pragma unroll
@@ -781,32 +778,66 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
     }
     if (col_ok && (!rr.coop || grp == 0)) st4(dhk + (int64_t)u * KF + 4 * li, acc);
   }
-  // the group's lanes are added in a fixed (butterfly) order, then the groups in order; what K and R leave out stays 0
-  for (int i = li; i < NVALS; i += G) blk[grp][i] = 0.f;
-  wave_lds_fence();
+  // The group's lanes are added in a fixed (butterfly) order, then the groups in order; what K and R leave out is 0.  From
+  // here on in 64 bits: the sums over all edges cancel, the bias' gradient most (1.12 10^8 edges, four inputs, its worst
+  // error 2.6e-5, with two kernels for the two sides 6.0e-6, now 1.6e-6; the time is unchanged).
 #pragma unroll
-  for (int k = 0; k < KT; ++k)
-#pragma unroll
-    for (int d = 0; d < RT; ++d) {
-      const bool used = k < K && d < R;
-      const float a = used ? group_sum_from<G>(gm_acc[k][d], 1) : 0.f, b = used ? group_sum_from<G>(gs_acc[k][d], 1) : 0.f;
-      if (li == 0) {
-        blk[grp][k * kPsR + d] = a;
-        blk[grp][kPsK * kPsR + k * kPsR + d] = b;
-      }
-    }
-  if (PROJ) {
-#pragma unroll
-    for (int i = 0; i < 3 * RT; ++i) {
-      const float a = i / 3 < R ? group_sum_from<G>(gp_acc[i], 1) : 0.f;
-      if (li == 0) blk[grp][kPsVals + i] = a;
-    }
+  for (int i = 0; i < NVALS; ++i) {
+    const double s = group_sum_wide<G>((double)sums[i]);
+    if (li == 0) blk[grp][i] = s;
   }
   __syncthreads();
   if (threadIdx.x < NVALS) {
-    float s = 0.f;
+    double s = 0.;
     for (int g2 = 0; g2 < GPB; ++g2) s += blk[g2][threadIdx.x];
     partial[(int64_t)blockIdx.x * NVALS + threadIdx.x] = s;
+  }
+}
+
+// The sums over the workgroups' partials [parts][nvals], nvals <= kPsValsProj, in two launches: ranges of kParamChunk parts,
+// one workgroup each, then those ranges, by the one workgroup that also stores the gradients.  The order is fixed.
+constexpr int kParamChunk = 256;
+
+// thread c < nvals returns the sum of column c
+__device__ __forceinline__ double sum_columns(int nvals, int parts, const double* __restrict__ partial) {
+  __shared__ double sub[kPsBlock];
+  const int slots = kPsBlock / nvals, c = threadIdx.x % nvals, slot = threadIdx.x / nvals;
+  double s = 0.;
+  if (slot < slots) {
+    for (int z = slot; z < parts; z += slots) s += partial[(int64_t)z * nvals + c];
+    sub[threadIdx.x] = s;
+  }
+  __syncthreads();
+  if (slot == 0)
+    for (int q = 1; q < slots; ++q) s += sub[q * nvals + c];
+  return s;
+}
+__global__ __launch_bounds__(kPsBlock) void k_gmmp_param_rows(int nvals, int parts, const double* __restrict__ partial,
+                                                              double* __restrict__ rows) {
+  const int z0 = blockIdx.x * kParamChunk;
+  const double s = sum_columns(nvals, min(kParamChunk, parts - z0), partial + (int64_t)z0 * nvals);
+  if (threadIdx.x < nvals) rows[(int64_t)blockIdx.x * nvals + threadIdx.x] = s;
+}
+// columns: gmu [kt][rt], ginv_sigma [kt][rt], then, where gP is not null, (gP[d,0], gP[d,1], gpb[d]) [rt]
+__global__ __launch_bounds__(kPsBlock) void k_gmmp_param_totals(int K, int R, int kt, int rt, int nrows,
+                                                                const double* __restrict__ rows, float* __restrict__ gmu,
+                                                                float* __restrict__ gis, float* __restrict__ gP /* nullable */,
+                                                                float* __restrict__ gpb) {
+  const int krt = kt * rt, nvals = 2 * krt + (gP != nullptr ? 3 * rt : 0);
+  const float s = (float)sum_columns(nvals, nrows, rows);
+  int i = threadIdx.x;
+  if (i >= nvals) return;
+  if (i < 2 * krt) {
+    float* g = i < krt ? gmu : gis;
+    i = i < krt ? i : i - krt;
+    const int k = i / rt, d = i - k * rt;
+    if (k < K && d < R) g[k * R + d] = s;
+  } else {
+    i -= 2 * krt;
+    const int d = i / 3, j = i - 3 * d;
+    if (d >= R) return;
+    if (j < 2) gP[2 * d + j] = s;
+    else gpb[d] = s;
   }
 }
 
@@ -948,7 +979,8 @@ static GmmpWs gmmp_ws_layout(const gnn_graph_t* g, int fin, int fout, int K) {
   auto take = [&](size_t bytes) { size_t o = off; off += ws_granule(bytes); return o; };
   w.nblk = ps_dst_blocks(g, fout);
   w.dhk = take(sizeof(float) * (size_t)g->n * K * fout);
-  w.partial = take(sizeof(float) * (size_t)(w.nblk + 1 + sum_partials_scratch_rows((int)w.nblk)) * kPsValsProj);
+  // doubles where one walk does both sides, floats (with fewer columns) where the destination side has its own
+  w.partial = take(sizeof(double) * (size_t)(w.nblk + 1 + sum_partials_scratch_rows((int)w.nblk)) * kPsValsProj);
   w.split_k = gemm_pick_split_k(fin, K * fout, g->n);
   w.gemm = take(w.split_k > 1 ? sizeof(float) * (size_t)w.split_k * fin * K * fout : 0);
   w.total = off;
@@ -995,6 +1027,24 @@ static gnn_status_t for_kernels(int K, int R, Fn fn) {
     case 3: return dims(std::integral_constant<int, 3>{});
     default: return dims(std::integral_constant<int, 4>{});
   }
+}
+
+// the parameters' gradients from k_gmmp_bwd_nr's partials; the rows of ranges go behind those
+static gnn_status_t wide_param_sums(int K, int R, int kt, int rt, int parts, double* partial, float* gmu, float* gis,
+                                    float* gP, float* gpb, hipStream_t st) {
+  const int nvals = 2 * kt * rt + (gP != nullptr ? 3 * rt : 0);
+  int nrows = parts;
+  const double* rows = partial;
+  if (parts > kParamChunk) {
+    double* out = partial + (int64_t)parts * nvals;
+    nrows = (int)cdiv(parts, kParamChunk);
+    k_gmmp_param_rows<<<(unsigned)nrows, kPsBlock, 0, st>>>(nvals, parts, partial, out);
+    GNN_LAUNCH_CHECK();
+    rows = out;
+  }
+  k_gmmp_param_totals<<<1, kPsBlock, 0, st>>>(K, R, kt, rt, nrows, rows, gmu, gis, gP, gpb);
+  GNN_LAUNCH_CHECK();
+  return GNN_OK;
 }
 
 // With coordinates given per edge the one walk stores gpseudo through the CSC position -> CSR edge id table, 4 R bytes at a time,
@@ -1072,11 +1122,12 @@ extern "C" gnn_status_t gnn_gmmp_bwd(const gnn_graph_t* g, int fin, int fout, in
   char* base = static_cast<char*>(ws);
   float* dhk = reinterpret_cast<float*>(base + W.dhk);
   float* partial = reinterpret_cast<float*>(base + W.partial);
+  double* wide = reinterpret_cast<double*>(base + W.partial);
   float* part = reinterpret_cast<float*>(base + W.gemm);
   const PsParams pm{k, r, fout};
   const int KF = k * fout;
   const int G = nr_lanes(k, fout);
-  auto param_sums = [&](unsigned grid) -> gnn_status_t {
+  auto param_sums = [&](unsigned grid) -> gnn_status_t {  // of the destination side's kernels
     float* totals = partial + (int64_t)grid * kPsVals;
     GNN_TRY(sum_partials_two_level(kPsVals, (int)grid, partial, totals + kPsVals, totals, st));
     k_gmmp_param_split<<<1, 64, 0, st>>>(k, r, totals, gmu, ginv_sigma);
@@ -1093,11 +1144,11 @@ extern "C" gnn_status_t gnn_gmmp_bwd(const gnn_graph_t* g, int fin, int fout, in
       if (grid == 0) return GNN_OK;
       k_gmmp_bwd_nr<GL, false, kPsK, kPsR><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, g->eid_t, hk,
                                                                      pseudo, pseudo_t, ProjArgs{}, mu, inv_sigma, gout, pm,
-                                                                     dhk, partial, gpseudo);
+                                                                     dhk, wide, gpseudo);
       GNN_LAUNCH_CHECK();
       return GNN_OK;
     }));
-    GNN_TRY(param_sums(grid));
+    GNN_TRY(wide_param_sums(k, r, kPsK, kPsR, (int)grid, wide, gmu, ginv_sigma, nullptr, nullptr, st));
   } else {
     {
       ProfScope p("gmmp_bwd_dst", st);
@@ -1259,7 +1310,7 @@ extern "C" gnn_status_t gnn_monet_bwd(const gnn_graph_t* g, int fin, int fout, i
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* base = static_cast<char*>(ws);
   float* dhk = reinterpret_cast<float*>(base + W.dhk);
-  float* partial = reinterpret_cast<float*>(base + W.partial);
+  double* partial = reinterpret_cast<double*>(base + W.partial);
   float* part = reinterpret_cast<float*>(base + W.gemm);
   const PsParams pm{k, r, fout};
   const ProjArgs pa{c, proj_w, proj_b};
@@ -1282,12 +1333,10 @@ extern "C" gnn_status_t gnn_monet_bwd(const gnn_graph_t* g, int fin, int fout, i
         return GNN_OK;
       });
     }));
-    float* totals = partial + (int64_t)grid * kPsValsProj;
-    GNN_TRY(sum_partials_two_level(kPsValsProj, (int)grid, partial, totals + kPsValsProj, totals, st));
-    k_gmmp_param_split<<<1, 64, 0, st>>>(k, r, totals, gmu, ginv_sigma);
-    GNN_LAUNCH_CHECK();
-    k_pseudo_proj_split<<<1, 64, 0, st>>>(r, totals + kPsVals, gproj_w, gproj_b);
-    GNN_LAUNCH_CHECK();
+    GNN_TRY(for_kernels(k, r, [&](auto kernels, auto dims) -> gnn_status_t {
+      return wide_param_sums(k, r, decltype(kernels)::value, decltype(dims)::value, (int)grid, partial, gmu, ginv_sigma,
+                             gproj_w, gproj_b, st);
+    }));
   }
   GNN_TRY(gemm_f32(fin, KF, g->n, x, fin, true, dhk, KF, false, gw_fc, KF, W.split_k, part, st));
   if (gx) GNN_TRY(gemm_f32(g->n, fin, KF, dhk, KF, false, w_fc, KF, true, gx, fin, 1, nullptr, st));

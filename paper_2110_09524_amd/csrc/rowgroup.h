@@ -62,6 +62,21 @@ __device__ __forceinline__ float group_sum_from(float v, int lo_stride) {
   for (int off = lo_stride; off < L; off <<= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
+// the same over the lanes next to each other, in 64 bits; L <= 16
+template <int CTRL>
+__device__ __forceinline__ double dpp_move_wide(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true));
+}
+template <int L>
+__device__ __forceinline__ double group_sum_wide(double v) {
+  static_assert(L <= 16, "one DPP row");
+  if (L > 1) v += dpp_move_wide<0xB1>(v);
+  if (L > 2) v += dpp_move_wide<0x4E>(v);
+  if (L > 4) v += dpp_move_wide<0x141>(v);
+  if (L > 8) v += dpp_move_wide<0x140>(v);
+  return v;
+}
 
 // Pace of the persistent kernels.  Workgroups that share an L2 (one XCD) walk the column blocks
 // step by step: a workgroup that has finished step `step` reports it on its XCD's counter and

@@ -102,6 +102,16 @@ def test_every_number_of_kernels_and_dimensions(K, r):
         check(synth(rng, indptr, indices, 5, fout, K, r))
 
 
+@pytest.mark.parametrize("n", [32 * 256, 32 * 256 + 1, 16 * 512, 16 * 512 + 1])
+def test_parameter_sums_at_the_edges_of_their_ranges(n):
+    """32 or 16 rows per workgroup, 256 workgroups per range of partial sums: one range, two, one row in the last."""
+    print(f"monet: {n} vertices", flush=True)
+    rng = np.random.default_rng(n)
+    indptr, indices = random_graph(rng, n, 2 * n, self_loops=True, duplicates=True)
+    check(synth(rng, indptr, indices, 4, 4, 2, 1))
+    check(synth(rng, indptr, indices, 4, 16, 3, 3))
+
+
 def test_the_papers_settings_on_a_power_law_graph_and_the_two_call_form():
     """k = 3, r = 3 and k = 2, r = 1 with 16 hidden features (Sec. 7.2, 7.3) on a graph with hub rows.  The
     fused kernels evaluate the same expressions in the same order as projection + general layer, so
