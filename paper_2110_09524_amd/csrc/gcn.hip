@@ -42,15 +42,16 @@ __global__ void k_scale_rows(int64_t quads, int q_per_row, const float* __restri
 
 // ---- single launch: out[row,:] = scale[row] * sum over the row's gathered vertices of feat ----
 // W: every edge carries a static weight (wgt, in the order of cols); scale may then be null
-template <int L, int NV, bool W = false>
+// Rows come with their bounds, and the next chunk's sources travel while a chunk is gathered: us, 30 000 vertices, 10^6 edges,
+// 64 columns, layer 111 -> 99 unsliced.  NS slices of 4 L columns, see xcd_slice and gather_slices.
+template <int L, int NV, bool W = false, int NS = 1>
 __global__ __launch_bounds__(kGcnBlock) void k_rowsum(
-    RowLaunch rl, const int32_t* __restrict__ order, const int32_t* __restrict__ ptr,
-    const int32_t* __restrict__ cols, const float* __restrict__ feat, int F,
+    RowLaunch rl, const int4* __restrict__ rows, const int32_t* __restrict__ cols, const float* __restrict__ feat, int F,
     const float* __restrict__ scale, float* __restrict__ out, const float* __restrict__ wgt = nullptr) {
   constexpr int G = kWave / L;
   constexpr int GPB = G * (kGcnBlock / kWave);
   constexpr int NC = 4 * NV;
-  constexpr int U = 4;
+  constexpr int U = NV == 1 && L >= 8 ? 8 : 4;  // gathered rows in flight per lane
   __shared__ int lds[GPB * L];
   __shared__ float lds_w[W ? GPB * L : 1];
   __shared__ float coop_buf[GPB * L * NC];
@@ -60,27 +61,38 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum(
   int64_t r;
   int gi, ngrp;
   RowRange rr;
-  if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp)) return;
+  unsigned block;
+  const int col0 = xcd_slice<NS>(block) * 4 * L;
+  if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp, block)) return;
+  feat += col0;
+  out += col0;
   int* l_idx = lds + grp * L;
   float* l_w = lds_w + (W ? grp * L : 0);
-  const int32_t v = order[r];
-  const int32_t beg = ptr[v], end = ptr[v + 1];
+  const int4 row = rows[r];
+  const int32_t v = row.x;
+  const uint32_t end = row.z;  // unsigned: positions past 2^31 - 1 are past every row's end
 
   bool slot_ok[NV];
   float4 acc[NV];
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
-    slot_ok[j] = 4 * (li + j * L) < F;
+    slot_ok[j] = NS > 1 || 4 * (li + j * L) < F;
     acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  for (int32_t c0 = beg + gi * L; c0 < end; c0 += ngrp * L) {
-    l_idx[li] = c0 + li < end ? cols[c0 + li] : 0;
-    if (W) l_w[li] = c0 + li < end ? wgt[c0 + li] : 0.f;
+  uint32_t c0 = row.y + gi * L;
+  int32_t c_next = c0 + li < end ? cols[c0 + li] : 0;  // the next chunk's sources travel while this one is gathered
+  float w_next = W && c0 + li < end ? wgt[c0 + li] : 0.f;
+  for (; c0 < end; c0 += ngrp * L) {
+    l_idx[li] = c_next;
+    if (W) l_w[li] = w_next;
     wave_lds_fence();
+    const uint32_t e = c0 + ngrp * L + li;
+    c_next = e < end ? cols[e] : 0;
+    if (W) w_next = e < end ? wgt[e] : 0.f;
     float4 part[NV];  // this chunk's share (two-level summation)
 #pragma unroll
     for (int j = 0; j < NV; ++j) part[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    const int cnt = min(L, end - c0);
+    const int cnt = min((uint32_t)L, end - c0);
     for (int t0 = 0; t0 < cnt; t0 += U) {
       int uu[U];
       float ww[U];
@@ -95,9 +107,17 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum(
         if (!slot_ok[j]) continue;
         float4 rowv[U];
 #pragma unroll
-        for (int t = 0; t < U; ++t) rowv[t] = ld4(feat + (int64_t)uu[t] * F + 4 * (li + j * L));
+        for (int q = 0; q < U; q += 4)
+          if (t0 + q < cnt) {
 #pragma unroll
-        for (int t = 0; t < U; ++t) fma4(part[j], ww[t], rowv[t]);
+            for (int t = q; t < q + 4; ++t) rowv[t] = ld4(feat + (int64_t)uu[t] * F + 4 * (li + j * L));
+          }
+#pragma unroll
+        for (int q = 0; q < U; q += 4)
+          if (t0 + q < cnt) {
+#pragma unroll
+            for (int t = q; t < q + 4; ++t) fma4(part[j], ww[t], rowv[t]);
+          }
       }
     }
 #pragma unroll
@@ -641,43 +661,48 @@ static gnn_status_t launch_rowsum_resident(const gnn_graph_t* g, int side, const
   return GNN_OK;
 }
 
+// W: the same sum with a static weight per edge (wgt in the order of the side's edge array)
+template <int L, int NV, bool W, int NS>
+static gnn_status_t launch_rowsum(const gnn_graph_t* g, int side, const float* feat, int F, const float* scale, float* out,
+                                  hipStream_t st, const float* wgt) {
+  constexpr int GPB = (kWave / L) * (kGcnBlock / kWave);
+  const RowSplit sp = split_rows(g, side, L, GPB);
+  const int32_t* cols = side == 0 ? g->indices : g->indices_t;
+  // hub rows (one workgroup each) and the rest in one launch
+  const unsigned grid = xcd_slice_grid(sp.hub_grid + sp.rest_grid, NS);
+  const RowLaunch rl{sp.hub.end, g->n};
+  if (grid != 0) {
+    k_rowsum<L, NV, W, NS><<<grid, kGcnBlock, 0, st>>>(rl, g->rows[side], cols, feat, F, scale, out, wgt);
+    GNN_LAUNCH_CHECK();
+  }
+  return GNN_OK;
+}
+
+template <bool W, int L, int NV>
+static gnn_status_t launch_rowsum_sliced(const gnn_graph_t* g, int side, const char* name, const float* feat, int F,
+                                         const float* scale, float* out, hipStream_t st, const float* wgt) {
+  ProfScope p(name, st);
+  switch (gather_slices(g, F)) {
+    case 2: return launch_rowsum<8, 1, W, 2>(g, side, feat, F, scale, out, st, wgt);
+    case 4: return launch_rowsum<8, 1, W, 4>(g, side, feat, F, scale, out, st, wgt);
+    case 8: return launch_rowsum<8, 1, W, 8>(g, side, feat, F, scale, out, st, wgt);
+    default: return launch_rowsum<L, NV, W, 1>(g, side, feat, F, scale, out, st, wgt);
+  }
+}
+
 template <int L, int NV>
 struct RowsumLauncher {
   static gnn_status_t run(const gnn_graph_t* g, int side, const char* name, const float* feat, int F,
                           const float* scale, float* out, hipStream_t st) {
-    constexpr int GPB = (kWave / L) * (kGcnBlock / kWave);
-    ProfScope p(name, st);
-    const RowSplit sp = split_rows(g, side, L, GPB);
-    const int32_t* ptr = side == 0 ? g->indptr : g->indptr_t;
-    const int32_t* cols = side == 0 ? g->indices : g->indices_t;
-    // hub rows (one workgroup each) and the rest in one launch
-    const unsigned grid = sp.hub_grid + sp.rest_grid;
-    const RowLaunch rl{sp.hub.end, g->n};
-    if (grid != 0) {
-      k_rowsum<L, NV><<<grid, kGcnBlock, 0, st>>>(rl, g->order[side], ptr, cols, feat, F, scale, out);
-      GNN_LAUNCH_CHECK();
-    }
-    return GNN_OK;
+    return launch_rowsum_sliced<false, L, NV>(g, side, name, feat, F, scale, out, st, nullptr);
   }
 };
 
-// the same sum with a static weight per edge (wgt in the order of the side's edge array)
 template <int L, int NV>
 struct RowsumWeightedLauncher {
   static gnn_status_t run(const gnn_graph_t* g, int side, const char* name, const float* feat, int F,
                           const float* wgt, float* out, hipStream_t st) {
-    constexpr int GPB = (kWave / L) * (kGcnBlock / kWave);
-    ProfScope p(name, st);
-    const RowSplit sp = split_rows(g, side, L, GPB);
-    const int32_t* ptr = side == 0 ? g->indptr : g->indptr_t;
-    const int32_t* cols = side == 0 ? g->indices : g->indices_t;
-    const unsigned grid = sp.hub_grid + sp.rest_grid;
-    const RowLaunch rl{sp.hub.end, g->n};
-    if (grid != 0) {
-      k_rowsum<L, NV, true><<<grid, kGcnBlock, 0, st>>>(rl, g->order[side], ptr, cols, feat, F, nullptr, out, wgt);
-      GNN_LAUNCH_CHECK();
-    }
-    return GNN_OK;
+    return launch_rowsum_sliced<true, L, NV>(g, side, name, feat, F, nullptr, out, st, wgt);
   }
 };
 

@@ -45,6 +45,22 @@ def test_shapes(fin, fout):
     check(synth(rng, indptr, indices, fin, fout))
 
 
+@pytest.mark.parametrize("fout", [64, 128, 256])
+@pytest.mark.parametrize("n", [31, 32, 33, 161, 400])
+def test_column_slices(n, fout):
+    """Slices of 32 columns on 8 / (fout / 32) XCDs each, 32 rows a workgroup: whole and partial workgroups, numbers of
+    them that do not divide by the XCDs of a slice, a shared row, rows of 0, 7, 8, 9, 16 and 17 edges."""
+    print(f"gcn: slices n={n} fout={fout}", flush=True)
+    rng = np.random.default_rng(n + fout)
+    edges = [(int(u), 1) for u in rng.integers(0, n, 300)]
+    edges += [(int(u), v) for v in range(2, n) for u in rng.integers(0, n, (0, 7, 8, 9, 16, 17)[v % 6])]
+    indptr, indices = tiny_graph(n, edges)
+    check(synth(rng, indptr, indices, 7, fout))
+    c = synth(rng, indptr, indices, 7, fout)
+    c["ew"] = rng.standard_normal(len(indices)).astype(np.float32)
+    check_edge(c)
+
+
 def test_empty_rows_hub_and_skipped_input_gradient():
     print("gcn: empty rows + hub", flush=True)
     rng = np.random.default_rng(8)
