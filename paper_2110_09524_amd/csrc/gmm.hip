@@ -19,6 +19,7 @@
 // half, the halves are walked apart: dhk as above, and gmu, gis per destination v from the same three
 // sums over its in-edges of hk[u,j,:] with the roles of the two coordinates exchanged.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "rowgroup.h"
@@ -293,15 +294,15 @@ __global__ __launch_bounds__(kGmmBlock) void k_gmm_fwd_eb(
 // When the input row is narrower than the K projected rows, an edge then gathers fin floats once
 // instead of K * fout, and the projection becomes one dense product on vertices,
 // out = agg [n, K*fin] . W' [K*fin, fout].
-template <int L>
+template <int L, int KB, int NS>
 __global__ __launch_bounds__(kGmmBlock) void k_gmm_fwd_x(
-    RowLaunch rl, const int32_t* __restrict__ order, const int32_t* __restrict__ indptr,
-    const int32_t* __restrict__ indices, const float* __restrict__ x, const float* __restrict__ c,
+    RowLaunch rl, const int4* __restrict__ rows, const int32_t* __restrict__ indices, const float* __restrict__ x, const float* __restrict__ c,
     const float* __restrict__ mu, const float* __restrict__ inv_sigma, int K, int fin,
     float* __restrict__ agg /* [n, K*fin] */) {
   constexpr int GPB = kGmmBlock / L;
-  constexpr int KB = kGmmKB, U = 4;
-  constexpr int GS = (1 + KB) * L;
+  constexpr int U = L == 8 ? 8 : 4;
+  constexpr int WS = KB == 2 ? 2 : 4;  // weights of an edge, read at once
+  constexpr int GS = (1 + WS) * L;
   __shared__ __align__(16) float lds[GPB * GS];
   __shared__ float coop_buf[GPB * L * 4 * KB];
   const int lane = threadIdx.x & 63;
@@ -310,14 +311,20 @@ __global__ __launch_bounds__(kGmmBlock) void k_gmm_fwd_x(
   int64_t r;
   int gi, ngrp;
   RowRange rr;
-  if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp)) return;
+  unsigned block;
+  const int col0 = xcd_slice<NS>(block) * 4 * L;
+  if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp, block)) return;
+  x += col0;
+  agg += col0;
   int* l_idx = reinterpret_cast<int*>(lds + grp * GS);
   float* l_w = lds + grp * GS + L;
   const float inv_k = 1.f / (float)K;
-  const int32_t v = order[r];
-  const int32_t beg = indptr[v], end = indptr[v + 1];
+  const int4 row = rows[r];
+  const int32_t v = row.x;
+  const uint32_t beg = row.y, end = row.z;  // unsigned: positions past 2^31 - 1 are past every row's end
   const float cv = c[v];
-  const bool col_ok = 4 * li < fin;
+  const bool col_ok = NS > 1 || 4 * li < fin;
+  auto source = [&](uint32_t e) { return e < end ? indices[e] : 0; };
   for (int k0 = 0; k0 < K; k0 += KB) {
     float mu0[KB], mu1[KB], is0[KB], is1[KB];
 #pragma unroll
@@ -336,31 +343,43 @@ __global__ __launch_bounds__(kGmmBlock) void k_gmm_fwd_x(
     }
     constexpr int kFold = L >= 32 ? 1 : 32 / L;  // two-level summation, as in k_gmm_fwd
     int chunk_no = 0;
-    for (int32_t c0 = beg + gi * L; c0 < end; c0 += ngrp * L) {
-      const bool e_ok = c0 + li < end;
-      const int32_t u = e_ok ? indices[c0 + li] : 0;
-      const float cu = c[u];
+    // the sources travel two chunks ahead, their scalars one
+    const uint32_t step = ngrp * L;
+    uint32_t c0 = beg + gi * L;
+    int32_t u = source(c0 + li), u1 = source(c0 + step + li);
+    float cu = c[u];
+    for (; c0 < end; c0 += step) {
       l_idx[li] = u;
 #pragma unroll
       for (int q = 0; q < KB; ++q)
-        l_w[q * L + li] = (e_ok && k0 + q < K) ? gauss_w(cu, cv, mu0[q], mu1[q], is0[q], is1[q]) * inv_k : 0.f;
+        l_w[WS * li + q] = (c0 + li < end && k0 + q < K) ? gauss_w(cu, cv, mu0[q], mu1[q], is0[q], is1[q]) * inv_k : 0.f;
       wave_lds_fence();
-      const int cnt = min(L, end - c0);
+      u = u1;
+      u1 = source(c0 + 2 * step + li);
+      cu = c[u];
+      const int cnt = min((uint32_t)L, end - c0);
       if (col_ok) {
         for (int t0 = 0; t0 < cnt; t0 += U) {
           float4 rowv[U];
 #pragma unroll
-          for (int t = 0; t < U; ++t) {
-            int uu = l_idx[min(t0 + t, L - 1)];  // past the chunk: a valid vertex with weight 0 or an unused slot
-            if (L == 64) uu = __builtin_amdgcn_readfirstlane(uu);
-            rowv[t] = ld4(x + (int64_t)uu * fin + 4 * li);
-          }
+          for (int t4 = 0; t4 < U; t4 += 4)
+            if (t0 + t4 < cnt) {  // past the row's end: a valid vertex with weight 0
+              const int4 i4 = *reinterpret_cast<const int4*>(l_idx + t0 + t4);
+              int uu[4] = {i4.x, i4.y, i4.z, i4.w};
 #pragma unroll
-          for (int t = 0; t < U; ++t) {
-            if (t0 + t < L) {
-#pragma unroll
-              for (int q = 0; q < KB; ++q) fma4(part[q], l_w[q * L + t0 + t], rowv[t]);
+              for (int t = 0; t < 4; ++t) {
+                if (L == 64) uu[t] = __builtin_amdgcn_readfirstlane(uu[t]);
+                rowv[t4 + t] = ld4(x + (int64_t)uu[t] * fin + 4 * li);
+              }
             }
+#pragma unroll
+          for (int t = 0; t < U; ++t) {
+            if (t0 + (t & ~3) >= cnt) continue;
+            float w[4];
+            if constexpr (WS == 4) pack4(w, *reinterpret_cast<const float4*>(l_w + 4 * (t0 + t)));
+            else *reinterpret_cast<float2*>(w) = *reinterpret_cast<const float2*>(l_w + 2 * (t0 + t));
+#pragma unroll
+            for (int q = 0; q < KB; ++q) fma4(part[q], w[q], rowv[t]);
           }
         }
       }
@@ -565,10 +584,9 @@ __global__ void k_gmm_param_split(int K, const float* __restrict__ totals, float
 // all, one gather per edge instead of two.  100 000 vertices, 2 10^6 edges, 64 columns, K = 3, us: destination side 131
 // and this kernel without MOMENTS 70 -> 98.  KB kernels per pass (2, 3 or 4, as many as K where that is one
 // pass); the vector units take 12 KB multiply-adds an edge and lane, the gathers past the L2s bound it.
-template <int L, int KB, bool MOMENTS>
+template <int L, int KB, bool MOMENTS, int NS>
 __global__ __launch_bounds__(kGmmBlock) void k_gmm_bwd_src(
-    RowLaunch rl, const int32_t* __restrict__ order_t, const int32_t* __restrict__ indptr_t,
-    const int32_t* __restrict__ indices_t, const float* __restrict__ c, const float* __restrict__ mu,
+    RowLaunch rl, const int4* __restrict__ rows_t, const int32_t* __restrict__ indices_t, const float* __restrict__ c, const float* __restrict__ mu,
     const float* __restrict__ inv_sigma, const float* __restrict__ gout, GmmParams pm, float* __restrict__ dhk,
     const float* __restrict__ hk, float* __restrict__ partial) {
   constexpr int GPB = kGmmBlock / L;
@@ -585,7 +603,9 @@ __global__ __launch_bounds__(kGmmBlock) void k_gmm_bwd_src(
   int64_t r;
   int gi, ngrp;
   RowRange rr;
-  const bool active = pick_row<GPB>(rl, grp, rr, r, gi, ngrp);
+  unsigned block;
+  const int col0 = xcd_slice<NS>(block) * 4 * L;
+  const bool active = pick_row<GPB>(rl, grp, rr, r, gi, ngrp, block);
   if (MOMENTS) {
     for (int i = li; i < kMaxK * 4; i += L) blk[grp][i >> 2][i & 3] = 0.f;
   } else if (!active) {
@@ -597,10 +617,15 @@ __global__ __launch_bounds__(kGmmBlock) void k_gmm_bwd_src(
     float* l_w = l_cv + L;
     const int K = pm.K, F = pm.F, KF = K * F;
     const float inv_k = 1.f / (float)K;
-    const int32_t u = order_t[r];
-    const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
+    const int4 row = rows_t[r];
+    const int32_t u = row.x;
+    const uint32_t beg = row.y, end = row.z;  // unsigned, as above
     const float cu = c[u];
-    const bool col_ok = 4 * li < F;
+    const bool col_ok = NS > 1 || 4 * li < F;
+    gout += col0;
+    dhk += col0;
+    if (MOMENTS) hk += col0;
+    auto target = [&](uint32_t e) { return e < end ? indices_t[e] : 0; };
     for (int k0 = 0; k0 < K; k0 += KB) {
       float mu0[KB], mu1[KB], is0[KB], is1[KB];
 #pragma unroll
@@ -618,21 +643,27 @@ __global__ __launch_bounds__(kGmmBlock) void k_gmm_bwd_src(
         acc[q] = zero;
         if (MOMENTS) aR[q] = aS[q] = zero;
       }
-      for (int32_t c0 = beg + gi * L; c0 < end; c0 += ngrp * L) {
+      // the targets travel two chunks ahead, their scalars one
+      const uint32_t step = ngrp * L;
+      uint32_t c0 = beg + gi * L;
+      int32_t v = target(c0 + li), v1 = target(c0 + step + li);
+      float cv = c[v];
+      for (; c0 < end; c0 += step) {
         // chunk phase: lane li owns out-edge c0 + li; edges past the end become vertex 0, weight 0
         const bool e_ok = c0 + li < end;
-        const int32_t v = e_ok ? indices_t[c0 + li] : 0;
-        const float cv = c[v];
         l_idx[li] = v;
         if (MOMENTS) l_cv[li] = cv;
 #pragma unroll
         for (int q = 0; q < KB; ++q)
           l_w[WS * li + q] = (e_ok && k0 + q < K) ? gauss_w(cu, cv, mu0[q], mu1[q], is0[q], is1[q]) * inv_k : 0.f;
         wave_lds_fence();
+        v = v1;
+        v1 = target(c0 + 2 * step + li);
+        cv = c[v];
         float4 part[KB];  // this chunk's share of A (two-level summation)
 #pragma unroll
         for (int q = 0; q < KB; ++q) part[q] = zero;
-        const int cnt = min(L, end - c0);
+        const int cnt = min((uint32_t)L, end - c0);
         for (int t0 = 0; t0 < cnt; t0 += U) {
           const int4 idx4 = *reinterpret_cast<const int4*>(l_idx + t0);
           int vv[U] = {idx4.x, idx4.y, idx4.z, idx4.w};
@@ -993,6 +1024,38 @@ __global__ __launch_bounds__(kGmmBlock) void k_gmm_bwd_dst_eb(
   }
 }
 
+// Column slices of the kernels below.  A slice evaluates every weight again, so they pay on smaller graphs than for plain sums:
+// forward and backward kernel, unsliced -> sliced, us: 2500 vertices, 10^4 edges, 64 columns, K = 3 11.4 and 15.4
+// -> 8.1 and 9.5; 30 000, 10^6, K = 4 (8 MB) 55 and 71 -> 44 and 67; 100 000, 2 10^6, K = 3 76 and 89 -> 77 and 111.
+constexpr int64_t kGmmSliceBytes = (int64_t)8 << 20;
+static int gmm_slices(const gnn_graph_t* g, int width) {
+  return (int64_t)sizeof(float) * width * g->n <= kGmmSliceBytes ? gather_slices(g, width) : 1;
+}
+// Calls fn with the kernels per pass over the edges (as many as K where that is one pass) and the column slices, which
+// only groups of 8 lanes have.
+template <int L, typename Fn>
+static gnn_status_t gmm_kernels_slices(const gnn_graph_t* g, int K, int width, Fn fn) {
+  auto slices = [&](auto kernels) -> gnn_status_t {
+    if constexpr (L == 8) {
+      if (width > 4 * L) {
+        switch (gmm_slices(g, width)) {
+          case 2: return fn(kernels, std::integral_constant<int, 2>{});
+          case 4: return fn(kernels, std::integral_constant<int, 4>{});
+          case 8: return fn(kernels, std::integral_constant<int, 8>{});
+        }
+      }
+    }
+    return fn(kernels, std::integral_constant<int, 1>{});
+  };
+  if (K <= 2) return slices(std::integral_constant<int, 2>{});
+  if (K == 3) return slices(std::integral_constant<int, 3>{});
+  return slices(std::integral_constant<int, 4>{});
+}
+// the group of such a kernel
+static GroupShape gmm_gather_group(const gnn_graph_t* g, int width) {
+  return pick_group(gmm_slices(g, width) > 1 ? kSliceCols : width);
+}
+
 template <int L, int NV>
 struct GmmFwdLauncher {
   static gnn_status_t run(const gnn_graph_t* g, const float* hk, const float* c, const float* mu,
@@ -1033,18 +1096,24 @@ struct GmmFwdEbLauncher {
 
 template <int L, int NV>
 struct GmmFwdXLauncher {
-  static gnn_status_t run(const gnn_graph_t* g, const float* x, const float* c, const float* mu,
-                          const float* is, int K, int fin, float* agg, hipStream_t st) {
-    constexpr int GPB = kGmmBlock / L;
-    ProfScope p("gmm_fwd_fused", st);
-    const RowSplit sp = split_rows(g, 0, L, GPB);
-    const unsigned grid = sp.hub_grid + sp.rest_grid;
+  template <int KB, int NS>
+  static gnn_status_t launch(const gnn_graph_t* g, const float* x, const float* c, const float* mu, const float* is, int K,
+                             int fin, float* agg, hipStream_t st) {
+    const RowSplit sp = split_rows(g, 0, L, kGmmBlock / L);
+    const unsigned grid = xcd_slice_grid(sp.hub_grid + sp.rest_grid, NS);
     const RowLaunch rl{sp.hub.end, g->n};
     if (grid != 0) {
-      k_gmm_fwd_x<L><<<grid, kGmmBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, x, c, mu, is, K, fin, agg);
+      k_gmm_fwd_x<L, KB, NS><<<grid, kGmmBlock, 0, st>>>(rl, g->rows[0], g->indices, x, c, mu, is, K, fin, agg);
       GNN_LAUNCH_CHECK();
     }
     return GNN_OK;
+  }
+  static gnn_status_t run(const gnn_graph_t* g, const float* x, const float* c, const float* mu,
+                          const float* is, int K, int fin, float* agg, hipStream_t st) {
+    ProfScope p("gmm_fwd_fused", st);
+    return gmm_kernels_slices<L>(g, K, fin, [&](auto kernels, auto slices) -> gnn_status_t {
+      return launch<decltype(kernels)::value, decltype(slices)::value>(g, x, c, mu, is, K, fin, agg, st);
+    });
   }
 };
 
@@ -1060,10 +1129,10 @@ static gnn_status_t gmm_param_sums(int K, unsigned grid, float* partial, float* 
 
 // number of workgroups (= partial slots) of the kernels that sum the gradients of mu and inv_sigma
 template <int L>
-static int64_t gmm_blocks(const gnn_graph_t* g, int side) {
+static int64_t gmm_blocks(const gnn_graph_t* g, int side, int slices) {
   constexpr int GPB = (kWave / L) * (kGmmBlock / kWave);
   const RowSplit sp = split_rows(g, side, L, GPB);
-  return (int64_t)sp.hub_grid + sp.rest_grid;
+  return xcd_slice_grid(sp.hub_grid + sp.rest_grid, slices);
 }
 
 template <int L, int NV>
@@ -1089,33 +1158,27 @@ struct GmmBwdDstLauncher {
 // hk == nullptr: dhk alone
 template <int L, int NV>
 struct GmmBwdSrcLauncher {
-  template <int KB, bool MOMENTS>
-  static gnn_status_t launch(const gnn_graph_t* g, const RowLaunch& rl, unsigned grid, const float* c, const float* mu,
-                             const float* is, const float* gout, GmmParams pm, float* dhk, const float* hk,
-                             float* partial, hipStream_t st) {
-    k_gmm_bwd_src<L, KB, MOMENTS><<<grid, kGmmBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, c, mu, is, gout,
-                                                              pm, dhk, hk, partial);
-    GNN_LAUNCH_CHECK();
-    return GNN_OK;
-  }
   static gnn_status_t run(const gnn_graph_t* g, const float* c, const float* mu, const float* is,
                           const float* gout, GmmParams pm, float* dhk, const float* hk, float* partial, float* gmu,
                           float* gis, hipStream_t st) {
-    constexpr int GPB = (kWave / L) * (kGmmBlock / kWave);
     ProfScope p(hk != nullptr ? "gmm_bwd" : "gmm_bwd_src", st);
-    const RowSplit sp = split_rows(g, 1, L, GPB);
+    const RowSplit sp = split_rows(g, 1, L, kGmmBlock / L);
     // hub rows (one workgroup each) and the rest in one launch
-    const unsigned grid = sp.hub_grid + sp.rest_grid;
     const RowLaunch rl{sp.hub.end, g->n};
-#define GNN_GMM_SRC(KB_)                                                                                     \
-  GNN_TRY(hk != nullptr ? (launch<KB_, true>(g, rl, grid, c, mu, is, gout, pm, dhk, hk, partial, st))        \
-                        : (launch<KB_, false>(g, rl, grid, c, mu, is, gout, pm, dhk, hk, partial, st)))
-    if (grid != 0) {
-      if (pm.K <= 2) GNN_GMM_SRC(2);
-      else if (pm.K == 3) GNN_GMM_SRC(3);
-      else GNN_GMM_SRC(4);
-    }
-#undef GNN_GMM_SRC
+    unsigned grid = 0;
+    GNN_TRY(gmm_kernels_slices<L>(g, pm.K, pm.F, [&](auto kernels, auto slices) -> gnn_status_t {
+      constexpr int KB = decltype(kernels)::value, NS = decltype(slices)::value;
+      grid = xcd_slice_grid(sp.hub_grid + sp.rest_grid, NS);
+      if (grid == 0) return GNN_OK;
+      if (hk != nullptr)
+        k_gmm_bwd_src<L, KB, true, NS><<<grid, kGmmBlock, 0, st>>>(rl, g->rows[1], g->indices_t, c, mu, is, gout, pm, dhk, hk,
+                                                                  partial);
+      else
+        k_gmm_bwd_src<L, KB, false, NS><<<grid, kGmmBlock, 0, st>>>(rl, g->rows[1], g->indices_t, c, mu, is, gout, pm, dhk,
+                                                                   hk, partial);
+      GNN_LAUNCH_CHECK();
+      return GNN_OK;
+    }));
     return hk != nullptr ? gmm_param_sums(pm.K, grid, partial, gmu, gis, st) : GNN_OK;
   }
 };
@@ -1205,13 +1268,13 @@ struct GmmWs {
   int64_t nblk;
 };
 
-static int64_t gmm_blocks_for(const gnn_graph_t* g, int side, int width) {
-  switch (pick_group(width).L) {
-    case 4: return gmm_blocks<4>(g, side);
-    case 8: return gmm_blocks<8>(g, side);
-    case 16: return gmm_blocks<16>(g, side);
-    case 32: return gmm_blocks<32>(g, side);
-    default: return gmm_blocks<64>(g, side);
+static int64_t gmm_blocks_for(const gnn_graph_t* g, int side, GroupShape gs, int slices) {
+  switch (gs.L) {
+    case 4: return gmm_blocks<4>(g, side, slices);
+    case 8: return gmm_blocks<8>(g, side, slices);
+    case 16: return gmm_blocks<16>(g, side, slices);
+    case 32: return gmm_blocks<32>(g, side, slices);
+    default: return gmm_blocks<64>(g, side, slices);
   }
 }
 
@@ -1221,7 +1284,8 @@ static GmmWs gmm_ws_layout(const gnn_graph_t* g, int fin, int fout, int K) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += ws_granule(bytes); return o; };
   const bool xg = gmm_aggregate_first(fin, fout, K);
-  w.nblk = std::max(gmm_blocks_for(g, 0, fout), gmm_blocks_for(g, 1, fout));
+  w.nblk = std::max(gmm_blocks_for(g, 0, pick_group(fout), 1),
+                    gmm_blocks_for(g, 1, gmm_gather_group(g, fout), gmm_slices(g, fout)));
   if (K <= kGmmKB) {  // the edge-balanced destination side: one slot per workgroup of runs
     const int64_t nb = cdiv(cdiv(g->nnz, kGmmEbEdges), kGmmBlock / pick_group(fout).L);
     if (nb > w.nblk) w.nblk = nb;
@@ -1282,7 +1346,7 @@ extern "C" gnn_status_t gnn_gmm_fwd(const gnn_graph_t* g, int fin, int fout, int
         k_gmm_wt<<<(unsigned)cdiv(cnt, 256), 256, 0, st>>>(fin, k, fout, w_fc, wt);
         GNN_LAUNCH_CHECK();
       }
-      GNN_TRY((gmm_dispatch<GmmFwdXLauncher>(pick_group(fin), g, x, c, mu, inv_sigma, k, fin, agg, st)));
+      GNN_TRY((gmm_dispatch<GmmFwdXLauncher>(gmm_gather_group(g, fin), g, x, c, mu, inv_sigma, k, fin, agg, st)));
       return gemm_f32(g->n, fout, (int64_t)k * fin, agg, (int64_t)k * fin, false, wt, fout, false, out, fout, 1,
                       nullptr, st);
     }
@@ -1389,7 +1453,7 @@ extern "C" gnn_status_t gnn_gmm_tune_bwd(gnn_graph_t* g, int fin, int fout, int 
     constexpr int kReps = 3;
     GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdDstLauncher>(gs, g, hk, c, mu, inv_sigma, gout, pm, partial, gmu, gis, st); }, &ms[0]));
     GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdDstEbLauncher>(gs, g, hk, c, mu, inv_sigma, gout, pm, partial, gmu, gis, st); }, &ms[1]));
-    GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdSrcLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, (const float*)nullptr, partial, gmu, gis, st); }, &ms[2]));
+    GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdSrcLauncher>(gmm_gather_group(g, fout), g, c, mu, inv_sigma, gout, pm, dhk, (const float*)nullptr, partial, gmu, gis, st); }, &ms[2]));
     GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdSrcEbLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, st); }, &ms[3]));
     g->gmm_bwd_edge_balanced[0] = ms[1] < ms[0] ? 1 : 0;
     g->gmm_bwd_edge_balanced[1] = ms[3] < ms[2] ? 1 : 0;
@@ -1444,7 +1508,7 @@ extern "C" gnn_status_t gnn_gmm_bwd(const gnn_graph_t* g, int fin, int fout, int
   if (eb_src)
     GNN_TRY(gmm_dispatch<GmmBwdSrcEbLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, st));
   else
-    GNN_TRY(gmm_dispatch<GmmBwdSrcLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, eb_dst ? no_hk : hk_use, partial, gmu,
+    GNN_TRY(gmm_dispatch<GmmBwdSrcLauncher>(gmm_gather_group(g, fout), g, c, mu, inv_sigma, gout, pm, dhk, eb_dst ? no_hk : hk_use, partial, gmu,
                                             ginv_sigma, st));
   GNN_TRY(gemm_f32(fin, KF, n, x, fin, true, dhk, KF, false, gw_fc, KF, L.split_k, part, st));
   if (gx) GNN_TRY(gemm_f32(n, fin, KF, dhk, KF, false, w_fc, KF, true, gx, fin, 1, nullptr, st));

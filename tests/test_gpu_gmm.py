@@ -61,6 +61,24 @@ def test_shapes(fin, fout, K):
     check(synth(rng, indptr, indices, fin, fout, K))
 
 
+@pytest.mark.parametrize("n", [31, 33, 161, 400])
+@pytest.mark.parametrize("fin,fout,K", [(64, 64, 3), (64, 64, 2), (128, 64, 4), (256, 128, 5), (7, 256, 1)])
+def test_column_slices(n, fin, fout, K):
+    """Both sides in slices of 32 columns: whole and partial workgroups of 32 rows, numbers of them that do not divide by
+    the XCDs of a slice, shared rows, rows around one and two chunks of 8 edges; the parameters' sums over the slices."""
+    print(f"gmm: slices n={n} {fin}->{fout} K={K}", flush=True)
+    rng = np.random.default_rng(n + fin + fout + K)
+    edges = [(int(u), 1) for u in rng.integers(0, n, 300)] + [(2, int(u)) for u in rng.integers(3, n, 300)]
+    edges += [(int(u), v) for v in range(2, n) for u in rng.integers(0, n, (0, 7, 8, 9, 16, 17)[v % 6])]
+    indptr, indices = tiny_graph(n, edges)
+    c = synth(rng, indptr, indices, fin, fout, K)
+    # gmu and ginv_sigma sum up 5000 edges' products of fout terms, 0.3 sqrt(fin) each: 5400 in root mean square at the
+    # widest, of which 2^-24 passes the literal bound where they cancel; scaled down it is 2^-24 * 54 = 3e-6
+    c["w_fc"] *= np.float32(0.1)
+    c["gout"] *= np.float32(0.1)
+    check(c)
+
+
 @pytest.mark.parametrize("fin,fout,K", [(64, 64, 3), (16, 16, 2), (8, 256, 4), (100, 64, 8), (4, 4, 2), (252, 100, 3)])
 def test_aggregate_first_and_project_first_agree_with_the_oracle(fin, fout, K):
     """Input rows narrower than the K projected rows: the forward call aggregates x per kernel and
