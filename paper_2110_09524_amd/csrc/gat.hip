@@ -65,7 +65,8 @@ struct GroupLds {
 // destination-side sums of the backward pass.  They ride on the same gathered rows, and
 // they are O(|V|) vertex state, which is cheaper to stash than to recompute (Sec. 6:
 // recompute only when computation / memory is O(1); here it is |E|/|V|).
-template <int L, int NV, bool WT, int ES>
+// NS column slices of 4 L columns, whole heads each (xcd_slice, gat_sliced): dm.log2Hp is for the heads of one slice.
+template <int L, int NV, bool WT, int ES, int NS>
 __global__ __launch_bounds__(kBlock) void k_gat_fwd(
     RowLaunch rl, const int4* __restrict__ rows, const int32_t* __restrict__ indices, const float* __restrict__ z,
     const float* __restrict__ el, const float* __restrict__ er, GatDims dm, float* __restrict__ out, float* __restrict__ m_out,
@@ -92,19 +93,33 @@ __global__ __launch_bounds__(kBlock) void k_gat_fwd(
   int64_t r;
   int gi, ngrp;
   RowRange rr;
-  if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp)) return;  // whole group (coop: whole workgroup) leaves together
+  unsigned block;
+  const int slice = xcd_slice<NS>(block);
+  if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp, block)) return;  // whole group (coop: whole workgroup) leaves together
   float* g_lds = lds + grp * GroupLds<GL, NV>::kFloats;
   int* l_idx = reinterpret_cast<int*>(g_lds);
   float* l_p = g_lds + GL;
   float* l_p2 = g_lds + 2 * GL;
   float* l_sc = g_lds + 3 * GL;
 
-  const int H = dm.H, HF = dm.HF;
+  const int H = dm.H, HF = dm.HF, heads = H / NS;
   const int Hp = 1 << dm.log2Hp;
+  if (NS > 1) {
+    z += slice * 4 * L;
+    out += slice * 4 * L;
+    el += slice * heads;
+    er += slice * heads;
+    m_out += slice * heads;
+    d_out += slice * heads;
+    if (WT) {
+      t_out += slice * 4 * L;
+      sg_out += slice * heads;
+    }
+  }
   const int epc = GL >> dm.log2Hp;  // edges per chunk
   const int e_loc = li >> dm.log2Hp;
   const int h = li & (Hp - 1);
-  const bool head_ok = h < H;
+  const bool head_ok = h < heads;
 
   const int4 ri = rows[r];
   const int32_t v = ri.x, beg = ri.y, end = ri.z;
@@ -116,7 +131,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_fwd(
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     int col = 4 * (cl + j * L);
-    slot_ok[j] = col < HF;
+    slot_ok[j] = NS > 1 || col < HF;
     hs[j] = slot_ok[j] ? col / dm.F : 0;
     acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     acc2[j] = acc[j];
@@ -443,7 +458,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_bwd_dst(
 
 // ---- a5: backward, source side (CSC walk, no atomics) ------------------------------
 // dz[u] = sum_out alpha_e gout[v] + a_l del[u] + a_r der[u];  writes del[u,h] too
-template <int L, int NV, int ES>
+template <int L, int NV, int ES, int NS>
 __global__ __launch_bounds__(kBlock) void k_gat_bwd_src(
     RowLaunch rl, const int4* __restrict__ rows_t, const int32_t* __restrict__ indices_t, const float* __restrict__ z,
     const float* __restrict__ el, const float4* __restrict__ vstate, const float* __restrict__ der, const float* __restrict__ gout,
@@ -467,7 +482,9 @@ __global__ __launch_bounds__(kBlock) void k_gat_bwd_src(
   int64_t r;
   int gi, ngrp;
   RowRange rr;
-  if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp)) return;
+  unsigned block;
+  const int slice = xcd_slice<NS>(block);
+  if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp, block)) return;
   float* g_lds = lds + grp * GroupLds<GL, NV>::kFloats;
   int* l_idx = reinterpret_cast<int*>(g_lds);
   float* l_p = g_lds + GL;
@@ -475,12 +492,24 @@ __global__ __launch_bounds__(kBlock) void k_gat_bwd_src(
   float* l_sc = g_lds + 3 * GL;
   float* l_red = g_lds + 4 * GL;
 
-  const int H = dm.H, HF = dm.HF;
+  const int H = dm.H, HF = dm.HF, heads = H / NS;
   const int Hp = 1 << dm.log2Hp;
+  if (NS > 1) {
+    z += slice * 4 * L;
+    gout += slice * 4 * L;
+    a_l += slice * 4 * L;
+    a_r += slice * 4 * L;
+    dz += slice * 4 * L;
+    el += slice * heads;
+    vstate += slice * heads;
+    der += slice * heads;
+    del += slice * heads;
+    if (alpha_t) alpha_t += slice * heads;
+  }
   const int epc = GL >> dm.log2Hp;
   const int e_loc = li >> dm.log2Hp;
   const int h = li & (Hp - 1);
-  const bool head_ok = h < H;
+  const bool head_ok = h < heads;
 
   const int4 ri = rows_t[r];
   const int32_t u = ri.x, beg = ri.y, end = ri.z;
@@ -492,7 +521,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_bwd_src(
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     int col = 4 * (cl + j * L);
-    slot_ok[j] = col < HF;
+    slot_ok[j] = NS > 1 || col < HF;
     hs[j] = slot_ok[j] ? col / dm.F : 0;
     acc1[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     acc2[j] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -766,9 +795,32 @@ static int pick_replicas(const GatDims& dm) {
   return es;
 }
 
+// Column slices of k_gat_fwd and k_gat_bwd_src (slices_pay): four heads of 64 columns, a head to a slice.  Layer, unsliced ->
+// sliced, us: 1500 vertices, 6000 edges 81 -> 72; 5000, 10^5 102 -> 85; 60 000, 1.2 10^6 488 -> 465; 100 000, 5 10^5 501 -> 523.
+// Narrower heads, several to a slice, and two heads of 64 gain nothing (100 000 vertices, 2 10^6 edges, 8 x 8 302 -> 313, 2 x
+// 64 414 -> 414; 30 000, 10^6, 4 x 32 172 -> 197).
+constexpr int kGatSlices = 4;
+static bool gat_sliced(const gnn_graph_t* g, const GatDims& dm) {
+  return dm.H == kGatSlices && dm.F == 64 && slices_pay(g, dm.HF);
+}
+static GroupShape gat_gather_group(const gnn_graph_t* g, const GatDims& dm) {
+  return pick_group(gat_sliced(g, dm) ? dm.F : dm.HF);
+}
+// calls fn with the slices and the dimensions of one
+template <int L, int NV, typename Fn>
+static gnn_status_t with_slices(const gnn_graph_t* g, GatDims dm, Fn fn) {
+  if constexpr (L == 16 && NV == 1) {
+    if (gat_sliced(g, dm)) {
+      dm.log2Hp = 0;
+      return fn(dm, std::integral_constant<int, kGatSlices>{});
+    }
+  }
+  return fn(dm, std::integral_constant<int, 1>{});
+}
+
 template <int L, int NV>
 struct FwdLauncher {
-  template <int ES>
+  template <int ES, int NS>
   static gnn_status_t launch(const gnn_graph_t* g, const float* z, const float* el, const float* er,
                              GatDims dm, float* out, float* m, float* d, float* t, float* sg,
                              hipStream_t st) {
@@ -777,13 +829,13 @@ struct FwdLauncher {
       constexpr int GPB = (kWave / GL) * (kBlock / kWave);
       const RowSplit sp = split_rows(g, 0, GL >> dm.log2Hp, GPB);
       // hub rows (one workgroup each) and the rest in one launch
-      const unsigned grid = sp.hub_grid + sp.rest_grid;
+      const unsigned grid = xcd_slice_grid(sp.hub_grid + sp.rest_grid, NS);
       const RowLaunch rl{sp.hub.end, g->n};
       if (grid != 0) {
         if (t)
-          k_gat_fwd<L, NV, true, ES><<<grid, kBlock, 0, st>>>(rl, g->rows[0], g->indices, z, el, er, dm, out, m, d, t, sg);
+          k_gat_fwd<L, NV, true, ES, NS><<<grid, kBlock, 0, st>>>(rl, g->rows[0], g->indices, z, el, er, dm, out, m, d, t, sg);
         else
-          k_gat_fwd<L, NV, false, ES><<<grid, kBlock, 0, st>>>(rl, g->rows[0], g->indices, z, el, er, dm, out, m, d, nullptr, nullptr);
+          k_gat_fwd<L, NV, false, ES, NS><<<grid, kBlock, 0, st>>>(rl, g->rows[0], g->indices, z, el, er, dm, out, m, d, nullptr, nullptr);
         GNN_LAUNCH_CHECK();
       }
     }
@@ -793,11 +845,14 @@ struct FwdLauncher {
                           GatDims dm, float* out, float* m, float* d, float* t, float* sg,
                           hipStream_t st) {
     ProfScope p("gat_fwd_fused", st);
-    switch (pick_replicas<L, NV>(dm)) {
-      case 4: return launch<4>(g, z, el, er, dm, out, m, d, t, sg, st);
-      case 2: return launch<2>(g, z, el, er, dm, out, m, d, t, sg, st);
-      default: return launch<1>(g, z, el, er, dm, out, m, d, t, sg, st);
-    }
+    return with_slices<L, NV>(g, dm, [&](const GatDims& ds, auto slices) -> gnn_status_t {
+      constexpr int NS = decltype(slices)::value;
+      switch (pick_replicas<L, NV>(ds)) {
+        case 4: return launch<4, NS>(g, z, el, er, ds, out, m, d, t, sg, st);
+        case 2: return launch<2, NS>(g, z, el, er, ds, out, m, d, t, sg, st);
+        default: return launch<1, NS>(g, z, el, er, ds, out, m, d, t, sg, st);
+      }
+    });
   }
 };
 
@@ -949,7 +1004,7 @@ struct BwdDstLauncher {
 
 template <int L, int NV>
 struct BwdSrcLauncher {
-  template <int ES>
+  template <int ES, int NS>
   static gnn_status_t launch(const gnn_graph_t* g, const float* z, const float* el, const float4* vstate,
                              const float* der, const float* gout, const float* a_l, const float* a_r,
                              GatDims dm, float* dz, float* del, const float* alpha_t, hipStream_t st) {
@@ -958,10 +1013,10 @@ struct BwdSrcLauncher {
       constexpr int GPB = (kWave / GL) * (kBlock / kWave);
       const RowSplit sp = split_rows(g, 1, GL >> dm.log2Hp, GPB);
       // hub rows (one workgroup each) and the rest in one launch
-      const unsigned grid = sp.hub_grid + sp.rest_grid;
+      const unsigned grid = xcd_slice_grid(sp.hub_grid + sp.rest_grid, NS);
       const RowLaunch rl{sp.hub.end, g->n};
       if (grid != 0) {
-        k_gat_bwd_src<L, NV, ES><<<grid, kBlock, 0, st>>>(rl, g->rows[1], g->indices_t, z, el, vstate, der, gout, a_l, a_r, dm, dz, del, alpha_t);
+        k_gat_bwd_src<L, NV, ES, NS><<<grid, kBlock, 0, st>>>(rl, g->rows[1], g->indices_t, z, el, vstate, der, gout, a_l, a_r, dm, dz, del, alpha_t);
         GNN_LAUNCH_CHECK();
       }
     }
@@ -971,11 +1026,14 @@ struct BwdSrcLauncher {
                           const float* der, const float* gout, const float* a_l, const float* a_r,
                           GatDims dm, float* dz, float* del, const float* alpha_t, hipStream_t st) {
     ProfScope p("gat_bwd_src", st);
-    switch (pick_replicas<L, NV>(dm)) {
-      case 4: return launch<4>(g, z, el, vstate, der, gout, a_l, a_r, dm, dz, del, alpha_t, st);
-      case 2: return launch<2>(g, z, el, vstate, der, gout, a_l, a_r, dm, dz, del, alpha_t, st);
-      default: return launch<1>(g, z, el, vstate, der, gout, a_l, a_r, dm, dz, del, alpha_t, st);
-    }
+    return with_slices<L, NV>(g, dm, [&](const GatDims& ds, auto slices) -> gnn_status_t {
+      constexpr int NS = decltype(slices)::value;
+      switch (pick_replicas<L, NV>(ds)) {
+        case 4: return launch<4, NS>(g, z, el, vstate, der, gout, a_l, a_r, ds, dz, del, alpha_t, st);
+        case 2: return launch<2, NS>(g, z, el, vstate, der, gout, a_l, a_r, ds, dz, del, alpha_t, st);
+        default: return launch<1, NS>(g, z, el, vstate, der, gout, a_l, a_r, ds, dz, del, alpha_t, st);
+      }
+    });
   }
 };
 
@@ -1083,8 +1141,9 @@ extern "C" gnn_status_t gnn_gat_fwd(const gnn_graph_t* g, int fin, int heads, in
                            reinterpret_cast<float4*>(base + L.dz),
                            gat_blocked_half(g, heads, f) ? base + L.blk_half : nullptr, st);
   }
-  return dispatch_group<FwdLauncher>(pick_group(HF), g, (const float*)z, (const float*)el,
-                                     (const float*)er, make_dims(heads, f, slope), out, m, d, t, sg, st);
+  const GatDims dm = make_dims(heads, f, slope);
+  return dispatch_group<FwdLauncher>(gat_gather_group(g, dm), g, (const float*)z, (const float*)el,
+                                     (const float*)er, dm, out, m, d, t, sg, st);
 }
 
 extern "C" gnn_status_t gnn_gat_bwd(const gnn_graph_t* g, int fin, int heads, int f, float slope,
@@ -1242,7 +1301,7 @@ static gnn_status_t gat_bwd_impl(const char* who, const gnn_graph_t* g, int fin,
                                 gat_blocked_half(g, heads, f) ? base + L.blk_half : nullptr, st, alpha_t));
   } else {
     // a5: source side
-    GNN_TRY(dispatch_group<BwdSrcLauncher>(gs, g, z, el, (const float4*)vstate, (const float*)der,
+    GNN_TRY(dispatch_group<BwdSrcLauncher>(gat_gather_group(g, dm), g, z, el, (const float4*)vstate, (const float*)der,
                                            gout, a_l, a_r, dm, dz, del, alpha_t, st));
   }
   // a6: parameter gradients

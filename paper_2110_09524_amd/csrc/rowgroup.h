@@ -278,10 +278,12 @@ inline int ilog2(int p) {
 constexpr int kSliceCols = 32;
 constexpr int64_t kSliceMinDegree = 16;             // on average, of graphs past
 constexpr int64_t kSliceBytes = (int64_t)32 << 20;  // the eight L2s
+inline bool slices_pay(const gnn_graph* g, int F) {
+  return g->nnz >= kSliceMinDegree * g->n || (int64_t)sizeof(float) * F * g->n <= kSliceBytes;
+}
 inline int gather_slices(const gnn_graph* g, int F) {
-  if (F != 2 * kSliceCols && F != 4 * kSliceCols && F != 8 * kSliceCols) return 1;
-  const bool pays = g->nnz >= kSliceMinDegree * g->n || (int64_t)sizeof(float) * F * g->n <= kSliceBytes;
-  return pays ? F / kSliceCols : 1;
+  const bool fits = F == 2 * kSliceCols || F == 4 * kSliceCols || F == 8 * kSliceCols;
+  return fits && slices_pay(g, F) ? F / kSliceCols : 1;
 }
 
 // Split of one side's degree order into a cooperative prefix (rows at least

@@ -90,6 +90,25 @@ def test_shapes_heads_and_widths(fin, H, F):
     compare(c, run_gat(c), fwd, bwd)
 
 
+@pytest.mark.parametrize("n", [31, 33, 161, 400])
+def test_column_slices(n):
+    """Four heads of 64 columns, a head to two XCDs: whole and partial workgroups of 16 rows, numbers of them that do not
+    divide by the XCDs of a slice, shared rows, rows around one chunk of 16 edges and without any; each way to keep or
+    recompute the forward pass."""
+    from gpu_harness import run_gat
+    print(f"gat: slices n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    edges = [(int(u), 1) for u in rng.integers(0, n, 300)] + [(2, int(u)) for u in rng.integers(3, n, 300)]
+    edges += [(int(u), v) for v in range(2, n) for u in rng.integers(0, n, (0, 1, 15, 16, 17, 33)[v % 6])]
+    indptr, indices = tiny_graph(n, edges)
+    c = synth(rng, indptr, indices, 11, 4, 64)
+    fwd, bwd = oracle_all(c)
+    for stash, alpha in ((True, False), (False, False), (True, True)):
+        res = run_gat(c, stash=stash, alpha_stash=alpha)
+        res.pop("alpha_t", None)
+        compare(c, res, fwd, bwd)
+
+
 def test_empty_rows_isolated_vertices_and_hub():
     from gpu_harness import run_gat
     print("gat: empty rows + hub", flush=True)
