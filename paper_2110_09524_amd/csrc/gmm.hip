@@ -1132,7 +1132,9 @@ template <int L>
 static int64_t gmm_blocks(const gnn_graph_t* g, int side, int slices) {
   constexpr int GPB = (kWave / L) * (kGmmBlock / kWave);
   const RowSplit sp = split_rows(g, side, L, GPB);
-  return xcd_slice_grid(sp.hub_grid + sp.rest_grid, slices);
+  // slices share rows of 32 edges already, up to kCoopCheapRows of them whatever the edges
+  if (slices > 1) return xcd_slice_grid(std::max(sp.hub_grid, (unsigned)std::min(g->n, kCoopCheapRows)) + (unsigned)cdiv(g->n, GPB), slices);
+  return (int64_t)sp.hub_grid + sp.rest_grid;
 }
 
 template <int L, int NV>
@@ -1162,12 +1164,12 @@ struct GmmBwdSrcLauncher {
                           const float* gout, GmmParams pm, float* dhk, const float* hk, float* partial, float* gmu,
                           float* gis, hipStream_t st) {
     ProfScope p(hk != nullptr ? "gmm_bwd" : "gmm_bwd_src", st);
-    const RowSplit sp = split_rows(g, 1, L, kGmmBlock / L);
-    // hub rows (one workgroup each) and the rest in one launch
-    const RowLaunch rl{sp.hub.end, g->n};
     unsigned grid = 0;
     GNN_TRY(gmm_kernels_slices<L>(g, pm.K, pm.F, [&](auto kernels, auto slices) -> gnn_status_t {
       constexpr int KB = decltype(kernels)::value, NS = decltype(slices)::value;
+      // hub rows (one workgroup each) and the rest in one launch
+      const RowSplit sp = split_rows(g, 1, L, kGmmBlock / L);
+      const RowLaunch rl{sp.hub.end, g->n};
       grid = xcd_slice_grid(sp.hub_grid + sp.rest_grid, NS);
       if (grid == 0) return GNN_OK;
       if (hk != nullptr)
