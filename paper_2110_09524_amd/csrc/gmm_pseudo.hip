@@ -329,14 +329,13 @@ __device__ __forceinline__ void read8f(const float* p, float (&v)[kNrU]) {
 }
 
 // forward: out[v, f] = (1/K) sum_e sum_k w_k(e) hk[u, k, f]; the sum over k is taken last, across lanes
-template <int G, bool PROJ>
+template <int G, bool PROJ, int KT, int RT>
 __global__ __launch_bounds__(kPsBlock) void k_gmmp_fwd_nr(
-    RowLaunch rl, const int32_t* __restrict__ order, const int32_t* __restrict__ indptr,
-    const int32_t* __restrict__ indices, const float* __restrict__ hk, const float* __restrict__ pseudo,
+    RowLaunch rl, const int4* __restrict__ rows, const int32_t* __restrict__ indices, const float* __restrict__ hk, const float* __restrict__ pseudo,
     ProjArgs pa, const float* __restrict__ mu, const float* __restrict__ inv_sigma, PsParams pm,
     float* __restrict__ out) {
   constexpr int GPB = kPsBlock / G;
-  constexpr int GS = kNrGroupFloats<G>;
+  constexpr int GS = G + KT * G;  // indices | weights [KT][G]
   __shared__ __align__(16) float lds[GPB * GS];
   __shared__ float coop_buf[GPB * G * 4];
   const int lane = threadIdx.x & 63;
@@ -348,50 +347,64 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_fwd_nr(
   if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp)) return;
   const int K = pm.K, R = pm.R, F = pm.F, KF = K * F, F4 = F / 4;
   const float inv_k = 1.f / (float)K;
-  const PsKernels<> pk = load_kernels(mu, inv_sigma, K, R);
-  const int32_t v = order[r];
-  const int32_t beg = indptr[v], end = indptr[v + 1];
-  ProjRegs<kPsR> pq;
+  const PsKernels<KT, RT> pk = load_kernels<KT, RT>(mu, inv_sigma, K, R);
+  const int4 row = rows[r];
+  const int32_t v = row.x;
+  const uint32_t beg = row.y, end = row.z;  // unsigned: positions past 2^31 - 1 are past every row's end
+  ProjRegs<RT> pq;
   float cv = 0.f;
   if (PROJ) {
-    pq = load_proj<kPsR>(pa, R);
+    pq = load_proj<RT>(pa, R);
     cv = pa.c[v];
   }
   const bool col_ok = li < K * F4;
   const int myk = col_ok ? li / F4 : 0;
   int* l_idx = reinterpret_cast<int*>(lds + grp * GS);
-  float* l_w = lds + grp * GS + G;  // [kPsK][G]
+  float* l_w = lds + grp * GS + G;
   const float* my_row = hk + 4 * li;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), part = acc;
   int folded = 0;
-  for (int32_t e0 = beg + gi * G; e0 < end; e0 += ngrp * G) {
+  // The sources travel two chunks ahead, their scalars one; the rows of a chunk are asked for before its weights are made.
+  const uint32_t step = ngrp * G;
+  auto source = [&](uint32_t e) { return e < end ? indices[e] : 0; };
+  uint32_t e0 = beg + gi * G;
+  int32_t u = source(e0 + li), u1 = source(e0 + step + li);
+  float cu = PROJ ? pa.c[u] : 0.f;
+  for (; e0 < end; e0 += step) {
     const bool e_ok = e0 + li < end;
-    const int cnt = min(G, end - e0);
-    int32_t u = 0;
-    float m[kPsR];
-#pragma unroll
-    for (int d = 0; d < kPsR; ++d) m[d] = 0.f;
-    if (e_ok) {
-      u = indices[e0 + li];
-      if (PROJ) project(pq, R, pa.c[u], cv, m);
-      else load_pseudo(pseudo, e0 + li, R, m);
-    }
+    const int cnt = min((uint32_t)G, end - e0);
     wave_lds_fence();  // the previous chunk's reads are done
     l_idx[li] = u;
+    wave_lds_fence();
+    float m[RT];
+    if (!PROJ) {
 #pragma unroll
-    for (int k = 0; k < kPsK; ++k)
+      for (int d = 0; d < RT; ++d) m[d] = 0.f;
+      if (e_ok) load_pseudo(pseudo, e0 + li, R, m);
+    }
+    const float c_here = cu;
+    u = u1;
+    u1 = source(e0 + 2 * step + li);
+    if (PROJ) cu = pa.c[u];
+    float4 rowv[kNrU];
+    auto fetch = [&](int t0) {
+      int idv[kNrU];
+      read8i(l_idx + t0, idv);
+#pragma unroll
+      for (int t = 0; t < kNrU; ++t)
+        if (col_ok && t0 + t < cnt) rowv[t] = ld4(my_row + (int64_t)idv[t] * KF);
+    };
+    fetch(0);
+    if (PROJ) project(pq, R, c_here, cv, m);
+#pragma unroll
+    for (int k = 0; k < KT; ++k)
       if (k < K) l_w[k * G + li] = e_ok ? gauss_k(pk, k, m) * inv_k : 0.f;
     wave_lds_fence();
 #pragma unroll
     for (int t0 = 0; t0 < G; t0 += kNrU) {
       if (t0 < cnt) {
-        int idv[kNrU];
+        if (t0 > 0) fetch(t0);
         float wv[kNrU];
-        read8i(l_idx + t0, idv);
-        float4 rowv[kNrU];
-#pragma unroll
-        for (int t = 0; t < kNrU; ++t)
-          if (col_ok && t0 + t < cnt) rowv[t] = ld4(my_row + (int64_t)idv[t] * KF);
         read8f(l_w + myk * G + t0, wv);
 #pragma unroll
         for (int t = 0; t < kNrU; ++t)
@@ -426,141 +439,18 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_fwd_nr(
   if (li < F4) st4(out + (int64_t)v * F + 4 * li, tot);
 }
 
-// destination side of backward: the row phase leaves every lane's part of <gout[v], hk[u, k, :]> in
-// LDS, and the lane that owns the edge adds the F/4 parts of each kernel in lane order
+// destination side of backward, the coordinates' gradient alone (the walk below has the rest): the row phase leaves every
+// lane's part of <gout[v], hk[u, k, :]> in LDS, and the lane that owns the edge adds the F/4 parts of each kernel in
+// lane order
 template <int G>
 __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_dst_nr(
     RowLaunch rl, const int32_t* __restrict__ order, const int32_t* __restrict__ indptr,
     const int32_t* __restrict__ indices, const float* __restrict__ hk, const float* __restrict__ pseudo,
     const float* __restrict__ mu, const float* __restrict__ inv_sigma,
-    const float* __restrict__ gout, PsParams pm, float* __restrict__ partial,
-    float* __restrict__ gpseudo /* nullable */) {
+    const float* __restrict__ gout, PsParams pm, float* __restrict__ gpseudo) {
   constexpr int GPB = kPsBlock / G;
   constexpr int GS = kNrGroupFloats<G>;
   __shared__ __align__(16) float lds[GPB * GS];
-  __shared__ float blk[GPB][kPsVals];
-  const int li = threadIdx.x & (G - 1);
-  const int grp = threadIdx.x / G;
-  int64_t r;
-  int gi, ngrp;
-  RowRange rr;
-  const bool active = pick_row<GPB>(rl, grp, rr, r, gi, ngrp);
-  const int K = pm.K, R = pm.R, F = pm.F, KF = K * F, F4 = F / 4;
-  const float inv_k = 1.f / (float)K;
-  float gm_acc[kPsK][kPsR], gs_acc[kPsK][kPsR];  // sums over the edges this lane owned
-#pragma unroll
-  for (int k = 0; k < kPsK; ++k)
-#pragma unroll
-    for (int d = 0; d < kPsR; ++d) {
-      gm_acc[k][d] = 0.f;
-      gs_acc[k][d] = 0.f;
-    }
-  if (active) {
-    const PsKernels<> pk = load_kernels(mu, inv_sigma, K, R);
-    const int32_t v = order[r];
-    const int32_t beg = indptr[v], end = indptr[v + 1];
-    const bool col_ok = li < K * F4;
-    const int f4 = col_ok ? li % F4 : 0;
-    const float4 g4 = col_ok ? ld4(gout + (int64_t)v * F + 4 * f4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    int* l_idx = reinterpret_cast<int*>(lds + grp * GS);
-    float* l_d = lds + grp * GS + G;  // [column lane][edge of the chunk]
-    const float* my_row = hk + 4 * li;
-    for (int32_t e0 = beg + gi * G; e0 < end; e0 += ngrp * G) {
-      const bool e_ok = e0 + li < end;
-      const int cnt = min(G, end - e0);
-      int32_t u = 0;
-      float m[kPsR];
-#pragma unroll
-      for (int d = 0; d < kPsR; ++d) m[d] = 0.f;
-      if (e_ok) {
-        u = indices[e0 + li];
-        load_pseudo(pseudo, e0 + li, R, m);
-      }
-      wave_lds_fence();
-      l_idx[li] = u;
-      wave_lds_fence();
-#pragma unroll
-      for (int t0 = 0; t0 < G; t0 += kNrU) {
-        if (t0 < cnt) {
-          int idv[kNrU];
-          read8i(l_idx + t0, idv);
-          float4 rowv[kNrU];
-#pragma unroll
-          for (int t = 0; t < kNrU; ++t)
-            if (col_ok && t0 + t < cnt) rowv[t] = ld4(my_row + (int64_t)idv[t] * KF);
-          float dv[kNrU];
-#pragma unroll
-          for (int t = 0; t < kNrU; ++t) dv[t] = (col_ok && t0 + t < cnt) ? dot4(g4, rowv[t]) : 0.f;
-          *reinterpret_cast<float4*>(l_d + li * G + t0) = make_float4(dv[0], dv[1], dv[2], dv[3]);
-          *reinterpret_cast<float4*>(l_d + li * G + t0 + 4) = make_float4(dv[4], dv[5], dv[6], dv[7]);
-        }
-      }
-      wave_lds_fence();
-      if (e_ok) {
-        float gm[kPsR];
-#pragma unroll
-        for (int d = 0; d < kPsR; ++d) gm[d] = 0.f;
-#pragma unroll
-        for (int k = 0; k < kPsK; ++k) {
-          if (k >= K) continue;
-          float dot = 0.f;
-          for (int j = 0; j < F4; ++j) dot += l_d[(k * F4 + j) * G + li];
-          const float dlog = dot * inv_k * gauss_k(pk, k, m);  // dw_k(e) w_k(e)
-#pragma unroll
-          for (int d = 0; d < kPsR; ++d) {
-            const float diff = m[d] - pk.mu[k][d];
-            const float is = pk.is[k][d];
-            const float t = dlog * diff * is;  // padded dimensions: is = 0
-            gm_acc[k][d] = fmaf(t, is, gm_acc[k][d]);
-            gs_acc[k][d] = fmaf(-t, diff, gs_acc[k][d]);
-            gm[d] = fmaf(-t, is, gm[d]);
-          }
-        }
-        if (gpseudo != nullptr) {
-#pragma unroll
-          for (int d = 0; d < kPsR; ++d)
-            if (d < R) gpseudo[(int64_t)(e0 + li) * R + d] = gm[d];
-        }
-      }
-    }
-  }
-  // the group's lanes are added in a fixed (butterfly) order, then the groups in order
-#pragma unroll
-  for (int k = 0; k < kPsK; ++k)
-#pragma unroll
-    for (int d = 0; d < kPsR; ++d) {
-      if (k < K && d < R) {
-        const float a = group_sum_from<G>(gm_acc[k][d], 1), b = group_sum_from<G>(gs_acc[k][d], 1);
-        if (li == 0) {
-          blk[grp][k * kPsR + d] = a;
-          blk[grp][kPsK * kPsR + k * kPsR + d] = b;
-        }
-      } else if (li == 0) {
-        blk[grp][k * kPsR + d] = 0.f;
-        blk[grp][kPsK * kPsR + k * kPsR + d] = 0.f;
-      }
-    }
-  __syncthreads();
-  if (threadIdx.x < kPsVals) {
-    float s = 0.f;
-    for (int g2 = 0; g2 < GPB; ++g2) s += blk[g2][threadIdx.x];
-    partial[(int64_t)blockIdx.x * kPsVals + threadIdx.x] = s;
-  }
-}
-
-// source side of backward: dhk[u, k, f] = (1/K) sum over out-edges w_k(e) gout[v, f]; the lanes of the K
-// kernels read the same columns of gout[v]
-template <int G>
-__global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_src_nr(
-    RowLaunch rl, const int32_t* __restrict__ order_t, const int32_t* __restrict__ indptr_t,
-    const int32_t* __restrict__ indices_t, const int32_t* __restrict__ eid_t,
-    const float* __restrict__ pseudo, const float* __restrict__ pseudo_t /* nullable: pseudo in this walk's order */,
-    const float* __restrict__ mu, const float* __restrict__ inv_sigma,
-    const float* __restrict__ gout, PsParams pm, float* __restrict__ dhk) {
-  constexpr int GPB = kPsBlock / G;
-  constexpr int GS = kNrGroupFloats<G>;
-  __shared__ __align__(16) float lds[GPB * GS];
-  __shared__ float coop_buf[GPB * G * 4];
   const int li = threadIdx.x & (G - 1);
   const int grp = threadIdx.x / G;
   int64_t r;
@@ -570,66 +460,68 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_src_nr(
   const int K = pm.K, R = pm.R, F = pm.F, KF = K * F, F4 = F / 4;
   const float inv_k = 1.f / (float)K;
   const PsKernels<> pk = load_kernels(mu, inv_sigma, K, R);
-  const int32_t u = order_t[r];
-  const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
+  const int32_t v = order[r];
+  const int32_t beg = indptr[v], end = indptr[v + 1];
   const bool col_ok = li < K * F4;
-  const int myk = col_ok ? li / F4 : 0;
   const int f4 = col_ok ? li % F4 : 0;
+  const float4 g4 = col_ok ? ld4(gout + (int64_t)v * F + 4 * f4) : make_float4(0.f, 0.f, 0.f, 0.f);
   int* l_idx = reinterpret_cast<int*>(lds + grp * GS);
-  float* l_w = lds + grp * GS + G;  // [kPsK][G]
-  const float* my_row = gout + 4 * f4;
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), part = acc;
-  int folded = 0;
-  for (int32_t p0 = beg + gi * G; p0 < end; p0 += ngrp * G) {
-    const bool e_ok = p0 + li < end;
-    const int cnt = min(G, end - p0);
-    int32_t v = 0;
+  float* l_d = lds + grp * GS + G;  // [column lane][edge of the chunk]
+  const float* my_row = hk + 4 * li;
+  for (int32_t e0 = beg + gi * G; e0 < end; e0 += ngrp * G) {
+    const bool e_ok = e0 + li < end;
+    const int cnt = min(G, end - e0);
+    int32_t u = 0;
     float m[kPsR];
 #pragma unroll
     for (int d = 0; d < kPsR; ++d) m[d] = 0.f;
     if (e_ok) {
-      v = indices_t[p0 + li];
-      if (pseudo_t != nullptr) load_pseudo(pseudo_t, p0 + li, R, m);
-      else load_pseudo(pseudo, eid_t[p0 + li], R, m);
+      u = indices[e0 + li];
+      load_pseudo(pseudo, e0 + li, R, m);
     }
     wave_lds_fence();
-    l_idx[li] = v;
-#pragma unroll
-    for (int k = 0; k < kPsK; ++k)
-      if (k < K) l_w[k * G + li] = e_ok ? gauss_k(pk, k, m) * inv_k : 0.f;
+    l_idx[li] = u;
     wave_lds_fence();
 #pragma unroll
     for (int t0 = 0; t0 < G; t0 += kNrU) {
       if (t0 < cnt) {
         int idv[kNrU];
-        float wv[kNrU];
         read8i(l_idx + t0, idv);
         float4 rowv[kNrU];
 #pragma unroll
         for (int t = 0; t < kNrU; ++t)
-          if (col_ok && t0 + t < cnt) rowv[t] = ld4(my_row + (int64_t)idv[t] * F);
-        read8f(l_w + myk * G + t0, wv);
+          if (col_ok && t0 + t < cnt) rowv[t] = ld4(my_row + (int64_t)idv[t] * KF);
+        float dv[kNrU];
 #pragma unroll
-        for (int t = 0; t < kNrU; ++t)
-          if (col_ok && t0 + t < cnt) fma4(part, wv[t], rowv[t]);
+        for (int t = 0; t < kNrU; ++t) dv[t] = (col_ok && t0 + t < cnt) ? dot4(g4, rowv[t]) : 0.f;
+        *reinterpret_cast<float4*>(l_d + li * G + t0) = make_float4(dv[0], dv[1], dv[2], dv[3]);
+        *reinterpret_cast<float4*>(l_d + li * G + t0 + 4) = make_float4(dv[4], dv[5], dv[6], dv[7]);
       }
     }
-    folded += G;
-    if (folded >= 32) {
-      add4(acc, part);
-      part = make_float4(0.f, 0.f, 0.f, 0.f);
-      folded = 0;
+    wave_lds_fence();
+    if (e_ok) {
+      float gm[kPsR];
+#pragma unroll
+      for (int d = 0; d < kPsR; ++d) gm[d] = 0.f;
+#pragma unroll
+      for (int k = 0; k < kPsK; ++k) {
+        if (k >= K) continue;
+        float dot = 0.f;
+        for (int j = 0; j < F4; ++j) dot += l_d[(k * F4 + j) * G + li];
+        const float dlog = dot * inv_k * gauss_k(pk, k, m);  // dw_k(e) w_k(e)
+#pragma unroll
+        for (int d = 0; d < kPsR; ++d) {
+          const float diff = m[d] - pk.mu[k][d];
+          const float is = pk.is[k][d];
+          const float t = dlog * diff * is;  // padded dimensions: is = 0
+          gm[d] = fmaf(-t, is, gm[d]);
+        }
+      }
+#pragma unroll
+      for (int d = 0; d < kPsR; ++d)
+        if (d < R) gpseudo[(int64_t)(e0 + li) * R + d] = gm[d];
     }
   }
-  add4(acc, part);
-  if (rr.coop) {
-    float vv[4];
-    pack4(vv, acc);
-    coop_sum<G, 4, GPB>(coop_buf, vv, grp, li);
-    if (grp != 0) return;
-    acc = unpack4(vv);
-  }
-  if (col_ok) st4(dhk + (int64_t)u * KF + 4 * li, acc);
 }
 
 // Backward, both sides in one walk over the out-edges.  A row owns hk[u] and dhk[u] and gathers gout[v], with which
@@ -640,8 +532,7 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_src_nr(
 // dimensions, as the forward kernel is, which the gathers of hk[u] bound: 1425, and 1478 compiled for K = 2, R = 1).
 template <int G, bool PROJ, int KT, int RT>
 __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
-    RowLaunch rl, const int32_t* __restrict__ order_t, const int32_t* __restrict__ indptr_t,
-    const int32_t* __restrict__ indices_t, const int32_t* __restrict__ eid_t, const float* __restrict__ hk,
+    RowLaunch rl, const int4* __restrict__ rows_t, const int32_t* __restrict__ indices_t, const int32_t* __restrict__ eid_t, const float* __restrict__ hk,
     const float* __restrict__ pseudo, const float* __restrict__ pseudo_t /* nullable: pseudo in this walk's order */,
     ProjArgs pa, const float* __restrict__ mu, const float* __restrict__ inv_sigma, const float* __restrict__ gout,
     PsParams pm, float* __restrict__ dhk, double* __restrict__ partial, float* __restrict__ gpseudo /* nullable */) {
@@ -664,8 +555,9 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
   for (int i = 0; i < NVALS; ++i) sums[i] = 0.f;
   if (active) {
     const PsKernels<KT, RT> pk = load_kernels<KT, RT>(mu, inv_sigma, K, R);
-    const int32_t u = order_t[r];
-    const int32_t beg = indptr_t[u], end = indptr_t[u + 1];
+    const int4 row = rows_t[r];
+    const int32_t u = row.x;
+    const uint32_t beg = row.y, end = row.z;  // unsigned, as in k_gmmp_fwd_nr
     ProjRegs<RT> pq;
     float cu = 0.f;
     if (PROJ) {
@@ -681,26 +573,43 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
     const float* my_row = gout + 4 * f4;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), part = acc;
     int folded = 0;
-    for (int32_t p0 = beg + gi * G; p0 < end; p0 += ngrp * G) {
+    // loads ahead as in k_gmmp_fwd_nr
+    const uint32_t step = ngrp * G;
+    auto target = [&](uint32_t p) { return p < end ? indices_t[p] : 0; };
+    uint32_t p0 = beg + gi * G;
+    int32_t v = target(p0 + li), v1 = target(p0 + step + li);
+    float cv_next = PROJ ? pa.c[v] : 0.f;
+    for (; p0 < end; p0 += step) {
       const bool e_ok = p0 + li < end;
-      const int cnt = min(G, end - p0);
-      int32_t v = 0, e = 0;
-      float cv = 0.f, m[RT], w[KT];
+      const int cnt = min((uint32_t)G, end - p0);
+      wave_lds_fence();  // the previous chunk's reads are done
+      l_idx[li] = v;
+      wave_lds_fence();
+      int32_t e = 0;
+      float m[RT], w[KT];
+      if (!PROJ) {
 #pragma unroll
-      for (int d = 0; d < RT; ++d) m[d] = 0.f;
-      if (e_ok) {
-        v = indices_t[p0 + li];
-        if (PROJ) {
-          cv = pa.c[v];
-          project(pq, R, cu, cv, m);
-        } else {
-          e = eid_t[p0 + li];
+        for (int d = 0; d < RT; ++d) m[d] = 0.f;
+        if (e_ok) {
+          if (pseudo_t == nullptr || gpseudo != nullptr) e = eid_t[p0 + li];
           if (pseudo_t != nullptr) load_pseudo(pseudo_t, p0 + li, R, m);
           else load_pseudo(pseudo, e, R, m);
         }
       }
-      wave_lds_fence();  // the previous chunk's reads are done
-      l_idx[li] = v;
+      const float cv = cv_next;
+      v = v1;
+      v1 = target(p0 + 2 * step + li);
+      if (PROJ) cv_next = pa.c[v];
+      float4 rowv[kNrU];
+      auto fetch = [&](int t0) {
+        int idv[kNrU];
+        read8i(l_idx + t0, idv);
+#pragma unroll
+        for (int t = 0; t < kNrU; ++t)
+          if (col_ok && t0 + t < cnt) rowv[t] = ld4(my_row + (int64_t)idv[t] * F);
+      };
+      fetch(0);
+      if (PROJ) project(pq, R, cu, cv, m);
 #pragma unroll
       for (int k = 0; k < KT; ++k)
         if (k < K) l_w[k * G + li] = w[k] = e_ok ? gauss_k(pk, k, m) * inv_k : 0.f;
@@ -708,13 +617,8 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
 #pragma unroll
       for (int t0 = 0; t0 < G; t0 += kNrU) {
         if (t0 < cnt) {
-          int idv[kNrU];
+          if (t0 > 0) fetch(t0);
           float wv[kNrU], dv[kNrU];
-          read8i(l_idx + t0, idv);
-          float4 rowv[kNrU];
-#pragma unroll
-          for (int t = 0; t < kNrU; ++t)
-            if (col_ok && t0 + t < cnt) rowv[t] = ld4(my_row + (int64_t)idv[t] * F);
           read8f(l_w + myk * G + t0, wv);
 #pragma unroll
           for (int t = 0; t < kNrU; ++t) {
@@ -798,18 +702,19 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
 // one workgroup each, then those ranges, by the one workgroup that also stores the gradients.  The order is fixed.
 constexpr int kParamChunk = 256;
 
-// thread c < nvals returns the sum of column c
+// thread c < nvals returns the sum of column c; the order does not depend on the columns there are
 __device__ __forceinline__ double sum_columns(int nvals, int parts, const double* __restrict__ partial) {
-  __shared__ double sub[kPsBlock];
-  const int slots = kPsBlock / nvals, c = threadIdx.x % nvals, slot = threadIdx.x / nvals;
+  constexpr int W = 64, SLOTS = kPsBlock / W;
+  static_assert(kPsValsProj <= W, "one thread per column");
+  __shared__ double sub[SLOTS][W];
+  const int c = threadIdx.x % W, slot = threadIdx.x / W;
   double s = 0.;
-  if (slot < slots) {
-    for (int z = slot; z < parts; z += slots) s += partial[(int64_t)z * nvals + c];
-    sub[threadIdx.x] = s;
-  }
+  if (c < nvals)
+    for (int z = slot; z < parts; z += SLOTS) s += partial[(int64_t)z * nvals + c];
+  sub[slot][c] = s;
   __syncthreads();
   if (slot == 0)
-    for (int q = 1; q < slots; ++q) s += sub[q * nvals + c];
+    for (int q = 1; q < SLOTS; ++q) s += sub[q][c];
   return s;
 }
 __global__ __launch_bounds__(kPsBlock) void k_gmmp_param_rows(int nvals, int parts, const double* __restrict__ partial,
@@ -953,6 +858,18 @@ static unsigned nr_grid(const gnn_graph_t* g, int side, RowLaunch& rl) {
   return sp.hub_grid + sp.rest_grid;
 }
 
+// LDS that k_gmmp_fwd_nr is launched with and does not use: three workgroups fit a CU instead of eight.  Past the L2s the kernel
+// is bound by what misses them, and fewer rows in flight miss less.  MoNet forward, without -> with, us: 232 965
+// vertices, 1.12 10^8 edges, K = 2, 16 columns (30 MB) 1646 -> 1573, 3 10^7 edges 407 -> 395; 100 000, 10^7, K = 3 (19 MB) 249 ->
+// 223, 2 10^7, K = 2 (13 MB) 223 -> 224; two workgroups 1728, 251.  The backward walk, which the vector units bound, loses
+// (1625 -> 1775).  A launch per 2 to 8 column blocks of the plan, which the L2s would hold: 2081 to 2440, bound by the
+// segments' fixed work.
+constexpr int64_t kFewWorkgroupsBytes = (int64_t)16 << 20;
+constexpr unsigned kFewWorkgroupsLds = 34 * 1024;
+static unsigned nr_fwd_lds(const gnn_graph_t* g, int KF) {
+  return (int64_t)sizeof(float) * KF * g->n > kFewWorkgroupsBytes ? kFewWorkgroupsLds : 0;
+}
+
 // partial slots of the kernels that sum the parameters' gradients: enough for any of them
 static int64_t ps_dst_blocks(const gnn_graph_t* g, int fout) {
   RowLaunch rl;
@@ -1082,9 +999,13 @@ extern "C" gnn_status_t gnn_gmmp_fwd(const gnn_graph_t* g, int fin, int fout, in
       RowLaunch rl;
       const unsigned grid = nr_grid<GL>(g, 0, rl);
       if (grid != 0) {
-        k_gmmp_fwd_nr<GL, false><<<grid, kPsBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, hk, pseudo,
-                                                           ProjArgs{}, mu, inv_sigma, pm, out);
-        GNN_LAUNCH_CHECK();
+        return for_kernels(k, r, [&](auto kernels, auto dims) -> gnn_status_t {
+          constexpr int KT = decltype(kernels)::value, RT = decltype(dims)::value;
+          k_gmmp_fwd_nr<GL, false, KT, RT><<<grid, kPsBlock, nr_fwd_lds(g, k * fout), st>>>(rl, g->rows[0], g->indices, hk, pseudo, ProjArgs{}, mu,
+                                                                     inv_sigma, pm, out);
+          GNN_LAUNCH_CHECK();
+          return GNN_OK;
+        });
       }
       return GNN_OK;
     });
@@ -1134,37 +1055,47 @@ extern "C" gnn_status_t gnn_gmmp_bwd(const gnn_graph_t* g, int fin, int fout, in
     GNN_LAUNCH_CHECK();
     return GNN_OK;
   };
-  if (G && one_walk_pays(g, r)) {
-    ProfScope p("gmmp_bwd", st);
-    unsigned grid = 0;
+  if (G) {
+    const bool apart = gpseudo != nullptr && !one_walk_pays(g, r);
+    if (apart) {
+      ProfScope p("gmmp_bwd_dst", st);
+      GNN_TRY(for_lanes(G, [&](auto lanes) -> gnn_status_t {
+        constexpr int GL = decltype(lanes)::value == 8 ? 8 : 16;
+        RowLaunch rl;
+        const unsigned grid = nr_grid<GL>(g, 0, rl);
+        if (grid == 0) return GNN_OK;
+        k_gmmp_bwd_dst_nr<GL><<<grid, kPsBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, hk, pseudo, mu, inv_sigma,
+                                                        gout, pm, gpseudo);
+        GNN_LAUNCH_CHECK();
+        return GNN_OK;
+      }));
+    }
+    ProfScope p(apart ? "gmmp_bwd_src" : "gmmp_bwd", st);
     GNN_TRY(for_lanes(G, [&](auto lanes) -> gnn_status_t {
       constexpr int GL = decltype(lanes)::value == 8 ? 8 : 16;
       RowLaunch rl;
-      grid = nr_grid<GL>(g, 1, rl);
+      const unsigned grid = nr_grid<GL>(g, 1, rl);
       if (grid == 0) return GNN_OK;
-      k_gmmp_bwd_nr<GL, false, kPsK, kPsR><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, g->eid_t, hk,
-                                                                     pseudo, pseudo_t, ProjArgs{}, mu, inv_sigma, gout, pm,
-                                                                     dhk, wide, gpseudo);
-      GNN_LAUNCH_CHECK();
-      return GNN_OK;
+      return for_kernels(k, r, [&](auto kernels, auto dims) -> gnn_status_t {
+        constexpr int KT = decltype(kernels)::value, RT = decltype(dims)::value;
+        k_gmmp_bwd_nr<GL, false, KT, RT><<<grid, kPsBlock, 0, st>>>(rl, g->rows[1], g->indices_t, g->eid_t, hk, pseudo, pseudo_t,
+                                                                   ProjArgs{}, mu, inv_sigma, gout, pm, dhk, wide,
+                                                                   apart ? nullptr : gpseudo);
+        GNN_LAUNCH_CHECK();
+        return wide_param_sums(k, r, KT, RT, (int)grid, wide, gmu, ginv_sigma, nullptr, nullptr, st);
+      });
     }));
-    GNN_TRY(wide_param_sums(k, r, kPsK, kPsR, (int)grid, wide, gmu, ginv_sigma, nullptr, nullptr, st));
   } else {
     {
       ProfScope p("gmmp_bwd_dst", st);
       unsigned grid = 0;
-      GNN_TRY(for_lanes(G ? G : ps_lanes(fout), [&](auto lanes) -> gnn_status_t {
+      GNN_TRY(for_lanes(ps_lanes(fout), [&](auto lanes) -> gnn_status_t {
         constexpr int L = decltype(lanes)::value;
-        constexpr int GL = L == 8 ? 8 : 16;
         RowLaunch rl;
-        grid = G ? nr_grid<GL>(g, 0, rl) : ps_grid<L>(g, 0, rl);
+        grid = ps_grid<L>(g, 0, rl);
         if (grid == 0) return GNN_OK;
-        if (G)
-          k_gmmp_bwd_dst_nr<GL><<<grid, kPsBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, hk, pseudo, mu,
-                                                          inv_sigma, gout, pm, partial, gpseudo);
-        else
-          k_gmmp_bwd_dst<L><<<grid, kPsBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, hk, pseudo, mu,
-                                                      inv_sigma, gout, pm, partial, gpseudo);
+        k_gmmp_bwd_dst<L><<<grid, kPsBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, hk, pseudo, mu,
+                                                    inv_sigma, gout, pm, partial, gpseudo);
         GNN_LAUNCH_CHECK();
         return GNN_OK;
       }));
@@ -1172,18 +1103,13 @@ extern "C" gnn_status_t gnn_gmmp_bwd(const gnn_graph_t* g, int fin, int fout, in
     }
     {
       ProfScope p("gmmp_bwd_src", st);
-      GNN_TRY(for_lanes(G ? G : ps_lanes(fout), [&](auto lanes) -> gnn_status_t {
+      GNN_TRY(for_lanes(ps_lanes(fout), [&](auto lanes) -> gnn_status_t {
         constexpr int L = decltype(lanes)::value;
-        constexpr int GL = L == 8 ? 8 : 16;
         RowLaunch rl;
-        const unsigned grid = G ? nr_grid<GL>(g, 1, rl) : ps_grid<L>(g, 1, rl);
+        const unsigned grid = ps_grid<L>(g, 1, rl);
         if (grid == 0) return GNN_OK;
-        if (G)
-          k_gmmp_bwd_src_nr<GL><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, g->eid_t, pseudo,
-                                                          pseudo_t, mu, inv_sigma, gout, pm, dhk);
-        else
-          k_gmmp_bwd_src<L><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, g->eid_t, pseudo,
-                                                      pseudo_t, mu, inv_sigma, gout, pm, dhk);
+        k_gmmp_bwd_src<L><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, g->eid_t, pseudo,
+                                                    pseudo_t, mu, inv_sigma, gout, pm, dhk);
         GNN_LAUNCH_CHECK();
         return GNN_OK;
       }));
@@ -1281,9 +1207,13 @@ extern "C" gnn_status_t gnn_monet_fwd(const gnn_graph_t* g, int fin, int fout, i
     RowLaunch rl;
     const unsigned grid = nr_grid<GL>(g, 0, rl);
     if (grid != 0) {
-      k_gmmp_fwd_nr<GL, true><<<grid, kPsBlock, 0, st>>>(rl, g->order[0], g->indptr, g->indices, hk, nullptr, pa, mu,
-                                                        inv_sigma, pm, out);
-      GNN_LAUNCH_CHECK();
+      return for_kernels(k, r, [&](auto kernels, auto dims) -> gnn_status_t {
+        constexpr int KT = decltype(kernels)::value, RT = decltype(dims)::value;
+        k_gmmp_fwd_nr<GL, true, KT, RT><<<grid, kPsBlock, nr_fwd_lds(g, k * fout), st>>>(rl, g->rows[0], g->indices, hk, nullptr, pa, mu, inv_sigma,
+                                                                  pm, out);
+        GNN_LAUNCH_CHECK();
+        return GNN_OK;
+      });
     }
     return GNN_OK;
   });
@@ -1326,7 +1256,7 @@ extern "C" gnn_status_t gnn_monet_bwd(const gnn_graph_t* g, int fin, int fout, i
       if (grid == 0) return GNN_OK;
       return for_kernels(k, r, [&](auto kernels, auto dims) -> gnn_status_t {
         constexpr int KT = decltype(kernels)::value, RT = decltype(dims)::value;
-        k_gmmp_bwd_nr<GL, true, KT, RT><<<grid, kPsBlock, 0, st>>>(rl, g->order[1], g->indptr_t, g->indices_t, g->eid_t, hk,
+        k_gmmp_bwd_nr<GL, true, KT, RT><<<grid, kPsBlock, 0, st>>>(rl, g->rows[1], g->indices_t, g->eid_t, hk,
                                                                   nullptr, nullptr, pa, mu, inv_sigma, gout, pm, dhk,
                                                                   partial, nullptr);
         GNN_LAUNCH_CHECK();
