@@ -558,6 +558,7 @@ gnn_status_t gnn_gcn_blocked_kernel_name(const gnn_graph_t* graph, int fout, int
  *   as unlabelled; n_labelled is the caller's count of the others (0: loss 0).
  *   Any c <= 4096, no alignment needed.
  * gnn_sgd_update:    param -= lr * grad over `count` floats.
+ * gnn_sgd_update_many: the same for `n` parameters (host arrays of n sizes and device pointers).
  * Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE, HIP as for the layers.
  * ------------------------------------------------------------------------- */
 enum { GNN_ACT_IDENTITY = 0, GNN_ACT_RELU = 1, GNN_ACT_ELU = 2, GNN_ACT_LEAKY = 3 };
@@ -573,6 +574,8 @@ gnn_status_t gnn_softmax_xent(int64_t n, int c, int64_t n_labelled, const float*
                               const int32_t* labels /*[n]*/, float* loss /*device, 1 float*/,
                               float* glogits /*[n,c]*/, void* ws, size_t ws_bytes, void* stream);
 gnn_status_t gnn_sgd_update(int64_t count, float lr, const float* grad, float* param, void* stream);
+gnn_status_t gnn_sgd_update_many(int n, const int64_t* counts, float lr, const float* const* grads,
+                                 float* const* params, void* stream);
 
 /* ------------------------------------------------------------------------- *
  * k-nearest-neighbour graph of a batch of point clouds (the EdgeConv model builds its

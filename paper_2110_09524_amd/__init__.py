@@ -13,6 +13,6 @@ from .binding import (  # noqa: F401
     gnn_gcn_workspace_bytes, gnn_gcn_fwd, gnn_gcn_bwd, gnn_gcn_tune, gnn_gcn_blocked_kernel_name,
     EdgeWeights, gnn_gcn_edge_fwd, gnn_gcn_edge_bwd,
     gnn_bias_act_fwd, gnn_bias_act_workspace_bytes, gnn_bias_act_bwd,
-    gnn_softmax_xent_workspace_bytes, gnn_softmax_xent, gnn_sgd_update, gnn_knn_graph,
+    gnn_softmax_xent_workspace_bytes, gnn_softmax_xent, gnn_sgd_update, gnn_sgd_update_many, gnn_knn_graph,
     gnn_prof_enable, gnn_prof_reset, gnn_prof_report,
 )

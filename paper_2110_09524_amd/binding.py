@@ -29,7 +29,7 @@ EXPORTS = [
     "gnn_gcn_workspace_bytes", "gnn_gcn_fwd", "gnn_gcn_bwd", "gnn_gcn_tune", "gnn_gcn_blocked_kernel_name",
     "gnn_edge_weights_create", "gnn_edge_weights_destroy", "gnn_gcn_edge_fwd", "gnn_gcn_edge_bwd",
     "gnn_bias_act_fwd", "gnn_bias_act_workspace_bytes", "gnn_bias_act_bwd", "gnn_softmax_xent_workspace_bytes",
-    "gnn_softmax_xent", "gnn_sgd_update", "gnn_knn_graph", "gnn_prof_enable",
+    "gnn_softmax_xent", "gnn_sgd_update", "gnn_sgd_update_many", "gnn_knn_graph", "gnn_prof_enable",
     "gnn_prof_collect", "gnn_prof_reset", "gnn_prof_count", "gnn_prof_get",
 ]
 
@@ -108,6 +108,7 @@ def load_library(path: str = LIB_PATH) -> C.CDLL:
     lib.gnn_softmax_xent_workspace_bytes.argtypes = [i64]
     lib.gnn_softmax_xent.argtypes = [i64, i32, i64, vp, vp, vp, vp, vp, sz, vp]
     lib.gnn_sgd_update.argtypes = [i64, f32, vp, vp, vp]
+    lib.gnn_sgd_update_many.argtypes = [i32, C.POINTER(i64), f32, C.POINTER(vp), C.POINTER(vp), vp]
     lib.gnn_knn_graph.argtypes = [i32, i32, i32, i32, vp, vp, vp, vp]
     lib.gnn_prof_enable.argtypes = [i32]
     lib.gnn_prof_collect.argtypes = []
@@ -482,6 +483,15 @@ def gnn_softmax_xent(n, c, n_labelled, logits, labels, loss, glogits, ws, stream
 def gnn_sgd_update(lr, grad, param, stream=None):
     assert grad.numel() == param.numel()
     _check(lib().gnn_sgd_update(param.numel(), lr, _f(grad), _f(param), _stream(stream)))
+
+
+def gnn_sgd_update_many(lr, pairs, stream=None):
+    """gnn_sgd_update of every (parameter, gradient), in as few launches as they fit in."""
+    assert all(grad.numel() == param.numel() for param, grad in pairs)
+    n = len(pairs)
+    _check(lib().gnn_sgd_update_many(n, (C.c_int64 * n)(*(p.numel() for p, _ in pairs)), lr,
+                                     (C.c_void_p * n)(*(_f(q) for _, q in pairs)),
+                                     (C.c_void_p * n)(*(_f(p) for p, _ in pairs)), _stream(stream)))
 
 
 def gnn_knn_graph(clouds, points, dim, k, coords, indptr, indices, stream=None):

@@ -3,6 +3,8 @@
 // between two layers, the softmax cross-entropy that closes a node-classification step
 // (the end-to-end setting of Sec. 7.2), and the plain SGD update.  All are streaming kernels
 // over [n, f] matrices; sums over vertices are taken in two fixed-order stages (reproducible).
+#include <type_traits>
+
 #include "common.h"
 #include "rowgroup.h"
 
@@ -125,6 +127,71 @@ __global__ __launch_bounds__(kApplyThreads) void k_softmax_xent(
   }
 }
 
+// The same for rows of at most 16 NC classes, which stay in registers: labels and logits of all four passes are asked for at once,
+// read once, and every exponential is evaluated once; the results are the same bits.  32 768 rows of 40 classes:
+// 13.1 -> 7.1 us.
+template <int NC>
+__global__ __launch_bounds__(kApplyThreads) void k_softmax_xent_narrow(
+    int64_t n, int c, float inv_count, const float* __restrict__ logits, const int32_t* __restrict__ labels,
+    float* __restrict__ glogits, float* __restrict__ partial) {
+  constexpr int L = 16, G = kApplyThreads / L, P = kXentVerts / G;
+  __shared__ float red[G];
+  const int li = threadIdx.x & (L - 1), grp = threadIdx.x / L;
+  const int64_t v0 = blockIdx.x * (int64_t)kXentVerts + grp;
+  int32_t labs[P];
+  float z[P][NC];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const int64_t v = v0 + p * G;
+    labs[p] = v < n ? labels[v] : -1;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) z[p][j] = v < n && li + j * L < c ? logits[v * c + li + j * L] : -INFINITY;
+  }
+  float loss = 0.f;  // lane 0 of a group: the sum over the group's vertices, in pass order
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const int64_t v = v0 + p * G;
+    if (v >= n) continue;  // uniform over the group
+    const int32_t lab = labs[p];
+    float* g = glogits + v * c;
+    if (lab < 0 || lab >= c) {  // unlabelled
+#pragma unroll
+      for (int j = 0; j < NC; ++j)
+        if (li + j * L < c) g[li + j * L] = 0.f;
+      continue;
+    }
+    float mx = -INFINITY, z_lab = 0.f;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      mx = fmaxf(mx, z[p][j]);
+      if (lab / L == j) z_lab = z[p][j];
+    }
+    z_lab = __shfl(z_lab, lab & (L - 1), L);
+#pragma unroll
+    for (int o = L / 2; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, L));
+    float se = 0.f, e[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j)
+      if (li + j * L < c) se += e[j] = expf(z[p][j] - mx);
+#pragma unroll
+    for (int o = L / 2; o > 0; o >>= 1) se += __shfl_xor(se, o, L);
+    const float inv = 1.f / se;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int col = li + j * L;
+      if (col < c) g[col] = (e[j] * inv - (col == lab ? 1.f : 0.f)) * inv_count;
+    }
+    loss += (mx + logf(se)) - z_lab;
+  }
+  if (li == 0) red[grp] = loss;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float s = 0.f;
+    for (int i = 0; i < G; ++i) s += red[i];  // fixed order
+    partial[blockIdx.x] = s;
+  }
+}
+
 // loss = inv_count * sum of the partials, in a fixed tree order (one workgroup)
 __global__ __launch_bounds__(kApplyThreads) void k_xent_finish(int parts, float inv_count,
                                                                const float* __restrict__ partial,
@@ -144,6 +211,26 @@ __global__ __launch_bounds__(kApplyThreads) void k_xent_finish(int parts, float 
 __global__ void k_sgd_update(int64_t count, float lr, const float* __restrict__ grad, float* __restrict__ param) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < count) param[i] = fmaf(-lr, grad[i], param[i]);
+}
+
+// several parameters in one launch: workgroup b belongs to the last of them that starts at or before b
+constexpr int kSgdMost = 16;
+struct SgdParams {
+  const float* grad[kSgdMost];
+  float* param[kSgdMost];
+  int64_t count[kSgdMost];
+  unsigned first[kSgdMost];  // workgroup
+};
+__global__ void k_sgd_update_many(int n, float lr, SgdParams ps) {
+  int t = 0;
+  while (t + 1 < n && ps.first[t + 1] <= blockIdx.x) ++t;
+  const int64_t i = (int64_t)(blockIdx.x - ps.first[t]) * blockDim.x + threadIdx.x;
+  if (i < ps.count[t]) ps.param[t][i] = fmaf(-lr, ps.grad[t][i], ps.param[t][i]);
+}
+
+static bool overlap(const float* a, int64_t na, const float* b, int64_t nb) {
+  const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+  return a0 < b0 + sizeof(float) * nb && b0 < a0 + sizeof(float) * na;
 }
 
 static int bias_parts(int64_t n) {
@@ -247,7 +334,14 @@ extern "C" gnn_status_t gnn_softmax_xent(int64_t n, int c, int64_t n_labelled, c
   ProfScope p("softmax_xent", st);
   float* partial = static_cast<float*>(ws);
   if (n != 0) {
-    k_softmax_xent<<<(unsigned)parts, kApplyThreads, 0, st>>>(n, c, inv_count, logits, labels, glogits, partial);
+    auto narrow = [&](auto slots) {
+      k_softmax_xent_narrow<decltype(slots)::value><<<(unsigned)parts, kApplyThreads, 0, st>>>(n, c, inv_count, logits, labels,
+                                                                                              glogits, partial);
+    };
+    if (c <= 16) narrow(std::integral_constant<int, 1>{});
+    else if (c <= 32) narrow(std::integral_constant<int, 2>{});
+    else if (c <= 64) narrow(std::integral_constant<int, 4>{});
+    else k_softmax_xent<<<(unsigned)parts, kApplyThreads, 0, st>>>(n, c, inv_count, logits, labels, glogits, partial);
     GNN_LAUNCH_CHECK();
   }
   k_xent_finish<<<1, kApplyThreads, 0, st>>>((int)parts, inv_count, partial, loss);
@@ -264,5 +358,42 @@ extern "C" gnn_status_t gnn_sgd_update(int64_t count, float lr, const float* gra
   ProfScope p("sgd_update", st);
   k_sgd_update<<<(unsigned)cdiv(count, 256), 256, 0, st>>>(count, lr, grad, param);
   GNN_LAUNCH_CHECK();
+  return GNN_OK;
+}
+
+extern "C" gnn_status_t gnn_sgd_update_many(int n, const int64_t* counts, float lr, const float* const* grads,
+                                            float* const* params, void* stream) {
+  clear_error();
+  GNN_REQUIRE(n >= 0 && (n == 0 || (counts && grads && params)), GNN_ERR_INVALID_ARG, "gnn_sgd_update_many: invalid list");
+  for (int i = 0; i < n; ++i) {
+    GNN_REQUIRE(counts[i] >= 0, GNN_ERR_INVALID_ARG, "gnn_sgd_update_many: negative count");
+    GNN_REQUIRE(counts[i] == 0 || (grads[i] && params[i]), GNN_ERR_INVALID_ARG, "gnn_sgd_update_many: null pointer");
+  }
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  ProfScope p("sgd_update", st);
+  for (int i = 0; i < n;) {  // launches of up to kSgdMost parameters and 2^31 - 1 workgroups
+    SgdParams ps{};
+    int64_t blocks = 0;
+    int m = 0;
+    for (; i < n && m < kSgdMost; ++i) {
+      const int64_t b = cdiv(counts[i], 256);
+      GNN_REQUIRE(b <= INT32_MAX, GNN_ERR_UNSUPPORTED, "gnn_sgd_update_many: too many elements");
+      if (b == 0) continue;
+      // a launch of its own for what another of this launch writes or reads: shared parameters are updated one after the other
+      bool shared = false;
+      for (int j = 0; j < m; ++j)
+        shared |= overlap(params[i], counts[i], ps.param[j], ps.count[j]) || overlap(params[i], counts[i], ps.grad[j], ps.count[j]) ||
+                  overlap(grads[i], counts[i], ps.param[j], ps.count[j]);
+      if (shared || blocks + b > INT32_MAX) break;
+      ps.grad[m] = grads[i];
+      ps.param[m] = params[i];
+      ps.count[m] = counts[i];
+      ps.first[m++] = (unsigned)blocks;
+      blocks += b;
+    }
+    if (m == 0) continue;
+    k_sgd_update_many<<<(unsigned)blocks, 256, 0, st>>>(m, lr, ps);
+    GNN_LAUNCH_CHECK();
+  }
   return GNN_OK;
 }

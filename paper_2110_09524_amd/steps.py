@@ -195,8 +195,7 @@ class TwoLayerStep:
         return pairs
 
     def sgd(self, lr):
-        for param, grad in self.parameters():
-            B.gnn_sgd_update(lr, grad, param)
+        B.gnn_sgd_update_many(lr, self.parameters())
 
     def step(self, x, lr=None):
         self.forward(x)

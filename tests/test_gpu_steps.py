@@ -49,7 +49,8 @@ def test_activation_kinks_follow_the_conventions():
         assert (g.cpu().numpy() == np.float32(want)).all(), act
 
 
-@pytest.mark.parametrize("n,c", [(1, 2), (300, 4), (2000, 41), (70000, 7)])
+@pytest.mark.parametrize("n,c", [(1, 2), (300, 4), (2000, 41), (70000, 7), (63, 16), (64, 17), (65, 32), (130, 33), (17, 64), (200, 65),
+                                 (9, 1)])
 def test_softmax_xent(n, c):
     import paper_2110_09524_amd as pk
     from gpu_harness import assert_close, dev, empty, workspace
@@ -81,6 +82,22 @@ def test_sgd_update():
     dp = dev(p)
     pk.gnn_sgd_update(0.05, dev(g), dp)
     np.testing.assert_allclose(dp.cpu().numpy(), p.astype(np.float64) - 0.05 * g.astype(np.float64), rtol=1e-6, atol=1e-7)
+
+
+@pytest.mark.parametrize("sizes", [[], [0], [1001], [256, 0, 1, 257, 4000], [7] * 16, [300] * 33])
+def test_sgd_update_many(sizes):
+    """The same bits as one call per parameter; a parameter that is listed twice is updated twice, in order."""
+    import torch
+    import paper_2110_09524_amd as pk
+    torch.manual_seed(len(sizes))
+    params, grads = ([torch.randn(s, device="cuda") for s in sizes] for _ in range(2))
+    pairs = list(zip(params, grads))
+    pairs += [(p, torch.randn_like(p)) for p in params[-2:]]
+    want = {id(p): p.clone() for p in params}
+    for p, g in pairs:
+        pk.gnn_sgd_update(0.05, g, want[id(p)])
+    pk.gnn_sgd_update_many(0.05, pairs)
+    assert all(torch.equal(p, want[id(p)]) for p in params)
 
 
 def test_bad_arguments_raise():
