@@ -703,28 +703,33 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
 constexpr int kParamChunk = 256;
 
 // thread c < nvals returns the sum of column c; the order does not depend on the columns there are
+constexpr int kParamThreads = 1024;
 __device__ __forceinline__ double sum_columns(int nvals, int parts, const double* __restrict__ partial) {
-  constexpr int W = 64, SLOTS = kPsBlock / W;
+  constexpr int W = 64, SLOTS = kParamThreads / W;
   static_assert(kPsValsProj <= W, "one thread per column");
   __shared__ double sub[SLOTS][W];
   const int c = threadIdx.x % W, slot = threadIdx.x / W;
   double s = 0.;
-  if (c < nvals)
+  if (c < nvals) {
+#pragma unroll 8
     for (int z = slot; z < parts; z += SLOTS) s += partial[(int64_t)z * nvals + c];
+  }
   sub[slot][c] = s;
   __syncthreads();
-  if (slot == 0)
+  if (slot == 0) {
+#pragma unroll
     for (int q = 1; q < SLOTS; ++q) s += sub[q][c];
+  }
   return s;
 }
-__global__ __launch_bounds__(kPsBlock) void k_gmmp_param_rows(int nvals, int parts, const double* __restrict__ partial,
-                                                              double* __restrict__ rows) {
+__global__ __launch_bounds__(kParamThreads) void k_gmmp_param_rows(int nvals, int parts, const double* __restrict__ partial,
+                                                                   double* __restrict__ rows) {
   const int z0 = blockIdx.x * kParamChunk;
   const double s = sum_columns(nvals, min(kParamChunk, parts - z0), partial + (int64_t)z0 * nvals);
   if (threadIdx.x < nvals) rows[(int64_t)blockIdx.x * nvals + threadIdx.x] = s;
 }
 // columns: gmu [kt][rt], ginv_sigma [kt][rt], then, where gP is not null, (gP[d,0], gP[d,1], gpb[d]) [rt]
-__global__ __launch_bounds__(kPsBlock) void k_gmmp_param_totals(int K, int R, int kt, int rt, int nrows,
+__global__ __launch_bounds__(kParamThreads) void k_gmmp_param_totals(int K, int R, int kt, int rt, int nrows,
                                                                 const double* __restrict__ rows, float* __restrict__ gmu,
                                                                 float* __restrict__ gis, float* __restrict__ gP /* nullable */,
                                                                 float* __restrict__ gpb) {
@@ -955,11 +960,11 @@ static gnn_status_t wide_param_sums(int K, int R, int kt, int rt, int parts, dou
   if (parts > kParamChunk) {
     double* out = partial + (int64_t)parts * nvals;
     nrows = (int)cdiv(parts, kParamChunk);
-    k_gmmp_param_rows<<<(unsigned)nrows, kPsBlock, 0, st>>>(nvals, parts, partial, out);
+    k_gmmp_param_rows<<<(unsigned)nrows, kParamThreads, 0, st>>>(nvals, parts, partial, out);
     GNN_LAUNCH_CHECK();
     rows = out;
   }
-  k_gmmp_param_totals<<<1, kPsBlock, 0, st>>>(K, R, kt, rt, nrows, rows, gmu, gis, gP, gpb);
+  k_gmmp_param_totals<<<1, kParamThreads, 0, st>>>(K, R, kt, rt, nrows, rows, gmu, gis, gP, gpb);
   GNN_LAUNCH_CHECK();
   return GNN_OK;
 }
