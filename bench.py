@@ -63,23 +63,19 @@ def edgeconv_models(n, e, fin, F):
 def gmm_models(n, e, fin, F, K):
     V = 4 * n * F
     I = 4 * e + 8 * n
+    # backward: one walk over the out-edges gathers gout and owns hk and dhk
+    bwd = (I + V + 4 * n + 2 * K * V, e * (8 + 4 * F), e * K * (6 * F + 14))
     if fin % 4 == 0 and fin <= 256 and fin < K * F:
-        # the library aggregates the input rows per kernel and projects afterwards: the edge kernels
-        # of the forward pass and of the destination side of backward gather x (fin wide)
+        # the library aggregates the input rows per kernel and projects afterwards: the forward edge kernel gathers
+        # x (fin wide)
         X = 4 * n * fin
-        unique = {"gmm_fwd_fused": I + X + 4 * n + K * X, "gmm_bwd_dst": I + X + 4 * n + K * X,
-                  "gmm_bwd_src": I + V + 4 * n + K * V}
-        gather = {"gmm_fwd_fused": e * (8 + 4 * fin), "gmm_bwd_dst": e * (8 + 4 * fin), "gmm_bwd_src": e * (8 + 4 * F)}
-        flops = {"gmm_fwd_fused": e * K * (2 * fin + 12), "gmm_bwd_dst": e * K * (6 * fin + 14),
-                 "gmm_bwd_src": e * K * (2 * F + 12)}
+        unique = {"gmm_fwd_fused": I + X + 4 * n + K * X, "gmm_bwd": bwd[0]}
+        gather = {"gmm_fwd_fused": e * (8 + 4 * fin), "gmm_bwd": bwd[1]}
+        flops = {"gmm_fwd_fused": e * K * (2 * fin + 12), "gmm_bwd": bwd[2]}
         return unique, gather, flops
-    unique = {"gmm_fwd_fused": I + K * V + 4 * n + V,
-              "gmm_bwd_dst": I + K * V + 4 * n + V,
-              "gmm_bwd_src": I + V + 4 * n + K * V}
-    gather = {"gmm_fwd_fused": e * (8 + 4 * K * F), "gmm_bwd_dst": e * (8 + 4 * K * F),
-              "gmm_bwd_src": e * (8 + 4 * F)}
-    flops = {"gmm_fwd_fused": e * K * (2 * F + 12), "gmm_bwd_dst": e * K * (6 * F + 14),
-             "gmm_bwd_src": e * K * (2 * F + 12)}
+    unique = {"gmm_fwd_fused": I + K * V + 4 * n + V, "gmm_bwd": bwd[0]}
+    gather = {"gmm_fwd_fused": e * (8 + 4 * K * F), "gmm_bwd": bwd[1]}
+    flops = {"gmm_fwd_fused": e * K * (2 * F + 12), "gmm_bwd": bwd[2]}
     return unique, gather, flops
 
 
@@ -520,13 +516,10 @@ def main():
                 pk.gnn_monet_bwd(g, fin, F, K, R, x, w_fc, cc, proj_w, proj_b, mu, inv_sigma, hk, gout, gx, gw_fc,
                                  gmu, gis, gproj_w, gproj_b, ws)
             # no per-edge array: the index list, the vertex scalar c (4 n bytes) and the rows
-            unique = {"monet_fwd_fused": I + 4 * n + K * V + V, "monet_bwd_dst": I + 4 * n + K * V + V,
-                      "monet_bwd_src": I + 4 * n + V + K * V}
-            gather = {"monet_fwd_fused": e * (4 + 4 + 4 * K * F), "monet_bwd_dst": e * (4 + 4 + 4 * K * F),
-                      "monet_bwd_src": e * (4 + 4 + 4 * F)}
+            unique = {"monet_fwd_fused": I + 4 * n + K * V + V, "monet_bwd": I + 4 * n + V + 2 * K * V}
+            gather = {"monet_fwd_fused": e * (4 + 4 + 4 * K * F), "monet_bwd": e * (4 + 4 + 4 * F)}
             flops = {"monet_fwd_fused": e * (K * (2 * F + 4 * R + 8) + 12 * R),
-                     "monet_bwd_dst": e * (K * (2 * F + 10 * R + 10) + 20 * R),
-                     "monet_bwd_src": e * (K * (2 * F + 4 * R + 8) + 12 * R)}
+                     "monet_bwd": e * (K * (4 * F + 10 * R + 10) + 20 * R)}
         else:
             pseudo, gpseudo = new(e, R), new(e, R)
             pseudo_t = None if args.no_pseudo_t else new(e, R)   # the coordinates in the transposed list's order
@@ -537,12 +530,13 @@ def main():
                 pk.gnn_gmmp_bwd(g, fin, F, K, R, x, w_fc, pseudo, mu, inv_sigma, hk, gout, gx, gw_fc, gmu, gis,
                                 gpseudo, ws, pseudo_t=pseudo_t)
                 pk.gnn_pseudo_proj_bwd(g, R, cc, pseudo, gpseudo, gproj_w, gproj_b, ws)
+            ids = 1 if pseudo_t is not None else 2   # edge ids beside the indices
             unique = {"gmmp_fwd_fused": I + 4 * e * R + K * V + V, "gmmp_bwd_dst": I + 8 * e * R + K * V + V,
-                      "gmmp_bwd_src": (1 if pseudo_t is not None else 2) * I + 4 * e * R + V + K * V}
+                      "gmmp_bwd_src": ids * I + 4 * e * R + V + 2 * K * V, "gmmp_bwd": 2 * I + 8 * e * R + V + 2 * K * V}
             gather = {"gmmp_fwd_fused": e * (4 + 4 * R + 4 * K * F), "gmmp_bwd_dst": e * (4 + 8 * R + 4 * K * F),
-                      "gmmp_bwd_src": e * ((4 if pseudo_t is not None else 8) + 4 * R + 4 * F)}
-            flops = {"gmmp_fwd_fused": e * K * (2 * F + 4 * R + 8), "gmmp_bwd_dst": e * K * (2 * F + 10 * R + 10),
-                     "gmmp_bwd_src": e * K * (2 * F + 4 * R + 8)}
+                      "gmmp_bwd_src": e * (4 * ids + 4 * R + 4 * F), "gmmp_bwd": e * (8 + 8 * R + 4 * F)}
+            flops = {"gmmp_fwd_fused": e * K * (2 * F + 4 * R + 8), "gmmp_bwd_dst": e * K * (2 * F + 6 * R + 10),
+                     "gmmp_bwd_src": e * K * (4 * F + 8 * R + 8), "gmmp_bwd": e * K * (4 * F + 10 * R + 10)}
         metric = "MoNet/GMM layer with projected pseudo-coordinates fwd+bwd edges/sec"
         cfg = {"in_feat": fin, "out_feat": F, "kernels": K, "pseudo_dim": R,
                "pseudo": "tanh(proj_w (1/sqrt(deg_u), 1/sqrt(deg_v)) + proj_b), " +
