@@ -516,18 +516,37 @@ __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk
 // that only serves cache residency), so an L2 serves one block at a time.  Inside a workgroup the
 // groups draw (row, slice) slots from an LDS counter, longest rows first.  A row's chunks are summed in the order of the launch-per-block kernels
 // (blocks ascending, edges in list order), so the results do not depend on who draws what.
-// MODE as k_gat_blk; one segment per phase, fp32 rows, per-edge scalars gathered from L2.
+// MODE as k_gat_blk; one segment per phase, per-edge scalars gathered from L2 or (TAB) read from LDS.
 constexpr int kGatResThreads = 1024;
+// Groups: SL / NA lanes, each with NA float4 of the slice.  NA = 2 is for rows of an fp16 copy, which a lane then reads in 16
+// instead of 8 bytes and a wavefront eight at a time: half as many gather instructions, and twice as many (row, slice) pairs share
+// what a pair costs whatever its length.  GAT layer, 232 965 vertices, 1.1 10^8 edges, fin = 602, forward, ms: 4 x 64 5.93 -> 4.77;
+// fin = 64, with the backward pass, 4 x 64 13.1 -> 11.9, 1 x 128 6.87 -> 6.50.  (fp32 rows, two float4 a lane, four rows in flight:
+// 7.18 -> 7.69 forward, 7.77 -> 8.02 source side.)  The longest rows then share a wavefront with seven groups that wait for
+// them, not three, so it is taken where a row is no longer than two groups' share of the edges.  4 x 64 and 2 x 64 by the longest row
+// in such shares, us: forward, 1.6 485 -> 456, 2.4 676 -> 664, 2.5 264 -> 262, 3.2 393 -> 409; with the backward pass, 0.5
+// 13 101 -> 11 881, 1.6 1752 -> 1737, 3.2 1045 -> 1151, 4 351 -> 397, 8.6 (1 x 128) 318 -> 385.
+constexpr int kGatPairShares = 2;
+// TAB: the block's part of el in LDS, where it leaves room for fewer rows at a time; its next part travels in registers during
+// a phase.  A gathered fp16 slice is one line, its score was another.  Forward of the layers above, NA = 2 without -> with it, us: 4 x 64
+// 4765 -> 4450, 1 x 128 2416 -> 2320; 60 000 vertices, 250 even edges, 4 x 64 572 -> 488 (NA = 1: 712).  With two sums a row
+// (MODE 3) the rows of a batch get too few: 11.9 -> 12.1 ms a training pass, and fp32 rows 16.8 -> 17.0.
+constexpr int kGatTabPerThread = 12;
+template <int SL, int MODE, int NA>
+constexpr int kGatResGroupInts = (kGatResThreads * NA / SL) * (MODE == 2 || MODE == 3 ? 3 : 2) * SL;  // idx, p, (p2) of all groups
+// a (row, slice) pair: sums (two for MODE 3) | state float4 | (beg, end) of two phases | row
 template <int SL, int MODE>
-constexpr int kGatResSlots = (kGatResThreads / SL) * (MODE == 3 ? 4 : 8);
-// LDS ints of a workgroup: sums (two for MODE 3) | state float4 | (beg, end) of two phases | rows |
-// per group idx, p, p2 | two counters
-template <int SL, int MODE>
-constexpr int kGatResLdsInts = (MODE == 3 ? 2 : 1) * 4 * SL * kGatResSlots<SL, MODE> + 4 * kGatResSlots<SL, MODE> +
-                               4 * kGatResSlots<SL, MODE> + kGatResSlots<SL, MODE> +
-                               (kGatResThreads / SL) * 3 * SL + 4;
+constexpr int kGatResSlotInts = (MODE == 3 ? 2 : 1) * 4 * SL + 4 + 4 + 1;
+constexpr int kGatResLdsBytes = 160 * 1024;
+// Pairs a workgroup holds beside `table` ints: what the LDS leaves, a multiple of 4 so that the arrays stay 16-byte aligned
+template <int SL, int MODE, int NA>
+constexpr int gat_res_slots(int table) {
+  constexpr int most = MODE == 3 ? 256 : 512;
+  const int fit = (kGatResLdsBytes / 4 - 4 - kGatResGroupInts<SL, MODE, NA> - table) / kGatResSlotInts<SL, MODE>;
+  return (fit < most ? fit : most) / 4 * 4;
+}
 
-template <int SL, int MODE, bool SKIP, bool HALF, bool NARROW>
+template <int SL, int MODE, int NA, bool TAB, bool SKIP, bool HALF, bool NARROW>
 __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
     int32_t n_rows, const int32_t* __restrict__ order, const int2* __restrict__ bseg /* [nblk][n_rows] */,
     const int32_t* __restrict__ bcol, const float* __restrict__ feat /* gathered rows: z or gout */,
@@ -538,42 +557,63 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
     float* __restrict__ m_out, float* __restrict__ d_out, int32_t* __restrict__ clock, int spin_limit, int sync_every,
     const float* __restrict__ alpha_b /* MODE 2, nullable: stashed signed softmax values, [H][nnz] in the order of
                                          bcol (the "fusion with stashing" arm) */,
-    int64_t nnz) {
-  constexpr int GPB = kGatResThreads / SL;
-  constexpr int NSLOT = kGatResSlots<SL, MODE>;
-  constexpr int R = NSLOT / GPB;
+    int64_t nnz, int nslot /* (row, slice) pairs the LDS holds */) {
+  constexpr int L = SL / NA;  // lanes of a group
   constexpr int U = SL < 8 ? 4 : 8;
+  static_assert(NA == 1 || HALF, "fp32 rows: one float4 a lane");
+  static_assert(!TAB || MODE != 2, "the source side needs 16 bytes per gathered vertex");
+  constexpr int GPB = kGatResThreads / L;
+  constexpr int GS = kGatResGroupInts<SL, MODE, NA> / GPB;  // LDS ints of a group
   constexpr bool DUAL = MODE == 3;
   constexpr bool SRC = MODE == 2;
   constexpr bool ONLINE = MODE == 0 || MODE == 3;
-  static_assert(NSLOT <= kGatResThreads, "one thread per slot loads its metadata");
   extern __shared__ __align__(16) int lds_gr[];
   const int lane = threadIdx.x & 63;
-  const int li = threadIdx.x & (SL - 1);
-  const int grp = threadIdx.x / SL;
+  const int li = threadIdx.x & (L - 1);
+  const int grp = threadIdx.x / L;
   const int slice = blockIdx.x % ns;
   const int64_t nwg = gridDim.x / ns, wg = blockIdx.x / ns;  // workgroups that serve this slice
-  const int64_t ngroups = nwg * GPB;
   const int H = dm.H, HF = dm.HF;
   const int h = slice / sph;
   const bool leader = (slice % sph) == 0;  // one slice per head keeps the per-head scalars
   // a row narrower than its slice (a single slice of fewer than 64 columns): the lanes past its end
   // gather the row's first columns again (same cache line) and keep zeros where it matters
-  const bool col_ok = slice * 4 * SL + 4 * li < HF;
-  const int col = col_ok ? slice * 4 * SL + 4 * li : 0;
+  const bool col_ok = slice * 4 * SL + 4 * NA * li < HF;
+  const int col = col_ok ? slice * 4 * SL + 4 * NA * li : 0;
 
-  float4* l_acc = reinterpret_cast<float4*>(lds_gr);                                   // [NSLOT][SL]
-  float4* l_acc2 = l_acc + (DUAL ? SL * NSLOT : 0);                                    // [NSLOT][SL] (MODE 3)
-  float4* l_state = l_acc2 + SL * NSLOT;                                               // [NSLOT]
-  int2* l_seg = reinterpret_cast<int2*>(l_state + NSLOT);                              // [2][NSLOT]
-  int* l_row = reinterpret_cast<int*>(l_seg + 2 * NSLOT);                              // [NSLOT]
-  int* l_idx = l_row + NSLOT + grp * 3 * SL;
+  float4* l_acc = reinterpret_cast<float4*>(lds_gr);                                   // [nslot][SL]
+  float4* l_acc2 = l_acc + (DUAL ? SL * nslot : 0);                                    // [nslot][SL] (MODE 3)
+  float4* l_state = l_acc2 + SL * nslot;                                               // [nslot]
+  int2* l_seg = reinterpret_cast<int2*>(l_state + nslot);                              // [2][nslot]
+  int* l_row = reinterpret_cast<int*>(l_seg + 2 * nslot);                              // [nslot]
+  int* l_idx = l_row + nslot + grp * GS;
   float* l_p = reinterpret_cast<float*>(l_idx + SL);
   float* l_p2 = l_p + SL;
-  int* l_cnt = l_row + NSLOT + GPB * 3 * SL;                                           // [2]
+  int* l_cnt = l_row + nslot + GPB * GS;                                               // [2]
+  float* l_tab = reinterpret_cast<float*>(l_cnt + 4);                                  // [block_cols] (TAB)
+  float tab[TAB ? kGatTabPerThread : 1] = {};
+  auto fetch_table = [&](int p) {
+#pragma unroll
+    for (int i = 0; i < (TAB ? kGatTabPerThread : 0); ++i) {
+      const int c = i * kGatResThreads + threadIdx.x;
+      const int64_t u = (int64_t)p * block_cols + c;
+      if (c < block_cols && u < n_rows) tab[i] = el_hm ? el[(int64_t)h * n_rows + u] : el[u * H + h];
+    }
+  };
+  auto store_table = [&]() {
+#pragma unroll
+    for (int i = 0; i < (TAB ? kGatTabPerThread : 0); ++i) {
+      const int c = i * kGatResThreads + threadIdx.x;
+      if (c < block_cols) l_tab[c] = tab[i];
+    }
+  };
+  if constexpr (TAB) {
+    fetch_table(0);
+    store_table();
+  }
 
-  const int64_t rows_per_group = (n_rows + ngroups - 1) / ngroups;
-  const int ngen = (int)((rows_per_group + R - 1) / R);
+  const int64_t rows_per_wg = (n_rows + nwg - 1) / nwg;
+  const int ngen = (int)((rows_per_wg + nslot - 1) / nslot);
   // workgroups go to the XCDs round-robin: those with the same id mod 8 share an L2
   PhaseClock pc{clock ? clock + (blockIdx.x % kXcds) * kClockStride : nullptr, (int)(gridDim.x / kXcds), spin_limit,
                 false, sync_every > 0 ? sync_every : nblk};
@@ -582,10 +622,11 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
   const char* feat_bytes = reinterpret_cast<const char*>(feat);
   constexpr uint32_t kElem = HALF ? 2u : 4u;  // bytes per stored element of the gathered matrix
   const uint32_t row_bytes = (uint32_t)HF * kElem, col_bytes = (uint32_t)col * kElem;
-  using RowRaw = std::conditional_t<HALF, uint2, float4>;  // a lane's four columns of a gathered row
-  auto widen = [](const RowRaw& r) {
+  using Halves = std::conditional_t<NA == 2, uint4, uint2>;
+  using RowRaw = std::conditional_t<HALF, Halves, float4>;  // a lane's columns of a gathered row
+  auto widen = [](const RowRaw& r, int a) {
     if constexpr (HALF) {
-      const __half2* hh = reinterpret_cast<const __half2*>(&r);
+      const __half2* hh = reinterpret_cast<const __half2*>(&r) + 2 * a;
       const float2 lo = __half22float2(hh[0]), hi = __half22float2(hh[1]);
       return make_float4(lo.x, lo.y, hi.x, hi.y);
     } else {
@@ -594,19 +635,19 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
   };
 
   struct Item {
-    int32_t beg, end, c_first;
-    float4 zr;  // MODE 2: the row's own z slice
+    int32_t beg, end, c_first[NA];
+    float4 zr[NA];  // MODE 2: the row's own z slice
   };
 
   for (int gen = 0; gen < ngen; ++gen) {
-    const int64_t j0 = gen * rows_per_group / ngen, j1 = (gen + 1) * rows_per_group / ngen;
-    const int nslots = (int)(j1 - j0) * GPB;  // slot q: row at position (j0 * GPB + q) * nwg + wg (or + nwg - 1 - wg)
+    const int64_t j0 = gen * rows_per_wg / ngen, j1 = (gen + 1) * rows_per_wg / ngen;
+    const int nslots = (int)(j1 - j0);  // slot q: row at position (j0 + q) * nwg + wg (or + nwg - 1 - wg)
     // (the previous generation ended with a workgroup barrier: its tables are free)
     int64_t pos = -1;                         // thread q < nslots: position of slot q's row in the degree order
     if ((int)threadIdx.x < nslots) {
       // consecutive positions of the degree order go to consecutive workgroups, in alternating
       // direction from one round to the next, so every workgroup gets the same mix of degrees
-      const int64_t r = (j0 * GPB + threadIdx.x) * nwg + ((threadIdx.x & 1) ? nwg - 1 - wg : wg);
+      const int64_t r = (j0 + threadIdx.x) * nwg + ((threadIdx.x & 1) ? nwg - 1 - wg : wg);
       if (r < n_rows) pos = r;
       const int32_t row = pos >= 0 ? order[pos] : -1;
       l_row[threadIdx.x] = row;
@@ -632,19 +673,26 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
     auto grab = [&](int p) {
       int q = 0;
       if (li == 0) q = atomicAdd(l_cnt + (p & 1), 1);
-      return __shfl(q, lane & ~(SL - 1), 64);
+      return __shfl(q, lane & ~(L - 1), 64);
     };
     // what a slot needs before its edge loop in phase p: bounds, first indices, (MODE 2) the row's own z
     auto fetch = [&](int p, int q) {
-      Item it{0, 0, p * block_cols, make_float4(0.f, 0.f, 0.f, 0.f)};
+      Item it{};
+#pragma unroll
+      for (int a = 0; a < NA; ++a) it.c_first[a] = p * block_cols;
       if (q >= nslots) return it;
-      const int2 sg = l_seg[(p & 1) * NSLOT + q];
+      const int2 sg = l_seg[(p & 1) * nslot + q];
       it.beg = sg.x;
       it.end = sg.y;
-      if (it.beg + li < it.end) it.c_first = bcol[it.beg + li];
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+        if (it.beg + li + L * a < it.end) it.c_first[a] = bcol[it.beg + li + L * a];
       if (SRC) {
         const int32_t row = l_row[q];
-        if (row >= 0 && it.beg < it.end && col_ok) it.zr = ld4_stream(rowfeat + (int64_t)row * HF + col);
+        if (row >= 0 && it.beg < it.end && col_ok) {
+#pragma unroll
+          for (int a = 0; a < NA; ++a) it.zr[a] = ld4_stream(rowfeat + (int64_t)row * HF + col + 4 * a);
+        }
       }
       return it;
     };
@@ -658,6 +706,7 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
       int2 seg_next = make_int2(0, 0);
       if (!last && pos >= 0) seg_next = bseg[(int64_t)(p + 1) * n_rows + pos];
       if (threadIdx.x == 0) l_cnt[(p + 1) & 1] = 0;
+      if constexpr (TAB) fetch_table(last ? 0 : p + 1);
 
       while (q < nslots) {
         const int qn = grab(p);
@@ -666,32 +715,58 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
         const int32_t beg = cur.beg, end = cur.end;
         if (row >= 0 && (beg < end || last)) {
           const float4 stt = l_state[q];
-          float4 acc = l_acc[q * SL + li], acc2 = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (DUAL) acc2 = l_acc2[q * SL + li];
-          if (SRC) acc2 = cur.zr;
+          float4 acc[NA], acc2[NA];
+#pragma unroll
+          for (int a = 0; a < NA; ++a) {
+            acc[a] = l_acc[q * SL + li + L * a];
+            acc2[a] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (DUAL) acc2[a] = l_acc2[q * SL + li + L * a];
+            if (SRC) acc2[a] = cur.zr[a];
+          }
           const float r_a = ONLINE ? stt.w : stt.y;
           const float r_m = stt.z, r_invd = stt.w;  // MODE 1
-          float s_run = 0.f;  // chunk-phase lanes: sum of alpha g (MODE 1), of alpha g D[v] (MODE 2)
-          float s_dot = 0.f;  // MODE 2, row-phase lanes: sum of alpha g <z[u], gout[v]> over the lane's columns
+          float s_run[NA], s_dot[NA], d_lane[NA], s2_lane[NA];
+#pragma unroll
+          for (int a = 0; a < NA; ++a) {
+            s_run[a] = 0.f;  // chunk-phase lanes: sum of alpha g (MODE 1), of alpha g D[v] (MODE 2)
+            s_dot[a] = 0.f;  // MODE 2, row-phase lanes: sum of alpha g <z[u], gout[v]> over the lane's columns
+            d_lane[a] = li == 0 && a == 0 ? stt.y : 0.f;
+            s2_lane[a] = li == 0 && a == 0 ? stt.z : 0.f;
+          }
           float m_run = stt.x;  // ONLINE
-          float d_lane = li == 0 ? stt.y : 0.f, s2_lane = li == 0 ? stt.z : 0.f;
-          int32_t c_next = cur.c_first;
+          int32_t c_next[NA];
+#pragma unroll
+          for (int a = 0; a < NA; ++a) c_next[a] = cur.c_first[a];
           for (int32_t c0 = beg; c0 < end; c0 += SL) {
-            const bool e_ok = c0 + li < end;
             const int cnt = min(SL, end - c0);
-            const int32_t c = e_ok ? c_next : col_begin;
-            if (c0 + SL + li < end) c_next = bcol[c0 + SL + li];
-            l_idx[li] = c;
-            float e_a = 0.f, a_st = 0.f;
-            float4 vs = make_float4(0.f, 0.f, 1.f, 0.f);
-            if (SRC && alpha_b != nullptr && e_ok) a_st = alpha_b[(int64_t)h * nnz + c0 + li];
-            if (e_ok) {
-              if (SRC) vs = vstate[(int64_t)h * n_rows + c];  // head-major (er, m, 1/d, D) of the destination
-              else e_a = el_hm ? el[(int64_t)h * n_rows + c] : el[(int64_t)c * H + h];
+            bool e_ok[NA];
+            float e_a[NA], a_st[NA];
+            float4 vs[NA];
+#pragma unroll
+            for (int a = 0; a < NA; ++a) {
+              e_ok[a] = li + L * a < cnt;
+              const int32_t c = e_ok[a] ? c_next[a] : col_begin;
+              if (c0 + SL + li + L * a < end) c_next[a] = bcol[c0 + SL + li + L * a];
+              l_idx[li + L * a] = c;
+              e_a[a] = 0.f;
+              a_st[a] = 0.f;
+              vs[a] = make_float4(0.f, 0.f, 1.f, 0.f);
+              if (SRC && alpha_b != nullptr && e_ok[a]) a_st[a] = alpha_b[(int64_t)h * nnz + c0 + li + L * a];
+              if (e_ok[a]) {
+                if (SRC) vs[a] = vstate[(int64_t)h * n_rows + c];  // head-major (er, m, 1/d, D) of the destination
+                else if constexpr (TAB) e_a[a] = l_tab[c - col_begin];
+                else e_a[a] = el_hm ? el[(int64_t)h * n_rows + c] : el[(int64_t)c * H + h];
+              }
             }
             wave_lds_fence();
-            float4 part = make_float4(0.f, 0.f, 0.f, 0.f), part2 = part;
-            float dpart = 0.f;
+            float4 part[NA], part2[NA];
+            float dpart[NA];
+#pragma unroll
+            for (int a = 0; a < NA; ++a) {
+              part[a] = make_float4(0.f, 0.f, 0.f, 0.f);
+              part2[a] = part[a];
+              dpart[a] = 0.f;
+            }
             float sc = 1.f;  // ONLINE: factor that brings the running sums to this chunk's maximum
 #pragma unroll
             for (int t0 = 0; t0 < SL; t0 += U) {
@@ -724,38 +799,54 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
               }
               if (gathers_first) __builtin_amdgcn_s_setprio(0);
               if (t0 == 0) {
-                float pe = 0.f, pe2 = 0.f;
-                if (e_ok) {
-                  if (SRC) {
-                    if (alpha_b != nullptr) {  // read back instead of recomputed; D[v] is still gathered
-                      pe = fabsf(a_st);
-                      pe2 = a_st > 0.f ? pe : dm.slope * pe;
-                    } else {
-                      const float raw = r_a + vs.x;
-                      pe = __expf(leaky(raw, dm.slope) - vs.y) * vs.z;
-                      pe2 = raw > 0.f ? pe : dm.slope * pe;
+                float pe[NA], pe2[NA];
+                if (ONLINE) {
+                  float raw[NA], sc_e[NA], top = -INFINITY;
+#pragma unroll
+                  for (int a = 0; a < NA; ++a) {
+                    raw[a] = e_a[a] + r_a;
+                    sc_e[a] = e_ok[a] ? leaky(raw[a], dm.slope) : -INFINITY;
+                    top = fmaxf(top, sc_e[a]);
+                  }
+                  const float m_new = fmaxf(m_run, group_max_from<L>(top, 1));  // finite: lane 0 of a chunk is valid
+                  sc = (m_run == -INFINITY) ? 0.f : __expf(m_run - m_new);
+#pragma unroll
+                  for (int a = 0; a < NA; ++a) {
+                    pe[a] = e_ok[a] ? __expf(sc_e[a] - m_new) : 0.f;
+                    pe2[a] = raw[a] > 0.f ? pe[a] : dm.slope * pe[a];
+                    d_lane[a] = fmaf(d_lane[a], sc, pe[a]);
+                    s2_lane[a] = fmaf(s2_lane[a], sc, pe2[a]);
+                  }
+                  m_run = m_new;
+                } else {
+#pragma unroll
+                  for (int a = 0; a < NA; ++a) {
+                    pe[a] = pe2[a] = 0.f;
+                    if (e_ok[a]) {
+                      if (SRC) {
+                        if (alpha_b != nullptr) {  // read back instead of recomputed; D[v] is still gathered
+                          pe[a] = fabsf(a_st[a]);
+                          pe2[a] = a_st[a] > 0.f ? pe[a] : dm.slope * pe[a];
+                        } else {
+                          const float raw = r_a + vs[a].x;
+                          pe[a] = __expf(leaky(raw, dm.slope) - vs[a].y) * vs[a].z;
+                          pe2[a] = raw > 0.f ? pe[a] : dm.slope * pe[a];
+                        }
+                        s_run[a] = fmaf(pe2[a], vs[a].w, s_run[a]);
+                      } else {
+                        const float raw = e_a[a] + r_a;
+                        pe[a] = __expf(leaky(raw, dm.slope) - r_m) * r_invd;
+                        pe[a] = raw > 0.f ? pe[a] : dm.slope * pe[a];  // MODE 1
+                        s_run[a] += pe[a];
+                      }
                     }
-                    s_run = fmaf(pe2, vs.w, s_run);
-                  } else if (!ONLINE) {
-                    const float raw = e_a + r_a;
-                    pe = __expf(leaky(raw, dm.slope) - r_m) * r_invd;
-                    pe = raw > 0.f ? pe : dm.slope * pe;  // MODE 1
-                    s_run += pe;
                   }
                 }
-                if (ONLINE) {
-                  const float raw = e_a + r_a;
-                  const float sc_e = e_ok ? leaky(raw, dm.slope) : -INFINITY;
-                  const float m_new = fmaxf(m_run, group_max_from<SL>(sc_e, 1));  // finite: lane 0 of a chunk is valid
-                  sc = (m_run == -INFINITY) ? 0.f : __expf(m_run - m_new);
-                  pe = e_ok ? __expf(sc_e - m_new) : 0.f;
-                  pe2 = raw > 0.f ? pe : dm.slope * pe;
-                  d_lane = fmaf(d_lane, sc, pe);
-                  s2_lane = fmaf(s2_lane, sc, pe2);
-                  m_run = m_new;
+#pragma unroll
+                for (int a = 0; a < NA; ++a) {
+                  l_p[li + L * a] = pe[a];
+                  if (DUAL || SRC) l_p2[li + L * a] = pe2[a];
                 }
-                l_p[li] = pe;
-                if (DUAL || SRC) l_p2[li] = pe2;
                 wave_lds_fence();
               }
               float pv[U], pv2[U];
@@ -772,35 +863,50 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
               for (int t4 = 0; t4 < U; t4 += 4) {
                 if (!SKIP || t0 + t4 < cnt) {
 #pragma unroll
-                  for (int t = t4; t < t4 + 4; ++t) {
-                    const float4 rv = widen(rowv[t]);
-                    fma4(part, pv[t], rv);
-                    if (DUAL) fma4(part2, pv2[t], rv);
-                    if (SRC) dpart = fmaf(pv2[t], dot4(acc2, rv), dpart);
-                  }
+                  for (int t = t4; t < t4 + 4; ++t)
+#pragma unroll
+                    for (int a = 0; a < NA; ++a) {
+                      const float4 rv = widen(rowv[t], a);
+                      fma4(part[a], pv[t], rv);
+                      if (DUAL) fma4(part2[a], pv2[t], rv);
+                      if (SRC) dpart[a] = fmaf(pv2[t], dot4(acc2[a], rv), dpart[a]);
+                    }
                 }
               }
             }
-            if (ONLINE) {
-              fold4(acc, sc, part);
-              if (DUAL) fold4(acc2, sc, part2);
-            } else {
-              add4(acc, part);
+#pragma unroll
+            for (int a = 0; a < NA; ++a) {
+              if (ONLINE) {
+                fold4(acc[a], sc, part[a]);
+                if (DUAL) fold4(acc2[a], sc, part2[a]);
+              } else {
+                add4(acc[a], part[a]);
+              }
+              if (SRC) s_dot[a] += dpart[a];
             }
-            if (SRC) s_dot += dpart;
             wave_lds_fence();
           }
+          // the sum over the lanes of all their values: that of SL lanes with one each, in the same order
+          auto total = [&](const float (&v)[NA]) {
+            float t = group_sum_from<L>(v[0], 1);
+#pragma unroll
+            for (int a = 1; a < NA; ++a) t += group_sum_from<L>(v[a], 1);
+            return t;
+          };
           // close the item: statistics back to the slot, or (last phase) the finished row to memory
           float4 st_new = stt;
           if (ONLINE) {
-            const float d_tot = group_sum_from<SL>(d_lane, 1);
-            const float s2_tot = MODE == 3 ? group_sum_from<SL>(s2_lane, 1) : 0.f;
+            const float d_tot = total(d_lane);
+            const float s2_tot = MODE == 3 ? total(s2_lane) : 0.f;
             st_new = make_float4(m_run, d_tot, s2_tot, stt.w);
             if (last) {
               // the row is complete: normalise (a row without in-edges keeps out = 0, m = 0, d = 1)
               const float inv = d_tot > 0.f ? 1.f / d_tot : 0.f;
-              scale4(acc, inv);
-              if (DUAL) scale4(acc2, inv);
+#pragma unroll
+              for (int a = 0; a < NA; ++a) {
+                scale4(acc[a], inv);
+                if (DUAL) scale4(acc2[a], inv);
+              }
               if (leader && li == 0) {
                 const int64_t rh = (int64_t)row * H + h;
                 m_out[rh] = d_tot > 0.f ? m_run : 0.f;
@@ -809,29 +915,33 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
               }
             }
           } else if (MODE == 1) {
-            if (leader) st_new.x = stt.x + group_sum_from<SL>(s_run, 1);
+            if (leader) st_new.x = stt.x + total(s_run);
             if (last && leader && li == 0) scal_buf[(int64_t)row * H + h] = st_new.x;
           } else {
             // this slice's share of del[u, h]; the D term is counted by one slice per head
-            st_new.x = stt.x + group_sum_from<SL>(s_dot - (leader ? s_run : 0.f), 1);
+#pragma unroll
+            for (int a = 0; a < NA; ++a) s_dot[a] -= leader ? s_run[a] : 0.f;
+            st_new.x = stt.x + total(s_dot);
             if (last && li == 0) scal_buf[(int64_t)row * kSlices + slice] = st_new.x;
           }
-          if (last) {
-            if (col_ok) {
-              st4_stream(acc_buf + (int64_t)row * HF + col, acc);
-              if (DUAL) st4_stream(acc2_buf + (int64_t)row * HF + col, acc2);
+#pragma unroll
+          for (int a = 0; a < NA; ++a) {
+            if (!last) {
+              l_acc[q * SL + li + L * a] = acc[a];
+              if (DUAL) l_acc2[q * SL + li + L * a] = acc2[a];
+            } else if (col_ok) {
+              st4_stream(acc_buf + (int64_t)row * HF + col + 4 * a, acc[a]);
+              if (DUAL) st4_stream(acc2_buf + (int64_t)row * HF + col + 4 * a, acc2[a]);
             }
-          } else {
-            l_acc[q * SL + li] = acc;
-            if (DUAL) l_acc2[q * SL + li] = acc2;
-            if (li == 0) l_state[q] = st_new;
           }
+          if (!last && li == 0) l_state[q] = st_new;
         }
         q = qn;
         cur = nxt;
       }
-      if ((int)threadIdx.x < nslots) l_seg[((p + 1) & 1) * NSLOT + threadIdx.x] = seg_next;
+      if ((int)threadIdx.x < nslots) l_seg[((p + 1) & 1) * nslot + threadIdx.x] = seg_next;
       __syncthreads();  // the workgroup is done with this block; the next phase's bounds are in LDS
+      if constexpr (TAB) store_table();  // read after the second barrier
       if (!last) {      // first slot of the next phase: its loads travel during the wait below
         q = grab(p + 1);
         cur = fetch(p + 1, q);
@@ -1028,7 +1138,19 @@ static bool gat_resident_applies(const gnn_graph_t* g, GatDims dm) {
   return pick_slicing(dm.H, dm.HF, sl) && sl.SL == 16;
 }
 
-template <int MODE, bool SKIP, bool HALF, bool NARROW>
+// one workgroup per CU, a multiple of 8 so that every XCD serves one slice
+static unsigned gat_resident_grid() { return (unsigned)(device_cu_count() / kXcds * kXcds); }
+
+// fp16 rows: two float4 a lane, and (forward, no stash) the block's part of el in LDS as well; see kGatPairShares, kGatTabPerThread
+static bool gat_resident_pairs(const gnn_graph_t* g, int side, GatDims dm) {
+  const int64_t groups = (int64_t)gat_resident_grid() / (dm.HF / 64) * (kGatResThreads / 8);
+  return (int64_t)g->max_degree[side] * groups <= kGatPairShares * g->nnz;
+}
+static bool gat_resident_table(const gnn_graph_t* g, GatDims dm) {
+  return gat_resident_pairs(g, 0, dm) && g->block_cols <= kGatTabPerThread * kGatResThreads;
+}
+
+template <int MODE, int NA, bool TAB, bool SKIP, bool HALF, bool NARROW>
 static gnn_status_t launch_resident_addr(const gnn_graph_t* g, int side, const char* name, GatDims dm, int el_hm,
                                          const float* feat, const float* rowfeat, const float* el, const float* er,
                                          const float* m, const float* d, const float4* vstate, float* acc,
@@ -1037,23 +1159,21 @@ static gnn_status_t launch_resident_addr(const gnn_graph_t* g, int side, const c
   constexpr int SL = 16;
   const int ns = dm.HF <= 4 * SL ? 1 : dm.HF / (4 * SL);
   const int sph = ns / dm.H;
-  const size_t lds = sizeof(int) * (size_t)kGatResLdsInts<SL, MODE>;
-  static_assert(sizeof(int) * (size_t)kGatResLdsInts<SL, MODE> <= 160 * 1024, "the slots must fit the LDS of a CU");
+  const int nslot = gat_res_slots<SL, MODE, NA>(TAB ? g->block_cols : 0);
   static std::atomic<bool> attr_set{false};
   if (!attr_set.load(std::memory_order_acquire)) {
-    GNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gat_res<SL, MODE, SKIP, HALF, NARROW>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    GNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gat_res<SL, MODE, NA, TAB, SKIP, HALF, NARROW>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kGatResLdsBytes));
     attr_set.store(true, std::memory_order_release);
   }
-  // one workgroup per CU, a multiple of 8 so that every XCD serves one slice
-  const unsigned grid = (unsigned)(device_cu_count() / kXcds * kXcds);
+  const unsigned grid = gat_resident_grid();
   ProfScope p(name, st);
   k_gat_zero_clock<<<1, kXcds * kClockStride, 0, st>>>(g->phase_clock);
   GNN_LAUNCH_CHECK();
-  k_gat_res<SL, MODE, SKIP, HALF, NARROW><<<grid, kGatResThreads, lds, st>>>(
+  k_gat_res<SL, MODE, NA, TAB, SKIP, HALF, NARROW><<<grid, kGatResThreads, kGatResLdsBytes, st>>>(
       g->n, g->order[side], reinterpret_cast<const int2*>(g->bseg[side]), g->bcol[side], feat, rowfeat, el, er, m, d,
       vstate, dm, sph, el_hm, g->block_cols, g->nblk, ns, acc, acc2, scal, m_out, d_out, g->phase_clock,
-      (int)config_get(kCfgResidentSpin), (int)config_get(kCfgResidentSyncEvery), alpha_b, g->nnz);
+      (int)config_get(kCfgResidentSpin), (int)config_get(kCfgResidentSyncEvery), alpha_b, g->nnz, nslot);
   GNN_LAUNCH_CHECK();
   return GNN_OK;
 }
@@ -1063,16 +1183,16 @@ static bool gat_resident_narrow(const gnn_graph_t* g, GatDims dm) {
   return (int64_t)g->n * dm.HF * 4 < ((int64_t)1 << 32) && g->n < (1 << 24) && !config_get(kCfgWideOffsets);
 }
 
-template <int MODE, bool SKIP, bool HALF>
+template <int MODE, int NA, bool TAB, bool SKIP, bool HALF>
 static gnn_status_t launch_resident_impl(const gnn_graph_t* g, int side, const char* name, GatDims dm, int el_hm,
                                          const float* feat, const float* rowfeat, const float* el, const float* er,
                                          const float* m, const float* d, const float4* vstate, float* acc,
                                          float* acc2, float* scal, float* m_out, float* d_out, hipStream_t st,
                                          const float* alpha_b) {
   if (gat_resident_narrow(g, dm))
-    return launch_resident_addr<MODE, SKIP, HALF, true>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate,
+    return launch_resident_addr<MODE, NA, TAB, SKIP, HALF, true>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate,
                                                         acc, acc2, scal, m_out, d_out, st, alpha_b);
-  return launch_resident_addr<MODE, SKIP, HALF, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate,
+  return launch_resident_addr<MODE, NA, TAB, SKIP, HALF, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate,
                                                        acc, acc2, scal, m_out, d_out, st, alpha_b);
 }
 
@@ -1083,17 +1203,25 @@ static gnn_status_t launch_resident(const gnn_graph_t* g, int side, const char* 
                                     float* scal, float* m_out, float* d_out, hipStream_t st, const float* alpha_b,
                                     bool half_feat) {
   if (half_feat) {
-    if constexpr (MODE != 1)
-      return launch_resident_impl<MODE, true, true>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc,
-                                                    acc2, scal, m_out, d_out, st, alpha_b);
+    if constexpr (MODE != 1) {
+#define GNN_GAT_HALF(NA_, TAB_)                                                                                             \
+  return launch_resident_impl<MODE, NA_, TAB_, true, true>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, \
+                                                           acc2, scal, m_out, d_out, st, alpha_b)
+      if constexpr (MODE == 0) {
+        if (gat_resident_table(g, dm)) GNN_GAT_HALF(2, true);
+      }
+      if (gat_resident_pairs(g, side, dm)) GNN_GAT_HALF(2, false);
+      GNN_GAT_HALF(1, false);
+#undef GNN_GAT_HALF
+    }
   }
   // gathers past a segment's end are skipped on rows of four and more slices; on narrower rows the
   // source side gains from it as well (6.48 -> 6.14 ms for the two layers of a 128 / 44-wide model at
   // Reddit scale), the forward modes lose a little (5.87 -> 5.96 ms)
   if (dm.HF / 64 >= 4 || MODE == 2)
-    return launch_resident_impl<MODE, true, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, acc2,
+    return launch_resident_impl<MODE, 1, false, true, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, acc2,
                                             scal, m_out, d_out, st, alpha_b);
-  return launch_resident_impl<MODE, false, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, acc2,
+  return launch_resident_impl<MODE, 1, false, false, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, acc2,
                                            scal, m_out, d_out, st, alpha_b);
 }
 
@@ -1254,9 +1382,12 @@ extern "C" gnn_status_t gnn_gat_blocked_kernel_name(const gnn_graph_t* g, int he
   Slicing sl;
   if (!pick_slicing(heads, heads * f, sl)) return GNN_OK;
   if (gat_resident_applies(g, make_dims(heads, f, 0.2f))) {
-    std::snprintf(buf, len, "k_gat_res<16, %d, %s, %s, %s>", mode,
+    const GatDims dm = make_dims(heads, f, 0.2f);
+    std::snprintf(buf, len, "k_gat_res<16, %d, %d, %s, %s, %s, %s>", mode,
+                  half && gat_resident_pairs(g, mode == 2, dm) ? 2 : 1,
+                  half && mode == 0 && gat_resident_table(g, dm) ? "true" : "false",
                   (half || heads * f / 64 >= 4 || mode == 2) ? "true" : "false", half ? "true" : "false",
-                  gat_resident_narrow(g, make_dims(heads, f, 0.2f)) ? "true" : "false");
+                  gat_resident_narrow(g, dm) ? "true" : "false");
     return GNN_OK;
   }
   const int SL = half ? 8 : sl.SL;

@@ -613,6 +613,56 @@ def test_fp16_gather_storage(H, F, resident):
     assert not np.array_equal(res16["gx"], ref32["gx"])
 
 
+@pytest.mark.parametrize("H,F,n,block_cols,table", [(4, 64, 9000, 256, True), (4, 64, 9000, 5000, True),
+                                                    (1, 128, 18000, 12288, True), (1, 128, 18000, 13000, False)])
+def test_fp16_gather_of_two_float4_a_lane(H, F, n, block_cols, table):
+    """Graphs without long rows: a lane takes 16 bytes of an fp16 row, and the forward pass reads the block's scores from LDS
+    (a block of more than 12288 vertices: from memory).  Segments of no, few and more than 16 edges.  What differs from fp32
+    is the rounding of the gathered rows, so the sums are compared with those of the rounded rows at the fp32 tolerance."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import assert_close, dev, empty, gat_kink_masks, run_gat, workspace
+    from oracle.segments import segment_sum
+    print(f"gat: fp16 rows in pairs H={H} F={F} n={n} block_cols={block_cols}", flush=True)
+    rng = np.random.default_rng(n + block_cols)
+    indptr, indices = random_graph(rng, n, 32 * n, self_loops=False, duplicates=True)
+    c = synth(rng, indptr, indices, 16, H, F)
+    pk.gnn_config_set("block_cols", block_cols)
+    try:
+        g = pk.Graph(dev(indptr), dev(indices))
+        pk.gnn_config_set("gather_precision", 1)
+        names = [pk.gnn_gat_blocked_kernel_name(g, H, F, mode) for mode in (0, 2, 3)]
+        infer, train = run_gat(c, backward=False, graph=g, stash=False), run_gat(c, backward=False, graph=g)
+        ws = workspace(pk.gnn_gat_workspace_bytes(g, 16, H, F))
+        pk.gnn_config_set("gather_precision", 0)
+        # the backward pass after a forward pass in fp32: only the rounding of gout is left
+        x, w, a_l, a_r = (dev(c[k]) for k in ("x", "w", "a_l", "a_r"))
+        z, out, t, sg = empty((n, H * F)), empty((n, H * F)), empty((n, H * F)), empty((n, H))
+        el, er, m, d = (empty((n, H)) for _ in range(4))
+        gx, gw, ga_l, ga_r = empty((n, 16)), empty((16, H * F)), empty((H, F)), empty((H, F))
+        pk.gnn_gat_fwd(g, 16, H, F, c["slope"], x, w, a_l, a_r, z, el, er, m, d, out, t, sg, ws)
+        pk.gnn_config_set("gather_precision", 1)
+        pk.gnn_gat_bwd(g, 16, H, F, c["slope"], x, w, a_l, a_r, z, el, er, m, d, out, t, sg, dev(c["gout"]), gx, gw, ga_l,
+                       ga_r, ws)
+        gx = gx.cpu().numpy()
+        g.close()
+    finally:
+        pk.gnn_config_set("gather_precision", 0)
+        pk.gnn_config_set("block_cols", 12288)
+    assert names[0].startswith(f"k_gat_res<16, 0, 2, {'true' if table else 'false'},"), names
+    assert names[1].startswith("k_gat_res<16, 2, 2, false,") and names[2].startswith("k_gat_res<16, 3, 2, false,"), names
+    c["gout"] = c["gout"].astype(np.float16).astype(np.float32)
+    fwd, bwd = oracle_all(c)
+    amb_vh, amb_vertex = gat_kink_masks(indptr, fwd)
+    rows = train["z"].astype(np.float16).astype(np.float64).reshape(n, H, F)[fwd["src"]]
+    ref = segment_sum(indptr, fwd["M2"][:, :, None] * rows).reshape(n, H * F)
+    assert_close("out, with stash", train["out"], ref)
+    assert_close("out", infer["out"], ref)
+    ag = fwd["M2"] * np.where(fwd["M0"] > 0, 1.0, c["slope"])
+    ref = segment_sum(indptr, ag[:, :, None] * rows).reshape(n, H * F)
+    assert_close("t", np.where(np.repeat(~amb_vh, F, axis=1), train["t"], ref), ref)
+    assert_close("gx", np.where(amb_vertex[:, None], bwd["gx"], gx), bwd["gx"])
+
+
 def test_fp16_gather_storage_leaves_uncovered_shapes_in_fp32():
     import paper_2110_09524_amd as pk
     from gpu_harness import dev, run_gat
