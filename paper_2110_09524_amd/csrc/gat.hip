@@ -747,7 +747,7 @@ static GatWs gat_ws_layout(const gnn_graph_t* g, int fin, int H, int F) {
   w.blk_scal = take(blocked ? sizeof(float) * n * 8 : 0);   // sg, then the slices' shares of del
   w.blk_elt = take(blocked ? sizeof(float) * n * H : 0);    // head-major el
   w.blk_queue = take(blocked ? sizeof(int32_t) * 8 * (size_t)g->nblk : 0);  // row counters of the staged kernels
-  // a narrow projection of a mid-sized graph has too few output tiles to fill the chip: split K
+  // a projection of a mid-sized graph has too few output tiles to fill the chip: split K (room for it also where one launch does it)
   w.fwd_split_k = gemm_pick_split_k(n, HF, fin);
   w.fwd_gemm = take(w.fwd_split_k > 1 ? sizeof(float) * (size_t)w.fwd_split_k * n * HF : 0);
   w.blk_half = take(gat_blocked_half(g, H, F) ? 2 * (size_t)n * HF : 0);  // fp16 copy of the gathered rows
@@ -1153,7 +1153,7 @@ extern "C" gnn_status_t gnn_gat_fwd(const gnn_graph_t* g, int fin, int heads, in
   const GatWs L = gat_ws_layout(g, fin, heads, f);
   const bool have_ws = ws != nullptr && ws_bytes >= L.total && aligned16(ws);
   bool halves_done = false;
-  if (have_ws && L.fwd_split_k > 1) {
+  if (have_ws && L.fwd_split_k > 1 && !gemm_has_few_tiles(n, HF, fin)) {
     GNN_TRY(gemm_f32(n, HF, fin, x, fin, false, w, HF, false, z, HF, L.fwd_split_k,
                      reinterpret_cast<float*>(static_cast<char*>(ws) + L.fwd_gemm), st));
   } else if (gemm_attn_epilogue_ok(heads, f) && fin < (1 << 24)) {

@@ -568,6 +568,203 @@ __global__ __launch_bounds__(64 * WR * WC, (kMinWaves<BM, BN, A_KMAJOR>)) void k
   }
 }
 
+// ---- products with few tiles ---------------------------------------------------------------------
+// Where a tile of k_gemm_f32 to a workgroup leaves the chip half empty, its slabs one after the other are what the product takes.  Here a
+// workgroup has a tile of 32 rows and deals the slabs out to its wavefronts, W runs of them.  A run's operands, 8 consecutive k
+// of a row or column to a lane, come straight from memory into the MFMA's layout and are split there: no LDS and no barrier before the
+// end, where the W sums meet in LDS, in the order of k.
+struct Parts {
+  bf16x8 v[kParts];
+};
+// scale * raw = h + m + l in bf16
+__device__ __forceinline__ Parts split_octet(const float (&raw)[8], float scale) {
+  uint32_t w[kParts][4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    float a = scale * raw[2 * q], b = scale * raw[2 * q + 1];
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) {
+      w[p][q] = pack_bf16(a, b);
+      if (p + 1 < kParts) {
+        a -= __uint_as_float(w[p][q] << 16);
+        b -= __uint_as_float(w[p][q] & 0xffff0000u);
+      }
+    }
+  }
+  Parts r;
+#pragma unroll
+  for (int p = 0; p < kParts; ++p) r.v[p] = __builtin_bit_cast(bf16x8, make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]));
+  return r;
+}
+
+template <int TN, int W, bool BKC, bool EPI>
+__global__ __launch_bounds__(64 * W) void k_gemm_few(int64_t M, int N, int K, const float* __restrict__ A, int64_t lda,
+                                                     const float* __restrict__ B, int64_t ldb, float* __restrict__ C,
+                                                     int64_t ldc, int tiles_m, AttnEpilogue epi) {
+  static_assert(W == 4 || W == 8, "a wavefront closes 16 / W registers of the tile");
+  constexpr int R = 16 / W;
+  __shared__ float l_sum[W][TN][16][64];
+  const int lane = threadIdx.x & 63, lrow = lane & 31, lk = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t m0 = (int64_t)(blockIdx.x % tiles_m) * 32;
+  const int n0 = (int)(blockIdx.x / tiles_m) * 32 * TN;
+  const int64_t row = m0 + lrow < M ? m0 + lrow : M - 1;  // past the matrix: its last row, for nothing
+  int col[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) col[j] = min(n0 + 32 * j + lrow, N - 1);
+
+  typedef float vec4 __attribute__((ext_vector_type(4), aligned(4)));
+  const float* pa = A + row * lda + 8 * lk;
+  auto load8 = [&](float (&raw)[8], const float* p, int k) {  // p: this lane's k of slab k / BK
+    if (k + BK <= K) {
+      const vec4 lo = *reinterpret_cast<const vec4*>(p), hi = *reinterpret_cast<const vec4*>(p + 4);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) raw[q] = lo[q], raw[4 + q] = hi[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) raw[q] = k + 8 * lk + q < K ? p[q] : 0.f;
+    }
+  };
+  float ra[2][8], rb[2][TN][8];
+  auto load = [&](auto slot, int s) {
+    constexpr int S = decltype(slot)::value;
+    const int k = BK * s;
+    load8(ra[S], pa + k, k);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      if constexpr (BKC) {
+        load8(rb[S][j], B + col[j] * ldb + k + 8 * lk, k);
+      } else {
+        const float* p = B + (int64_t)(k + 8 * lk) * ldb + col[j];
+        if (k + BK <= K) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) rb[S][j][q] = p[q * ldb];
+        } else {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) rb[S][j][q] = k + 8 * lk + q < K ? p[q * ldb] : 0.f;
+        }
+      }
+    }
+  };
+  floatx16 part[2][TN];  // even and odd slabs, as in k_gemm_f32
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) part[h][j][r] = 0.f;
+  const int slabs = (K + BK - 1) / BK, per = (slabs + W - 1) / W;
+  const int s0 = min(w * per, slabs), s1 = min(s0 + per, slabs);
+  auto step = [&](auto slot, int s) {
+    constexpr int S = decltype(slot)::value;
+    constexpr int ia[6] = {1, 2, 0, 0, 1, 0}, ib[6] = {1, 0, 2, 1, 0, 0};  // smallest products first
+    const Parts a = split_octet(ra[S], S ? -kScale : kScale);
+    Parts b[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) b[j] = split_octet(rb[S][j], kScale);
+    if (s + 2 < s1) load(slot, s + 2);
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        part[S][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v[ia[q]], b[j].v[ib[q]], part[S][j], 0, 0, 0);
+  };
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
+  if (s0 < s1) load(even, s0);
+  if (s0 + 1 < s1) load(odd, s0 + 1);
+  for (int s = s0; s < s1; s += 2) {
+    step(even, s);
+    if (s + 1 < s1) step(odd, s + 1);
+  }
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) l_sum[w][j][r][lane] = part[0][j][r] - part[1][j][r];
+  __syncthreads();
+
+  // wavefront w closes registers R w .. of the tile, which hold rows 8 (r / 4) + 4 lk + r % 4
+  float acc[TN][R];
+  float zero = 0.f;  // stays so as long as everything is finite
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      float sum = l_sum[0][j][R * w + i][lane];
+#pragma unroll
+      for (int q = 1; q < W; ++q) sum += l_sum[q][j][R * w + i][lane];
+      acc[j][i] = sum * (1.f / (kScale * kScale));
+      zero = __builtin_fmaf(acc[j][i], 0.f, zero);
+    }
+  if (__any(zero != 0.f)) {  // what is not finite, as the fp32 chain gives it
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      floatx16 chain;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) chain[r] = 0.f;
+      for (int k0 = 0; k0 < K; k0 += 2) {
+        const int k = k0 + lk;
+        const float a = k < K ? A[row * lda + k] : 0.f;
+        const float b = k < K ? B[BKC ? col[j] * ldb + k : k * ldb + col[j]] : 0.f;
+        chain = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, chain, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (r / R == w && !(fabsf(acc[j][r % R]) <= 3.402823466e38f)) acc[j][r % R] = chain[r];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int r = R * w + i, n = n0 + 32 * j + lrow;
+      const int64_t m = m0 + (r >> 2) * 8 + lk * 4 + (r & 3);
+      if (m < M && n < N) C[m * ldc + n] = acc[j][i];
+    }
+  if constexpr (EPI) {  // el, er as in k_gemm_f32; the wavefront has all columns of its rows
+    const int F = epi.F, H = epi.H;
+    const bool whole = F > 32 || H == 1;  // all of the tile's columns belong to one head
+    const int seg = whole ? 32 : F;
+    float wl[TN], wr[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int n = n0 + 32 * j + lrow;
+      wl[j] = n < N ? epi.a_l[n] : 0.f;
+      wr[j] = n < N ? epi.a_r[n] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int r = R * w + i;
+      const int64_t m = m0 + (r >> 2) * 8 + lk * 4 + (r & 3);
+      float vl[TN], vr[TN];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const bool in = n0 + 32 * j + lrow < N;  // columns past N hold products of a clamped one
+        vl[j] = in ? wl[j] * acc[j][i] : 0.f;
+        vr[j] = in ? wr[j] * acc[j][i] : 0.f;
+      }
+      if (whole) {
+#pragma unroll
+        for (int j = 1; j < TN; ++j) {
+          vl[0] += vl[j];
+          vr[0] += vr[j];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < (whole ? 1 : TN); ++j) {
+        const float sl = segment_sum(vl[j], seg), sr = segment_sum(vr[j], seg);
+        const int n = n0 + 32 * j + lrow;
+        if ((lrow & (seg - 1)) == 0 && n < N && m < M) {
+          const int h = H == 1 ? 0 : n / F;
+          epi.el[m * H + h] = sl;
+          epi.er[m * H + h] = sr;
+        }
+      }
+    }
+  }
+}
+
+
 // c = a b, a [M,K], b [K,N], every element fma(a[k], b[k], ...) over ascending k: the fp32 MFMA adds its two products one
 // after the other, each with one rounding.  The MFMAs (64 cycles each) are busy 60 % of the time; while one wavefront issues a slab's
 // worth of them, the vector instructions of the others on its SIMD wait, so the loop keeps those few: uniform addresses,
@@ -884,6 +1081,42 @@ static gnn_status_t launch_tile(int64_t M, int N, int64_t K, const float* a, int
 #undef GNN_GEMM_TILE
 }
 
+template <int TN, int W, bool BKC, bool EPI>
+static gnn_status_t launch_few_tile(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
+                                    float* c, int64_t ldc, const AttnEpilogue& epi, hipStream_t s) {
+  const int64_t tm = cdiv(M, 32), tn = cdiv(N, 32 * TN);
+  ProfScope p(EPI ? "gemm_f32_mfma_attn" : "gemm_f32_mfma", s);
+  k_gemm_few<TN, W, BKC, EPI><<<(unsigned)(tm * tn), 64 * W, 0, s>>>(M, N, (int)K, a, lda, b, ldb, c, ldc, (int)tm, epi);
+  GNN_LAUNCH_CHECK();
+  return GNN_OK;
+}
+
+// Up to two tiles of 32 x 64 to a CU; below one, twice as many wavefronts to a tile, and tiles half as wide where those are
+// no more than the CUs.  x w, us, k_gemm_f32 -> here: 2000 x 500 x 64 15.4 -> 6.4, 8000 17.5 -> 10.4, 16384 (512 tiles) 19.3 -> 18.0, 20000
+// (625) 22.6 against 24.8; 2000 x 602 x 256 25.3 -> 11.7, 5000 (628) 27.3 against 28.2; 8000 x 256 x 32 10.6 -> 5.4; 16384 x 64 x 64
+// 6.2 -> 5.6, 32768 7.5 against 9.3.  Its sums are shorter: error against 64 bits, 2-norm, 1000 x 65 x 33 8.2e-8 -> 5.6e-8,
+// 5000 x 602 x 32 2.6e-7 -> 1.0e-7.
+constexpr int kFewTilesPerCu = 2;
+bool gemm_has_few_tiles(int64_t M, int N, int64_t K) {
+  return K > kShallowK && K < (1 << 24) && cdiv(M, 32) * cdiv(N, 64) <= (int64_t)kFewTilesPerCu * device_cu_count();
+}
+
+template <bool BKC, bool EPI>
+static gnn_status_t launch_few(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
+                               float* c, int64_t ldc, const AttnEpilogue& epi, hipStream_t s) {
+  const int64_t tm = cdiv(M, 32), cus = device_cu_count();
+  // attention halves: all columns of a head are one wavefront's
+  const bool wide = EPI && N > 32 && (epi.H == 1 || epi.F == 64);
+  const int tn = N <= 32 || (!wide && tm * cdiv(N, 32) <= cus) ? 1 : 2;
+  const bool many = tm * cdiv(N, 32 * tn) <= cus && K > 6 * BK;
+#define GNN_FEW(TN_, W_) return launch_few_tile<TN_, W_, BKC, EPI>(M, N, K, a, lda, b, ldb, c, ldc, epi, s)
+  if (tn == 1 && many) GNN_FEW(1, 8);
+  if (tn == 1) GNN_FEW(1, 4);
+  if (many) GNN_FEW(2, 8);
+  GNN_FEW(2, 4);
+#undef GNN_FEW
+}
+
 template <int BM, int BN, int VB>
 static gnn_status_t launch_chain_tile(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
                                       float* c, int64_t ldc, hipStream_t s) {
@@ -930,6 +1163,9 @@ gnn_status_t gemm_f32(int64_t M, int N, int64_t K, const float* a, int64_t lda, 
               "gemm_f32: split-K needs a dense output (ldc == N)");
   const AttnEpilogue none{nullptr, nullptr, nullptr, nullptr, 0, 0};
   const bool shallow = K <= kShallowK && split_k == 1;
+  if (!a_kmajor && split_k == 1 && gemm_has_few_tiles(M, N, K))
+    return b_kcontig ? launch_few<true, false>(M, N, K, a, lda, b, ldb, c, ldc, none, s)
+                     : launch_few<false, false>(M, N, K, a, lda, b, ldb, c, ldc, none, s);
 #define GNN_GEMM_RUN(...) \
   GNN_TRY((launch_tile<__VA_ARGS__>(M, N, K, a, lda, b, ldb, c, ldc, split_k, partials, none, s)))
   if (a_kmajor) {
@@ -976,6 +1212,7 @@ gnn_status_t gemm_f32_attn(int64_t M, int heads, int f, int64_t K, const float* 
   GNN_REQUIRE(K > 0 && K < (1 << 24) && N < (1 << 24) && cdiv(M, 32) < (int64_t)INT32_MAX, GNN_ERR_UNSUPPORTED,
               "gemm_f32_attn: sizes out of range");
   const AttnEpilogue epi{a_l, a_r, el, er, heads, f};
+  if (gemm_has_few_tiles(M, N, K) && (heads > 1 || N <= 64)) return launch_few<false, true>(M, N, K, x, K, w, N, z, N, epi, s);
   if (K <= kShallowK) return launch_tile<false, false, true, kShallow>(M, N, K, x, K, w, N, z, N, 1, nullptr, epi, s);
   return launch_tile<false, false, true, kLoop>(M, N, K, x, K, w, N, z, N, 1, nullptr, epi, s);
 }

@@ -61,6 +61,34 @@ def test_products_of_every_layout_and_tile(n, fin, fout):
     _assert_within_rounding("x^T g", gw.cpu().numpy(), np.ascontiguousarray(x.T), gout, max(1, min(n // 128, 512)))
 
 
+@pytest.mark.parametrize("n,fin,fout", [(1, 33, 1), (8192, 97, 32), (8192, 96, 33), (8193, 113, 32), (8192, 97, 64), (8224, 97, 64),
+                                        (16384, 34, 64), (16384, 47, 61), (16416, 34, 64), (33, 640, 8), (4064, 200, 128)])
+def test_products_of_few_tiles(n, fin, fout):
+    """Tiles of 32 rows with the slabs of 16 k dealt out to 4 or 8 wavefronts: one and two tiles to a CU and the first product
+    beyond, runs of slabs that are uneven or empty, a last slab of 1 to 15; x w and g w^T."""
+    import paper_2110_09524_amd as pk
+    import torch
+    from gpu_harness import dev, empty
+    print(f"few tiles: {n} x {fin} x {fout}", flush=True)
+    rng = np.random.default_rng(n + fin)
+    x, w, gout = (rng.standard_normal(s).astype(np.float32) for s in ((n, fin), (fin, fout), (n, fin)))
+    y = torch.full((n + 1, fout), 7.0, device="cuda")
+    pk.gnn_linear_fwd(dev(x), dev(w), y[:n])
+    torch.cuda.synchronize()
+    assert (y[n] == 7).all()        # nothing past the last row
+    _assert_within_rounding("x w", y[:n].cpu().numpy(), x, w, 8)
+    # gx = gout v^T of a layer fout -> fin
+    g = pk.Graph(dev(np.arange(n + 1, dtype=np.int32)), dev(np.arange(n, dtype=np.int32)))
+    v = np.ascontiguousarray(w.T)
+    gx, gw = empty((n, fout)), empty((fout, fin))
+    ws = torch.empty(max(pk.gnn_gcn_workspace_bytes(g, fout, fin), 16), dtype=torch.uint8, device="cuda")
+    if fin % 4 == 0:
+        pk.gnn_gcn_bwd(g, fout, fin, dev(np.zeros((n, fout), np.float32)), dev(v), dev(np.ones(n, np.float32)),
+                       dev(np.ones(n, np.float32)), dev(gout), gx, gw, ws)
+        torch.cuda.synchronize()
+        _assert_within_rounding("g w^T", gx.cpu().numpy(), gout, w, 8)
+
+
 def test_as_many_rows_as_vertices_can_have():
     """2^31 - 100 rows: their 128-row tiles have 2^32 threads, more than one launch may."""
     import paper_2110_09524_amd as pk
