@@ -165,7 +165,10 @@ gnn_status_t gnn_release_cached_memory(void);
  *                           serves cache residency); layer calls on ONE graph that overlap in
  *                           time share those counters: their results stay right, their cache
  *                           hit rates suffer.  0: one launch per block or group of blocks.
- *                           Both give the same bits as one launch per block.
+ *                           Both give the same bits as one launch per block.  gnn_monet_fwd has
+ *                           such a launch, too, which it takes where a rule on the graph finds it
+ *                           faster, with 2 on every graph with column blocks, and with 0 never;
+ *                           its sums are grouped by block, so they round differently.
  *   "resident_spin"         polls after which a workgroup of that launch stops waiting for the
  *                           others of its XCD (default 4096; 0 = never wait; meant for tests)
  *   "resident_sync_every"   the workgroups of an XCD meet after every k-th column block instead

@@ -20,6 +20,7 @@
 // over the in-edges of its own.
 // At most 4 kernels and 4 pseudo-coordinate dimensions; fout <= 256.
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "common.h"
@@ -454,6 +455,259 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_fwd_nr(
   }
   if (li < F4) st4(out + (int64_t)v * F + 4 * li, tot);
 }
+
+__global__ void k_monet_zero_clock(int32_t* __restrict__ p) { p[threadIdx.x] = 0; }
+
+// ---- forward past the L2s: all column blocks in one persistent launch, the sums in LDS ----------------
+// k_gmmp_fwd_nr gathers a row of hk and a scalar per edge from anywhere, and the rows that miss the L2s come at the rate of the fabric
+// behind them.  Here one 1024-thread workgroup to a CU keeps the sums of its rows in LDS, F floats each, and takes all of them through
+// the plan's column blocks one after the other; the block's rows of hk are in the L2 then, and its scalars in LDS: one line to an edge.
+// Rows are dealt to the workgroups one position of the degree order at a time, in alternating direction, and inside a workgroup
+// the groups draw them from a counter, longest first.  A row with more than its share of edges would be what a workgroup waits for
+// in every block, so it is cut into 2, 4, ... parts, drawn like rows; the parts' sums are added in order at the end.
+// Bound by the instructions of the vector units, some 150 to a wavefront's 64 edges with tanhf a third of them, and by segments that
+// are shorter than a chunk.  MoNet forward, us, k_gmmp_fwd_nr -> here: 232 965 vertices, 1.12 10^8 edges, K = 2, 16 columns
+// 1410 -> 970 (a branch to each gather instead of the buffer loads: 1000; workgroups that meet after every block 1015, every
+// fourth 975); 2 x 32, R = 2 2380 -> 1200; 100 000 vertices, 3 10^7 edges, K = 3 410 -> 250; uniform, 230 000 x 320, K = 2 973 -> 639,
+// 100 000 x 200, K = 3 360 -> 290.
+constexpr int kMonetThreads = 1024;
+constexpr int kMonetTabPerThread = 12;
+constexpr int kMonetLevels = 6;
+// the first rows[i] rows of a workgroup, in the order of their degrees, are cut into at least 2^(i + 1) parts
+struct MonetParts {
+  int rows[kMonetLevels];
+};
+constexpr uint32_t kPastTable = 0xFFFFF000u;  // 4 KB below the end of 32 bits
+template <int G, int KT>
+constexpr int kMonetGroupInts = (kMonetThreads / G) * (1 + KT) * G;  // idx, weights of all groups
+// a slot: sum, (beg, end) of two blocks, row, c of the row
+constexpr int monet_slot_ints(int F) { return F + 4 + 1 + 1; }
+
+template <int G, int KT, int RT>
+__global__ __launch_bounds__(kMonetThreads) void k_monet_res(
+    int32_t n_rows, const int32_t* __restrict__ order, const int2* __restrict__ bseg /* [nblk][n_rows] */,
+    const int32_t* __restrict__ bcol, const float* __restrict__ hk, ProjArgs pa, const float* __restrict__ mu,
+    const float* __restrict__ inv_sigma, PsParams pm, int32_t block_cols, int nblk, int cap /* slots the LDS holds */,
+    MonetParts cut, int32_t* __restrict__ clock, int spin_limit, int sync_every, float* __restrict__ out) {
+  constexpr int GPB = kMonetThreads / G, U = 8;
+  extern __shared__ __align__(16) int lds_mr[];
+  const int lane = threadIdx.x & 63, li = threadIdx.x & (G - 1), grp = threadIdx.x / G;
+  const int64_t nwg = gridDim.x, wg = blockIdx.x;
+  const int K = pm.K, R = pm.R, F = pm.F, KF = K * F, F4 = F / 4;
+  const float inv_k = 1.f / (float)K;
+  const PsKernels<KT, RT> pk = load_kernels<KT, RT>(mu, inv_sigma, K, R);
+  const ProjRegs<RT> pq = load_proj<RT>(pa, R);
+  // a lane's columns; lanes past the row's end take its first ones again, for nothing
+  const bool col_ok = li < K * F4;
+  const int myk = col_ok ? li / F4 : 0;
+  const uint32_t lane_off = col_ok ? 16u * li : 0u;
+  // Rows come through a buffer resource: the offset kPastTable, of edges past the segment's end, reads zeros and no memory, so
+  // a chunk's loads are issued without a branch to each.
+  const auto table = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(hk), 0, (uint32_t)((int64_t)n_rows * KF * 4), 0x00020000);
+  float4* l_sum = reinterpret_cast<float4*>(lds_mr);        // [cap][F4]
+  uint32_t* l_off = reinterpret_cast<uint32_t*>(lds_mr + cap * F + grp * (1 + KT) * G);  // [G], weights [KT][G]
+  float* l_w = reinterpret_cast<float*>(l_off + G);
+  int2* l_seg = reinterpret_cast<int2*>(lds_mr + cap * F + kMonetGroupInts<G, KT>);  // [2][cap]
+  int* l_row = reinterpret_cast<int*>(l_seg + 2 * cap);     // [cap]
+  float* l_cv = reinterpret_cast<float*>(l_row + cap);      // [cap]
+  int* l_cnt = reinterpret_cast<int*>(l_cv + cap);          // [2]
+  float* l_tab = reinterpret_cast<float*>(l_cnt + 2);       // [block_cols]
+
+  float tab[kMonetTabPerThread] = {};
+  auto fetch_table = [&](int p) {
+#pragma unroll
+    for (int i = 0; i < kMonetTabPerThread; ++i) {
+      const int c = i * kMonetThreads + threadIdx.x;
+      const int64_t u = (int64_t)p * block_cols + c;
+      if (c < block_cols && u < n_rows) tab[i] = pa.c[u];
+    }
+  };
+  auto store_table = [&]() {
+#pragma unroll
+    for (int i = 0; i < kMonetTabPerThread; ++i) {
+      const int c = i * kMonetThreads + threadIdx.x;
+      if (c < block_cols) l_tab[c] = tab[i];
+    }
+  };
+  fetch_table(0);
+  store_table();
+
+  // parts of the workgroup's j-th row, as a power of two; slots before it
+  auto log_parts = [&](int j) {
+    int l = 0;
+#pragma unroll
+    for (int i = 0; i < kMonetLevels; ++i) l += j < cut.rows[i] ? 1 : 0;
+    return l;
+  };
+  auto slots_before = [&](int j) {
+    int s = j;
+#pragma unroll
+    for (int i = 0; i < kMonetLevels; ++i) s += min(j, cut.rows[i]) << i;  // level i doubles: 2^i more slots
+    return s;
+  };
+  const int rows_here = (int)((n_rows + nwg - 1) / nwg);
+  // workgroups go to the XCDs round-robin: those with the same id mod 8 share an L2
+  PhaseClock pc{clock ? clock + (blockIdx.x % kXcds) * kClockStride : nullptr, (int)(gridDim.x / kXcds), spin_limit,
+                false, sync_every > 0 ? sync_every : nblk};
+  struct Item {
+    int32_t beg, end, c_first;
+  };
+
+  int phase = 0;
+  for (int j0 = 0, j1; j0 < rows_here; j0 = j1) {
+    // rows j0 .. j1 - 1: as many as there are slots for (a row has at most 2^kMonetLevels)
+    const int s0 = slots_before(j0);
+    j1 = j0;
+    for (int step = 1 << 30; step > 0; step >>= 1)
+      if (step <= rows_here - j1 && slots_before(j1 + step) - s0 <= cap) j1 += step;
+    const int nslots = slots_before(j1) - s0;
+    // thread q: slot q
+    int64_t pos = -1;
+    int part = 0, logp = 0;
+    if ((int)threadIdx.x < nslots) {
+      int lo = j0, hi = j1;  // the last row that starts at or before this slot
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (slots_before(mid) - s0 <= (int)threadIdx.x) lo = mid; else hi = mid;
+      }
+      part = (int)threadIdx.x - (slots_before(lo) - s0);
+      logp = log_parts(lo);
+      const int64_t r = (int64_t)lo * nwg + ((lo & 1) ? nwg - 1 - wg : wg);
+      if (r < n_rows) pos = r;
+    }
+    auto bounds = [&](int p) {  // this thread's piece of its row's segment of block p
+      if (pos < 0) return make_int2(0, 0);
+      const int2 sg = bseg[(int64_t)p * n_rows + pos];
+      const int64_t len = sg.y - sg.x;
+      return make_int2(sg.x + (int)(len * part >> logp), sg.x + (int)(len * (part + 1) >> logp));
+    };
+    if ((int)threadIdx.x < nslots) {
+      const int32_t row = pos >= 0 ? order[pos] : -1;
+      l_row[threadIdx.x] = part == 0 ? row : -2;  // -2: a further part of the row before
+      l_cv[threadIdx.x] = row >= 0 ? pa.c[row] : 0.f;
+      l_seg[threadIdx.x] = bounds(0);
+    }
+    for (int i = threadIdx.x; i < nslots * F4; i += kMonetThreads) l_sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (threadIdx.x == 0) l_cnt[0] = 0;
+    __syncthreads();  // the tables are in place
+
+    auto grab = [&](int p) {  // a group's next slot of block p, from that block's counter
+      int q = 0;
+      if (li == 0) q = atomicAdd(l_cnt + (p & 1), 1);
+      return __shfl(q, lane & ~(G - 1), 64);
+    };
+    auto fetch = [&](int p, int q) {
+      Item it{0, 0, p * block_cols};
+      if (q >= nslots) return it;
+      const int2 sg = l_seg[(p & 1) * cap + q];
+      it.beg = sg.x;
+      it.end = sg.y;
+      if (it.beg + li < it.end) it.c_first = bcol[it.beg + li];
+      return it;
+    };
+    int q = grab(0);
+    Item cur = fetch(0, q);
+    for (int p = 0; p < nblk; ++p) {
+      const int32_t col_begin = p * block_cols;
+      const bool last = p + 1 == nblk;
+      // the next block's bounds and scalars travel while this one is worked on
+      int2 seg_next = make_int2(0, 0);
+      if (!last) seg_next = bounds(p + 1);
+      if (threadIdx.x == 0) l_cnt[(p + 1) & 1] = 0;
+      fetch_table(last ? 0 : p + 1);
+
+      while (q < nslots) {
+        const int qn = grab(p);
+        const Item nxt = fetch(p, qn);
+        if (cur.beg < cur.end) {
+          const float cv = l_cv[q];
+          float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), part4 = acc;
+          int folded = 0;
+          int32_t c_next = cur.c_first;
+          for (int32_t e0 = cur.beg; e0 < cur.end; e0 += G) {
+            const bool e_ok = e0 + li < cur.end;
+            const int32_t c = e_ok ? c_next : col_begin;
+            if (e0 + G + li < cur.end) c_next = bcol[e0 + G + li];
+            wave_lds_fence();  // the previous chunk's reads are done
+            l_off[li] = e_ok ? __umul24((uint32_t)c, 4u * KF) : kPastTable;
+            wave_lds_fence();
+            uint4 rowv[U];
+            auto rows_of = [&](int t0) {
+              uint32_t off[U];
+              read_run(l_off + t0, off);
+#pragma unroll
+              for (int t = 0; t < U; ++t)
+                rowv[t] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(table, off[t] + lane_off, 0, 0));
+            };
+            rows_of(0);
+            float m[RT];
+            project(pq, R, l_tab[c - col_begin], cv, m);
+#pragma unroll
+            for (int k = 0; k < KT; ++k) {
+              const float w = gauss_k(pk, k, m) * inv_k;
+              l_w[k * G + li] = e_ok ? w : 0.f;
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (int t0 = 0; t0 < G; t0 += U) {
+              if (t0 == 0 || e0 + t0 < cur.end) {
+                if (t0 > 0) rows_of(t0);
+                float wv[U];
+                read_run(l_w + myk * G + t0, wv);
+#pragma unroll
+                for (int t = 0; t < U; ++t)
+                  fma4(part4, wv[t], make_float4(__uint_as_float(rowv[t].x), __uint_as_float(rowv[t].y),
+                                                 __uint_as_float(rowv[t].z), __uint_as_float(rowv[t].w)));
+              }
+            }
+            folded += G;
+            if (folded >= 32) {  // two-level summation, as in k_gmmp_fwd_nr
+              add4(acc, part4);
+              part4 = make_float4(0.f, 0.f, 0.f, 0.f);
+              folded = 0;
+            }
+          }
+          add4(acc, part4);
+          // kernels 1 .. K-1 sit F/4 lanes further on: add them in order
+          float4 tot = acc;
+          const int base = lane & ~(G - 1);
+          for (int k = 1; k < K; ++k) {
+            const int srcl = base + ((li + k * F4) & (G - 1));
+            tot.x += __shfl(acc.x, srcl, 64);
+            tot.y += __shfl(acc.y, srcl, 64);
+            tot.z += __shfl(acc.z, srcl, 64);
+            tot.w += __shfl(acc.w, srcl, 64);
+          }
+          if (li < F4) {
+            add4(tot, l_sum[q * F4 + li]);
+            l_sum[q * F4 + li] = tot;
+          }
+        }
+        q = qn;
+        cur = nxt;
+      }
+      if ((int)threadIdx.x < nslots) l_seg[((p + 1) & 1) * cap + threadIdx.x] = seg_next;
+      __syncthreads();  // the workgroup is done with this block; the next one's bounds are in LDS
+      store_table();
+      if (!last) {      // first slot of the next block: its loads travel during the wait below
+        q = grab(p + 1);
+        cur = fetch(p + 1, q);
+      }
+      phase_step_done(pc, phase++);
+      __syncthreads();  // every workgroup of the XCD is done with this block (or the wait ran out)
+    }
+    // the rows' sums, parts added in order
+    for (int s = grp; s < nslots; s += GPB) {
+      const int32_t row = l_row[s];
+      if (row < 0 || li >= F4) continue;
+      float4 acc = l_sum[s * F4 + li];
+      for (int t = s + 1; t < nslots && l_row[t] == -2; ++t) add4(acc, l_sum[t * F4 + li]);
+      st4_stream(out + (int64_t)row * F + 4 * li, acc);
+    }
+    __syncthreads();  // the tables are free for the next rows
+  }
+}
+
 
 // destination side of backward, the coordinates' gradient alone (the walk below has the rest): the row phase leaves every
 // lane's part of <gout[v], hk[u, k, :]> in LDS, and the lane that owns the edge adds the F/4 parts of each kernel in
@@ -914,6 +1168,52 @@ static gnn_status_t with_rows_in_flight(const gnn_graph_t* g, int KF, Fn fn) {
   return fn(std::integral_constant<int, 1>{}, 0u);
 }
 
+// k_monet_res takes graphs with column blocks from so many edges on: below, its launch and its barriers per block are not repaid,
+// and where degrees are uneven they are sooner, since k_gmmp_fwd_nr then waits for the longest rows.  k_gmmp_fwd_nr | k_monet_res, K = 2,
+// 16 columns, us: uneven 13 000 vertices, 5 10^5 edges 25 | 30 (K = 4: 40 | 33), 20 000, 1.2 10^6 44 | 34, 13 000, 1.3 10^6 40 | 34, 14 000, 4.2 10^6
+// 125 | 67 (K = 3); even 30 000, 3 10^6 41 | 46, 50 000, 4.5 10^6 101 | 102 (3 x 20), 5 10^6 104 | 98 (K = 4), 20 000, 6 10^6 60 | 58 (8
+// columns), 25 000, 10^7 179 | 154 (3 x 20), 100 000, 1.5 10^7 169 | 159 (8).
+constexpr int64_t kMonetEdgesUneven = (int64_t)1 << 20, kMonetEdgesEven = (int64_t)5 << 20;
+constexpr int64_t kMonetEdgesPerBlock = 16;  // of a row, on average: fewer were not timed
+static bool monet_res_applies(const gnn_graph_t* g, int KF) {
+  const bool uneven = gathers_skewed(g, 0) || gathers_skewed(g, 1);
+  const bool enough = g->nnz >= (uneven ? kMonetEdgesUneven : kMonetEdgesEven) &&
+                      g->nnz >= kMonetEdgesPerBlock * (int64_t)g->n * g->nblk;
+  return (enough || config_get(kCfgResidentSums) == 2) && g->blocked_pays() && !config_get(kCfgForceSimple) && config_get(kCfgResidentSums) && g->phase_clock != nullptr &&
+         g->block_cols <= kMonetTabPerThread * kMonetThreads && g->n < (1 << 24) &&
+         (int64_t)sizeof(float) * KF * g->n <= (int64_t)kPastTable;
+}
+
+template <int G, int KT, int RT>
+static gnn_status_t launch_monet_res(const gnn_graph_t* g, const float* hk, const ProjArgs& pa, const float* mu,
+                                     const float* inv_sigma, const PsParams& pm, float* out, hipStream_t st) {
+  constexpr int kLds = 160 * 1024;
+  static std::atomic<bool> allowed{false};
+  if (!allowed.load(std::memory_order_acquire)) {
+    GNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_monet_res<G, KT, RT>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kLds));
+    allowed.store(true, std::memory_order_release);
+  }
+  const int64_t grid = device_cu_count() / kXcds * kXcds;
+  const int room = (kLds / 4 - 2 - (g->block_cols + 3) / 4 * 4 - kMonetGroupInts<G, KT>) / monet_slot_ints(pm.F);
+  const int cap = std::min(room, kMonetThreads) / 4 * 4;
+  // parts of more than half of what a group has on average, and at most twice that (a quarter as long: 970 -> 970 us, see above)
+  MonetParts cut{};
+  const int64_t share = std::max<int64_t>(64, g->nnz / (grid * (kMonetThreads / G)));
+  for (int i = 0; i < kMonetLevels; ++i) {
+    int k = 0;  // rows of at least 2^k edges are cut into 2^(i + 1): the first power of two above share 2^i
+    while (k < 31 && ((int64_t)1 << k) <= share << i) ++k;
+    cut.rows[i] = k >= 31 ? 0 : (int)cdiv(g->h_bucket_offsets[0][32 - k], grid);
+  }
+  k_monet_zero_clock<<<1, kXcds * kClockStride, 0, st>>>(g->phase_clock);
+  GNN_LAUNCH_CHECK();
+  k_monet_res<G, KT, RT><<<(unsigned)grid, kMonetThreads, kLds, st>>>(
+      g->n, g->order[0], reinterpret_cast<const int2*>(g->bseg[0]), g->bcol[0], hk, pa, mu, inv_sigma, pm, g->block_cols,
+      g->nblk, cap, cut, g->phase_clock, (int)config_get(kCfgResidentSpin), (int)config_get(kCfgResidentSyncEvery), out);
+  GNN_LAUNCH_CHECK();
+  return GNN_OK;
+}
+
 // partial slots of the kernels that sum the parameters' gradients: enough for any of them
 static int64_t ps_dst_blocks(const gnn_graph_t* g, int fout) {
   RowLaunch rl;
@@ -1262,6 +1562,8 @@ extern "C" gnn_status_t gnn_monet_fwd(const gnn_graph_t* g, int fin, int fout, i
     if (grid != 0) {
       return for_kernels(k, r, [&](auto kernels, auto dims) -> gnn_status_t {
         constexpr int KT = decltype(kernels)::value, RT = decltype(dims)::value;
+        if (monet_res_applies(g, k * fout))
+          return launch_monet_res<GL, KT, RT>(g, hk, pa, mu, inv_sigma, pm, out, st);
         return with_rows_in_flight(g, k * fout, [&](auto u, unsigned lds) -> gnn_status_t {
           k_gmmp_fwd_nr<GL, true, KT, RT, decltype(u)::value><<<grid, kPsBlock, lds, st>>>(rl, g->rows[0], g->indices, hk, nullptr, pa, mu,
                                                                                            inv_sigma, pm, out);

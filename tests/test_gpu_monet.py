@@ -157,3 +157,47 @@ def test_hub_empty_rows_no_edges_optional_gx_and_limits():
     assert e.value.status == 3                           # no workspace
     assert pk.gnn_monet_workspace_bytes(g, 4, 16, 2) > 0
     g.close()
+
+
+@pytest.mark.parametrize("fout,K,r,block_cols", [(16, 2, 1, 256), (16, 2, 1, 700), (32, 2, 2, 256), (4, 1, 1, 256), (64, 1, 3, 256),
+                                                 (16, 4, 4, 500), (20, 3, 2, 256), (12, 3, 1, 1400), (8, 2, 1, 100)])
+def test_all_column_blocks_in_one_launch(fout, K, r, block_cols):
+    """The forward launch that keeps its sums in LDS: segments of no, few and many edges, rows cut into parts (one of 40 000
+    edges into 64), rows without edges, and more rows than a workgroup holds.  Its sums are grouped by block, so they are compared with
+    the oracle and with the other kernels; what is not finite stays in the rows that gather it."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import assert_close
+    print(f"monet: one launch, {fout} x {K}, r={r}, block_cols={block_cols}", flush=True)
+    rng = np.random.default_rng(block_cols + fout)
+    n = 1500
+    deg = rng.integers(0, 40, n)
+    deg[[5, 30, 700, 1499]] = 40000, 12, 3000, 300
+    indptr = np.concatenate(([0], np.cumsum(deg))).astype(np.int32)
+    indices = rng.integers(0, n, indptr[-1]).astype(np.int32)
+    indices[indptr[20]:indptr[21]] = 77                     # a row that gathers one vertex only
+    for v in range(n):
+        row = indices[indptr[v]:indptr[v + 1]]
+        row[row == 9] = 10                                   # vertex 9 is gathered by row 30 alone
+    indices[indptr[30]] = 9
+    c = synth(rng, indptr, indices, 16, fout, K, r)
+    pk.gnn_config_set("block_cols", block_cols)
+    pk.gnn_config_set("resident_sums", 2)       # this launch on any graph with column blocks
+    try:
+        one = run(c)
+        bad = dict(c, x=c["x"].copy())
+        bad["x"][9] = np.inf
+        beside = run(bad)
+        pk.gnn_config_set("resident_sums", 0)
+        other = run(c)
+    finally:
+        pk.gnn_config_set("resident_sums", 1)
+        pk.gnn_config_set("block_cols", 12288)
+    ps = om.pseudo_projection_forward(indptr, indices, c["c"], c["proj_w"], c["proj_b"])
+    ref = om.gmm_pseudo_forward(indptr, indices, c["x"], c["w_fc"], ps, c["mu"], c["inv_sigma"])["out"]
+    # 40 000 terms of either sign round by the row's scale
+    assert_close("out", one["out"], ref, row_scale=True)
+    assert_close("out of the other kernel", other["out"], ref, row_scale=True)
+    assert not np.array_equal(one["out"], other["out"])      # another kernel it was
+    rest = np.arange(n) != 30
+    assert np.array_equal(beside["out"][rest], one["out"][rest]) and not np.isfinite(beside["out"][30]).any()
+    assert (one["out"][deg == 0] == 0).all()
