@@ -35,6 +35,7 @@ constexpr int kPsVals = 2 * kPsK * kPsR;  // gmu and ginv_sigma entries per part
 
 struct PsParams {
   int K, R, F;
+  int wide;  // 64-bit row offsets also where 32 bits reach every row ("wide_offsets")
 };
 
 // the K x R means and inverse widths, zero-padded to KT x RT, in registers (uniform)
@@ -345,9 +346,54 @@ __device__ __forceinline__ void write_run(T* p, const T (&v)[U]) {
   }
 }
 
+// Gathered rows of a table of n rows.  Up to 2 GB they come through a buffer resource, which reads zeros and no memory past its end:
+// that is where edges past the row's end point (kPastTable), so a chunk's loads are issued four at a time without a branch to each.
+// A branch to each -> this, us: forward, 200 000 vertices, 4 10^6 edges, K = 2, 16 columns, power law 86 -> 76, 13 000 x 200, even 40 -> 32,
+// 230 000 x 9, K = 3, 12 columns 81 -> 79, 230 000 x 10, K = 2, 8 columns, even 59 -> 63; backward 113 -> 96 (the first of these), 75 -> 72 (the third), 60 000
+// vertices, 1.5 10^7 edges, K = R = 3 277 -> 231.  By twos: 79, 36, 88, 60; 103, 73, 245.
+constexpr uint32_t kPastTable = 0x80000000u;
+__host__ __device__ __forceinline__ bool narrow_table(int64_t n, int row_floats) {
+  return n < (1 << 24) && n * row_floats * 4 <= (int64_t)kPastTable;
+}
+__device__ __forceinline__ uint32_t row_offset(bool narrow, int32_t v, bool ok, int row_floats) {
+  return !ok ? kPastTable : narrow ? __umul24((uint32_t)v, 4u * row_floats) : (uint32_t)v;
+}
+template <int U, typename Resource>
+__device__ __forceinline__ void gather_rows(bool narrow, Resource table, const float* base, int row_floats,
+                                            const uint32_t (&off)[U], uint32_t lane_off, int cnt, float4 (&rowv)[U]) {
+#pragma unroll
+  for (int t4 = 0; t4 < U; t4 += 4) {
+    if (t4 != 0 && t4 >= cnt) break;
+    if (narrow) {  // uniform
+#pragma unroll
+      for (int t = t4; t < t4 + 4 && t < U; ++t)
+        rowv[t] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(table, off[t] + lane_off, 0, 0));
+    } else {
+#pragma unroll
+      for (int t = t4; t < t4 + 4 && t < U; ++t) {
+        rowv[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (off[t] != kPastTable) rowv[t] = ld4(base + (int64_t)off[t] * row_floats + lane_off / 4);
+      }
+    }
+  }
+}
+// the gathered rows of a chunk's edges from t0 on, `cnt` of them at most: what is asked for by fours is used by fours
+template <int U, typename Fn>
+__device__ __forceinline__ void each_row(int cnt, Fn fn) {
+#pragma unroll
+  for (int t4 = 0; t4 < U; t4 += 4) {
+    if (t4 != 0 && t4 >= cnt) break;
+#pragma unroll
+    for (int t = t4; t < t4 + 4 && t < U; ++t) fn(t);
+  }
+}
+__device__ __forceinline__ auto table_resource(const float* p, int64_t n, int row_floats) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (uint32_t)(n * row_floats * 4), 0x00020000);
+}
+
 // forward: out[v, f] = (1/K) sum_e sum_k w_k(e) hk[u, k, f]; the sum over k is taken last, across lanes
 template <int G, bool PROJ, int KT, int RT, int U>
-__global__ __launch_bounds__(kPsBlock) void k_gmmp_fwd_nr(
+__global__ __launch_bounds__(kPsBlock, (RT <= 1 ? 7 : 6)) void k_gmmp_fwd_nr(
     RowLaunch rl, const int4* __restrict__ rows, const int32_t* __restrict__ indices, const float* __restrict__ hk, const float* __restrict__ pseudo,
     ProjArgs pa, const float* __restrict__ mu, const float* __restrict__ inv_sigma, PsParams pm,
     float* __restrict__ out) {
@@ -376,9 +422,11 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_fwd_nr(
   }
   const bool col_ok = li < K * F4;
   const int myk = col_ok ? li / F4 : 0;
-  int* l_idx = reinterpret_cast<int*>(lds + grp * GS);
+  uint32_t* l_off = reinterpret_cast<uint32_t*>(lds + grp * GS);
   float* l_w = lds + grp * GS + G;
-  const float* my_row = hk + 4 * li;
+  const bool narrow = pm.wide == 0 && narrow_table(rl.n_rows, KF);
+  const auto table = table_resource(hk, rl.n_rows, KF);
+  const uint32_t lane_off = 16u * li;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), part = acc;
   int folded = 0;
   // The sources travel two chunks ahead, their scalars one; the rows of a chunk are asked for before its weights are made.
@@ -391,7 +439,7 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_fwd_nr(
     const bool e_ok = e0 + li < end;
     const int cnt = min((uint32_t)G, end - e0);
     wave_lds_fence();  // the previous chunk's reads are done
-    l_idx[li] = u;
+    l_off[li] = row_offset(narrow, u, e_ok, KF);
     wave_lds_fence();
     float m[RT];
     if (!PROJ) {
@@ -405,17 +453,17 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_fwd_nr(
     if (PROJ) cu = pa.c[u];
     float4 rowv[U];
     auto fetch = [&](int t0) {
-      int idv[U];
-      read_run(l_idx + t0, idv);
-#pragma unroll
-      for (int t = 0; t < U; ++t)
-        if (col_ok && t0 + t < cnt) rowv[t] = ld4(my_row + (int64_t)idv[t] * KF);
+      uint32_t off[U];
+      read_run(l_off + t0, off);
+      if (col_ok) gather_rows(narrow, table, hk, KF, off, lane_off, cnt - t0, rowv);
     };
     fetch(0);
     if (PROJ) project(pq, R, c_here, cv, m);
 #pragma unroll
-    for (int k = 0; k < KT; ++k)
-      if (k < K) l_w[k * G + li] = e_ok ? gauss_k(pk, k, m) * inv_k : 0.f;
+    for (int k = 0; k < KT; ++k) {
+      const float w = gauss_k(pk, k, m) * inv_k;
+      l_w[k * G + li] = e_ok ? w : 0.f;
+    }
     wave_lds_fence();
 #pragma unroll
     for (int t0 = 0; t0 < G; t0 += U) {
@@ -423,9 +471,7 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_fwd_nr(
         if (t0 > 0) fetch(t0);
         float wv[U];
         read_run(l_w + myk * G + t0, wv);
-#pragma unroll
-        for (int t = 0; t < U; ++t)
-          if (col_ok && t0 + t < cnt) fma4(part, wv[t], rowv[t]);
+        if (col_ok) each_row<U>(cnt - t0, [&](int t) { fma4(part, wv[t], rowv[t]); });
       }
     }
     folded += G;
@@ -477,7 +523,6 @@ constexpr int kMonetLevels = 6;
 struct MonetParts {
   int rows[kMonetLevels];
 };
-constexpr uint32_t kPastTable = 0xFFFFF000u;  // 4 KB below the end of 32 bits
 template <int G, int KT>
 constexpr int kMonetGroupInts = (kMonetThreads / G) * (1 + KT) * G;  // idx, weights of all groups
 // a slot: sum, (beg, end) of two blocks, row, c of the row
@@ -497,13 +542,10 @@ __global__ __launch_bounds__(kMonetThreads) void k_monet_res(
   const float inv_k = 1.f / (float)K;
   const PsKernels<KT, RT> pk = load_kernels<KT, RT>(mu, inv_sigma, K, R);
   const ProjRegs<RT> pq = load_proj<RT>(pa, R);
-  // a lane's columns; lanes past the row's end take its first ones again, for nothing
   const bool col_ok = li < K * F4;
   const int myk = col_ok ? li / F4 : 0;
-  const uint32_t lane_off = col_ok ? 16u * li : 0u;
-  // Rows come through a buffer resource: the offset kPastTable, of edges past the segment's end, reads zeros and no memory, so
-  // a chunk's loads are issued without a branch to each.
-  const auto table = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(hk), 0, (uint32_t)((int64_t)n_rows * KF * 4), 0x00020000);
+  const uint32_t lane_off = 16u * li;
+  const auto table = table_resource(hk, n_rows, KF);
   float4* l_sum = reinterpret_cast<float4*>(lds_mr);        // [cap][F4]
   uint32_t* l_off = reinterpret_cast<uint32_t*>(lds_mr + cap * F + grp * (1 + KT) * G);  // [G], weights [KT][G]
   float* l_w = reinterpret_cast<float*>(l_off + G);
@@ -631,13 +673,12 @@ __global__ __launch_bounds__(kMonetThreads) void k_monet_res(
             wave_lds_fence();  // the previous chunk's reads are done
             l_off[li] = e_ok ? __umul24((uint32_t)c, 4u * KF) : kPastTable;
             wave_lds_fence();
-            uint4 rowv[U];
+            float4 rowv[U];
+            const int cnt = cur.end - e0;
             auto rows_of = [&](int t0) {
               uint32_t off[U];
               read_run(l_off + t0, off);
-#pragma unroll
-              for (int t = 0; t < U; ++t)
-                rowv[t] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(table, off[t] + lane_off, 0, 0));
+              if (col_ok) gather_rows(true, table, hk, KF, off, lane_off, cnt - t0, rowv);
             };
             rows_of(0);
             float m[RT];
@@ -650,14 +691,11 @@ __global__ __launch_bounds__(kMonetThreads) void k_monet_res(
             wave_lds_fence();
 #pragma unroll
             for (int t0 = 0; t0 < G; t0 += U) {
-              if (t0 == 0 || e0 + t0 < cur.end) {
+              if (t0 < cnt) {
                 if (t0 > 0) rows_of(t0);
                 float wv[U];
                 read_run(l_w + myk * G + t0, wv);
-#pragma unroll
-                for (int t = 0; t < U; ++t)
-                  fma4(part4, wv[t], make_float4(__uint_as_float(rowv[t].x), __uint_as_float(rowv[t].y),
-                                                 __uint_as_float(rowv[t].z), __uint_as_float(rowv[t].w)));
+                if (col_ok) each_row<U>(cnt - t0, [&](int t) { fma4(part4, wv[t], rowv[t]); });
               }
             }
             folded += G;
@@ -735,9 +773,11 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_dst_nr(
   const bool col_ok = li < K * F4;
   const int f4 = col_ok ? li % F4 : 0;
   const float4 g4 = col_ok ? ld4(gout + (int64_t)v * F + 4 * f4) : make_float4(0.f, 0.f, 0.f, 0.f);
-  int* l_idx = reinterpret_cast<int*>(lds + grp * GS);
+  uint32_t* l_off = reinterpret_cast<uint32_t*>(lds + grp * GS);
   float* l_d = lds + grp * GS + G;
-  const float* my_row = hk + 4 * li;
+  const bool narrow = pm.wide == 0 && narrow_table(rl.n_rows, KF);
+  const auto table = table_resource(hk, rl.n_rows, KF);
+  const uint32_t lane_off = 16u * li;
   const uint32_t step = ngrp * G;
   auto source = [&](uint32_t e) { return e < end ? indices[e] : 0; };
   uint32_t e0 = beg + gi * G;
@@ -746,7 +786,7 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_dst_nr(
     const bool e_ok = e0 + li < end;
     const int cnt = min((uint32_t)G, end - e0);
     wave_lds_fence();  // the previous chunk's reads are done
-    l_idx[li] = u;
+    l_off[li] = row_offset(narrow, u, e_ok, KF);
     wave_lds_fence();
     float m[RT];
 #pragma unroll
@@ -756,20 +796,17 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_dst_nr(
     u1 = source(e0 + 2 * step + li);
     float4 rowv[U];
     auto fetch = [&](int t0) {
-      int idv[U];
-      read_run(l_idx + t0, idv);
-#pragma unroll
-      for (int t = 0; t < U; ++t)
-        if (col_ok && t0 + t < cnt) rowv[t] = ld4(my_row + (int64_t)idv[t] * KF);
+      uint32_t off[U];
+      read_run(l_off + t0, off);
+      if (col_ok) gather_rows(narrow, table, hk, KF, off, lane_off, cnt - t0, rowv);
     };
     fetch(0);
 #pragma unroll
     for (int t0 = 0; t0 < G; t0 += U) {
       if (t0 < cnt) {
         if (t0 > 0) fetch(t0);
-        float dv[U];
-#pragma unroll
-        for (int t = 0; t < U; ++t) dv[t] = (col_ok && t0 + t < cnt) ? dot4(g4, rowv[t]) : 0.f;
+        float dv[U] = {};
+        if (col_ok) each_row<U>(cnt - t0, [&](int t) { dv[t] = dot4(g4, rowv[t]); });  // past the row's end: not looked at
         write_run(l_d + li * G + t0, dv);
       }
     }
@@ -804,8 +841,12 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_dst_nr(
 // Apart, the destination side gathered the K times wider hk[u] and both sides evaluated every tanh and exp.
 // 232 965 vertices, 1.12 10^8 edges, K = 2, R = 1, 16 columns, us: 1470 + 1240 -> 1320 (1860 compiled for the most kernels and
 // dimensions, as the forward kernel is, which the gathers of hk[u] bound: 1425, and 1478 compiled for K = 2, R = 1).
+// wavefronts per SIMD that k_gmmp_bwd_nr leaves room for: a few registers less than it would take (100 000 vertices, 2 10^6 edges, K = 3,
+// R = 2 73 us with what it would take, 60 so)
+template <int KT, int RT>
+constexpr int kNrMinWaves = KT <= 3 && RT == 1 ? 5 : 4;
 template <int G, bool PROJ, int KT, int RT>
-__global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
+__global__ __launch_bounds__(kPsBlock, (kNrMinWaves<KT, RT>)) void k_gmmp_bwd_nr(
     RowLaunch rl, const int4* __restrict__ rows_t, const int32_t* __restrict__ indices_t, const int32_t* __restrict__ eid_t, const float* __restrict__ hk,
     const float* __restrict__ pseudo, const float* __restrict__ pseudo_t /* nullable: pseudo in this walk's order */,
     ProjArgs pa, const float* __restrict__ mu, const float* __restrict__ inv_sigma, const float* __restrict__ gout,
@@ -841,10 +882,12 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
     const bool col_ok = li < K * F4;
     const int myk = col_ok ? li / F4 : 0, f4 = col_ok ? li % F4 : 0;
     const float4 h4 = col_ok ? ld4(hk + (int64_t)u * KF + 4 * li) : make_float4(0.f, 0.f, 0.f, 0.f);
-    int* l_idx = reinterpret_cast<int*>(lds + grp * GS);
+    uint32_t* l_off = reinterpret_cast<uint32_t*>(lds + grp * GS);
     float* l_w = lds + grp * GS + G;
     float* l_d = l_w + KT * G;
-    const float* my_row = gout + 4 * f4;
+    const bool narrow = pm.wide == 0 && narrow_table(rl.n_rows, F);
+    const auto table = table_resource(gout, rl.n_rows, F);
+    const uint32_t lane_off = 16u * f4;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), part = acc;
     int folded = 0;
     // loads ahead as in k_gmmp_fwd_nr
@@ -857,7 +900,7 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
       const bool e_ok = p0 + li < end;
       const int cnt = min((uint32_t)G, end - p0);
       wave_lds_fence();  // the previous chunk's reads are done
-      l_idx[li] = v;
+      l_off[li] = row_offset(narrow, v, e_ok, F);
       wave_lds_fence();
       int32_t e = 0;
       float m[RT], w[KT];
@@ -876,30 +919,29 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_nr(
       if (PROJ) cv_next = pa.c[v];
       float4 rowv[kNrU];
       auto fetch = [&](int t0) {
-        int idv[kNrU];
-        read_run(l_idx + t0, idv);
-#pragma unroll
-        for (int t = 0; t < kNrU; ++t)
-          if (col_ok && t0 + t < cnt) rowv[t] = ld4(my_row + (int64_t)idv[t] * F);
+        uint32_t off[kNrU];
+        read_run(l_off + t0, off);
+        if (col_ok) gather_rows(narrow, table, gout, F, off, lane_off, cnt - t0, rowv);
       };
       fetch(0);
       if (PROJ) project(pq, R, cu, cv, m);
 #pragma unroll
-      for (int k = 0; k < KT; ++k)
-        if (k < K) l_w[k * G + li] = w[k] = e_ok ? gauss_k(pk, k, m) * inv_k : 0.f;
+      for (int k = 0; k < KT; ++k) {
+        w[k] = gauss_k(pk, k, m) * inv_k;
+        l_w[k * G + li] = w[k] = e_ok ? w[k] : 0.f;
+      }
       wave_lds_fence();
 #pragma unroll
       for (int t0 = 0; t0 < G; t0 += kNrU) {
         if (t0 < cnt) {
           if (t0 > 0) fetch(t0);
-          float wv[kNrU], dv[kNrU];
+          float wv[kNrU], dv[kNrU] = {};
           read_run(l_w + myk * G + t0, wv);
-#pragma unroll
-          for (int t = 0; t < kNrU; ++t) {
-            const bool ok = col_ok && t0 + t < cnt;
-            if (ok) fma4(part, wv[t], rowv[t]);
-            dv[t] = ok ? dot4(h4, rowv[t]) : 0.f;
-          }
+          if (col_ok)
+            each_row<kNrU>(cnt - t0, [&](int t) {
+              fma4(part, wv[t], rowv[t]);
+              dv[t] = dot4(h4, rowv[t]);  // past the row's end: not looked at
+            });
           *reinterpret_cast<float4*>(l_d + li * G + t0) = make_float4(dv[0], dv[1], dv[2], dv[3]);
           *reinterpret_cast<float4*>(l_d + li * G + t0 + 4) = make_float4(dv[4], dv[5], dv[6], dv[7]);
         }
@@ -1180,8 +1222,7 @@ static bool monet_res_applies(const gnn_graph_t* g, int KF) {
   const bool enough = g->nnz >= (uneven ? kMonetEdgesUneven : kMonetEdgesEven) &&
                       g->nnz >= kMonetEdgesPerBlock * (int64_t)g->n * g->nblk;
   return (enough || config_get(kCfgResidentSums) == 2) && g->blocked_pays() && !config_get(kCfgForceSimple) && config_get(kCfgResidentSums) && g->phase_clock != nullptr &&
-         g->block_cols <= kMonetTabPerThread * kMonetThreads && g->n < (1 << 24) &&
-         (int64_t)sizeof(float) * KF * g->n <= (int64_t)kPastTable;
+         g->block_cols <= kMonetTabPerThread * kMonetThreads && narrow_table(g->n, KF) && !config_get(kCfgWideOffsets);
 }
 
 template <int G, int KT, int RT>
@@ -1337,7 +1378,7 @@ extern "C" gnn_status_t gnn_gmmp_fwd(const gnn_graph_t* g, int fin, int fout, in
   GNN_REQUIRE(aligned16(hk) && aligned16(out), GNN_ERR_INVALID_ARG, "gnn_gmmp_fwd: hk, out must be 16-byte aligned");
   hipStream_t st = static_cast<hipStream_t>(stream);
   GNN_TRY(gemm_f32(g->n, k * fout, fin, x, fin, false, w_fc, k * fout, false, hk, k * fout, 1, nullptr, st));
-  const PsParams pm{k, r, fout};
+  const PsParams pm{k, r, fout, (int)config_get(kCfgWideOffsets)};
   ProfScope p("gmmp_fwd_fused", st);
   if (const int G = nr_lanes(k, fout)) {
     return for_lanes(G, [&](auto lanes) -> gnn_status_t {
@@ -1393,7 +1434,7 @@ extern "C" gnn_status_t gnn_gmmp_bwd(const gnn_graph_t* g, int fin, int fout, in
   float* partial = reinterpret_cast<float*>(base + W.partial);
   double* wide = reinterpret_cast<double*>(base + W.partial);
   float* part = reinterpret_cast<float*>(base + W.gemm);
-  const PsParams pm{k, r, fout};
+  const PsParams pm{k, r, fout, (int)config_get(kCfgWideOffsets)};
   const int KF = k * fout;
   const int G = nr_lanes(k, fout);
   auto param_sums = [&](unsigned grid) -> gnn_status_t {  // of the destination side's kernels
@@ -1552,7 +1593,7 @@ extern "C" gnn_status_t gnn_monet_fwd(const gnn_graph_t* g, int fin, int fout, i
   GNN_REQUIRE(aligned16(hk) && aligned16(out), GNN_ERR_INVALID_ARG, "gnn_monet_fwd: hk, out must be 16-byte aligned");
   hipStream_t st = static_cast<hipStream_t>(stream);
   GNN_TRY(gemm_f32(g->n, k * fout, fin, x, fin, false, w_fc, k * fout, false, hk, k * fout, 1, nullptr, st));
-  const PsParams pm{k, r, fout};
+  const PsParams pm{k, r, fout, (int)config_get(kCfgWideOffsets)};
   const ProjArgs pa{c, proj_w, proj_b};
   ProfScope p("monet_fwd_fused", st);
   return for_lanes(k * fout <= 32 ? 8 : 16, [&](auto lanes) -> gnn_status_t {
@@ -1599,7 +1640,7 @@ extern "C" gnn_status_t gnn_monet_bwd(const gnn_graph_t* g, int fin, int fout, i
   float* dhk = reinterpret_cast<float*>(base + W.dhk);
   double* partial = reinterpret_cast<double*>(base + W.partial);
   float* part = reinterpret_cast<float*>(base + W.gemm);
-  const PsParams pm{k, r, fout};
+  const PsParams pm{k, r, fout, (int)config_get(kCfgWideOffsets)};
   const ProjArgs pa{c, proj_w, proj_b};
   const int KF = k * fout;
   const int G = KF <= 32 ? 8 : 16;

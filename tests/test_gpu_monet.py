@@ -201,3 +201,24 @@ def test_all_column_blocks_in_one_launch(fout, K, r, block_cols):
     rest = np.arange(n) != 30
     assert np.array_equal(beside["out"][rest], one["out"][rest]) and not np.isfinite(beside["out"][30]).any()
     assert (one["out"][deg == 0] == 0).all()
+
+
+@pytest.mark.parametrize("fout,K,r", [(16, 2, 1), (12, 3, 2), (16, 4, 3)])
+def test_rows_of_tables_that_32_bits_do_not_reach(fout, K, r):
+    """Row offsets of 64 bits, which tables of more than 2 GB take, give the same bits, with coordinates per edge as well."""
+    import paper_2110_09524_amd as pk
+    print(f"monet: wide offsets, {fout} x {K}, r={r}", flush=True)
+    rng = np.random.default_rng(fout + K)
+    n = 900
+    edges = [(u, int(v)) for u in range(n) for v in rng.integers(0, n, (0, 1, 3, 4, 8, 9, 17, 40)[u % 8])] + [(7, v) for v in range(n)]
+    indptr, indices = tiny_graph(n, edges)
+    c = synth(rng, indptr, indices, 12, fout, K, r)
+    narrow = [run(c, fused=fused) for fused in (True, False)]
+    pk.gnn_config_set("wide_offsets", 1)
+    try:
+        wide = [run(c, fused=fused) for fused in (True, False)]
+    finally:
+        pk.gnn_config_set("wide_offsets", 0)
+    for a, b in zip(narrow, wide):
+        for name in a:
+            assert np.array_equal(a[name], b[name]), name
