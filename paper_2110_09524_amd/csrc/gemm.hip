@@ -646,7 +646,7 @@ __global__ __launch_bounds__(64 * W) void k_gemm_few(int64_t M, int N, int K, co
       }
     }
   };
-  floatx16 part[2][TN];  // even and odd slabs, as in k_gemm_f32
+  floatx16 part[2][TN];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -655,10 +655,13 @@ __global__ __launch_bounds__(64 * W) void k_gemm_few(int64_t M, int N, int K, co
       for (int r = 0; r < 16; ++r) part[h][j][r] = 0.f;
   const int slabs = (K + BK - 1) / BK, per = (slabs + W - 1) / W;
   const int s0 = min(w * per, slabs), s1 = min(s0 + per, slabs);
+  // The product's odd slabs are summed negated, as in k_gemm_f32: in part[1], or in part[0] of a run that starts with one.  (Were
+  // it a run's odd slabs, runs of one slab would all lose to the same side: a GMM layer of 8104 vertices, 114 -> 3 x 20, then is off by 3.4e-7, not 1.4e-7.)
+  const bool odd_first = (s0 & 1) != 0;
   auto step = [&](auto slot, int s) {
     constexpr int S = decltype(slot)::value;
     constexpr int ia[6] = {1, 2, 0, 0, 1, 0}, ib[6] = {1, 0, 2, 1, 0, 0};  // smallest products first
-    const Parts a = split_octet(ra[S], S ? -kScale : kScale);
+    const Parts a = split_octet(ra[S], (S != 0) != odd_first ? -kScale : kScale);
     Parts b[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) b[j] = split_octet(rb[S][j], kScale);
@@ -680,7 +683,7 @@ __global__ __launch_bounds__(64 * W) void k_gemm_few(int64_t M, int N, int K, co
 #pragma unroll
   for (int j = 0; j < TN; ++j)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) l_sum[w][j][r][lane] = part[0][j][r] - part[1][j][r];
+    for (int r = 0; r < 16; ++r) l_sum[w][j][r][lane] = odd_first ? part[1][j][r] - part[0][j][r] : part[0][j][r] - part[1][j][r];
   __syncthreads();
 
   // wavefront w closes registers R w .. of the tile, which hold rows 8 (r / 4) + 4 lk + r % 4
