@@ -165,9 +165,11 @@ gnn_status_t gnn_release_cached_memory(void);
  *                           serves cache residency); layer calls on ONE graph that overlap in
  *                           time share those counters: their results stay right, their cache
  *                           hit rates suffer.  0: one launch per block or group of blocks.
- *                           Both give the same bits as one launch per block.  gnn_monet_fwd has
- *                           such a launch, too, which it takes where a rule on the graph finds it
- *                           faster, with 2 on every graph with column blocks, and with 0 never;
+ *                           Both give the same bits, but for GAT rows far longer than the mean:
+ *                           the one launch sums them in parts.  GAT layers whose heads have 8, 16
+ *                           or 32 columns (rows of 64, 128, 256 or 512) and gnn_monet_fwd have such
+ *                           a launch in place of their other kernels, where rules on the graph find
+ *                           it faster, with 2 on every graph with column blocks, and with 0 never;
  *                           its sums are grouped by block, so they round differently.
  *   "resident_spin"         polls after which a workgroup of that launch stops waiting for the
  *                           others of its XCD (default 4096; 0 = never wait; meant for tests)
@@ -288,7 +290,7 @@ gnn_status_t gnn_gat_bwd_noalloc(const gnn_graph_t* graph, int fin, int heads, i
 /* Introspection for measurement scripts: the instantiation of the column-blocked edge kernel that
  * a pass over this graph launches for `heads` x `f` (mode 0 forward, 1 destination side recomputing,
  * 2 source side, 3 forward with stash) under the current configuration, spelled as a profiler
- * prints it, e.g. "k_gat_res<16, 2, 1, false, true, false, true>" (the persistent launch) or
+ * prints it, e.g. "k_gat_res<16, 2, 1, false, true, false, true, 1, false>" (the persistent launch) or
  * "k_gat_blk<16, 2, false, false, true>" (one launch per block); the empty string when the
  * single-launch kernels run.  buf is a HOST buffer of len bytes. */
 gnn_status_t gnn_gat_blocked_kernel_name(const gnn_graph_t* graph, int heads, int f, int mode,

@@ -742,7 +742,7 @@ static GatWs gat_ws_layout(const gnn_graph_t* g, int fin, int H, int F) {
   w.partial = take(sizeof(float) * 2 * (size_t)w.nblk * HF);
   w.split_k = gemm_pick_split_k(fin, HF, n);
   w.gemm = take(w.split_k > 1 ? sizeof(float) * (size_t)w.split_k * fin * HF : 0);
-  const bool blocked = gat_blocked_applies(g, H, F);
+  const bool blocked = gat_blocked_whole(g, H, F);
   w.blk_rows = take(blocked ? sizeof(float) * n * HF : 0);  // T, then A2
   w.blk_scal = take(blocked ? sizeof(float) * n * 8 : 0);   // sg, then the slices' shares of del
   w.blk_elt = take(blocked ? sizeof(float) * n * H : 0);    // head-major el
@@ -1327,12 +1327,12 @@ static gnn_status_t gat_bwd_impl(const char* who, const gnn_graph_t* g, int fin,
 
   // the per-edge stash is laid out for whichever source-side kernel this graph and shape take
   const bool blocked = gat_blocked_applies(g, heads, f);
-  const int dst_flags = (blocked ? kDstHeadMajor : 0) | (blocked && gat_blocked_half(g, heads, f) ? kDstHalfGout : 0);
+  const int dst_flags = (blocked && !gat_blocked_shared(g, heads, f) ? kDstHeadMajor : 0) | (blocked && gat_blocked_half(g, heads, f) ? kDstHalfGout : 0);
   // a4: destination side.  With t and sg stashed by the forward call it is a vertex pass;
   // without them the sums are recomputed over the in-edges.
   if (t) {
     GNN_TRY(gat_dst_finish(g, dm, gout, t, out, sg, er, m, d, dst_flags, der, vstate, st));
-  } else if (blocked) {
+  } else if (gat_blocked_whole(g, heads, f)) {
     float* rows_buf = reinterpret_cast<float*>(base + L.blk_rows);
     float* scal_buf = reinterpret_cast<float*>(base + L.blk_scal);
     float* el_t = reinterpret_cast<float*>(base + L.blk_elt);

@@ -41,11 +41,12 @@ constexpr int kSlices = 8;  // column slices of a wide row: one per XCD
 // different rows) and each L2 still holds one slice of the column block.  A gather of a half line
 // would cost the L1 the same fill as a full one.  Rows of 256 bytes and less are not blocked: at
 // Reddit scale the single-launch kernels were faster there (the whole matrix then fits the
-// Infinity Cache, and a launch per block costs more than it saves).
+// Infinity Cache, and a launch per block costs more than it saves); the persistent kernels do take them.
 struct Slicing {
   int SL, ns;
+  int hs = 1;  // heads that share a slice
 };
-static bool pick_slicing(int heads, int HF, Slicing& sl) {
+static bool pick_whole_slicing(int heads, int HF, Slicing& sl) {  // every slice inside one head
   // One head of at most 64 columns: the row is a single slice of up to 256 bytes, every XCD holds the
   // whole column block (12288 x 256 bytes = 3 MB).  Only the persistent kernels take it: a launch per
   // block measured slower than the single-launch kernels here (4.04 against 3.69 ms for the source
@@ -78,6 +79,21 @@ static bool pick_slicing(int heads, int HF, Slicing& sl) {
   }
   sl = Slicing{q, kSlices};  // 64-byte slices, every slice inside one head
   return q == 4 && kSlices % heads == 0;
+}
+
+// Heads narrower than a slice share it: the lanes of a group then make the scores of two, four or eight heads, each lane those of the
+// head it has its columns in, and the persistent kernels keep the statistics of each.  A head to a slice of 128 bytes (4 x 32, 8 x 32) or
+// 64 bytes (8 x 16) fetched the lists and scalars of an edge as often per byte of row as there were slices, in a launch per block, and
+// had its hub rows wait in groups of 8 or 4 lanes.  Training pass, 232 965 vertices, 1.14 10^8 edges, power law | even, ms:
+// 4 x 32 12.8 -> 9.7 | 12.0 -> 10.2, 8 x 16 25.8 -> 10.0 | 24.1 -> 10.5; 22 308, 10^7: 4 x 32 2.23 -> 0.77 | 0.86 -> 0.74.
+static bool pick_slicing(int heads, int HF, Slicing& sl) {
+  const int f = heads > 0 ? HF / heads : 0, ns = HF / 64;
+  if (config_get(kCfgResidentSums) && heads > 1 && HF % 64 == 0 && (f == 8 || f == 16 || f == 32) &&
+      (ns == 1 || ns == 2 || ns == 4 || ns == 8)) {
+    sl = Slicing{16, ns, 64 / f};
+    return true;
+  }
+  return pick_whole_slicing(heads, HF, sl);
 }
 
 // ---- one column block of a weighted row aggregation ---------------------------------
@@ -506,7 +522,7 @@ __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk
 // ---- all column blocks in one persistent launch: the running sums stay in LDS -------------------
 // The launches of k_gat_blk pay for cache residency with a read-add-write of the rows' running
 // sums (and softmax statistics) per block.  Here one 1024-thread workgroup per CU runs for the
-// whole pass and keeps the state of kGatResSlots (row, slice) pairs in LDS: the running sums, the
+// whole pass and keeps the state of gat_res_slots (row, slice) pairs in LDS: the running sums, the
 // softmax statistics, the row's own scalars.  It takes all of them through column block 0, then
 // all of them through block 1, ... ("phases"), writes each row out in the last phase and then
 // takes its next rows ("generation").  Every workgroup of the chip owns the same number of rows
@@ -514,39 +530,43 @@ __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk
 // so the workgroups carry nearly equal loads in every phase and walk the blocks in step by
 // themselves; the workgroups of an XCD meet once per generation (phase_step_done: a bounded wait
 // that only serves cache residency), so an L2 serves one block at a time.  Inside a workgroup the
-// groups draw (row, slice) slots from an LDS counter, longest rows first.  A row's chunks are summed in the order of the launch-per-block kernels
-// (blocks ascending, edges in list order), so the results do not depend on who draws what.
+// groups draw (row, slice) slots from an LDS counter, longest rows first.  The chunks of a row, or of each of its parts, are summed in the
+// order of the launch-per-block kernels (blocks ascending, edges in list order), so the results do not depend on who draws what.
 // MODE as k_gat_blk; one segment per phase, per-edge scalars gathered from L2 or (TAB) read from LDS.
 constexpr int kGatResThreads = 1024;
 // Groups: SL / NA lanes, each with NA float4 of the slice.  NA = 2 is for rows of an fp16 copy, which a lane then reads in 16
 // instead of 8 bytes and a wavefront eight at a time: half as many gather instructions, and twice as many (row, slice) pairs share
 // what a pair costs whatever its length.  GAT layer, 232 965 vertices, 1.1 10^8 edges, fin = 602, forward, ms: 4 x 64 5.93 -> 4.77;
 // fin = 64, with the backward pass, 4 x 64 13.1 -> 11.9, 1 x 128 6.87 -> 6.50.  (fp32 rows, two float4 a lane, four rows in flight:
-// 7.18 -> 7.69 forward, 7.77 -> 8.02 source side.)  The longest rows then share a wavefront with seven groups that wait for
-// them, not three, so it is taken where a row is no longer than two groups' share of the edges.  4 x 64 and 2 x 64 by the longest row
-// in such shares, us: forward, 1.6 485 -> 456, 2.4 676 -> 664, 2.5 264 -> 262, 3.2 393 -> 409; with the backward pass, 0.5
-// 13 101 -> 11 881, 1.6 1752 -> 1737, 3.2 1045 -> 1151, 4 351 -> 397, 8.6 (1 x 128) 318 -> 385.
-constexpr int kGatPairShares = 2;
+// 7.18 -> 7.69 forward, 7.77 -> 8.02 source side.)
 // TAB: the block's part of el in LDS, where it leaves room for fewer rows at a time; its next part travels in registers during
 // a phase.  A gathered fp16 slice is one line, its score was another.  Forward of the layers above, NA = 2 without -> with it, us: 4 x 64
 // 4765 -> 4450, 1 x 128 2416 -> 2320; 60 000 vertices, 250 even edges, 4 x 64 572 -> 488 (NA = 1: 712).  With two sums a row
 // (MODE 3) the rows of a batch get too few: 11.9 -> 12.1 ms a training pass, and fp32 rows 16.8 -> 17.0.
 constexpr int kGatTabPerThread = 12;
-template <int SL, int MODE, int NA>
-constexpr int kGatResGroupInts = (kGatResThreads * NA / SL) * (MODE == 2 || MODE == 3 ? 3 : 2) * SL;  // idx, p, (p2) of all groups
-// a (row, slice) pair: sums (two for MODE 3) | state float4 | (beg, end) of two phases | row
-template <int SL, int MODE>
-constexpr int kGatResSlotInts = (MODE == 3 ? 2 : 1) * 4 * SL + 4 + 4 + 1;
+// idx, p of each head, (p2) of all groups
+template <int SL, int MODE, int NA, int HS>
+constexpr int kGatResGroupInts = (kGatResThreads * NA / SL) * (1 + HS + (HS == 1 && (MODE == 2 || MODE == 3) ? 1 : 0)) * SL;
+// a (row, slice) pair: sums (two for MODE 3) | state float4 of each head | (beg, end) of two phases | row
+template <int SL, int MODE, int HS>
+constexpr int kGatResSlotInts = (MODE == 3 ? 2 : 1) * 4 * SL + 4 * HS + 4 + 1;
 constexpr int kGatResLdsBytes = 160 * 1024;
 // Pairs a workgroup holds beside `table` ints: what the LDS leaves, a multiple of 4 so that the arrays stay 16-byte aligned
-template <int SL, int MODE, int NA>
+template <int SL, int MODE, int NA, int HS>
 constexpr int gat_res_slots(int table) {
   constexpr int most = MODE == 3 ? 256 : 512;
-  const int fit = (kGatResLdsBytes / 4 - 4 - kGatResGroupInts<SL, MODE, NA> - table) / kGatResSlotInts<SL, MODE>;
+  const int fit = (kGatResLdsBytes / 4 - 4 - kGatResGroupInts<SL, MODE, NA, HS> - table) / kGatResSlotInts<SL, MODE, HS>;
   return (fit < most ? fit : most) / 4 * 4;
 }
 
-template <int SL, int MODE, int NA, bool TAB, bool SKIP, bool HALF, bool NARROW>
+// Long rows are cut into parts (gat_long_rows), which are drawn like rows and added, with their statistics, after the last phase: the
+// first rows[i] rows of a workgroup, in the order of their degrees, into at least 2^(i + 1).
+constexpr int kGatLevels = 7;
+struct GatParts {
+  int rows[kGatLevels];
+};
+
+template <int SL, int MODE, int NA, bool TAB, bool SKIP, bool HALF, bool NARROW, int HS, bool PARTS>
 __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
     int32_t n_rows, const int32_t* __restrict__ order, const int2* __restrict__ bseg /* [nblk][n_rows] */,
     const int32_t* __restrict__ bcol, const float* __restrict__ feat /* gathered rows: z or gout */,
@@ -557,13 +577,15 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
     float* __restrict__ m_out, float* __restrict__ d_out, int32_t* __restrict__ clock, int spin_limit, int sync_every,
     const float* __restrict__ alpha_b /* MODE 2, nullable: stashed signed softmax values, [H][nnz] in the order of
                                          bcol (the "fusion with stashing" arm) */,
-    int64_t nnz, int nslot /* (row, slice) pairs the LDS holds */) {
-  constexpr int L = SL / NA;  // lanes of a group
+    int64_t nnz, int nslot /* (row, slice) pairs the LDS holds */, GatParts cut) {
+  constexpr int L = SL / NA;   // lanes of a group
+  constexpr int NE = NA * HS;  // edges of a chunk that a lane makes the score of, for the head it has its columns in
+  static_assert(HS == 1 || (NA == 1 && !HALF && !TAB && MODE != 1 && L % HS == 0), "shared slices: fp32 rows, no table");
   constexpr int U = SL < 8 ? 4 : 8;
   static_assert(NA == 1 || HALF, "fp32 rows: one float4 a lane");
   static_assert(!TAB || MODE != 2, "the source side needs 16 bytes per gathered vertex");
   constexpr int GPB = kGatResThreads / L;
-  constexpr int GS = kGatResGroupInts<SL, MODE, NA> / GPB;  // LDS ints of a group
+  constexpr int GS = kGatResGroupInts<SL, MODE, NA, HS> / GPB;  // LDS ints of a group
   constexpr bool DUAL = MODE == 3;
   constexpr bool SRC = MODE == 2;
   constexpr bool ONLINE = MODE == 0 || MODE == 3;
@@ -574,21 +596,24 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
   const int slice = blockIdx.x % ns;
   const int64_t nwg = gridDim.x / ns, wg = blockIdx.x / ns;  // workgroups that serve this slice
   const int H = dm.H, HF = dm.HF;
-  const int h = slice / sph;
-  const bool leader = (slice % sph) == 0;  // one slice per head keeps the per-head scalars
+  const int hd = li % HS;  // the lane's head among those of the slice
+  const int h = HS > 1 ? slice * HS + hd : slice / sph;
+  const bool leader = HS > 1 || (slice % sph) == 0;  // one slice per head keeps the per-head scalars
+  const int piece = hd * (L / HS) + li / HS;          // the lane's columns: a piece of its head's
+  auto edge_of = [&](int a) { return li / HS + (L / HS) * a; };  // a < NE: the chunk's edges that the lane makes the scores of
   // a row narrower than its slice (a single slice of fewer than 64 columns): the lanes past its end
   // gather the row's first columns again (same cache line) and keep zeros where it matters
-  const bool col_ok = slice * 4 * SL + 4 * NA * li < HF;
-  const int col = col_ok ? slice * 4 * SL + 4 * NA * li : 0;
+  const bool col_ok = slice * 4 * SL + 4 * NA * piece < HF;
+  const int col = col_ok ? slice * 4 * SL + 4 * NA * piece : 0;
 
   float4* l_acc = reinterpret_cast<float4*>(lds_gr);                                   // [nslot][SL]
   float4* l_acc2 = l_acc + (DUAL ? SL * nslot : 0);                                    // [nslot][SL] (MODE 3)
-  float4* l_state = l_acc2 + SL * nslot;                                               // [nslot]
-  int2* l_seg = reinterpret_cast<int2*>(l_state + nslot);                              // [2][nslot]
+  float4* l_state = l_acc2 + SL * nslot;                                               // [nslot][HS]
+  int2* l_seg = reinterpret_cast<int2*>(l_state + HS * nslot);                         // [2][nslot]
   int* l_row = reinterpret_cast<int*>(l_seg + 2 * nslot);                              // [nslot]
   int* l_idx = l_row + nslot + grp * GS;
   float* l_p = reinterpret_cast<float*>(l_idx + SL);
-  float* l_p2 = l_p + SL;
+  float* l_p2 = l_p + SL;                                                              // HS = 1
   int* l_cnt = l_row + nslot + GPB * GS;                                               // [2]
   float* l_tab = reinterpret_cast<float*>(l_cnt + 4);                                  // [block_cols] (TAB)
   float tab[TAB ? kGatTabPerThread : 1] = {};
@@ -612,8 +637,20 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
     store_table();
   }
 
-  const int64_t rows_per_wg = (n_rows + nwg - 1) / nwg;
-  const int ngen = (int)((rows_per_wg + nslot - 1) / nslot);
+  const int rows_here = (int)((n_rows + nwg - 1) / nwg);
+  auto log_parts = [&](int j) {  // parts of the workgroup's j-th row, as a power of two
+    int l = 0;
+#pragma unroll
+    for (int i = 0; i < (PARTS ? kGatLevels : 0); ++i) l += j < cut.rows[i] ? 1 : 0;
+    return l;
+  };
+  auto slots_before = [&](int j) {
+    int s = j;
+#pragma unroll
+    for (int i = 0; i < (PARTS ? kGatLevels : 0); ++i) s += min(j, cut.rows[i]) << i;  // level i doubles: 2^i more slots
+    return s;
+  };
+  const int all_slots = slots_before(rows_here);
   // workgroups go to the XCDs round-robin: those with the same id mod 8 share an L2
   PhaseClock pc{clock ? clock + (blockIdx.x % kXcds) * kClockStride : nullptr, (int)(gridDim.x / kXcds), spin_limit,
                 false, sync_every > 0 ? sync_every : nblk};
@@ -639,28 +676,94 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
     float4 zr[NA];  // MODE 2: the row's own z slice
   };
 
-  for (int gen = 0; gen < ngen; ++gen) {
-    const int64_t j0 = gen * rows_per_wg / ngen, j1 = (gen + 1) * rows_per_wg / ngen;
-    const int nslots = (int)(j1 - j0);  // slot q: row at position (j0 + q) * nwg + wg (or + nwg - 1 - wg)
+  // a finished row, normalised and written out
+  auto finish = [&](int32_t row, float4 (&acc)[NA], float4 (&acc2)[NA], const float4& st) {
+    if (ONLINE) {
+      // normalise (a row without in-edges keeps out = 0, m = 0, d = 1)
+      const float inv = st.y > 0.f ? 1.f / st.y : 0.f;
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        scale4(acc[a], inv);
+        if (DUAL) scale4(acc2[a], inv);
+      }
+      if (leader && li < HS) {
+        const int64_t rh = (int64_t)row * H + h;
+        m_out[rh] = st.y > 0.f ? st.x : 0.f;
+        d_out[rh] = st.y > 0.f ? st.y : 1.f;
+        if (MODE == 3) scal_buf[rh] = st.z * inv;
+      }
+    } else if (MODE == 1) {
+      if (leader && li == 0) scal_buf[(int64_t)row * H + h] = st.x;
+    } else if (li < HS) {
+      scal_buf[HS > 1 ? (int64_t)row * H + h : (int64_t)row * kSlices + slice] = st.x;
+    }
+    if (col_ok) {
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        st4_stream(acc_buf + (int64_t)row * HF + col + 4 * a, acc[a]);
+        if (DUAL) st4_stream(acc2_buf + (int64_t)row * HF + col + 4 * a, acc2[a]);
+      }
+    }
+  };
+
+  int phase = 0;
+  for (int j0 = 0, j1; j0 < rows_here; j0 = j1) {
+    // rows j0 .. j1 - 1, an even share of the slots that are left, and at least one row (its parts fit: see the launch)
+    const int s0 = slots_before(j0), left = all_slots - s0, gens = (left + nslot - 1) / nslot;
+    const int room = min(nslot, max((left + gens - 1) / gens, 1 << log_parts(j0)));
+    j1 = min(rows_here, j0 + room);
+    if (PARTS && slots_before(j1) - s0 > room) {
+      int over = j1;  // the most rows whose slots fit
+      j1 = j0 + 1;
+      while (over - j1 > 1) {
+        const int mid = (j1 + over) >> 1;
+        if (slots_before(mid) - s0 <= room) j1 = mid; else over = mid;
+      }
+    }
+    const int nslots = slots_before(j1) - s0;
     // (the previous generation ended with a workgroup barrier: its tables are free)
     int64_t pos = -1;                         // thread q < nslots: position of slot q's row in the degree order
+    int part = 0, logp = 0;                   // and which of the row's 2^logp parts
+    auto bounds = [&](int p) {                // this thread's piece of its row's segment of block p, cut at whole chunks
+      if (pos < 0) return make_int2(0, 0);
+      const int2 sg = bseg[(int64_t)p * n_rows + pos];
+      if (!PARTS) return sg;
+      const int64_t len = sg.y - sg.x;
+      auto at = [&](int i) { return sg.x + (int)((len * i >> logp) & ~(int64_t)(SL - 1)); };
+      return make_int2(at(part), part + 1 == 1 << logp ? sg.y : at(part + 1));
+    };
     if ((int)threadIdx.x < nslots) {
+      int lo = j0, hi = j1;  // the last row that starts at or before this slot
+      if (!PARTS) lo = j0 + threadIdx.x;
+      while (PARTS && hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (slots_before(mid) - s0 <= (int)threadIdx.x) lo = mid; else hi = mid;
+      }
+      part = (int)threadIdx.x - (slots_before(lo) - s0);
+      logp = log_parts(lo);
       // consecutive positions of the degree order go to consecutive workgroups, in alternating
       // direction from one round to the next, so every workgroup gets the same mix of degrees
-      const int64_t r = (j0 + threadIdx.x) * nwg + ((threadIdx.x & 1) ? nwg - 1 - wg : wg);
-      if (r < n_rows) pos = r;
-      const int32_t row = pos >= 0 ? order[pos] : -1;
-      l_row[threadIdx.x] = row;
-      l_seg[threadIdx.x] = pos >= 0 ? bseg[pos] : make_int2(0, 0);
-      // state: forward (m_run, d, s2, er[row]); MODE 1 (sum alpha g, er, m, 1/d); MODE 2 (del share, el[row])
-      float4 stt = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (row >= 0) {
-        const int64_t rh = (int64_t)row * H + h;
-        if (ONLINE) stt = make_float4(-INFINITY, 0.f, 0.f, er[rh]);
-        else if (MODE == 1) stt = make_float4(0.f, er[rh], m_in[rh], 1.f / d_in[rh]);
-        else stt = make_float4(0.f, el[rh], 0.f, 0.f);
+      const int64_t r = (int64_t)lo * nwg + ((lo & 1) ? nwg - 1 - wg : wg);
+      int32_t row = -1;
+      int2 seg = make_int2(0, 0);
+      if (r < n_rows) {
+        pos = r;
+        row = order[r];
+        seg = bounds(0);
       }
-      l_state[threadIdx.x] = stt;
+      l_row[threadIdx.x] = PARTS && row >= 0 && logp > 0 ? -2 - row : row;  // a row in parts: below -1
+      l_seg[threadIdx.x] = seg;
+      // state: forward (m_run, d, s2, er[row]); MODE 1 (sum alpha g, er, m, 1/d); MODE 2 (del share, el[row])
+      for (int a = 0; a < HS; ++a) {
+        float4 stt = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (row >= 0) {
+          const int64_t rh = (int64_t)row * H + (HS > 1 ? slice * HS + a : h);
+          if (ONLINE) stt = make_float4(-INFINITY, 0.f, 0.f, er[rh]);
+          else if (MODE == 1) stt = make_float4(0.f, er[rh], m_in[rh], 1.f / d_in[rh]);
+          else stt = make_float4(0.f, el[rh], 0.f, 0.f);
+        }
+        l_state[threadIdx.x * HS + a] = stt;
+      }
     }
     for (int i = threadIdx.x; i < nslots * SL; i += kGatResThreads) {
       l_acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -688,7 +791,7 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
       for (int a = 0; a < NA; ++a)
         if (it.beg + li + L * a < it.end) it.c_first[a] = bcol[it.beg + li + L * a];
       if (SRC) {
-        const int32_t row = l_row[q];
+        const int32_t tag = l_row[q], row = PARTS && tag < -1 ? -2 - tag : tag;
         if (row >= 0 && it.beg < it.end && col_ok) {
 #pragma unroll
           for (int a = 0; a < NA; ++a) it.zr[a] = ld4_stream(rowfeat + (int64_t)row * HF + col + 4 * a);
@@ -704,17 +807,18 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
       const bool last = p + 1 == nblk;
       // the next phase's bounds travel while this one is worked on
       int2 seg_next = make_int2(0, 0);
-      if (!last && pos >= 0) seg_next = bseg[(int64_t)(p + 1) * n_rows + pos];
+      if (!last) seg_next = bounds(p + 1);
       if (threadIdx.x == 0) l_cnt[(p + 1) & 1] = 0;
       if constexpr (TAB) fetch_table(last ? 0 : p + 1);
 
       while (q < nslots) {
         const int qn = grab(p);
         const Item nxt = fetch(p, qn);
-        const int32_t row = l_row[q];
+        const int32_t row = l_row[q];  // a row in parts is finished after the last phase
         const int32_t beg = cur.beg, end = cur.end;
-        if (row >= 0 && (beg < end || last)) {
-          const float4 stt = l_state[q];
+        const bool ends = last && (!PARTS || row >= 0);
+        if (row != -1 && (beg < end || ends)) {
+          const float4 stt = l_state[q * HS + hd];
           float4 acc[NA], acc2[NA];
 #pragma unroll
           for (int a = 0; a < NA; ++a) {
@@ -730,8 +834,8 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
           for (int a = 0; a < NA; ++a) {
             s_run[a] = 0.f;  // chunk-phase lanes: sum of alpha g (MODE 1), of alpha g D[v] (MODE 2)
             s_dot[a] = 0.f;  // MODE 2, row-phase lanes: sum of alpha g <z[u], gout[v]> over the lane's columns
-            d_lane[a] = li == 0 && a == 0 ? stt.y : 0.f;
-            s2_lane[a] = li == 0 && a == 0 ? stt.z : 0.f;
+            d_lane[a] = li < HS && a == 0 ? stt.y : 0.f;
+            s2_lane[a] = li < HS && a == 0 ? stt.z : 0.f;
           }
           float m_run = stt.x;  // ONLINE
           int32_t c_next[NA];
@@ -739,26 +843,37 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
           for (int a = 0; a < NA; ++a) c_next[a] = cur.c_first[a];
           for (int32_t c0 = beg; c0 < end; c0 += SL) {
             const int cnt = min(SL, end - c0);
-            bool e_ok[NA];
-            float e_a[NA], a_st[NA];
-            float4 vs[NA];
+            bool e_ok[NE];
+            float e_a[NE], a_st[NE];
+            float4 vs[NE];
+            int32_t ce[NE];  // the vertices at the far end of the lane's edges
 #pragma unroll
             for (int a = 0; a < NA; ++a) {
-              e_ok[a] = li + L * a < cnt;
-              const int32_t c = e_ok[a] ? c_next[a] : col_begin;
+              const int32_t c = li + L * a < cnt ? c_next[a] : col_begin;
               if (c0 + SL + li + L * a < end) c_next[a] = bcol[c0 + SL + li + L * a];
               l_idx[li + L * a] = c;
+              ce[a] = c;
+            }
+            if constexpr (HS > 1) {
+              wave_lds_fence();
+#pragma unroll
+              for (int a = 0; a < NE; ++a) ce[a] = l_idx[edge_of(a)];
+            }
+#pragma unroll
+            for (int a = 0; a < NE; ++a) {
+              e_ok[a] = edge_of(a) < cnt;
               e_a[a] = 0.f;
               a_st[a] = 0.f;
               vs[a] = make_float4(0.f, 0.f, 1.f, 0.f);
-              if (SRC && alpha_b != nullptr && e_ok[a]) a_st[a] = alpha_b[(int64_t)h * nnz + c0 + li + L * a];
+              if (SRC && alpha_b != nullptr && e_ok[a]) a_st[a] = alpha_b[(int64_t)h * nnz + c0 + edge_of(a)];
               if (e_ok[a]) {
-                if (SRC) vs[a] = vstate[(int64_t)h * n_rows + c];  // head-major (er, m, 1/d, D) of the destination
-                else if constexpr (TAB) e_a[a] = l_tab[c - col_begin];
-                else e_a[a] = el_hm ? el[(int64_t)h * n_rows + c] : el[(int64_t)c * H + h];
+                // (er, m, 1/d, D) of the destination: head-major, or the heads of a slice side by side
+                if (SRC) vs[a] = vstate[HS > 1 ? (int64_t)ce[a] * H + h : (int64_t)h * n_rows + ce[a]];
+                else if constexpr (TAB) e_a[a] = l_tab[ce[a] - col_begin];
+                else e_a[a] = el_hm ? el[(int64_t)h * n_rows + ce[a]] : el[(int64_t)ce[a] * H + h];
               }
             }
-            wave_lds_fence();
+            if constexpr (HS == 1) wave_lds_fence();
             float4 part[NA], part2[NA];
             float dpart[NA];
 #pragma unroll
@@ -799,40 +914,56 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
               }
               if (gathers_first) __builtin_amdgcn_s_setprio(0);
               if (t0 == 0) {
-                float pe[NA], pe2[NA];
+                float pe[NE], pe2[NE];
                 if (ONLINE) {
-                  float raw[NA], sc_e[NA], top = -INFINITY;
+                  float raw[NE], sc_e[NE], top = -INFINITY;
 #pragma unroll
-                  for (int a = 0; a < NA; ++a) {
+                  for (int a = 0; a < NE; ++a) {
                     raw[a] = e_a[a] + r_a;
                     sc_e[a] = e_ok[a] ? leaky(raw[a], dm.slope) : -INFINITY;
                     top = fmaxf(top, sc_e[a]);
                   }
-                  const float m_new = fmaxf(m_run, group_max_from<L>(top, 1));  // finite: lane 0 of a chunk is valid
+                  const float m_new = fmaxf(m_run, group_max_from<L>(top, HS));  // finite: a chunk's first edge is valid
                   sc = (m_run == -INFINITY) ? 0.f : __expf(m_run - m_new);
 #pragma unroll
-                  for (int a = 0; a < NA; ++a) {
+                  for (int a = 0; a < NE; ++a) {
                     pe[a] = e_ok[a] ? __expf(sc_e[a] - m_new) : 0.f;
                     pe2[a] = raw[a] > 0.f ? pe[a] : dm.slope * pe[a];
-                    d_lane[a] = fmaf(d_lane[a], sc, pe[a]);
-                    s2_lane[a] = fmaf(s2_lane[a], sc, pe2[a]);
+                  }
+#pragma unroll
+                  for (int a = 0; a < NA; ++a) {
+                    float dsum = pe[a], s2sum = pe2[a];
+#pragma unroll
+                    for (int j = 1; j < HS; ++j) {
+                      dsum += pe[a + NA * j];
+                      s2sum += pe2[a + NA * j];
+                    }
+                    d_lane[a] = fmaf(d_lane[a], sc, dsum);
+                    s2_lane[a] = fmaf(s2_lane[a], sc, s2sum);
+                  }
+                  if constexpr (HS > 1 && DUAL) {  // which of the two weights: the sign
+#pragma unroll
+                    for (int a = 0; a < NE; ++a) pe[a] = raw[a] > 0.f ? pe[a] : -pe[a];
                   }
                   m_run = m_new;
                 } else {
 #pragma unroll
-                  for (int a = 0; a < NA; ++a) {
+                  for (int a = 0; a < NE; ++a) {
                     pe[a] = pe2[a] = 0.f;
                     if (e_ok[a]) {
                       if (SRC) {
+                        bool pass;  // the score's slope is 1
                         if (alpha_b != nullptr) {  // read back instead of recomputed; D[v] is still gathered
                           pe[a] = fabsf(a_st[a]);
-                          pe2[a] = a_st[a] > 0.f ? pe[a] : dm.slope * pe[a];
+                          pass = a_st[a] > 0.f;
                         } else {
                           const float raw = r_a + vs[a].x;
                           pe[a] = __expf(leaky(raw, dm.slope) - vs[a].y) * vs[a].z;
-                          pe2[a] = raw > 0.f ? pe[a] : dm.slope * pe[a];
+                          pass = raw > 0.f;
                         }
-                        s_run[a] = fmaf(pe2[a], vs[a].w, s_run[a]);
+                        pe2[a] = pass ? pe[a] : dm.slope * pe[a];
+                        if (HS > 1) pe[a] = pass ? pe[a] : -pe[a];
+                        s_run[a % NA] = fmaf(pe2[a], vs[a].w, s_run[a % NA]);
                       } else {
                         const float raw = e_a[a] + r_a;
                         pe[a] = __expf(leaky(raw, dm.slope) - r_m) * r_invd;
@@ -843,20 +974,28 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
                   }
                 }
 #pragma unroll
-                for (int a = 0; a < NA; ++a) {
-                  l_p[li + L * a] = pe[a];
-                  if (DUAL || SRC) l_p2[li + L * a] = pe2[a];
+                for (int a = 0; a < NE; ++a) {
+                  l_p[hd * SL + edge_of(a)] = pe[a];
+                  if (HS == 1 && (DUAL || SRC)) l_p2[edge_of(a)] = pe2[a];
                 }
                 wave_lds_fence();
               }
               float pv[U], pv2[U];
 #pragma unroll
               for (int qq = 0; qq < U / 4; ++qq) {
-                const float4 p4 = *reinterpret_cast<const float4*>(l_p + t0 + 4 * qq);
+                const float4 p4 = *reinterpret_cast<const float4*>(l_p + hd * SL + t0 + 4 * qq);
                 pv[4 * qq] = p4.x; pv[4 * qq + 1] = p4.y; pv[4 * qq + 2] = p4.z; pv[4 * qq + 3] = p4.w;
-                if (DUAL || SRC) {
+                if (HS == 1 && (DUAL || SRC)) {
                   const float4 q4 = *reinterpret_cast<const float4*>(l_p2 + t0 + 4 * qq);
                   pv2[4 * qq] = q4.x; pv2[4 * qq + 1] = q4.y; pv2[4 * qq + 2] = q4.z; pv2[4 * qq + 3] = q4.w;
+                }
+              }
+              if constexpr (HS > 1 && (DUAL || SRC)) {
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                  const float w = fabsf(pv[t]);
+                  pv2[t] = pv[t] > 0.f ? w : dm.slope * w;
+                  pv[t] = w;
                 }
               }
 #pragma unroll
@@ -888,53 +1027,35 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
           }
           // the sum over the lanes of all their values: that of SL lanes with one each, in the same order
           auto total = [&](const float (&v)[NA]) {
-            float t = group_sum_from<L>(v[0], 1);
+            float t = group_sum_from<L>(v[0], HS);
 #pragma unroll
-            for (int a = 1; a < NA; ++a) t += group_sum_from<L>(v[a], 1);
+            for (int a = 1; a < NA; ++a) t += group_sum_from<L>(v[a], HS);
             return t;
           };
-          // close the item: statistics back to the slot, or (last phase) the finished row to memory
+          // close the item: statistics and sums back to the slot, or (last phase) the finished row to memory
           float4 st_new = stt;
           if (ONLINE) {
             const float d_tot = total(d_lane);
             const float s2_tot = MODE == 3 ? total(s2_lane) : 0.f;
             st_new = make_float4(m_run, d_tot, s2_tot, stt.w);
-            if (last) {
-              // the row is complete: normalise (a row without in-edges keeps out = 0, m = 0, d = 1)
-              const float inv = d_tot > 0.f ? 1.f / d_tot : 0.f;
-#pragma unroll
-              for (int a = 0; a < NA; ++a) {
-                scale4(acc[a], inv);
-                if (DUAL) scale4(acc2[a], inv);
-              }
-              if (leader && li == 0) {
-                const int64_t rh = (int64_t)row * H + h;
-                m_out[rh] = d_tot > 0.f ? m_run : 0.f;
-                d_out[rh] = d_tot > 0.f ? d_tot : 1.f;
-                if (MODE == 3) scal_buf[rh] = s2_tot * inv;
-              }
-            }
           } else if (MODE == 1) {
             if (leader) st_new.x = stt.x + total(s_run);
-            if (last && leader && li == 0) scal_buf[(int64_t)row * H + h] = st_new.x;
           } else {
             // this slice's share of del[u, h]; the D term is counted by one slice per head
 #pragma unroll
             for (int a = 0; a < NA; ++a) s_dot[a] -= leader ? s_run[a] : 0.f;
             st_new.x = stt.x + total(s_dot);
-            if (last && li == 0) scal_buf[(int64_t)row * kSlices + slice] = st_new.x;
           }
+          if (ends) {
+            finish(row, acc, acc2, st_new);
+          } else {
 #pragma unroll
-          for (int a = 0; a < NA; ++a) {
-            if (!last) {
+            for (int a = 0; a < NA; ++a) {
               l_acc[q * SL + li + L * a] = acc[a];
               if (DUAL) l_acc2[q * SL + li + L * a] = acc2[a];
-            } else if (col_ok) {
-              st4_stream(acc_buf + (int64_t)row * HF + col + 4 * a, acc[a]);
-              if (DUAL) st4_stream(acc2_buf + (int64_t)row * HF + col + 4 * a, acc2[a]);
             }
+            if (li < HS) l_state[q * HS + hd] = st_new;
           }
-          if (!last && li == 0) l_state[q] = st_new;
         }
         q = qn;
         cur = nxt;
@@ -946,9 +1067,38 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
         q = grab(p + 1);
         cur = fetch(p + 1, q);
       }
-      phase_step_done(pc, gen * nblk + p);
+      phase_step_done(pc, phase++);
       __syncthreads();  // every workgroup of the XCD is done with this block (or the wait ran out)
+    }
 
+    if (PARTS && nslots != j1 - j0) {  // rows in parts: their sums, in order, by the group that has the first part
+      for (int q0 = grp; q0 < nslots; q0 += GPB) {
+        const int tag = l_row[q0];
+        if (tag >= -1 || (q0 > 0 && l_row[q0 - 1] == tag)) continue;
+        float4 st = make_float4(ONLINE ? -INFINITY : 0.f, 0.f, 0.f, 0.f), acc[NA], acc2[NA];
+#pragma unroll
+        for (int a = 0; a < NA; ++a) acc[a] = acc2[a] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (ONLINE)
+          for (int i = q0; i < nslots && l_row[i] == tag; ++i) st.x = fmaxf(st.x, l_state[i * HS + hd].x);
+        for (int i = q0; i < nslots && l_row[i] == tag; ++i) {
+          const float4 si = l_state[i * HS + hd];
+          float sc = 1.f;  // to the maximum of all parts
+          if (ONLINE) {
+            sc = si.x == -INFINITY ? 0.f : __expf(si.x - st.x);
+            st.y = fmaf(sc, si.y, st.y);
+            st.z = fmaf(sc, si.z, st.z);
+          } else {
+            st.x += si.x;
+          }
+#pragma unroll
+          for (int a = 0; a < NA; ++a) {
+            fma4(acc[a], sc, l_acc[i * SL + li + L * a]);
+            if (DUAL) fma4(acc2[a], sc, l_acc2[i * SL + li + L * a]);
+          }
+        }
+        finish(-2 - tag, acc, acc2, st);
+      }
+      __syncthreads();  // the next rows take the slots
     }
   }
 }
@@ -976,7 +1126,7 @@ static gnn_status_t head_major(const gnn_graph_t* g, int H, const float* a, floa
 // fp16 copy of the gathered matrix (configuration key "gather_precision" = 1): rows of 2*HF bytes
 // are cut into slices of 64 columns (one 128-byte line), each inside one head
 bool gat_blocked_half(const gnn_graph_t* g, int heads, int f) {
-  if (config_get(kCfgGatherPrecision) != 1 || !gat_blocked_applies(g, heads, f)) return false;
+  if (config_get(kCfgGatherPrecision) != 1 || !gat_blocked_whole(g, heads, f)) return false;
   const int HF = heads * f;
   if (HF % 64 != 0 || HF < 128) return false;
   const int q = HF / 64;
@@ -1000,11 +1150,30 @@ static gnn_status_t to_half(const gnn_graph_t* g, int HF, const float* src, void
   return GNN_OK;
 }
 
+// Rows of 64 columns with several heads: the single-launch kernels up to here, whose gathers stay in the L2s, the persistent ones above.
+// Training pass, single launch | persistent, us: 8 x 8 power law 15 523 rows, 8 10^5 edges 98 | 124, 2.1 10^6 151 | 161, 22 308, 3 10^6
+// 212 | 193, 47 029, 1.2 10^7 728 | 530, 232 965, 1.14 10^8 8590 | 5190; 4 x 16 22 308, 10^7 409 | 424, 40 000, 4 10^6 233 | 270,
+// 47 029, 1.2 10^7 567 | 544, 10^5, 2 10^7 1198 | 1030, 232 965, 1.14 10^8 8280 | 5150; even degrees favour the persistent kernels more.
+// Wider rows: every size (15 523, 8 10^5, 16 x 8: 162 | 156; 8 x 16, 2.1 10^6 in slices of one head 1645, so 241).
+constexpr int64_t kSharedEdgesOf8 = (int64_t)5 << 19;  // slices of eight heads
+constexpr int64_t kSharedEdges = (int64_t)10 << 20;    // of two or four, and more rows than
+constexpr int64_t kSharedRows = 32768;
 bool gat_blocked_applies(const gnn_graph_t* g, int heads, int f) {
   if (!g->blocked_pays() || config_get(kCfgForceSimple)) return false;
   const int HF = heads * f;
   Slicing sl;
-  return pick_slicing(heads, HF, sl);
+  if (!pick_slicing(heads, HF, sl)) return false;
+  if (sl.hs == 1 || sl.ns > 1 || config_get(kCfgResidentSums) == 2) return true;
+  return sl.hs == 8 ? g->nnz >= kSharedEdgesOf8 : g->nnz >= kSharedEdges && g->n > kSharedRows;
+}
+
+bool gat_blocked_whole(const gnn_graph_t* g, int heads, int f) {
+  Slicing sl;
+  return gat_blocked_applies(g, heads, f) && pick_whole_slicing(heads, heads * f, sl);
+}
+bool gat_blocked_shared(const gnn_graph_t* g, int heads, int f) {
+  Slicing sl;
+  return gat_blocked_applies(g, heads, f) && pick_slicing(heads, heads * f, sl) && sl.hs > 1;
 }
 
 size_t gat_blocked_ws_bytes(const gnn_graph_t* g, int heads, int f) {
@@ -1132,25 +1301,44 @@ static gnn_status_t launch_blocks(const gnn_graph_t* g, int side, const char* na
 
 // The persistent kernel applies to rows cut into slices of 64 columns (256 bytes of fp32, or one
 // 128-byte line of an fp16 copy)
-static bool gat_resident_applies(const gnn_graph_t* g, GatDims dm) {
+static bool gat_resident_applies(const gnn_graph_t* g, GatDims dm, bool whole = false /* slices inside one head */) {
   if (!config_get(kCfgResidentSums) || g->phase_clock == nullptr) return false;
   Slicing sl;
-  return pick_slicing(dm.H, dm.HF, sl) && sl.SL == 16;
+  return (whole ? pick_whole_slicing(dm.H, dm.HF, sl) : pick_slicing(dm.H, dm.HF, sl)) && sl.SL == 16;
 }
 
 // one workgroup per CU, a multiple of 8 so that every XCD serves one slice
 static unsigned gat_resident_grid() { return (unsigned)(device_cu_count() / kXcds * kXcds); }
 
-// fp16 rows: two float4 a lane, and (forward, no stash) the block's part of el in LDS as well; see kGatPairShares, kGatTabPerThread
-static bool gat_resident_pairs(const gnn_graph_t* g, int side, GatDims dm) {
-  const int64_t groups = (int64_t)gat_resident_grid() / (dm.HF / 64) * (kGatResThreads / 8);
-  return (int64_t)g->max_degree[side] * groups <= kGatPairShares * g->nnz;
-}
-static bool gat_resident_table(const gnn_graph_t* g, GatDims dm) {
-  return gat_resident_pairs(g, 0, dm) && g->block_cols <= kGatTabPerThread * kGatResThreads;
+// fp16 rows, forward without a stash: the block's part of el in LDS as well; see kGatTabPerThread
+static bool gat_resident_table(const gnn_graph_t* g) {
+  return g->block_cols <= kGatTabPerThread * kGatResThreads;
 }
 
-template <int MODE, int NA, bool TAB, bool SKIP, bool HALF, bool NARROW>
+// Which graphs have their long rows cut, and into what.  A row as long as its share (what a group has of the edges on average) is
+// what its workgroup waits for in every phase, unless all rows are about as long: 15 523 rows of 132 even edges, 1 x 64, uncut 122 us a
+// training pass, cut 138.  So: rows longer than four times the mean and 0.7 shares (232 965 power-law rows, 8 x 8, longest 1.08 shares:
+// 6042 -> 5187; longest row 0.27 shares, 4 x 64: 15.41 ms cut, 15.35 uncut).  Pieces of a quarter to half a share, and of at
+// least half a chunk in a block: 22 308 rows, 10^7 edges, 1 x 64 325 us (twice as long 344, half 330), 100 000 rows, 4 10^7 edges, 8 x 8
+// 1807 (2086, 1775).
+constexpr int64_t kGatPieceEdges = 32;  // to a block: rows shorter than two such pieces stay whole
+static int64_t gat_share(const gnn_graph_t* g, int ns, int groups) { return g->nnz / (gat_resident_grid() / ns * groups); }
+static bool gat_long_rows(const gnn_graph_t* g, int side, int ns, int groups) {
+  const int64_t longest = g->max_degree[side];
+  return 10 * longest > 7 * gat_share(g, ns, groups) && longest > 2 * kGatPieceEdges * g->nblk && longest * g->n > 4 * g->nnz;
+}
+static GatParts gat_resident_parts(const gnn_graph_t* g, int side, int ns, int groups, int nslot) {
+  GatParts cut{};
+  const int64_t piece = std::max(kGatPieceEdges * g->nblk, gat_share(g, ns, groups) / 2);
+  for (int i = 0; i < kGatLevels && (2 << i) <= nslot; ++i) {
+    int k = 0;  // rows of at least 2^k edges are cut into 2^(i + 1): the first power of two above piece 2^i
+    while (k < 31 && ((int64_t)1 << k) <= piece << i) ++k;
+    cut.rows[i] = k >= 31 ? 0 : (int)cdiv(g->h_bucket_offsets[side][32 - k], gat_resident_grid() / ns);
+  }
+  return cut;
+}
+
+template <int MODE, int NA, int HS, bool TAB, bool SKIP, bool HALF, bool NARROW, bool PARTS>
 static gnn_status_t launch_resident_addr(const gnn_graph_t* g, int side, const char* name, GatDims dm, int el_hm,
                                          const float* feat, const float* rowfeat, const float* el, const float* er,
                                          const float* m, const float* d, const float4* vstate, float* acc,
@@ -1158,11 +1346,11 @@ static gnn_status_t launch_resident_addr(const gnn_graph_t* g, int side, const c
                                          const float* alpha_b) {
   constexpr int SL = 16;
   const int ns = dm.HF <= 4 * SL ? 1 : dm.HF / (4 * SL);
-  const int sph = ns / dm.H;
-  const int nslot = gat_res_slots<SL, MODE, NA>(TAB ? g->block_cols : 0);
+  const int sph = HS > 1 ? 1 : ns / dm.H;
+  const int nslot = gat_res_slots<SL, MODE, NA, HS>(TAB ? g->block_cols : 0);
   static std::atomic<bool> attr_set{false};
   if (!attr_set.load(std::memory_order_acquire)) {
-    GNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gat_res<SL, MODE, NA, TAB, SKIP, HALF, NARROW>),
+    GNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gat_res<SL, MODE, NA, TAB, SKIP, HALF, NARROW, HS, PARTS>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kGatResLdsBytes));
     attr_set.store(true, std::memory_order_release);
   }
@@ -1170,12 +1358,27 @@ static gnn_status_t launch_resident_addr(const gnn_graph_t* g, int side, const c
   ProfScope p(name, st);
   k_gat_zero_clock<<<1, kXcds * kClockStride, 0, st>>>(g->phase_clock);
   GNN_LAUNCH_CHECK();
-  k_gat_res<SL, MODE, NA, TAB, SKIP, HALF, NARROW><<<grid, kGatResThreads, kGatResLdsBytes, st>>>(
+  k_gat_res<SL, MODE, NA, TAB, SKIP, HALF, NARROW, HS, PARTS><<<grid, kGatResThreads, kGatResLdsBytes, st>>>(
       g->n, g->order[side], reinterpret_cast<const int2*>(g->bseg[side]), g->bcol[side], feat, rowfeat, el, er, m, d,
       vstate, dm, sph, el_hm, g->block_cols, g->nblk, ns, acc, acc2, scal, m_out, d_out, g->phase_clock,
-      (int)config_get(kCfgResidentSpin), (int)config_get(kCfgResidentSyncEvery), alpha_b, g->nnz, nslot);
+      (int)config_get(kCfgResidentSpin), (int)config_get(kCfgResidentSyncEvery), alpha_b, g->nnz, nslot,
+      PARTS ? gat_resident_parts(g, side, ns, kGatResThreads * NA / SL, nslot) : GatParts{});
   GNN_LAUNCH_CHECK();
   return GNN_OK;
+}
+
+template <int MODE, int NA, int HS, bool TAB, bool SKIP, bool HALF, bool NARROW>
+static gnn_status_t launch_resident_parts(const gnn_graph_t* g, int side, const char* name, GatDims dm, int el_hm,
+                                          const float* feat, const float* rowfeat, const float* el, const float* er,
+                                          const float* m, const float* d, const float4* vstate, float* acc,
+                                          float* acc2, float* scal, float* m_out, float* d_out, hipStream_t st,
+                                          const float* alpha_b) {
+  const int ns = dm.HF <= 64 ? 1 : dm.HF / 64;
+  if (gat_long_rows(g, side, ns, kGatResThreads * NA / 16))
+    return launch_resident_addr<MODE, NA, HS, TAB, SKIP, HALF, NARROW, true>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d,
+                                                                           vstate, acc, acc2, scal, m_out, d_out, st, alpha_b);
+  return launch_resident_addr<MODE, NA, HS, TAB, SKIP, HALF, NARROW, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d,
+                                                                          vstate, acc, acc2, scal, m_out, d_out, st, alpha_b);
 }
 
 // 32-bit byte offsets (and 24-bit multiplies) reach every gathered row
@@ -1183,16 +1386,16 @@ static bool gat_resident_narrow(const gnn_graph_t* g, GatDims dm) {
   return (int64_t)g->n * dm.HF * 4 < ((int64_t)1 << 32) && g->n < (1 << 24) && !config_get(kCfgWideOffsets);
 }
 
-template <int MODE, int NA, bool TAB, bool SKIP, bool HALF>
+template <int MODE, int NA, int HS, bool TAB, bool SKIP, bool HALF>
 static gnn_status_t launch_resident_impl(const gnn_graph_t* g, int side, const char* name, GatDims dm, int el_hm,
                                          const float* feat, const float* rowfeat, const float* el, const float* er,
                                          const float* m, const float* d, const float4* vstate, float* acc,
                                          float* acc2, float* scal, float* m_out, float* d_out, hipStream_t st,
                                          const float* alpha_b) {
   if (gat_resident_narrow(g, dm))
-    return launch_resident_addr<MODE, NA, TAB, SKIP, HALF, true>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate,
+    return launch_resident_parts<MODE, NA, HS, TAB, SKIP, HALF, true>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate,
                                                         acc, acc2, scal, m_out, d_out, st, alpha_b);
-  return launch_resident_addr<MODE, NA, TAB, SKIP, HALF, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate,
+  return launch_resident_parts<MODE, NA, HS, TAB, SKIP, HALF, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate,
                                                        acc, acc2, scal, m_out, d_out, st, alpha_b);
 }
 
@@ -1205,24 +1408,40 @@ static gnn_status_t launch_resident(const gnn_graph_t* g, int side, const char* 
   if (half_feat) {
     if constexpr (MODE != 1) {
 #define GNN_GAT_HALF(NA_, TAB_)                                                                                             \
-  return launch_resident_impl<MODE, NA_, TAB_, true, true>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, \
+  return launch_resident_impl<MODE, NA_, 1, TAB_, true, true>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, \
                                                            acc2, scal, m_out, d_out, st, alpha_b)
       if constexpr (MODE == 0) {
-        if (gat_resident_table(g, dm)) GNN_GAT_HALF(2, true);
+        if (gat_resident_table(g)) GNN_GAT_HALF(2, true);
       }
-      if (gat_resident_pairs(g, side, dm)) GNN_GAT_HALF(2, false);
-      GNN_GAT_HALF(1, false);
+      GNN_GAT_HALF(2, false);
 #undef GNN_GAT_HALF
+    }
+  }
+  Slicing sl;
+  if constexpr (MODE != 1) {
+    if (pick_slicing(dm.H, dm.HF, sl) && sl.hs > 1) {
+#define GNN_GAT_SHARED(HS_)                                                                                              \
+  case HS_:                                                                                                              \
+    return launch_resident_impl<MODE, 1, HS_, false, true, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, \
+                                                                  vstate, acc, acc2, scal, m_out, d_out, st, alpha_b)
+      switch (sl.hs) {
+        GNN_GAT_SHARED(2);
+        GNN_GAT_SHARED(4);
+        GNN_GAT_SHARED(8);
+      }
+#undef GNN_GAT_SHARED
     }
   }
   // gathers past a segment's end are skipped on rows of four and more slices; on narrower rows the
   // source side gains from it as well (6.48 -> 6.14 ms for the two layers of a 128 / 44-wide model at
   // Reddit scale), the forward modes lose a little (5.87 -> 5.96 ms)
-  if (dm.HF / 64 >= 4 || MODE == 2)
-    return launch_resident_impl<MODE, 1, false, true, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, acc2,
-                                            scal, m_out, d_out, st, alpha_b);
-  return launch_resident_impl<MODE, 1, false, false, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, acc2,
-                                           scal, m_out, d_out, st, alpha_b);
+  if (MODE == 2 || dm.HF / 64 >= 4)
+    return launch_resident_impl<MODE, 1, 1, false, true, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc,
+                                                                acc2, scal, m_out, d_out, st, alpha_b);
+  if constexpr (MODE != 2)
+    return launch_resident_impl<MODE, 1, 1, false, false, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc,
+                                                                 acc2, scal, m_out, d_out, st, alpha_b);
+  return GNN_ERR_UNSUPPORTED;  // not reached
 }
 
 template <int MODE>
@@ -1231,7 +1450,7 @@ static gnn_status_t run_blocks(const gnn_graph_t* g, int side, const char* name,
                                const float* d, const float4* vstate, float* acc, float* acc2,
                                float* scal, int32_t* queue, float4* state, float* m_out, float* d_out,
                                hipStream_t st, bool half_feat = false, const float* alpha_b = nullptr) {
-  if (gat_resident_applies(g, dm))
+  if (gat_resident_applies(g, dm, MODE == 1))
     return launch_resident<MODE>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, acc2, scal,
                                  m_out, d_out, st, alpha_b, half_feat);
   if (half_feat) {
@@ -1240,7 +1459,7 @@ static gnn_status_t run_blocks(const gnn_graph_t* g, int side, const char* name,
                                           queue, state, m_out, d_out, st, alpha_b);
   }
   Slicing sl;
-  if (!pick_slicing(dm.H, dm.HF, sl)) sl.SL = 0;
+  if (!pick_whole_slicing(dm.H, dm.HF, sl)) sl.SL = 0;
   GNN_REQUIRE(sl.SL == 0 || dm.HF >= 128, GNN_ERR_UNSUPPORTED,
               "gat blocked: rows of one slice are served by the persistent kernels only");
   switch (sl.SL) {
@@ -1256,6 +1475,7 @@ static gnn_status_t run_blocks(const gnn_graph_t* g, int side, const char* name,
 gnn_status_t gat_blocked_fwd(const gnn_graph_t* g, GatDims dm, const float* z, const float* el,
                              const float* er, float* m, float* d, float* out, float* t, float* sg,
                              float* el_t, int32_t* queue, float4* state, void* half_buf, hipStream_t st) {
+  if (gat_blocked_shared(g, dm.H, dm.F)) el_t = nullptr;  // the heads of a slice stand side by side
   if (el_t) GNN_TRY(head_major(g, dm.H, el, el_t, st));
   if (!config_get(kCfgLdsScalarTable)) queue = nullptr;
   const float* el_use = el_t ? el_t : el;
@@ -1282,15 +1502,16 @@ gnn_status_t gat_blocked_bwd_dst(const gnn_graph_t* g, GatDims dm, const float* 
   GNN_TRY(run_blocks<1>(g, 0, "gat_bwd_dst", dm, el_t != nullptr, z, nullptr, el_t ? el_t : el, er, m, d, nullptr,
                         t_buf, nullptr, sg_buf, queue, nullptr, nullptr, nullptr, st));
   return gat_dst_finish(g, dm, gout, t_buf, out, sg_buf, er, m, d,
-                        kDstHeadMajor | (gat_blocked_half(g, dm.H, dm.F) ? kDstHalfGout : 0), der, vstate, st);
+                        (gat_blocked_shared(g, dm.H, dm.F) ? 0 : kDstHeadMajor) |
+                            (gat_blocked_half(g, dm.H, dm.F) ? kDstHalfGout : 0), der, vstate, st);
 }
 
 // dz[u,h,:] += a_l[h,:] del[u,h] + a_r[h,:] der[u,h], with del[u,h] = the sum of the shares its
 // slices left in sd ([n][8], slice-major inside a vertex); one thread per float4 of dz
-__global__ void k_gat_src_finish_blk(int64_t n, GatDims dm, int ns, const float* __restrict__ sd,
+__global__ void k_gat_src_finish_blk(int64_t n, GatDims dm, int ns, const float* sd,
                                      const float* __restrict__ der, const float* __restrict__ a_l,
                                      const float* __restrict__ a_r, float* __restrict__ dz,
-                                     float* __restrict__ del) {
+                                     float* del /* sd itself where ns is 0 */) {
   const int qpr = dm.HF / 4;  // float4 per row
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= n * qpr) return;
@@ -1298,8 +1519,12 @@ __global__ void k_gat_src_finish_blk(int64_t n, GatDims dm, int ns, const float*
   const int col = 4 * (int)(i - u * qpr);
   const int h = col / dm.F, sph = ns / dm.H;
   float dl = 0.f;
-  for (int s = 0; s < sph; ++s) dl += sd[u * kSlices + h * sph + s];  // fixed order
-  if (col == h * dm.F) del[u * dm.H + h] = dl;
+  if (ns == 0) {  // del is there
+    dl = sd[u * dm.H + h];
+  } else {
+    for (int s = 0; s < sph; ++s) dl += sd[u * kSlices + h * sph + s];  // fixed order
+    if (col == h * dm.F) del[u * dm.H + h] = dl;
+  }
   float4 o = ld4(dz + u * dm.HF + col);
   fma4(o, dl, ld4(a_l + col));
   fma4(o, der[u * dm.H + h], ld4(a_r + col));
@@ -1349,16 +1574,18 @@ gnn_status_t gat_blocked_bwd_src(const gnn_graph_t* g, GatDims dm, const float* 
     GNN_TRY(to_half(g, dm.HF, gout, half_buf, st));
     feat = static_cast<const float*>(half_buf);
   }
+  const bool shared = gat_blocked_shared(g, dm.H, dm.F);
+  if (shared) sd_buf = del;  // a slice has all of its heads: no shares
   GNN_TRY(run_blocks<2>(g, 1, "gat_bwd_src", dm, 0, feat, z, el, nullptr, nullptr, nullptr, vstate, dz,
                         nullptr, sd_buf, nullptr, nullptr, nullptr, nullptr, st, half, alpha_b));
   Slicing sl;
   int ns = 0;
   if (half) ns = dm.HF / 64;
   else if (pick_slicing(dm.H, dm.HF, sl)) ns = sl.ns;
-  GNN_REQUIRE(ns >= dm.H && ns % dm.H == 0 && ns <= kSlices, GNN_ERR_UNSUPPORTED, "gat blocked: bad slicing");
+  GNN_REQUIRE(shared || (ns >= dm.H && ns % dm.H == 0 && ns <= kSlices), GNN_ERR_UNSUPPORTED, "gat blocked: bad slicing");
   ProfScope p("gat_bwd_src_finish", st);
   const int64_t quads = (int64_t)g->n * (dm.HF / 4);
-  k_gat_src_finish_blk<<<(unsigned)cdiv(quads, 256), 256, 0, st>>>(g->n, dm, ns, sd_buf, der, a_l, a_r, dz, del);
+  k_gat_src_finish_blk<<<(unsigned)cdiv(quads, 256), 256, 0, st>>>(g->n, dm, shared ? 0 : ns, sd_buf, der, a_l, a_r, dz, del);
   GNN_LAUNCH_CHECK();
   return GNN_OK;
 }
@@ -1381,13 +1608,15 @@ extern "C" gnn_status_t gnn_gat_blocked_kernel_name(const gnn_graph_t* g, int he
   const bool half = mode != 1 && gat_blocked_half(g, heads, f);
   Slicing sl;
   if (!pick_slicing(heads, heads * f, sl)) return GNN_OK;
-  if (gat_resident_applies(g, make_dims(heads, f, 0.2f))) {
+  if (mode == 1 && !pick_whole_slicing(heads, heads * f, sl)) return GNN_OK;
+  if (gat_resident_applies(g, make_dims(heads, f, 0.2f), mode == 1)) {
     const GatDims dm = make_dims(heads, f, 0.2f);
-    std::snprintf(buf, len, "k_gat_res<16, %d, %d, %s, %s, %s, %s>", mode,
-                  half && gat_resident_pairs(g, mode == 2, dm) ? 2 : 1,
-                  half && mode == 0 && gat_resident_table(g, dm) ? "true" : "false",
-                  (half || heads * f / 64 >= 4 || mode == 2) ? "true" : "false", half ? "true" : "false",
-                  gat_resident_narrow(g, dm) ? "true" : "false");
+    std::snprintf(buf, len, "k_gat_res<16, %d, %d, %s, %s, %s, %s, %d, %s>", mode,
+                  half ? 2 : 1,
+                  half && mode == 0 && gat_resident_table(g) ? "true" : "false",
+                  (half || sl.hs > 1 || heads * f / 64 >= 4 || mode == 2) ? "true" : "false", half ? "true" : "false",
+                  gat_resident_narrow(g, dm) ? "true" : "false", sl.hs,
+                  gat_long_rows(g, mode == 2, dm.HF <= 64 ? 1 : dm.HF / 64, kGatResThreads * (half ? 2 : 1) / 16) ? "true" : "false");
     return GNN_OK;
   }
   const int SL = half ? 8 : sl.SL;

@@ -25,10 +25,13 @@ inline GatDims make_dims(int H, int F, float slope) {
 __device__ __forceinline__ float leaky(float x, float slope) { return x > 0.f ? x : slope * x; }
 
 // ---- column-blocked path (gat_blocked.hip) -----------------------------------------
-// True when the blocked kernels apply: several column blocks in the plan, a row of
-// heads*f floats that splits into 8 slices (one per XCD) of 4..64 float4 each, and every
-// slice inside one head.
+// True when the blocked kernels apply: several column blocks in the plan, and a row of heads*f floats
+// that splits into slices inside one head, or into slices of 64 columns that heads of 8, 16 or 32 share.
 bool gat_blocked_applies(const gnn_graph_t* g, int heads, int f);
+// ... into slices inside one head (also where it could be cut the other way): the kernels that need scratch of the workspace;
+// ... into slices that heads share: vstate is [n][H], as for the single-launch kernels, and no scratch is used
+bool gat_blocked_whole(const gnn_graph_t* g, int heads, int f);
+bool gat_blocked_shared(const gnn_graph_t* g, int heads, int f);
 size_t gat_blocked_ws_bytes(const gnn_graph_t* g, int heads, int f);  // extra workspace (bwd)
 // t, sg: optional stash of the destination-side backward sums (both or neither);
 // state: n * 8 float4 of scratch for the running softmax statistics (required)

@@ -712,3 +712,91 @@ def test_column_blocked_path_with_64_bit_row_offsets(H, F, resident):
         pk.gnn_config_set("resident_sums", 1)
     compare(c, res, fwd, bwd)
 
+
+
+def hub_graph(rng, n, pairs):
+    """A random graph with duplicates, one vertex with an edge from and one with an edge to every other, and some without any."""
+    indptr, indices = random_graph(rng, n, pairs, self_loops=False, duplicates=True)
+    rows = [indices[indptr[v]:indptr[v + 1]] for v in range(n)]
+    for v in range(n):
+        rows[v] = np.append(rows[v], 11) if v % 50 else rows[v][:0]
+    rows[7] = np.arange(n, dtype=np.int32)
+    counts = np.array([len(r) for r in rows])
+    return np.concatenate(([0], np.cumsum(counts))).astype(np.int32), np.concatenate(rows).astype(np.int32)
+
+
+@pytest.mark.parametrize("H,F,block_cols", [(2, 32, 256), (4, 16, 300), (8, 8, 1000), (4, 32, 300), (8, 16, 256), (16, 8, 1000),
+                                            (8, 32, 300), (16, 32, 256)])
+@pytest.mark.parametrize("hub", [False, True])
+def test_heads_that_share_a_slice(H, F, block_cols, hub):
+    """Two, four or eight heads in a 64-column slice of the persistent kernels: with stashed and recomputed sums of the
+    destination side, stored softmax values and 64-bit row offsets; rows whole and in parts."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import dev, run_gat
+    print(f"gat: shared slices H={H} F={F} block_cols={block_cols} hub={hub}", flush=True)
+    rng = np.random.default_rng(block_cols + H + F)
+    n = 1500
+    indptr, indices = hub_graph(rng, n, 20000) if hub else random_graph(rng, n, 30000, self_loops=False, duplicates=True)
+    c = synth(rng, indptr, indices, 24, H, F)
+    fwd, bwd = oracle_all(c)
+    pk.gnn_config_set("block_cols", block_cols)
+    pk.gnn_config_set("resident_sums", 2)
+    try:
+        g = pk.Graph(dev(indptr), dev(indices))
+        for mode in (0, 2, 3):
+            name = pk.gnn_gat_blocked_kernel_name(g, H, F, mode)
+            assert name == f"k_gat_res<16, {mode}, 1, false, true, false, true, {64 // F}, {'true' if hub else 'false'}>", name
+        res, recompute = run_gat(c, graph=g), run_gat(c, graph=g, stash=False)
+        stored = run_gat(c, graph=g, alpha_stash=True)
+        stored.pop("alpha_t")
+        pk.gnn_config_set("wide_offsets", 1)
+        wide = run_gat(c, graph=g)
+        g.close()
+    finally:
+        pk.gnn_config_set("wide_offsets", 0)
+        pk.gnn_config_set("resident_sums", 1)
+        pk.gnn_config_set("block_cols", 12288)
+    compare(c, res, fwd, bwd)
+    compare(c, recompute, fwd, bwd)
+    compare(c, stored, fwd, bwd)
+    for key in res:
+        assert np.array_equal(res[key], wide[key]), key
+
+
+@pytest.mark.parametrize("H,F,block_cols", [(1, 64, 256), (1, 44, 300), (1, 128, 1000), (2, 64, 300), (4, 64, 256)])
+def test_long_rows_in_parts(H, F, block_cols):
+    """Rows that the persistent kernels cut into parts, against the oracle, and from fp16 rows against the launches per block,
+    which take a row in one piece."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import assert_close, dev, run_gat
+    print(f"gat: long rows in parts H={H} F={F} block_cols={block_cols}", flush=True)
+    rng = np.random.default_rng(block_cols + H + F)
+    n = 1700
+    indptr, indices = hub_graph(rng, n, 20000)
+    c = synth(rng, indptr, indices, 24, H, F)
+    fwd, bwd = oracle_all(c)
+    half = {}
+    pk.gnn_config_set("block_cols", block_cols)
+    try:
+        g = pk.Graph(dev(indptr), dev(indices))
+        for mode in (0, 1, 2, 3):
+            name = pk.gnn_gat_blocked_kernel_name(g, H, F, mode)
+            assert name.startswith(f"k_gat_res<16, {mode}, ") and name.endswith(", 1, true>"), name
+        res, recompute, infer = run_gat(c, graph=g), run_gat(c, graph=g, stash=False), run_gat(c, backward=False, graph=g, stash=False)
+        if F % 64 == 0 and H * F > 64:
+            pk.gnn_config_set("gather_precision", 1)
+            for resident in (0, 1):
+                pk.gnn_config_set("resident_sums", resident)
+                half[resident] = (run_gat(c, backward=False, graph=g, stash=False), run_gat(c, graph=g))
+        g.close()
+    finally:
+        pk.gnn_config_set("gather_precision", 0)
+        pk.gnn_config_set("resident_sums", 1)
+        pk.gnn_config_set("block_cols", 12288)
+    compare(c, res, fwd, bwd)
+    compare(c, recompute, fwd, bwd)
+    compare(c, infer, fwd, None)
+    if half:
+        assert_close("out, forward only", half[1][0]["out"], half[0][0]["out"])
+        for key in ("out", "t", "sg", "m", "d", "gx"):
+            assert_close(key, half[1][1][key], half[0][1][key])
