@@ -155,7 +155,8 @@ gnn_status_t gnn_release_cached_memory(void);
  *                           12288 rows x one 256-byte slice = 3 MB of an XCD's 4 MB L2);
  *                           0 disables blocking.  Read by gnn_graph_create.
  *   "resident_sums"         1 (default): where rows are cut into 256-byte slices (and for single-head
- *                           or GCN rows of at most 64 floats, one slice) the column-blocked
+ *                           rows of at most 64 floats, one slice, and GCN rows of up to 512 floats
+ *                           where a rule on the graph finds it faster) the column-blocked
  *                           GAT and GCN kernels run all blocks of a pass in ONE persistent launch
  *                           (one 1024-thread workgroup per CU) that keeps the rows' running sums
  *                           and softmax statistics in LDS, a few thousand rows per workgroup at a
@@ -165,7 +166,7 @@ gnn_status_t gnn_release_cached_memory(void);
  *                           serves cache residency); layer calls on ONE graph that overlap in
  *                           time share those counters: their results stay right, their cache
  *                           hit rates suffer.  0: one launch per block or group of blocks.
- *                           Both give the same bits, but for GAT rows far longer than the mean:
+ *                           Both give the same bits, but for rows far longer than the mean:
  *                           the one launch sums them in parts.  GAT layers whose heads have 8, 16
  *                           or 32 columns (rows of 64, 128, 256 or 512) and gnn_monet_fwd have such
  *                           a launch in place of their other kernels, where rules on the graph find
@@ -193,8 +194,8 @@ gnn_status_t gnn_release_cached_memory(void);
  *                           the worst gradient entries) instead of the 1e-4 contract.  Set it before workspace sizes are
  *                           queried; shapes it does not cover (heads*f % 64 != 0, a 64-column
  *                           slice spanning heads) stay fp32.
- *   "wide_offsets"          1: the column-blocked GAT kernels and the narrow MoNet kernels address the
- *                           gathered rows with 64-bit offsets also where 32 bits reach every row (the
+ *   "wide_offsets"          1: the column-blocked GAT and GCN kernels and the narrow MoNet kernels address
+ *                           the gathered rows with 64-bit offsets also where 32 bits reach every row (the
  *                           code path of gathered matrices of 4 GB and more, MoNet's of 2 GB and
  *                           more; meant for tests).  Default 0.
  *   "force_simple_kernels"  1: always use the single-launch kernels
@@ -557,7 +558,7 @@ gnn_status_t gnn_gcn_tune(gnn_graph_t* graph, int fout, void* ws, size_t ws_byte
                           float* ms_out /*host [4], nullable*/);
 
 /* The same for the GCN sums over rows of `fout` floats (weighted = 1: the layer with a general weight
- * per edge), e.g. "k_rowsum_res<16, false>" or "k_rowsum_blk<16, true, false>"; the empty string
+ * per edge), e.g. "k_rowsum_res<16, false, true, false>" (as for the in-edges) or "k_rowsum_blk<16, true, false>"; the empty string
  * when the single-launch or edge-balanced kernels run. */
 gnn_status_t gnn_gcn_blocked_kernel_name(const gnn_graph_t* graph, int fout, int weighted,
                                          char* buf /*host*/, size_t len);

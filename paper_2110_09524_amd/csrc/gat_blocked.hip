@@ -28,6 +28,7 @@
 
 #include "common.h"
 #include "gat_common.h"
+#include "row_parts.h"
 #include "rowgroup.h"
 
 namespace gnn {
@@ -559,13 +560,7 @@ constexpr int gat_res_slots(int table) {
   return (fit < most ? fit : most) / 4 * 4;
 }
 
-// Long rows are cut into parts (gat_long_rows), which are drawn like rows and added, with their statistics, after the last phase: the
-// first rows[i] rows of a workgroup, in the order of their degrees, into at least 2^(i + 1).
-constexpr int kGatLevels = 7;
-struct GatParts {
-  int rows[kGatLevels];
-};
-
+// PARTS: long rows are cut into parts (has_long_rows), which are added, with their statistics, after the last phase.
 template <int SL, int MODE, int NA, bool TAB, bool SKIP, bool HALF, bool NARROW, int HS, bool PARTS>
 __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
     int32_t n_rows, const int32_t* __restrict__ order, const int2* __restrict__ bseg /* [nblk][n_rows] */,
@@ -577,7 +572,7 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
     float* __restrict__ m_out, float* __restrict__ d_out, int32_t* __restrict__ clock, int spin_limit, int sync_every,
     const float* __restrict__ alpha_b /* MODE 2, nullable: stashed signed softmax values, [H][nnz] in the order of
                                          bcol (the "fusion with stashing" arm) */,
-    int64_t nnz, int nslot /* (row, slice) pairs the LDS holds */, GatParts cut) {
+    int64_t nnz, int nslot /* (row, slice) pairs the LDS holds */, RowParts cut) {
   constexpr int L = SL / NA;   // lanes of a group
   constexpr int NE = NA * HS;  // edges of a chunk that a lane makes the score of, for the head it has its columns in
   static_assert(HS == 1 || (NA == 1 && !HALF && !TAB && MODE != 1 && L % HS == 0), "shared slices: fp32 rows, no table");
@@ -638,19 +633,8 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
   }
 
   const int rows_here = (int)((n_rows + nwg - 1) / nwg);
-  auto log_parts = [&](int j) {  // parts of the workgroup's j-th row, as a power of two
-    int l = 0;
-#pragma unroll
-    for (int i = 0; i < (PARTS ? kGatLevels : 0); ++i) l += j < cut.rows[i] ? 1 : 0;
-    return l;
-  };
-  auto slots_before = [&](int j) {
-    int s = j;
-#pragma unroll
-    for (int i = 0; i < (PARTS ? kGatLevels : 0); ++i) s += min(j, cut.rows[i]) << i;  // level i doubles: 2^i more slots
-    return s;
-  };
-  const int all_slots = slots_before(rows_here);
+  auto slots_to = [&](int j) { return PARTS ? slots_before(cut, j) : j; };
+  const int all_slots = slots_to(rows_here);
   // workgroups go to the XCDs round-robin: those with the same id mod 8 share an L2
   PhaseClock pc{clock ? clock + (blockIdx.x % kXcds) * kClockStride : nullptr, (int)(gridDim.x / kXcds), spin_limit,
                 false, sync_every > 0 ? sync_every : nblk};
@@ -709,38 +693,24 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
   int phase = 0;
   for (int j0 = 0, j1; j0 < rows_here; j0 = j1) {
     // rows j0 .. j1 - 1, an even share of the slots that are left, and at least one row (its parts fit: see the launch)
-    const int s0 = slots_before(j0), left = all_slots - s0, gens = (left + nslot - 1) / nslot;
-    const int room = min(nslot, max((left + gens - 1) / gens, 1 << log_parts(j0)));
-    j1 = min(rows_here, j0 + room);
-    if (PARTS && slots_before(j1) - s0 > room) {
-      int over = j1;  // the most rows whose slots fit
-      j1 = j0 + 1;
-      while (over - j1 > 1) {
-        const int mid = (j1 + over) >> 1;
-        if (slots_before(mid) - s0 <= room) j1 = mid; else over = mid;
-      }
-    }
-    const int nslots = slots_before(j1) - s0;
+    const int s0 = slots_to(j0), left = all_slots - s0, gens = (left + nslot - 1) / nslot;
+    const int room = min(nslot, max((left + gens - 1) / gens, PARTS ? 1 << log_parts(cut, j0) : 1));
+    j1 = PARTS ? rows_that_fit(cut, j0, rows_here, room) : min(rows_here, j0 + room);
+    const int nslots = slots_to(j1) - s0;
     // (the previous generation ended with a workgroup barrier: its tables are free)
     int64_t pos = -1;                         // thread q < nslots: position of slot q's row in the degree order
     int part = 0, logp = 0;                   // and which of the row's 2^logp parts
     auto bounds = [&](int p) {                // this thread's piece of its row's segment of block p, cut at whole chunks
       if (pos < 0) return make_int2(0, 0);
       const int2 sg = bseg[(int64_t)p * n_rows + pos];
-      if (!PARTS) return sg;
-      const int64_t len = sg.y - sg.x;
-      auto at = [&](int i) { return sg.x + (int)((len * i >> logp) & ~(int64_t)(SL - 1)); };
-      return make_int2(at(part), part + 1 == 1 << logp ? sg.y : at(part + 1));
+      return PARTS ? part_of_segment(sg, part, logp, SL) : sg;
     };
     if ((int)threadIdx.x < nslots) {
-      int lo = j0, hi = j1;  // the last row that starts at or before this slot
-      if (!PARTS) lo = j0 + threadIdx.x;
-      while (PARTS && hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (slots_before(mid) - s0 <= (int)threadIdx.x) lo = mid; else hi = mid;
+      const int lo = PARTS ? row_of_slot(cut, j0, j1, threadIdx.x) : j0 + threadIdx.x;
+      if (PARTS) {
+        part = (int)threadIdx.x - (slots_before(cut, lo) - s0);
+        logp = log_parts(cut, lo);
       }
-      part = (int)threadIdx.x - (slots_before(lo) - s0);
-      logp = log_parts(lo);
       // consecutive positions of the degree order go to consecutive workgroups, in alternating
       // direction from one round to the next, so every workgroup gets the same mix of degrees
       const int64_t r = (int64_t)lo * nwg + ((lo & 1) ? nwg - 1 - wg : wg);
@@ -1315,28 +1285,7 @@ static bool gat_resident_table(const gnn_graph_t* g) {
   return g->block_cols <= kGatTabPerThread * kGatResThreads;
 }
 
-// Which graphs have their long rows cut, and into what.  A row as long as its share (what a group has of the edges on average) is
-// what its workgroup waits for in every phase, unless all rows are about as long: 15 523 rows of 132 even edges, 1 x 64, uncut 122 us a
-// training pass, cut 138.  So: rows longer than four times the mean and 0.7 shares (232 965 power-law rows, 8 x 8, longest 1.08 shares:
-// 6042 -> 5187; longest row 0.27 shares, 4 x 64: 15.41 ms cut, 15.35 uncut).  Pieces of a quarter to half a share, and of at
-// least half a chunk in a block: 22 308 rows, 10^7 edges, 1 x 64 325 us (twice as long 344, half 330), 100 000 rows, 4 10^7 edges, 8 x 8
-// 1807 (2086, 1775).
-constexpr int64_t kGatPieceEdges = 32;  // to a block: rows shorter than two such pieces stay whole
-static int64_t gat_share(const gnn_graph_t* g, int ns, int groups) { return g->nnz / (gat_resident_grid() / ns * groups); }
-static bool gat_long_rows(const gnn_graph_t* g, int side, int ns, int groups) {
-  const int64_t longest = g->max_degree[side];
-  return 10 * longest > 7 * gat_share(g, ns, groups) && longest > 2 * kGatPieceEdges * g->nblk && longest * g->n > 4 * g->nnz;
-}
-static GatParts gat_resident_parts(const gnn_graph_t* g, int side, int ns, int groups, int nslot) {
-  GatParts cut{};
-  const int64_t piece = std::max(kGatPieceEdges * g->nblk, gat_share(g, ns, groups) / 2);
-  for (int i = 0; i < kGatLevels && (2 << i) <= nslot; ++i) {
-    int k = 0;  // rows of at least 2^k edges are cut into 2^(i + 1): the first power of two above piece 2^i
-    while (k < 31 && ((int64_t)1 << k) <= piece << i) ++k;
-    cut.rows[i] = k >= 31 ? 0 : (int)cdiv(g->h_bucket_offsets[side][32 - k], gat_resident_grid() / ns);
-  }
-  return cut;
-}
+static int64_t gat_resident_groups(int ns, int na) { return (int64_t)gat_resident_grid() / ns * (kGatResThreads * na / 16); }
 
 template <int MODE, int NA, int HS, bool TAB, bool SKIP, bool HALF, bool NARROW, bool PARTS>
 static gnn_status_t launch_resident_addr(const gnn_graph_t* g, int side, const char* name, GatDims dm, int el_hm,
@@ -1362,7 +1311,7 @@ static gnn_status_t launch_resident_addr(const gnn_graph_t* g, int side, const c
       g->n, g->order[side], reinterpret_cast<const int2*>(g->bseg[side]), g->bcol[side], feat, rowfeat, el, er, m, d,
       vstate, dm, sph, el_hm, g->block_cols, g->nblk, ns, acc, acc2, scal, m_out, d_out, g->phase_clock,
       (int)config_get(kCfgResidentSpin), (int)config_get(kCfgResidentSyncEvery), alpha_b, g->nnz, nslot,
-      PARTS ? gat_resident_parts(g, side, ns, kGatResThreads * NA / SL, nslot) : GatParts{});
+      PARTS ? cut_long_rows(g, side, gat_resident_groups(ns, NA), grid / ns, nslot) : RowParts{});
   GNN_LAUNCH_CHECK();
   return GNN_OK;
 }
@@ -1374,7 +1323,7 @@ static gnn_status_t launch_resident_parts(const gnn_graph_t* g, int side, const 
                                           float* acc2, float* scal, float* m_out, float* d_out, hipStream_t st,
                                           const float* alpha_b) {
   const int ns = dm.HF <= 64 ? 1 : dm.HF / 64;
-  if (gat_long_rows(g, side, ns, kGatResThreads * NA / 16))
+  if (has_long_rows(g, side, gat_resident_groups(ns, NA)))
     return launch_resident_addr<MODE, NA, HS, TAB, SKIP, HALF, NARROW, true>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d,
                                                                            vstate, acc, acc2, scal, m_out, d_out, st, alpha_b);
   return launch_resident_addr<MODE, NA, HS, TAB, SKIP, HALF, NARROW, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d,
@@ -1616,7 +1565,7 @@ extern "C" gnn_status_t gnn_gat_blocked_kernel_name(const gnn_graph_t* g, int he
                   half && mode == 0 && gat_resident_table(g) ? "true" : "false",
                   (half || sl.hs > 1 || heads * f / 64 >= 4 || mode == 2) ? "true" : "false", half ? "true" : "false",
                   gat_resident_narrow(g, dm) ? "true" : "false", sl.hs,
-                  gat_long_rows(g, mode == 2, dm.HF <= 64 ? 1 : dm.HF / 64, kGatResThreads * (half ? 2 : 1) / 16) ? "true" : "false");
+                  has_long_rows(g, mode == 2, gat_resident_groups(dm.HF <= 64 ? 1 : dm.HF / 64, half ? 2 : 1)) ? "true" : "false");
     return GNN_OK;
   }
   const int SL = half ? 8 : sl.SL;

@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "row_parts.h"
 #include "rowgroup.h"
 
 namespace gnn {
@@ -390,7 +391,7 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum_blk(
 // ---- all column blocks in one persistent launch: the running sums stay in LDS ------------
 // The launches above pay for cache residency with one read-add-write of the [n, F] running sums
 // per block.  Here one workgroup per CU runs for the whole pass and keeps the sums of up to
-// kResSlots (row, slice) pairs in LDS.  It takes all of them through column block 0, then all of
+// res_slots (row, slice) pairs in LDS.  It takes all of them through column block 0, then all of
 // them through block 1, and so on ("phases"); after the last block it writes the rows out once
 // and takes its next rows ("generation").  Every workgroup owns the same number of rows per
 // generation, dealt from the degree order one position at a time in alternating direction, so
@@ -399,29 +400,37 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum_blk(
 // wait), so an L2 serves gathers from one block at a time.  Inside a workgroup the groups draw
 // rows from an LDS counter, longest rows first, which levels the segments' lengths.  A row's
 // sums run in block order and its edges in list order, so the result is bit-identical to the
-// launch-per-block path whoever draws what.
+// launch-per-block path whoever draws what; long rows (PARTS) are cut into parts, drawn like rows, which are added at the end.
+// Groups of four or eight lanes for narrow rows, the parts and the widths beside 64, 128, 256 and 512 gave, us a layer, power law:
+// 20 000 vertices, 2 10^6 edges, 16 columns 192 -> 76, 64 219 -> 102, 128 243 -> 153; 47 029, 2.2 10^7, 32 718 -> 310, 64 839 -> 497,
+// 120 1890 -> 1270; 232 965, 1.14 10^8, 16 2890 -> 1620, 32 2990 -> 1780, 64 3650 -> 3080, 100 12 770 -> 6530, 240 29 200 -> 15 500, 256
+// 11 420 -> 11 410; even degrees, 47 029, 16 407 -> 264, 64 502 -> 500.
 constexpr int kResThreads = 1024;
-constexpr int kResRows = 8;  // rows per group and generation (on average: the groups draw them)
-
+constexpr int kResLdsBytes = 160 * 1024;
+constexpr int kResMostRows = 8;  // (row, slice) pairs of a group at a time; more leave fewer blocks to a batch of rows, for nothing
+// A group takes 16 edges of a row at a time; with SL = 4 or 8 a lane has several of their indices.
+constexpr int kResChunk = 16;
+template <int SL, bool W>
+constexpr int kResGroupInts = (kResThreads / SL) * (W ? 2 : 1) * kResChunk;  // idx, (weights) of all groups
 template <int SL>
-constexpr int kResSlots = (kResThreads / SL) * kResRows;
-// LDS ints of a workgroup: sums | (beg, end) of two phases | row ids | per group idx (and weights) | two counters
+constexpr int kResSlotInts = 4 * SL + 4 + 1;  // sum | (beg, end) of two phases | row
 template <int SL, bool W>
-constexpr int kResLdsInts = 4 * SL * kResSlots<SL> + 2 * 2 * kResSlots<SL> + kResSlots<SL> +
-                            (kResThreads / SL) * (W ? 2 : 1) * SL + 4;
+constexpr int res_slots() {
+  constexpr int fit = (kResLdsBytes / 4 - 4 - kResGroupInts<SL, W>) / kResSlotInts<SL>, most = kResThreads / SL * kResMostRows;
+  return std::min({fit, most, kResThreads}) / 4 * 4;
+}
 
-template <int SL, bool W>
+template <int SL, bool W, bool NARROW, bool PARTS>
 __global__ __launch_bounds__(kResThreads) void k_rowsum_res(
     int32_t n_rows, const int32_t* __restrict__ order, const int2* __restrict__ bseg /* [nblk][n_rows] */,
     const int32_t* __restrict__ bcol, const float* __restrict__ feat, int32_t block_cols, int nblk, int F,
-    int ns, const float* __restrict__ scale /* nullable: factor per row */, float* __restrict__ out,
+    int ns, int sw /* columns of a slice */, const float* __restrict__ scale /* nullable: factor per row */, float* __restrict__ out,
     const float* __restrict__ bw, int32_t* __restrict__ clock /* nullable: step counters, zeroed */,
-    int spin_limit, int sync_every) {
+    int spin_limit, int sync_every, RowParts cut) {
   constexpr int GPB = kResThreads / SL;
-  constexpr int R = kResRows;
-  constexpr int NSLOT = kResSlots<SL>;
-  constexpr int U = SL < 8 ? 4 : 8;
-  static_assert(NSLOT <= kResThreads, "one thread per slot loads its segment bounds");
+  constexpr int NSLOT = res_slots<SL, W>();
+  constexpr int U = 8, CH = kResChunk, NI = CH / SL;
+  static_assert(CH % SL == 0, "a lane has the same number of a chunk's indices as every other");
   extern __shared__ __align__(16) int lds_res[];
   const int lane = threadIdx.x & 63;
   const int li = threadIdx.x & (SL - 1);
@@ -429,41 +438,64 @@ __global__ __launch_bounds__(kResThreads) void k_rowsum_res(
   const int slice = blockIdx.x % ns;
   const int64_t nwg = gridDim.x / ns;         // workgroups that serve this slice
   const int64_t wg = blockIdx.x / ns;
-  const int64_t ngroups = nwg * GPB;
   float4* l_acc = reinterpret_cast<float4*>(lds_res);            // [NSLOT][SL]
   int2* l_seg = reinterpret_cast<int2*>(lds_res + 4 * SL * NSLOT);  // [2][NSLOT]
   int* l_row = lds_res + 4 * SL * NSLOT + 4 * NSLOT;             // [NSLOT]
-  int* l_idx = l_row + NSLOT + grp * (W ? 2 : 1) * SL;
-  float* l_w = reinterpret_cast<float*>(l_idx + SL);
-  int* l_cnt = l_row + NSLOT + GPB * (W ? 2 : 1) * SL;           // [2]
-  // a row narrower than its slice: the lanes past its end gather its first columns again (same
+  int* l_idx = l_row + NSLOT + grp * (W ? 2 : 1) * CH;
+  float* l_w = reinterpret_cast<float*>(l_idx + CH);
+  int* l_cnt = l_row + NSLOT + kResGroupInts<SL, W>;             // [2]
+  // a row narrower than its slices: the lanes past its end gather its first columns again (same
   // cache line) and store nothing
-  const bool col_ok = slice * 4 * SL + 4 * li < F;
-  const int col = col_ok ? slice * 4 * SL + 4 * li : 0;
+  const bool col_ok = 4 * li < sw && slice * sw + 4 * li < F;
+  const int col = col_ok ? slice * sw + 4 * li : slice * sw;
+  const char* feat_bytes = reinterpret_cast<const char*>(feat);
+  const uint32_t row_bytes = 4u * F, col_bytes = 4u * col;
 
-  const int64_t rows_per_group = (n_rows + ngroups - 1) / ngroups;
-  const int ngen = (int)((rows_per_group + R - 1) / R);
+  const int rows_here = (int)((n_rows + nwg - 1) / nwg);
+  auto slots_to = [&](int j) { return PARTS ? slots_before(cut, j) : j; };
+  const int all_slots = slots_to(rows_here);
   // workgroups go to the XCDs round-robin: those with the same id mod 8 share an L2
   PhaseClock pc{clock ? clock + (blockIdx.x % kXcds) * kClockStride : nullptr, (int)(gridDim.x / kXcds), spin_limit,
                 false, sync_every > 0 ? sync_every : nblk};
 
   struct Item {
-    int32_t beg, end, c_first;
-    float w_first;
+    int32_t beg, end, c_first[NI];
+    float w_first[NI];
   };
 
-  for (int gen = 0; gen < ngen; ++gen) {
-    const int64_t j0 = gen * rows_per_group / ngen, j1 = (gen + 1) * rows_per_group / ngen;
-    const int nslots = (int)(j1 - j0) * GPB;  // slot q: row at position (j0 * GPB + q) * nwg + wg (or + nwg - 1 - wg)
+  int phase = 0;
+  for (int j0 = 0, j1; j0 < rows_here; j0 = j1) {
+    // rows j0 .. j1 - 1, an even share of the slots that are left, and at least one row (its parts fit: see the launch)
+    const int s0 = slots_to(j0), left = all_slots - s0, gens = (left + NSLOT - 1) / NSLOT;
+    const int room = min(NSLOT, max((left + gens - 1) / gens, PARTS ? 1 << log_parts(cut, j0) : 1));
+    j1 = PARTS ? rows_that_fit(cut, j0, rows_here, room) : min(rows_here, j0 + room);
+    const int nslots = slots_to(j1) - s0;
     __syncthreads();                          // the previous generation's rows are written out
     int64_t pos = -1;                         // thread q < nslots: position of slot q's row in the degree order
+    int part = 0, logp = 0;                   // and which of the row's 2^logp parts
+    auto bounds = [&](int p) {
+      if (pos < 0) return make_int2(0, 0);
+      const int2 sg = bseg[(int64_t)p * n_rows + pos];
+      return PARTS ? part_of_segment(sg, part, logp, CH) : sg;
+    };
     if ((int)threadIdx.x < nslots) {
+      const int lo = PARTS ? row_of_slot(cut, j0, j1, threadIdx.x) : j0 + threadIdx.x;
+      if (PARTS) {
+        part = (int)threadIdx.x - (slots_before(cut, lo) - s0);
+        logp = log_parts(cut, lo);
+      }
       // consecutive positions of the degree order go to consecutive workgroups, in alternating
       // direction from one round to the next, so every workgroup gets the same mix of degrees
-      const int64_t r = (j0 * GPB + threadIdx.x) * nwg + ((threadIdx.x & 1) ? nwg - 1 - wg : wg);
-      if (r < n_rows) pos = r;
-      l_row[threadIdx.x] = pos >= 0 ? order[pos] : -1;
-      l_seg[threadIdx.x] = pos >= 0 ? bseg[pos] : make_int2(0, 0);
+      const int64_t r = (int64_t)lo * nwg + ((lo & 1) ? nwg - 1 - wg : wg);
+      int32_t row = -1;
+      int2 seg = make_int2(0, 0);
+      if (r < n_rows) {
+        pos = r;
+        row = order[r];
+        seg = bounds(0);
+      }
+      l_row[threadIdx.x] = part == 0 ? row : -2;  // -2: a further part of the row before
+      l_seg[threadIdx.x] = seg;
     }
     for (int i = threadIdx.x; i < nslots * SL; i += kResThreads) l_acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (threadIdx.x == 0) l_cnt[0] = 0;
@@ -477,14 +509,20 @@ __global__ __launch_bounds__(kResThreads) void k_rowsum_res(
     };
     // what a slot needs before its edge loop in phase p: bounds and first indices
     auto fetch = [&](int p, int q) {
-      Item it{0, 0, p * block_cols, 0.f};
+      Item it{};
+#pragma unroll
+      for (int a = 0; a < NI; ++a) it.c_first[a] = p * block_cols;
       if (q >= nslots) return it;
       const int2 sg = l_seg[(p & 1) * NSLOT + q];
       it.beg = sg.x;
       it.end = sg.y;
-      if (it.beg + li < it.end) {
-        it.c_first = bcol[it.beg + li];
-        if (W) it.w_first = bw[it.beg + li];
+#pragma unroll
+      for (int a = 0; a < NI; ++a) {
+        const int32_t e = it.beg + li + SL * a;
+        if (e < it.end) {
+          it.c_first[a] = bcol[e];
+          if (W) it.w_first[a] = bw[e];
+        }
       }
       return it;
     };
@@ -495,7 +533,7 @@ __global__ __launch_bounds__(kResThreads) void k_rowsum_res(
       const int32_t col_begin = p * block_cols;
       // the next phase's bounds travel while this one is worked on
       int2 seg_next = make_int2(0, 0);
-      if (p + 1 < nblk && pos >= 0) seg_next = bseg[(int64_t)(p + 1) * n_rows + pos];
+      if (p + 1 < nblk) seg_next = bounds(p + 1);
       if (threadIdx.x == 0) l_cnt[(p + 1) & 1] = 0;
 
       while (q < nslots) {
@@ -504,43 +542,63 @@ __global__ __launch_bounds__(kResThreads) void k_rowsum_res(
         const int32_t beg = cur.beg, end = cur.end;
         if (beg < end) {
           float4 acc = l_acc[q * SL + li];
-          int32_t c_next = cur.c_first;
-          float w_next = cur.w_first;
-          for (int32_t c0 = beg; c0 < end; c0 += SL) {
-            const int32_t c = c0 + li < end ? c_next : col_begin;
-            const float wv = c0 + li < end ? w_next : 0.f;
-            if (c0 + SL + li < end) {
-              c_next = bcol[c0 + SL + li];
-              if (W) w_next = bw[c0 + SL + li];
-            }
-            l_idx[li] = c;
-            if (W) l_w[li] = wv;
-            wave_lds_fence();
-            const int cn = min(SL, end - c0);
-            float4 part = make_float4(0.f, 0.f, 0.f, 0.f);
+          int32_t c_next[NI];
+          float w_next[NI];
 #pragma unroll
-            for (int t0 = 0; t0 < SL; t0 += U) {
+          for (int a = 0; a < NI; ++a) {
+            c_next[a] = cur.c_first[a];
+            w_next[a] = cur.w_first[a];
+          }
+          for (int32_t c0 = beg; c0 < end; c0 += CH) {
+#pragma unroll
+            for (int a = 0; a < NI; ++a) {
+              const int32_t e = c0 + li + SL * a;
+              l_idx[li + SL * a] = e < end ? c_next[a] : col_begin;
+              if (W) l_w[li + SL * a] = e < end ? w_next[a] : 0.f;
+              if (e + CH < end) {
+                c_next[a] = bcol[e + CH];
+                if (W) w_next[a] = bw[e + CH];
+              }
+            }
+            wave_lds_fence();
+            const int cn = min(CH, end - c0);
+            float4 part4 = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int t0 = 0; t0 < CH; t0 += U) {
               int idv[U];
 #pragma unroll
               for (int qq = 0; qq < U / 4; ++qq) {
                 const int4 i4 = *reinterpret_cast<const int4*>(l_idx + t0 + 4 * qq);
                 idv[4 * qq] = i4.x; idv[4 * qq + 1] = i4.y; idv[4 * qq + 2] = i4.z; idv[4 * qq + 3] = i4.w;
               }
+              float wv[U] = {};
+              if (W) {
+#pragma unroll
+                for (int qq = 0; qq < U / 4; ++qq) {
+                  const float4 w4 = *reinterpret_cast<const float4*>(l_w + t0 + 4 * qq);
+                  wv[4 * qq] = w4.x; wv[4 * qq + 1] = w4.y; wv[4 * qq + 2] = w4.z; wv[4 * qq + 3] = w4.w;
+                }
+              }
               float4 rowv[U];
 #pragma unroll
               for (int t4 = 0; t4 < U; t4 += 4)
                 if (t0 + t4 < cn) {
 #pragma unroll
-                  for (int t = t4; t < t4 + 4; ++t) rowv[t] = ld4(feat + (int64_t)idv[t] * F + col);
+                  for (int t = t4; t < t4 + 4; ++t) {
+                    if constexpr (NARROW)  // 32-bit byte offsets from a scalar base reach every row
+                      rowv[t] = *reinterpret_cast<const float4*>(feat_bytes + (__umul24((uint32_t)idv[t], row_bytes) + col_bytes));
+                    else
+                      rowv[t] = ld4(feat + (int64_t)idv[t] * F + col);
+                  }
                 }
 #pragma unroll
               for (int t4 = 0; t4 < U; t4 += 4)
                 if (t0 + t4 < cn) {
 #pragma unroll
-                  for (int t = t4; t < t4 + 4; ++t) fma4(part, W ? l_w[t0 + t] : (t0 + t < cn ? 1.f : 0.f), rowv[t]);
+                  for (int t = t4; t < t4 + 4; ++t) fma4(part4, W ? wv[t] : (t0 + t < cn ? 1.f : 0.f), rowv[t]);
                 }
             }
-            add4(acc, part);
+            add4(acc, part4);
             wave_lds_fence();
           }
           l_acc[q * SL + li] = acc;
@@ -554,13 +612,15 @@ __global__ __launch_bounds__(kResThreads) void k_rowsum_res(
         q = grab(p + 1);
         cur = fetch(p + 1, q);
       }
-      phase_step_done(pc, gen * nblk + p);
+      phase_step_done(pc, phase++);
       __syncthreads();  // every workgroup of the XCD is done with this block (or the wait ran out)
     }
     for (int q = grp; q < nslots; q += GPB) {
       const int32_t row = l_row[q];
       if (row < 0 || !col_ok) continue;
       float4 acc = l_acc[q * SL + li];
+      if (PARTS)
+        for (int i = q + 1; i < nslots && l_row[i] == -2; ++i) add4(acc, l_acc[i * SL + li]);
       if (scale != nullptr) scale4(acc, scale[row]);
       st4_stream(out + (int64_t)row * F + col, acc);
     }
@@ -571,14 +631,31 @@ __global__ __launch_bounds__(kResThreads) void k_rowsum_res(
 // 2, 4 or 8 of them (measured at 1 KB rows: 17.8 -> 17.2 ms per layer against 8 slices of 128
 // bytes, 22.9 ms with two of 512); wider rows have 8 slices, one per XCD.  With fewer than 8,
 // workgroup id mod `ns` picks the slice, so XCD k and XCD k + ns share columns and split the rows.
-static bool gcn_slicing(int F, int& SL, int& ns) {
-  // rows of at most 64 floats: one slice, persistent kernel only (a launch per block would move
-  // as many bytes of running sums as of gathered rows)
-  if (F <= 64 && F % 4 == 0 && config_get(kCfgResidentSums)) {
-    SL = 16;
-    ns = 1;
-    return true;
-  }
+// The persistent kernel cuts rows of up to 512 floats into the fewest such slices, of the same width up to a float4, and has four
+// or eight lanes to a row of up to 16 or 32 floats.  (Rows of at most 64 floats are not for a launch per block: it would move as
+// many bytes of running sums as of gathered rows.)
+struct GcnSlices {
+  int SL, ns, sw;  // lanes, slices, columns of a slice
+};
+static GcnSlices gcn_resident_slices(int F) {
+  int ns = 1;
+  while (cdiv(F / 4, ns) > 16) ns *= 2;
+  const int sw = 4 * (int)cdiv(F / 4, ns);
+  return {sw <= 16 ? 4 : sw <= 32 ? 8 : 16, ns, sw};
+}
+// Rows whose slices are not whole lines fetch parts of lines twice, so they take the persistent kernel only where the single-launch kernels
+// leave the L2s for most gathers.  Layer, single launch | persistent, us, power law / even: 20 000 vertices, 2 10^6 edges, 120 columns
+// 208 | 183 / 151 | 167, 200 columns 304 | 276 / 220 | 268; 47 029, 2.2 10^7, 84 (15 MiB) 1274 | 1040 / 866 | 1073, 100 (18 MiB) 1550 | 1116
+// / 1264 | 1144, 200 (36 MiB) 3450 | 2262 / 1978 | 2340; 100 000, 1.5 10^7, 72 (27 MiB) 953 | 920 / 676 | 918, 100 1357 | 1033 / 1590 |
+// 1028, 200 (76 MiB) 2760 | 2019 / 3196 | 2079; 232 965, 1.14 10^8, 72 (64 MiB) 8967 | 6043, 156 19 700 | 11 900, 240 29 200 | 15 500.
+constexpr int64_t kRaggedBytes = (int64_t)16 << 20, kRaggedBytesFar = (int64_t)60 << 20;
+static bool gcn_resident_applies(const gnn_graph_t* g, int F) {
+  if (!config_get(kCfgResidentSums) || g->phase_clock == nullptr || F % 4 != 0 || F > 64 * kGcnSlices) return false;
+  if (F <= 64 || F == 128 || F == 256 || F == 512 || config_get(kCfgResidentSums) == 2) return true;
+  const bool near = gathers_skewed(g, 0) || gathers_skewed(g, 1) ? F >= 80 : F >= 100 && F <= 128;
+  return (int64_t)g->n * F * 4 >= (near ? kRaggedBytes : kRaggedBytesFar);
+}
+static bool gcn_slicing(int F, int& SL, int& ns) {  // of the launches per block
   if (F % 32 != 0) return false;
   const int q = F / 32;
   if (q == 4 || q == 8 || q == 16) {
@@ -597,7 +674,7 @@ static bool gcn_slicing(int F, int& SL, int& ns) {
 static bool gcn_blocked_applies(const gnn_graph_t* g, int F) {
   if (!g->blocked_pays() || config_get(kCfgForceSimple)) return false;
   int SL, ns;
-  return gcn_slicing(F, SL, ns);
+  return gcn_resident_applies(g, F) || gcn_slicing(F, SL, ns);
 }
 
 template <int SL>
@@ -633,34 +710,56 @@ static gnn_status_t launch_rowsum_blocks(const gnn_graph_t* g, int side, const c
 
 __global__ void k_zero_clock(int32_t* __restrict__ clock) { clock[threadIdx.x] = 0; }
 
-// LDS of the persistent kernel; more than 64 KB of dynamic LDS needs the attribute once per instantiation
-constexpr size_t kResLdsLimit = 152 * 1024;
-template <int SL, bool W>
-static gnn_status_t launch_rowsum_resident(const gnn_graph_t* g, int side, const char* name, const float* feat,
-                                           int F, const float* scale, float* out, hipStream_t st,
-                                           const float* bw) {
-  const int ns = F <= 4 * SL ? 1 : F / (4 * SL);
-  const size_t lds = sizeof(int) * (size_t)kResLdsInts<SL, W>;
-  GNN_REQUIRE(lds <= kResLdsLimit, GNN_ERR_UNSUPPORTED, "gcn resident: %zu bytes of LDS", lds);
-  static std::atomic<bool> attr_set{false};
+// one workgroup per CU, a multiple of the slice count so that every XCD serves one slice
+static unsigned gcn_resident_grid() { return (unsigned)(device_cu_count() / kXcds * kXcds); }
+static int64_t gcn_resident_groups(const GcnSlices& sl) { return (int64_t)gcn_resident_grid() / sl.ns * (kResThreads / sl.SL); }
+// 32-bit byte offsets (and 24-bit multiplies) reach every gathered row
+static bool gcn_resident_narrow(const gnn_graph_t* g, int F) {
+  return (int64_t)g->n * F * 4 < ((int64_t)1 << 32) && g->n < (1 << 24) && !config_get(kCfgWideOffsets);
+}
+
+template <int SL, bool W, bool NARROW, bool PARTS>
+static gnn_status_t launch_rowsum_resident_as(const gnn_graph_t* g, int side, const char* name, const float* feat, int F,
+                                              const GcnSlices& sl, const float* scale, float* out, hipStream_t st, const float* bw) {
+  static std::atomic<bool> attr_set{false};  // more than 64 KB of dynamic LDS, once per instantiation
   if (!attr_set.load(std::memory_order_acquire)) {
-    GNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_rowsum_res<SL, W>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResLdsLimit));
+    GNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_rowsum_res<SL, W, NARROW, PARTS>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsBytes));
     attr_set.store(true, std::memory_order_release);
   }
-  // one workgroup per CU, a multiple of the slice count so that every XCD serves one slice
-  const unsigned grid = (unsigned)(device_cu_count() / kXcds * kXcds);
+  const unsigned grid = gcn_resident_grid();
   ProfScope p(name, st);
-  int32_t* clock = g->phase_clock;
-  if (clock != nullptr) {
-    k_zero_clock<<<1, kXcds * kClockStride, 0, st>>>(clock);
-    GNN_LAUNCH_CHECK();
-  }
-  k_rowsum_res<SL, W><<<grid, kResThreads, lds, st>>>(g->n, g->order[side], reinterpret_cast<const int2*>(g->bseg[side]),
-                                                     g->bcol[side], feat, g->block_cols, g->nblk, F, ns, scale, out, bw,
-                                                     clock, (int)config_get(kCfgResidentSpin), (int)config_get(kCfgResidentSyncEvery));
+  k_zero_clock<<<1, kXcds * kClockStride, 0, st>>>(g->phase_clock);
+  GNN_LAUNCH_CHECK();
+  constexpr int slots = res_slots<SL, W>();
+  k_rowsum_res<SL, W, NARROW, PARTS><<<grid, kResThreads, kResLdsBytes, st>>>(
+      g->n, g->order[side], reinterpret_cast<const int2*>(g->bseg[side]), g->bcol[side], feat, g->block_cols, g->nblk, F, sl.ns,
+      sl.sw, scale, out, bw, g->phase_clock, (int)config_get(kCfgResidentSpin), (int)config_get(kCfgResidentSyncEvery),
+      PARTS ? cut_long_rows(g, side, gcn_resident_groups(sl), grid / sl.ns, slots) : RowParts{});
   GNN_LAUNCH_CHECK();
   return GNN_OK;
+}
+
+template <int SL, bool W>
+static gnn_status_t launch_rowsum_resident_of(const gnn_graph_t* g, int side, const char* name, const float* feat, int F,
+                                              const GcnSlices& sl, const float* scale, float* out, hipStream_t st, const float* bw) {
+  const bool parts = has_long_rows(g, side, gcn_resident_groups(sl));
+  if (gcn_resident_narrow(g, F))
+    return parts ? launch_rowsum_resident_as<SL, W, true, true>(g, side, name, feat, F, sl, scale, out, st, bw)
+                 : launch_rowsum_resident_as<SL, W, true, false>(g, side, name, feat, F, sl, scale, out, st, bw);
+  return parts ? launch_rowsum_resident_as<SL, W, false, true>(g, side, name, feat, F, sl, scale, out, st, bw)
+               : launch_rowsum_resident_as<SL, W, false, false>(g, side, name, feat, F, sl, scale, out, st, bw);
+}
+
+template <bool W>
+static gnn_status_t launch_rowsum_resident(const gnn_graph_t* g, int side, const char* name, const float* feat, int F,
+                                           const float* scale, float* out, hipStream_t st, const float* bw) {
+  const GcnSlices sl = gcn_resident_slices(F);
+  switch (sl.SL) {
+    case 4: return launch_rowsum_resident_of<4, W>(g, side, name, feat, F, sl, scale, out, st, bw);
+    case 8: return launch_rowsum_resident_of<8, W>(g, side, name, feat, F, sl, scale, out, st, bw);
+    default: return launch_rowsum_resident_of<16, W>(g, side, name, feat, F, sl, scale, out, st, bw);
+  }
 }
 
 // Gathered rows in flight per lane: eight, four of the narrowest and widest rows, and two where gathers are even (gathers_abreast) and
@@ -795,10 +894,9 @@ static bool use_edge_balanced(const gnn_graph_t* g, int side) {
 static gnn_status_t gcn_aggregate_vertex(const gnn_graph_t* g, int side, const char* name, const float* feat,
                                          int F, const float* scale, float* out, hipStream_t st) {
   if (gcn_blocked_applies(g, F)) {
+    if (gcn_resident_applies(g, F)) return launch_rowsum_resident<false>(g, side, name, feat, F, scale, out, st, nullptr);
     int SL = 0, ns = 0;
     gcn_slicing(F, SL, ns);
-    if (config_get(kCfgResidentSums) && SL == 16)
-      return launch_rowsum_resident<16, false>(g, side, name, feat, F, scale, out, st, nullptr);
     switch (SL) {
       case 8: GNN_TRY(launch_rowsum_blocks<8>(g, side, name, feat, F, out, st)); break;
       case 16: GNN_TRY(launch_rowsum_blocks<16>(g, side, name, feat, F, out, st)); break;
@@ -829,10 +927,10 @@ static gnn_status_t gcn_aggregate_weighted(const gnn_graph_t* g, const gnn_edge_
   if (config_get(kCfgGcnMapping) == 1)
     return dispatch_rowsum<RowsumWeightedEbLauncher>(g, side, name, feat, F, ew->w_side[side], out, st);
   if (gcn_blocked_applies(g, F) && ew->w_blk[side] != nullptr) {
+    if (gcn_resident_applies(g, F))
+      return launch_rowsum_resident<true>(g, side, name, feat, F, nullptr, out, st, ew->w_blk[side]);
     int SL = 0, ns = 0;
     gcn_slicing(F, SL, ns);
-    if (config_get(kCfgResidentSums) && SL == 16)
-      return launch_rowsum_resident<16, true>(g, side, name, feat, F, nullptr, out, st, ew->w_blk[side]);
     switch (SL) {
       case 8: return launch_rowsum_blocks<8>(g, side, name, feat, F, out, st, ew->w_blk[side]);
       case 16: return launch_rowsum_blocks<16>(g, side, name, feat, F, out, st, ew->w_blk[side]);
@@ -1042,8 +1140,11 @@ extern "C" gnn_status_t gnn_gcn_blocked_kernel_name(const gnn_graph_t* g, int fo
   if (fout <= 0 || !gcn_blocked_applies(g, fout) || config_get(kCfgGcnMapping) == 1) return GNN_OK;
   int SL = 0, ns = 0;
   gcn_slicing(fout, SL, ns);
-  if (config_get(kCfgResidentSums) && SL == 16 && g->phase_clock != nullptr)
-    std::snprintf(buf, len, "k_rowsum_res<16, %s>", weighted ? "true" : "false");
+  const GcnSlices sl = gcn_resident_slices(fout);
+  if (gcn_resident_applies(g, fout))
+    std::snprintf(buf, len, "k_rowsum_res<%d, %s, %s, %s>", sl.SL, weighted ? "true" : "false",
+                  gcn_resident_narrow(g, fout) ? "true" : "false",
+                  has_long_rows(g, 0, gcn_resident_groups(sl)) ? "true" : "false");
   else
     std::snprintf(buf, len, "k_rowsum_blk<%d, %s, %s>", SL, ns >= 4 ? "true" : "false", weighted ? "true" : "false");
   return GNN_OK;

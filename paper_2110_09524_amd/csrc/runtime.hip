@@ -36,7 +36,7 @@ void clear_error() { g_err[0] = 0; }
 // gather_precision: 0 the column-blocked GAT kernels gather fp32 rows, 1 they gather an fp16 copy
 // merge_blocks: 1 (default) adjacent sparse column blocks share one launch of a blocked kernel
 // (read at gnn_graph_create), 0 every block has its own launch
-// wide_offsets: 1 makes the column-blocked GAT and the narrow MoNet kernels address gathered rows with 64-bit offsets
+// wide_offsets: 1 makes the column-blocked GAT and GCN and the narrow MoNet kernels address gathered rows with 64-bit offsets
 // also where 32 bits reach every row (the path of matrices of 4 GB and more; a test hook)
 // resident_sums: 1 (default) lets the column-blocked aggregations run all blocks in one persistent
 // launch that keeps the rows' running sums on the chip (LDS); 2: the MoNet forward pass on every graph with

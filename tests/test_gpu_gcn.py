@@ -428,3 +428,43 @@ def test_edge_weighted_edge_balanced_mapping(edge_balanced, fin, fout):
     c["ew"] = rng.uniform(-2.0, 2.0, len(indices)).astype(np.float32)
     res, _ = check_edge(c)
     assert (res["out"][np.diff(indptr) == 0] == 0).all()
+
+
+@pytest.mark.parametrize("fout,lanes", [(4, 4), (16, 4), (20, 8), (32, 8), (36, 16), (64, 16), (68, 16), (100, 16), (132, 16),
+                                        (260, 16), (500, 16), (512, 16)])
+@pytest.mark.parametrize("hub", [False, True])
+def test_widths_of_the_persistent_launch(fout, lanes, hub):
+    """Groups of 4, 8 and 16 lanes, one, two, four and eight slices with a last one that is narrower, rows whole and in parts,
+    32-bit and 64-bit row offsets; without and with a weight per edge."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import dev, run_gcn
+    print(f"gcn: persistent launch fout={fout} hub={hub}", flush=True)
+    rng = np.random.default_rng(fout)
+    n = 1500
+    indptr, indices = random_graph(rng, n, 20000, self_loops=False, duplicates=True)
+    if hub:   # a row of all vertices, a vertex in all rows but every 50th, which is empty
+        rows = [np.append(indices[indptr[v]:indptr[v + 1]], 11)[:len(indices) * (v % 50 > 0)] for v in range(n)]
+        rows[7] = np.arange(n)
+        indptr = np.concatenate(([0], np.cumsum([len(r) for r in rows]))).astype(np.int32)
+        indices = np.concatenate(rows).astype(np.int32)
+    c = synth(rng, indptr, indices, 12, fout)
+    c["ew"] = rng.uniform(-2.0, 2.0, len(indices)).astype(np.float32)
+    pk.gnn_config_set("block_cols", 300)
+    pk.gnn_config_set("resident_sums", 2)
+    try:
+        g = pk.Graph(dev(indptr), dev(indices))
+        for weighted in (False, True):
+            flags = [str(x).lower() for x in (weighted, True, hub)]
+            assert pk.gnn_gcn_blocked_kernel_name(g, fout, weighted) == f"k_rowsum_res<{lanes}, {', '.join(flags)}>"
+        res = check(c, graph=g)
+        edge, _ = check_edge(c)
+        pk.gnn_config_set("wide_offsets", 1)
+        wide, wide_edge = run_gcn(c, graph=g), run_gcn_edge(c)[0]
+        g.close()
+    finally:
+        pk.gnn_config_set("wide_offsets", 0)
+        pk.gnn_config_set("resident_sums", 1)
+        pk.gnn_config_set("block_cols", 12288)
+    for a, b in ((res, wide), (edge, wide_edge)):
+        for key in a:
+            assert np.array_equal(a[key], b[key]), key
