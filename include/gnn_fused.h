@@ -168,10 +168,12 @@ gnn_status_t gnn_release_cached_memory(void);
  *                           hit rates suffer.  0: one launch per block or group of blocks.
  *                           Both give the same bits, but for rows far longer than the mean:
  *                           the one launch sums them in parts.  GAT layers whose heads have 8, 16
- *                           or 32 columns (rows of 64, 128, 256 or 512) and gnn_monet_fwd have such
- *                           a launch in place of their other kernels, where rules on the graph find
- *                           it faster, with 2 on every graph with column blocks, and with 0 never;
- *                           its sums are grouped by block, so they round differently.
+ *                           or 32 columns (rows of 64, 128, 256 or 512), GCN rows of other widths
+ *                           up to 512, gnn_monet_fwd and gnn_gmmp_fwd have such a launch in place of
+ *                           their other kernels, where rules on the graph find it faster, with 2 on
+ *                           every graph with column blocks (the latter two: whose rows have their
+ *                           edges in the order of the blocks), and with 0 never; its sums are
+ *                           grouped by block, so they round differently.
  *   "resident_spin"         polls after which a workgroup of that launch stops waiting for the
  *                           others of its XCD (default 4096; 0 = never wait; meant for tests)
  *   "resident_sync_every"   the workgroups of an XCD meet after every k-th column block instead

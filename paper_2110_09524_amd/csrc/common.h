@@ -161,6 +161,7 @@ struct gnn_graph {
   int32_t* bucket_offsets[2];            // device copies
   int32_t h_bucket_offsets[2][GNN_NUM_BUCKETS + 1];  // host copies
   int32_t max_degree[2];
+  bool in_block_order[2];  // with column blocks: every row's edges are in the order of their blocks
   // Tiles: consecutive runs of vertices that no edge leaves (the clouds of a batch, say), n_tiles of them from
   // tile_start[i] to tile_start[i + 1], the longest of max_tile vertices; n_tiles = 0 when there are none short enough.
   int32_t* tile_start;

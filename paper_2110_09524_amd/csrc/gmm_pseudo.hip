@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "row_parts.h"
 #include "rowgroup.h"
 
 namespace gnn {
@@ -518,22 +519,18 @@ __global__ void k_monet_zero_clock(int32_t* __restrict__ p) { p[threadIdx.x] = 0
 // 100 000 x 200, K = 3 360 -> 290.
 constexpr int kMonetThreads = 1024;
 constexpr int kMonetTabPerThread = 12;
-constexpr int kMonetLevels = 6;
-// the first rows[i] rows of a workgroup, in the order of their degrees, are cut into at least 2^(i + 1) parts
-struct MonetParts {
-  int rows[kMonetLevels];
-};
 template <int G, int KT>
 constexpr int kMonetGroupInts = (kMonetThreads / G) * (1 + KT) * G;  // idx, weights of all groups
 // a slot: sum, (beg, end) of two blocks, row, c of the row
 constexpr int monet_slot_ints(int F) { return F + 4 + 1 + 1; }
 
-template <int G, int KT, int RT>
+template <int G, bool PROJ, int KT, int RT>
 __global__ __launch_bounds__(kMonetThreads) void k_monet_res(
     int32_t n_rows, const int32_t* __restrict__ order, const int2* __restrict__ bseg /* [nblk][n_rows] */,
-    const int32_t* __restrict__ bcol, const float* __restrict__ hk, ProjArgs pa, const float* __restrict__ mu,
-    const float* __restrict__ inv_sigma, PsParams pm, int32_t block_cols, int nblk, int cap /* slots the LDS holds */,
-    MonetParts cut, int32_t* __restrict__ clock, int spin_limit, int sync_every, float* __restrict__ out) {
+    const int32_t* __restrict__ indptr, const int32_t* __restrict__ cols /* PROJ: block by block, else row by row */,
+    const float* __restrict__ hk, const float* __restrict__ pseudo, ProjArgs pa, const float* __restrict__ mu, const float* __restrict__ inv_sigma, PsParams pm,
+    int32_t block_cols, int nblk, int cap /* slots the LDS holds */, RowParts cut, int32_t* __restrict__ clock, int spin_limit,
+    int sync_every, float* __restrict__ out) {
   constexpr int GPB = kMonetThreads / G, U = 8;
   extern __shared__ __align__(16) int lds_mr[];
   const int lane = threadIdx.x & 63, li = threadIdx.x & (G - 1), grp = threadIdx.x / G;
@@ -541,7 +538,7 @@ __global__ __launch_bounds__(kMonetThreads) void k_monet_res(
   const int K = pm.K, R = pm.R, F = pm.F, KF = K * F, F4 = F / 4;
   const float inv_k = 1.f / (float)K;
   const PsKernels<KT, RT> pk = load_kernels<KT, RT>(mu, inv_sigma, K, R);
-  const ProjRegs<RT> pq = load_proj<RT>(pa, R);
+  const ProjRegs<RT> pq = PROJ ? load_proj<RT>(pa, R) : ProjRegs<RT>{};
   const bool col_ok = li < K * F4;
   const int myk = col_ok ? li / F4 : 0;
   const uint32_t lane_off = 16u * li;
@@ -558,7 +555,7 @@ __global__ __launch_bounds__(kMonetThreads) void k_monet_res(
   float tab[kMonetTabPerThread] = {};
   auto fetch_table = [&](int p) {
 #pragma unroll
-    for (int i = 0; i < kMonetTabPerThread; ++i) {
+    for (int i = 0; i < (PROJ ? kMonetTabPerThread : 0); ++i) {
       const int c = i * kMonetThreads + threadIdx.x;
       const int64_t u = (int64_t)p * block_cols + c;
       if (c < block_cols && u < n_rows) tab[i] = pa.c[u];
@@ -566,7 +563,7 @@ __global__ __launch_bounds__(kMonetThreads) void k_monet_res(
   };
   auto store_table = [&]() {
 #pragma unroll
-    for (int i = 0; i < kMonetTabPerThread; ++i) {
+    for (int i = 0; i < (PROJ ? kMonetTabPerThread : 0); ++i) {
       const int c = i * kMonetThreads + threadIdx.x;
       if (c < block_cols) l_tab[c] = tab[i];
     }
@@ -574,19 +571,6 @@ __global__ __launch_bounds__(kMonetThreads) void k_monet_res(
   fetch_table(0);
   store_table();
 
-  // parts of the workgroup's j-th row, as a power of two; slots before it
-  auto log_parts = [&](int j) {
-    int l = 0;
-#pragma unroll
-    for (int i = 0; i < kMonetLevels; ++i) l += j < cut.rows[i] ? 1 : 0;
-    return l;
-  };
-  auto slots_before = [&](int j) {
-    int s = j;
-#pragma unroll
-    for (int i = 0; i < kMonetLevels; ++i) s += min(j, cut.rows[i]) << i;  // level i doubles: 2^i more slots
-    return s;
-  };
   const int rows_here = (int)((n_rows + nwg - 1) / nwg);
   // workgroups go to the XCDs round-robin: those with the same id mod 8 share an L2
   PhaseClock pc{clock ? clock + (blockIdx.x % kXcds) * kClockStride : nullptr, (int)(gridDim.x / kXcds), spin_limit,
@@ -597,36 +581,38 @@ __global__ __launch_bounds__(kMonetThreads) void k_monet_res(
 
   int phase = 0;
   for (int j0 = 0, j1; j0 < rows_here; j0 = j1) {
-    // rows j0 .. j1 - 1: as many as there are slots for (a row has at most 2^kMonetLevels)
-    const int s0 = slots_before(j0);
-    j1 = j0;
-    for (int step = 1 << 30; step > 0; step >>= 1)
-      if (step <= rows_here - j1 && slots_before(j1 + step) - s0 <= cap) j1 += step;
-    const int nslots = slots_before(j1) - s0;
+    // rows j0 .. j1 - 1: as many as there are slots for (a row's parts fit: see the launch)
+    const int s0 = slots_before(cut, j0);
+    j1 = rows_that_fit(cut, j0, rows_here, cap);
+    const int nslots = slots_before(cut, j1) - s0;
     // thread q: slot q
     int64_t pos = -1;
     int part = 0, logp = 0;
+    int32_t row = -1, next = 0;  // the row, and where its edges of the next block begin
     if ((int)threadIdx.x < nslots) {
-      int lo = j0, hi = j1;  // the last row that starts at or before this slot
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (slots_before(mid) - s0 <= (int)threadIdx.x) lo = mid; else hi = mid;
-      }
-      part = (int)threadIdx.x - (slots_before(lo) - s0);
-      logp = log_parts(lo);
+      const int lo = row_of_slot(cut, j0, j1, threadIdx.x);
+      part = (int)threadIdx.x - (slots_before(cut, lo) - s0);
+      logp = log_parts(cut, lo);
       const int64_t r = (int64_t)lo * nwg + ((lo & 1) ? nwg - 1 - wg : wg);
-      if (r < n_rows) pos = r;
+      if (r < n_rows) {
+        pos = r;
+        row = order[r];
+        if (!PROJ) next = indptr[row];
+      }
     }
-    auto bounds = [&](int p) {  // this thread's piece of its row's segment of block p
+    // This thread's piece of its row's segment of block p, asked for block by block.  Coordinates of edges are in the order of the rows, which
+    // is walked then; the rows' edges are in the order of the blocks.  (With projected ones, too, 2750 us a training pass, see above, not 2695.)
+    auto bounds = [&](int p) {
       if (pos < 0) return make_int2(0, 0);
       const int2 sg = bseg[(int64_t)p * n_rows + pos];
       const int64_t len = sg.y - sg.x;
-      return make_int2(sg.x + (int)(len * part >> logp), sg.x + (int)(len * (part + 1) >> logp));
+      const int beg = PROJ ? sg.x : next;
+      next += (int)len;
+      return make_int2(beg + (int)(len * part >> logp), beg + (int)(len * (part + 1) >> logp));
     };
     if ((int)threadIdx.x < nslots) {
-      const int32_t row = pos >= 0 ? order[pos] : -1;
       l_row[threadIdx.x] = part == 0 ? row : -2;  // -2: a further part of the row before
-      l_cv[threadIdx.x] = row >= 0 ? pa.c[row] : 0.f;
+      if (PROJ) l_cv[threadIdx.x] = row >= 0 ? pa.c[row] : 0.f;
       l_seg[threadIdx.x] = bounds(0);
     }
     for (int i = threadIdx.x; i < nslots * F4; i += kMonetThreads) l_sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -644,7 +630,7 @@ __global__ __launch_bounds__(kMonetThreads) void k_monet_res(
       const int2 sg = l_seg[(p & 1) * cap + q];
       it.beg = sg.x;
       it.end = sg.y;
-      if (it.beg + li < it.end) it.c_first = bcol[it.beg + li];
+      if (it.beg + li < it.end) it.c_first = cols[it.beg + li];
       return it;
     };
     int q = grab(0);
@@ -662,17 +648,23 @@ __global__ __launch_bounds__(kMonetThreads) void k_monet_res(
         const int qn = grab(p);
         const Item nxt = fetch(p, qn);
         if (cur.beg < cur.end) {
-          const float cv = l_cv[q];
+          const float cv = PROJ ? l_cv[q] : 0.f;
           float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), part4 = acc;
           int folded = 0;
           int32_t c_next = cur.c_first;
           for (int32_t e0 = cur.beg; e0 < cur.end; e0 += G) {
             const bool e_ok = e0 + li < cur.end;
             const int32_t c = e_ok ? c_next : col_begin;
-            if (e0 + G + li < cur.end) c_next = bcol[e0 + G + li];
+            if (e0 + G + li < cur.end) c_next = cols[e0 + G + li];
             wave_lds_fence();  // the previous chunk's reads are done
             l_off[li] = e_ok ? __umul24((uint32_t)c, 4u * KF) : kPastTable;
             wave_lds_fence();
+            float m[RT];
+            if (!PROJ) {
+#pragma unroll
+              for (int d = 0; d < RT; ++d) m[d] = 0.f;
+              if (e_ok) load_pseudo(pseudo, e0 + li, R, m);
+            }
             float4 rowv[U];
             const int cnt = cur.end - e0;
             auto rows_of = [&](int t0) {
@@ -681,8 +673,7 @@ __global__ __launch_bounds__(kMonetThreads) void k_monet_res(
               if (col_ok) gather_rows(true, table, hk, KF, off, lane_off, cnt - t0, rowv);
             };
             rows_of(0);
-            float m[RT];
-            project(pq, R, l_tab[c - col_begin], cv, m);
+            if (PROJ) project(pq, R, l_tab[c - col_begin], cv, m);
 #pragma unroll
             for (int k = 0; k < KT; ++k) {
               const float w = gauss_k(pk, k, m) * inv_k;
@@ -1215,6 +1206,8 @@ static gnn_status_t with_rows_in_flight(const gnn_graph_t* g, int KF, Fn fn) {
 // 16 columns, us: uneven 13 000 vertices, 5 10^5 edges 25 | 30 (K = 4: 40 | 33), 20 000, 1.2 10^6 44 | 34, 13 000, 1.3 10^6 40 | 34, 14 000, 4.2 10^6
 // 125 | 67 (K = 3); even 30 000, 3 10^6 41 | 46, 50 000, 4.5 10^6 101 | 102 (3 x 20), 5 10^6 104 | 98 (K = 4), 20 000, 6 10^6 60 | 58 (8
 // columns), 25 000, 10^7 179 | 154 (3 x 20), 100 000, 1.5 10^7 169 | 159 (8).
+// Rows whose edges are not in the order of the blocks leave a graph to k_gmmp_fwd_nr: coordinates of edges could not be found block by
+// block, and projected and given coordinates have the same sums, bit for bit.
 constexpr int64_t kMonetEdgesUneven = (int64_t)1 << 20, kMonetEdgesEven = (int64_t)5 << 20;
 constexpr int64_t kMonetEdgesPerBlock = 16;  // of a row, on average: fewer were not timed
 static bool monet_res_applies(const gnn_graph_t* g, int KF) {
@@ -1222,16 +1215,16 @@ static bool monet_res_applies(const gnn_graph_t* g, int KF) {
   const bool enough = g->nnz >= (uneven ? kMonetEdgesUneven : kMonetEdgesEven) &&
                       g->nnz >= kMonetEdgesPerBlock * (int64_t)g->n * g->nblk;
   return (enough || config_get(kCfgResidentSums) == 2) && g->blocked_pays() && !config_get(kCfgForceSimple) && config_get(kCfgResidentSums) && g->phase_clock != nullptr &&
-         g->block_cols <= kMonetTabPerThread * kMonetThreads && narrow_table(g->n, KF) && !config_get(kCfgWideOffsets);
+         g->in_block_order[0] && g->block_cols <= kMonetTabPerThread * kMonetThreads && narrow_table(g->n, KF) && !config_get(kCfgWideOffsets);
 }
 
-template <int G, int KT, int RT>
-static gnn_status_t launch_monet_res(const gnn_graph_t* g, const float* hk, const ProjArgs& pa, const float* mu,
+template <int G, bool PROJ, int KT, int RT>
+static gnn_status_t launch_monet_res(const gnn_graph_t* g, const float* hk, const float* pseudo, const ProjArgs& pa, const float* mu,
                                      const float* inv_sigma, const PsParams& pm, float* out, hipStream_t st) {
   constexpr int kLds = 160 * 1024;
   static std::atomic<bool> allowed{false};
   if (!allowed.load(std::memory_order_acquire)) {
-    GNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_monet_res<G, KT, RT>),
+    GNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_monet_res<G, PROJ, KT, RT>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kLds));
     allowed.store(true, std::memory_order_release);
   }
@@ -1239,18 +1232,13 @@ static gnn_status_t launch_monet_res(const gnn_graph_t* g, const float* hk, cons
   const int room = (kLds / 4 - 2 - (g->block_cols + 3) / 4 * 4 - kMonetGroupInts<G, KT>) / monet_slot_ints(pm.F);
   const int cap = std::min(room, kMonetThreads) / 4 * 4;
   // parts of more than half of what a group has on average, and at most twice that (a quarter as long: 970 -> 970 us, see above)
-  MonetParts cut{};
-  const int64_t share = std::max<int64_t>(64, g->nnz / (grid * (kMonetThreads / G)));
-  for (int i = 0; i < kMonetLevels; ++i) {
-    int k = 0;  // rows of at least 2^k edges are cut into 2^(i + 1): the first power of two above share 2^i
-    while (k < 31 && ((int64_t)1 << k) <= share << i) ++k;
-    cut.rows[i] = k >= 31 ? 0 : (int)cdiv(g->h_bucket_offsets[0][32 - k], grid);
-  }
+  const RowParts cut = cut_rows(g, 0, std::max<int64_t>(64, g->nnz / (grid * (kMonetThreads / G))), grid, cap);
   k_monet_zero_clock<<<1, kXcds * kClockStride, 0, st>>>(g->phase_clock);
   GNN_LAUNCH_CHECK();
-  k_monet_res<G, KT, RT><<<(unsigned)grid, kMonetThreads, kLds, st>>>(
-      g->n, g->order[0], reinterpret_cast<const int2*>(g->bseg[0]), g->bcol[0], hk, pa, mu, inv_sigma, pm, g->block_cols,
-      g->nblk, cap, cut, g->phase_clock, (int)config_get(kCfgResidentSpin), (int)config_get(kCfgResidentSyncEvery), out);
+  k_monet_res<G, PROJ, KT, RT><<<(unsigned)grid, kMonetThreads, kLds, st>>>(
+      g->n, g->order[0], reinterpret_cast<const int2*>(g->bseg[0]), g->indptr, PROJ ? g->bcol[0] : g->indices, hk, pseudo, pa, mu,
+      inv_sigma, pm, g->block_cols, g->nblk, cap, cut, g->phase_clock, (int)config_get(kCfgResidentSpin),
+      (int)config_get(kCfgResidentSyncEvery), out);
   GNN_LAUNCH_CHECK();
   return GNN_OK;
 }
@@ -1388,6 +1376,8 @@ extern "C" gnn_status_t gnn_gmmp_fwd(const gnn_graph_t* g, int fin, int fout, in
       if (grid != 0) {
         return for_kernels(k, r, [&](auto kernels, auto dims) -> gnn_status_t {
           constexpr int KT = decltype(kernels)::value, RT = decltype(dims)::value;
+          if (monet_res_applies(g, k * fout))
+            return launch_monet_res<GL, false, KT, RT>(g, hk, pseudo, ProjArgs{}, mu, inv_sigma, pm, out, st);
           return with_rows_in_flight(g, k * fout, [&](auto u, unsigned lds) -> gnn_status_t {
             k_gmmp_fwd_nr<GL, false, KT, RT, decltype(u)::value><<<grid, kPsBlock, lds, st>>>(rl, g->rows[0], g->indices, hk, pseudo,
                                                                                               ProjArgs{}, mu, inv_sigma, pm, out);
@@ -1604,7 +1594,7 @@ extern "C" gnn_status_t gnn_monet_fwd(const gnn_graph_t* g, int fin, int fout, i
       return for_kernels(k, r, [&](auto kernels, auto dims) -> gnn_status_t {
         constexpr int KT = decltype(kernels)::value, RT = decltype(dims)::value;
         if (monet_res_applies(g, k * fout))
-          return launch_monet_res<GL, KT, RT>(g, hk, pa, mu, inv_sigma, pm, out, st);
+          return launch_monet_res<GL, true, KT, RT>(g, hk, nullptr, pa, mu, inv_sigma, pm, out, st);
         return with_rows_in_flight(g, k * fout, [&](auto u, unsigned lds) -> gnn_status_t {
           k_gmmp_fwd_nr<GL, true, KT, RT, decltype(u)::value><<<grid, kPsBlock, lds, st>>>(rl, g->rows[0], g->indices, hk, nullptr, pa, mu,
                                                                                            inv_sigma, pm, out);

@@ -657,9 +657,10 @@ __global__ __launch_bounds__(256) void k_degree_and_bucket(int32_t n, const int3
 
 // key of an edge for the column-blocked order: (block of its column) * n + its row.
 // One wavefront per row, lanes strided over the row's edges (coalesced, no search).
+// disorder: set where a row's edges are not in the order of their blocks.
 __global__ void k_block_keys(int32_t n, int64_t nnz, const int32_t* __restrict__ ptr,
                              const int32_t* __restrict__ cols, int32_t block_cols,
-                             uint64_t* __restrict__ keys, int32_t* __restrict__ counts) {
+                             uint64_t* __restrict__ keys, int32_t* __restrict__ counts, int32_t* __restrict__ disorder) {
   const int lane = threadIdx.x & 63;
   const int64_t row = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
   if (row >= n) return;
@@ -667,6 +668,8 @@ __global__ void k_block_keys(int32_t n, int64_t nnz, const int32_t* __restrict__
   // The lanes of a wavefront share the row, and within a row equal blocks usually sit next to each
   // other (sorted columns): only the first lane of a run of equal blocks adds the run's length
   // (one atomic per run instead of one per edge; integer counts, so the order does not matter).
+  int32_t b_last = -1;  // of the edge before i0
+  bool falls = false;
   for (int32_t i0 = beg; i0 < end; i0 += 64) {
     const int32_t i = i0 + lane;
     const bool valid = i < end;
@@ -674,6 +677,8 @@ __global__ void k_block_keys(int32_t n, int64_t nnz, const int32_t* __restrict__
     const uint64_t key = (uint64_t)(uint32_t)b * (uint64_t)n + (uint64_t)row;
     if (valid) keys[i] = key;
     const int32_t b_prev = __shfl_up(b, 1, 64);
+    falls |= valid && b < (lane == 0 ? b_last : b_prev);
+    b_last = __shfl(b, 63, 64);
     const bool head = valid && (lane == 0 || b != b_prev);
     const uint64_t heads = __ballot(head);
     const int nvalid = min(64, end - i0);  // the valid lanes are a prefix
@@ -683,6 +688,7 @@ __global__ void k_block_keys(int32_t n, int64_t nnz, const int32_t* __restrict__
       atomicAdd(&counts[key], next - lane);
     }
   }
+  if (falls) *disorder = 1;
 }
 
 // bseg[b*n + r] = (bptr[b*n + row], bptr[b*n + row + 1]) with row = order[r]: the blocked
@@ -1001,7 +1007,10 @@ static gnn_status_t build_blocked(gnn_graph* g, int side, const int32_t* ptr, co
   GNN_HIP(pool_alloc((void**)&g->bptr[side], sizeof(int32_t) * ((size_t)slots + 1)));
   GNN_HIP(pool_alloc((void**)&g->bcol[side], sizeof(int32_t) * (size_t)nnz));
   GNN_HIP(hipMemsetAsync(counts, 0, sizeof(int32_t) * ((size_t)slots + 1), st));
-  k_block_keys<<<cdiv((int64_t)n * 64, thr), thr, 0, st>>>(n, nnz, ptr, cols, g->block_cols, keys, counts);
+  int32_t* starts = nullptr;  // of the blocks; then whether edges are out of their order
+  GNN_HIP(tmp.alloc(&starts, (size_t)g->nblk + 2));
+  GNN_HIP(hipMemsetAsync(starts + g->nblk + 1, 0, sizeof(int32_t), st));
+  k_block_keys<<<cdiv((int64_t)n * 64, thr), thr, 0, st>>>(n, nnz, ptr, cols, g->block_cols, keys, counts, starts + g->nblk + 1);
   GNN_LAUNCH_CHECK();
   {
     size_t bytes = 0;
@@ -1028,14 +1037,14 @@ static gnn_status_t build_blocked(gnn_graph* g, int side, const int32_t* ptr, co
                                                      reinterpret_cast<int2*>(g->bseg[side]));
   GNN_LAUNCH_CHECK();
   // edges per block, for the host's choice of kernel variant: bptr[b * n], b = 0 .. nblk
-  g->h_block_begin[side].assign((size_t)g->nblk + 1, 0);
-  int32_t* starts = nullptr;
-  GNN_HIP(tmp.alloc(&starts, (size_t)g->nblk + 1));
+  g->h_block_begin[side].assign((size_t)g->nblk + 2, 0);
   k_gather_strided<<<cdiv((int64_t)g->nblk + 1, thr), thr, 0, st>>>(g->nblk + 1, g->bptr[side], n, starts);
   GNN_LAUNCH_CHECK();
-  GNN_HIP(hipMemcpyAsync(g->h_block_begin[side].data(), starts, sizeof(int32_t) * ((size_t)g->nblk + 1),
+  GNN_HIP(hipMemcpyAsync(g->h_block_begin[side].data(), starts, sizeof(int32_t) * ((size_t)g->nblk + 2),
                          hipMemcpyDeviceToHost, st));
   GNN_HIP(hipStreamSynchronize(st));
+  g->in_block_order[side] = g->h_block_begin[side].back() == 0;
+  g->h_block_begin[side].pop_back();
   const bool merge = config_get(kCfgMergeBlocks) != 0;
   g->h_group[side][0] = launch_groups(g->h_block_begin[side], n, g->block_cols, merge, 6.0);
   g->h_group[side][1] = launch_groups(g->h_block_begin[side], n, g->block_cols, merge, 10.0);

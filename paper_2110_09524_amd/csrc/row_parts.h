@@ -71,15 +71,18 @@ inline bool has_long_rows(const gnn_graph_t* g, int side, int64_t groups) {
   const int64_t longest = g->max_degree[side];
   return 10 * longest > 7 * (g->nnz / groups) && longest > 2 * kPieceEdges * g->nblk && longest * g->n > 4 * g->nnz;
 }
-inline RowParts cut_long_rows(const gnn_graph_t* g, int side, int64_t groups, int64_t workgroups, int slots) {
+// into parts of more than half of `piece` edges, and at most twice that
+inline RowParts cut_rows(const gnn_graph_t* g, int side, int64_t piece, int64_t workgroups, int slots) {
   RowParts cut{};
-  const int64_t piece = std::max<int64_t>(kPieceEdges * g->nblk, g->nnz / groups / 2);
   for (int i = 0; i < kPartLevels && (2 << i) <= slots; ++i) {
     int k = 0;  // rows of at least 2^k edges are cut into 2^(i + 1): the first power of two above piece 2^i
     while (k < 31 && ((int64_t)1 << k) <= piece << i) ++k;
     cut.rows[i] = k >= 31 ? 0 : (int)cdiv(g->h_bucket_offsets[side][32 - k], workgroups);
   }
   return cut;
+}
+inline RowParts cut_long_rows(const gnn_graph_t* g, int side, int64_t groups, int64_t workgroups, int slots) {
+  return cut_rows(g, side, std::max<int64_t>(kPieceEdges * g->nblk, g->nnz / groups / 2), workgroups, slots);
 }
 
 }  // namespace gnn

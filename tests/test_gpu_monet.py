@@ -163,8 +163,9 @@ def test_hub_empty_rows_no_edges_optional_gx_and_limits():
                                                  (16, 4, 4, 500), (20, 3, 2, 256), (12, 3, 1, 1400), (8, 2, 1, 100)])
 def test_all_column_blocks_in_one_launch(fout, K, r, block_cols):
     """The forward launch that keeps its sums in LDS: segments of no, few and many edges, rows cut into parts (one of 40 000
-    edges into 64), rows without edges, and more rows than a workgroup holds.  Its sums are grouped by block, so they are compared with
-    the oracle and with the other kernels; what is not finite stays in the rows that gather it."""
+    edges into 128), rows without edges, and more rows than a workgroup holds.  Its sums are grouped by block, so they are compared with
+    the oracle and with the other kernels; what is not finite stays in the rows that gather it.  With coordinates per edge the
+    same bits; a row out of the order of the blocks leaves it to the other kernels."""
     import paper_2110_09524_amd as pk
     from gpu_harness import assert_close
     print(f"monet: one launch, {fout} x {K}, r={r}, block_cols={block_cols}", flush=True)
@@ -178,17 +179,22 @@ def test_all_column_blocks_in_one_launch(fout, K, r, block_cols):
     for v in range(n):
         row = indices[indptr[v]:indptr[v + 1]]
         row[row == 9] = 10                                   # vertex 9 is gathered by row 30 alone
+        row.sort()
     indices[indptr[30]] = 9
+    indices[indptr[30]:indptr[31]].sort()
     c = synth(rng, indptr, indices, 16, fout, K, r)
     pk.gnn_config_set("block_cols", block_cols)
     pk.gnn_config_set("resident_sums", 2)       # this launch on any graph with column blocks
     try:
-        one = run(c)
+        one, apart = run(c), run(c, fused=False)
         bad = dict(c, x=c["x"].copy())
         bad["x"][9] = np.inf
         beside = run(bad)
+        turned = dict(c, indices=indices.copy())
+        turned["indices"][indptr[5]:indptr[6]] = indices[indptr[5]:indptr[6]][::-1]
+        disorder = run(turned)["out"]
         pk.gnn_config_set("resident_sums", 0)
-        other = run(c)
+        other, turned = run(c), run(turned)["out"]
     finally:
         pk.gnn_config_set("resident_sums", 1)
         pk.gnn_config_set("block_cols", 12288)
@@ -198,6 +204,7 @@ def test_all_column_blocks_in_one_launch(fout, K, r, block_cols):
     assert_close("out", one["out"], ref, row_scale=True)
     assert_close("out of the other kernel", other["out"], ref, row_scale=True)
     assert not np.array_equal(one["out"], other["out"])      # another kernel it was
+    assert np.array_equal(apart["out"], one["out"]) and np.array_equal(disorder, turned)
     rest = np.arange(n) != 30
     assert np.array_equal(beside["out"][rest], one["out"][rest]) and not np.isfinite(beside["out"][30]).any()
     assert (one["out"][deg == 0] == 0).all()
