@@ -129,6 +129,9 @@ gnn_status_t sum_partials_strided(int64_t count, int parts, const float* partial
 // partials is [parts][2][count]: first halves into out0, second halves into out1, one launch
 gnn_status_t sum_partials_pair(int64_t count, int parts, const float* partials, float* out0, float* out1,
                                hipStream_t s);
+// that and the sum of product[splits][size] into out, in one launch
+gnn_status_t sum_partials_pair_and(int64_t count, int parts, const float* partials, float* out0, float* out1, int64_t size, int splits,
+                                   const float* product, float* out, hipStream_t s);
 
 }  // namespace gnn
 

@@ -1357,11 +1357,15 @@ static gnn_status_t gat_bwd_impl(const char* who, const gnn_graph_t* g, int fin,
     const int64_t rpb = cdiv(n, L.nblk);
     k_gat_param_partial<<<L.nblk, kParamThreads, 0, st>>>(n, heads, f, rpb, z, del, der, partial);
     GNN_LAUNCH_CHECK();
-    // partial is [nblk][2][HF]: the l and the r halves summed by one launch, block order fixed
-    GNN_TRY(sum_partials_pair(HF, L.nblk, partial, ga_l, ga_r, st));
+    // partial is [nblk][2][HF]: the l and the r halves summed by one launch, block order fixed, with the parts of gw if there are any
+    if (L.split_k == 1) GNN_TRY(sum_partials_pair(HF, L.nblk, partial, ga_l, ga_r, st));
   }
   // gw = x^T dz   (x read k-major: row index of x is the contraction index)
-  GNN_TRY(gemm_f32(fin, HF, n, x, fin, true, dz, HF, false, gw, HF, L.split_k, gemm_part, st));
+  GNN_TRY(gemm_f32(fin, HF, n, x, fin, true, dz, HF, false, L.split_k == 1 ? gw : nullptr, HF, L.split_k, gemm_part, st));
+  if (L.split_k > 1) {
+    ProfScope p("gemm_sum_partials", st);
+    GNN_TRY(sum_partials_pair_and(HF, L.nblk, partial, ga_l, ga_r, (int64_t)fin * HF, L.split_k, gemm_part, gw, st));
+  }
   // gx = dz w^T   (w read with its row index as the output column)
   if (gx) GNN_TRY(gemm_f32(n, fin, HF, dz, HF, false, w, HF, true, gx, fin, 1, nullptr, st));
   return GNN_OK;

@@ -800,3 +800,20 @@ def test_long_rows_in_parts(H, F, block_cols):
         assert_close("out, forward only", half[1][0]["out"], half[0][0]["out"])
         for key in ("out", "t", "sg", "m", "d", "gx"):
             assert_close(key, half[1][1][key], half[0][1][key])
+
+
+@pytest.mark.parametrize("n,fin,H,F", [
+    (130, 7, 1, 8),        # no parts of gw
+    (300, 33, 2, 16),      # both sums short: 5 and 2 parts
+    (1100, 20, 1, 4),      # long sums of the attention gradients, few parts of gw
+    (2500, 20, 3, 8),      # both long, ends inside a workgroup
+    (2500, 520, 4, 16),    # gw a sum to a thread, the other eight threads to a sum
+    (2500, 513, 4, 64),    # few tiles of gw, so fewer parts
+])
+def test_parameter_gradients_summed_in_one_launch(n, fin, H, F):
+    from gpu_harness import run_gat
+    rng = np.random.default_rng(n + fin)
+    indptr, indices = random_graph(rng, n, 4 * n)
+    c = synth(rng, indptr, indices, fin, H, F)
+    fwd, bwd = oracle_all(c)
+    compare(c, run_gat(c), fwd, bwd)
