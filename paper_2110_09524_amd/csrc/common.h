@@ -129,9 +129,22 @@ gnn_status_t sum_partials_strided(int64_t count, int parts, const float* partial
 // partials is [parts][2][count]: first halves into out0, second halves into out1, one launch
 gnn_status_t sum_partials_pair(int64_t count, int parts, const float* partials, float* out0, float* out1,
                                hipStream_t s);
-// that and the sum of product[splits][size] into out, in one launch
-gnn_status_t sum_partials_pair_and(int64_t count, int parts, const float* partials, float* out0, float* out1, int64_t size, int splits,
-                                   const float* product, float* out, hipStream_t s);
+// The same as a description: c[i] = sum over z < parts of partials[z * stride + i] for i < count.  c2: elements from `cut` on go there;
+// quads: elements are (j, q), q < 4, of which those of j < quads are kept, (j, 0) and (j, 1) in c, the others in c2
+struct PartialSum {
+  int64_t count, stride;
+  int parts;
+  const float* partials;
+  float* c;
+  float* c2 = nullptr;
+  int64_t cut = 0;
+  int quads = 0;
+};
+gnn_status_t sum_partials_of(const PartialSum& j, hipStream_t s);
+// two of them, neither empty, in one launch: what gemm_f32 leaves with c = nullptr and some other sum
+gnn_status_t sum_partials_two(const PartialSum& a, const PartialSum& b, hipStream_t s);
+// the first of two levels, where there are parts enough for two: j then describes the second
+gnn_status_t sum_partials_ranges(PartialSum& j, float* scratch, hipStream_t s);
 
 }  // namespace gnn
 

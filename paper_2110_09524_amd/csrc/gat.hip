@@ -1364,7 +1364,8 @@ static gnn_status_t gat_bwd_impl(const char* who, const gnn_graph_t* g, int fin,
   GNN_TRY(gemm_f32(fin, HF, n, x, fin, true, dz, HF, false, L.split_k == 1 ? gw : nullptr, HF, L.split_k, gemm_part, st));
   if (L.split_k > 1) {
     ProfScope p("gemm_sum_partials", st);
-    GNN_TRY(sum_partials_pair_and(HF, L.nblk, partial, ga_l, ga_r, (int64_t)fin * HF, L.split_k, gemm_part, gw, st));
+    const int64_t size = (int64_t)fin * HF;
+    GNN_TRY(sum_partials_two({2 * HF, 2 * HF, L.nblk, partial, ga_l, ga_r, HF}, {size, size, L.split_k, gemm_part, gw}, st));
   }
   // gx = dz w^T   (w read with its row index as the output column)
   if (gx) GNN_TRY(gemm_f32(n, fin, HF, dz, HF, false, w, HF, true, gx, fin, 1, nullptr, st));

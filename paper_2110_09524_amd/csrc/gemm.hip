@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "partial_sums.h"
 
 namespace gnn {
 
@@ -891,87 +892,26 @@ __global__ __launch_bounds__(256, 3) void k_chain_f32(int64_t M, int N, int64_t 
     }
 }
 
-// c[i] = sum over z of partials[z][i], z ascending (fixed order => reproducible)
-// c2 != null: elements from index `cut` on go to c2[i - cut] (two results from one launch)
-struct PartialSum {
-  int64_t count, stride;
-  int parts;
-  const float* partials;
-  float *c, *c2;
-  int64_t cut;
-};
-__device__ __forceinline__ void store_split(const PartialSum& j, int64_t i, float v) {
-  if (j.c2 != nullptr && i >= j.cut) j.c2[i - j.cut] = v;
-  else j.c[i] = v;
-}
-
-__device__ __forceinline__ void sum_partials_thin(const PartialSum& j, int64_t block) {
-  const int64_t i = block * 256 + threadIdx.x;
-  if (i >= j.count) return;
-  // four interleaved running sums keep four loads in flight; their order is fixed
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-  int z = 0;
-  for (; z + 4 <= j.parts; z += 4) {
-    const float* p = j.partials + (int64_t)z * j.stride + i;
-    const float v0 = p[0], v1 = p[j.stride], v2 = p[2 * j.stride], v3 = p[3 * j.stride];
-    s0 += v0; s1 += v1; s2 += v2; s3 += v3;
-  }
-  for (; z < j.parts; ++z) s0 += j.partials[(int64_t)z * j.stride + i];
-  store_split(j, i, (s0 + s1) + (s2 + s3));
-}
-
-// Same sum for short outputs and many parts: 8 threads share one output element, each
-// adds every 8th part of its range (in four interleaved running sums), then the 8 subtotals are
-// added in order through LDS.  `range` selects `chunk` consecutive parts, whose subtotal goes
-// to row `range` of the output (a second call then adds the rows).
-// The grouping is fixed, so the result is reproducible.
-__device__ __forceinline__ void sum_partials_wide(const PartialSum& j, int64_t block, int range, int chunk) {
-  __shared__ float sub[8][32];
-  const int col = threadIdx.x & 31, lane8 = threadIdx.x >> 5;
-  const int64_t i = block * 32 + col;
-  const int z0 = range * chunk;
-  const int z1 = z0 + chunk < j.parts ? z0 + chunk : j.parts;
-  float s = 0.f;
-  if (i < j.count) {
-    // four interleaved running sums keep four loads in flight; their order is fixed
-    float s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    int z = z0 + lane8;
-    for (; z + 24 < z1; z += 32) {
-      const float* p = j.partials + (int64_t)z * j.stride + i;
-      const float v0 = p[0], v1 = p[8 * j.stride], v2 = p[16 * j.stride], v3 = p[24 * j.stride];
-      s += v0; s1 += v1; s2 += v2; s3 += v3;
-    }
-    for (; z < z1; z += 8) s += j.partials[(int64_t)z * j.stride + i];
-    s = (s + s1) + (s2 + s3);
-  }
-  sub[lane8][col] = s;
-  __syncthreads();
-  if (lane8 == 0 && i < j.count) {
-    float tot = 0.f;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) tot += sub[q][col];
-    store_split(j, (int64_t)range * j.count + i, tot);
-  }
-}
-
-__global__ __launch_bounds__(256) void k_sum_partials(PartialSum j) { sum_partials_thin(j, blockIdx.x); }
+__global__ __launch_bounds__(256) void k_sum_partials(PartialSum j) { sum_partials_thin(j, blockIdx.x, threadIdx.x); }
 __global__ __launch_bounds__(256) void k_sum_partials_wide(PartialSum j, int chunk) {
-  sum_partials_wide(j, blockIdx.x, blockIdx.y, chunk);
+  __shared__ float sub[8][32];
+  sum_partials_wide(j, blockIdx.x, blockIdx.y, chunk, threadIdx.x, sub);
 }
-// Two sums in one launch, a's workgroups first: either is some 5 us of memory latency on a few workgroups.  GAT training pass, a launch each ->
-// this, us: 20 000 vertices, 10^5 edges, 500 -> 8 x 8 125.9 -> 121.4.
+// Two sums in one launch, a's workgroups first: either is some 5 us of memory latency on a few workgroups.  Training pass, a launch each ->
+// this, us: GAT, 20 000 vertices, 10^5 edges, 500 -> 8 x 8 125.9 -> 121.4, 1856, 1.3 10^5, 16 -> 1 x 64 57.6 -> 52.9; GMM (with the last
+// step of the parameters' gradients, too) 100 000, 2 10^6, 64 -> 3 x 64 291.5 -> 285.8, 17 036, 1.3 10^5, 22 -> 4 x 32 68.4 -> 65.1.
 __global__ __launch_bounds__(256) void k_sum_partials_two(PartialSum a, PartialSum b, unsigned blocks_a, bool wide_a, bool wide_b) {
-  const bool first = blockIdx.x < blocks_a;  // uniform, as what follows
-  const PartialSum& j = first ? a : b;
-  const unsigned block = first ? blockIdx.x : blockIdx.x - blocks_a;
-  if (first ? wide_a : wide_b) sum_partials_wide(j, block, 0, j.parts);
-  else sum_partials_thin(j, block);
+  __shared__ float sub[8][32];
+  auto sum = [&](const PartialSum& j, unsigned block, bool wide) {  // uniform
+    if (wide) sum_partials_wide(j, block, 0, j.parts, threadIdx.x, sub);
+    else sum_partials_thin(j, block, threadIdx.x);
+  };
+  // not one call for the one or the other: the compiler would copy both descriptions to scratch memory, and index there
+  if (blockIdx.x < blocks_a) sum(a, blockIdx.x, wide_a);
+  else sum(b, blockIdx.x - blocks_a, wide_b);
 }
 
-static bool sums_wide(const PartialSum& j) { return j.count < 32768 && j.parts >= 16; }
-static unsigned sum_blocks(const PartialSum& j) { return (unsigned)cdiv(j.count, sums_wide(j) ? 32 : 256); }
-
-static gnn_status_t sum_partials_launch(const PartialSum& j, hipStream_t s) {
+gnn_status_t sum_partials_of(const PartialSum& j, hipStream_t s) {
   if (j.count <= 0) return GNN_OK;
   if (sums_wide(j)) k_sum_partials_wide<<<dim3(sum_blocks(j), 1), 256, 0, s>>>(j, j.parts);
   else k_sum_partials<<<sum_blocks(j), 256, 0, s>>>(j);
@@ -981,19 +921,16 @@ static gnn_status_t sum_partials_launch(const PartialSum& j, hipStream_t s) {
 
 gnn_status_t sum_partials_strided(int64_t count, int parts, const float* partials, int64_t stride,
                                   float* out, hipStream_t s) {
-  return sum_partials_launch({count, stride, parts, partials, out, nullptr, 0}, s);
+  return sum_partials_of({count, stride, parts, partials, out}, s);
 }
 
 // partials is [parts][2][count]: the first halves are summed into out0, the second into out1
 gnn_status_t sum_partials_pair(int64_t count, int parts, const float* partials, float* out0, float* out1,
                                hipStream_t s) {
-  return sum_partials_launch({2 * count, 2 * count, parts, partials, out0, out1, count}, s);
+  return sum_partials_of({2 * count, 2 * count, parts, partials, out0, out1, count}, s);
 }
 
-// ... and the parts of a product of `size` elements (gemm_f32 with c = nullptr left them), the sums of either alone, in one launch
-gnn_status_t sum_partials_pair_and(int64_t count, int parts, const float* partials, float* out0, float* out1, int64_t size, int splits,
-                                   const float* product, float* out, hipStream_t s) {
-  const PartialSum a{2 * count, 2 * count, parts, partials, out0, out1, count}, b{size, size, splits, product, out, nullptr, 0};
+gnn_status_t sum_partials_two(const PartialSum& a, const PartialSum& b, hipStream_t s) {
   const unsigned blocks_a = sum_blocks(a);
   k_sum_partials_two<<<blocks_a + sum_blocks(b), 256, 0, s>>>(a, b, blocks_a, sums_wide(a), sums_wide(b));
   GNN_LAUNCH_CHECK();
@@ -1008,15 +945,23 @@ gnn_status_t sum_partials(int64_t count, int parts, const float* partials, float
 // (sum_partials_scratch_rows(parts) rows of `count` floats), then those rows into `out`.
 int sum_partials_scratch_rows(int parts) { return (int)cdiv(parts, kSumChunk); }
 
+gnn_status_t sum_partials_ranges(PartialSum& j, float* scratch, hipStream_t s) {
+  const int rows = sum_partials_scratch_rows(j.parts);
+  if (j.count <= 0 || rows <= 1) return GNN_OK;
+  k_sum_partials_wide<<<dim3((unsigned)cdiv(j.count, 32), (unsigned)rows), 256, 0, s>>>({j.count, j.stride, j.parts, j.partials, scratch},
+                                                                                       kSumChunk);
+  GNN_LAUNCH_CHECK();
+  j.partials = scratch;
+  j.parts = rows;
+  j.stride = j.count;
+  return GNN_OK;
+}
+
 gnn_status_t sum_partials_two_level(int64_t count, int parts, const float* partials, float* scratch,
                                     float* out, hipStream_t s) {
-  if (count <= 0) return GNN_OK;
-  const int rows = sum_partials_scratch_rows(parts);
-  if (rows <= 1) return sum_partials(count, parts, partials, out, s);
-  k_sum_partials_wide<<<dim3((unsigned)cdiv(count, 32), (unsigned)rows), 256, 0, s>>>({count, count, parts, partials, scratch, nullptr, 0},
-                                                                                     kSumChunk);
-  GNN_LAUNCH_CHECK();
-  return sum_partials(count, rows, scratch, out, s);
+  PartialSum j{count, count, parts, partials, out};
+  GNN_TRY(sum_partials_ranges(j, scratch, s));
+  return sum_partials_of(j, s);
 }
 
 // ---- choice of the tile -----------------------------------------------------------------

@@ -694,15 +694,6 @@ __global__ __launch_bounds__(kGmmBlock) void k_gmm_bwd_dst(
   }
 }
 
-// totals[j][4] -> gmu[j, 0..1], gis[j, 0..1]
-__global__ void k_gmm_param_split(int K, const float* __restrict__ totals, float* __restrict__ gmu,
-                                  float* __restrict__ gis) {
-  const int t = threadIdx.x;  // (k, q)
-  if (t >= K * 4) return;
-  const int k = t >> 2, q = t & 3;
-  if (q < 2) gmu[2 * k + q] = totals[t]; else gis[2 * k + (q - 2)] = totals[t];
-}
-
 // ---- a10, source side: dhk[u,j,:] = (1/K) sum over out-edges w_j(e) gout[v,:] ----------
 // MOMENTS: with R_j and S_j, from which the gradients of mu and inv_sigma come: the destination side need not be walked at
 // all, one gather per edge instead of two.  100 000 vertices, 2 10^6 edges, 64 columns, K = 3, us: destination side 131
@@ -1241,14 +1232,15 @@ struct GmmFwdXLauncher {
   }
 };
 
-// gradients of mu and inv_sigma from the workgroups' partial sums; behind their slots lie one for the totals and the
-// second-level scratch
-static gnn_status_t gmm_param_sums(int K, unsigned grid, float* partial, float* gmu, float* gis, hipStream_t st) {
-  float* totals = partial + (int64_t)grid * kMaxK * 4;
-  GNN_TRY(sum_partials_two_level(kMaxK * 4, (int)grid, partial, totals + kMaxK * 4, totals, st));
-  k_gmm_param_split<<<1, 64, 0, st>>>(K, totals, gmu, gis);
-  GNN_LAUNCH_CHECK();
-  return GNN_OK;
+// gradients of mu and inv_sigma from the workgroups' partial sums; the caller launches the last sum, which the kernels leave in `last`, with another
+struct GmmParamSums {
+  float *gmu, *gis;
+  PartialSum last;
+};
+static gnn_status_t gmm_param_sums(int K, unsigned grid, float* partial, GmmParamSums* sums, hipStream_t st) {
+  constexpr int count = kMaxK * 4;
+  sums->last = {count, count, (int)grid, partial, sums->gmu, sums->gis, 0, K};
+  return sum_partials_ranges(sums->last, partial + (int64_t)(grid + 1) * count, st);
 }
 
 // number of workgroups (= partial slots) of the kernels that sum the gradients of mu and inv_sigma
@@ -1265,7 +1257,7 @@ template <int L, int NV>
 struct GmmBwdDstLauncher {
   static gnn_status_t run(const gnn_graph_t* g, const float* hk, const float* c, const float* mu,
                           const float* is, const float* gout, GmmParams pm, float* partial,
-                          float* gmu, float* gis, hipStream_t st) {
+                          GmmParamSums* sums, hipStream_t st) {
     constexpr int GPB = (kWave / L) * (kGmmBlock / kWave);
     ProfScope p("gmm_bwd_dst", st);
     const RowSplit sp = split_rows(g, 0, L, GPB);
@@ -1277,15 +1269,15 @@ struct GmmBwdDstLauncher {
                                                        gout, pm, partial);
       GNN_LAUNCH_CHECK();
     }
-    return gmm_param_sums(pm.K, grid, partial, gmu, gis, st);
+    return gmm_param_sums(pm.K, grid, partial, sums, st);
   }
 };
 
 template <int L, int NV>
 struct GmmBwdDstXLauncher {
   static gnn_status_t run(const gnn_graph_t* g, const float* x, const float* c, const float* mu,
-                          const float* is, const float* G, int K, int fin, float* partial, float* gmu,
-                          float* gis, hipStream_t st) {
+                          const float* is, const float* G, int K, int fin, float* partial, GmmParamSums* sums,
+                          hipStream_t st) {
     constexpr int GPB = kGmmBlock / L;
     ProfScope p("gmm_bwd_dst", st);
     const RowSplit sp = split_rows(g, 0, L, GPB);
@@ -1295,7 +1287,7 @@ struct GmmBwdDstXLauncher {
       k_gmm_bwd_dst_x<L><<<grid, kGmmBlock, 0, st>>>(rl, g->rows[0], g->indices, x, c, mu, is, G, K, fin, partial);
       GNN_LAUNCH_CHECK();
     }
-    return gmm_param_sums(K, grid, partial, gmu, gis, st);
+    return gmm_param_sums(K, grid, partial, sums, st);
   }
 };
 
@@ -1303,8 +1295,8 @@ struct GmmBwdDstXLauncher {
 template <int L, int NV>
 struct GmmBwdSrcLauncher {
   static gnn_status_t run(const gnn_graph_t* g, const float* c, const float* mu, const float* is,
-                          const float* gout, GmmParams pm, float* dhk, const float* hk, float* partial, float* gmu,
-                          float* gis, hipStream_t st) {
+                          const float* gout, GmmParams pm, float* dhk, const float* hk, float* partial, GmmParamSums* sums,
+                          hipStream_t st) {
     ProfScope p(hk != nullptr ? "gmm_bwd" : "gmm_bwd_src", st);
     unsigned grid = 0;
     GNN_TRY(gmm_kernels_slices<L>(g, pm.K, pm.F, [&](auto kernels, auto slices) -> gnn_status_t {
@@ -1323,7 +1315,7 @@ struct GmmBwdSrcLauncher {
       GNN_LAUNCH_CHECK();
       return GNN_OK;
     }));
-    return hk != nullptr ? gmm_param_sums(pm.K, grid, partial, gmu, gis, st) : GNN_OK;
+    return hk != nullptr ? gmm_param_sums(pm.K, grid, partial, sums, st) : GNN_OK;
   }
 };
 
@@ -1331,7 +1323,7 @@ template <int L, int NV>
 struct GmmBwdDstEbLauncher {
   static gnn_status_t run(const gnn_graph_t* g, const float* hk, const float* c, const float* mu,
                           const float* is, const float* gout, GmmParams pm, float* partial,
-                          float* gmu, float* gis, hipStream_t st) {
+                          GmmParamSums* sums, hipStream_t st) {
     constexpr int GPB = kGmmBlock / L;
     ProfScope p("gmm_bwd_dst", st);
     const unsigned grid = (unsigned)cdiv(cdiv(g->nnz, kGmmEbEdges), GPB);
@@ -1340,7 +1332,7 @@ struct GmmBwdDstEbLauncher {
                                                           is, gout, pm, partial);
       GNN_LAUNCH_CHECK();
     }
-    return gmm_param_sums(pm.K, grid, partial, gmu, gis, st);
+    return gmm_param_sums(pm.K, grid, partial, sums, st);
   }
 };
 
@@ -1608,24 +1600,23 @@ extern "C" gnn_status_t gnn_gmm_tune_bwd(gnn_graph_t* g, int fin, int fout, int 
     char* base = static_cast<char*>(ws);
     float* dhk = reinterpret_cast<float*>(base + L.dhk);
     float* partial = reinterpret_cast<float*>(base + L.partial);
-    float* gmu = dhk;  // the destination side's results are not kept: they land in the dhk area (4 k floats)
-    float* gis = dhk + 2 * k;
+    GmmParamSums param_sums{}, *const sums = &param_sums;  // the last sum is not timed: it goes out with another one
     GmmParams pm{k, fout};
     const GroupShape gs = pick_group(fout);
     constexpr int kReps = 3;
-    GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdDstLauncher>(gs, g, hk, c, mu, inv_sigma, gout, pm, partial, gmu, gis, st); }, &ms[0]));
-    GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdDstEbLauncher>(gs, g, hk, c, mu, inv_sigma, gout, pm, partial, gmu, gis, st); }, &ms[1]));
-    GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdSrcLauncher>(gmm_gather_group(g, fout), g, c, mu, inv_sigma, gout, pm, dhk, (const float*)nullptr, partial, gmu, gis, st); }, &ms[2]));
+    GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdDstLauncher>(gs, g, hk, c, mu, inv_sigma, gout, pm, partial, sums, st); }, &ms[0]));
+    GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdDstEbLauncher>(gs, g, hk, c, mu, inv_sigma, gout, pm, partial, sums, st); }, &ms[1]));
+    GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdSrcLauncher>(gmm_gather_group(g, fout), g, c, mu, inv_sigma, gout, pm, dhk, (const float*)nullptr, partial, sums, st); }, &ms[2]));
     GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdSrcEbLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, st); }, &ms[3]));
     // What gnn_gmm_bwd runs untuned against the pairs of halves it could run instead.  Where the layer aggregates first, the
     // destination side gathers x: timed on whatever the scratch areas hold, since x is no argument here, and without the
     // products (of as many operations) that make hk or G.
     const bool agg = gmm_aggregate_first(fin, fout, k);
     float walk = 0.f, dst = ms[0];
-    GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdSrcLauncher>(gmm_gather_group(g, fout), g, c, mu, inv_sigma, gout, pm, dhk, hk, partial, gmu, gis, st); }, &walk));
+    GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdSrcLauncher>(gmm_gather_group(g, fout), g, c, mu, inv_sigma, gout, pm, dhk, hk, partial, sums, st); }, &walk));
     if (agg) {
       const float *x = dhk, *G = reinterpret_cast<const float*>(base + L.agg);
-      GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdDstXLauncher>(pick_group(fin), g, x, c, mu, inv_sigma, G, k, fin, partial, gmu, gis, st); }, &dst));
+      GNN_TRY(time_passes(st, kReps, [&] { return gmm_dispatch<GmmBwdDstXLauncher>(pick_group(fin), g, x, c, mu, inv_sigma, G, k, fin, partial, sums, st); }, &dst));
     }
     float best = gmm_one_walk(g, fin, fout, k) ? walk : dst + ms[2];
     g->gmm_bwd_edge_balanced[0] = g->gmm_bwd_edge_balanced[1] = 0;
@@ -1664,6 +1655,7 @@ extern "C" gnn_status_t gnn_gmm_bwd(const gnn_graph_t* g, int fin, int fout, int
   float* dhk = reinterpret_cast<float*>(base + L.dhk);
   float* partial = reinterpret_cast<float*>(base + L.partial);
   float* part = reinterpret_cast<float*>(base + L.gemm);
+  GmmParamSums param_sums{gmu, ginv_sigma, {}}, *const sums = &param_sums;
   const int64_t n = g->n;
   const int KF = k * fout;
   GmmParams pm{k, fout};
@@ -1681,7 +1673,7 @@ extern "C" gnn_status_t gnn_gmm_bwd(const gnn_graph_t* g, int fin, int fout, int
     hk_use = agg_buf;
   }
   if (eb_dst) {
-    GNN_TRY(gmm_dispatch<GmmBwdDstEbLauncher>(gs, g, hk_use, c, mu, inv_sigma, gout, pm, partial, gmu, ginv_sigma, st));
+    GNN_TRY(gmm_dispatch<GmmBwdDstEbLauncher>(gs, g, hk_use, c, mu, inv_sigma, gout, pm, partial, sums, st));
   } else if (!one_walk && agg) {
     // <gout[v], hk[u,j,:]> = <G_j[v], x[u]>, G = gout W'^T: the destination side gathers x rows
     float* wt = reinterpret_cast<float*>(base + L.wt);
@@ -1693,17 +1685,25 @@ extern "C" gnn_status_t gnn_gmm_bwd(const gnn_graph_t* g, int fin, int fout, int
     }
     GNN_TRY(gemm_f32(n, k * fin, fout, gout, fout, false, wt, fout, true, agg_buf, (int64_t)k * fin, 1, nullptr, st));
     GNN_TRY((gmm_dispatch<GmmBwdDstXLauncher>(pick_group(fin), g, x, c, mu, inv_sigma, (const float*)agg_buf, k, fin,
-                                              partial, gmu, ginv_sigma, st)));
+                                              partial, sums, st)));
   } else if (!one_walk) {
-    GNN_TRY(gmm_dispatch<GmmBwdDstLauncher>(gs, g, hk_use, c, mu, inv_sigma, gout, pm, partial, gmu, ginv_sigma, st));
+    GNN_TRY(gmm_dispatch<GmmBwdDstLauncher>(gs, g, hk_use, c, mu, inv_sigma, gout, pm, partial, sums, st));
   }
   const float* no_hk = nullptr;
   if (eb_src)
     GNN_TRY(gmm_dispatch<GmmBwdSrcEbLauncher>(gs, g, c, mu, inv_sigma, gout, pm, dhk, st));
   else
     GNN_TRY(gmm_dispatch<GmmBwdSrcLauncher>(gmm_gather_group(g, fout), g, c, mu, inv_sigma, gout, pm, dhk, one_walk ? hk_use : no_hk,
-                                            partial, gmu, ginv_sigma, st));
-  GNN_TRY(gemm_f32(fin, KF, n, x, fin, true, dhk, KF, false, gw_fc, KF, L.split_k, part, st));
+                                            partial, sums, st));
+  if (L.split_k == 1) {
+    GNN_TRY(sum_partials_of(param_sums.last, st));
+    GNN_TRY(gemm_f32(fin, KF, n, x, fin, true, dhk, KF, false, gw_fc, KF, 1, nullptr, st));
+  } else {
+    GNN_TRY(gemm_f32(fin, KF, n, x, fin, true, dhk, KF, false, nullptr, KF, L.split_k, part, st));
+    ProfScope p("gemm_sum_partials", st);
+    const int64_t size = (int64_t)fin * KF;
+    GNN_TRY(sum_partials_two(param_sums.last, {size, size, L.split_k, part, gw_fc}, st));
+  }
   if (gx) GNN_TRY(gemm_f32(n, fin, KF, dhk, KF, false, w_fc, KF, true, gx, fin, 1, nullptr, st));
   return GNN_OK;
 }

@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "partial_sums.h"
 #include "row_parts.h"
 #include "rowgroup.h"
 
@@ -1036,14 +1037,8 @@ __global__ __launch_bounds__(kParamThreads) void k_gmmp_param_rows(int nvals, in
   if (threadIdx.x < nvals) rows[(int64_t)blockIdx.x * nvals + threadIdx.x] = s;
 }
 // columns: gmu [kt][rt], ginv_sigma [kt][rt], then, where gP is not null, (gP[d,0], gP[d,1], gpb[d]) [rt]
-__global__ __launch_bounds__(kParamThreads) void k_gmmp_param_totals(int K, int R, int kt, int rt, int nrows,
-                                                                const double* __restrict__ rows, float* __restrict__ gmu,
-                                                                float* __restrict__ gis, float* __restrict__ gP /* nullable */,
-                                                                float* __restrict__ gpb) {
-  const int krt = kt * rt, nvals = 2 * krt + (gP != nullptr ? 3 * rt : 0);
-  const float s = (float)sum_columns(nvals, nrows, rows);
-  int i = threadIdx.x;
-  if (i >= nvals) return;
+__device__ __forceinline__ void store_param_total(int K, int R, int kt, int rt, int i, float s, float* gmu, float* gis, float* gP, float* gpb) {
+  const int krt = kt * rt;
   if (i < 2 * krt) {
     float* g = i < krt ? gmu : gis;
     i = i < krt ? i : i - krt;
@@ -1056,6 +1051,24 @@ __global__ __launch_bounds__(kParamThreads) void k_gmmp_param_totals(int K, int 
     if (j < 2) gP[2 * d + j] = s;
     else gpb[d] = s;
   }
+}
+// The workgroups but the first sum the parts of the product beside (count = 0: none), 256 threads to each of its blocks: a launch of its own
+// is some 5 us, of memory latency like this one.
+__global__ __launch_bounds__(kParamThreads) void k_gmmp_param_totals(int K, int R, int kt, int rt, int nrows,
+                                                                const double* __restrict__ rows, float* __restrict__ gmu,
+                                                                float* __restrict__ gis, float* __restrict__ gP /* nullable */,
+                                                                float* __restrict__ gpb, PartialSum product, bool wide) {
+  __shared__ float sub[kParamThreads / 256][8][32];
+  if (blockIdx.x == 0) {
+    const int nvals = 2 * kt * rt + (gP != nullptr ? 3 * rt : 0);
+    const float s = (float)sum_columns(nvals, nrows, rows);
+    if ((int)threadIdx.x < nvals) store_param_total(K, R, kt, rt, threadIdx.x, s, gmu, gis, gP, gpb);
+    return;
+  }
+  const int quarter = threadIdx.x / 256, t = threadIdx.x % 256;
+  const int64_t block = (int64_t)(blockIdx.x - 1) * (kParamThreads / 256) + quarter;
+  if (wide) sum_partials_wide(product, block, 0, product.parts, t, sub[quarter]);
+  else sum_partials_thin(product, block, t);
 }
 
 // ---- the projection that makes pseudo-coordinates from the degree pair ------------------------
@@ -1319,9 +1332,15 @@ static gnn_status_t for_kernels(int K, int R, Fn fn) {
   }
 }
 
-// the parameters' gradients from k_gmmp_bwd_nr's partials; the rows of ranges go behind those
+// what a product gw = x^T dhk that was split over K left to sum up; nothing if it was not
+static PartialSum parts_of_product(int fin, int KF, int split_k, const float* parts, float* gw) {
+  const int64_t size = split_k > 1 ? (int64_t)fin * KF : 0;
+  return {size, size, split_k, parts, gw};
+}
+
+// the parameters' gradients from k_gmmp_bwd_nr's partials, and the sum of a product's; the rows of ranges go behind those
 static gnn_status_t wide_param_sums(int K, int R, int kt, int rt, int parts, double* partial, float* gmu, float* gis,
-                                    float* gP, float* gpb, hipStream_t st) {
+                                    float* gP, float* gpb, const PartialSum& product, hipStream_t st) {
   const int nvals = 2 * kt * rt + (gP != nullptr ? 3 * rt : 0);
   int nrows = parts;
   const double* rows = partial;
@@ -1332,7 +1351,8 @@ static gnn_status_t wide_param_sums(int K, int R, int kt, int rt, int parts, dou
     GNN_LAUNCH_CHECK();
     rows = out;
   }
-  k_gmmp_param_totals<<<1, kParamThreads, 0, st>>>(K, R, kt, rt, nrows, rows, gmu, gis, gP, gpb);
+  const unsigned blocks = product.count > 0 ? (unsigned)cdiv(sum_blocks(product), kParamThreads / 256) : 0;
+  k_gmmp_param_totals<<<1 + blocks, kParamThreads, 0, st>>>(K, R, kt, rt, nrows, rows, gmu, gis, gP, gpb, product, sums_wide(product));
   GNN_LAUNCH_CHECK();
   return GNN_OK;
 }
@@ -1466,7 +1486,7 @@ extern "C" gnn_status_t gnn_gmmp_bwd(const gnn_graph_t* g, int fin, int fout, in
                                                                    ProjArgs{}, mu, inv_sigma, gout, pm, dhk, wide,
                                                                    apart ? nullptr : gpseudo);
         GNN_LAUNCH_CHECK();
-        return wide_param_sums(k, r, KT, RT, (int)grid, wide, gmu, ginv_sigma, nullptr, nullptr, st);
+        return wide_param_sums(k, r, KT, RT, (int)grid, wide, gmu, ginv_sigma, nullptr, nullptr, PartialSum{}, st);
       });
     }));
   } else {
@@ -1634,9 +1654,9 @@ extern "C" gnn_status_t gnn_monet_bwd(const gnn_graph_t* g, int fin, int fout, i
   const ProjArgs pa{c, proj_w, proj_b};
   const int KF = k * fout;
   const int G = KF <= 32 ? 8 : 16;
+  unsigned grid = 0;
   {
     ProfScope p("monet_bwd", st);
-    unsigned grid = 0;
     GNN_TRY(for_lanes(G, [&](auto lanes) -> gnn_status_t {
       constexpr int GL = decltype(lanes)::value == 8 ? 8 : 16;
       RowLaunch rl;
@@ -1651,12 +1671,15 @@ extern "C" gnn_status_t gnn_monet_bwd(const gnn_graph_t* g, int fin, int fout, i
         return GNN_OK;
       });
     }));
+  }
+  GNN_TRY(gemm_f32(fin, KF, g->n, x, fin, true, dhk, KF, false, W.split_k > 1 ? nullptr : gw_fc, KF, W.split_k, part, st));
+  {
+    ProfScope p("monet_param_grad", st);
     GNN_TRY(for_kernels(k, r, [&](auto kernels, auto dims) -> gnn_status_t {
       return wide_param_sums(k, r, decltype(kernels)::value, decltype(dims)::value, (int)grid, partial, gmu, ginv_sigma,
-                             gproj_w, gproj_b, st);
+                             gproj_w, gproj_b, parts_of_product(fin, KF, W.split_k, part, gw_fc), st);
     }));
   }
-  GNN_TRY(gemm_f32(fin, KF, g->n, x, fin, true, dhk, KF, false, gw_fc, KF, W.split_k, part, st));
   if (gx) GNN_TRY(gemm_f32(g->n, fin, KF, dhk, KF, false, w_fc, KF, true, gx, fin, 1, nullptr, st));
   return GNN_OK;
 }

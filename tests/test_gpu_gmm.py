@@ -137,6 +137,18 @@ def test_destination_side_apart(n, fin, fout, K, apart):
     assert names & {"gmm_bwd", "gmm_bwd_dst", "gmm_bwd_src"} == ({"gmm_bwd_dst", "gmm_bwd_src"} if apart else {"gmm_bwd"})
 
 
+@pytest.mark.parametrize("n,fin,fout,K", [(200, 5, 16, 2), (300, 33, 12, 3), (2300, 5, 4, 1), (2300, 33, 12, 8), (2300, 260, 64, 2)])
+def test_parameter_sums_beside_the_parts_of_the_weight_gradient(n, fin, fout, K):
+    """No parts; two, a sum to a thread; 17, a sum to eight threads, one block of sums or several; a sum to a thread again.
+    One range of the parameters' partial sums and several; one kernel to eight."""
+    print(f"gmm: {n} vertices {fin}->{fout} K={K}", flush=True)
+    rng = np.random.default_rng(n + fin)
+    indptr, indices = random_graph(rng, n, 2 * n, self_loops=True, duplicates=True)
+    c = synth(rng, indptr, indices, fin, fout, K)
+    c["w_fc"] *= np.float32(fin ** -0.5)      # hk of the size of x
+    check(c)
+
+
 def test_graph_without_edges():
     print("gmm: no edges", flush=True)
     rng = np.random.default_rng(62)

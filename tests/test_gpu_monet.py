@@ -112,6 +112,17 @@ def test_parameter_sums_at_the_edges_of_their_ranges(n):
     check(synth(rng, indptr, indices, 4, 16, 3, 3))
 
 
+@pytest.mark.parametrize("n,fin,fout,K", [(200, 5, 16, 2), (300, 33, 12, 3), (2300, 5, 4, 1), (2300, 33, 12, 3), (2300, 601, 32, 2)])
+def test_parameter_sums_beside_the_parts_of_the_weight_gradient(n, fin, fout, K):
+    """No parts; two, a sum to a thread; 17, a sum to eight threads, one block of sums or several; a sum to a thread again."""
+    print(f"monet: {n} vertices {fin}->{fout} K={K}", flush=True)
+    rng = np.random.default_rng(n + fin)
+    indptr, indices = random_graph(rng, n, 2 * n, self_loops=True, duplicates=True)
+    c = synth(rng, indptr, indices, fin, fout, K, 2)
+    c["w_fc"] *= np.float32(fin ** -0.5)      # hk of the size of x
+    check(c)
+
+
 def test_the_papers_settings_on_a_power_law_graph_and_the_two_call_form():
     """k = 3, r = 3 and k = 2, r = 1 with 16 hidden features (Sec. 7.2, 7.3) on a graph with hub rows.  The
     fused kernels evaluate the same expressions in the same order as projection + general layer, so
