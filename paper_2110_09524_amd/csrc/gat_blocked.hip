@@ -148,6 +148,12 @@ __device__ __forceinline__ float dot8_half(const float4 (&zr)[2], const uint4& r
   return dot4(zr[0], make_float4(a.x, a.y, b.x, b.y)) + dot4(zr[1], make_float4(c.x, c.y, d.x, d.y));
 }
 
+// sum += w d for an edge; a lane without one has weight 0, but its product with the row's own z may be 0 * Inf
+__device__ __forceinline__ void add_dot(bool edge, float w, float d, float& sum) {
+  const float s = fmaf(w, d, sum);
+  sum = edge ? s : sum;
+}
+
 // STAGE: the per-edge scalar el[u] of the slice's head is read from an LDS copy of the block's
 // part of the head-major table instead of being gathered from L2.  Such a scalar gather
 // costs a CU one 128-byte line fill per edge, as much as the 128-byte row slice itself; with
@@ -304,9 +310,9 @@ __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk
 
     // Gathered rows are addressed with 32-bit byte offsets when the matrix is below 4 GB
     // (one 24-bit multiply-add per row instead of 64-bit arithmetic).
-    const char* feat_bytes = reinterpret_cast<const char*>(feat);
     constexpr uint32_t kElem = HALF ? 2u : 4u;  // bytes per stored element of the gathered matrix
     const uint32_t row_bytes = (uint32_t)HF * kElem, col_bytes = (uint32_t)col * kElem;
+    const auto table = row_table(feat, (int64_t)n_rows * row_bytes);  // used where `narrow`
 
     BlkRow<NA> cur, nxt;
     fetch(0, cur);
@@ -340,10 +346,9 @@ __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk
         for (int32_t c0 = beg; c0 < end; c0 += SL) {
           const bool e_ok = c0 + li < end;
           const int cnt = min(SL, end - c0);  // valid edges of this chunk (uniform in the group)
-          // gathered vertex of edge c0 + li; lanes past the end point at the block's first
-          // vertex (a valid, cache-resident row) and get weight 0, so the row phase below
-          // needs no per-edge conditionals
-          const int32_t c = e_ok ? c_next : col_begin;
+          // gathered vertex of edge c0 + li; lanes past the end gather zeros and get weight 0,
+          // so the row phase below needs no per-edge conditionals
+          const int32_t c = e_ok ? c_next : n_rows;
           if (c0 + SL + li < end) c_next = bcol[c0 + SL + li];
           l_idx[li] = c;
           // per-edge scalars: issue the loads now, use them after the row loads are in flight
@@ -384,14 +389,10 @@ __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk
               if (!SKIP || t0 + t4 < cnt) {
                 if (narrow) {
 #pragma unroll
-                  for (int t = t4; t < t4 + 4; ++t)
-                    rowv[t] = *reinterpret_cast<const uint4*>(
-                        feat_bytes + (__umul24((uint32_t)idv[t], row_bytes) + col_bytes));
+                  for (int t = t4; t < t4 + 4; ++t) rowv[t] = table_load<uint4>(table, idv[t], row_bytes, col_bytes);
                 } else {
 #pragma unroll
-                  for (int t = t4; t < t4 + 4; ++t)
-                    rowv[t] = *reinterpret_cast<const uint4*>(feat_bytes +
-                                                              ((int64_t)idv[t] * row_bytes + col_bytes));
+                  for (int t = t4; t < t4 + 4; ++t) rowv[t] = table_load_wide<uint4>(feat, n_rows, idv[t], row_bytes, col_bytes);
                 }
               }
             }
@@ -448,13 +449,13 @@ __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk
                   if constexpr (HALF) {
                     fma8_half(part, pv[t], rowv[t]);
                     if (DUAL) fma8_half(part2, pv2[t], rowv[t]);
-                    if constexpr (SRC && NA == 2) dpart = fmaf(pv2[t], dot8_half(acc2, rowv[t]), dpart);
+                    if constexpr (SRC && NA == 2) add_dot(t0 + t < cnt, pv2[t], dot8_half(acc2, rowv[t]), dpart);
                   } else {
                     const float4 rv = make_float4(__uint_as_float(rowv[t].x), __uint_as_float(rowv[t].y),
                                                   __uint_as_float(rowv[t].z), __uint_as_float(rowv[t].w));
                     fma4(part[0], pv[t], rv);
                     if (DUAL) fma4(part2[0], pv2[t], rv);
-                    if (SRC) dpart = fmaf(pv2[t], dot4(acc2[0], rv), dpart);
+                    if (SRC) add_dot(t0 + t < cnt, pv2[t], dot4(acc2[0], rv), dpart);
                   }
                 }
               }
@@ -640,9 +641,9 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
                 false, sync_every > 0 ? sync_every : nblk};
 
   const bool gathers_first = ns >= 4;
-  const char* feat_bytes = reinterpret_cast<const char*>(feat);
   constexpr uint32_t kElem = HALF ? 2u : 4u;  // bytes per stored element of the gathered matrix
   const uint32_t row_bytes = (uint32_t)HF * kElem, col_bytes = (uint32_t)col * kElem;
+  const auto table = row_table(feat, NARROW ? (int64_t)n_rows * row_bytes : 0);
   using Halves = std::conditional_t<NA == 2, uint4, uint2>;
   using RowRaw = std::conditional_t<HALF, Halves, float4>;  // a lane's columns of a gathered row
   auto widen = [](const RowRaw& r, int a) {
@@ -751,8 +752,6 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
     // what a slot needs before its edge loop in phase p: bounds, first indices, (MODE 2) the row's own z
     auto fetch = [&](int p, int q) {
       Item it{};
-#pragma unroll
-      for (int a = 0; a < NA; ++a) it.c_first[a] = p * block_cols;
       if (q >= nslots) return it;
       const int2 sg = l_seg[(p & 1) * nslot + q];
       it.beg = sg.x;
@@ -819,7 +818,7 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
             int32_t ce[NE];  // the vertices at the far end of the lane's edges
 #pragma unroll
             for (int a = 0; a < NA; ++a) {
-              const int32_t c = li + L * a < cnt ? c_next[a] : col_begin;
+              const int32_t c = li + L * a < cnt ? c_next[a] : n_rows;  // no edge: zeros
               if (c0 + SL + li + L * a < end) c_next[a] = bcol[c0 + SL + li + L * a];
               l_idx[li + L * a] = c;
               ce[a] = c;
@@ -870,15 +869,10 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
 #pragma unroll
               for (int t4 = 0; t4 < U; t4 += 4) {
                 if (!SKIP || t0 + t4 < cnt) {
-                  if constexpr (NARROW) {  // 32-bit byte offsets from a scalar base reach every row
 #pragma unroll
-                    for (int t = t4; t < t4 + 4; ++t)
-                      rowv[t] = *reinterpret_cast<const RowRaw*>(
-                          feat_bytes + (__umul24((uint32_t)idv[t], row_bytes) + col_bytes));
-                  } else {
-#pragma unroll
-                    for (int t = t4; t < t4 + 4; ++t)
-                      rowv[t] = *reinterpret_cast<const RowRaw*>(feat_bytes + ((int64_t)idv[t] * row_bytes + col_bytes));
+                  for (int t = t4; t < t4 + 4; ++t) {
+                    if constexpr (NARROW) rowv[t] = table_load<RowRaw>(table, idv[t], row_bytes, col_bytes);
+                    else rowv[t] = table_load_wide<RowRaw>(feat, n_rows, idv[t], row_bytes, col_bytes);
                   }
                 }
               }
@@ -978,7 +972,7 @@ __global__ __launch_bounds__(kGatResThreads) void k_gat_res(
                       const float4 rv = widen(rowv[t], a);
                       fma4(part[a], pv[t], rv);
                       if (DUAL) fma4(part2[a], pv2[t], rv);
-                      if (SRC) dpart[a] = fmaf(pv2[t], dot4(acc2[a], rv), dpart[a]);
+                      if (SRC) add_dot(t0 + t < cnt, pv2[t], dot4(acc2[a], rv), dpart[a]);
                     }
                 }
               }
@@ -1189,8 +1183,7 @@ static gnn_status_t launch_blocks_impl(const gnn_graph_t* g, int side, const cha
   const int ns = dm.HF / ((HALF ? 8 : 4) * SL);
   const int sph = ns / dm.H;
   // 32-bit byte offsets (and 24-bit multiplies) reach every gathered row
-  const int narrow = (int64_t)g->n * dm.HF * 4 < ((int64_t)1 << 32) && g->n < (1 << 24) &&
-                     !config_get(kCfgWideOffsets);
+  const int narrow = row_offsets_ok(g->n, 4 * dm.HF) && !config_get(kCfgWideOffsets);
   constexpr int GS = kBlkGroupFloats<SL>;
   const int rows_per_wg = (kBlkThreads / SL) * kRowsPerGroup;
   const unsigned grid = (unsigned)(cdiv(g->n, rows_per_wg) * ns);
@@ -1332,7 +1325,7 @@ static gnn_status_t launch_resident_parts(const gnn_graph_t* g, int side, const 
 
 // 32-bit byte offsets (and 24-bit multiplies) reach every gathered row
 static bool gat_resident_narrow(const gnn_graph_t* g, GatDims dm) {
-  return (int64_t)g->n * dm.HF * 4 < ((int64_t)1 << 32) && g->n < (1 << 24) && !config_get(kCfgWideOffsets);
+  return row_offsets_ok(g->n, 4 * dm.HF) && !config_get(kCfgWideOffsets);
 }
 
 template <int MODE, int NA, int HS, bool TAB, bool SKIP, bool HALF>

@@ -105,6 +105,30 @@ __device__ __forceinline__ void phase_step_done(PhaseClock& pc, int step) {
 
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 __device__ __forceinline__ void st4(float* p, float4 v) { *reinterpret_cast<float4*>(p) = v; }
+// Rows of a table of n rows that a kernel gathers with 32-bit byte offsets come through a buffer resource: a load past the table's end
+// gives zeros and touches no memory.  Lanes without an edge gather row n, so what is not finite in a row stays with the rows that gather
+// it: with weight 0, a row of the table in its place would give 0 * Inf.
+__host__ __device__ __forceinline__ bool row_offsets_ok(int64_t n, int row_bytes) {  // and the factors fit __umul24
+  return n < (1 << 24) && row_bytes < (1 << 24) && (n + 1) * row_bytes <= (int64_t)0xFFFFFFFF;
+}
+__device__ __forceinline__ auto row_table(const void* p, int64_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (uint32_t)bytes, 0x00020000);
+}
+template <typename T, typename Table>
+__device__ __forceinline__ T table_load(Table table, int32_t row, uint32_t row_bytes, uint32_t lane_bytes) {
+  static_assert(sizeof(T) == 8 || sizeof(T) == 16, "two or four words");
+  const uint32_t offset = __umul24((uint32_t)row, row_bytes) + lane_bytes;
+  if constexpr (sizeof(T) == 16) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(table, offset, 0, 0));
+  else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(table, offset, 0, 0));
+}
+// the same of a table that needs wider offsets
+template <typename T>
+__device__ __forceinline__ T table_load_wide(const void* base, int32_t n, int32_t row, uint32_t row_bytes, uint32_t lane_bytes) {
+  T v{};
+  if (row != n) v = *reinterpret_cast<const T*>(static_cast<const char*>(base) + ((int64_t)row * row_bytes + lane_bytes));
+  return v;
+}
+
 // streaming variants: data that is touched once per launch is marked non-temporal so that it
 // does not displace the cache-resident gathered rows
 typedef float nt_f4 __attribute__((ext_vector_type(4)));

@@ -51,3 +51,15 @@ PRODUCT_RTOL = 1e-6
 
 def relative_error(got, ref):
     return np.linalg.norm(np.asarray(got, dtype=np.float64) - ref) / np.linalg.norm(ref)
+
+
+def graph_with_unheard_vertices(rng, n, pairs, block_cols):
+    """A random graph whose first vertex of every column block is without edges, but for one: vertex `block_cols` hears from
+    vertex 3 and is heard by vertex 5.  Most rows have no multiple of four edges in a block."""
+    indptr, indices = random_graph(rng, n, pairs, self_loops=False, duplicates=True)
+    rows = [indices[indptr[v]:indptr[v + 1]] for v in range(n)]
+    rows = [row[row % block_cols != 0] if v % block_cols else row[:0] for v, row in enumerate(rows)]
+    rows[block_cols] = np.array([3])
+    rows[5] = np.sort(np.append(rows[5], block_cols))
+    indptr = np.concatenate(([0], np.cumsum([len(r) for r in rows]))).astype(np.int32)
+    return indptr, np.concatenate(rows).astype(np.int32)

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 from oracle import gat as og
-from helpers import random_graph, tiny_graph
+from helpers import graph_with_unheard_vertices, random_graph, tiny_graph
 from workloads import make
 
 pytestmark = pytest.mark.gpu
@@ -817,3 +817,46 @@ def test_parameter_gradients_summed_in_one_launch(n, fin, H, F):
     c = synth(rng, indptr, indices, fin, H, F)
     fwd, bwd = oracle_all(c)
     compare(c, run_gat(c), fwd, bwd)
+
+
+@pytest.mark.parametrize("H,F,block_cols", [(8, 8, 300), (4, 16, 256), (2, 32, 300), (8, 16, 256), (4, 32, 300), (1, 44, 256), (1, 64, 300),
+                                            (1, 128, 256), (4, 64, 300), (2, 256, 256), (4, 256, 300)])
+@pytest.mark.parametrize("resident", [2, 0])
+def test_what_is_not_finite_stays_with_its_neighbours(H, F, block_cols, resident):
+    """Non-finite rows of z (forward) and gout (backward) at the first vertex of every column block, which one row gathers in one
+    block and none in the others: every other row keeps its bits.  fp32 and fp16 rows, 32-bit and 64-bit offsets."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import dev, run_gat
+    print(f"gat: not finite H={H} F={F} block_cols={block_cols} resident={resident}", flush=True)
+    rng = np.random.default_rng(block_cols + H + F)
+    n = 1500
+    indptr, indices = graph_with_unheard_vertices(rng, n, 30000, block_cols)
+    c = synth(rng, indptr, indices, 24, H, F)
+    first = np.arange(0, n, block_cols)
+    bad_x, bad_g = dict(c, x=c["x"].copy()), dict(c, gout=c["gout"].copy())
+    bad_x["x"][first[::2]], bad_x["x"][first[1::2]] = np.inf, np.nan
+    bad_g["gout"][first[::2]], bad_g["gout"][first[1::2]] = np.nan, -np.inf
+    out_rows, gx_rows = np.ones(n, bool), np.ones(n, bool)
+    out_rows[[5, *first]] = False
+    gx_rows[[3, *first]] = False
+    pk.gnn_config_set("block_cols", block_cols)
+    pk.gnn_config_set("resident_sums", resident)
+    try:
+        g = pk.Graph(dev(indptr), dev(indices))
+        for half, wide in ((0, 0), (0, 1), (1, 0)):
+            pk.gnn_config_set("gather_precision", half)
+            pk.gnn_config_set("wide_offsets", wide)
+            for kw in (dict(stash=True), dict(stash=False), dict(alpha_stash=True)):
+                ok, x, go = (run_gat(d, graph=g, **kw) for d in (c, bad_x, bad_g))
+                for key in ("out", "t", "sg", "m", "d"):
+                    if key in ok:
+                        assert np.array_equal(x[key][out_rows], ok[key][out_rows]), (half, wide, kw, key)
+                assert not np.isfinite(x["out"][5]).any()
+                assert np.array_equal(go["gx"][gx_rows], ok["gx"][gx_rows]), (half, wide, kw)
+                assert not np.isfinite(go["gx"][3]).any()
+        g.close()
+    finally:
+        pk.gnn_config_set("gather_precision", 0)
+        pk.gnn_config_set("wide_offsets", 0)
+        pk.gnn_config_set("resident_sums", 1)
+        pk.gnn_config_set("block_cols", 12288)
