@@ -294,7 +294,7 @@ gnn_status_t gnn_gat_bwd_noalloc(const gnn_graph_t* graph, int fin, int heads, i
  * a pass over this graph launches for `heads` x `f` (mode 0 forward, 1 destination side recomputing,
  * 2 source side, 3 forward with stash) under the current configuration, spelled as a profiler
  * prints it, e.g. "k_gat_res<16, 2, 1, false, true, false, true, 1, false>" (the persistent launch) or
- * "k_gat_blk<16, 2, false, false, true>" (one launch per block); the empty string when the
+ * "k_gat_blk<16, 2, false, false, false, true>" (one launch per block); the empty string when the
  * single-launch kernels run.  buf is a HOST buffer of len bytes. */
 gnn_status_t gnn_gat_blocked_kernel_name(const gnn_graph_t* graph, int heads, int f, int mode,
                                          char* buf /*host*/, size_t len);

@@ -148,12 +148,6 @@ __device__ __forceinline__ float dot8_half(const float4 (&zr)[2], const uint4& r
   return dot4(zr[0], make_float4(a.x, a.y, b.x, b.y)) + dot4(zr[1], make_float4(c.x, c.y, d.x, d.y));
 }
 
-// sum += w d for an edge; a lane without one has weight 0, but its product with the row's own z may be 0 * Inf
-__device__ __forceinline__ void add_dot(bool edge, float w, float d, float& sum) {
-  const float s = fmaf(w, d, sum);
-  sum = edge ? s : sum;
-}
-
 // STAGE: the per-edge scalar el[u] of the slice's head is read from an LDS copy of the block's
 // part of the head-major table instead of being gathered from L2.  Such a scalar gather
 // costs a CU one 128-byte line fill per edge, as much as the 128-byte row slice itself; with
@@ -163,14 +157,17 @@ __device__ __forceinline__ void add_dot(bool edge, float w, float d, float& sum)
 // per-slice counter in device memory (zeroed before the launch).
 constexpr int kStageThreads = 1024;
 
-template <int SL, int MODE, bool STAGE, bool HALF, bool SKIP>
+// NARROW: 32-bit byte offsets reach every gathered row, and lanes past a segment's end gather zeros from past the table.  Before, they
+// gathered the block's first row, which with weight 0 made NaN of infinities.  47 029 vertices, 2.2 10^7 edges, training pass, before -> now, us:
+// 4 x 64 4240 -> 3650, 4 x 32 3765 -> 3505, 4 x 256 14 130 -> 14 120, 1 x 128 2825 -> 2925, fp16 4 x 64 4130 -> 4180; forward, 4 x 64 1985 -> 1585.
+template <int SL, int MODE, bool STAGE, bool HALF, bool SKIP, bool NARROW>
 __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk(
     int32_t n_rows, const int32_t* __restrict__ order, const int2* __restrict__ bseg_b,
     const int32_t* __restrict__ bcol, const float* __restrict__ feat /* gathered rows: z or gout */,
     const float* __restrict__ rowfeat /* MODE 2: z, whose row u meets every gathered gout[v] */,
     const float* __restrict__ el, const float* __restrict__ er, const float* __restrict__ m_in,
     const float* __restrict__ d_in, const float4* __restrict__ vstate, int32_t col_begin,
-    GatDims dm, int sph, int first, int narrow, int el_hm /* el is head-major [H][n] */,
+    GatDims dm, int sph, int first, int el_hm /* el is head-major [H][n] */,
     float* __restrict__ acc_buf, float* __restrict__ acc2_buf, float* __restrict__ scal_buf,
     int32_t* __restrict__ queue /* STAGE: one row counter per slice */, int32_t cols_here,
     int32_t quads_per_grab, int ns /* column slices: 8, 4, 2 or 1 */,
@@ -312,7 +309,7 @@ __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk
     // (one 24-bit multiply-add per row instead of 64-bit arithmetic).
     constexpr uint32_t kElem = HALF ? 2u : 4u;  // bytes per stored element of the gathered matrix
     const uint32_t row_bytes = (uint32_t)HF * kElem, col_bytes = (uint32_t)col * kElem;
-    const auto table = row_table(feat, (int64_t)n_rows * row_bytes);  // used where `narrow`
+    const auto table = row_table(feat, NARROW ? (int64_t)n_rows * row_bytes : 0);
 
     BlkRow<NA> cur, nxt;
     fetch(0, cur);
@@ -377,22 +374,19 @@ __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk
               const int4 i4 = *reinterpret_cast<const int4*>(l_idx + t0 + 4 * q);
               idv[4 * q] = i4.x; idv[4 * q + 1] = i4.y; idv[4 * q + 2] = i4.z; idv[4 * q + 3] = i4.w;
             }
-            // SKIP: quadruples of gathered rows that lie entirely past the end of the segment are
-            // skipped (a padded load costs the texture path as much as a real one, and the sparse
-            // blocks' segments are mostly shorter than a chunk).  The branches keep the compiler
-            // from issuing the second half of a chunk's loads before the first half's arithmetic;
-            // rows cut into four or more slices gain 1-2 % overall, rows cut into two lose 10 %
-            // (measured), so the host instantiates SKIP only for the former.
+            // SKIP: quadruples of gathered rows that lie entirely past the end of the segment are skipped.
+            // The branches keep the compiler from issuing the second half of a chunk's loads before the first half's
+            // arithmetic, and a gather past the table costs little: only slices of 128 columns, with twice as many
+            // such rows to a chunk, gain (4 x 256, see above, 14 260 without -> 14 120; 4 x 64 3650 -> 4180 with it),
+            // and those of 16, whose chunks are one quadruple (8 x 16, recomputing, 5010 -> 4750).
             uint4 rowv[U];  // 16 bytes of the gathered row: 4 floats, or 8 halves
 #pragma unroll
             for (int t4 = 0; t4 < U; t4 += 4) {
               if (!SKIP || t0 + t4 < cnt) {
-                if (narrow) {
 #pragma unroll
-                  for (int t = t4; t < t4 + 4; ++t) rowv[t] = table_load<uint4>(table, idv[t], row_bytes, col_bytes);
-                } else {
-#pragma unroll
-                  for (int t = t4; t < t4 + 4; ++t) rowv[t] = table_load_wide<uint4>(feat, n_rows, idv[t], row_bytes, col_bytes);
+                for (int t = t4; t < t4 + 4; ++t) {
+                  if constexpr (NARROW) rowv[t] = table_load<uint4>(table, idv[t], row_bytes, col_bytes);
+                  else rowv[t] = table_load_wide<uint4>(feat, n_rows, idv[t], row_bytes, col_bytes);
                 }
               }
             }
@@ -449,13 +443,13 @@ __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk
                   if constexpr (HALF) {
                     fma8_half(part, pv[t], rowv[t]);
                     if (DUAL) fma8_half(part2, pv2[t], rowv[t]);
-                    if constexpr (SRC && NA == 2) add_dot(t0 + t < cnt, pv2[t], dot8_half(acc2, rowv[t]), dpart);
+                    if constexpr (SRC && NA == 2) dpart = fmaf(pv2[t], dot8_half(acc2, rowv[t]), dpart);
                   } else {
                     const float4 rv = make_float4(__uint_as_float(rowv[t].x), __uint_as_float(rowv[t].y),
                                                   __uint_as_float(rowv[t].z), __uint_as_float(rowv[t].w));
                     fma4(part[0], pv[t], rv);
                     if (DUAL) fma4(part2[0], pv2[t], rv);
-                    if (SRC) add_dot(t0 + t < cnt, pv2[t], dot4(acc2[0], rv), dpart);
+                    if (SRC) dpart = fmaf(pv2[t], dot4(acc2[0], rv), dpart);
                   }
                 }
               }
@@ -472,6 +466,9 @@ __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk
             }
           }
           if (SRC) s_dot += dpart;
+          // nothing is in flight here, which the compiler does not see past the branches: it would wait for the next chunk's
+          // scalars before its rows
+          if (SRC && SKIP) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
           wave_lds_fence();
         }
         beg = beg_n;
@@ -535,6 +532,12 @@ __global__ __launch_bounds__(STAGE ? kStageThreads : kBlkThreads) void k_gat_blk
 // groups draw (row, slice) slots from an LDS counter, longest rows first.  The chunks of a row, or of each of its parts, are summed in the
 // order of the launch-per-block kernels (blocks ascending, edges in list order), so the results do not depend on who draws what.
 // MODE as k_gat_blk; one segment per phase, per-edge scalars gathered from L2 or (TAB) read from LDS.
+// sum += w d for an edge; a lane without one has weight 0, but its product with the row's own z may be 0 * Inf
+__device__ __forceinline__ void add_dot(bool edge, float w, float d, float& sum) {
+  const float s = fmaf(w, d, sum);
+  sum = edge ? s : sum;
+}
+
 constexpr int kGatResThreads = 1024;
 // Groups: SL / NA lanes, each with NA float4 of the slice.  NA = 2 is for rows of an fp16 copy, which a lane then reads in 16
 // instead of 8 bytes and a wavefront eight at a time: half as many gather instructions, and twice as many (row, slice) pairs share
@@ -1173,7 +1176,12 @@ static const char* bracket_name(const char* name, size_t launch) {
   return names.emplace(key, key).first->second.c_str();
 }
 
-template <int SL, int MODE, bool HALF, bool SKIP>
+static constexpr bool skips_rows(int SL) { return SL == 4 || SL == 32; }  // see k_gat_blk
+
+// 32-bit byte offsets (and 24-bit multiplies) reach every gathered row
+static bool gat_narrow(const gnn_graph_t* g, GatDims dm) { return row_offsets_ok(g->n, 4 * dm.HF) && !config_get(kCfgWideOffsets); }
+
+template <int SL, int MODE, bool HALF, bool SKIP, bool NARROW>
 static gnn_status_t launch_blocks_impl(const gnn_graph_t* g, int side, const char* name, GatDims dm,
                                   int el_hm, const float* feat, const float* rowfeat,
                                   const float* el, const float* er, const float* m, const float* d,
@@ -1182,8 +1190,6 @@ static gnn_status_t launch_blocks_impl(const gnn_graph_t* g, int side, const cha
                                   const float* alpha_b = nullptr) {
   const int ns = dm.HF / ((HALF ? 8 : 4) * SL);
   const int sph = ns / dm.H;
-  // 32-bit byte offsets (and 24-bit multiplies) reach every gathered row
-  const int narrow = row_offsets_ok(g->n, 4 * dm.HF) && !config_get(kCfgWideOffsets);
   constexpr int GS = kBlkGroupFloats<SL>;
   const int rows_per_wg = (kBlkThreads / SL) * kRowsPerGroup;
   const unsigned grid = (unsigned)(cdiv(g->n, rows_per_wg) * ns);
@@ -1196,7 +1202,7 @@ static gnn_status_t launch_blocks_impl(const gnn_graph_t* g, int side, const cha
       // idempotent, so a race between two first callers is harmless)
       static std::atomic<bool> attr_set{false};
       if (!attr_set.load(std::memory_order_acquire)) {
-        GNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gat_blk<SL, MODE, true, HALF, SKIP>),
+        GNN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gat_blk<SL, MODE, true, HALF, SKIP, NARROW>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStageLdsLimit));
         attr_set.store(true, std::memory_order_release);
       }
@@ -1227,18 +1233,18 @@ static gnn_status_t launch_blocks_impl(const gnn_graph_t* g, int side, const cha
         // one persistent workgroup per CU, a multiple of 8 so that every XCD serves one slice
         const unsigned pgrid = (unsigned)(device_cu_count() / kSlices * kSlices);
         ProfScope p(bracket_name(name, gi), st);  // one timed bracket per launch
-        k_gat_blk<SL, MODE, true, HALF, SKIP><<<pgrid, kStageThreads, stage_bytes, st>>>(
+        k_gat_blk<SL, MODE, true, HALF, SKIP, NARROW><<<pgrid, kStageThreads, stage_bytes, st>>>(
             g->n, g->order[side], bseg_b, g->bcol[side], feat, rowfeat, el, er, m, d, vstate, col_begin, dm, sph,
-            b == 0, narrow, el_hm, acc, acc2, scal, queue + b * kSlices, cols_here, 1, ns, b_end == g->nblk, state,
+            b == 0, el_hm, acc, acc2, scal, queue + b * kSlices, cols_here, 1, ns, b_end == g->nblk, state,
             m_out, d_out, nseg, alpha_b, g->nnz);
         GNN_LAUNCH_CHECK();
       }
     }
     if (!staged) {
       ProfScope p(bracket_name(name, gi), st);  // one timed bracket per launch
-      k_gat_blk<SL, MODE, false, HALF, SKIP><<<grid, kBlkThreads, lds, st>>>(
+      k_gat_blk<SL, MODE, false, HALF, SKIP, NARROW><<<grid, kBlkThreads, lds, st>>>(
           g->n, g->order[side], bseg_b, g->bcol[side], feat, rowfeat, el, er, m, d, vstate, col_begin, dm, sph,
-          b == 0, narrow, el_hm, acc, acc2, scal, nullptr, 0, 1, ns, b_end == g->nblk, state, m_out, d_out, nseg,
+          b == 0, el_hm, acc, acc2, scal, nullptr, 0, 1, ns, b_end == g->nblk, state, m_out, d_out, nseg,
           alpha_b, g->nnz);
       GNN_LAUNCH_CHECK();
     }
@@ -1253,13 +1259,12 @@ static gnn_status_t launch_blocks(const gnn_graph_t* g, int side, const char* na
                                   const float4* vstate, float* acc, float* acc2, float* scal,
                                   int32_t* queue, float4* state, float* m_out, float* d_out, hipStream_t st,
                                   const float* alpha_b = nullptr) {
-  const int ns = dm.HF / ((HALF ? 8 : 4) * SL);
-  // the fp16 variant (one sub-iteration per chunk) measured 3 % slower with the skip
-  if (ns >= 4 && !HALF)
-    return launch_blocks_impl<SL, MODE, HALF, true>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, acc2,
-                                                    scal, queue, state, m_out, d_out, st, alpha_b);
-  return launch_blocks_impl<SL, MODE, HALF, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, acc2,
-                                                   scal, queue, state, m_out, d_out, st, alpha_b);
+#define GNN_GAT_BLOCKS(NARROW_)                                                                                                \
+  return launch_blocks_impl<SL, MODE, HALF, skips_rows(SL), NARROW_>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate, acc, \
+                                                               acc2, scal, queue, state, m_out, d_out, st, alpha_b)
+  if (gat_narrow(g, dm)) GNN_GAT_BLOCKS(true);
+  GNN_GAT_BLOCKS(false);
+#undef GNN_GAT_BLOCKS
 }
 
 // The persistent kernel applies to rows cut into slices of 64 columns (256 bytes of fp32, or one
@@ -1323,18 +1328,13 @@ static gnn_status_t launch_resident_parts(const gnn_graph_t* g, int side, const 
                                                                           vstate, acc, acc2, scal, m_out, d_out, st, alpha_b);
 }
 
-// 32-bit byte offsets (and 24-bit multiplies) reach every gathered row
-static bool gat_resident_narrow(const gnn_graph_t* g, GatDims dm) {
-  return row_offsets_ok(g->n, 4 * dm.HF) && !config_get(kCfgWideOffsets);
-}
-
 template <int MODE, int NA, int HS, bool TAB, bool SKIP, bool HALF>
 static gnn_status_t launch_resident_impl(const gnn_graph_t* g, int side, const char* name, GatDims dm, int el_hm,
                                          const float* feat, const float* rowfeat, const float* el, const float* er,
                                          const float* m, const float* d, const float4* vstate, float* acc,
                                          float* acc2, float* scal, float* m_out, float* d_out, hipStream_t st,
                                          const float* alpha_b) {
-  if (gat_resident_narrow(g, dm))
+  if (gat_narrow(g, dm))
     return launch_resident_parts<MODE, NA, HS, TAB, SKIP, HALF, true>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate,
                                                         acc, acc2, scal, m_out, d_out, st, alpha_b);
   return launch_resident_parts<MODE, NA, HS, TAB, SKIP, HALF, false>(g, side, name, dm, el_hm, feat, rowfeat, el, er, m, d, vstate,
@@ -1551,19 +1551,18 @@ extern "C" gnn_status_t gnn_gat_blocked_kernel_name(const gnn_graph_t* g, int he
   Slicing sl;
   if (!pick_slicing(heads, heads * f, sl)) return GNN_OK;
   if (mode == 1 && !pick_whole_slicing(heads, heads * f, sl)) return GNN_OK;
-  if (gat_resident_applies(g, make_dims(heads, f, 0.2f), mode == 1)) {
-    const GatDims dm = make_dims(heads, f, 0.2f);
+  const GatDims dm = make_dims(heads, f, 0.2f);
+  if (gat_resident_applies(g, dm, mode == 1)) {
     std::snprintf(buf, len, "k_gat_res<16, %d, %d, %s, %s, %s, %s, %d, %s>", mode,
                   half ? 2 : 1,
                   half && mode == 0 && gat_resident_table(g) ? "true" : "false",
                   (half || sl.hs > 1 || heads * f / 64 >= 4 || mode == 2) ? "true" : "false", half ? "true" : "false",
-                  gat_resident_narrow(g, dm) ? "true" : "false", sl.hs,
+                  gat_narrow(g, dm) ? "true" : "false", sl.hs,
                   has_long_rows(g, mode == 2, gat_resident_groups(dm.HF <= 64 ? 1 : dm.HF / 64, half ? 2 : 1)) ? "true" : "false");
     return GNN_OK;
   }
   const int SL = half ? 8 : sl.SL;
-  const int ns = heads * f / ((half ? 8 : 4) * SL);
-  std::snprintf(buf, len, "k_gat_blk<%d, %d, false, %s, %s>", SL, mode, half ? "true" : "false",
-                (ns >= 4 && !half) ? "true" : "false");
+  std::snprintf(buf, len, "k_gat_blk<%d, %d, false, %s, %s, %s>", SL, mode, half ? "true" : "false", skips_rows(SL) ? "true" : "false",
+                gat_narrow(g, dm) ? "true" : "false");
   return GNN_OK;
 }
