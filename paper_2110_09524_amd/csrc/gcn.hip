@@ -42,12 +42,16 @@ __global__ void k_scale_rows(int64_t quads, int q_per_row, const float* __restri
   st4(out + 4 * i, make_float4(s * v.x, s * v.y, s * v.z, s * v.w));
 }
 
+static bool gcn_narrow(const gnn_graph_t* g, int F) { return row_offsets_ok(g->n, 4 * F) && !config_get(kCfgWideOffsets); }
+
 // ---- single launch: out[row,:] = scale[row] * sum over the row's gathered vertices of feat ----
 // W: every edge carries a static weight (wgt, in the order of cols); scale may then be null
 // Rows come with their bounds, and the next chunk's sources travel while a chunk is gathered: us, 30 000 vertices, 10^6 edges,
 // 64 columns, layer 111 -> 99 unsliced.  NS slices of 4 L columns, see xcd_slice and gather_slices.
 // U gathered rows in flight per lane, see launch_rowsum.
-template <int L, int NV, bool W, int NS, int U>
+// NARROW: 32-bit byte offsets reach every gathered row (told at run time, the loads of one kind wait for those of the other: 64 columns
+// with a weight per edge, 10^5 vertices, 2 10^6 edges, layer 145.9 -> 147.4 us).
+template <int L, int NV, bool W, int NS, int U, bool NARROW>
 __global__ __launch_bounds__(kGcnBlock) void k_rowsum(
     RowLaunch rl, const int4* __restrict__ rows, const int32_t* __restrict__ cols, const float* __restrict__ feat, int F,
     const float* __restrict__ scale, float* __restrict__ out, const float* __restrict__ wgt = nullptr) {
@@ -67,8 +71,9 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum(
   unsigned block;
   const int col0 = xcd_slice<NS>(block) * 4 * L;
   if (!pick_row<GPB>(rl, grp, rr, r, gi, ngrp, block)) return;
-  feat += col0;
   out += col0;
+  const uint32_t row_bytes = 4u * F, lane_bytes = 4u * (col0 + 4 * li);
+  const auto table = row_table(feat, NARROW ? (int64_t)rl.n_rows * row_bytes : 0);
   int* l_idx = lds + grp * L;
   float* l_w = lds_w + (W ? grp * L : 0);
   const int4 row = rows[r];
@@ -83,14 +88,15 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum(
     acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   uint32_t c0 = row.y + gi * L;
-  int32_t c_next = c0 + li < end ? cols[c0 + li] : 0;  // the next chunk's sources travel while this one is gathered
+  // the next chunk's sources travel while this one is gathered; no edge: row n_rows, zeros
+  int32_t c_next = c0 + li < end ? cols[c0 + li] : rl.n_rows;
   float w_next = W && c0 + li < end ? wgt[c0 + li] : 0.f;
   for (; c0 < end; c0 += ngrp * L) {
     l_idx[li] = c_next;
     if (W) l_w[li] = w_next;
     wave_lds_fence();
     const uint32_t e = c0 + ngrp * L + li;
-    c_next = e < end ? cols[e] : 0;
+    c_next = e < end ? cols[e] : rl.n_rows;
     if (W) w_next = e < end ? wgt[e] : 0.f;
     float4 part[NV];  // this chunk's share (two-level summation)
 #pragma unroll
@@ -103,7 +109,7 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum(
       for (int t = 0; t < U; ++t) {
         uu[t] = l_idx[t0 + t];
         if (L == 64) uu[t] = __builtin_amdgcn_readfirstlane(uu[t]);
-        ww[t] = W ? l_w[t0 + t] : (t0 + t < cnt ? 1.f : 0.f);  // padding adds 0 * row 0
+        if (W) ww[t] = l_w[t0 + t];
       }
 #pragma unroll
       for (int j = 0; j < NV; ++j) {
@@ -112,14 +118,21 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum(
 #pragma unroll
         for (int q = 0; q < U; q += B)
           if (t0 + q < cnt) {
+            const uint32_t at = lane_bytes + 16u * (j * L);
 #pragma unroll
-            for (int t = q; t < q + B; ++t) rowv[t] = ld4(feat + (int64_t)uu[t] * F + 4 * (li + j * L));
+            for (int t = q; t < q + B; ++t) {
+              if constexpr (NARROW) rowv[t] = table_load<float4>(table, uu[t], row_bytes, at);
+              else rowv[t] = table_load_wide<float4>(feat, rl.n_rows, uu[t], row_bytes, at);
+            }
           }
 #pragma unroll
         for (int q = 0; q < U; q += B)
           if (t0 + q < cnt) {
 #pragma unroll
-            for (int t = q; t < q + B; ++t) fma4(part[j], ww[t], rowv[t]);
+            for (int t = q; t < q + B; ++t) {
+              if (W) fma4(part[j], ww[t], rowv[t]);
+              else add4(part[j], rowv[t]);
+            }
           }
       }
     }
@@ -178,7 +191,7 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum_eb(
   int* l_idx = lds + grp * GS;
   float* l_wt = reinterpret_cast<float*>(l_idx + kEbEdges + U);
   for (int i = li; i < kEbEdges + U; i += L) {
-    l_idx[i] = e0 + i < e1 ? cols[e0 + i] : 0;  // padding gathers row 0, weight 0
+    l_idx[i] = e0 + i < e1 ? cols[e0 + i] : 0;  // padding gathers row 0, for nothing
     if (W) l_wt[i] = e0 + i < e1 ? wgt[e0 + i] : 0.f;
   }
 
@@ -216,7 +229,7 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum_eb(
         for (int t = 0; t < U; ++t) rowv[t] = ld4(feat + (int64_t)uu[t] * F + 4 * (li + j * L));
 #pragma unroll
         for (int t = 0; t < U; ++t)
-          fma4(acc[j], t0 + t < seg_end ? (W ? l_wt[t0 - e0 + t] : 1.f) : 0.f, rowv[t]);
+          if (t0 + t < seg_end) fma4(acc[j], W ? l_wt[t0 - e0 + t] : 1.f, rowv[t]);
       }
     }
     const float s = scale != nullptr ? scale[v] : 1.f;
@@ -251,11 +264,11 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum_eb(
 template <int SL, bool SKIP, bool W = false>
 __global__ __launch_bounds__(kGcnBlock) void k_rowsum_blk(
     int32_t n_rows, const int32_t* __restrict__ order, const int2* __restrict__ bseg_b,
-    const int32_t* __restrict__ bcol, const float* __restrict__ feat, int32_t col_begin, int F,
+    const int32_t* __restrict__ bcol, const float* __restrict__ feat, int F,
     int first, int ns /* column slices: 8, 4, 2 or 1 */, float* __restrict__ acc_buf,
     int nseg /* adjacent column blocks of this launch (1 .. kMaxMerge): segment j of the row at
                 position r of the degree order is bseg_b[j * n_rows + r] */,
-    const float* __restrict__ bw = nullptr) {
+    int narrow /* 32-bit byte offsets reach every gathered row */, const float* __restrict__ bw = nullptr) {
   constexpr int GPB = kGcnBlock / SL;
   constexpr int R = kGcnRows;
   constexpr int U = SL < 8 ? 4 : 8;
@@ -274,6 +287,8 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum_blk(
   int2* l_seg = reinterpret_cast<int2*>(l_row + R);  // [R][kMaxMerge]
   float* l_w = reinterpret_cast<float*>(l_idx + SL + R + 2 * R * kMaxMerge);
   const int col = slice * 4 * SL + 4 * li;
+  const uint32_t row_bytes = 4u * F, col_bytes = 4u * col;
+  const auto table = row_table(feat, (int64_t)n_rows * row_bytes);  // used where `narrow`
 
   if (li < R) {
     const int64_t r = r0 + li;
@@ -301,7 +316,7 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum_blk(
     const int2 seg0 = l_seg[k * kMaxMerge];
     s.beg = seg0.x;
     s.end = seg0.y;
-    s.c_first = col_begin;
+    s.c_first = 0;
     s.w_first = 0.f;
     s.acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (s.row < 0) return;
@@ -323,7 +338,7 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum_blk(
       for (int sgi = 0; sgi < nseg; ++sgi) {
       // the bounds and the first indices of the row's segment in the next block are in flight
       // while this one is processed
-      int32_t beg_n = 0, end_n = 0, c_first_n = col_begin;
+      int32_t beg_n = 0, end_n = 0, c_first_n = 0;
       float w_first_n = 0.f;
       if (sgi + 1 < nseg) {
         const int2 sn = l_seg[k * kMaxMerge + sgi + 1];
@@ -335,13 +350,11 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum_blk(
         }
       }
       for (int32_t c0 = beg; c0 < end; c0 += SL) {
-        // lanes past the end point at the block's first vertex (valid, cache-resident) and
-        // their rows are multiplied by 0; with SKIP, quadruples of gathered rows that lie
-        // entirely past the end are skipped (a padded load costs the texture path as much as a
-        // real one).  The branches cost the overlap of the second half's loads with the first
+        // lanes past the end gather zeros; with SKIP, quadruples of gathered rows that lie
+        // entirely past the end are skipped.  The branches cost the overlap of the second half's loads with the first
         // half's sums: rows cut into four or more slices gain 2 % overall, rows cut into two lose
         // 24 % (measured), so SKIP is instantiated only for the former.
-        const int32_t c = c0 + li < end ? c_next : col_begin;
+        const int32_t c = c0 + li < end ? c_next : n_rows;
         const float wv = c0 + li < end ? w_next : 0.f;
         if (c0 + SL + li < end) {
           c_next = bcol[c0 + SL + li];
@@ -364,14 +377,22 @@ __global__ __launch_bounds__(kGcnBlock) void k_rowsum_blk(
 #pragma unroll
           for (int t4 = 0; t4 < U; t4 += 4)
             if (!SKIP || t0 + t4 < cnt) {
+              if (narrow) {  // uniform
 #pragma unroll
-              for (int t = t4; t < t4 + 4; ++t) rowv[t] = ld4(feat + (int64_t)idv[t] * F + col);
+                for (int t = t4; t < t4 + 4; ++t) rowv[t] = table_load<float4>(table, idv[t], row_bytes, col_bytes);
+              } else {
+#pragma unroll
+                for (int t = t4; t < t4 + 4; ++t) rowv[t] = table_load_wide<float4>(feat, n_rows, idv[t], row_bytes, col_bytes);
+              }
             }
 #pragma unroll
           for (int t4 = 0; t4 < U; t4 += 4)
             if (!SKIP || t0 + t4 < cnt) {
 #pragma unroll
-              for (int t = t4; t < t4 + 4; ++t) fma4(part, W ? l_w[t0 + t] : (t0 + t < cnt ? 1.f : 0.f), rowv[t]);
+              for (int t = t4; t < t4 + 4; ++t) {
+                if (W) fma4(part, l_w[t0 + t], rowv[t]);
+                else add4(part, rowv[t]);
+              }
             }
         }
         add4(acc, part);
@@ -448,8 +469,8 @@ __global__ __launch_bounds__(kResThreads) void k_rowsum_res(
   // cache line) and store nothing
   const bool col_ok = 4 * li < sw && slice * sw + 4 * li < F;
   const int col = col_ok ? slice * sw + 4 * li : slice * sw;
-  const char* feat_bytes = reinterpret_cast<const char*>(feat);
   const uint32_t row_bytes = 4u * F, col_bytes = 4u * col;
+  const auto table = row_table(feat, NARROW ? (int64_t)n_rows * row_bytes : 0);
 
   const int rows_here = (int)((n_rows + nwg - 1) / nwg);
   auto slots_to = [&](int j) { return PARTS ? slots_before(cut, j) : j; };
@@ -510,8 +531,6 @@ __global__ __launch_bounds__(kResThreads) void k_rowsum_res(
     // what a slot needs before its edge loop in phase p: bounds and first indices
     auto fetch = [&](int p, int q) {
       Item it{};
-#pragma unroll
-      for (int a = 0; a < NI; ++a) it.c_first[a] = p * block_cols;
       if (q >= nslots) return it;
       const int2 sg = l_seg[(p & 1) * NSLOT + q];
       it.beg = sg.x;
@@ -530,7 +549,6 @@ __global__ __launch_bounds__(kResThreads) void k_rowsum_res(
     Item cur = fetch(0, q);
 
     for (int p = 0; p < nblk; ++p) {
-      const int32_t col_begin = p * block_cols;
       // the next phase's bounds travel while this one is worked on
       int2 seg_next = make_int2(0, 0);
       if (p + 1 < nblk) seg_next = bounds(p + 1);
@@ -553,7 +571,7 @@ __global__ __launch_bounds__(kResThreads) void k_rowsum_res(
 #pragma unroll
             for (int a = 0; a < NI; ++a) {
               const int32_t e = c0 + li + SL * a;
-              l_idx[li + SL * a] = e < end ? c_next[a] : col_begin;
+              l_idx[li + SL * a] = e < end ? c_next[a] : n_rows;  // no edge: zeros
               if (W) l_w[li + SL * a] = e < end ? w_next[a] : 0.f;
               if (e + CH < end) {
                 c_next[a] = bcol[e + CH];
@@ -585,17 +603,18 @@ __global__ __launch_bounds__(kResThreads) void k_rowsum_res(
                 if (t0 + t4 < cn) {
 #pragma unroll
                   for (int t = t4; t < t4 + 4; ++t) {
-                    if constexpr (NARROW)  // 32-bit byte offsets from a scalar base reach every row
-                      rowv[t] = *reinterpret_cast<const float4*>(feat_bytes + (__umul24((uint32_t)idv[t], row_bytes) + col_bytes));
-                    else
-                      rowv[t] = ld4(feat + (int64_t)idv[t] * F + col);
+                    if constexpr (NARROW) rowv[t] = table_load<float4>(table, idv[t], row_bytes, col_bytes);
+                    else rowv[t] = table_load_wide<float4>(feat, n_rows, idv[t], row_bytes, col_bytes);
                   }
                 }
 #pragma unroll
               for (int t4 = 0; t4 < U; t4 += 4)
                 if (t0 + t4 < cn) {
 #pragma unroll
-                  for (int t = t4; t < t4 + 4; ++t) fma4(part4, W ? wv[t] : (t0 + t < cn ? 1.f : 0.f), rowv[t]);
+                  for (int t = t4; t < t4 + 4; ++t) {
+                    if (W) fma4(part4, wv[t], rowv[t]);
+                    else add4(part4, rowv[t]);
+                  }
                 }
             }
             add4(acc, part4);
@@ -683,6 +702,7 @@ static gnn_status_t launch_rowsum_blocks(const gnn_graph_t* g, int side, const c
   const int rows_per_wg = (kGcnBlock / SL) * kGcnRows;
   const int ns = F / (4 * SL);
   const unsigned grid = (unsigned)(cdiv(g->n, rows_per_wg) * ns);
+  const int narrow = gcn_narrow(g, F);
   const std::vector<int32_t>& groups = g->h_group[side][0];
   GNN_REQUIRE(groups.size() >= 2 && groups.front() == 0 && groups.back() == g->nblk, GNN_ERR_UNSUPPORTED,
               "gcn blocked: the plan has no launch groups");
@@ -691,18 +711,19 @@ static gnn_status_t launch_rowsum_blocks(const gnn_graph_t* g, int side, const c
     GNN_REQUIRE(nseg >= 1 && nseg <= kMaxMerge, GNN_ERR_UNSUPPORTED, "gcn blocked: bad launch group");
     const int2* bseg_b = reinterpret_cast<const int2*>(g->bseg[side]) + (int64_t)b * g->n;
     ProfScope p(name, st);  // one timed bracket per launch
+    const bool first = b == 0;
     if (bw != nullptr && ns >= 4)
-      k_rowsum_blk<SL, true, true><<<grid, kGcnBlock, 0, st>>>(g->n, g->order[side], bseg_b, g->bcol[side], feat,
-                                                              b * g->block_cols, F, b == 0, ns, acc, nseg, bw);
+      k_rowsum_blk<SL, true, true><<<grid, kGcnBlock, 0, st>>>(g->n, g->order[side], bseg_b, g->bcol[side], feat, F, first, ns, acc,
+                                                              nseg, narrow, bw);
     else if (bw != nullptr)
-      k_rowsum_blk<SL, false, true><<<grid, kGcnBlock, 0, st>>>(g->n, g->order[side], bseg_b, g->bcol[side], feat,
-                                                               b * g->block_cols, F, b == 0, ns, acc, nseg, bw);
+      k_rowsum_blk<SL, false, true><<<grid, kGcnBlock, 0, st>>>(g->n, g->order[side], bseg_b, g->bcol[side], feat, F, first, ns, acc,
+                                                               nseg, narrow, bw);
     else if (ns >= 4)
-      k_rowsum_blk<SL, true><<<grid, kGcnBlock, 0, st>>>(g->n, g->order[side], bseg_b, g->bcol[side], feat,
-                                                        b * g->block_cols, F, b == 0, ns, acc, nseg);
+      k_rowsum_blk<SL, true><<<grid, kGcnBlock, 0, st>>>(g->n, g->order[side], bseg_b, g->bcol[side], feat, F, first, ns, acc, nseg,
+                                                        narrow);
     else
-      k_rowsum_blk<SL, false><<<grid, kGcnBlock, 0, st>>>(g->n, g->order[side], bseg_b, g->bcol[side], feat,
-                                                         b * g->block_cols, F, b == 0, ns, acc, nseg);
+      k_rowsum_blk<SL, false><<<grid, kGcnBlock, 0, st>>>(g->n, g->order[side], bseg_b, g->bcol[side], feat, F, first, ns, acc, nseg,
+                                                         narrow);
     GNN_LAUNCH_CHECK();
   }
   return GNN_OK;
@@ -713,10 +734,6 @@ __global__ void k_zero_clock(int32_t* __restrict__ clock) { clock[threadIdx.x] =
 // one workgroup per CU, a multiple of the slice count so that every XCD serves one slice
 static unsigned gcn_resident_grid() { return (unsigned)(device_cu_count() / kXcds * kXcds); }
 static int64_t gcn_resident_groups(const GcnSlices& sl) { return (int64_t)gcn_resident_grid() / sl.ns * (kResThreads / sl.SL); }
-// 32-bit byte offsets (and 24-bit multiplies) reach every gathered row
-static bool gcn_resident_narrow(const gnn_graph_t* g, int F) {
-  return (int64_t)g->n * F * 4 < ((int64_t)1 << 32) && g->n < (1 << 24) && !config_get(kCfgWideOffsets);
-}
 
 template <int SL, bool W, bool NARROW, bool PARTS>
 static gnn_status_t launch_rowsum_resident_as(const gnn_graph_t* g, int side, const char* name, const float* feat, int F,
@@ -744,7 +761,7 @@ template <int SL, bool W>
 static gnn_status_t launch_rowsum_resident_of(const gnn_graph_t* g, int side, const char* name, const float* feat, int F,
                                               const GcnSlices& sl, const float* scale, float* out, hipStream_t st, const float* bw) {
   const bool parts = has_long_rows(g, side, gcn_resident_groups(sl));
-  if (gcn_resident_narrow(g, F))
+  if (gcn_narrow(g, F))
     return parts ? launch_rowsum_resident_as<SL, W, true, true>(g, side, name, feat, F, sl, scale, out, st, bw)
                  : launch_rowsum_resident_as<SL, W, true, false>(g, side, name, feat, F, sl, scale, out, st, bw);
   return parts ? launch_rowsum_resident_as<SL, W, false, true>(g, side, name, feat, F, sl, scale, out, st, bw)
@@ -782,7 +799,9 @@ static gnn_status_t launch_rowsum(const gnn_graph_t* g, int side, const float* f
   constexpr int kAhead = NV == 1 && L >= 8 ? 8 : 4;
   if (grid != 0) {
     auto launch = [&](auto u) {
-      k_rowsum<L, NV, W, NS, decltype(u)::value><<<grid, kGcnBlock, 0, st>>>(rl, g->rows[side], cols, feat, F, scale, out, wgt);
+      constexpr int U = decltype(u)::value;
+      if (gcn_narrow(g, F)) k_rowsum<L, NV, W, NS, U, true><<<grid, kGcnBlock, 0, st>>>(rl, g->rows[side], cols, feat, F, scale, out, wgt);
+      else k_rowsum<L, NV, W, NS, U, false><<<grid, kGcnBlock, 0, st>>>(rl, g->rows[side], cols, feat, F, scale, out, wgt);
     };
     if constexpr (kAhead > 4 && NS == 1) {
       if (gathers_abreast(g, side, F, kTwoRowsBytes)) launch(std::integral_constant<int, 2>{});
@@ -1143,7 +1162,7 @@ extern "C" gnn_status_t gnn_gcn_blocked_kernel_name(const gnn_graph_t* g, int fo
   const GcnSlices sl = gcn_resident_slices(fout);
   if (gcn_resident_applies(g, fout))
     std::snprintf(buf, len, "k_rowsum_res<%d, %s, %s, %s>", sl.SL, weighted ? "true" : "false",
-                  gcn_resident_narrow(g, fout) ? "true" : "false",
+                  gcn_narrow(g, fout) ? "true" : "false",
                   has_long_rows(g, 0, gcn_resident_groups(sl)) ? "true" : "false");
   else
     std::snprintf(buf, len, "k_rowsum_blk<%d, %s, %s>", SL, ns >= 4 ? "true" : "false", weighted ? "true" : "false");

@@ -2,7 +2,7 @@
 import numpy as np
 import pytest
 
-from helpers import random_graph, tiny_graph
+from helpers import graph_with_unheard_vertices, random_graph, tiny_graph
 from oracle import gcn as og
 from workloads import make
 
@@ -468,3 +468,43 @@ def test_widths_of_the_persistent_launch(fout, lanes, hub):
     for a, b in ((res, wide), (edge, wide_edge)):
         for key in a:
             assert np.array_equal(a[key], b[key]), key
+
+
+@pytest.mark.parametrize("fout,block_cols", [(16, 300), (32, 256), (64, 300), (100, 256), (128, 300), (256, 256), (512, 300), (1024, 256)])
+@pytest.mark.parametrize("path", ["one launch", "by blocks", "persistent", "edge-balanced"])
+def test_what_is_not_finite_stays_with_its_neighbours(fout, block_cols, path):
+    """Non-finite rows of z (forward) and gout (backward) at vertex 0 and the first vertex of every other column block, which one row gathers
+    in one block and none in the others: every other row keeps its values, with and without a weight per edge."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import dev, run_gcn
+    print(f"gcn: not finite fout={fout} block_cols={block_cols} {path}", flush=True)
+    rng = np.random.default_rng(block_cols + fout)
+    n = 1500
+    indptr, indices = graph_with_unheard_vertices(rng, n, 30000, block_cols)
+    c = synth(rng, indptr, indices, 24, fout)
+    c["ew"] = rng.uniform(-2.0, 2.0, len(indices)).astype(np.float32)
+    first = np.arange(0, n, block_cols)
+    bad_x, bad_g = dict(c, x=c["x"].copy()), dict(c, gout=c["gout"].copy())
+    bad_x["x"][first[::2]], bad_x["x"][first[1::2]] = np.inf, np.nan
+    bad_g["gout"][first[::2]], bad_g["gout"][first[1::2]] = np.nan, -np.inf
+    # pieces of rows are added in any order there: a few dozen terms of size one, and products of 1024 such sums, round by less
+    same = (lambda a, b: np.allclose(a, b, rtol=0, atol=1e-3)) if path == "edge-balanced" else np.array_equal
+    pk.gnn_config_set("block_cols", 0 if path == "one launch" else block_cols)
+    pk.gnn_config_set("resident_sums", 2 if path == "persistent" else 0)
+    pk.gnn_config_set("gcn_mapping", 1 if path == "edge-balanced" else 2)
+    try:
+        g = pk.Graph(dev(indptr), dev(indices))
+        for wide in (0, 1):
+            pk.gnn_config_set("wide_offsets", wide)
+            for run in (lambda d: run_gcn(d, graph=g), lambda d: run_gcn_edge(d)[0]):
+                ok, x, go = (run(d) for d in (c, bad_x, bad_g))
+                rows = np.arange(n) != 5
+                assert same(x["out"][rows], ok["out"][rows]) and not np.isfinite(x["out"][5]).any()
+                rows = np.arange(n) != 3
+                assert same(go["gx"][rows], ok["gx"][rows]) and not np.isfinite(go["gx"][3]).any()
+        g.close()
+    finally:
+        pk.gnn_config_set("wide_offsets", 0)
+        pk.gnn_config_set("gcn_mapping", 2)
+        pk.gnn_config_set("resident_sums", 1)
+        pk.gnn_config_set("block_cols", 12288)
