@@ -107,9 +107,11 @@ gnn_status_t gemm_f32(int64_t M, int N, int64_t K, const float* a, int64_t lda, 
 // products that decide a comparison, so that the choice does not move with the way a product is summed up
 gnn_status_t gemm_f32_chain(int64_t M, int N, int64_t K, const float* a, int64_t lda, const float* b, int64_t ldb,
                             float* c, int64_t ldc, hipStream_t s);
+constexpr int kGemmSplitTerms = 256;  // shorter sums are not split
 int gemm_pick_split_k(int64_t M, int N, int64_t K);
-// a [M,K] times [K,N] that one launch sums over the wavefronts of a workgroup: no need to split K any further
+// a [M,K] times [K,N] that one launch of gemm_f32 sums over the wavefronts of a workgroup; ... and faster than with K split over launches
 bool gemm_has_few_tiles(int64_t M, int N, int64_t K);
+bool gemm_few_or_split(int64_t M, int N, int64_t K);
 // z[M, heads*f] = x[M, K] w[K, heads*f] with the attention halves el = <a_l, z>, er = <a_r, z> ([M, heads])
 // taken from the accumulators; gemm_attn_epilogue_ok says for which head widths this exists
 bool gemm_attn_epilogue_ok(int heads, int f);

@@ -1153,10 +1153,14 @@ extern "C" gnn_status_t gnn_gat_fwd(const gnn_graph_t* g, int fin, int heads, in
   const GatWs L = gat_ws_layout(g, fin, heads, f);
   const bool have_ws = ws != nullptr && ws_bytes >= L.total && aligned16(ws);
   bool halves_done = false;
-  if (have_ws && L.fwd_split_k > 1 && !gemm_has_few_tiles(n, HF, fin)) {
+  // one head of more than 64 columns, whose halves would need a tile as wide: gemm_f32's few tiles and a launch for the halves,
+  // from the terms on that K would be split at.  Split | tiles as wide | these, us: 100 rows, 1 x 128, 256 terms 24.1 | 21.1 | 16.4, 602
+  // 25.3 | 32.9 | 16.9, 1433 26.6 | 58.3 | 21.3; 2000, 1 x 72, 602 26.4 | 33.5 | 17.3; 8000, 1 x 128, 256 38.1 | 23.8 | 24.3, 602 44.3 | 35.7 | 30.9.
+  const bool wide_head = heads == 1 && HF > 64 && fin >= kGemmSplitTerms && gemm_has_few_tiles(n, HF, fin);
+  if (have_ws && L.fwd_split_k > 1 && !gemm_few_or_split(n, HF, fin)) {
     GNN_TRY(gemm_f32(n, HF, fin, x, fin, false, w, HF, false, z, HF, L.fwd_split_k,
                      reinterpret_cast<float*>(static_cast<char*>(ws) + L.fwd_gemm), st));
-  } else if (gemm_attn_epilogue_ok(heads, f) && fin < (1 << 24)) {
+  } else if (gemm_attn_epilogue_ok(heads, f) && fin < (1 << 24) && !wide_head) {
     // a1 + a2: the attention halves come out of the projection's accumulators
     GNN_TRY(gemm_f32_attn(n, heads, f, fin, x, w, a_l, a_r, z, el, er, st));
     halves_done = true;

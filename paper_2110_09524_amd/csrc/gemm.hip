@@ -992,7 +992,7 @@ static int gemm_tile_rows(int64_t M, int N, int bn, int split_k) {
 // holds, at least 128 of K each
 int gemm_pick_split_k(int64_t M, int N, int64_t K) {
   const int64_t tiles = cdiv(M, 128) * cdiv(N, gemm_tile_cols(N));
-  if (tiles >= 128 || K < 256) return 1;
+  if (tiles >= 128 || K < kGemmSplitTerms) return 1;
   int64_t want = 768 / tiles;
   const int64_t max_by_k = K / 128;
   if (want > max_by_k) want = max_by_k;
@@ -1071,6 +1071,19 @@ static gnn_status_t launch_few_tile(int64_t M, int N, int64_t K, const float* a,
 constexpr int kFewTilesPerCu = 2;
 bool gemm_has_few_tiles(int64_t M, int N, int64_t K) {
   return K > kShallowK && K < (1 << 24) && cdiv(M, 32) * cdiv(N, 64) <= (int64_t)kFewTilesPerCu * device_cu_count();
+}
+
+// Where K can be split as well.  A tile's slabs are a fixed number of wavefronts' work, so long sums are for parts of K on the whole chip and
+// a launch that adds them up; most tiles to that work have a chip that one round of them nearly fills, fewest one that goes for a second
+// with narrow rows.  GAT layer on loops, K split | slabs dealt out, us: 100 rows, 8 x 8, 1433 terms 18.3 | 15.4, 2048 16.7 | 18.6, 60 000 28.5 | 335;
+// 2000, 8 x 8, 1433 20.6 | 16.2, 3703 26.6 | 31.7; 6144, 8 x 8, 2048 31.7 | 31.0, 3703 41.4 | 48.6, 2 x 64 (384 tiles), 1433 51.0 | 39.6, 2048
+// 47.7 | 50.1; 2000, 4 x 64 (252 tiles), 3703 52.3 | 49.6, 8192 76.8 | 93.5; 8000, 1 x 16 (250), 3703 43.8 | 31.5, 8192 96.6 | 64.2, 8 x 8 57.9 |
+// 50.3, 103 | 99; 12 000, 8 x 8 (375), 602 38.4 | 27.9, 1433 40.6 | 44.8, 3703 63.1 | 88.2.
+bool gemm_few_or_split(int64_t M, int N, int64_t K) {
+  if (!gemm_has_few_tiles(M, N, K)) return false;
+  const int64_t tiles = cdiv(M, 32) * cdiv(N, 64), cus = device_cu_count();
+  if (tiles <= cus && 8 * tiles > 7 * cus) return N <= 64 || K <= 4096;
+  return K <= (tiles > cus && N <= 64 ? 1024 : 1792);
 }
 
 template <bool BKC, bool EPI>

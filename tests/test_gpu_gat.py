@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 from oracle import gat as og
-from helpers import graph_with_unheard_vertices, random_graph, tiny_graph
+from helpers import PRODUCT_RTOL, graph_with_unheard_vertices, random_graph, relative_error, tiny_graph
 from workloads import make
 
 pytestmark = pytest.mark.gpu
@@ -860,3 +860,32 @@ def test_what_is_not_finite_stays_with_its_neighbours(H, F, block_cols, resident
         pk.gnn_config_set("wide_offsets", 0)
         pk.gnn_config_set("resident_sums", 1)
         pk.gnn_config_set("block_cols", 12288)
+
+
+FEW, HALVES, SPLIT = {"gemm_f32_mfma_attn"}, {"gemm_f32_mfma", "gat_attn_halves"}, {"gemm_f32_mfma_splitk", "gemm_sum_partials", "gat_attn_halves"}
+
+
+@pytest.mark.parametrize("n,fin,H,F,route", [
+    (70, 255, 1, 128, FEW), (70, 256, 1, 128, HALVES), (33, 602, 1, 72, HALVES), (129, 1792, 1, 128, HALVES), (31, 1793, 1, 128, SPLIT),
+    (90, 1792, 8, 8, FEW), (90, 1793, 8, 8, SPLIT), (100, 20_001, 8, 8, SPLIT), (40, 3000, 2, 64, SPLIT),
+    (7168, 1793, 1, 16, SPLIT), (7169, 1793, 1, 16, FEW), (8193, 1024, 1, 16, FEW), (8193, 1025, 1, 16, SPLIT),
+    (3600, 4096, 2, 64, FEW), (3600, 4097, 2, 64, SPLIT)])
+def test_routes_of_the_projection(n, fin, H, F, route):
+    """Slabs dealt out to wavefronts, with the halves in the epilogue or (one head past 64 columns) in a launch of their own, or K split
+    over workgroups: long sums of few rows go the last way.  Errors of the product as on every tile and layout."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import run_gat
+    print(f"gat: projection {n} x {fin} x {H} x {F}", flush=True)
+    rng = np.random.default_rng(n + fin)
+    indptr, indices = random_graph(rng, n, 2 * n)
+    c = synth(rng, indptr, indices, fin, H, F)
+    pk.gnn_prof_reset()
+    pk.gnn_prof_enable(True)
+    try:
+        res = run_gat(c, backward=False)
+    finally:
+        pk.gnn_prof_enable(False)
+    names = {s for s in pk.gnn_prof_report() if s.startswith("gemm") or s == "gat_attn_halves"}
+    assert names == route
+    assert relative_error(res["z"], c["x"].astype(np.float64) @ c["w"].astype(np.float64)) <= PRODUCT_RTOL
+    compare(c, res, *oracle_all(c, backward=False))
