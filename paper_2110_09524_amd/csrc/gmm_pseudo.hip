@@ -833,10 +833,12 @@ __global__ __launch_bounds__(kPsBlock) void k_gmmp_bwd_dst_nr(
 // Apart, the destination side gathered the K times wider hk[u] and both sides evaluated every tanh and exp.
 // 232 965 vertices, 1.12 10^8 edges, K = 2, R = 1, 16 columns, us: 1470 + 1240 -> 1320 (1860 compiled for the most kernels and
 // dimensions, as the forward kernel is, which the gathers of hk[u] bound: 1425, and 1478 compiled for K = 2, R = 1).
-// wavefronts per SIMD that k_gmmp_bwd_nr leaves room for: a few registers less than it would take (100 000 vertices, 2 10^6 edges, K = 3,
-// R = 2 73 us with what it would take, 60 so)
+// Wavefronts per SIMD that k_gmmp_bwd_nr leaves room for: a few registers less than it would take (100 000 vertices, 2 10^6 edges, K = 3,
+// R = 2 73 us with what it would take, 60 so).  Three where four would keep up to 36 registers of the sums in scratch memory: 100 000, 2 10^6,
+// 8 columns, power law | even, unbounded, room for four, three: K = R = 4 268, 440, 233 | 91, 126, 86; K = 4, R = 3 256, 266, 216 |
+// 79, 83, 81; K = 3, R = 4 250, 253, 213 | 86, 83, 81.
 template <int KT, int RT>
-constexpr int kNrMinWaves = KT <= 3 && RT == 1 ? 5 : 4;
+constexpr int kNrMinWaves = KT <= 3 && RT == 1 ? 5 : KT * RT < 12 ? 4 : 3;
 template <int G, bool PROJ, int KT, int RT>
 __global__ __launch_bounds__(kPsBlock, (kNrMinWaves<KT, RT>)) void k_gmmp_bwd_nr(
     RowLaunch rl, const int4* __restrict__ rows_t, const int32_t* __restrict__ indices_t, const int32_t* __restrict__ eid_t, const float* __restrict__ hk,
