@@ -351,8 +351,8 @@ __device__ __forceinline__ void write_run(T* p, const T (&v)[U]) {
 // Gathered rows of a table of n rows.  Up to 2 GB they come through a buffer resource, which reads zeros and no memory past its end:
 // that is where edges past the row's end point (kPastTable), so a chunk's loads are issued four at a time without a branch to each.
 // A branch to each -> this, us: forward, 200 000 vertices, 4 10^6 edges, K = 2, 16 columns, power law 86 -> 76, 13 000 x 200, even 40 -> 32,
-// 230 000 x 9, K = 3, 12 columns 81 -> 79, 230 000 x 10, K = 2, 8 columns, even 59 -> 63; backward 113 -> 96 (the first of these), 75 -> 72 (the third), 60 000
-// vertices, 1.5 10^7 edges, K = R = 3 277 -> 231.  By twos: 79, 36, 88, 60; 103, 73, 245.
+// 230 000 x 9, K = 3, 12 columns 81 -> 79, 230 000 x 10, K = 2, 8 columns, even 55 -> 55; backward 113 -> 96 (the first of these), 75 -> 72 (the third), 60 000
+// vertices, 1.5 10^7 edges, K = R = 3 277 -> 231.  By twos: 79, 36, 88, 55; 103, 73, 245.
 constexpr uint32_t kPastTable = 0x80000000u;
 __host__ __device__ __forceinline__ bool narrow_table(int64_t n, int row_floats) {
   return n < (1 << 24) && n * row_floats * 4 <= (int64_t)kPastTable;
@@ -394,8 +394,9 @@ __device__ __forceinline__ auto table_resource(const float* p, int64_t n, int ro
 }
 
 // forward: out[v, f] = (1/K) sum_e sum_k w_k(e) hk[u, k, f]; the sum over k is taken last, across lanes
-template <int G, bool PROJ, int KT, int RT, int U>
-__global__ __launch_bounds__(kPsBlock, (RT <= 1 ? 7 : 6)) void k_gmmp_fwd_nr(
+// W: wavefronts per SIMD that it leaves room for, see launch_fwd_nr
+template <int G, bool PROJ, int KT, int RT, int U, int W>
+__global__ __launch_bounds__(kPsBlock, W) void k_gmmp_fwd_nr(
     RowLaunch rl, const int4* __restrict__ rows, const int32_t* __restrict__ indices, const float* __restrict__ hk, const float* __restrict__ pseudo,
     ProjArgs pa, const float* __restrict__ mu, const float* __restrict__ inv_sigma, PsParams pm,
     float* __restrict__ out) {
@@ -426,7 +427,10 @@ __global__ __launch_bounds__(kPsBlock, (RT <= 1 ? 7 : 6)) void k_gmmp_fwd_nr(
   const int myk = col_ok ? li / F4 : 0;
   uint32_t* l_off = reinterpret_cast<uint32_t*>(lds + grp * GS);
   float* l_w = lds + grp * GS + G;
-  const bool narrow = pm.wide == 0 && narrow_table(rl.n_rows, KF);
+  // four kernels of four coordinates are bound by the vector units, where a branch to each row between two kinds of loads shows: forward,
+  // 100 000 vertices, 60 even edges, 8 columns 102 -> 91, 12 156 -> 143 (one row in flight)
+  constexpr bool kPlain = PROJ && U < kNrU && KT * RT >= 16;
+  const bool narrow = !kPlain && pm.wide == 0 && narrow_table(rl.n_rows, KF);
   const auto table = table_resource(hk, rl.n_rows, KF);
   const uint32_t lane_off = 16u * li;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f), part = acc;
@@ -1216,6 +1220,29 @@ static gnn_status_t with_rows_in_flight(const gnn_graph_t* g, int KF, Fn fn) {
   return fn(std::integral_constant<int, 1>{}, 0u);
 }
 
+// Wavefronts per SIMD that k_gmmp_fwd_nr leaves room for: 7 (72 registers) with one coordinate, 6 with more.  Projected, in groups of eight
+// lanes, it would take 73, and keeps two values in scratch memory to have one wavefront more.  Skewed gathers, which wait for their longest rows, are
+// repaid for that with two or three kernels, and nothing else is.  Forward, us, room for 7 | 6: 2 x 8 columns, 230 000 vertices, 10 even edges
+// 58.7 | 55.0, 2 x 16 65.3 | 59.9, 3 x 8 78.1 | 75.6, 4 x 8 63.0 | 58.9; power law, 2 x 8, 100 000, 60 198.6 | 204.6, 4 x 8 226.9 | 221.1.
+template <int G, bool PROJ, int KT, int RT>
+static gnn_status_t launch_fwd_nr(const gnn_graph_t* g, const RowLaunch& rl, unsigned grid, const float* hk, const float* pseudo, const ProjArgs& pa,
+                                  const float* mu, const float* inv_sigma, const PsParams& pm, float* out, hipStream_t st) {
+  return with_rows_in_flight(g, pm.K * pm.F, [&](auto u, unsigned lds) -> gnn_status_t {
+    constexpr int U = decltype(u)::value;
+    constexpr bool crowded = PROJ && G == 8 && RT == 1 && U == kNrU;
+    auto run = [&](auto waves) -> gnn_status_t {
+      k_gmmp_fwd_nr<G, PROJ, KT, RT, U, decltype(waves)::value><<<grid, kPsBlock, lds, st>>>(rl, g->rows[0], g->indices, hk, pseudo, pa, mu,
+                                                                                             inv_sigma, pm, out);
+      GNN_LAUNCH_CHECK();
+      return GNN_OK;
+    };
+    if constexpr (crowded && KT < 4) {
+      if (gathers_skewed(g, 0)) return run(std::integral_constant<int, 7>{});
+    }
+    return run(std::integral_constant<int, (RT == 1 && !crowded ? 7 : 6)>{});
+  });
+}
+
 // k_monet_res takes graphs with column blocks from so many edges on: below, its launch and its barriers per block are not repaid,
 // and where degrees are uneven they are sooner, since k_gmmp_fwd_nr then waits for the longest rows.  k_gmmp_fwd_nr | k_monet_res, K = 2,
 // 16 columns, us: uneven 13 000 vertices, 5 10^5 edges 25 | 30 (K = 4: 40 | 33), 20 000, 1.2 10^6 44 | 34, 13 000, 1.3 10^6 40 | 34, 14 000, 4.2 10^6
@@ -1400,12 +1427,7 @@ extern "C" gnn_status_t gnn_gmmp_fwd(const gnn_graph_t* g, int fin, int fout, in
           constexpr int KT = decltype(kernels)::value, RT = decltype(dims)::value;
           if (monet_res_applies(g, k * fout))
             return launch_monet_res<GL, false, KT, RT>(g, hk, pseudo, ProjArgs{}, mu, inv_sigma, pm, out, st);
-          return with_rows_in_flight(g, k * fout, [&](auto u, unsigned lds) -> gnn_status_t {
-            k_gmmp_fwd_nr<GL, false, KT, RT, decltype(u)::value><<<grid, kPsBlock, lds, st>>>(rl, g->rows[0], g->indices, hk, pseudo,
-                                                                                              ProjArgs{}, mu, inv_sigma, pm, out);
-            GNN_LAUNCH_CHECK();
-            return GNN_OK;
-          });
+          return launch_fwd_nr<GL, false, KT, RT>(g, rl, grid, hk, pseudo, ProjArgs{}, mu, inv_sigma, pm, out, st);
         });
       }
       return GNN_OK;
@@ -1617,12 +1639,7 @@ extern "C" gnn_status_t gnn_monet_fwd(const gnn_graph_t* g, int fin, int fout, i
         constexpr int KT = decltype(kernels)::value, RT = decltype(dims)::value;
         if (monet_res_applies(g, k * fout))
           return launch_monet_res<GL, true, KT, RT>(g, hk, nullptr, pa, mu, inv_sigma, pm, out, st);
-        return with_rows_in_flight(g, k * fout, [&](auto u, unsigned lds) -> gnn_status_t {
-          k_gmmp_fwd_nr<GL, true, KT, RT, decltype(u)::value><<<grid, kPsBlock, lds, st>>>(rl, g->rows[0], g->indices, hk, nullptr, pa, mu,
-                                                                                           inv_sigma, pm, out);
-          GNN_LAUNCH_CHECK();
-          return GNN_OK;
-        });
+        return launch_fwd_nr<GL, true, KT, RT>(g, rl, grid, hk, nullptr, pa, mu, inv_sigma, pm, out, st);
       });
     }
     return GNN_OK;

@@ -240,3 +240,30 @@ def test_rows_of_tables_that_32_bits_do_not_reach(fout, K, r):
     for a, b in zip(narrow, wide):
         for name in a:
             assert np.array_equal(a[name], b[name]), name
+
+
+@pytest.mark.parametrize("n,fout,K,r", [(98_305, 8, 2, 1), (41_000, 16, 4, 4)])
+def test_few_rows_in_flight(n, fout, K, r):
+    """Rows of 6 MB that are gathered evenly are asked for two at a time, longer ones of 10 MB one at a time, in the latter with four kernels of
+    four coordinates by their addresses.  Rows of 0, 1, 2, 7, 8, 9 edges and more; the same bits with offsets of 64 bits and with
+    coordinates per edge."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import assert_close
+    print(f"monet: few rows in flight n={n} {fout} x {K}, r={r}", flush=True)
+    rng = np.random.default_rng(n)
+    deg = np.array([0, 1, 2, 7, 8, 9, 15, 33, 40, 55])[np.arange(n) % 10]
+    indptr = np.concatenate(([0], np.cumsum(deg))).astype(np.int32)
+    indices = rng.integers(0, n, indptr[-1]).astype(np.int32)
+    c = synth(rng, indptr, indices, 6, fout, K, r)
+    ps = om.pseudo_projection_forward(indptr, indices, c["c"], c["proj_w"], c["proj_b"])
+    ref = om.gmm_pseudo_forward(indptr, indices, c["x"], c["w_fc"], ps, c["mu"], c["inv_sigma"])["out"]
+    pk.gnn_config_set("blocked_min_edges", 16)
+    try:
+        out = run(c)["out"]
+        assert_close("out", out, ref)
+        assert np.array_equal(run(c, fused=False)["out"], out)
+        pk.gnn_config_set("wide_offsets", 1)
+        assert np.array_equal(run(c)["out"], out)
+    finally:
+        pk.gnn_config_set("wide_offsets", 0)
+        pk.gnn_config_set("blocked_min_edges", 0)

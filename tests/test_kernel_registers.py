@@ -33,9 +33,11 @@ def scratch_bytes(tmp_path):
 
 
 @pytest.mark.skipif(not (os.path.exists(READELF) and os.path.exists(pk.LIB_PATH)), reason="needs the built library and llvm-readelf")
-@pytest.mark.parametrize("kernel", ["k_gmmp_bwd_nr", "k_gmmp_bwd_dst_nr"])
+@pytest.mark.parametrize("kernel", ["k_gmmp_fwd_nr", "k_gmmp_bwd_nr", "k_gmmp_bwd_dst_nr"])
 def test_narrow_monet_walks_keep_their_values_in_registers(kernel, tmp_path):
     """A bound on registers that has the sums of a walk in scratch memory costs more than the wavefronts it makes room for."""
     found = {n: b for n, b in scratch_bytes(tmp_path).items() if re.search(rf"\d{kernel}I", n)}
     assert len(found) >= 24
-    assert not {n: b for n, b in found.items() if b}
+    # projected, two or three kernels, one coordinate, groups of eight lanes, room for seven wavefronts: for skewed gathers
+    repaid = re.compile(r"k_gmmp_fwd_nrILi8ELb1ELi[23]ELi1ELi8ELi7E")
+    assert not {n: b for n, b in found.items() if b > (12 if repaid.search(n) else 0)}
