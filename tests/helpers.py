@@ -63,3 +63,17 @@ def graph_with_unheard_vertices(rng, n, pairs, block_cols):
     rows[5] = np.sort(np.append(rows[5], block_cols))
     indptr = np.concatenate(([0], np.cumsum([len(r) for r in rows]))).astype(np.int32)
     return indptr, np.concatenate(rows).astype(np.int32)
+
+
+def sparse_graph_with_hubs(rng, n, hubs):
+    """Rows of 0 to 3 edges, sources ascending; with hubs also rows of n and n / 2 and a vertex that every third row gathers."""
+    deg = rng.integers(0, 4, n)
+    if hubs:
+        deg[7], deg[n - 3] = n, n // 2
+    indptr = np.concatenate(([0], np.cumsum(deg))).astype(np.int32)
+    row = np.repeat(np.arange(n), deg)
+    src = rng.integers(0, n, len(row))
+    if hubs:
+        first = indptr[:-1][(deg > 0) & (np.arange(n) % 3 == 0)]
+        src[first] = 11
+    return indptr, src[np.lexsort((src, row))].astype(np.int32)

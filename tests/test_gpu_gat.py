@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 from oracle import gat as og
-from helpers import PRODUCT_RTOL, graph_with_unheard_vertices, random_graph, relative_error, tiny_graph
+from helpers import PRODUCT_RTOL, graph_with_unheard_vertices, random_graph, relative_error, sparse_graph_with_hubs, tiny_graph
 from workloads import make
 
 pytestmark = pytest.mark.gpu
@@ -889,3 +889,40 @@ def test_routes_of_the_projection(n, fin, H, F, route):
     assert names == route
     assert relative_error(res["z"], c["x"].astype(np.float64) @ c["w"].astype(np.float64)) <= PRODUCT_RTOL
     compare(c, res, *oracle_all(c, backward=False))
+
+
+@pytest.mark.parametrize("H,F,n,half", [(4, 64, 33_500, 0), (4, 64, 31_000, 1), (16, 8, 41_000, 0)])
+@pytest.mark.parametrize("hubs", [False, True])
+def test_more_rows_than_the_workgroups_hold(H, F, n, half, hubs):
+    """The persistent kernels take their rows in several batches: 256 workgroups, of which each has H F / 64 slices to serve, hold at most
+    512 (row, slice) pairs (with scores in LDS 336, with heads that share a slice 314, with two sums 256 or 192).  Rows whole, as the
+    launches per block give them bit for bit, and in parts; shared slices as the single-launch kernels give them."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import assert_close, dev, run_gat
+    print(f"gat: rows in batches H={H} F={F} n={n} half={half} hubs={hubs}", flush=True)
+    rng = np.random.default_rng(n + H)
+    indptr, indices = sparse_graph_with_hubs(rng, n, hubs)
+    c = synth(rng, indptr, indices, 16, H, F)
+    res, infer = {}, {}
+    pk.gnn_config_set("gather_precision", half)
+    pk.gnn_config_set("merge_blocks", 0)        # each block by itself, like the persistent kernels
+    try:
+        g = pk.Graph(dev(indptr), dev(indices))
+        for resident in (2, 0):
+            pk.gnn_config_set("resident_sums", resident)
+            if resident:
+                names = [pk.gnn_gat_blocked_kernel_name(g, H, F, mode) for mode in (0, 2, 3)]
+            res[resident], infer[resident] = run_gat(c, graph=g), run_gat(c, backward=False, graph=g, stash=False)
+        g.close()
+    finally:
+        pk.gnn_config_set("merge_blocks", 1)
+        pk.gnn_config_set("gather_precision", 0)
+        pk.gnn_config_set("resident_sums", 1)
+    assert all(name.startswith("k_gat_res<") and name.endswith(f"{str(hubs).lower()}>") for name in names), names
+    for key in res[0]:
+        if not hubs and F == 64 and not (half and key.startswith("g")):     # del of fp16 rows: other lanes add up other columns
+            assert np.array_equal(res[2][key], res[0][key]), key
+        else:   # vertex 11 sums over a third of the rows
+            assert_close(key, res[2][key], res[0][key], reduce_scale=key in ("gw", "ga_l", "ga_r"), row_scale=hubs and key == "gx")
+    assert_close("out, forward only", infer[2]["out"], infer[0]["out"])
+    assert_close("out", infer[2]["out"], res[2]["out"])

@@ -2,7 +2,7 @@
 import numpy as np
 import pytest
 
-from helpers import graph_with_unheard_vertices, random_graph, tiny_graph
+from helpers import graph_with_unheard_vertices, random_graph, sparse_graph_with_hubs, tiny_graph
 from oracle import gcn as og
 from workloads import make
 
@@ -508,3 +508,36 @@ def test_what_is_not_finite_stays_with_its_neighbours(fout, block_cols, path):
         pk.gnn_config_set("gcn_mapping", 2)
         pk.gnn_config_set("resident_sums", 1)
         pk.gnn_config_set("block_cols", 12288)
+
+
+@pytest.mark.parametrize("fout,n", [(256, 33_500), (64, 132_000), (16, 263_000)])
+@pytest.mark.parametrize("hubs", [False, True])
+def test_more_rows_than_the_workgroups_hold(fout, n, hubs):
+    """The persistent launch takes its rows in several batches: 256 workgroups, four to a slice of 256 columns, hold 512 rows each, 1024
+    narrow ones.  Rows whole, as the launches per block give them bit for bit, and in parts; narrow rows as the single-launch kernels
+    give them."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import assert_close, dev, run_gcn
+    print(f"gcn: rows in batches fout={fout} n={n} hubs={hubs}", flush=True)
+    rng = np.random.default_rng(n + fout)
+    indptr, indices = sparse_graph_with_hubs(rng, n, hubs)
+    c = synth(rng, indptr, indices, 8, fout)
+    c["ew"] = rng.standard_normal(len(indices)).astype(np.float32)
+    g = pk.Graph(dev(indptr), dev(indices))
+    res = {}
+    try:
+        for resident in (2, 0):
+            pk.gnn_config_set("resident_sums", resident)
+            if resident:
+                names = [pk.gnn_gcn_blocked_kernel_name(g, fout, weighted) for weighted in (0, 1)]
+            res[resident] = run_gcn(c, graph=g), run_gcn_edge(c)[0]
+    finally:
+        pk.gnn_config_set("resident_sums", 1)
+    g.close()
+    assert all(name.startswith("k_rowsum_res<") and name.endswith(f"{str(hubs).lower()}>") for name in names), names
+    for kind, (got, ref) in enumerate(zip(res[2], res[0])):
+        for key in ref:
+            if not hubs and fout == 256:
+                assert np.array_equal(got[key], ref[key]), (kind, key)
+            else:   # hub rows are unnormalised sums of up to n terms
+                assert_close(key, got[key], ref[key], reduce_scale=key == "gw", row_scale=hubs and key in ("out", "gx"))

@@ -4,7 +4,7 @@ two-call form of the library, which it must reproduce bit for bit wherever the s
 import numpy as np
 import pytest
 
-from helpers import random_graph, tiny_graph
+from helpers import sparse_graph_with_hubs, random_graph, tiny_graph
 from oracle import gmm as om
 
 pytestmark = pytest.mark.gpu
@@ -174,8 +174,7 @@ def test_hub_empty_rows_no_edges_optional_gx_and_limits():
                                                  (16, 4, 4, 500), (20, 3, 2, 256), (12, 3, 1, 1400), (8, 2, 1, 100)])
 def test_all_column_blocks_in_one_launch(fout, K, r, block_cols):
     """The forward launch that keeps its sums in LDS: segments of no, few and many edges, rows cut into parts (one of 40 000
-    edges into 128), rows without edges, and more rows than a workgroup holds.  Its sums are grouped by block, so they are compared with
-    the oracle and with the other kernels; what is not finite stays in the rows that gather it.  With coordinates per edge the
+    edges into 128), rows without edges.  Its sums are grouped by block, so they are compared with the oracle and with the other kernels; what is not finite stays in the rows that gather it.  With coordinates per edge the
     same bits; a row out of the order of the blocks leaves it to the other kernels."""
     import paper_2110_09524_amd as pk
     from gpu_harness import assert_close
@@ -267,3 +266,26 @@ def test_few_rows_in_flight(n, fout, K, r):
     finally:
         pk.gnn_config_set("wide_offsets", 0)
         pk.gnn_config_set("blocked_min_edges", 0)
+
+
+@pytest.mark.parametrize("n,fout,K", [(95_000, 64, 1), (173_000, 32, 2)])
+@pytest.mark.parametrize("hubs", [False, True])
+def test_more_rows_than_the_workgroups_hold(n, fout, K, hubs):
+    """The forward launch over all column blocks takes its rows in several batches: 256 workgroups hold up to 366 rows of 64 columns
+    each, or 673 of 32, beside a block's scalars; rows whole and in parts.  The same bits with coordinates per edge."""
+    import paper_2110_09524_amd as pk
+    from gpu_harness import assert_close
+    print(f"monet: rows in batches n={n} {fout} x {K} hubs={hubs}", flush=True)
+    rng = np.random.default_rng(n + fout)
+    indptr, indices = sparse_graph_with_hubs(rng, n, hubs)
+    c = synth(rng, indptr, indices, 6, fout, K, 1)
+    res = {}
+    try:
+        for resident in (2, 0):
+            pk.gnn_config_set("resident_sums", resident)
+            res[resident] = run(c)["out"], run(c, fused=False)["out"]
+    finally:
+        pk.gnn_config_set("resident_sums", 1)
+    assert np.array_equal(*res[2]) and np.array_equal(*res[0])
+    assert hubs is False or not np.array_equal(res[2][0], res[0][0])     # rows of several blocks: another kernel it was
+    assert_close("out", res[2][0], res[0][0], row_scale=hubs)
