@@ -166,14 +166,18 @@ gnn_status_t gnn_release_cached_memory(void);
  *                           serves cache residency); layer calls on ONE graph that overlap in
  *                           time share those counters: their results stay right, their cache
  *                           hit rates suffer.  0: one launch per block or group of blocks.
- *                           Both give the same bits, but for rows far longer than the mean:
- *                           the one launch sums them in parts.  GAT layers whose heads have 8, 16
+ *                           Both give the same bits, but for rows far longer than the mean, which
+ *                           the one launch sums in parts, sparse blocks that share a launch
+ *                           ("merge_blocks") and the backward sums over fp16 rows ("gather_precision"),
+ *                           which are grouped otherwise.  GAT layers whose heads have 8, 16
  *                           or 32 columns (rows of 64, 128, 256 or 512), GCN rows of other widths
  *                           up to 512, gnn_monet_fwd and gnn_gmmp_fwd have such a launch in place of
  *                           their other kernels, where rules on the graph find it faster, with 2 on
  *                           every graph with column blocks (the latter two: whose rows have their
  *                           edges in the order of the blocks), and with 0 never; its sums are
- *                           grouped by block, so they round differently.
+ *                           grouped by block, so they round differently.  For heads of 8, 16 or 32
+ *                           columns, the destination side that recomputes its sums (backward without a
+ *                           stash) stays with the other kernels, several times slower on large graphs.
  *   "resident_spin"         polls after which a workgroup of that launch stops waiting for the
  *                           others of its XCD (default 4096; 0 = never wait; meant for tests)
  *   "resident_sync_every"   the workgroups of an XCD meet after every k-th column block instead

@@ -1178,8 +1178,8 @@ extern "C" gnn_status_t gnn_gat_fwd(const gnn_graph_t* g, int fin, int heads, in
   // running softmax statistics, which borrow the dz area the backward call uses later: 128 of
   // its >= 512 bytes per vertex); without a workspace the single-launch kernels run.
   // Rows of 512 bytes and more take them (two 256-byte slices at 512 bytes; measured at Reddit
-  // scale, 1 x 128: 7.9 ms against 8.5 ms for the single-launch forward kernel), and single-head
-  // rows of up to 256 bytes as one slice of the persistent kernels.
+  // scale, 1 x 128: 7.9 ms against 8.5 ms for the single-launch forward kernel), and in one slice of the persistent
+  // kernels single-head rows of up to 256 bytes and, on graphs with edges enough, 64 columns of heads of 8, 16 or 32.
   if (gat_blocked_applies(g, heads, f) && have_ws) {
     char* base = static_cast<char*>(ws);
     return gat_blocked_fwd(g, make_dims(heads, f, slope), z, el, er, m, d, out, t, sg,

@@ -40,9 +40,10 @@ constexpr int kSlices = 8;  // column slices of a wide row: one per XCD
 // XCD its own slice.  512-byte rows keep slices of a full 128-byte line (SL = 8) and have four of
 // them: workgroup id mod 4 picks the slice, so XCD k and XCD k + 4 work on the same columns (for
 // different rows) and each L2 still holds one slice of the column block.  A gather of a half line
-// would cost the L1 the same fill as a full one.  Rows of 256 bytes and less are not blocked: at
+// would cost the L1 the same fill as a full one.  Rows of 256 bytes and less are not for a launch per block: at
 // Reddit scale the single-launch kernels were faster there (the whole matrix then fits the
-// Infinity Cache, and a launch per block costs more than it saves); the persistent kernels do take them.
+// Infinity Cache, and a launch per block costs more than it saves).  The persistent kernels do take them, with one head
+// whole and with heads of 8, 16 or 32 columns that share the slice.
 struct Slicing {
   int SL, ns;
   int hs = 1;  // heads that share a slice
@@ -87,6 +88,8 @@ static bool pick_whole_slicing(int heads, int HF, Slicing& sl) {  // every slice
 // 64 bytes (8 x 16) fetched the lists and scalars of an edge as often per byte of row as there were slices, in a launch per block, and
 // had its hub rows wait in groups of 8 or 4 lanes.  Training pass, 232 965 vertices, 1.14 10^8 edges, power law | even, ms:
 // 4 x 32 12.8 -> 9.7 | 12.0 -> 10.2, 8 x 16 25.8 -> 10.0 | 24.1 -> 10.5; 22 308, 10^7: 4 x 32 2.23 -> 0.77 | 0.86 -> 0.74.
+// (All that with the source side's eight heads to a slice keeping 12 of a lane's registers in scratch memory, 24 and more with rows in
+// parts: the vertex states of a chunk's edges alone are 32.)
 static bool pick_slicing(int heads, int HF, Slicing& sl) {
   const int f = heads > 0 ? HF / heads : 0, ns = HF / 64;
   if (config_get(kCfgResidentSums) && heads > 1 && HF % 64 == 0 && (f == 8 || f == 16 || f == 32) &&
@@ -1141,13 +1144,6 @@ bool gat_blocked_whole(const gnn_graph_t* g, int heads, int f) {
 bool gat_blocked_shared(const gnn_graph_t* g, int heads, int f) {
   Slicing sl;
   return gat_blocked_applies(g, heads, f) && pick_slicing(heads, heads * f, sl) && sl.hs > 1;
-}
-
-size_t gat_blocked_ws_bytes(const gnn_graph_t* g, int heads, int f) {
-  if (!gat_blocked_applies(g, heads, f)) return 0;
-  return ws_granule(sizeof(float) * (size_t)g->n * heads * f) +   // T, then A2
-         ws_granule(sizeof(float) * (size_t)g->n * kSlices) +     // sg, then the slices' shares of del
-         ws_granule(sizeof(float) * (size_t)g->n * heads);        // head-major el
 }
 
 __global__ void k_zero_i32(int n, int32_t* __restrict__ p) {

@@ -32,7 +32,6 @@ bool gat_blocked_applies(const gnn_graph_t* g, int heads, int f);
 // ... into slices that heads share: vstate is [n][H], as for the single-launch kernels, and no scratch is used
 bool gat_blocked_whole(const gnn_graph_t* g, int heads, int f);
 bool gat_blocked_shared(const gnn_graph_t* g, int heads, int f);
-size_t gat_blocked_ws_bytes(const gnn_graph_t* g, int heads, int f);  // extra workspace (bwd)
 // t, sg: optional stash of the destination-side backward sums (both or neither);
 // state: n * 8 float4 of scratch for the running softmax statistics (required)
 gnn_status_t gat_blocked_fwd(const gnn_graph_t* g, GatDims dm, const float* z, const float* el,

@@ -39,9 +39,9 @@ void clear_error() { g_err[0] = 0; }
 // wide_offsets: 1 makes the column-blocked GAT and GCN and the narrow MoNet kernels address gathered rows with 64-bit offsets
 // also where 32 bits reach every row (the path of matrices of 4 GB and more; a test hook)
 // resident_sums: 1 (default) lets the column-blocked aggregations run all blocks in one persistent
-// launch that keeps the rows' running sums on the chip (LDS); 2: the MoNet forward pass on every graph with
-// column blocks, not only where its own rule finds it faster; 0: one launch per block or group of
-// blocks, the sums read and written in between
+// launch that keeps the rows' running sums on the chip (LDS); 2: also GAT heads that share a slice, GCN rows of any width up to
+// 512 and the MoNet forward pass on every graph with column blocks, not only where their own rules find it faster; 0: one
+// launch per block or group of blocks, the sums read and written in between
 static std::atomic<int64_t> g_config[kCfgCount] = {{12288}, {0}, {1}, {2}, {2}, {16}, {0}, {1}, {0}, {1}, {4096}, {0}};
 // resident_sync_every: the workgroups of an XCD meet after every k-th column block (0, default: once
 // per generation of rows, after the last block)
